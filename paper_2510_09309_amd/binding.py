@@ -1,9 +1,10 @@
-"""ctypes binding of libmaskkv.so: argument marshalling only.
+"""Binding of libmaskkv.so: argument marshalling only.
 
 Every function mirrors the C entry point of the same name in ``include/maskkv.h`` and takes
 torch device tensors; torch is used for device memory and streams, nothing is computed here.
-If the shared library has not been built the import of this module fails loudly: there is no
-CPU or PyTorch fallback.
+The arguments are unpacked by a small CPython extension (``csrc/python.cpp``), which is what a
+call costs besides its kernel launches.  If the shared library or the extension has not been
+built the import of this module fails loudly: there is no CPU or PyTorch fallback.
 """
 from __future__ import annotations
 
@@ -67,6 +68,19 @@ def _load() -> ct.CDLL:
 _lib = _load()
 
 
+def _load_marshal():
+    try:
+        from . import _marshal
+    except ImportError as e:
+        raise ImportError(f"the argument marshalling extension of this package is missing or does not load ({e}): build "
+                          "it first (python -m paper_2510_09309_amd.build)") from e
+    _marshal.bind({name: ct.cast(getattr(_lib, name), ct.c_void_p).value for name in SYMBOLS})
+    return _marshal
+
+
+_native = _load_marshal()
+
+
 @dataclass
 class Desc:
     """Python mirror of maskkv_desc."""
@@ -88,14 +102,6 @@ class Desc:
             c._keep = arr
             c.prompt_len = ct.cast(arr, ct.POINTER(ct.c_int32))
         return c
-
-
-def _dtype_code(t: torch.Tensor) -> int:
-    if t.dtype == torch.bfloat16:
-        return MASKKV_BF16
-    if t.dtype == torch.float32:
-        return MASKKV_F32
-    raise TypeError(f"unsupported tensor dtype {t.dtype}")
 
 
 def tensor_view(t: torch.Tensor, seq_start: Optional[Sequence[int]] = None) -> _CTensor:
@@ -138,97 +144,85 @@ def maskkv_version() -> int:
     return int(_lib.maskkv_version())
 
 
+def _size(n: int, what: str) -> int:
+    if n < 0:
+        _check(-n, what)
+    return n
+
+
 def maskkv_score_workspace_bytes(desc: Desc) -> int:
-    n = ct.c_size_t(0)
-    _check(_lib.maskkv_score_workspace_bytes(ct.byref(desc.c()), ct.byref(n)), "maskkv_score_workspace_bytes")
-    return int(n.value)
+    return _size(_native.score_ws(desc), "maskkv_score_workspace_bytes")
 
 
 def maskkv_select_workspace_bytes(desc: Desc) -> int:
-    n = ct.c_size_t(0)
-    _check(_lib.maskkv_select_workspace_bytes(ct.byref(desc.c()), ct.byref(n)), "maskkv_select_workspace_bytes")
-    return int(n.value)
+    return _size(_native.select_ws(desc), "maskkv_select_workspace_bytes")
 
 
 def maskkv_attend_workspace_bytes(desc: Desc, full: bool) -> int:
-    n = ct.c_size_t(0)
-    _check(_lib.maskkv_attend_workspace_bytes(ct.byref(desc.c()), ct.c_int(1 if full else 0), ct.byref(n)),
-           "maskkv_attend_workspace_bytes")
-    return int(n.value)
+    return _size(_native.attend_ws(desc, full), "maskkv_attend_workspace_bytes")
 
 
 def maskkv_score(desc: Desc, Q_mask, K_full, scale: float, scores: torch.Tensor, score_stride: int,
                  prompt_mass: Optional[torch.Tensor], workspace: Optional[torch.Tensor], stream=None) -> None:
-    q, k = _as_view(Q_mask), _as_view(K_full)
-    wp, wn = _ws(workspace)
-    _check(_lib.maskkv_score(ct.byref(desc.c()), ct.byref(q), ct.byref(k), ct.c_float(scale), _ptr(scores),
-                             ct.c_int64(score_stride), _ptr(prompt_mass), wp, wn, _stream(stream)), "maskkv_score")
+    status = _native.score(desc, Q_mask, K_full, scale, scores, score_stride, prompt_mass, workspace, stream)
+    if status:
+        _check(status, "maskkv_score")
 
 
 def maskkv_score_given_lse(desc: Desc, Q_mask, K_full, scale: float, row_lse: torch.Tensor, scores: torch.Tensor,
                            score_stride: int, prompt_mass: Optional[torch.Tensor], workspace: Optional[torch.Tensor],
                            stream=None) -> None:
     """maskkv_score from the rows' natural-log softmax normalisers (as maskkv_attend_full returns them)."""
-    q, k = _as_view(Q_mask), _as_view(K_full)
-    wp, wn = _ws(workspace)
-    _check(_lib.maskkv_score_given_lse(ct.byref(desc.c()), ct.byref(q), ct.byref(k), ct.c_float(scale), _ptr(row_lse),
-                                       _ptr(scores), ct.c_int64(score_stride), _ptr(prompt_mass), wp, wn,
-                                       _stream(stream)), "maskkv_score_given_lse")
+    status = _native.score_given_lse(desc, Q_mask, K_full, scale, row_lse, scores, score_stride, prompt_mass, workspace,
+                                     stream)
+    if status:
+        _check(status, "maskkv_score_given_lse")
 
 
 def maskkv_score_static(desc: Desc, Q_mask, K_full, scale: float, scores: torch.Tensor, score_stride: int,
                         prompt_mass: Optional[torch.Tensor], stream=None) -> None:
     """maskkv_score with the library's own static scratch array instead of a caller workspace."""
-    q, k = _as_view(Q_mask), _as_view(K_full)
-    _check(_lib.maskkv_score_static(ct.byref(desc.c()), ct.byref(q), ct.byref(k), ct.c_float(scale), _ptr(scores),
-                                    ct.c_int64(score_stride), _ptr(prompt_mass), _stream(stream)),
-           "maskkv_score_static")
-
-
-def _host_i32(values: Optional[Sequence[int]]):
-    if values is None:
-        return None
-    return (ct.c_int32 * len(values))(*[int(x) for x in values])
+    status = _native.score_static(desc, Q_mask, K_full, scale, scores, score_stride, prompt_mass, stream)
+    if status:
+        _check(status, "maskkv_score_static")
 
 
 def maskkv_select(desc: Desc, scores: torch.Tensor, score_stride: int, pool_window: int, pool_mode: int,
                   budgets: torch.Tensor, idx: torch.Tensor, cu_budget: torch.Tensor, capacity: int,
                   workspace: Optional[torch.Tensor], stream=None, budgets_host: Optional[Sequence[int]] = None) -> None:
-    wp, wn = _ws(workspace)
-    _check(_lib.maskkv_select(ct.byref(desc.c()), _ptr(scores), ct.c_int64(score_stride), ct.c_int(pool_window),
-                              ct.c_int(pool_mode), _ptr(budgets), _host_i32(budgets_host), _ptr(idx), _ptr(cu_budget),
-                              ct.c_int64(capacity), wp, wn, _stream(stream)), "maskkv_select")
+    status = _native.select(desc, scores, score_stride, pool_window, pool_mode, budgets, budgets_host, idx, cu_budget,
+                            capacity, workspace, stream)
+    if status:
+        _check(status, "maskkv_select")
 
 
 def maskkv_compact(desc: Desc, K, V, idx: torch.Tensor, cu_budget: torch.Tensor, capacity: int,
                    Kc: torch.Tensor, Vc: torch.Tensor, stream=None) -> None:
-    k, v = _as_view(K), _as_view(V)
-    _check(_lib.maskkv_compact(ct.byref(desc.c()), ct.byref(k), ct.byref(v), _ptr(idx), _ptr(cu_budget),
-                               ct.c_int64(capacity), _ptr(Kc), _ptr(Vc), _stream(stream)), "maskkv_compact")
+    status = _native.compact(desc, K, V, idx, cu_budget, capacity, Kc, Vc, stream)
+    if status:
+        _check(status, "maskkv_compact")
 
 
 def maskkv_attend(desc: Desc, Q_resp, Kc: torch.Tensor, Vc: torch.Tensor, cu_budget: torch.Tensor, capacity: int,
                   K_resp, V_resp, scale: float, O, lse: Optional[torch.Tensor],
                   workspace: Optional[torch.Tensor], stream=None) -> None:
-    q, k2, v2, o = _as_view(Q_resp), _as_view(K_resp), _as_view(V_resp), _as_view(O)
-    wp, wn = _ws(workspace)
-    _check(_lib.maskkv_attend(ct.byref(desc.c()), ct.byref(q), _ptr(Kc), _ptr(Vc), _ptr(cu_budget),
-                              ct.c_int64(capacity), ct.byref(k2), ct.byref(v2), ct.c_float(scale), ct.byref(o),
-                              _ptr(lse), wp, wn, _stream(stream)), "maskkv_attend")
+    status = _native.attend(desc, Q_resp, Kc, Vc, cu_budget, capacity, K_resp, V_resp, scale, O, lse, workspace, stream)
+    if status:
+        _check(status, "maskkv_attend")
 
 
 def maskkv_attend_full(desc: Desc, Q_resp, K_full, V_full, scale: float, O, lse: Optional[torch.Tensor],
                        workspace: Optional[torch.Tensor], stream=None) -> None:
-    q, k2, v2, o = _as_view(Q_resp), _as_view(K_full), _as_view(V_full), _as_view(O)
-    wp, wn = _ws(workspace)
-    _check(_lib.maskkv_attend_full(ct.byref(desc.c()), ct.byref(q), ct.byref(k2), ct.byref(v2), ct.c_float(scale),
-                                   ct.byref(o), _ptr(lse), wp, wn, _stream(stream)), "maskkv_attend_full")
+    status = _native.attend_full(desc, Q_resp, K_full, V_full, scale, O, lse, workspace, stream)
+    if status:
+        _check(status, "maskkv_attend_full")
 
 
 def maskkv_head_budgets(desc: Desc, prompt_mass: torch.Tensor, k_l: int, alpha: float, budgets: torch.Tensor,
                         stream=None) -> None:
-    _check(_lib.maskkv_head_budgets(ct.byref(desc.c()), _ptr(prompt_mass), ct.c_int32(k_l), ct.c_float(alpha),
-                                    _ptr(budgets), _stream(stream)), "maskkv_head_budgets")
+    status = _native.head_budgets(desc, prompt_mass, k_l, alpha, budgets, stream)
+    if status:
+        _check(status, "maskkv_head_budgets")
 
 
 def maskkv_layer_importance_workspace_bytes() -> int:
@@ -240,12 +234,9 @@ def maskkv_layer_importance_workspace_bytes() -> int:
 def maskkv_layer_importance(h_in: torch.Tensor, h_out: torch.Tensor, importance: torch.Tensor,
                             workspace: Optional[torch.Tensor], stream=None) -> None:
     """h_in, h_out: [n_tokens, hidden] device tensors of the same dtype and row stride; importance: float32 [1]."""
-    assert h_in.is_cuda and h_in.dim() == 2 and h_in.stride(1) == 1 and h_out.shape == h_in.shape
-    assert h_out.stride() == h_in.stride() and h_out.dtype == h_in.dtype
-    wp, wn = _ws(workspace)
-    _check(_lib.maskkv_layer_importance(_ptr(h_in), _ptr(h_out), ct.c_int64(h_in.shape[0]), ct.c_int32(h_in.shape[1]),
-                                        ct.c_int32(_dtype_code(h_in)), ct.c_int64(h_in.stride(0)), _ptr(importance),
-                                        wp, wn, _stream(stream)), "maskkv_layer_importance")
+    status = _native.layer_importance(h_in, h_out, importance, workspace, stream)
+    if status:
+        _check(status, "maskkv_layer_importance")
 
 
 def maskkv_layer_budgets(importance: Sequence[float], k_p: int, beta: float,
@@ -267,13 +258,9 @@ def maskkv_layer_budgets(importance: Sequence[float], k_p: int, beta: float,
 def maskkv_value_shift(V_now: torch.Tensor, V_prev: torch.Tensor, delta: float, cos: torch.Tensor,
                        refresh: torch.Tensor, count: torch.Tensor, stream=None) -> None:
     """V_now, V_prev: [n_tokens, width] device tensors; cos: float32 [n]; refresh: int32 [n]; count: int32 [1]."""
-    assert V_now.is_cuda and V_now.dim() == 2 and V_now.stride(1) == 1 and V_prev.shape == V_now.shape
-    assert V_prev.stride() == V_now.stride() and V_prev.dtype == V_now.dtype
-    assert cos.dtype == torch.float32 and cos.numel() >= V_now.shape[0]
-    assert refresh.dtype == torch.int32 and refresh.numel() >= V_now.shape[0] and count.dtype == torch.int32
-    _check(_lib.maskkv_value_shift(_ptr(V_now), _ptr(V_prev), ct.c_int64(V_now.shape[0]), ct.c_int32(V_now.shape[1]),
-                                   ct.c_int32(_dtype_code(V_now)), ct.c_int64(V_now.stride(0)), ct.c_float(delta),
-                                   _ptr(cos), _ptr(refresh), _ptr(count), _stream(stream)), "maskkv_value_shift")
+    status = _native.value_shift(V_now, V_prev, delta, cos, refresh, count, stream)
+    if status:
+        _check(status, "maskkv_value_shift")
 
 
 def raw_library() -> ct.CDLL:
