@@ -250,7 +250,9 @@ int maskkv_score_static(const maskkv_desc* desc, const maskkv_tensor* Q_mask, co
     set_error("scores is NULL or score_stride %lld < P_max %d", (long long)score_stride, desc->P_max);
     return MASKKV_EINVAL;
   }
-  const size_t need = score_workspace_bytes(desc, lens);
+  // (the single sweep needs more scratch than the two passes: a description that only the latter fit takes them)
+  const bool two_pass = score_workspace_bytes(desc, lens) > kStaticScratchBytes;
+  const size_t need = score_workspace_bytes(desc, lens, two_pass);
   if (need > kStaticScratchBytes) {
     set_error("score_static: this description needs %zu bytes of scratch, the static array holds %zu; use maskkv_score "
               "with a caller workspace", need, kStaticScratchBytes);
@@ -259,7 +261,7 @@ int maskkv_score_static(const maskkv_desc* desc, const maskkv_tensor* Q_mask, co
   void* ws = nullptr;
   if (int e = static_scratch(&ws)) return e;
   return launch_score(desc, q, k, lens, pick_scale(desc, scale), scores, score_stride, prompt_mass, ws,
-                      reinterpret_cast<hipStream_t>(stream), nullptr);
+                      reinterpret_cast<hipStream_t>(stream), nullptr, nullptr, two_pass);
 }
 
 int maskkv_select_workspace_bytes(const maskkv_desc* desc, size_t* bytes) {

@@ -6,10 +6,17 @@
 namespace maskkv {
 
 // score.hip
-size_t score_workspace_bytes(const maskkv_desc* d, const Lens& lens);
+size_t score_workspace_bytes(const maskkv_desc* d, const Lens& lens, bool two_pass = false);
 int launch_score(const maskkv_desc* d, const View& Q, const View& K, const Lens& lens, float scale, float* scores,
                  int64_t score_stride, float* prompt_mass, void* workspace, hipStream_t stream,
-                 void* const* events, const float* row_lse = nullptr);
+                 void* const* events, const float* row_lse = nullptr, bool two_pass = false);
+
+// sweep.hip: the scores in one sweep over the keys
+bool sweep_wanted(const maskkv_desc* d, const Lens& lens, int nqg);
+size_t sweep_workspace_bytes(const maskkv_desc* d, int nqg);
+int launch_sweep(const maskkv_desc* d, const View& Q, const View& K, const Lens& lens, float scale, float* scores,
+                 int64_t score_stride, float* prompt_mass, float* group_sums, int64_t group_stride, int nqg, void* area,
+                 hipStream_t stream, const float** unit_mass);
 
 // select.hip
 size_t select_workspace_bytes(const maskkv_desc* d);

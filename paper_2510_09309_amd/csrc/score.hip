@@ -6,6 +6,8 @@
 //   merge   per-row log-sum-exp over the segments (+ the prompt's share of each row = prompt mass),
 //   pass 2  logits again, p = exp2(s*c - lse), summed over the queries for every prompt key.
 // Storing the n_m x N logits instead would cost far more HBM traffic than the second MFMA pass.
+// These passes serve fp32, prompts of more than one chunk of 128 keys per compute unit, the shapes at which they are the faster
+// way (see Plan in sweep.hip), and given normalisers; everything else is scored in one sweep (sweep.hip).
 //
 // Work decomposition: the key axis of every (b, h) is cut into 64-key tiles (prompt tiles, then response
 // tiles; a tile never straddles the prompt/response boundary).  All tiles of the launch form one global
@@ -86,6 +88,7 @@ struct ScoreParams {
   float* group_sums;  // [B*H][nqg][group_stride] column sums per query group (more than one group only)
   int64_t group_stride;
   float* prompt_mass; // [B*H] or null
+  const float* unit_mass;  // [B*H][nqg] prompt masses of the query groups, from the single sweep, or null
 };
 
 __device__ __forceinline__ int ceil_div(int a, int b) { return (a + b - 1) / b; }
@@ -408,6 +411,11 @@ __global__ __launch_bounds__(256) void score_group_sum_kernel(const ScoreParams 
   const int bh = blockIdx.y;
   const int P = prm.lens.P[bh / prm.H];
   const int j = (int)blockIdx.x * 256 + (int)threadIdx.x;
+  if (j == 0 && prm.unit_mass && prm.prompt_mass) {
+    float m = 0.f;
+    for (int i = 0; i < nqg; ++i) m += prm.unit_mass[(int64_t)bh * nqg + i];
+    prm.prompt_mass[bh] = m;
+  }
   if (j >= P) return;
   const float* src = prm.group_sums + (int64_t)bh * nqg * prm.group_stride + j;
   float v = src[0];
@@ -517,6 +525,12 @@ int launch_pass(const ScoreParams& prm, hipStream_t stream) {
   return check_launch(PASS == 1 ? "score pass 1" : "score pass 2");
 }
 
+int launch_group_sum(const ScoreParams& prm, int nqg, hipStream_t stream) {
+  const dim3 grid((unsigned)((prm.group_stride + 255) / 256), prm.B * prm.H);
+  hipLaunchKernelGGL(score_group_sum_kernel, grid, dim3(256), 0, stream, prm, nqg);
+  return check_launch("score (group sums)");
+}
+
 template <typename T, int D>
 int launch_score_t(ScoreParams& prm, const TileMap& map2, hipStream_t stream, void* const* events) {
   if (int e = mark(events, 0, stream)) return e;
@@ -531,11 +545,8 @@ int launch_score_t(ScoreParams& prm, const TileMap& map2, hipStream_t stream, vo
   if (map2.T > 0) {
     prm.map = map2;
     if (int e = launch_pass<T, D, 2>(prm, stream)) return e;
-    if (map2.nqg > 1) {
-      const dim3 grid((unsigned)((prm.group_stride + 255) / 256), prm.B * prm.H);
-      hipLaunchKernelGGL(score_group_sum_kernel, grid, dim3(256), 0, stream, prm, map2.nqg);
-      if (int e = check_launch("score (group sums)")) return e;
-    }
+    if (map2.nqg > 1)
+      if (int e = launch_group_sum(prm, map2.nqg, stream)) return e;
   }
   if (prm.row_lse && prm.prompt_mass) {
     hipLaunchKernelGGL(score_mass_kernel, dim3(prm.B * prm.H), dim3(kMassThreads), 0, stream, prm);
@@ -546,22 +557,34 @@ int launch_score_t(ScoreParams& prm, const TileMap& map2, hipStream_t stream, vo
 
 }  // namespace
 
-size_t score_workspace_bytes(const maskkv_desc* d, const Lens& lens) {
-  int pp, pr;
-  stat_slots(d, lens, make_map(d, lens, true), &pp, &pr);
-  const int64_t bh = (int64_t)d->B * d->H;
-  const int64_t nq = (int64_t)d->n_query * query_heads_per_kv(d);
-  size_t stats = (size_t)(bh * (pp + pr) * nq) * sizeof(float2);
-  stats = (stats + 255) / 256 * 256;
-  const size_t lse = ((size_t)(bh * nq) * sizeof(float) + 255) / 256 * 256;
-  const int nqg = query_groups(d);
-  const size_t sums = nqg > 1 ? (size_t)(bh * nqg * group_stride(d)) * sizeof(float) : 0;
-  return stats + lse + sums;
+namespace {
+
+// Workspace: [row statistics and normalisers, or what the single sweep needs][column sums per query group]
+struct ScoreArea {
+  size_t stats, sums, bytes;
+  ScoreArea(const maskkv_desc* d, const Lens& lens, bool sweep) {
+    int pp, pr;
+    stat_slots(d, lens, make_map(d, lens, true), &pp, &pr);
+    const int64_t bh = (int64_t)d->B * d->H;
+    const int64_t nq = (int64_t)d->n_query * query_heads_per_kv(d);
+    const int nqg = query_groups(d);
+    stats = ((size_t)(bh * (pp + pr) * nq) * sizeof(float2) + 255) / 256 * 256;
+    const size_t lse = ((size_t)(bh * nq) * sizeof(float) + 255) / 256 * 256;
+    sums = stats + lse;
+    if (sweep) sums = max(sums, sweep_workspace_bytes(d, nqg));
+    bytes = sums + (nqg > 1 ? (size_t)(bh * nqg * group_stride(d)) * sizeof(float) : 0);
+  }
+};
+
+}  // namespace
+
+size_t score_workspace_bytes(const maskkv_desc* d, const Lens& lens, bool two_pass) {
+  return ScoreArea(d, lens, !two_pass && sweep_wanted(d, lens, query_groups(d))).bytes;
 }
 
 int launch_score(const maskkv_desc* d, const View& Q, const View& K, const Lens& lens, float scale, float* scores,
                  int64_t score_stride, float* prompt_mass, void* workspace, hipStream_t stream,
-                 void* const* events, const float* row_lse) {
+                 void* const* events, const float* row_lse, bool two_pass) {
   ScoreParams prm;
   prm.row_lse = row_lse;
   prm.Q = Q;
@@ -577,17 +600,28 @@ int launch_score(const maskkv_desc* d, const View& Q, const View& K, const Lens&
   prm.n_query = d->n_query * prm.q_per_kv;
   stat_slots(d, lens, prm.map1, &prm.parts_p, &prm.parts_r);
   prm.c = scale * kLog2e;
-  const int64_t bh = (int64_t)d->B * d->H;
-  size_t stats = (size_t)(bh * (prm.parts_p + prm.parts_r) * prm.n_query) * sizeof(float2);
-  stats = (stats + 255) / 256 * 256;
-  prm.stats = reinterpret_cast<float2*>(workspace);
-  prm.lse2 = reinterpret_cast<float*>(reinterpret_cast<char*>(workspace) + stats);
-  const size_t lse = ((size_t)(bh * prm.n_query) * sizeof(float) + 255) / 256 * 256;
-  prm.group_sums = reinterpret_cast<float*>(reinterpret_cast<char*>(workspace) + stats + lse);
+  const bool sweep = !two_pass && !row_lse && sweep_wanted(d, lens, query_groups(d));
+  const ScoreArea area(d, lens, sweep);
+  char* ws = reinterpret_cast<char*>(workspace);
+  prm.stats = reinterpret_cast<float2*>(ws);
+  prm.lse2 = reinterpret_cast<float*>(ws + area.stats);
+  prm.group_sums = reinterpret_cast<float*>(ws + area.sums);
   prm.group_stride = group_stride(d);
   prm.scores = scores;
   prm.score_stride = score_stride;
   prm.prompt_mass = prompt_mass;
+  prm.unit_mass = nullptr;
+  if (sweep) {
+    if (int e = mark(events, 0, stream)) return e;
+    if (int e = launch_sweep(d, Q, K, lens, scale, scores, score_stride, prompt_mass, prm.group_sums, prm.group_stride,
+                             query_groups(d), ws, stream, &prm.unit_mass))
+      return e;
+    if (int e = mark(events, 1, stream)) return e;
+    if (int e = mark(events, 2, stream)) return e;
+    if (map2.nqg > 1)
+      if (int e = launch_group_sum(prm, map2.nqg, stream)) return e;
+    return mark(events, 3, stream);
+  }
   if (d->dtype == MASKKV_BF16)
     return d->d == 128 ? launch_score_t<bf16_t, 128>(prm, map2, stream, events)
                        : launch_score_t<bf16_t, 64>(prm, map2, stream, events);

@@ -1,0 +1,989 @@
+// Mask-Voting scores in one sweep over the prompt's keys (see score.hip for the two-pass form and the definitions).
+//
+// A column sum I_j = sum_i exp(s_ij) / L_i needs the normaliser L_i of every row before the first column can be summed, so
+// score.hip forms the logits twice.  Here they are formed once: a workgroup forms the exponentials of a chunk of 128 keys x 256
+// voting rows, keeps them in registers (64 per lane), publishes the chunk's row sums, forms the next chunk, and by then
+// the row sums of all chunks of that unit have arrived and the kept chunk is turned into column sums.
+//
+//   start kernel  row references (the response span's log-sum-exp, which is also the rows' sum over the response keys), zeroed
+//                 sums, and the voting rows packed in MFMA fragment order.
+//   sweep kernel  one workgroup of eight waves (32 rows each) per compute unit; chunk x of the launch, all units end to
+//                 end, belongs to workgroup x mod G, so that the workgroups work on the same unit at the same time.
+//
+// Per step a workgroup loads 64 KB of packed rows (from L2, into registers, each fragment as soon as the last MFMA that read
+// the old one is issued) and 32 KB of keys (direct transfers into a ring of four chunks, two steps ahead).  Row sums are added
+// with 64-bit integer atomics, 4 copies of each sum; a step later every wave reads the sums of its own rows.  Nothing
+// waits for a sum that is not needed yet, and every wait is bounded: if the workgroups turn out not to be all resident, or a
+// row's sum leaves the range of the integers, a two-pass fallback at the end of the same kernel does the work.
+//
+// What bounds it (32 heads x 128, 32k tokens, 256 rows: 119 us for the sweep, of 163 us for two passes and merge before): in a
+// loop of such calls the board's power.  The clock falls to 1.6 GHz, where a step is 5400 cycles, 2048 of them MFMAs, and
+// variants with fewer vector instructions take the same time at a lower clock; without the MFMAs 66 us, without the
+// loads of rows and keys 87, without exponentials 96, without exchange and column sums 94.  At 8k tokens (1.9 GHz) the call
+// takes 38 us, 58 before; the ragged batch of bench.py 505 us, 730 before.  Both waves of a SIMD half a step apart, 2 or 8
+// copies of the sums, or asking for the sums earlier in the step: slower (a sum that is asked for before it is
+// complete has to be asked for again, and a line that is being read is slow to add to).
+#include "kernels.hpp"
+namespace maskkv {
+
+namespace {
+
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+
+constexpr int kRows = 256;                 // voting rows per unit at most; a unit is one (sequence, head, group of voting rows)
+constexpr int kWaves = 8;                  // each owns 32 rows
+constexpr int kThreads = 64 * kWaves;
+constexpr int kNB = 4;                     // 32-key blocks per chunk
+constexpr int kKeys = 32 * kNB;
+constexpr int kAhead = 3;                  // slots between the LDS read of a fragment and its use
+constexpr int kLag = 2;                    // slots between the last MFMA of a block and its first exponential
+constexpr int kCopies = 4;                 // of every row's `low` sum: workgroups spread their additions over them
+
+// Row sums are exchanged as integers, so that their total does not depend on the order of arrival: 10 bits count the chunks
+// that have been added, 54 bits hold the sum in units of 2^-28 of the response span's own sum (`low`) or, for a chunk
+// whose sum is above 2^16 of it, in units of 2^-4 (`high`).
+constexpr int kCountShift = 54;
+constexpr uint64_t kSumMask = (1ull << kCountShift) - 1;
+constexpr float kLowScale = 268435456.f;   // 2^28
+constexpr float kLowLimit = 65536.f;       // 2^16
+constexpr float kHighScale = 16.f;         // 2^4
+constexpr float kHighLimit = 1099511627776.f;  // 2^40 (kMaxGroups chunks of either limit stay below 2^54)
+constexpr uint64_t kPatience = 2000000;    // 20 ms of the 100 MHz clock
+
+constexpr int kMaxGroups = 256;            // workgroups of a sweep, and chunks of a unit, at most (one per compute unit)
+
+struct Control {
+  int run;      // this call holds the device's sweep lock
+  int redo;     // the sweep could not do the work: the fallback at the end of the kernel does
+  int ticket;   // next task of the fallback
+  int pad;
+  int started[kMaxGroups];  // by workgroup of the sweep
+};
+
+constexpr int kSpans = 8;                  // pieces of a unit's keys in the fallback
+
+struct SweepParams {
+  View Q, K;
+  Lens lens;
+  int B, H, n_resp;
+  int n_query;      // voting rows per key/value head: q_per_kv query heads of n_qh mask queries each
+  int n_qh, q_per_kv, nqg;
+  int rows;         // voting rows per unit, a multiple of 32 (the last unit of a head may have fewer)
+  int chunks;       // in total
+  float c;          // scale * log2(e)
+  uint64_t* low;    // [units][kCopies][256]
+  uint64_t* high;   // [units][256]
+  float* start;     // [units][256]: minus the response span's log-sum-exp, in units of the raw logits
+  char* qpack;      // [units][8 waves] 32 rows in MFMA fragment order
+  Control* ctl;
+  int* spans_done;  // [units] spans of the unit whose statistics are there (fallback)
+  float2* stats;    // [units][kSpans][256] (reference, sum) of a span of chunks (fallback)
+  float* out;       // [units][out_stride]: the scores, or with more than one query group the groups' column sums
+  int64_t out_stride;
+  float* mass;      // [units] or null
+};
+
+// One sweep kernel at a time may run on a device: its workgroups wait for each other, so all of them have to be resident.
+__device__ int sweep_lock;
+
+__device__ __forceinline__ int ceil_div(int a, int b) { return (a + b - 1) / b; }
+
+template <int D>
+struct Cfg {
+  static constexpr int kRowB = D * 2;
+  static constexpr int kRing = 4;                   // chunks of keys in LDS
+  static constexpr int kSteps = kRowB / 32;
+  static constexpr int kPPR = kRowB / 16;           // 16-byte pieces per row
+  static constexpr int kRPI = 1024 / kRowB;         // rows moved by one wave instruction
+  static constexpr int kMoves = kKeys / kWaves / kRPI;  // transfers per wave and chunk
+  static constexpr int kKBytes = kKeys * kRowB;
+  static constexpr int kQBytes = 32 * kRowB;        // per wave
+  static constexpr int kOffStart = kRing * kKBytes; // behind the ring of chunks: [2][kWaves][64] floats
+  static constexpr int kOffCs = kOffStart + 2 * kWaves * 256;  // [2][kWaves][kKeys] floats
+  static constexpr int kOffW = kOffCs + 2 * kWaves * kKeys * 4;  // [kWaves][32] floats
+  static constexpr int kOffInf = kOffW + kWaves * 128;         // 32 floats: -inf
+  static constexpr int kOffMass = kOffInf + 128;               // [2][kWaves] floats
+  static constexpr int kOffBad = kOffMass + 2 * kWaves * 4;    // one int
+  static constexpr int kLds = kOffBad + 64;
+  // Rows are stored without padding (a direct transfer writes 1 KiB of consecutive LDS); piece p of row r sits in
+  // slot p ^ swz(r), which spreads the fragment reads of 16 consecutive rows over all banks.
+  __device__ static int swz(int row) { return D == 128 ? row & 15 : (row >> 1) & 7; }
+};
+
+// Direct global -> LDS transfer of 16 (4) bytes per lane from base + off to lds + lane * 16 (4).
+__device__ __forceinline__ void dma16(const char* base, uint32_t off, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds) : "memory");
+}
+__device__ __forceinline__ void dma4(const char* base, uint32_t off, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" ::"v"(off), "s"(base), "s"(lds) : "memory");
+}
+
+// Global memory by a uniform base (two scalar registers, hidden from the optimiser, which would otherwise form one 64-bit
+// address per lane and keep it) and a 32-bit offset per lane.
+typedef __attribute__((address_space(1))) char* Base;
+__device__ __forceinline__ Base base_of(const void* p) {
+  Base b = (Base)p;
+  asm volatile("" : "+s"(b));
+  return b;
+}
+template <typename T>
+__device__ __forceinline__ __attribute__((address_space(1))) T* at(Base b, uint32_t off, int imm = 0) {
+  return reinterpret_cast<__attribute__((address_space(1))) T*>(b + off + imm);
+}
+// LDS by its own 32-bit address (the name of the array would be added to every lane's offset again and again).
+template <typename T>
+__device__ __forceinline__ __attribute__((address_space(3))) T* in_lds(uint32_t addr, int imm = 0) {
+  return reinterpret_cast<__attribute__((address_space(3))) T*>((__attribute__((address_space(3))) char*)(uintptr_t)addr + imm);
+}
+
+__device__ __forceinline__ uint64_t peek(Base b, uint32_t off) {
+  return __hip_atomic_load(at<uint64_t>(b, off), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, false));
+}
+
+// ---- response span: row references, zeroed sums, and the voting rows in the order in which the sweep reads them.
+// A workgroup serves BLOCKS blocks of 32 rows of a unit; 8 / BLOCKS waves share a block's keys, which come through LDS 128
+// at a time.  (Eight blocks where there are units enough to fill the chip: each key is then read once per unit.)
+template <int D, int BLOCKS>
+__global__ __launch_bounds__(kThreads) void sweep_start_kernel(const SweepParams prm) {
+  using C = Cfg<D>;
+  constexpr int S = C::kSteps, SPLIT = kWaves / BLOCKS;
+  extern __shared__ __attribute__((aligned(1024))) char lds[];  // two tiles of 128 keys
+  __shared__ float2 part[kWaves][32];
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
+  const int lane = threadIdx.x & 63, r = lane & 31, g = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int unit = blockIdx.x / SPLIT;
+  const int bh = unit / prm.nqg, qg = unit - bh * prm.nqg;
+  const int b = bh / prm.H, h = bh - b * prm.H;
+  const int P = prm.lens.P[b];
+  const char* keys = prm.K.row(b, h, P);
+  auto dma = [&](int t) {
+#pragma unroll
+    for (int j = 0; j < C::kMoves; ++j) {
+      const int row = wave * (kKeys / kWaves) + j * C::kRPI + lane / C::kPPR;
+      const int piece = (lane % C::kPPR) ^ C::swz(row);
+      dma16(keys, (uint32_t)min(row + t * kKeys, prm.n_resp - 1) * (uint32_t)prm.K.stride_t + piece * 16,
+            lds0 + (t & 1) * C::kKBytes + (wave * (kKeys / kWaves) + j * C::kRPI) * C::kRowB);
+    }
+  };
+  const int tiles = ceil_div(prm.n_resp, kKeys);
+  dma(0);
+  const int rb = (blockIdx.x % SPLIT) * BLOCKS + wave / SPLIT;  // block of 32 rows
+  const int part_of = wave % SPLIT;
+  const int q0 = qg * prm.rows + rb * 32;
+  u32x4 qf[S];
+  const char* qrow = prm.Q.group_row(b, h, prm.q_per_kv, prm.n_qh, min(q0 + r, prm.n_query - 1)) + g * 16;
+#pragma unroll
+  for (int s = 0; s < S; ++s) qf[s] = *reinterpret_cast<const u32x4*>(qrow + s * 32);
+
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    const int run = atomicCAS(&sweep_lock, 0, 1) == 0;
+    prm.ctl->run = run;
+    prm.ctl->redo = !run;
+    prm.ctl->ticket = 0;
+  }
+  if (blockIdx.x == 0)
+    for (int i = threadIdx.x; i < kMaxGroups; i += kThreads) prm.ctl->started[i] = 0;
+  if (rb == 0 && part_of == 0 && lane == 0) {
+    prm.spans_done[unit] = 0;
+    if (P == 0 && prm.mass) prm.mass[unit] = 0.f;
+  }
+  const int64_t row0 = (int64_t)unit * kRows + rb * 32;
+  if (part_of == 0) {
+    if (lane < 32) {
+#pragma unroll
+      for (int i = 0; i < kCopies; ++i) prm.low[((int64_t)unit * kCopies + i) * kRows + rb * 32 + lane] = 0;
+      prm.high[row0 + lane] = 0;
+    }
+    u32x4* pack = reinterpret_cast<u32x4*>(prm.qpack + row0 * C::kRowB) + lane;
+#pragma unroll
+    for (int s = 0; s < S; ++s) pack[s * 64] = qf[s];
+  }
+  float m = kNegBig, l = 0.f;
+  for (int t = 0; t < tiles; ++t) {
+    if (t + 1 < tiles) dma(t + 1);  // (its tile was read two steps ago, before the last barrier)
+    if (t + 1 < tiles)
+      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"i"(C::kMoves) : "memory");
+    else
+      asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    for (int kb = part_of; kb < kNB; kb += SPLIT) {
+      const int k0 = t * kKeys + kb * 32;
+      if (k0 >= prm.n_resp) break;
+      f32x16 a{};
+#pragma unroll
+      for (int s = 0; s < S; ++s) {
+        const u32x4 kf = *in_lds<const u32x4>(lds0 + (t & 1) * C::kKBytes + (kb * 32 + r) * C::kRowB + (((2 * s + g) ^ C::swz(r)) << 4));
+        mfma_step<bf16_t>(kf, qf[s], a);
+      }
+      float bm = kNegBig;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        if (k0 + 8 * (i / 4) + 4 * g + (i % 4) >= prm.n_resp) a[i] = -INFINITY;
+        bm = fmaxf(bm, a[i] * prm.c);
+      }
+      const float m_new = fmaxf(m, bm);
+      float s = 0.f;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) s += fast_exp2(fmaf(a[i], prm.c, -m_new));
+      l = l * fast_exp2(m - m_new) + s;
+      m = m_new;
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  }
+  {
+    const float mo = xor32(m), lo = xor32(l);
+    const float mm = fmaxf(m, mo);
+    l = l * fast_exp2(m - mm) + lo * fast_exp2(mo - mm);
+    m = mm;
+  }
+  if (SPLIT > 1) {
+    if (g == 0) part[wave][r] = make_float2(m, l);
+    __syncthreads();
+  }
+  if (part_of == 0 && lane < 32) {
+    if (SPLIT > 1) {
+      float M = kNegBig, L = 0.f;
+#pragma unroll
+      for (int w = 0; w < SPLIT; ++w) M = fmaxf(M, part[wave + w][lane].x);
+#pragma unroll
+      for (int w = 0; w < SPLIT; ++w) L += part[wave + w][lane].y * fast_exp2(part[wave + w][lane].x - M);
+      m = M;
+      l = L;
+    }
+    prm.start[row0 + lane] = rb * 32 < prm.rows && q0 + lane < prm.n_query ? -(m + __log2f(l)) / prm.c : -INFINITY;
+  }
+}
+
+// ---- fallback: the scores in two passes, as tasks that workgroups take by ticket, whatever their number.  A task is a
+// span of a unit's chunks; first come all tasks that form row statistics, then all that form column sums.  The latter wait
+// for the former of their unit, which have smaller tickets and therefore are with workgroups that are running.
+template <int D>
+__device__ __forceinline__ void sweep_redo(const SweepParams& prm, uint32_t lds0) {
+  using C = Cfg<D>;
+  constexpr int S = C::kSteps;
+  const int lane = threadIdx.x & 63, r = lane & 31, g = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int units = prm.B * prm.H * prm.nqg;
+  const uint32_t word = lds0 + C::kOffMass;                   // one int: the ticket, or whether to go on
+  const uint32_t colsum = lds0 + C::kOffCs;                   // [kWaves][kKeys] floats
+  for (;;) {
+    __syncthreads();
+    if (threadIdx.x == 0) *in_lds<int>(word) = __hip_atomic_fetch_add(&prm.ctl->ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    const int ticket = *in_lds<int>(word);
+    if (ticket >= 2 * units * kSpans) return;
+    const bool second = ticket >= units * kSpans;
+    const int task = second ? ticket - units * kSpans : ticket;
+    const int unit = task / kSpans, span = task % kSpans;
+    const int bh = unit / prm.nqg;
+    const int b = bh / prm.H, h = bh - b * prm.H;
+    const int P = prm.lens.P[b];
+    const int nc = ceil_div(P, kKeys);
+    const int c0 = nc * span / kSpans, c1 = nc * (span + 1) / kSpans;
+    const int64_t row0 = (int64_t)unit * kRows + wave * 32;
+    u32x4 qf[S];
+#pragma unroll
+    for (int s = 0; s < S; ++s) qf[s] = *reinterpret_cast<const u32x4*>(prm.qpack + row0 * C::kRowB + s * 1024 + lane * 16);
+    float2* st = prm.stats + (int64_t)unit * kSpans * kRows + wave * 32 + r;  // (of query row r; one span is kRows further)
+    float m = kNegBig, l = 0.f;
+    float nl[16];  // second pass: minus the base-2 log-sum-exp of this lane's rows
+    if (second) {
+      if (threadIdx.x == 0) {
+        const uint64_t t0 = wall_clock64();
+        while (__hip_atomic_load(&prm.spans_done[unit], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) < kSpans && wall_clock64() - t0 < 50 * kPatience)
+          __builtin_amdgcn_s_sleep(8);
+      }
+      __syncthreads();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+      // all spans and the response span (whose sum is 1 in units of its own log-sum-exp)
+      const float ref = -prm.start[row0 + r] * prm.c;  // +inf for a row that does not exist
+      const bool live = ref != INFINITY;
+      float M = live ? ref : 0.f, Lp = 0.f;
+      float2 v[kSpans];
+#pragma unroll
+      for (int i = 0; i < kSpans; ++i) {
+        v[i].x = __hip_atomic_load(&st[i * kRows].x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        v[i].y = __hip_atomic_load(&st[i * kRows].y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        M = fmaxf(M, v[i].x);
+      }
+#pragma unroll
+      for (int i = 0; i < kSpans; ++i) Lp += v[i].y * fast_exp2(v[i].x - M);
+      const float L = Lp + fast_exp2(ref - M);
+      const float nlse = live ? -(M + __log2f(L)) : -INFINITY;
+      if (span == 0 && prm.mass) {
+        float mass = live && g == 0 ? Lp / L : 0.f;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) mass += __shfl_xor(mass, o, 64);
+        if (lane == 0) *in_lds<float>(colsum + wave * 4) = mass;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+          float t = 0.f;
+          for (int w = 0; w < kWaves; ++w) t += *in_lds<float>(colsum + w * 4);
+          prm.mass[unit] = t;
+        }
+        __syncthreads();
+      }
+#pragma unroll
+      for (int i = 0; i < 16; ++i) nl[i] = __shfl(nlse, 8 * (i / 4) + 4 * g + (i % 4), 64);
+    }
+    for (int ci = c0; ci < c1; ++ci) {
+      __syncthreads();
+#pragma unroll
+      for (int j = 0; j < C::kMoves; ++j) {
+        const int row = wave * (kKeys / kWaves) + j * C::kRPI + lane / C::kPPR;
+        const int piece = (lane % C::kPPR) ^ C::swz(row);
+        *in_lds<u32x4>(lds0 + row * C::kRowB + (lane % C::kPPR) * 16) =
+            *reinterpret_cast<const u32x4*>(prm.K.row(b, h, min(ci * kKeys + row, P - 1)) + piece * 16);
+      }
+      __syncthreads();
+      float col[kNB];
+#pragma unroll
+      for (int kb = 0; kb < kNB; ++kb) {
+        f32x16 a{};
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+          const u32x4 kf = *in_lds<const u32x4>(lds0 + (kb * 32 + r) * C::kRowB + (((2 * s + g) ^ C::swz(r)) << 4));
+          if (second)
+            mfma_step<bf16_t>(qf[s], kf, a);
+          else
+            mfma_step<bf16_t>(kf, qf[s], a);
+        }
+        if (second) {
+          float v = 0.f;
+#pragma unroll
+          for (int i = 0; i < 16; ++i) v += fast_exp2(fmaf(a[i], prm.c, nl[i]));
+          col[kb] = v + xor32(v);
+        } else {
+          float bm = m;
+#pragma unroll
+          for (int i = 0; i < 16; ++i) {
+            if (ci * kKeys + kb * 32 + 8 * (i / 4) + 4 * g + (i % 4) >= P) a[i] = -INFINITY;
+            bm = fmaxf(bm, a[i] * prm.c);
+          }
+          float v = 0.f;
+#pragma unroll
+          for (int i = 0; i < 16; ++i) v += fast_exp2(fmaf(a[i], prm.c, -bm));
+          l = l * fast_exp2(m - bm) + v;
+          m = bm;
+        }
+      }
+      if (second) {
+        if (g == 0)
+#pragma unroll
+          for (int kb = 0; kb < kNB; ++kb) *in_lds<float>(colsum + (wave * kKeys + kb * 32 + r) * 4) = col[kb];
+        __syncthreads();
+        const int j = ci * kKeys + (int)threadIdx.x;
+        if ((int)threadIdx.x < kKeys && j < P) {
+          float v = 0.f;
+#pragma unroll
+          for (int w = 0; w < kWaves; ++w) v += *in_lds<const float>(colsum + (w * kKeys + threadIdx.x) * 4);
+          prm.out[(int64_t)unit * prm.out_stride + j] = v;
+        }
+      }
+    }
+    if (!second) {
+      const float mo = xor32(m), lo = xor32(l);
+      const float mm = fmaxf(m, mo);
+      if (g == 0) {
+        __hip_atomic_store(&st[span * kRows].x, mm, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&st[span * kRows].y, l * fast_exp2(m - mm) + lo * fast_exp2(mo - mm), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+      __syncthreads();
+      if (threadIdx.x == 0) __hip_atomic_fetch_add(&prm.spans_done[unit], 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+    }
+  }
+}
+
+// A chunk: number ci of the nc of its unit.
+struct Chunk {
+  int unit, ci, nc, P;
+};
+
+template <int D>
+__device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t lds0) {
+  using C = Cfg<D>;
+  constexpr int S = C::kSteps;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int r = lane & 31, g = lane >> 5;
+  const float c = prm.c;
+  const int G = gridDim.x;
+  const int mine = (prm.chunks - (int)blockIdx.x + G - 1) / G;  // chunks blockIdx.x, + G, + 2G, ...
+  // A value hidden from the optimiser: what a step derives from it is then worth an instruction or two each time instead of
+  // a register for the whole loop.
+  auto here = [&](uint32_t v) {
+    asm volatile("" : "+v"(v));
+    return v;
+  };
+  auto lane_now = [&]() { return (int)here(lane); };
+
+  // ---- the walk over this workgroup's chunks
+  int at_b = 0, at_h = 0, at_g = 0;
+  Chunk ahead{0, (int)blockIdx.x, (prm.lens.P[0] + kKeys - 1) / kKeys, prm.lens.P[0]};
+  const char* kbase = prm.K.row(0, 0, 0);
+  auto settle = [&]() {
+    while (ahead.ci >= ahead.nc) {
+      ahead.ci -= ahead.nc;
+      ++ahead.unit;
+      if (++at_g == prm.nqg) {
+        at_g = 0;
+        kbase += prm.K.stride_h;
+        if (++at_h == prm.H) {
+          at_h = 0;
+          ++at_b;
+          kbase = prm.K.row(at_b, 0, 0);
+          ahead.P = prm.lens.P[at_b];
+          ahead.nc = (ahead.P + kKeys - 1) / kKeys;
+        }
+      }
+    }
+  };
+  const uint32_t kstride = (uint32_t)prm.K.stride_t;
+  const uint32_t lane16 = lane * 16;
+  // Row wave * 16 + j * kRPI + rl of the chunk (rl: this lane's row of transfer j) has its pieces permuted by the low bits of
+  // that number, which are j's and rl's side by side: one exclusive-or with a constant per transfer.
+  const uint32_t krow = (uint32_t)lane / C::kPPR, kpiece = ((uint32_t)lane % C::kPPR ^ C::swz(krow)) << 4;
+  const uint32_t koff = krow * kstride;
+  auto dma_k = [&](int slot) {  // the chunk `ahead` into slot `slot` of the ring
+    const char* base = kbase + (int64_t)(ahead.ci * kKeys + wave * (kKeys / kWaves)) * prm.K.stride_t;
+    const int last = ahead.P - 1 - ahead.ci * kKeys - wave * (kKeys / kWaves);  // row of the last key, counted from this wave's first
+    const uint32_t to = lds0 + slot * C::kKBytes + wave * (kKeys / kWaves) * C::kRowB;
+    if (last >= kKeys / kWaves - 1) {
+      const uint32_t piece = here(kpiece);
+#pragma unroll
+      for (int j = 0; j < C::kMoves; ++j)
+        dma16(base + (int64_t)(j * C::kRPI) * prm.K.stride_t, (piece ^ (C::swz(j * C::kRPI) << 4)) + koff, to + j * 1024);
+    } else {
+#pragma unroll
+      for (int j = 0; j < C::kMoves; ++j) {
+        const int row = min(j * C::kRPI + (int)here(krow), max(last, 0));
+        dma16(last >= 0 ? base : kbase, (here(kpiece) ^ (C::swz(j * C::kRPI) << 4)) + (uint32_t)row * kstride, to + j * 1024);
+      }
+    }
+  };
+  auto dma_start = [&](const Chunk& k, int par) {
+    dma4(reinterpret_cast<const char*>(prm.start + (int64_t)k.unit * kRows + wave * 32), here(lane16) >> 2,
+         lds0 + C::kOffStart + (par * kWaves + wave) * 256);
+  };
+  u32x4 qf[S];
+  Base qlo, qhi;  // (two: an immediate offset reaches 4 KiB)
+  auto aim_q = [&](const Chunk& k) {
+    const char* q = prm.qpack + ((int64_t)k.unit * kWaves + wave) * C::kQBytes;
+    qlo = base_of(q);
+    qhi = base_of(q + 4096);
+  };
+  auto load_q = [&](int ks, uint32_t off) { qf[ks] = *at<const u32x4>(ks < 4 ? qlo : qhi, off, ks % 4 * 1024); };
+
+  // the row (of this wave's 32) whose sum the butterfly below leaves in a lane; lanes 2n and 2n+1 hold the same one
+  auto row_of = [](int ln) {
+    return 8 * (((ln >> 4) & 1) * 2 + ((ln >> 3) & 1)) + 4 * (ln >> 5) + (((ln >> 2) & 1) * 2 + ((ln >> 1) & 1));
+  };
+  const uint32_t row8 = row_of(lane) * 8;
+  const int copy = (int)blockIdx.x % kCopies;
+  bool patient = true;
+
+  // The logits are formed 32 keys at a time, minus the rows' references, which are the accumulators' initial values (a
+  // key past the prompt starts from -inf).  Matrix and vector instructions are interleaved by hand, in slots of one
+  // MFMA, the exponentials of 16 / S logits of the block before, and the LDS read of the fragment of the MFMA
+  // two slots on: left to itself the compiler waits for every fragment and moves the exponentials out of the way.
+  auto init = [&](int par, int kb, int left, f32x16& a) {
+    const uint32_t nb = (left > kb * 32 ? lds0 + C::kOffStart + (par * kWaves + wave) * 256 : lds0 + C::kOffInf) + 16 * g;
+#pragma unroll
+    for (int i4 = 0; i4 < 4; ++i4) {
+      const f32x4 v = *in_lds<const f32x4>(nb, 32 * i4);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) a[4 * i4 + e] = v[e];
+    }
+  };
+  // The ring's four chunks are addressed as two pairs: fa points at this lane's fragments of the first chunk of a pair (the
+  // second is an immediate offset away) and changes sides every other step.
+  uint32_t fa[S];
+#pragma unroll
+  for (int ks = 0; ks < S; ++ks) {
+    fa[ks] = lds0 + r * C::kRowB + (((2 * ks + g) ^ C::swz(r)) << 4);
+    asm volatile("" : "+v"(fa[ks]));
+  }
+  auto turn = [&]() {
+#pragma unroll
+    for (int ks = 0; ks < S; ++ks) fa[ks] ^= 2 * C::kKBytes;
+  };
+  u32x4 kf[kAhead + 1];
+  auto fetch = [&](int par, int n) {  // fragment n % S of block n / S of chunk `par` of the pair
+    kf[n % (kAhead + 1)] = *in_lds<const u32x4>(fa[n % S], par * C::kKBytes + n / S * 32 * C::kRowB);
+  };
+  float rs[16];
+  constexpr int E = 16 / S;  // logits per slot
+  float arg[E];
+  // Slot m of the exponentials of a chunk: the arguments of the next slot's, this slot's exponentials, the sums of the last
+  // slot's (three independent strands: a wave issues in order and would wait for each result in turn).
+  auto expo = [&](int m, const f32x16& pre, f32x16 (&p)[kNB]) {
+    float v[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int i = m % S * E + e;
+      if (m >= 0 && m < kNB * S) v[e] = fast_exp2(arg[e]);
+      if (m + 1 >= 0 && m + 1 < kNB * S) {
+        const int j = (m + 1) % S * E + e;
+        arg[e] = (m + 1 < S ? pre[j] : p[(m + 1) / S][j]) * c;
+        asm volatile("" : "+v"(arg[e]));
+      }
+      if (m >= 1) {
+        const int q = (m - 1) / S, j = (m - 1) % S * E + e;
+        if (q > 0) {
+          rs[j] = (q == 1 ? p[0][j] : rs[j]) + p[q][j];
+          asm volatile("" : "+v"(rs[j]));
+        }
+      }
+      if (m >= 0 && m < kNB * S) {
+        asm volatile("" : "+v"(v[e]));
+        p[m / S][i] = v[e];
+      }
+    }
+  };
+
+  // Column sums of a completed chunk: add the waves' parts.  Two waves do it, another pair at every step.
+  auto flush = [&](const Chunk& k, int par, int turn) {
+    if (wave / 2 != turn % (kWaves / 2) || *in_lds<const int>(lds0 + C::kOffBad)) return;
+    const int col = (wave & 1) * 64 + lane_now();
+    const uint32_t cs = lds0 + C::kOffCs + par * kWaves * kKeys * 4 + col * 4;
+    float v = *in_lds<const float>(cs);
+#pragma unroll
+    for (int w = 1; w < kWaves; ++w) v += *in_lds<const float>(cs, w * kKeys * 4);
+    const Base out = base_of(prm.out + (int64_t)k.unit * prm.out_stride + k.ci * kKeys);
+    if (col < k.P - k.ci * kKeys) *at<float>(out, col * 4) = v;
+    if (k.ci == 0 && col == 0 && prm.mass) {
+      const uint32_t ms = lds0 + C::kOffMass + par * kWaves * 4;
+      float m = 0.f;
+#pragma unroll
+      for (int w = 0; w < kWaves; ++w) m += *in_lds<const float>(ms, w * 4);
+      prm.mass[k.unit] = m;
+    }
+  };
+
+  uint64_t seen[kCopies];
+  auto ask = [&](const Chunk& k) {
+    const uint64_t* low = prm.low + ((int64_t)k.unit * kCopies * kRows + wave * 32);
+    const uint32_t off = here(row8);
+#pragma unroll
+    for (int i = 0; i < kCopies; ++i) seen[i] = peek(base_of(low + i * kRows), off);
+    asm volatile("" ::: "memory");
+  };
+  auto add = [&](const uint64_t* to, float f) {  // one chunk and the whole number f < 2^44
+    const float top = floorf(f * 2.3283064365386963e-10f);  // 2^-32
+    const uint32_t hi = (uint32_t)top + (1u << (kCountShift - 32));
+    const uint32_t lo = (uint32_t)fmaf(top, -4294967296.f, f);
+    __hip_atomic_fetch_add(at<uint64_t>(base_of(to), here(row8)), ((uint64_t)hi << 32) | lo, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+  };
+  auto publish = [&](const Chunk& k) {  // this wave's row sums (rs) of the chunk just formed
+    // sum over the 32 lanes of a half: 16 values, halved at every exchange
+    float t8[8], t4[4], t2[2];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const auto sw = __builtin_amdgcn_permlane16_swap(as_u32(rs[i]), as_u32(rs[i + 8]), false, false);
+      const unsigned u0 = sw[0], u1 = sw[1];
+      t8[i] = as_f32(u0) + as_f32(u1);
+    }
+    // x + (x of the mirrored lane) in the lanes whose bit is clear, y + (y of the mirrored lane) in the others
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      asm("s_nop 1\n\tv_add_f32_dpp %0, %1, %1 row_mirror row_mask:0xf bank_mask:0x3\n\t"
+          "v_add_f32_dpp %0, %2, %2 row_mirror row_mask:0xf bank_mask:0xc" : "=&v"(t4[i]) : "v"(t8[i]), "v"(t8[i + 4]));
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+      asm("s_nop 1\n\tv_add_f32_dpp %0, %1, %1 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
+          "v_add_f32_dpp %0, %2, %2 row_half_mirror row_mask:0xf bank_mask:0xa" : "=&v"(t2[i]) : "v"(t4[i]), "v"(t4[i + 2]));
+    const int ln = lane_now();
+    const float q0 = t2[0] + dpp<0x1B>(t2[0]), q1 = t2[1] + dpp<0x1B>(t2[1]);  // quad mirror
+    float sum = (ln & 2) ? q1 : q0;
+    sum += dpp<0xB1>(sum);  // neighbours
+    const bool low = sum < kLowLimit;
+    if (!(ln & 1) && low) add(prm.low + (((int64_t)k.unit * kCopies + copy) * kRows + wave * 32), sum * kLowScale);
+    if (!__all(low)) {  // (rare)
+      const bool fits = sum < kHighLimit;
+      if (!__all(low || fits)) {  // known to every workgroup of the unit before its row sums are complete
+        __hip_atomic_store(&prm.ctl->redo, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+      }
+      if (!(ln & 1) && !low) add(prm.high + ((int64_t)k.unit * kRows + wave * 32), fits ? sum * kHighScale : 0.f);
+    }
+  };
+  // Column sums of the chunk held in pc, once the row sums of its unit are all there.
+  auto complete = [&](const Chunk& k, int par, f32x16 (&pc)[kNB]) {
+    uint64_t lo = 0, hi = 0;
+#pragma unroll
+    for (int i = 0; i < kCopies; ++i) lo += seen[i];
+    bool ready = __all((int)(lo >> kCountShift) == k.nc);
+    if (!ready && patient) {
+      const uint64_t t0 = wall_clock64();
+      do {
+        __builtin_amdgcn_s_sleep(8);  // (a line that is asked for is slow to add to)
+        ask(k);
+        hi = peek(base_of(prm.high + ((int64_t)k.unit * kRows + wave * 32)), row8);
+        lo = 0;
+#pragma unroll
+        for (int i = 0; i < kCopies; ++i) lo += seen[i];
+        ready = __all((int)(lo >> kCountShift) + (int)(hi >> kCountShift) == k.nc);
+      } while (!ready && wall_clock64() - t0 < kPatience);
+      // Not every workgroup is running, or a row's sum is out of range: the scores of this workgroup are void from here on.
+      if (!ready) {
+        patient = false;
+        __hip_atomic_store(&prm.ctl->redo, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+      if (__any(hi != 0)) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+      if (!ready || (__any(hi != 0) && __hip_atomic_load(&prm.ctl->redo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)))
+        *in_lds<int>(lds0 + C::kOffBad) = 1;
+    }
+    auto whole = [](uint64_t v) {  // the sum without the count
+      return fmaf((float)((uint32_t)(v >> 32) & ((1u << (kCountShift - 32)) - 1)), 4294967296.f, (float)(uint32_t)v);
+    };
+    float L = fmaf(whole(lo), 1.f / kLowScale, 1.f);
+    if (__any(hi != 0)) L = fmaf(whole(hi), 1.f / kHighScale, L);
+    float w_row = __builtin_amdgcn_rcpf(L);
+    w_row = fmaf(fmaf(-L, w_row, 1.f), w_row, w_row);
+    const uint32_t wt = lds0 + C::kOffW + wave * 128;
+    *in_lds<float>(wt + row8 / 2) = w_row;
+    if (k.ci == 0) {
+      const int ln = lane_now();
+      float ms = (ln & 1) ? 0.f : (L - 1.f) * w_row;
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) ms += __shfl_xor(ms, o, 64);
+      if (ln == 0) *in_lds<float>(lds0 + C::kOffMass + (par * kWaves + wave) * 4) = ms;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    float w[16];
+#pragma unroll
+    for (int i4 = 0; i4 < 4; ++i4) {
+      const f32x4 v = *in_lds<const f32x4>(wt + 16 * g, 32 * i4);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) w[4 * i4 + e] = v[e];
+    }
+    float col[kNB];
+#pragma unroll
+    for (int kb = 0; kb < kNB; ++kb) {
+      float a = 0.f, b = 0.f;
+#pragma unroll
+      for (int i = 0; i < 16; i += 2) {
+        a = fmaf(pc[kb][i], w[i], a);
+        b = fmaf(pc[kb][i + 1], w[i + 1], b);
+      }
+      col[kb] = a + b;
+    }
+    const uint32_t cs = lds0 + C::kOffCs + (par * kWaves + wave) * kKeys * 4 + lane16 / 4;
+#pragma unroll
+    for (int j = 0; j < kNB; j += 2) {  // lanes below 32 get block j, the others block j+1
+      const auto sw = __builtin_amdgcn_permlane32_swap(as_u32(col[j]), as_u32(col[j + 1]), false, false);
+      const unsigned u0 = sw[0], u1 = sw[1];
+      *in_lds<float>(cs, j * 128) = as_f32(u0) + as_f32(u1);
+    }
+  };
+
+  // ---- prologue: the first two chunks' keys, the first chunk's rows and its first block of logits
+  settle();
+  Chunk cur = ahead, next = ahead, prev = ahead, done = ahead;
+  dma_start(cur, 0);
+  dma_k(0);
+  aim_q(cur);
+  uint32_t q_off = lane16;
+#pragma unroll
+  for (int ks = 0; ks < S; ++ks) load_q(ks, q_off);
+  if (mine > 1) {
+    ahead.ci += G;
+    settle();
+    dma_k(1);
+  }
+  next = ahead;
+  if (threadIdx.x < 32) *in_lds<float>(lds0 + C::kOffInf + threadIdx.x * 4) = -INFINITY;
+  if (threadIdx.x == 0) *in_lds<int>(lds0 + C::kOffBad) = 0;
+  for (int i = threadIdx.x; i < 2 * kWaves * kKeys; i += kThreads) *in_lds<float>(lds0 + C::kOffCs + i * 4) = 0.f;
+  if (threadIdx.x < 2 * kWaves) *in_lds<float>(lds0 + C::kOffMass + threadIdx.x * 4) = 0.f;
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  f32x16 pre, pa[kNB], pb[kNB];
+  auto first_block = [&](int par, const Chunk& k) {
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) fetch(par, i);
+    init(par, 0, k.P - k.ci * kKeys - r, pre);
+  };
+  first_block(0, cur);
+#pragma unroll
+  for (int n = 0; n < S; ++n) {
+    if (n + kAhead < S) fetch(0, n + kAhead);
+    mfma_step<bf16_t>(qf[n], kf[n % (kAhead + 1)], pre);
+  }
+#pragma unroll
+  for (int kb = 0; kb < kNB; ++kb) {
+    pa[kb] = f32x16{};
+    pb[kb] = f32x16{};
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  auto meet = [&]() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+
+  if (wave * 32 >= prm.rows) {  // no rows for this wave: it only helps to move keys and to add columns
+    for (int s = 0; s < mine; ++s) {
+      if (s + 2 < mine) {
+        ahead.ci += G;
+        settle();
+      }
+      dma_k((s + 2) % C::kRing);
+      asm volatile("s_waitcnt vmcnt(%0)" ::"i"(C::kMoves) : "memory");  // its part of chunk s+1
+      meet();
+      if (s >= 2) flush(done, s & 1 ^ 1, s);
+      done = prev;
+      prev = cur;
+      cur = next;
+      next = ahead;
+    }
+    meet();
+    if (mine >= 2) flush(done, mine & 1 ^ 1, mine);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    meet();
+    flush(prev, mine & 1, mine + 1);
+    return;
+  }
+
+  // Step s: chunk s is formed into pf (its first block of logits is in `pre`), chunk s-1, held in pc, is completed; the rows
+  // of chunk s+1 and the keys of chunk s+2 are asked for.  (At the end of the walk the last chunk is asked for again, so
+  // that the counts of outstanding accesses below hold in every step.)
+  auto step = [&](int s, int par, f32x16 (&pf)[kNB], f32x16 (&pc)[kNB]) {
+    dma_start(next, par ^ 1);
+    if (s + 2 < mine) {
+      ahead.ci += G;
+      settle();
+    }
+    dma_k((s + 2) % C::kRing);
+    aim_q(next);
+    const int left = cur.P - cur.ci * kKeys - r;  // keys of the chunk from this lane's on
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) fetch(par, S + i);
+    init(par, 1, left, pf[1]);
+#pragma unroll
+    for (int n = S; n < kNB * S; ++n) {
+      const int kb = n / S, ks = n % S;
+      if (n == kNB * S - 1) ask(prev);  // as late as an answer can be hidden: a sum that is asked for too early has to be asked for twice
+      if (n == (kNB - 1) * S) q_off = here(lane16);
+      if (n + kAhead < kNB * S) fetch(par, n + kAhead);
+      if (ks == S / 2 && kb + 1 < kNB) init(par, kb + 1, left, pf[kb + 1]);
+      mfma_step<bf16_t>(qf[ks], kf[n % (kAhead + 1)], pf[kb]);
+      expo(n - S - kLag, pre, pf);
+      if (kb == kNB - 1) load_q(ks, q_off);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    meet();
+    // Chunk s+1's keys were there a step ago (its rows' loads were waited for after them), its rows' references are there now:
+    // only this step's transfers of keys, the loads of ask() and those of the rows are younger.
+    asm volatile("s_waitcnt vmcnt(%0)" ::"i"(C::kMoves + kCopies + S) : "memory");
+    if (par) turn();
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) fetch(par ^ 1, i);
+    init(par ^ 1, 0, next.P - next.ci * kKeys - r, pre);
+    expo(kNB * S - S - kLag, pre, pf);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int n = 0; n < S; ++n) {
+      if (n + kAhead < S) fetch(par ^ 1, n + kAhead);
+      mfma_step<bf16_t>(qf[n], kf[n % (kAhead + 1)], pre);
+      expo(kNB * S - S - kLag + 1 + n, pre, pf);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int m = kNB * S - kLag + 1; m <= kNB * S; ++m) expo(m, pre, pf);
+    // The row sums asked for are waited for before this step's additions go out: accesses are counted in order.
+#pragma unroll
+    for (int i = 0; i < kCopies; ++i) asm volatile("" : "+v"(seen[i]));
+    if (s >= 2) flush(done, par ^ 1, s);
+    publish(cur);
+    if (s > 0) complete(prev, par, pc);
+    done = prev;
+    prev = cur;
+    cur = next;
+    next = ahead;
+  };
+  for (int s = 0; s < mine; s += 2) {
+    step(s, 0, pa, pb);
+    if (s + 1 < mine) step(s + 1, 1, pb, pa);
+  }
+  // ---- the last chunk
+  const int par = mine & 1;
+  meet();
+  if (mine >= 2) flush(done, par ^ 1, mine);
+  ask(prev);
+  if (par)
+    complete(prev, par, pa);
+  else
+    complete(prev, par, pb);
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");  // (also this workgroup's last transfers into LDS)
+  flush(prev, par, mine + 1);
+}
+
+template <int D>
+__global__ __launch_bounds__(kThreads, 2) void sweep_kernel(const SweepParams prm) {
+  extern __shared__ __attribute__((aligned(1024))) char lds[];
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
+  const bool run = prm.ctl->run;  // (if not, another call's sweep is running on this device)
+  if (threadIdx.x == 0) __hip_atomic_store(&prm.ctl->started[blockIdx.x], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (run) sweep_chunks<D>(prm, lds0);
+  if (__hip_atomic_load(&prm.ctl->redo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) sweep_redo<D>(prm, lds0);
+  // The lock is given back once every workgroup has been placed: from then on they cannot be kept waiting for each other.
+  if (run && blockIdx.x == 0 && threadIdx.x < 64) {
+    const uint64_t t0 = wall_clock64();
+    bool all;
+    do {
+      all = true;
+      for (int i = threadIdx.x; i < (int)gridDim.x; i += 64)
+        all = all && __hip_atomic_load(&prm.ctl->started[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    } while (!__all(all) && wall_clock64() - t0 < kPatience);
+    if (threadIdx.x == 0) __hip_atomic_store(&sweep_lock, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+}
+
+int cus() {
+  static int n = 0;
+  if (!n) {
+    int dev = 0, v = 0;
+    if (hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess) n = v;
+    if (n < 1) n = 256;
+  }
+  return n;
+}
+
+size_t pad256(size_t n) { return (n + 255) / 256 * 256; }
+
+struct Layout {
+  size_t control, low, high, start, mass, done, qpack, stats, bytes;  // offsets from the start of the area
+  Layout(const maskkv_desc* d, int nqg) {
+    const size_t units = (size_t)d->B * d->H * nqg;
+    control = 0;
+    low = pad256(sizeof(Control));
+    high = low + units * kCopies * kRows * sizeof(uint64_t);
+    start = high + units * kRows * sizeof(uint64_t);
+    mass = start + units * kRows * sizeof(float);
+    done = mass + units * sizeof(float);
+    qpack = pad256(done + units * sizeof(int));
+    stats = qpack + units * kRows * d->d * 2;
+    bytes = stats + units * kSpans * kRows * sizeof(float2);
+  }
+};
+
+// How a description would be swept: by how many workgroups, and whether that is faster than the two passes.
+//
+// At most one workgroup per compute unit, since all have to be resident.  Units whose chunks do not divide the workgroups evenly
+// straddle two steps, and the first of them then waits for the second: measured at 32 heads of dimension 128, a step of 256
+// workgroups takes 3.3 us where units are whole, and where they are not 4.0 us at 120 chunks per unit, 5.9 us at 160, 7.5 us at 235.
+// So the candidates are all compute units, or as many as hold whole units of some sequence, and the cheapest is taken.
+struct Plan {
+  int groups;
+  bool faster;
+  Plan(const maskkv_desc* d, const Lens& lens, int nqg) : groups(0), faster(false) {
+    const int n = cus();
+    int nc[MASKKV_MAX_BATCH], most = 0;
+    int64_t chunks = 0;
+    for (int b = 0; b < d->B; ++b) {
+      nc[b] = (lens.P[b] + kKeys - 1) / kKeys;
+      most = max(most, nc[b]);
+      chunks += (int64_t)nc[b] * d->H * nqg;
+    }
+    if (most == 0 || most > n || n > kMaxGroups || chunks > 0x7FFFFFFF) return;
+    double best = 0.0;
+    for (int i = -1; i < d->B; ++i) {
+      const int g = i < 0 ? n : nc[i] > 0 ? n / nc[i] * nc[i] : 0;
+      if (g < most) continue;
+      double steps = 0.0;
+      for (int b = 0; b < d->B; ++b) {
+        const double share = (double)nc[b] / g;
+        steps += share * (nc[b] > 0 && g % nc[b] != 0 ? 1.0 + fmin(1.3, 3.0 * share * share) : 1.0);
+      }
+      steps *= (double)d->H * nqg;
+      if (groups == 0 || steps < best) {
+        best = steps;
+        groups = g;
+      }
+    }
+    groups = (int)min((int64_t)groups, chunks);
+    // Microseconds.  A step: 2.72 (head_dim 64: 2.45), and more where more than 150 workgroups add to one row's sum; the two
+    // passes: 0.017 (0.010) per chunk; what either costs besides.  (32 heads, head_dim 128: 122 against 163 at 32k tokens, 75 / 85
+    // at 15k, 39 / 59 at 8k, but 103 / 95 at 17k; head_dim 64: 32 / 42 at 8k, 51 / 61 at 16k, but 57 / 53 at 12.5k, 140 / 105 at 32k.)
+    const bool wide = d->d == 128;
+    const double step = (wide ? 2.72 : 2.45) + max(0, most - 150) * (wide ? 0.007 : 0.0157);
+    faster = 14.0 + best * step < 23.0 + (double)chunks * (wide ? 0.0169 : 0.0101);
+  }
+};
+
+template <int D>
+int launch(const maskkv_desc* d, const SweepParams& prm, hipStream_t stream) {
+  const int lds_start = 2 * Cfg<D>::kKBytes;
+  static bool raised = false;
+  if (!raised) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&sweep_kernel<D>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, Cfg<D>::kLds);
+    if (e == hipSuccess)
+      e = hipFuncSetAttribute(reinterpret_cast<const void*>(&sweep_start_kernel<D, 8>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, lds_start);
+    if (e == hipSuccess)
+      e = hipFuncSetAttribute(reinterpret_cast<const void*>(&sweep_start_kernel<D, 2>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, lds_start);
+    if (e != hipSuccess) {
+      set_error("score: cannot raise dynamic LDS limit: %s", hipGetErrorString(e));
+      (void)hipGetLastError();
+      return MASKKV_EHIP;
+    }
+    raised = true;
+  }
+  const int units = prm.B * prm.H * prm.nqg;
+  if (units >= 128)
+    hipLaunchKernelGGL((sweep_start_kernel<D, 8>), dim3(units), dim3(kThreads), lds_start, stream, prm);
+  else
+    hipLaunchKernelGGL((sweep_start_kernel<D, 2>), dim3(units * 4), dim3(kThreads), lds_start, stream, prm);
+  if (int e = check_launch("score (sweep start)")) return e;
+  hipLaunchKernelGGL(sweep_kernel<D>, dim3(Plan(d, prm.lens, prm.nqg).groups), dim3(kThreads), Cfg<D>::kLds, stream, prm);
+  return check_launch("score (sweep)");
+}
+
+}  // namespace
+
+bool sweep_wanted(const maskkv_desc* d, const Lens& lens, int nqg) { return d->dtype == MASKKV_BF16 && Plan(d, lens, nqg).faster; }
+
+size_t sweep_workspace_bytes(const maskkv_desc* d, int nqg) { return Layout(d, nqg).bytes; }
+
+int launch_sweep(const maskkv_desc* d, const View& Q, const View& K, const Lens& lens, float scale, float* scores,
+                 int64_t score_stride, float* prompt_mass, float* group_sums, int64_t group_stride, int nqg, void* area,
+                 hipStream_t stream, const float** unit_mass) {
+  SweepParams prm;
+  prm.Q = Q;
+  prm.K = K;
+  prm.lens = lens;
+  prm.B = d->B;
+  prm.H = d->H;
+  prm.n_resp = d->n_resp;
+  prm.q_per_kv = query_heads_per_kv(d);
+  prm.n_qh = d->n_query;
+  prm.n_query = d->n_query * prm.q_per_kv;
+  prm.nqg = nqg;
+  prm.rows = ((prm.n_query + nqg - 1) / nqg + 31) / 32 * 32;  // (as even as they can be: 300 rows are 160 and 140)
+  int x = 0;
+  for (int b = 0; b < d->B; ++b) x += (lens.P[b] + kKeys - 1) / kKeys * d->H * nqg;
+  prm.chunks = x;
+  prm.c = scale * kLog2e;
+  const Layout l(d, nqg);
+  char* base = reinterpret_cast<char*>(area);
+  prm.ctl = reinterpret_cast<Control*>(base + l.control);
+  prm.spans_done = reinterpret_cast<int*>(base + l.done);
+  prm.stats = reinterpret_cast<float2*>(base + l.stats);
+  prm.low = reinterpret_cast<uint64_t*>(base + l.low);
+  prm.high = reinterpret_cast<uint64_t*>(base + l.high);
+  prm.start = reinterpret_cast<float*>(base + l.start);
+  prm.qpack = base + l.qpack;
+  prm.out = nqg == 1 ? scores : group_sums;
+  prm.out_stride = nqg == 1 ? score_stride : group_stride;
+  prm.mass = nqg == 1 ? prompt_mass : reinterpret_cast<float*>(base + l.mass);
+  *unit_mass = nqg == 1 ? nullptr : prm.mass;
+  return d->d == 128 ? launch<128>(d, prm, stream) : launch<64>(d, prm, stream);
+}
+
+}  // namespace maskkv
