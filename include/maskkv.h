@@ -165,7 +165,7 @@ int maskkv_score_static(const maskkv_desc* desc, const maskkv_tensor* Q_mask, co
 
 /* Workspace (DEVICE bytes) needed by maskkv_select: the candidates that the first
  * stage (one workgroup per 4096 prompt positions) hands to the per-head final stage, and their counts; 0 for
- * prompts of at most 4096 tokens.  256-byte alignment. */
+ * prompts of at most 16384 tokens (selected in one stage).  256-byte alignment. */
 int maskkv_select_workspace_bytes(const maskkv_desc* desc, size_t* bytes);
 
 /*

@@ -1,28 +1,25 @@
 // Score smoothing + per-head top-k (MaskKV Section 3.3: S_keep = argtopk(I, k_{l,h})), and the head-level
 // budget formula of Stage 2.
 //
-// Two stages, because one workgroup per head would leave most of the chip idle:
-//   chunk stage  one workgroup per 4096 prompt positions of a head: pools the scores, turns them into
-//                order-preserving 32-bit keys and writes, in ascending position order, every (key, position)
-//                whose key is at least t0, the k-th largest key of the chunk (k = the head's budget).  The
-//                head's k-th largest key tau is never below a chunk's k-th largest key (fewer than k keys of
-//                the whole head are above tau), so every key >= tau of every chunk - all members of the
-//                answer and all their ties - is among the candidates.
-//   final stage  one workgroup per head: exact selection over the candidates (larger key first, ties to the
-//                lower position), positions emitted in ascending order.
-// Prompts of at most one chunk skip the chunk stage: the final stage pools the scores itself.
+// Prompts of up to 16384 positions: one workgroup per head pools the scores into registers (order-preserving
+// 32-bit keys, up to 16 a thread), finds the exact cut and emits the positions in ascending order: one kernel.
+// Longer prompts take two stages, because the keys of a head no longer fit a workgroup's registers:
+//   chunk stage  one workgroup per 4096 prompt positions of a head: pools the scores and writes, in ascending
+//                position order, every (key, position) whose key is at least t0, a lower bound of the k-th
+//                largest key of the chunk (k = the head's budget).  The head's k-th largest key is never below a
+//                chunk's k-th largest key (fewer than k keys of the whole head are above it), so every member of
+//                the answer and all its ties are among the candidates.
+//   final stage  one workgroup per head: exact selection over the candidates.
 //
-// Selection inside a workgroup (both stages): range refinement.  The key range [lo, hi] is cut into at most 2048 equal bins,
-// an LDS histogram (votes of a wave for one bin are merged into one atomic) locates the bin that holds the
-// k-th largest key, and that bin becomes the range: at most three rounds reach a single key tau.  One wave
-// walks the bins (32 consecutive bins per lane, a wave scan, then the owning lane's own 32), so a round is
-// two barriers.  The kept set is "key > tau" plus the first (k - count_gt) entries with key == tau, written
-// in order with ballot/popcount prefix sums, each wave walking one contiguous slice.
+// What bounds all of this is latency, not bandwidth: the scores of 32 heads are 4 MB at most, and each kernel is a chain
+// of load, reduction, histogram, scan and ordered write with a barrier between each two.  So the chain is kept short:
+//   - range refinement: the key range [lo, hi] is cut into two bins per thread, an LDS histogram and one scan by
+//     all threads locate the bin that holds the k-th largest key; that bin becomes the range.
+//   - as soon as the bin holds at most 64 entries (after the first round, for scores without many ties) they are
+//     listed and ranked against each other by one wave, larger key first, ties to the lower position.  That gives
+//     a cut (key, position) and an entry is kept iff it does not come after the cut: ties need no further pass.
+//   - a bin that is a single key with more entries than that is refined over the positions in the same way.
 #include "kernels.hpp"
-
-#ifndef SEL_SLACK
-#define SEL_SLACK 64
-#endif
 
 namespace maskkv {
 
@@ -31,12 +28,11 @@ namespace {
 constexpr int kSelThreads = 1024;
 constexpr int kSelWaves = kSelThreads / 64;
 constexpr int kChunk = 4096;       // prompt positions per chunk-stage workgroup
-constexpr int kSelLdsCap = 32768;  // final stage: keys kept in LDS (128 KB) next to the histogram
-constexpr int kBins = 2048;
-constexpr int kBinsPerLane = kBins / 64;
-constexpr int kHistWords = kBins + kBins / kBinsPerLane;  // one pad word per 32 bins: conflict-free lane walks
-constexpr int kChunkSlack = SEL_SLACK;  // a chunk stops refining its threshold at this many keys in the bin
+constexpr int kSelLdsCap = 32768;  // final stage: candidates (keys, then positions) kept in LDS: 128 KB
+constexpr int kRankable = 64;      // entries that one wave ranks against each other
 constexpr int kMaxChunks = 1024;   // chunk offsets of a head are kept in LDS: prompts of up to 4 Mi tokens
+// Prompts that one workgroup selects alone.
+constexpr int kSinglePrompt = 16 * kSelThreads;
 
 struct SelectParams {
   Lens lens;
@@ -48,16 +44,9 @@ struct SelectParams {
   int32_t* idx;
   int32_t* cu;
   int64_t capacity;
-  int lds_words;       // final stage: keys that fit its dynamic LDS
   uint32_t* cand_key;  // [BH][max_chunks][kChunk] candidates of the chunk stage
   int32_t* cand_pos;   // [BH][max_chunks][kChunk]
   int32_t* cand_cnt;   // [BH][max_chunks] candidates per chunk
-};
-
-struct SelState {
-  uint32_t lo, hi;  // current key range
-  int krem;         // rank wanted inside it
-  int binpop;       // keys inside it
 };
 
 __device__ __forceinline__ uint32_t order_key(float v) {
@@ -79,77 +68,141 @@ __device__ __forceinline__ int wave_scan(int v, int identity, Op op) {
   return v;
 }
 
-__device__ __forceinline__ int wave_incl_scan(int v, int) {
+__device__ __forceinline__ int wave_incl_scan(int v) {
   return wave_scan(v, 0, [](int a, int b) { return a + b; });
 }
-
-// Bins are numbered from the top of the range (bin 0 holds the largest keys) and padded by one word per 32.
-__device__ __forceinline__ int hist_slot(int top_bin) { return top_bin + top_bin / kBinsPerLane; }
-
-// One histogram vote per lane; the lanes of a wave that vote for the bin of the first (then second) voting
-// lane are merged into one atomic each, the rest vote on their own.  Called by all 64 lanes.
-__device__ __forceinline__ void vote(int* hist, bool cand, int top_bin, int lane) {
-  uint64_t cmask = __ballot(cand);
-#pragma unroll
-  for (int it = 0; it < 2; ++it) {
-    if (!cmask) return;
-    const int leader = __ffsll((unsigned long long)cmask) - 1;
-    const int b0 = __builtin_amdgcn_readlane(top_bin, leader);
-    const bool mine = cand && top_bin == b0;
-    const uint64_t same = __ballot(mine);
-    if (lane == leader) atomicAdd(&hist[hist_slot(b0)], __popcll(same));
-    if (mine) cand = false;
-    cmask &= ~same;
-  }
-  if (cand) atomicAdd(&hist[hist_slot(top_bin)], 1);
+__device__ __forceinline__ uint32_t wave_min(uint32_t v) {
+  const int r = wave_scan((int)v, -1, [](int a, int b) { return (int)min((uint32_t)a, (uint32_t)b); });
+  return (uint32_t)__builtin_amdgcn_readlane(r, 63);
+}
+__device__ __forceinline__ uint32_t wave_max(uint32_t v) {
+  const int r = wave_scan((int)v, 0, [](int a, int b) { return (int)max((uint32_t)a, (uint32_t)b); });
+  return (uint32_t)__builtin_amdgcn_readlane(r, 63);
 }
 
-// Geometry of one refinement round over the key range [lo, hi].
-struct Round {
-  uint32_t lo;
-  int shift, nb;
-  __device__ __forceinline__ Round(uint32_t lo_, uint32_t hi_) : lo(lo_) {
-    const uint32_t width = hi_ - lo_;
-    shift = max(0, 32 - __clz(width) - 11);  // (width >> shift) < 2048
-    nb = (int)(width >> shift) + 1;
-  }
-  __device__ __forceinline__ int top_bin(uint32_t key) const { return nb - 1 - (int)((key - lo) >> shift); }
+// Entries in the order of the answer: larger key first, ties to the lower position.
+__device__ __forceinline__ uint64_t code_of(uint32_t key, uint32_t pos) { return (uint64_t)key << 32 | (uint32_t)~pos; }
+
+template <int THREADS>
+struct SelShared {
+  static constexpr int kWaves = THREADS / 64;
+  static constexpr int kBins = 2 * THREADS;
+  int hist[kBins];
+  uint32_t wmin[kWaves], wmax[kWaves];
+  int wtot[kWaves], wbase[kWaves], wsum[2][kWaves];
+  uint64_t list[kRankable];
+  int listed;
+  uint32_t lo, hi;
+  int krem, pop;
+  uint64_t cut;
 };
 
-// One wave, after all votes of a round: find the bin (from the top) that holds the krem-th largest key, make it
-// the new range, and leave the histogram zeroed for the next round.
-__device__ __forceinline__ void pick_bin(int* hist, const Round& rd, uint32_t hi, int krem, int lane, SelState* st) {
-  int h[kBinsPerLane];
-  int s = 0;
-  int* mine = hist + lane * (kBinsPerLane + 1);
+template <int THREADS>
+__device__ __forceinline__ void sel_clear(SelShared<THREADS>& s) {
+  reinterpret_cast<u32x2*>(s.hist)[threadIdx.x] = u32x2{0u, 0u};
+  if (threadIdx.x == 0) s.listed = 0;
+}
+
+// The current range [lo, hi] of values, the rank wanted inside it (from the largest) and how many entries it holds.
+struct Range {
+  uint32_t lo, hi;
+  int krem, pop;
+};
+
+// Narrow `g` until it holds at most `enough` entries or a single value.  `each(f)` calls f(value, valid) for the entries of
+// this thread.  All threads call this; the histogram is clear on entry and on return.
+template <int THREADS, typename Each>
+__device__ __forceinline__ void refine(SelShared<THREADS>& s, Range& g, int enough, Each&& each) {
+  constexpr int kBins = SelShared<THREADS>::kBins;
+  constexpr int kWaves = SelShared<THREADS>::kWaves;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  while (g.lo != g.hi && g.pop > enough) {
+    const uint32_t width = g.hi - g.lo;
+    const int shift = max(0, 32 - __clz(width) - (31 - __builtin_clz(kBins)));  // (width >> shift) < kBins
+    const int top = (int)(width >> shift);
+    // bins are numbered from the top of the range: bin 0 holds the largest values
+    each([&](uint32_t v, bool valid) {
+      if (valid && v >= g.lo && v <= g.hi) atomicAdd(&s.hist[top - (int)((v - g.lo) >> shift)], 1);
+    });
+    __syncthreads();
+    const u32x2 two = reinterpret_cast<u32x2*>(s.hist)[tid];
+    reinterpret_cast<u32x2*>(s.hist)[tid] = u32x2{0u, 0u};
+    const int h0 = (int)two[0], h1 = (int)two[1];
+    const int incl = wave_incl_scan(h0 + h1);
+    if (lane == 63) s.wtot[wave] = incl;
+    __syncthreads();
+    int above = incl - (h0 + h1);
 #pragma unroll
-  for (int j = 0; j < kBinsPerLane; ++j) {
-    h[j] = mine[j];
-    mine[j] = 0;
-    s += h[j];
-  }
-  const int incl = wave_incl_scan(s, lane);
-  int above = incl - s;
-  if (incl >= krem && above < krem) {  // exactly one lane owns the bin
-    int bsel = -1, pop = 0;
-#pragma unroll
-    for (int j = 0; j < kBinsPerLane; ++j) {
-      if (bsel < 0) {
-        if (above + h[j] >= krem) {
-          bsel = lane * kBinsPerLane + j;
-          pop = h[j];
-        } else {
-          above += h[j];
-        }
-      }
+    for (int w = 0; w < kWaves; ++w) {
+      const int t = s.wtot[w];
+      above += w < wave ? t : 0;
     }
-    const uint32_t nlo = rd.lo + ((uint32_t)(rd.nb - 1 - bsel) << rd.shift);
-    const uint32_t span = rd.shift == 0 ? 0u : ((1u << rd.shift) - 1u);
-    st->lo = nlo;
-    st->hi = (uint32_t)min((uint64_t)hi, (uint64_t)nlo + span);
-    st->krem = krem - above;
-    st->binpop = pop;
+    if (above < g.krem && above + h0 + h1 >= g.krem) {  // exactly one thread owns the bin
+      const bool second = above + h0 < g.krem;
+      const int bin = 2 * tid + (second ? 1 : 0);
+      const uint32_t nlo = g.lo + ((uint32_t)(top - bin) << shift);
+      const uint32_t span = shift == 0 ? 0u : ((1u << shift) - 1u);
+      s.lo = nlo;
+      s.hi = (uint32_t)min((uint64_t)g.hi, (uint64_t)nlo + span);
+      s.krem = g.krem - above - (second ? h0 : 0);
+      s.pop = second ? h1 : h0;
+    }
+    __syncthreads();
+    g = Range{s.lo, s.hi, s.krem, s.pop};
   }
+}
+
+// Key range of the workgroup's entries from every thread's own (one barrier).
+template <int THREADS>
+__device__ __forceinline__ void key_range(SelShared<THREADS>& s, uint32_t kmin, uint32_t kmax, uint32_t& lo, uint32_t& hi) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  kmin = wave_min(kmin);
+  kmax = wave_max(kmax);
+  if (lane == 0) {
+    s.wmin[wave] = kmin;
+    s.wmax[wave] = kmax;
+  }
+  __syncthreads();
+  lo = s.wmin[0];
+  hi = s.wmax[0];
+#pragma unroll
+  for (int w = 1; w < SelShared<THREADS>::kWaves; ++w) {
+    lo = min(lo, s.wmin[w]);
+    hi = max(hi, s.wmax[w]);
+  }
+}
+
+// The code of the k-th entry in the order of the answer, or one that separates the first k from the rest (1 <= k <= n);
+// `each(f)` calls f(key, position, valid) for the entries of this thread.
+template <int THREADS, typename Each>
+__device__ __forceinline__ uint64_t exact_cut(SelShared<THREADS>& s, uint32_t lo, uint32_t hi, int k, int n, uint32_t last_pos,
+                                              Each&& each) {
+  Range g{lo, hi, k, n};
+  refine(s, g, kRankable, [&](auto&& f) { each([&](uint32_t key, uint32_t, bool valid) { f(key, valid); }); });
+  if (g.krem == g.pop) return (uint64_t)g.lo << 32;  // the whole bin is kept
+  uint64_t from = (uint64_t)g.lo << 32, to = (uint64_t)g.hi << 32 | 0xFFFFFFFFu;
+  if (g.pop > kRankable) {  // one key, many entries: refine over their positions (lowest first: ~position descending)
+    const uint32_t tau = g.lo;
+    g.lo = ~last_pos;
+    g.hi = 0xFFFFFFFFu;
+    refine(s, g, kRankable, [&](auto&& f) { each([&](uint32_t key, uint32_t pos, bool valid) { f(~pos, valid && key == tau); }); });
+    from = (uint64_t)tau << 32 | g.lo;
+    to = (uint64_t)tau << 32 | g.hi;
+    if (g.krem == g.pop) return from;
+  }
+  each([&](uint32_t key, uint32_t pos, bool valid) {
+    const uint64_t code = code_of(key, pos);
+    if (valid && code >= from && code <= to) s.list[atomicAdd(&s.listed, 1)] = code;  // (g.pop <= kRankable of them)
+  });
+  __syncthreads();
+  if (threadIdx.x < 64) {
+    const uint64_t mine = (int)threadIdx.x < g.pop ? s.list[threadIdx.x] : 0u;
+    int better = 0;
+    for (int i = 0; i < g.pop; ++i) better += s.list[i] > mine ? 1 : 0;
+    if ((int)threadIdx.x < g.pop && better == g.krem - 1) s.cut = mine;  // (codes are distinct)
+  }
+  __syncthreads();
+  return s.cut;
 }
 
 // Pooled score of position j of a head (mean: in-range terms added from the lowest index upwards in fp32, one
@@ -167,58 +220,204 @@ __device__ __forceinline__ uint32_t pooled_key(const float* x, int j, int P, int
   return order_key(v);
 }
 
-// Keys of the four consecutive positions j0 .. j0+3 (0 for positions past the prompt: below every real key).
-__device__ __forceinline__ void pooled_keys4(const float* x, int j0, int P, int r, int mode, uint32_t (&key)[4]) {
-  if (r <= 3 && mode == MASKKV_POOL_MEAN) {
-    // ten loads serve four windows of up to seven terms
-    float v[10];
+// Keys of G groups of four consecutive positions, group i at j0 + i * step (0 for positions past the prompt).  A group's
+// windows overlap, so it is loaded as whole 16-byte pieces (R rounded up to a piece on either side), all groups before the
+// first use; only groups that touch an end of the prompt are read again, element by element.  Positions outside the prompt
+// take the neutral element of the pooling, which leaves the sum (resp. the maximum) of the in-range terms as it is.
+// R: radius of the window, or (not FIXED) a bound of it.  P >= 4.
+template <int R, bool FIXED, int G>
+__device__ __forceinline__ void pool_groups(const float* x, int j0, int step, int P, int r, int mode, uint32_t (&key)[4 * G]) {
+  typedef __attribute__((ext_vector_type(4), aligned(4))) float f32x4u;
+  constexpr int A = (R + 3) / 4 * 4;
+  constexpr int N = 4 + 2 * A;
+  if (FIXED) r = R;
+  float v[G][N];
 #pragma unroll
-    for (int i = 0; i < 10; ++i) {
-      const int j = j0 - 3 + i;
-      v[i] = (j >= 0 && j < P) ? x[j] : 0.f;
+  for (int i = 0; i < G; ++i)
+#pragma unroll
+    for (int p = 0; p < N / 4; ++p) {
+      const int at = min(max(j0 + i * step - A + 4 * p, 0), P - 4);
+      const f32x4u w = *reinterpret_cast<const f32x4u*>(x + at);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[i][4 * p + e] = w[e];
+    }
+#pragma unroll
+  for (int i = 0; i < G; ++i) {
+    const int g0 = j0 + i * step;
+    const bool inner = g0 >= A && g0 + 4 + A <= P;
+    if (!inner) {
+      const float neutral = mode == MASKKV_POOL_MAX ? __builtin_nanf("") : 0.f;  // (fmaxf passes over a NaN)
+#pragma unroll
+      for (int t = 0; t < N; ++t) {
+        const int j = g0 - A + t;
+        v[i][t] = (j >= 0 && j < P) ? x[j] : neutral;
+      }
     }
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const int j = j0 + e;
-      key[e] = 0u;
-      if (j < P) {
-        const int lo = max(0, j - r), hi = min(P - 1, j + r);
-        float acc = 0.f;
-        bool first = true;
+      const int j = g0 + e;
+      float acc;
+      if (mode == MASKKV_POOL_MAX) {
+        acc = __builtin_nanf("");
 #pragma unroll
-        for (int t = -3; t <= 3; ++t) {
-          const int jj = j + t;
-          if (jj >= lo && jj <= hi) {  // in-range terms only, lowest index first
-            acc = first ? v[e + 3 + t] : __fadd_rn(acc, v[e + 3 + t]);
-            first = false;
-          }
-        }
-        key[e] = order_key(__fdiv_rn(acc, (float)(hi - lo + 1)));
+        for (int t = -R; t <= R; ++t)
+          if (FIXED || (t >= -r && t <= r)) acc = fmaxf(acc, v[i][e + A + t]);
+      } else {
+        acc = 0.f;  // (0 + x is x but for the sign of a zero, which the key does not see)
+#pragma unroll
+        for (int t = -R; t <= R; ++t)
+          if (FIXED || (t >= -r && t <= r)) acc = __fadd_rn(acc, v[i][e + A + t]);
+        if (R > 0) acc = __fdiv_rn(acc, (float)(min(P - 1, j + r) - max(0, j - r) + 1));
       }
+      key[4 * i + e] = j < P ? order_key(acc) : 0u;
     }
-  } else {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) key[e] = j0 + e < P ? pooled_key(x, j0 + e, P, r, mode) : 0u;
   }
 }
 
-__device__ __forceinline__ uint32_t wave_min(uint32_t v) {
-  const int r = wave_scan((int)v, -1, [](int a, int b) { return (int)min((uint32_t)a, (uint32_t)b); });
-  return (uint32_t)__builtin_amdgcn_readlane(r, 63);
-}
-__device__ __forceinline__ uint32_t wave_max(uint32_t v) {
-  const int r = wave_scan((int)v, 0, [](int a, int b) { return (int)max((uint32_t)a, (uint32_t)b); });
-  return (uint32_t)__builtin_amdgcn_readlane(r, 63);
+template <int G>
+__device__ __forceinline__ void pooled_keys(const float* x, int j0, int step, int P, int window, int mode, uint32_t (&key)[4 * G]) {
+  const int r = (window - 1) / 2;
+  if (P >= 4 && r == 3 && mode == MASKKV_POOL_MEAN) {
+    pool_groups<3, true, G>(x, j0, step, P, r, MASKKV_POOL_MEAN, key);
+  } else if (P >= 4 && r <= 8) {  // group by group: registers of one group's wide windows only
+#pragma unroll 1
+    for (int i = 0; i < G; ++i) {
+      uint32_t k4[4];
+      if (r <= 4)
+        pool_groups<4, false, 1>(x, j0 + i * step, 0, P, r, mode, k4);
+      else
+        pool_groups<8, false, 1>(x, j0 + i * step, 0, P, r, mode, k4);
+#pragma unroll
+      for (int u = 0; u < G; ++u)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (u == i) key[4 * u + e] = k4[e];
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < G; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int j = j0 + i * step + e;
+        key[4 * i + e] = j < P ? pooled_key(x, j, P, r, mode) : 0u;
+      }
+  }
 }
 
-// ---- chunk stage: grid (BH, max_chunks).  Eight waves per SIMD, i.e. at most 64 registers: two of these 1024-thread
-// workgroups then fit a compute unit, which halves the rounds a batch with more chunks than compute units needs.
+// Kept rows of the heads before `bh` (the sum of their clamped budgets): this thread's part, to be added up over the workgroup.
+template <int THREADS>
+__device__ __forceinline__ int rows_before(const SelectParams& prm, int bh) {
+  int part = 0;
+  for (int i = threadIdx.x; i < bh; i += THREADS) part += min(max(prm.budgets[i], 0), prm.lens.P[i / prm.H]);
+  return part;
+}
+
+template <int THREADS>
+__device__ __forceinline__ int take_base(const SelShared<THREADS>& s) {
+  int base = 0;
+#pragma unroll
+  for (int w = 0; w < SelShared<THREADS>::kWaves; ++w) base += s.wbase[w];
+  return base;
+}
+
+// ---- one workgroup per head: grid (BH), 4 * G keys a thread.  32 heads of 4096 positions: 16.0 us before (keys in LDS, one
+// wave walking the histogram, refinement to a single key, two passes for the ordered output), 6.6 us now; 8192
+// positions 20.0 us before (two stages) and 8.5 now; 256 heads of 4096 ... 16384 positions 38 and 15 us.
+template <int THREADS, int G>
+__global__ __launch_bounds__(THREADS) void select_head_kernel(const SelectParams prm) {
+  __shared__ SelShared<THREADS> s;
+  const int bh = blockIdx.x;
+  const int b = bh / prm.H;
+  const int P = prm.lens.P[b];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int kh = min(max(prm.budgets[bh], 0), P);
+
+  uint32_t key[4 * G];
+  if (kh > 0)
+    pooled_keys<G>(prm.scores + (int64_t)bh * prm.score_stride, 4 * tid, 4 * THREADS, P, prm.window, prm.mode, key);
+  sel_clear(s);
+  const int part = wave_incl_scan(rows_before<THREADS>(prm, bh));
+  if (lane == 63) s.wbase[wave] = part;
+  auto valid = [&](int i, int e) { return 4 * (tid + i * THREADS) + e < P; };
+  uint32_t kmin = 0xFFFFFFFFu, kmax = 0u;
+  if (kh > 0) {
+#pragma unroll
+    for (int i = 0; i < G; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (valid(i, e)) {
+          kmin = min(kmin, key[4 * i + e]);
+          kmax = max(kmax, key[4 * i + e]);
+        }
+  }
+  uint32_t lo, hi;
+  key_range(s, kmin, kmax, lo, hi);
+  const int base = take_base(s);
+  if (tid == 0) {
+    prm.cu[bh] = base;
+    if (bh == prm.BH - 1) prm.cu[prm.BH] = base + kh;
+  }
+  if (kh == 0) return;
+
+  const uint64_t cut = exact_cut(s, lo, hi, kh, P, (uint32_t)(P - 1), [&](auto&& f) {
+#pragma unroll
+    for (int i = 0; i < G; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) f(key[4 * i + e], (uint32_t)(4 * (tid + i * THREADS) + e), valid(i, e));
+  });
+
+  // ---- ordered output: the groups of all threads follow one another, so every group has a scan of its own; the counts of
+  // two groups (at most 4 * THREADS <= 4096 each) share a word
+  auto kept = [&](int i, int e) {
+    return valid(i, e) && code_of(key[4 * i + e], (uint32_t)(4 * (tid + i * THREADS) + e)) >= cut;
+  };
+  constexpr int kPairs = (G + 1) / 2;
+  int own[kPairs], incl[kPairs];
+#pragma unroll
+  for (int p = 0; p < kPairs; ++p) own[p] = 0;
+#pragma unroll
+  for (int i = 0; i < G; ++i)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) own[i / 2] += kept(i, e) ? 1 << (16 * (i % 2)) : 0;
+#pragma unroll
+  for (int p = 0; p < kPairs; ++p) {
+    incl[p] = wave_incl_scan(own[p]);
+    if (lane == 63) s.wsum[p][wave] = incl[p];
+  }
+  __syncthreads();
+  const int64_t room = prm.capacity - base;  // rows of idx this head may write
+  const int rows = (int)min((int64_t)kh, max(room, (int64_t)0));
+  int done = 0;  // rows of the groups before
+#pragma unroll
+  for (int p = 0; p < kPairs; ++p) {
+    int before = incl[p] - own[p], total = 0;
+#pragma unroll
+    for (int w = 0; w < SelShared<THREADS>::kWaves; ++w) {
+      const int t = s.wsum[p][w];
+      before += w < wave ? t : 0;
+      total += t;
+    }
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+      const int i = 2 * p + half;
+      if (i < G) {
+        int at = done + ((before >> (16 * half)) & 0xFFFF);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (kept(i < G ? i : 0, e)) {
+            if (at < rows) prm.idx[base + at] = 4 * (tid + i * THREADS) + e;
+            ++at;
+          }
+        done += (total >> (16 * half)) & 0xFFFF;
+      }
+    }
+  }
+}
+
+// ---- chunk stage: grid (BH, max_chunks).  Eight waves per SIMD, i.e. at most 64 registers: two workgroups then fit a
+// compute unit.  32 heads of 32768 positions: 10.8 us before, 7.0 now.
 __global__ __launch_bounds__(kSelThreads, 8) void select_chunk_kernel(const SelectParams prm) {
-  __shared__ int hist[kHistWords];
-  __shared__ uint32_t wmin[kSelWaves], wmax[kSelWaves];
-  __shared__ int wsum[kSelWaves];
-  __shared__ SelState st;
-
+  __shared__ SelShared<kSelThreads> s;
   const int bh = blockIdx.x;
   const int b = bh / prm.H;
   const int P = prm.lens.P[b];
@@ -229,9 +428,9 @@ __global__ __launch_bounds__(kSelThreads, 8) void select_chunk_kernel(const Sele
   const int n = min(kChunk, P - c0);
   const int kc = min(kh, n);
 
-  for (int i = tid; i < kHistWords; i += kSelThreads) hist[i] = 0;
   uint32_t key[4];
-  pooled_keys4(prm.scores + (int64_t)bh * prm.score_stride, c0 + 4 * tid, P, (prm.window - 1) / 2, prm.mode, key);
+  pooled_keys<1>(prm.scores + (int64_t)bh * prm.score_stride, c0 + 4 * tid, 0, P, prm.window, prm.mode, key);
+  sel_clear(s);
   const int nmine = min(max(n - 4 * tid, 0), 4);  // this thread's real keys: key[0 .. nmine)
   uint32_t kmin = 0xFFFFFFFFu, kmax = 0u;
 #pragma unroll
@@ -240,55 +439,31 @@ __global__ __launch_bounds__(kSelThreads, 8) void select_chunk_kernel(const Sele
       kmin = min(kmin, key[e]);
       kmax = max(kmax, key[e]);
     }
-  kmin = wave_min(kmin);
-  kmax = wave_max(kmax);
-  if (lane == 0) {
-    wmin[wave] = kmin;
-    wmax[wave] = kmax;
-  }
-  __syncthreads();
-  uint32_t lo = wmin[0], hi = wmax[0];
+  uint32_t lo, hi;
+  key_range(s, kmin, kmax, lo, hi);
+  // A lower bound of the chunk's kc-th largest key: refinement until the bin that holds it has few keys left (every key
+  // of that bin becomes a candidate, so the bound need not be tight; the final stage finds the cut exactly).
+  Range g{lo, hi, kc, n};
+  if (kc < n)
+    refine(s, g, kRankable, [&](auto&& f) {
 #pragma unroll
-  for (int w = 1; w < kSelWaves; ++w) {
-    lo = min(lo, wmin[w]);
-    hi = max(hi, wmax[w]);
-  }
-  // ---- a lower bound of the chunk's kc-th largest key: range refinement over the keys in registers, until the
-  // bin that holds it has few keys left (every key of that bin becomes a candidate, so the bound need not be tight;
-  // the final stage finds the head's threshold exactly)
-  if (kc < n) {
-    int krem = kc, binpop = n;
-    for (int round = 0; round < 4 && lo != hi && binpop > kChunkSlack; ++round) {
-      const Round rd(lo, hi);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const bool cand = e < nmine && key[e] >= lo && key[e] <= hi;
-        vote(hist, cand, cand ? rd.top_bin(key[e]) : 0, lane);
-      }
-      __syncthreads();
-      if (wave == 0) pick_bin(hist, rd, hi, krem, lane, &st);
-      __syncthreads();
-      lo = st.lo;
-      hi = st.hi;
-      krem = st.krem;
-      binpop = st.binpop;
-    }
-  }
-  const uint32_t t0 = lo;  // kc >= n: the smallest key, everything is a candidate
+      for (int e = 0; e < 4; ++e) f(key[e], e < nmine);
+    });
+  const uint32_t t0 = g.lo;  // kc >= n: the smallest key, everything is a candidate
 
   // ---- every key >= t0, in position order
   int mine = 0;
 #pragma unroll
   for (int e = 0; e < 4; ++e) mine += (e < nmine && key[e] >= t0) ? 1 : 0;
-  const int incl = wave_incl_scan(mine, lane);
-  if (lane == 63) wsum[wave] = incl;
+  const int incl = wave_incl_scan(mine);
+  if (lane == 63) s.wsum[0][wave] = incl;
   __syncthreads();
   int before = incl - mine;
   int total = 0;
 #pragma unroll
   for (int w = 0; w < kSelWaves; ++w) {
-    const int v = wsum[w];
-    if (w < wave) before += v;
+    const int v = s.wsum[0][w];
+    before += w < wave ? v : 0;
     total += v;
   }
   const int64_t ws = ((int64_t)bh * prm.max_chunks + blockIdx.y) * kChunk;
@@ -303,56 +478,61 @@ __global__ __launch_bounds__(kSelThreads, 8) void select_chunk_kernel(const Sele
   if (tid == 0) prm.cand_cnt[(int64_t)bh * prm.max_chunks + blockIdx.y] = total;
 }
 
-// ---- final stage: grid (BH).  POOL: the keys are the pooled scores of a prompt of at most one chunk;
-// otherwise they are the chunk stage's candidates.
-template <bool POOL>
+// ---- final stage: grid (BH), over the chunk stage's candidates.  32 heads of 32768 positions and 171 ... 341 kept rows:
+// 14.0 us before, 8.4 now.
 __global__ __launch_bounds__(kSelThreads) void select_final_kernel(const SelectParams prm) {
-  extern __shared__ uint32_t lds_keys[];
-  __shared__ int hist[kHistWords];
+  extern __shared__ uint32_t lds_words[];
+  __shared__ SelShared<kSelThreads> s;
   __shared__ int coff[kMaxChunks + 1];  // candidates before chunk c
-  __shared__ int wsum[kSelWaves][2];
-  __shared__ uint32_t wmin[kSelWaves], wmax[kSelWaves];
-  __shared__ SelState st;
 
   const int bh = blockIdx.x;
   const int b = bh / prm.H;
-  const int h = bh - b * prm.H;
   const int P = prm.lens.P[b];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int kh = min(max(prm.budgets[bh], 0), P);
-  const int nch = POOL ? 1 : (P + kChunk - 1) / kChunk;  // (POOL: the prompt is one flat list)
+  const int nch = (P + kChunk - 1) / kChunk;
   const int64_t head_ws = (int64_t)bh * prm.max_chunks * kChunk;
 
-  // ---- offset of this head's slice (exclusive prefix sum of the clamped budgets) and of every chunk's
-  // candidates (inclusive scan of the chunk counts): wave scans now, wave totals combined after the barrier
-  int part = 0;
-  for (int i = tid; i < bh; i += kSelThreads) part += min(max(prm.budgets[i], 0), prm.lens.P[i / prm.H]);
-  part = wave_incl_scan(part, lane);
-  const int cnt = (!POOL && kh > 0 && tid < nch) ? prm.cand_cnt[(int64_t)bh * prm.max_chunks + tid] : 0;
-  const int cincl = wave_incl_scan(cnt, lane);
-  if (lane == 63) {
-    wsum[wave][0] = part;
-    wsum[wave][1] = cincl;
-  }
-  for (int i = tid; i < kHistWords; i += kSelThreads) hist[i] = 0;
-  __syncthreads();
-  int base = 0, cbefore = 0;
+  // The first candidates of this wave's first chunk are asked for along with the counts that say how many there are: a
+  // chunk's list has room for all its positions, so the addresses are good whatever the count.
+  constexpr int kEarly = 5;
+  uint32_t ekey[kEarly], epos[kEarly];
+  if (kh > 0 && wave < nch) {
+    const int64_t at = head_ws + (int64_t)wave * kChunk + lane;
 #pragma unroll
-  for (int w = 0; w < kSelWaves; ++w) {
-    base += wsum[w][0];
-    if (w < wave) cbefore += wsum[w][1];
+    for (int u = 0; u < kEarly; ++u) {
+      ekey[u] = prm.cand_key[at + 64 * u];
+      epos[u] = (uint32_t)prm.cand_pos[at + 64 * u];
+    }
   }
+  sel_clear(s);
+  const int part = wave_incl_scan(rows_before<kSelThreads>(prm, bh));
+  const int cnt = (kh > 0 && tid < nch) ? prm.cand_cnt[(int64_t)bh * prm.max_chunks + tid] : 0;
+  const int cincl = wave_incl_scan(cnt);
+  if (lane == 63) {
+    s.wbase[wave] = part;
+    s.wtot[wave] = cincl;
+  }
+  __syncthreads();
+  const int base = take_base(s);
   if (tid == 0) {
     prm.cu[bh] = base;
     if (bh == prm.BH - 1) prm.cu[prm.BH] = base + kh;
     coff[0] = 0;
   }
   if (kh == 0) return;
-  if (!POOL && tid < nch) coff[tid + 1] = cbefore + cincl;
+  int cbefore = 0;
+#pragma unroll
+  for (int w = 0; w < kSelWaves; ++w) {
+    const int t = s.wtot[w];
+    cbefore += w < wave ? t : 0;
+  }
+  if (tid < nch) coff[tid + 1] = cbefore + cincl;
   __syncthreads();
 
-  const int n = POOL ? P : coff[nch];
-  const bool in_lds = n <= prm.lds_words;
+  const int n = coff[nch];
+  const bool in_lds = n <= kSelLdsCap;           // the keys sit at lds_words[0 .. n)
+  const bool pos_in_lds = 2 * n <= kSelLdsCap;   // the positions at lds_words[n .. 2n)
   // candidate e of the head sits in chunk c = the last one with coff[c] <= e
   auto slot_of = [&](int e) -> int64_t {
     int a = 0, z = nch;  // coff[a] <= e < coff[z]
@@ -365,134 +545,72 @@ __global__ __launch_bounds__(kSelThreads) void select_final_kernel(const SelectP
     }
     return head_ws + (int64_t)a * kChunk + (e - coff[a]);
   };
-  auto key_at = [&](int e) -> uint32_t { return in_lds ? lds_keys[e] : prm.cand_key[slot_of(e)]; };
+  auto key_at = [&](int e) -> uint32_t { return in_lds ? lds_words[e] : prm.cand_key[slot_of(e)]; };
+  auto pos_at = [&](int e) -> int { return pos_in_lds ? (int)lds_words[n + e] : prm.cand_pos[slot_of(e)]; };
 
-  // ---- the keys (into LDS when they fit) and their range
+  // ---- the chunks' lists into one (in LDS when they fit), and the range of the keys
   uint32_t kmin = 0xFFFFFFFFu, kmax = 0u;
-  uint32_t pkey[4] = {0u, 0u, 0u, 0u};  // POOL: this thread's four consecutive keys (n <= 4096)
-  if (POOL) {
-    pooled_keys4(prm.scores + (int64_t)bh * prm.score_stride, 4 * tid, P, (prm.window - 1) / 2, prm.mode, pkey);
+  for (int c = wave; c < nch; c += kSelWaves) {
+    const int first = coff[c], m = coff[c + 1] - first;
+    const int64_t at = head_ws + (int64_t)c * kChunk;
+    auto take = [&](int i, uint32_t k, uint32_t p) {
+      if (in_lds) lds_words[first + i] = k;
+      if (pos_in_lds) lds_words[n + first + i] = p;
+      kmin = min(kmin, k);
+      kmax = max(kmax, k);
+    };
+    int from = 0;
+    if (c == wave) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
-      if (4 * tid + e < n) {
-        lds_keys[4 * tid + e] = pkey[e];
-        kmin = min(kmin, pkey[e]);
-        kmax = max(kmax, pkey[e]);
-      }
-  } else {
-    // four independent loads in flight per thread (the chunks' candidate lists are read as one flat list)
-    for (int e0 = 0; e0 < n; e0 += 4 * kSelThreads) {
-      uint32_t kk[4];
+      for (int u = 0; u < kEarly; ++u)
+        if (64 * u + lane < m) take(64 * u + lane, ekey[u], epos[u]);
+      from = 64 * kEarly;
+    }
+    for (int i0 = from; i0 < m; i0 += 256) {  // four independent loads in flight per lane
+      uint32_t k[4], p[4];
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        const int e = e0 + u * kSelThreads + tid;
-        kk[u] = e < n ? prm.cand_key[slot_of(e)] : 0u;
+        const int i = min(i0 + 64 * u + lane, m - 1);
+        k[u] = prm.cand_key[at + i];
+        p[u] = pos_in_lds ? (uint32_t)prm.cand_pos[at + i] : 0u;
       }
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int e = e0 + u * kSelThreads + tid;
-        if (e < n) {
-          if (in_lds) lds_keys[e] = kk[u];
-          kmin = min(kmin, kk[u]);
-          kmax = max(kmax, kk[u]);
-        }
-      }
+      for (int u = 0; u < 4; ++u)
+        if (i0 + 64 * u + lane < m) take(i0 + 64 * u + lane, k[u], p[u]);
     }
   }
-  kmin = wave_min(kmin);
-  kmax = wave_max(kmax);
-  if (lane == 0) {
-    wmin[wave] = kmin;
-    wmax[wave] = kmax;
-  }
-  __syncthreads();
-  uint32_t lo = wmin[0], hi = wmax[0];
-#pragma unroll
-  for (int w = 1; w < kSelWaves; ++w) {
-    lo = min(lo, wmin[w]);
-    hi = max(hi, wmax[w]);
-  }
-  int krem = kh;
+  uint32_t lo, hi;
+  key_range(s, kmin, kmax, lo, hi);
 
-  // ---- range refinement until a single key remains (three rounds at most; the bound is only a guard)
-  for (int round = 0; round < 4 && lo != hi; ++round) {
-    const Round rd(lo, hi);
-    for (int e0 = 0; e0 < n; e0 += kSelThreads) {
-      const int e = e0 + tid;
-      const uint32_t key = e < n ? key_at(e) : 0u;
-      const bool cand = e < n && key >= lo && key <= hi;
-      vote(hist, cand, cand ? rd.top_bin(key) : 0, lane);
-    }
-    __syncthreads();
-    if (wave == 0) pick_bin(hist, rd, hi, krem, lane, &st);
-    __syncthreads();
-    lo = st.lo;
-    hi = st.hi;
-    krem = st.krem;
-  }
-  const uint32_t tau = lo;
-  const int need_eq = krem;  // how many entries equal to tau are kept (lowest positions first)
+  // (an entry's number in the list stands for its position: the list is in position order)
+  const uint64_t cut = exact_cut(s, lo, hi, kh, n, (uint32_t)(n - 1), [&](auto&& f) {
+    for (int e = tid; e < n; e += kSelThreads) f(key_at(e), (uint32_t)e, true);
+  });
 
-  // ---- ordered emit: wave w owns entries [w*seg, (w+1)*seg)
+  // ---- ordered output: wave w owns entries [w*seg, (w+1)*seg)
   const int seg = ((n + kSelWaves - 1) / kSelWaves + 63) / 64 * 64;
   const int s0 = wave * seg;
   const int s1 = min(n, s0 + seg);
-  int cgt = 0, ceq = 0;
-  for (int e0 = s0; e0 < s1; e0 += 64) {
-    const int e = e0 + lane;
-    const uint32_t kv = e < s1 ? key_at(e) : 0u;
-    cgt += __popcll(__ballot(e < s1 && kv > tau));
-    ceq += __popcll(__ballot(e < s1 && kv == tau));
-  }
-  if (lane == 0) {
-    wsum[wave][0] = cgt;
-    wsum[wave][1] = ceq;
-  }
+  auto kept = [&](int e) { return e < s1 && code_of(key_at(e), (uint32_t)e) >= cut; };
+  int count = 0;
+  for (int e0 = s0; e0 < s1; e0 += 64) count += __popcll(__ballot(kept(e0 + lane)));
+  if (lane == 0) s.wsum[0][wave] = count;
   __syncthreads();
-  int gt_before = 0, eq_before = 0;
+  int before = 0;
 #pragma unroll
   for (int w = 0; w < kSelWaves; ++w) {
-    if (w < wave) {
-      gt_before += wsum[w][0];
-      eq_before += wsum[w][1];
-    }
+    const int t = s.wsum[0][w];
+    before += w < wave ? t : 0;
   }
   const int64_t room = prm.capacity - base;  // rows of idx this head may write
   const int rows = (int)min((int64_t)kh, max(room, (int64_t)0));
-  // The kept candidates' positions sit in global memory.  When there is room behind the keys, the kept entry
-  // numbers first go to an LDS list in output order, and the positions are then fetched with independent loads
-  // (one per thread) instead of one dependent load per step of a wave's slice.
-  const bool listed = !POOL && in_lds && n + kh <= prm.lds_words;
-  uint32_t* kept = lds_keys + n;
   for (int e0 = s0; e0 < s1; e0 += 64) {
     const int e = e0 + lane;
-    const uint32_t kv = e < s1 ? key_at(e) : 0u;
-    const bool gt = e < s1 && kv > tau;
-    const bool eq = e < s1 && kv == tau;
-    const uint64_t mgt = __ballot(gt);
-    const uint64_t meq = __ballot(eq);
-    const uint64_t below = (1ull << lane) - 1ull;
-    const int eq_rank = eq_before + __popcll(meq & below);
-    if (gt || (eq && eq_rank < need_eq)) {
-      const int pos = gt_before + __popcll(mgt & below) + min(eq_rank, need_eq);
-      if (pos < rows) {
-        if (POOL)
-          prm.idx[base + pos] = e;
-        else if (listed)
-          kept[pos] = (uint32_t)e;
-        else
-          prm.idx[base + pos] = prm.cand_pos[slot_of(e)];
-      }
-    }
-    gt_before += __popcll(mgt);
-    eq_before += __popcll(meq);
-  }
-  if (listed) {
-    __syncthreads();
-    for (int rr = tid; rr < rows; rr += kSelThreads) {
-      const int pos = prm.cand_pos[slot_of((int)kept[rr])];
-      prm.idx[base + rr] = pos;
-    }
+    const bool k = kept(e);
+    const uint64_t mask = __ballot(k);
+    const int at = before + __popcll(mask & ((1ull << lane) - 1ull));
+    if (k && at < rows) prm.idx[base + at] = pos_at(e);
+    before += __popcll(mask);
   }
 }
 
@@ -505,19 +623,27 @@ struct BudgetParams {
 };
 
 // k_{l,h} = floor(alpha*k_l + (1-alpha) * N_h * k_l * P_h / sum_j P_j), P_h = mass_h / n_query.
-__global__ __launch_bounds__(256) void head_budgets_kernel(const BudgetParams prm) {
-  __shared__ float red[256];
+// The sum is a tree over 256 threads' terms, halving the distance.  Up to 64 heads need one wave (THREADS 64): the
+// upper halves would only add zeros, and the rest of the same tree needs neither LDS nor barriers.
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void head_budgets_kernel(const BudgetParams prm) {
   const int b = blockIdx.x;
   float s = 0.f;
-  for (int h = threadIdx.x; h < prm.H; h += 256) s += prm.mass[b * prm.H + h] / (float)prm.n_query;
-  red[threadIdx.x] = s;
-  __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
+  for (int h = threadIdx.x; h < prm.H; h += THREADS) s += prm.mass[b * prm.H + h] / (float)prm.n_query;
+  if (THREADS > 64) {
+    __shared__ float red[THREADS];
+    red[threadIdx.x] = s;
     __syncthreads();
+    for (int o = THREADS / 2; o >= 64; o >>= 1) {
+      if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
+      __syncthreads();
+    }
+    s = red[threadIdx.x & 63];
   }
-  const float total = red[0];
-  for (int h = threadIdx.x; h < prm.H; h += 256) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
+  const float total = __shfl(s, 0, 64);
+  for (int h = threadIdx.x; h < prm.H; h += THREADS) {
     // a sequence without any prompt mass (empty prompt) has no preference: every head gets k_l
     const float p_hat = total > 0.f ? (prm.mass[b * prm.H + h] / (float)prm.n_query) / total : 1.f / (float)prm.H;
     const float v = prm.alpha * (float)prm.k_l + (1.f - prm.alpha) * (float)prm.H * (float)prm.k_l * p_hat;
@@ -540,7 +666,7 @@ int64_t select_max_prompt() { return (int64_t)kMaxChunks * kChunk; }
 
 // The (key, position) candidates that the chunk stage hands to the final stage, and their count per chunk.
 size_t select_workspace_bytes(const maskkv_desc* d) {
-  if (select_chunks(d) <= 1) return 0;  // single-chunk prompts are selected in one kernel
+  if (d->P_max <= kSinglePrompt) return 0;
   return (size_t)select_cand_slots(d) * (sizeof(uint32_t) + sizeof(int32_t)) + select_count_bytes(d);
 }
 
@@ -564,16 +690,25 @@ int launch_select(const maskkv_desc* d, const Lens& lens, const float* scores, i
   prm.cand_key = reinterpret_cast<uint32_t*>(workspace);
   prm.cand_pos = reinterpret_cast<int32_t*>(prm.cand_key + select_cand_slots(d));
   prm.cand_cnt = prm.cand_pos + select_cand_slots(d);
-  prm.lds_words = (int)min((int64_t)kSelLdsCap, ((int64_t)max(d->P_max, 1) + 63) / 64 * 64);
-  const size_t dyn = (size_t)prm.lds_words * sizeof(uint32_t);
+  // The fewest keys a thread that the prompt allows: the chain's length is what counts, and four waves start and meet at a
+  // barrier sooner than sixteen.
+  if (d->P_max <= kSinglePrompt) {
+    const dim3 grid(prm.BH);
+    if (d->P_max <= 1024)
+      hipLaunchKernelGGL((select_head_kernel<256, 1>), grid, dim3(256), 0, stream, prm);
+    else if (d->P_max <= 4096)
+      hipLaunchKernelGGL((select_head_kernel<1024, 1>), grid, dim3(1024), 0, stream, prm);
+    else if (d->P_max <= 8192)
+      hipLaunchKernelGGL((select_head_kernel<1024, 2>), grid, dim3(1024), 0, stream, prm);
+    else
+      hipLaunchKernelGGL((select_head_kernel<1024, 4>), grid, dim3(1024), 0, stream, prm);
+    return check_launch("select (one stage)");
+  }
+  constexpr size_t dyn = (size_t)kSelLdsCap * sizeof(uint32_t);
   static bool granted = false;  // one-time opt-in to more than the default dynamic LDS size
   if (!granted) {
-    const size_t want = (size_t)kSelLdsCap * sizeof(uint32_t);
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&select_final_kernel<false>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)want);
-    if (e == hipSuccess)
-      e = hipFuncSetAttribute(reinterpret_cast<const void*>(&select_final_kernel<true>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)want);
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&select_final_kernel),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn);
     if (e != hipSuccess) {
       set_error("select: cannot raise dynamic LDS limit: %s", hipGetErrorString(e));
       (void)hipGetLastError();
@@ -581,20 +716,19 @@ int launch_select(const maskkv_desc* d, const Lens& lens, const float* scores, i
     }
     granted = true;
   }
-  if (prm.max_chunks <= 1) {  // every prompt fits one chunk: pool, select and emit in a single kernel
-    hipLaunchKernelGGL((select_final_kernel<true>), dim3(prm.BH), dim3(kSelThreads), dyn, stream, prm);
-    return check_launch("select (single stage)");
-  }
   hipLaunchKernelGGL(select_chunk_kernel, dim3(prm.BH, prm.max_chunks), dim3(kSelThreads), 0, stream, prm);
   if (int e = check_launch("select (chunk stage)")) return e;
-  hipLaunchKernelGGL((select_final_kernel<false>), dim3(prm.BH), dim3(kSelThreads), dyn, stream, prm);
+  hipLaunchKernelGGL(select_final_kernel, dim3(prm.BH), dim3(kSelThreads), dyn, stream, prm);
   return check_launch("select (final stage)");
 }
 
 int launch_head_budgets(const maskkv_desc* d, const float* prompt_mass, int32_t k_l, float alpha, int32_t* budgets,
                         hipStream_t stream) {
   BudgetParams prm{d->H, d->n_query * query_heads_per_kv(d), prompt_mass, k_l, alpha, budgets};
-  hipLaunchKernelGGL(head_budgets_kernel, dim3(d->B), dim3(256), 0, stream, prm);
+  if (d->H <= 64)
+    hipLaunchKernelGGL(head_budgets_kernel<64>, dim3(d->B), dim3(64), 0, stream, prm);
+  else
+    hipLaunchKernelGGL(head_budgets_kernel<256>, dim3(d->B), dim3(256), 0, stream, prm);
   return check_launch("head_budgets");
 }
 
