@@ -2,77 +2,46 @@
 // (MaskKV Section 3.1 layer forward equation; appendix: AttnOut_m = sum_j alpha_mj V_j), and the
 // same attention over the un-evicted sequence.
 //
-// Flash-style single pass with an online softmax.  One workgroup = 8 waves = 256 queries of one (b, h)
-// sharing every staged K/V tile (4 waves at bf16 head_dim 64); each wave owns 32 queries.  The logits are formed transposed (keys on the MFMA row axis, queries on
-// the column axis), so a lane owns one query: its running max / sum stay in the lane and the
-// probabilities it holds are already laid out as the B operand of O^T = V^T P^T.  V tiles are written
-// to LDS transposed so that the A operand of that product is read with 8/16-byte LDS loads.
-// The key axis is the concatenation of two segments (packed cache rows, then a strided view); long key
-// axes are split across workgroups and merged by a second small kernel.
-#include "kernels.hpp"
+// Flash-style single pass with an online softmax.  The logits are formed transposed (keys on the MFMA row axis, queries on
+// the column axis), so a lane owns one query: its running max / sum stay in the lane and the probabilities it holds are
+// already laid out as the B operand of O^T = V^T P^T.  The key axis is the concatenation of two segments (packed cache rows,
+// then a strided view); long key axes are split across workgroups and merged by a second small kernel.
+//
+// Here: the tiled kernel for fp32 (8 waves = 256 queries of one (b, h) sharing every staged K/V tile, V written to LDS
+// transposed so that the A operand of the second product is read with 16-byte LDS loads), the narrow kernel for small bf16
+// launches, the merge and the rules that choose.  attend_tiles.hip: the tiled kernel for bf16.
+#include "attend.hpp"
 
 namespace maskkv {
 
 namespace {
 
-// Launches of fewer 128-query tiles than this take the narrow kernel (measured at 256 queries and about 512 keys
-// per head: 32 heads 17 vs 30 us, 64 heads 30 vs 31 us, 96 heads 44 vs 32 us for narrow vs tiled).
-constexpr int kNarrowBelow = 144;
-constexpr float kLazyBump = 8.f;  // log2 of the largest probability tolerated before the running reference is raised
+constexpr int kUnits = 256;  // compute units
 
-template <typename T, int D>
+template <int D>
 struct AttCfg {
-  static constexpr int kRowB = D * (int)sizeof(T);
+  static constexpr int kEB = 4;  // bytes per element
+  static constexpr int kRowB = D * kEB;
   static constexpr int kRowP = kRowB + 16;
   static constexpr int kSteps = kRowB / 32;
   static constexpr int kTK = (kRowB <= 256) ? 64 : 32;
   static constexpr int kNKB = kTK / 32;
   static constexpr int kPiecesPerRow = kRowB / 16;
-  // Waves (32 queries each) that share a K/V tile: eight where a thread still moves whole 16-byte pieces of K
-  // and pairs of V rows, i.e. everywhere but bf16 at head_dim 64.
-  static constexpr int kWaves = (sizeof(T) == 2 && D == 64) ? 4 : 8;
+  static constexpr int kWaves = 8;  // waves (32 queries each) that share a K/V tile
   static constexpr int kThreads = kWaves * 64;
   static constexpr int kQPerBlock = kWaves * 32;
   static constexpr int kPieces = kTK * kRowB / 16 / kThreads;
   static constexpr int kSV = kTK + 4;  // elements per transposed-V row (padding keeps LDS reads conflict-free)
-  // bf16: every group of 32 transposed-V rows is shifted by a further 16 bytes.  The fragment reads of a wave stay
-  // inside one group and are unaffected; the transposing stores of a wave touch one row of every group, which
-  // without the shift fall on the same LDS banks four at a time.
-  static constexpr int kVGroupShift = sizeof(T) == 2 ? 16 : 0;
   static constexpr int kDB = D / 32;
   static constexpr int kKtBytes = kTK * kRowP;
-  static constexpr int kVtBytes = D * kSV * (int)sizeof(T) + (D / 32) * kVGroupShift;
+  static constexpr int kVtBytes = D * kSV * kEB;
   static constexpr int kLds = 2 * (kKtBytes + kVtBytes);  // K and V^T tiles, double-buffered
 };
 
-struct AttendParams {
-  View Q, K2, V2, O;
-  Lens lens;
-  const char* Kc;
-  const char* Vc;
-  const int32_t* cu;
-  int64_t capacity;
-  int H, BH, n_resp, full, n_splits;
-  int q_per_kv;  // query heads per key/value head
-  int n_q;       // query rows per key/value head = q_per_kv * n_resp
-  float c;  // scale * log2(e)
-  float* lse;
-  const int32_t* order;  // [BH] heads by descending key count (compressed call of the tiled kernel), or null
-  float* part_o;     // [BH][n_splits][n_q][D]
-  float2* part_ml;   // [BH][n_splits][n_q]
-};
-
-struct KeySpace {
-  const char* a_k;  // packed segment base (row 0 of this head), rows contiguous
-  const char* a_v;
-  int len_a;
-  int len_b;
-};
-
-template <typename T, int D>
+template <int D>
 __device__ __forceinline__ void load_kv(const AttendParams& prm, const KeySpace& ks, int b, int h, int key0, int klast,
-                                        u32x4 (&kr)[AttCfg<T, D>::kPieces], u32x4 (&vr)[AttCfg<T, D>::kPieces]) {
-  using C = AttCfg<T, D>;
+                                        u32x4 (&kr)[AttCfg<D>::kPieces], u32x4 (&vr)[AttCfg<D>::kPieces]) {
+  using C = AttCfg<D>;
 #pragma unroll
   for (int i = 0; i < C::kPieces; ++i) {
     const int p = threadIdx.x + i * C::kThreads;
@@ -83,15 +52,7 @@ __device__ __forceinline__ void load_kv(const AttendParams& prm, const KeySpace&
       kr[i] = *reinterpret_cast<const u32x4*>(src + col * 16);
     }
     {
-      int row, col;
-      if (sizeof(T) == 2) {  // item = (key pair, 16-byte slice); pieces 2i and 2i+1 are the pair's two rows
-        const int item = threadIdx.x + (i / 2) * C::kThreads;
-        row = 2 * (item / C::kPiecesPerRow) + (i & 1);
-        col = item % C::kPiecesPerRow;
-      } else {
-        row = p / C::kPiecesPerRow;
-        col = p % C::kPiecesPerRow;
-      }
+      const int row = p / C::kPiecesPerRow, col = p % C::kPiecesPerRow;
       const int j = min(key0 + row, klast);
       const char* src = j < ks.len_a ? ks.a_v + (int64_t)j * C::kRowB : prm.V2.row(b, h, j - ks.len_a);
       vr[i] = *reinterpret_cast<const u32x4*>(src + col * 16);
@@ -99,10 +60,10 @@ __device__ __forceinline__ void load_kv(const AttendParams& prm, const KeySpace&
   }
 }
 
-template <typename T, int D>
-__device__ __forceinline__ void store_kv(char* kt, char* vt, const u32x4 (&kr)[AttCfg<T, D>::kPieces],
-                                         const u32x4 (&vr)[AttCfg<T, D>::kPieces]) {
-  using C = AttCfg<T, D>;
+template <int D>
+__device__ __forceinline__ void store_kv(char* kt, char* vt, const u32x4 (&kr)[AttCfg<D>::kPieces],
+                                         const u32x4 (&vr)[AttCfg<D>::kPieces]) {
+  using C = AttCfg<D>;
 #pragma unroll
   for (int i = 0; i < C::kPieces; ++i) {
     const int p = threadIdx.x + i * C::kThreads;
@@ -110,37 +71,18 @@ __device__ __forceinline__ void store_kv(char* kt, char* vt, const u32x4 (&kr)[A
     *reinterpret_cast<u32x4*>(kt + row * C::kRowP + col * 16) = kr[i];
   }
   uint32_t* vt32 = reinterpret_cast<uint32_t*>(vt);
-  if (sizeof(T) == 2) {
-    // vt[e][key] as bf16: a 32-bit word holds keys (2*pair, 2*pair+1) of one head-dim element
 #pragma unroll
-    for (int i = 0; i < C::kPieces / 2; ++i) {
-      const int item = threadIdx.x + i * C::kThreads;
-      const int pair = item / C::kPiecesPerRow, col = item % C::kPiecesPerRow;
-      const u32x4 a = vr[2 * i], bq = vr[2 * i + 1];
+  for (int i = 0; i < C::kPieces; ++i) {
+    const int p = threadIdx.x + i * C::kThreads;
+    const int row = p / C::kPiecesPerRow, col = p % C::kPiecesPerRow;
 #pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        const uint32_t lo = (a[w] & 0xFFFFu) | (bq[w] << 16);
-        const uint32_t hi = (a[w] >> 16) | (bq[w] & 0xFFFF0000u);
-        const int row = col * 8 + 2 * w;
-        const int word = row * (C::kSV / 2) + (row / 32) * (C::kVGroupShift / 4) + pair;  // (row is even)
-        vt32[word] = lo;
-        vt32[word + C::kSV / 2] = hi;
-      }
-    }
-  } else {
-#pragma unroll
-    for (int i = 0; i < C::kPieces; ++i) {
-      const int p = threadIdx.x + i * C::kThreads;
-      const int row = p / C::kPiecesPerRow, col = p % C::kPiecesPerRow;
-#pragma unroll
-      for (int w = 0; w < 4; ++w) vt32[(col * 4 + w) * C::kSV + row] = vr[i][w];
-    }
+    for (int w = 0; w < 4; ++w) vt32[(col * 4 + w) * C::kSV + row] = vr[i][w];
   }
 }
 
-template <typename T, int D>
-__global__ __launch_bounds__((AttCfg<T, D>::kThreads)) void attend_kernel(const AttendParams prm) {
-  using C = AttCfg<T, D>;
+template <int D>
+__global__ __launch_bounds__((AttCfg<D>::kThreads)) void attend_kernel(const AttendParams prm) {
+  using C = AttCfg<D>;
   extern __shared__ __attribute__((aligned(16))) char att_lds[];  // two buffers of (K tile, V^T tile)
 
   // Workgroup numbers that are congruent modulo 8 run on the same XCD and share its L2.  The query tiles of
@@ -199,11 +141,11 @@ __global__ __launch_bounds__((AttCfg<T, D>::kThreads)) void attend_kernel(const 
   // chain of tiles, so the memory latency of each request has to hide behind two tiles of arithmetic).
   u32x4 kra[C::kPieces], vra[C::kPieces], krb[C::kPieces], vrb[C::kPieces];
   // Tile t is computed from LDS buffer t&1 while tile t+1 is written to the other one: one barrier per tile.
-  if (ntiles > 0) load_kv<T, D>(prm, ks, b, h, j0, j1 - 1, kra, vra);
-  if (ntiles > 1) load_kv<T, D>(prm, ks, b, h, j0 + C::kTK, j1 - 1, krb, vrb);
+  if (ntiles > 0) load_kv<D>(prm, ks, b, h, j0, j1 - 1, kra, vra);
+  if (ntiles > 1) load_kv<D>(prm, ks, b, h, j0 + C::kTK, j1 - 1, krb, vrb);
   if (ntiles > 0) {
-    store_kv<T, D>(att_lds, att_lds + C::kKtBytes, kra, vra);
-    if (ntiles > 2) load_kv<T, D>(prm, ks, b, h, j0 + 2 * C::kTK, j1 - 1, kra, vra);
+    store_kv<D>(att_lds, att_lds + C::kKtBytes, kra, vra);
+    if (ntiles > 2) load_kv<D>(prm, ks, b, h, j0 + 2 * C::kTK, j1 - 1, kra, vra);
   }
   __syncthreads();
 
@@ -214,8 +156,8 @@ __global__ __launch_bounds__((AttCfg<T, D>::kThreads)) void attend_kernel(const 
     const char* vt = kt + C::kKtBytes;
     if (t + 1 < ntiles) {  // the other buffer's readers (tile t-1) passed the barrier that ended the previous step
       char* nk = att_lds + ((t + 1) & 1) * (C::kKtBytes + C::kVtBytes);
-      store_kv<T, D>(nk, nk + C::kKtBytes, kr, vr);
-      if (t + 3 < ntiles) load_kv<T, D>(prm, ks, b, h, key0 + 3 * C::kTK, j1 - 1, kr, vr);
+      store_kv<D>(nk, nk + C::kKtBytes, kr, vr);
+      if (t + 3 < ntiles) load_kv<D>(prm, ks, b, h, key0 + 3 * C::kTK, j1 - 1, kr, vr);
     }
 
     // S^T = K Q^T for this tile
@@ -226,7 +168,7 @@ __global__ __launch_bounds__((AttCfg<T, D>::kThreads)) void attend_kernel(const 
 #pragma unroll
       for (int st = 0; st < C::kSteps; ++st) {
         const u32x4 kf = *reinterpret_cast<const u32x4*>(kt + (kb * 32 + r) * C::kRowP + st * 32 + g * 16);
-        mfma_step<T>(kf, qf[st], s[kb]);
+        mfma_step<float>(kf, qf[st], s[kb]);
       }
       const int nvalid = j1 - (key0 + kb * 32);
       if (nvalid < 32) {
@@ -269,43 +211,22 @@ __global__ __launch_bounds__((AttCfg<T, D>::kThreads)) void attend_kernel(const 
     l += psum;
 
     // O^T += V^T P^T
-    if (sizeof(T) == 2) {
 #pragma unroll
-      for (int kb = 0; kb < C::kNKB; ++kb)
+    for (int kb = 0; kb < C::kNKB; ++kb)
 #pragma unroll
-        for (int tp = 0; tp < 2; ++tp) {
-          u32x4 pf;
+      for (int qd = 0; qd < 4; ++qd) {
+        u32x4 pf;
 #pragma unroll
-          for (int w = 0; w < 4; ++w)
-            pf[w] = pack_bf16x2(s[kb][8 * tp + 2 * w], s[kb][8 * tp + 2 * w + 1]);
-#pragma unroll
-          for (int db = 0; db < C::kDB; ++db) {
-            const char* rowp = vt + ((db * 32 + r) * C::kSV + kb * 32 + 16 * tp + 4 * g) * 2 + db * C::kVGroupShift;
-            const u32x2 lo = *reinterpret_cast<const u32x2*>(rowp);
-            const u32x2 hi = *reinterpret_cast<const u32x2*>(rowp + 16);
-            const u32x4 vf = {lo[0], lo[1], hi[0], hi[1]};
-            mfma_step<T>(vf, pf, o[db]);
-          }
+        for (int w = 0; w < 4; ++w) {
+          const float pv = s[kb][4 * qd + w];
+          pf[w] = as_u32(pv);
         }
-    } else {
 #pragma unroll
-      for (int kb = 0; kb < C::kNKB; ++kb)
-#pragma unroll
-        for (int qd = 0; qd < 4; ++qd) {
-          u32x4 pf;
-#pragma unroll
-          for (int w = 0; w < 4; ++w) {
-            const float pv = s[kb][4 * qd + w];
-            pf[w] = as_u32(pv);
-          }
-#pragma unroll
-          for (int db = 0; db < C::kDB; ++db) {
-            const u32x4 vf =
-                *reinterpret_cast<const u32x4*>(vt + ((db * 32 + r) * C::kSV + kb * 32 + 8 * qd + 4 * g) * 4);
-            mfma_step<T>(vf, pf, o[db]);
-          }
+        for (int db = 0; db < C::kDB; ++db) {
+          const u32x4 vf = *reinterpret_cast<const u32x4*>(vt + ((db * 32 + r) * C::kSV + kb * 32 + 8 * qd + 4 * g) * 4);
+          mfma_step<float>(vf, pf, o[db]);
         }
-    }
+      }
     __syncthreads();  // tile t+1 is visible; every wave is done with tile t
   };
   for (int t = 0; t < ntiles; t += 2) {
@@ -325,14 +246,7 @@ __global__ __launch_bounds__((AttCfg<T, D>::kThreads)) void attend_kernel(const 
         const int e = db * 32 + 8 * qd + 4 * g;
         const float v0 = o[db][4 * qd] * inv, v1 = o[db][4 * qd + 1] * inv;
         const float v2 = o[db][4 * qd + 2] * inv, v3 = o[db][4 * qd + 3] * inv;
-        if (sizeof(T) == 2) {
-          u32x2 w;
-          w[0] = pack_bf16x2(v0, v1);
-          w[1] = pack_bf16x2(v2, v3);
-          *reinterpret_cast<u32x2*>(orow + e * 2) = w;
-        } else {
-          *reinterpret_cast<float4*>(orow + e * 4) = make_float4(v0, v1, v2, v3);
-        }
+        *reinterpret_cast<float4*>(orow + e * 4) = make_float4(v0, v1, v2, v3);
       }
     if (prm.lse && g == 0) prm.lse[(int64_t)bh * prm.n_q + q] = (m + __log2f(l_tot)) * kLn2;
   } else {
@@ -356,8 +270,9 @@ __global__ __launch_bounds__((AttCfg<T, D>::kThreads)) void attend_kernel(const 
 // split the key axis: wave w takes the 32-key blocks w, w+4, ... on its own - K fragments straight from
 // global memory into registers, V through a wave-private transposed LDS tile, no workgroup barrier in the
 // loop - and the four partial (O, m, l) are merged through LDS at the end.  Two blocks per wave are kept in
-// flight.  Workgroups of one head are given indices that are congruent modulo 8, which places them on one
-// XCD, so the head's K/V rows are fetched into one L2 only.
+// flight.  Every XCD (workgroup numbers that are congruent modulo 8) takes one run of (head, query tile) pairs, so that a
+// head's K/V rows are fetched into one or two L2s and four heads still reach all eight XCDs (4 heads x 1792 queries: 23.7 us
+// with a head on one XCD, 12.6 now).
 constexpr int kNarrowVS = 36;      // bf16 elements per transposed-V row: 32 keys + padding
 constexpr int kNarrowShift = 16;   // bytes by which every group of 32 rows is shifted further (as in the tiled kernel)
 
@@ -382,9 +297,10 @@ __global__ __launch_bounds__((NarrowCfg<D, NW>::kThreads)) void attend_narrow_ke
   extern __shared__ __attribute__((aligned(16))) char smem[];
 
   const int nqt = (prm.n_q + 31) / 32;
-  const int id = blockIdx.x;
-  const int bh = (id / (8 * nqt)) * 8 + id % 8;
-  const int qt = (id / 8) % nqt;
+  // eight runs of consecutive (head, query tile) pairs, one per XCD
+  const int pair = (blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
+  const int bh = pair / nqt;
+  const int qt = pair % nqt;
   if (bh >= prm.BH) return;
   const int b = bh / prm.H;
   const int h = bh % prm.H;
@@ -643,15 +559,18 @@ __global__ __launch_bounds__(kOrderThreads) void attend_order_kernel(const int32
 }
 
 // Queries per workgroup of the tiled kernel for this description.
-int tiled_queries(const maskkv_desc* d) {
-  return (d->dtype == MASKKV_BF16 && d->d == 64) ? AttCfg<bf16_t, 64>::kQPerBlock : AttCfg<bf16_t, 128>::kQPerBlock;
+int tiled_queries(const maskkv_desc* d, bool full) {
+  if (d->dtype != MASKKV_BF16) return AttCfg<128>::kQPerBlock;
+  return attend_tiles_queries((int64_t)d->B * d->H, d->n_resp * query_heads_per_kv(d), full);
 }
 
 int attend_splits(const maskkv_desc* d, bool full) {
   if (!full) return 1;
-  const int64_t qtiles = ((int64_t)d->n_resp * query_heads_per_kv(d) + tiled_queries(d) - 1) / tiled_queries(d);
+  const int per_block = tiled_queries(d, full);
+  const int64_t qtiles = ((int64_t)d->n_resp * query_heads_per_kv(d) + per_block - 1) / per_block;
   const int64_t blocks = qtiles * d->B * d->H;
-  int64_t s = (256 + blocks - 1) / blocks;  // one workgroup per compute unit, a single round (measured best)
+  // one workgroup per compute unit, a single round (bf16: 4 heads x 7 tiles of queries are 252 workgroups, not 280)
+  int64_t s = d->dtype == MASKKV_BF16 ? kUnits / blocks : (kUnits + blocks - 1) / blocks;
   const int64_t by_len = ((int64_t)d->P_max + d->n_resp + 511) / 512;
   if (s > by_len) s = by_len;
   if (s > 64) s = 64;
@@ -659,11 +578,21 @@ int attend_splits(const maskkv_desc* d, bool full) {
   return (int)s;
 }
 
-// The narrow kernel is used when the tiled kernel would launch fewer workgroups than there are compute units.
+// The narrow kernel is used where its workgroups of 32 queries are all resident at once and fast: one per compute unit at
+// head_dim 128, about two at 64 (measured, narrow against tiled, us a call without the tiled kernel's ordering: head_dim 128 and
+// 256 queries, 32 heads 11.8 / 15.6, 64 heads 22.2 / 16; 32 heads x 512 queries x 1536 keys 43 / 28; 4 heads x 1792 queries
+// 14 / 17; head_dim 64, 512 workgroups 9.5 / 10.2).
 bool attend_is_narrow(const maskkv_desc* d, bool full) {
   if (full || d->dtype != MASKKV_BF16) return false;
-  const int64_t qtiles = ((int64_t)d->n_resp * query_heads_per_kv(d) + 127) / 128;
-  return qtiles * d->B * d->H < kNarrowBelow;
+  const int64_t qtiles = ((int64_t)d->n_resp * query_heads_per_kv(d) + 31) / 32;
+  return qtiles * d->B * d->H <= (d->d == 128 ? kUnits : 9 * kUnits / 4);
+}
+
+// Heads are only put in order where not every workgroup of the tiled kernel starts at once.
+bool attend_is_ordered(const maskkv_desc* d, bool full) {
+  if (full || attend_is_narrow(d, full)) return false;
+  const int per_block = tiled_queries(d, full);
+  return ((int64_t)d->n_resp * query_heads_per_kv(d) + per_block - 1) / per_block * d->B * d->H > kUnits;
 }
 
 template <int D, int NW>
@@ -681,15 +610,16 @@ int launch_attend_narrow(const AttendParams& prm, hipStream_t stream) {
     raised = true;
   }
   const int nqt = (prm.n_q + 31) / 32;
-  const int groups = (prm.BH + 7) / 8 * 8 * nqt;
+  const int groups = (prm.BH * nqt + 7) / 8 * 8;
   hipLaunchKernelGGL((attend_narrow_kernel<D, NW>), dim3(groups), dim3(C::kThreads), C::kLds, stream, prm);
   return check_launch("attend (narrow)");
 }
 
 template <typename T, int D>
 int launch_attend_t(const AttendParams& prm, int B, hipStream_t stream) {
-  using C = AttCfg<T, D>;
-  const int64_t qtiles = (prm.n_q + C::kQPerBlock - 1) / C::kQPerBlock;
+  using C = AttCfg<D>;
+  const int per_block = sizeof(T) == 2 ? attend_tiles_queries((int64_t)B * prm.H, prm.n_q, prm.full) : C::kQPerBlock;
+  const int64_t qtiles = (prm.n_q + per_block - 1) / per_block;
   const int64_t units = ((int64_t)B * prm.H * prm.n_splits + 7) / 8 * 8;  // (head, split) pairs, whole rounds of XCDs
   if (units * qtiles > 0x7FFFFFFF) {
     set_error("attend: %lld workgroups exceed the launch limit", (long long)(units * qtiles));
@@ -700,20 +630,24 @@ int launch_attend_t(const AttendParams& prm, int B, hipStream_t stream) {
                        prm.n_resp, const_cast<int32_t*>(prm.order));
     if (int e = check_launch("attend (order)")) return e;
   }
-  static bool raised = false;  // one-time opt-in to more than the default dynamic LDS size
-  if (C::kLds > 48 * 1024 && !raised) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attend_kernel<T, D>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, C::kLds);
-    if (e != hipSuccess) {
-      set_error("attend: cannot raise dynamic LDS limit: %s", hipGetErrorString(e));
-      (void)hipGetLastError();
-      return MASKKV_EHIP;
+  if constexpr (sizeof(T) == 2) {
+    if (int e = launch_attend_tiles(prm, D, per_block, stream)) return e;
+  } else {
+    static bool raised = false;  // one-time opt-in to more than the default dynamic LDS size
+    if (C::kLds > 48 * 1024 && !raised) {
+      const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attend_kernel<D>),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, C::kLds);
+      if (e != hipSuccess) {
+        set_error("attend: cannot raise dynamic LDS limit: %s", hipGetErrorString(e));
+        (void)hipGetLastError();
+        return MASKKV_EHIP;
+      }
+      raised = true;
     }
-    raised = true;
+    hipLaunchKernelGGL((attend_kernel<D>), dim3((unsigned)(units * qtiles)), dim3(C::kThreads), C::kLds, stream,
+                       prm);
+    if (int e = check_launch("attend")) return e;
   }
-  hipLaunchKernelGGL((attend_kernel<T, D>), dim3((unsigned)(units * qtiles)), dim3(C::kThreads), C::kLds, stream,
-                     prm);
-  if (int e = check_launch("attend")) return e;
   if (prm.n_splits > 1) {
     constexpr int kRows = 256 / (D / 4);
     hipLaunchKernelGGL((attend_merge_kernel<T, D>), dim3((prm.n_q + kRows - 1) / kRows, B * prm.H), dim3(256), 0,
@@ -727,7 +661,7 @@ int launch_attend_t(const AttendParams& prm, int B, hipStream_t stream) {
 
 size_t attend_workspace_bytes(const maskkv_desc* d, bool full) {
   const int s = attend_splits(d, full);
-  if (!full) return attend_is_narrow(d, full) ? 0 : ((size_t)d->B * d->H * sizeof(int32_t) + 255) / 256 * 256;
+  if (!full) return attend_is_ordered(d, full) ? ((size_t)d->B * d->H * sizeof(int32_t) + 255) / 256 * 256 : 0;
   if (s == 1) return 0;
   const size_t rows = (size_t)d->B * d->H * s * d->n_resp * query_heads_per_kv(d);
   return (rows * d->d * sizeof(float) + 255) / 256 * 256 + rows * sizeof(float2);
@@ -755,7 +689,7 @@ int launch_attend(const maskkv_desc* d, const Lens& lens, bool full, const View&
   prm.n_splits = attend_splits(d, full);
   prm.c = scale * kLog2e;
   prm.lse = lse;
-  prm.order = (!full && !attend_is_narrow(d, full)) ? reinterpret_cast<const int32_t*>(workspace) : nullptr;
+  prm.order = attend_is_ordered(d, full) ? reinterpret_cast<const int32_t*>(workspace) : nullptr;
   prm.part_o = nullptr;
   prm.part_ml = nullptr;
   if (prm.n_splits > 1) {

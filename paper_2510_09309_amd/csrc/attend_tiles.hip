@@ -1,0 +1,423 @@
+// Tiled attention for bf16: one workgroup of eight waves serves 256 queries of one (b, h), 32 a wave, over 64-key tiles.
+//
+// The layout of the products is that of attend.hip (logits transposed, a lane owns one query, its probabilities are the B
+// operand of O^T = V^T P^T).  What differs is how the three pipes of a SIMD are kept busy at the same time:
+//
+//   - K and V tiles come by direct transfers into two rings of four LDS slots, three tiles ahead, and no register or vector
+//     instruction touches them on the way.  V stays row-major; the A operand V^T is read with transposing LDS loads.
+//   - Waves 0-3 and 4-7 (one of each on a SIMD) run half a tile apart.  A tile is a matrix phase (its logits, and the output
+//     update of the tile before) and a vector phase (its softmax); a barrier after every phase keeps one group of waves
+//     in the one while the other is in the other.
+//
+// Slot k lies between two barriers: group 0 has the matrix phase of tile t in slot 2t and its softmax in 2t+1, group 1
+// the same one slot later.  The transfers K(t+3), V(t+2) ("pair t+3") are issued at the start of the vector phase of tile t;
+// their slots were last read in matrix phases t-1 (K(t-1), V(t-2)), which both groups have left.
+//
+// Where 256 queries a workgroup leave compute units idle (HALVES), a workgroup serves 128: both groups have the same queries, group
+// i takes tiles 2u + i through rings of two slots of its own, and the two partial results are merged through LDS.
+//
+// What bounds it: 33024 keys x 32 heads x 256 queries (head_dim 128) take 150-185 us, depending on the clock that the board's power
+// leaves (181 us and 64-row tiles staged through registers before; with head_dim 64 about 105, 180 before).  Transfers and barriers
+// alone take 107 us, which is the 541 MB of K and V at 5 TB/s; the MFMAs with their LDS reads alone 105-118, the softmax alone
+// 79-86: the three overlap, but each takes power from the others.  Eight sequences x 32 heads x 512 queries over 576 ... 1536 keys
+// (33 tiles on the busiest compute unit, 28 on average): 84 us for the call, 96 before.  Grouping even and odd waves instead
+// (both of a SIMD in the same phase): 173-215 and 100 us.  Raised wave priority in the matrix phase: the same.
+#include "attend.hpp"
+#include "lds.hpp"
+
+namespace maskkv {
+
+namespace {
+
+constexpr int kWaves = 8;
+constexpr int kTK = 64;      // keys per tile
+constexpr int kAheadFrag = 3;  // LDS fragments requested ahead of the MFMA that takes them
+
+template <int D, bool HALVES>
+struct TileCfg {
+  static constexpr int kQueries = HALVES ? 128 : 256;  // per workgroup
+  static constexpr int kMovers = HALVES ? 4 : 8;       // waves that move a tile
+  static constexpr int kMoveRows = kTK / kMovers;
+  static constexpr int kRowB = D * 2;
+  static constexpr int kSteps = D / 16;
+  static constexpr int kDB = D / 32;
+  static constexpr int kPPR = kRowB / 16;           // 16-byte pieces per row
+  static constexpr int kRPI = 1024 / kRowB;         // rows moved by one wave instruction
+  static constexpr int kMoves = kMoveRows / kRPI;   // transfers per wave and tile of K (and of V)
+  static constexpr int kTileB = kTK * kRowB;
+  static constexpr int kLds = 8 * kTileB;           // four K tiles, then four V tiles
+  static constexpr int kQK = 2 * kSteps;            // MFMAs of a tile's logits
+  static constexpr int kPV = 4 * kDB;               // MFMAs of a tile's output update
+  // A direct transfer writes 1 KiB of consecutive LDS, so rows carry no padding; instead a row's pieces are permuted.
+  // K: piece p sits in slot p ^ swz_k(row): 16 consecutive rows of a fragment read fall on different 16-byte columns.
+  // V: 32-byte unit u sits in slot u ^ swz_v(row): a transposing read takes 32 bytes of four rows per 16 lanes and 64
+  // bytes of four rows per 32 lanes, and both sets fall on different banks.
+  __device__ static uint32_t swz_k(uint32_t row) { return D == 128 ? row & 15 : (row >> 1) & 7; }
+  __device__ static uint32_t swz_v(uint32_t row) { return D == 128 ? ((row & 3) << 1 | (row & 3) >> 1) : row & 3; }
+};
+
+typedef __attribute__((ext_vector_type(4))) short s16x4;
+
+// LDS read of 8 bytes a lane with a transposition inside each group of 16 lanes: lanes 4j .. 4j+3 point at 16 elements of row j,
+// lane i receives element i of rows 0 .. 3.
+__device__ __forceinline__ u32x2 read_transposed(uint32_t addr, int imm) {
+  return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16(in_lds<s16x4>(addr, imm)));
+}
+
+template <int D, bool HALVES>
+__global__ __launch_bounds__(kWaves * 64) void attend_tiles_kernel(const AttendParams prm) {
+  using C = TileCfg<D, HALVES>;
+  extern __shared__ __attribute__((aligned(1024))) char tiles_lds[];
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)tiles_lds;
+
+  // Workgroup numbers that are congruent modulo 8 run on the same XCD and share its L2: the query tiles of one (head, key
+  // split) get consecutive slots of one XCD, and their K/V rows come from HBM once.  Ordered heads are dealt to the XCDs in
+  // turn, otherwise each XCD takes a run of units.
+  const int qtiles = (prm.n_q + C::kQueries - 1) / C::kQueries;
+  const int slot = blockIdx.x / 8 + (prm.order ? 0 : blockIdx.x % 8 * (gridDim.x / 8));
+  const int unit = prm.order ? (slot / qtiles) * 8 + blockIdx.x % 8 : slot / qtiles;  // (head, split) pair
+  const int qtile = slot % qtiles;
+  if (unit >= prm.BH * prm.n_splits) return;
+  const int bh = __builtin_amdgcn_readfirstlane(prm.order ? prm.order[unit] : unit / prm.n_splits);  // (an order is only given without splits)
+  const int split = prm.order ? 0 : unit % prm.n_splits;
+  const int b = bh / prm.H;
+  const int h = bh % prm.H;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const bool second = wave >= kWaves / 2;  // the group that runs one slot behind
+  const int part = HALVES ? wave % 4 : wave;  // this wave's queries, and its rows of the tiles that it moves
+  const int r = lane & 31;
+  const int g = lane >> 5;
+
+  const char *a_k = nullptr, *a_v = nullptr;  // packed segment
+  int len_a = 0, len_b = prm.n_resp;
+  if (prm.full) {
+    len_b = prm.lens.P[b] + prm.n_resp;
+  } else {
+    const int64_t c0 = min((int64_t)prm.cu[bh], prm.capacity);
+    const int64_t c1 = min((int64_t)prm.cu[bh + 1], prm.capacity);
+    a_k = prm.Kc + c0 * C::kRowB;
+    a_v = prm.Vc + c0 * C::kRowB;
+    len_a = (int)(c1 - c0);
+  }
+  const int Lk = len_a + len_b;
+  const int Ls = ((Lk + prm.n_splits - 1) / prm.n_splits + kTK - 1) / kTK * kTK;
+  const int j0 = split * Ls;
+  const int j1 = min(Lk, j0 + Ls);
+  const int all_tiles = j1 > j0 ? (j1 - j0 + kTK - 1) / kTK : 0;
+  // Tiles of this group: t stands for tile t, or 2t + group.  Both groups make `ntiles` steps; a last step may be without a tile.
+  const int ntiles = HALVES ? (all_tiles + 1) / 2 : all_tiles;
+  const int mine = HALVES ? (all_tiles + (second ? 0 : 1)) / 2 : all_tiles;
+  auto first_key = [&](int t) { return j0 + (HALVES ? 2 * t + (second ? 1 : 0) : t) * kTK; };
+  const char* rest_k = prm.K2.row(b, h, 0);
+  const char* rest_v = prm.V2.row(b, h, 0);
+
+  // ---- transfers: a wave moves kMoveRows rows of a tile
+  const uint32_t mrow = (uint32_t)lane / C::kPPR, mpiece = (uint32_t)lane % C::kPPR;
+  auto move = [&](const char* packed, const char* rest, int64_t stride, int t, uint32_t to, uint32_t swz, uint32_t swz_step) {
+    const int first = first_key(t) + part * C::kMoveRows;  // (t beyond the last tile: rows past the end re-read the last row)
+    to += part * C::kMoveRows * C::kRowB;
+    const uint32_t piece = (mpiece ^ swz) << 4;
+    if (first + C::kMoveRows <= j1 && (first >= len_a || first + C::kMoveRows <= len_a)) {
+      const bool in_a = first < len_a;
+      const int64_t st = in_a ? C::kRowB : stride;
+      const char* base = in_a ? packed + (int64_t)first * C::kRowB : rest + (int64_t)(first - len_a) * stride;
+      const uint32_t off = mrow * (uint32_t)st;
+#pragma unroll
+      for (int j = 0; j < C::kMoves; ++j)
+        dma16(base + j * C::kRPI * st, off + (piece ^ swz_step * j), to + j * 1024);
+    } else {
+#pragma unroll
+      for (int j = 0; j < C::kMoves; ++j) {
+        const int k = min(first + j * C::kRPI + (int)mrow, j1 - 1);
+        const char* src = k < len_a ? packed + (int64_t)k * C::kRowB : rest + (int64_t)(k - len_a) * stride;
+        dma16_from(src + (piece ^ swz_step * j), to + j * 1024);
+      }
+    }
+  };
+  // K's permutation depends on the transfer j by one exclusive-or (j * kRPI and the lane's row are row bits side by side, and
+  // the permutation of j rows of transfers is j times that of one), V's does not.
+  const uint32_t ksw = C::swz_k(part * C::kMoveRows + mrow), vsw = C::swz_v(mrow) << 1;
+  auto ring = [&](int t) { return HALVES ? (second ? 2 : 0) + (t & 1) : t & 3; };
+  auto move_k = [&](int t) {
+    move(a_k, rest_k, prm.K2.stride_t, t, lds0 + ring(t) * C::kTileB, ksw, C::swz_k(C::kRPI) << 4);
+  };
+  auto move_v = [&](int t) { move(a_v, rest_v, prm.V2.stride_t, t, lds0 + (4 + ring(t)) * C::kTileB, vsw, 0); };
+
+  const int q = qtile * C::kQueries + part * 32 + r;
+  const bool active = qtile * C::kQueries + part * 32 < prm.n_q;  // (a wave without queries only helps to move the tiles)
+  u32x4 qf[C::kSteps];
+  {
+    const char* qrow = prm.Q.group_row(b, h, prm.q_per_kv, prm.n_resp, min(q, prm.n_q - 1));
+#pragma unroll
+    for (int s = 0; s < C::kSteps; ++s) qf[s] = *reinterpret_cast<const u32x4*>(qrow + s * 32 + g * 16);
+  }
+
+  f32x16 o[C::kDB], s[2];
+  u32x4 pf[4];  // probabilities of a tile as B operands: keys 32*(n/2) + 16*(n%2) ..
+#pragma unroll
+  for (int db = 0; db < C::kDB; ++db) o[db] = f32x16{};
+  float m = kNegBig, l = 0.f;
+  const float c = prm.c;
+
+  // ---- fragment addresses.  Four ring slots are two pairs: the second of a pair is an immediate offset away.
+  const uint32_t own = lds0 + (HALVES && second ? 2 * C::kTileB : 0);
+  uint32_t ka[C::kSteps], va[C::kDB];
+#pragma unroll
+  for (int i = 0; i < C::kSteps; ++i) ka[i] = own + r * C::kRowB + (((2 * i + g) ^ C::swz_k(r)) << 4);
+  {
+    const uint32_t i = lane & 15, row = i >> 2;
+#pragma unroll
+    for (int db = 0; db < C::kDB; ++db)
+      va[db] = own + 4 * C::kTileB + (4 * g + row) * C::kRowB + (((2 * db + ((lane >> 4) & 1)) ^ C::swz_v(row)) << 5) + (i & 3) * 8;
+  }
+#pragma unroll
+  for (int i = 0; i < C::kSteps; ++i) asm volatile("" : "+v"(ka[i]));
+#pragma unroll
+  for (int i = 0; i < C::kDB; ++i) asm volatile("" : "+v"(va[i]));
+  auto turn_k = [&]() {
+    if (HALVES) return;
+#pragma unroll
+    for (int i = 0; i < C::kSteps; ++i) ka[i] ^= 2 * C::kTileB;
+  };
+  auto turn_v = [&]() {
+    if (HALVES) return;
+#pragma unroll
+    for (int i = 0; i < C::kDB; ++i) va[i] ^= 2 * C::kTileB;
+  };
+
+  // ---- matrix phase: fragments n = 0 .. kQK-1 are the logits' (two chains, one per block of 32 keys), then the output's
+  u32x4 fr[kAheadFrag + 1];
+  auto fetch = [&](int n, int pk, int pv) {
+    u32x4& f = fr[n % (kAheadFrag + 1)];
+    if (n < C::kQK) {
+      f = *in_lds<const u32x4>(ka[n / 2], pk * C::kTileB + (n % 2) * 32 * C::kRowB);
+    } else {
+      const int i = n - C::kQK, imm = pv * C::kTileB + (i / C::kDB) * 16 * C::kRowB;
+      const u32x2 lo = read_transposed(va[i % C::kDB], imm), hi = read_transposed(va[i % C::kDB], imm + 8 * C::kRowB);
+      f = u32x4{lo[0], lo[1], hi[0], hi[1]};
+    }
+  };
+  auto matrix = [&](int from, int to, int pk, int pv) {
+#pragma unroll
+    for (int i = 0; i < kAheadFrag; ++i) fetch(from + i, pk, pv);
+    if (from == 0) s[0] = s[1] = f32x16{};
+#pragma unroll
+    for (int n = from; n < to; ++n) {
+      if (n + kAheadFrag < to) fetch(n + kAheadFrag, pk, pv);
+      const u32x4& f = fr[n % (kAheadFrag + 1)];
+      if (n < C::kQK)
+        mfma_step<bf16_t>(f, qf[n / 2], s[n % 2]);
+      else
+        mfma_step<bf16_t>(f, pf[(n - C::kQK) / C::kDB], o[(n - C::kQK) % C::kDB]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+
+  // ---- vector phase: online softmax of the logits; lanes l and l^32 hold the same query
+  auto softmax = [&](int t) {
+    const int left = j1 - first_key(t);
+    if (left < kTK) {
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+          if (kb * 32 + 8 * (i / 4) + 4 * g + (i % 4) >= left) s[kb][i] = -INFINITY;
+    }
+    float bm = s[0][0];
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) bm = fmaxf(bm, s[kb][i]);
+    {
+      const auto sw = __builtin_amdgcn_permlane32_swap(as_u32(bm), as_u32(bm), false, false);
+      const uint32_t s0 = sw[0], s1 = sw[1];
+      bm = fmaxf(as_f32(s0), as_f32(s1));
+    }
+    // The reference m is only raised when a tile exceeds it by more than 2^kLazyBump (see attend.hip).
+    const float cand = bm * c;
+    const bool bump = cand > m + kLazyBump;
+    if (__any(bump)) {
+      const float m_new = bump ? cand : m;
+      const float alpha = fast_exp2(m - m_new);
+      m = m_new;
+      l *= alpha;
+#pragma unroll
+      for (int db = 0; db < C::kDB; ++db)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) o[db][i] *= alpha;
+    }
+    float psum = 0.f;
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const float p = fast_exp2(fmaf(s[kb][i], c, -m));
+        s[kb][i] = p;
+        psum += p;
+      }
+#pragma unroll
+      for (int tp = 0; tp < 2; ++tp)
+#pragma unroll
+        for (int w = 0; w < 4; ++w) pf[2 * kb + tp][w] = pack_bf16x2(s[kb][8 * tp + 2 * w], s[kb][8 * tp + 2 * w + 1]);
+    }
+    l += psum;
+  };
+
+  // ---- barriers.  Before matrix phase t of group 0 every wave has waited for its part of pair t: group 0 at the end of its
+  // vector phase t-1, where pairs t+1 and t+2 are younger, group 1 at the end of its matrix phase t-1, where pair t+1 is.
+  // With HALVES a group moves its own tiles, pair t+2 in vector phase t (into the slots of K(t) and V(t-1), which it has
+  // read), and waits for pair t+1 at the end of that phase.
+  auto end_matrix = [&]() {
+    __builtin_amdgcn_sched_barrier(0);
+    if (!HALVES && second)
+      asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"i"(2 * C::kMoves) : "memory");
+    else
+      asm volatile("s_barrier" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto end_vector = [&]() {
+    __builtin_amdgcn_sched_barrier(0);
+    if (HALVES)
+      asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"i"(2 * C::kMoves) : "memory");
+    else if (second)
+      asm volatile("s_barrier" ::: "memory");
+    else
+      asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"i"(4 * C::kMoves) : "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto vector = [&](int t) {
+    if (!HALVES || t < mine) {  // (a step without a tile has left V(t-1) unread)
+      move_k(t + (HALVES ? 2 : 3));
+      move_v(t + (HALVES ? 1 : 2));
+    }
+    if (active && t < mine) softmax(t);
+    end_vector();
+  };
+
+  if (ntiles > 0) {
+    move_k(0);
+    move_k(1);
+    move_v(0);
+    if (!HALVES) {
+      move_k(2);
+      move_v(1);
+    }
+#pragma unroll
+    for (int i = 0; i < C::kSteps; ++i) asm volatile("" : "+v"(qf[i]));
+    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"i"((HALVES ? 2 : 4) * C::kMoves) : "memory");
+    if (second) asm volatile("s_barrier" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    if (active && mine > 0) matrix(0, C::kQK, 0, 0);
+    end_matrix();
+    vector(0);
+    for (int t = 1; t < ntiles; t += 2) {
+      if (active && t < mine) matrix(0, C::kQK + C::kPV, 1, 0);
+      turn_k();
+      end_matrix();
+      vector(t);
+      if (t + 1 < ntiles) {
+        if (active && t + 1 < mine) matrix(0, C::kQK + C::kPV, 0, 1);
+        turn_v();
+        end_matrix();
+        vector(t + 1);
+      }
+    }
+    if (active && mine > 0) {
+      if (mine & 1)
+        matrix(C::kQK, C::kQK + C::kPV, 0, 0);
+      else
+        matrix(C::kQK, C::kQK + C::kPV, 0, 1);
+    }
+    if (!second) asm volatile("s_barrier" ::: "memory");
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (no transfer into LDS outlives its workgroup)
+  }
+
+  float l_tot = l + xor32(l);
+  if (HALVES) {  // group 1 leaves its part in LDS, group 0 adds it to its own
+    float* po = reinterpret_cast<float*>(tiles_lds) + part * (C::kDB * 16 * 64);  // [db][i][lane]
+    float2* ml = reinterpret_cast<float2*>(tiles_lds + 4 * C::kDB * 16 * 64 * 4) + part * 64;
+    __syncthreads();
+    if (second) {
+#pragma unroll
+      for (int db = 0; db < C::kDB; ++db)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) po[(db * 16 + i) * 64 + lane] = o[db][i];
+      ml[lane] = make_float2(m, l_tot);
+    }
+    __syncthreads();
+    if (second) return;
+    const float2 other = ml[lane];
+    const float top = fmaxf(m, other.x);
+    const float wa = fast_exp2(m - top), wb = fast_exp2(other.x - top);
+    m = top;
+    l_tot = wa * l_tot + wb * other.y;
+#pragma unroll
+    for (int db = 0; db < C::kDB; ++db)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) o[db][i] = wa * o[db][i] + wb * po[(db * 16 + i) * 64 + lane];
+  }
+  if (q >= prm.n_q) return;
+  if (prm.n_splits == 1) {
+    const float inv = 1.f / l_tot;
+    char* orow = prm.O.group_row(b, h, prm.q_per_kv, prm.n_resp, q);
+#pragma unroll
+    for (int db = 0; db < C::kDB; ++db)
+#pragma unroll
+      for (int qd = 0; qd < 4; ++qd) {
+        const int e = db * 32 + 8 * qd + 4 * g;
+        u32x2 w;
+        w[0] = pack_bf16x2(o[db][4 * qd] * inv, o[db][4 * qd + 1] * inv);
+        w[1] = pack_bf16x2(o[db][4 * qd + 2] * inv, o[db][4 * qd + 3] * inv);
+        *reinterpret_cast<u32x2*>(orow + e * 2) = w;
+      }
+    if (prm.lse && g == 0) prm.lse[(int64_t)bh * prm.n_q + q] = (m + __log2f(l_tot)) * kLn2;
+  } else {
+    const int64_t at = ((int64_t)bh * prm.n_splits + split) * prm.n_q + q;
+    float* po = prm.part_o + at * D;
+#pragma unroll
+    for (int db = 0; db < C::kDB; ++db)
+#pragma unroll
+      for (int qd = 0; qd < 4; ++qd)
+        *reinterpret_cast<float4*>(po + db * 32 + 8 * qd + 4 * g) =
+            make_float4(o[db][4 * qd], o[db][4 * qd + 1], o[db][4 * qd + 2], o[db][4 * qd + 3]);
+    if (g == 0) prm.part_ml[at] = make_float2(m, l_tot);
+  }
+}
+
+template <int D, bool HALVES>
+int launch(const AttendParams& prm, unsigned groups, hipStream_t stream) {
+  using C = TileCfg<D, HALVES>;
+  static bool raised = false;  // one-time opt-in to more than the default dynamic LDS size
+  if (!raised) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attend_tiles_kernel<D, HALVES>),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, C::kLds);
+    if (e != hipSuccess) {
+      set_error("attend: cannot raise dynamic LDS limit: %s", hipGetErrorString(e));
+      (void)hipGetLastError();
+      return MASKKV_EHIP;
+    }
+    raised = true;
+  }
+  hipLaunchKernelGGL((attend_tiles_kernel<D, HALVES>), dim3(groups), dim3(kWaves * 64), C::kLds, stream, prm);
+  return check_launch("attend (tiles)");
+}
+
+}  // namespace
+
+// 128 queries a workgroup where 256 would leave compute units without one (measured, 128 against 256: 128 heads x 256 queries
+// 23.6 / 29.3 us, 256 heads x 100 queries 29.1 / 34.3, head_dim 64 128 heads x 200 queries 22.8 / 33.4; but 256 heads x 512
+// queries 102 / 85).  The un-evicted call fills the chip by splitting the keys instead.
+int attend_tiles_queries(int64_t units, int n_q, bool full) {
+  if (n_q <= 128) return 128;
+  return !full && (n_q + 255) / 256 * units < 256 ? 128 : 256;
+}
+
+int launch_attend_tiles(const AttendParams& prm, int d, int queries, hipStream_t stream) {
+  const int64_t qtiles = (prm.n_q + queries - 1) / queries, units = (int64_t)prm.BH * prm.n_splits;
+  const unsigned groups = (unsigned)(prm.order ? (units + 7) / 8 * 8 * qtiles : (units * qtiles + 7) / 8 * 8);
+  if (queries == 128) return d == 128 ? launch<128, true>(prm, groups, stream) : launch<64, true>(prm, groups, stream);
+  return d == 128 ? launch<128, false>(prm, groups, stream) : launch<64, false>(prm, groups, stream);
+}
+
+}  // namespace maskkv

@@ -24,6 +24,7 @@
 // copies of the sums, or asking for the sums earlier in the step: slower (a sum that is asked for before it is
 // complete has to be asked for again, and a line that is being read is slow to add to).
 #include "kernels.hpp"
+#include "lds.hpp"
 namespace maskkv {
 
 namespace {
@@ -109,32 +110,6 @@ struct Cfg {
   // slot p ^ swz(r), which spreads the fragment reads of 16 consecutive rows over all banks.
   __device__ static int swz(int row) { return D == 128 ? row & 15 : (row >> 1) & 7; }
 };
-
-// Direct global -> LDS transfer of 16 (4) bytes per lane from base + off to lds + lane * 16 (4).
-__device__ __forceinline__ void dma16(const char* base, uint32_t off, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds) : "memory");
-}
-__device__ __forceinline__ void dma4(const char* base, uint32_t off, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" ::"v"(off), "s"(base), "s"(lds) : "memory");
-}
-
-// Global memory by a uniform base (two scalar registers, hidden from the optimiser, which would otherwise form one 64-bit
-// address per lane and keep it) and a 32-bit offset per lane.
-typedef __attribute__((address_space(1))) char* Base;
-__device__ __forceinline__ Base base_of(const void* p) {
-  Base b = (Base)p;
-  asm volatile("" : "+s"(b));
-  return b;
-}
-template <typename T>
-__device__ __forceinline__ __attribute__((address_space(1))) T* at(Base b, uint32_t off, int imm = 0) {
-  return reinterpret_cast<__attribute__((address_space(1))) T*>(b + off + imm);
-}
-// LDS by its own 32-bit address (the name of the array would be added to every lane's offset again and again).
-template <typename T>
-__device__ __forceinline__ __attribute__((address_space(3))) T* in_lds(uint32_t addr, int imm = 0) {
-  return reinterpret_cast<__attribute__((address_space(3))) T*>((__attribute__((address_space(3))) char*)(uintptr_t)addr + imm);
-}
 
 __device__ __forceinline__ uint64_t peek(Base b, uint32_t off) {
   return __hip_atomic_load(at<uint64_t>(b, off), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
