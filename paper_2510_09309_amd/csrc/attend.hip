@@ -265,7 +265,7 @@ __global__ __launch_bounds__((AttCfg<D>::kThreads)) void attend_kernel(const Att
 }
 
 // ---------------------------------------------------------------------------------------------
-// Narrow launches (few heads x query tiles, bf16): the kernel above would occupy a fraction of the compute
+// Narrow launches (few heads x query tiles): a tiled kernel would occupy a fraction of the compute
 // units with one long serial chain of tiles each.  Here a workgroup serves 32 queries and its four waves
 // split the key axis: wave w takes the 32-key blocks w, w+4, ... on its own - K fragments straight from
 // global memory into registers, V through a wave-private transposed LDS tile, no workgroup barrier in the
@@ -273,27 +273,29 @@ __global__ __launch_bounds__((AttCfg<D>::kThreads)) void attend_kernel(const Att
 // flight.  Every XCD (workgroup numbers that are congruent modulo 8) takes one run of (head, query tile) pairs, so that a
 // head's K/V rows are fetched into one or two L2s and four heads still reach all eight XCDs (4 heads x 1792 queries: 23.7 us
 // with a head on one XCD, 12.6 now).
-constexpr int kNarrowVS = 36;      // bf16 elements per transposed-V row: 32 keys + padding
+constexpr int kNarrowVS = 36;      // elements per transposed-V row: 32 keys + padding
 constexpr int kNarrowShift = 16;   // bytes by which every group of 32 rows is shifted further (as in the tiled kernel)
 
 // NW waves per workgroup split the key axis.
-template <int D, int NW>
+template <typename T, int D, int NW>
 struct NarrowCfg {
+  static constexpr int kEB = (int)sizeof(T);
   static constexpr int kThreads = 64 * NW;
-  static constexpr int kRowB = D * 2;
+  static constexpr int kRowB = D * kEB;
   static constexpr int kSteps = kRowB / 32;
   static constexpr int kPPR = kRowB / 16;        // 16-byte pieces per row
   static constexpr int kVP = 32 * kPPR / 64;     // V pieces per lane per block
   static constexpr int kDB = D / 32;
-  static constexpr int kVtBytes = D * kNarrowVS * 2 + (D / 32) * kNarrowShift;  // per wave
+  static constexpr int kSets = kRowB <= 256 ? 2 : 1;  // blocks a wave keeps in flight (512-byte rows: registers for one)
+  static constexpr int kVtBytes = D * kNarrowVS * kEB + (D / 32) * kNarrowShift;  // per wave
   static constexpr int kMergeBytes = NW * kDB * 16 * 64 * 4;        // partial O of the waves
   static constexpr int kLds = (kMergeBytes > NW * kVtBytes ? kMergeBytes : NW * kVtBytes) + NW * 32 * 8;
 };
 
-template <int D, int NW>
-__global__ __launch_bounds__((NarrowCfg<D, NW>::kThreads)) void attend_narrow_kernel(const AttendParams prm) {
-  using T = bf16_t;
-  using C = NarrowCfg<D, NW>;
+template <typename T, int D, int NW>
+__global__ __launch_bounds__((NarrowCfg<T, D, NW>::kThreads)) void attend_narrow_kernel(const AttendParams prm) {
+  using C = NarrowCfg<T, D, NW>;
+  constexpr bool kPairs = sizeof(T) == 2;
   extern __shared__ __attribute__((aligned(16))) char smem[];
 
   const int nqt = (prm.n_q + 31) / 32;
@@ -321,12 +323,20 @@ __global__ __launch_bounds__((NarrowCfg<D, NW>::kThreads)) void attend_narrow_ke
     return j < len_a ? packed + (int64_t)j * C::kRowB : rest.row(b, h, j - len_a);
   };
   // Ask for block blk: K in MFMA fragment layout (lane = key row), V as row pieces for the transposition
-  // (item = (key pair, 16-byte slice); pieces 2i and 2i+1 are the pair's two rows).  Rows past the end of
+  // (bf16: item = (key pair, 16-byte slice); pieces 2i and 2i+1 are the pair's two rows).  Rows past the end of
   // the key axis re-read its last row and are masked.
   auto request = [&](int blk, u32x4 (&kf)[C::kSteps], u32x4 (&vr)[C::kVP]) {
     const char* krow = key_row(a_k, prm.K2, min(blk * 32 + r, Lk - 1)) + g * 16;
 #pragma unroll
     for (int s = 0; s < C::kSteps; ++s) kf[s] = *reinterpret_cast<const u32x4*>(krow + s * 32);
+    if constexpr (!kPairs) {
+#pragma unroll
+      for (int i = 0; i < C::kVP; ++i) {
+        const int p = lane + i * 64;
+        vr[i] = *reinterpret_cast<const u32x4*>(key_row(a_v, prm.V2, min(blk * 32 + p / C::kPPR, Lk - 1)) + p % C::kPPR * 16);
+      }
+      return;
+    }
 #pragma unroll
     for (int i = 0; i < C::kVP / 2; ++i) {
       const int item = lane + i * 64;
@@ -337,10 +347,10 @@ __global__ __launch_bounds__((NarrowCfg<D, NW>::kThreads)) void attend_narrow_ke
     }
   };
 
-  // the first two blocks of this wave are asked for before anything else: their latency covers the query loads
+  // the first blocks of this wave are asked for before anything else: their latency covers the query loads
   u32x4 kfa[C::kSteps], vra[C::kVP], kfb[C::kSteps], vrb[C::kVP];
   if (wave < nblk) request(wave, kfa, vra);
-  if (wave + NW < nblk) request(wave + NW, kfb, vrb);
+  if (C::kSets == 2 && wave + NW < nblk) request(wave + NW, kfb, vrb);
 
   const int q = qt * 32 + r;
   u32x4 qf[C::kSteps];
@@ -362,16 +372,25 @@ __global__ __launch_bounds__((NarrowCfg<D, NW>::kThreads)) void attend_narrow_ke
     // fragment loads and before this block's.
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
+    if constexpr (kPairs) {
 #pragma unroll
-    for (int i = 0; i < C::kVP / 2; ++i) {
-      const int item = lane + i * 64;
-      const int pair = item / C::kPPR, col = item % C::kPPR;
-      const u32x4 a = vr[2 * i], bq = vr[2 * i + 1];
+      for (int i = 0; i < C::kVP / 2; ++i) {
+        const int item = lane + i * 64;
+        const int pair = item / C::kPPR, col = item % C::kPPR;
+        const u32x4 a = vr[2 * i], bq = vr[2 * i + 1];
 #pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        const int word = (col * 8 + 2 * w) * (kNarrowVS / 2) + (col / 4) * (kNarrowShift / 4) + pair;
-        vt32[word] = (a[w] & 0xFFFFu) | (bq[w] << 16);
-        vt32[word + kNarrowVS / 2] = (a[w] >> 16) | (bq[w] & 0xFFFF0000u);
+        for (int w = 0; w < 4; ++w) {
+          const int word = (col * 8 + 2 * w) * (kNarrowVS / 2) + (col / 4) * (kNarrowShift / 4) + pair;
+          vt32[word] = (a[w] & 0xFFFFu) | (bq[w] << 16);
+          vt32[word + kNarrowVS / 2] = (a[w] >> 16) | (bq[w] & 0xFFFF0000u);
+        }
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < C::kVP; ++i) {
+        const int p = lane + i * 64, row = p / C::kPPR, col = p % C::kPPR;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) vt32[(col * 4 + w) * kNarrowVS + (col / 8) * (kNarrowShift / 4) + row] = vr[i][w];
       }
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -380,7 +399,7 @@ __global__ __launch_bounds__((NarrowCfg<D, NW>::kThreads)) void attend_narrow_ke
     f32x16 s = f32x16{};
 #pragma unroll
     for (int st = 0; st < C::kSteps; ++st) mfma_step<T>(kf[st], qf[st], s);
-    if (blk + 2 * NW < nblk) request(blk + 2 * NW, kf, vr);
+    if (blk + C::kSets * NW < nblk) request(blk + C::kSets * NW, kf, vr);
     const int nvalid = Lk - blk * 32;
     if (nvalid < 32) {
 #pragma unroll
@@ -413,26 +432,42 @@ __global__ __launch_bounds__((NarrowCfg<D, NW>::kThreads)) void attend_narrow_ke
     }
     l += psum;
     // O^T += V^T P^T
+    const char* vt = reinterpret_cast<const char*>(vt32);
+    if constexpr (kPairs) {
 #pragma unroll
-    for (int tp = 0; tp < 2; ++tp) {
-      u32x4 pf;
+      for (int tp = 0; tp < 2; ++tp) {
+        u32x4 pf;
 #pragma unroll
-      for (int w = 0; w < 4; ++w) pf[w] = pack_bf16x2(s[8 * tp + 2 * w], s[8 * tp + 2 * w + 1]);
+        for (int w = 0; w < 4; ++w) pf[w] = pack_bf16x2(s[8 * tp + 2 * w], s[8 * tp + 2 * w + 1]);
 #pragma unroll
-      for (int db = 0; db < C::kDB; ++db) {
-        const char* rowp =
-            reinterpret_cast<const char*>(vt32) + ((db * 32 + r) * kNarrowVS + 16 * tp + 4 * g) * 2 + db * kNarrowShift;
-        const u32x2 lo = *reinterpret_cast<const u32x2*>(rowp);
-        const u32x2 hi = *reinterpret_cast<const u32x2*>(rowp + 16);
-        const u32x4 vf = {lo[0], lo[1], hi[0], hi[1]};
-        mfma_step<T>(vf, pf, o[db]);
+        for (int db = 0; db < C::kDB; ++db) {
+          const char* rowp =
+              vt + ((db * 32 + r) * kNarrowVS + 16 * tp + 4 * g) * 2 + db * kNarrowShift;
+          const u32x2 lo = *reinterpret_cast<const u32x2*>(rowp);
+          const u32x2 hi = *reinterpret_cast<const u32x2*>(rowp + 16);
+          const u32x4 vf = {lo[0], lo[1], hi[0], hi[1]};
+          mfma_step<T>(vf, pf, o[db]);
+        }
+      }
+    } else {
+#pragma unroll
+      for (int qd = 0; qd < 4; ++qd) {
+        u32x4 pf;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+          const float pv = s[4 * qd + w];
+          pf[w] = as_u32(pv);
+        }
+#pragma unroll
+        for (int db = 0; db < C::kDB; ++db)
+          mfma_step<T>(*reinterpret_cast<const u32x4*>(vt + ((db * 32 + r) * kNarrowVS + 8 * qd + 4 * g) * 4 + db * kNarrowShift), pf, o[db]);
       }
     }
   };
 
-  for (int blk = wave; blk < nblk; blk += 2 * NW) {
+  for (int blk = wave; blk < nblk; blk += C::kSets * NW) {
     step(blk, kfa, vra);
-    if (blk + NW < nblk) step(blk + NW, kfb, vrb);
+    if (C::kSets == 2 && blk + NW < nblk) step(blk + NW, kfb, vrb);
   }
 
   // ---- merge the waves' partial results through LDS (the V tiles are no longer needed)
@@ -471,10 +506,15 @@ __global__ __launch_bounds__((NarrowCfg<D, NW>::kThreads)) void attend_narrow_ke
       for (int w = 0; w < NW; ++w) acc += wgt[w] * mo[((w * C::kDB + db) * 16 + 4 * qd + e) * 64 + lane];
       v[e] = acc * inv;
     }
-    u32x2 wout;
-    wout[0] = pack_bf16x2(v[0], v[1]);
-    wout[1] = pack_bf16x2(v[2], v[3]);
-    *reinterpret_cast<u32x2*>(orow + (db * 32 + 8 * qd + 4 * g) * 2) = wout;
+    char* to = orow + (db * 32 + 8 * qd + 4 * g) * C::kEB;
+    if constexpr (kPairs) {
+      u32x2 wout;
+      wout[0] = pack_bf16x2(v[0], v[1]);
+      wout[1] = pack_bf16x2(v[2], v[3]);
+      *reinterpret_cast<u32x2*>(to) = wout;
+    } else {
+      *reinterpret_cast<float4*>(to) = make_float4(v[0], v[1], v[2], v[3]);
+    }
   }
   if (prm.lse && wave == 0 && g == 0) prm.lse[(int64_t)bh * prm.n_q + q] = (M + __log2f(L)) * kLn2;
 }
@@ -578,14 +618,20 @@ int attend_splits(const maskkv_desc* d, bool full) {
   return (int)s;
 }
 
-// The narrow kernel is used where its workgroups of 32 queries are all resident at once and fast: one per compute unit at
-// head_dim 128, about two at 64 (measured, narrow against tiled, us a call without the tiled kernel's ordering: head_dim 128 and
-// 256 queries, 32 heads 11.8 / 15.6, 64 heads 22.2 / 16; 32 heads x 512 queries x 1536 keys 43 / 28; 4 heads x 1792 queries
-// 14 / 17; head_dim 64, 512 workgroups 9.5 / 10.2).
+// bf16: the narrow kernel is used where its workgroups of 32 queries are all resident at once and fast: one per compute unit
+// at head_dim 128, about two at 64 (measured, narrow against tiled, us a call without the tiled kernel's ordering: head_dim 128
+// and 256 queries, 32 heads 11.8 / 15.6, 64 heads 22.2 / 16; 32 heads x 512 queries x 1536 keys 43 / 28; 4 heads x 1792
+// queries 14 / 17; head_dim 64, 512 workgroups 9.5 / 10.2).
+// fp32: a round of narrow workgroups takes a quarter (head_dim 64) to a seventh (128) of a round of the tiled kernel's, whose eight
+// waves walk the whole key axis (32 heads x 256 queries x 512 keys: 16.8 / 75 and 29.5 / 143 us; 4 heads x 64 queries x 576 keys
+// 18.7 / 78.6), so it is taken up to four times as many rounds.
 bool attend_is_narrow(const maskkv_desc* d, bool full) {
-  if (full || d->dtype != MASKKV_BF16) return false;
-  const int64_t qtiles = ((int64_t)d->n_resp * query_heads_per_kv(d) + 31) / 32;
-  return qtiles * d->B * d->H <= (d->d == 128 ? kUnits : 9 * kUnits / 4);
+  if (full) return false;
+  const int64_t n_q = (int64_t)d->n_resp * query_heads_per_kv(d), heads = (int64_t)d->B * d->H;
+  const int64_t groups = (n_q + 31) / 32 * heads;
+  if (d->dtype == MASKKV_BF16) return groups <= (d->d == 128 ? kUnits : 9 * kUnits / 4);
+  const int64_t tiled = (n_q + AttCfg<128>::kQPerBlock - 1) / AttCfg<128>::kQPerBlock * heads;
+  return groups <= 4 * kUnits * ((tiled + kUnits - 1) / kUnits);
 }
 
 // Heads are only put in order where not every workgroup of the tiled kernel starts at once.
@@ -595,12 +641,12 @@ bool attend_is_ordered(const maskkv_desc* d, bool full) {
   return ((int64_t)d->n_resp * query_heads_per_kv(d) + per_block - 1) / per_block * d->B * d->H > kUnits;
 }
 
-template <int D, int NW>
+template <typename T, int D, int NW>
 int launch_attend_narrow(const AttendParams& prm, hipStream_t stream) {
-  using C = NarrowCfg<D, NW>;
+  using C = NarrowCfg<T, D, NW>;
   static bool raised = false;  // one-time opt-in to more than the default dynamic LDS size
   if (C::kLds > 48 * 1024 && !raised) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attend_narrow_kernel<D, NW>),
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attend_narrow_kernel<T, D, NW>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, C::kLds);
     if (e != hipSuccess) {
       set_error("attend: cannot raise dynamic LDS limit: %s", hipGetErrorString(e));
@@ -611,7 +657,7 @@ int launch_attend_narrow(const AttendParams& prm, hipStream_t stream) {
   }
   const int nqt = (prm.n_q + 31) / 32;
   const int groups = (prm.BH * nqt + 7) / 8 * 8;
-  hipLaunchKernelGGL((attend_narrow_kernel<D, NW>), dim3(groups), dim3(C::kThreads), C::kLds, stream, prm);
+  hipLaunchKernelGGL((attend_narrow_kernel<T, D, NW>), dim3(groups), dim3(C::kThreads), C::kLds, stream, prm);
   return check_launch("attend (narrow)");
 }
 
@@ -698,8 +744,11 @@ int launch_attend(const maskkv_desc* d, const Lens& lens, bool full, const View&
     prm.part_ml = reinterpret_cast<float2*>(reinterpret_cast<char*>(workspace) +
                                             (rows * d->d * sizeof(float) + 255) / 256 * 256);
   }
-  if (attend_is_narrow(d, full))  // (eight waves per 32-query tile measured slower: 20.6 vs 17.6 us at the 32k prompt)
-    return d->d == 128 ? launch_attend_narrow<128, 4>(prm, stream) : launch_attend_narrow<64, 4>(prm, stream);
+  if (attend_is_narrow(d, full)) {  // (eight waves per 32-query tile measured slower: 20.6 vs 17.6 us at the 32k prompt)
+    if (d->dtype == MASKKV_BF16)
+      return d->d == 128 ? launch_attend_narrow<bf16_t, 128, 4>(prm, stream) : launch_attend_narrow<bf16_t, 64, 4>(prm, stream);
+    return d->d == 128 ? launch_attend_narrow<float, 128, 4>(prm, stream) : launch_attend_narrow<float, 64, 4>(prm, stream);
+  }
   if (d->dtype == MASKKV_BF16)
     return d->d == 128 ? launch_attend_t<bf16_t, 128>(prm, d->B, stream) : launch_attend_t<bf16_t, 64>(prm, d->B, stream);
   return d->d == 128 ? launch_attend_t<float, 128>(prm, d->B, stream) : launch_attend_t<float, 64>(prm, d->B, stream);
