@@ -11,6 +11,7 @@
 // transposed so that the A operand of the second product is read with 16-byte LDS loads), the narrow kernel for small bf16
 // launches, the merge and the rules that choose.  attend_tiles.hip: the tiled kernel for bf16.
 #include "attend.hpp"
+#include "lds.hpp"
 
 namespace maskkv {
 
@@ -265,16 +266,18 @@ __global__ __launch_bounds__((AttCfg<D>::kThreads)) void attend_kernel(const Att
 }
 
 // ---------------------------------------------------------------------------------------------
-// Narrow launches (few heads x query tiles): a tiled kernel would occupy a fraction of the compute
-// units with one long serial chain of tiles each.  Here a workgroup serves 32 queries and its four waves
-// split the key axis: wave w takes the 32-key blocks w, w+4, ... on its own - K fragments straight from
-// global memory into registers, V through a wave-private transposed LDS tile, no workgroup barrier in the
-// loop - and the four partial (O, m, l) are merged through LDS at the end.  Two blocks per wave are kept in
-// flight.  Every XCD (workgroup numbers that are congruent modulo 8) takes one run of (head, query tile) pairs, so that a
-// head's K/V rows are fetched into one or two L2s and four heads still reach all eight XCDs (4 heads x 1792 queries: 23.7 us
-// with a head on one XCD, 12.6 now).
-constexpr int kNarrowVS = 36;      // elements per transposed-V row: 32 keys + padding
-constexpr int kNarrowShift = 16;   // bytes by which every group of 32 rows is shifted further (as in the tiled kernel)
+// Narrow launches (few heads x query tiles): a tiled kernel would occupy a fraction of the compute units with one long serial
+// chain of tiles each.  Here a workgroup serves 32 queries and its four waves split the key axis: wave w takes the 32-key
+// blocks w, w+4, ... on its own - K fragments straight from global memory into registers, V (bf16) by direct transfers into
+// wave-private LDS, read with transposing loads, or (fp32) through a wave-private transposed LDS tile, no workgroup barrier
+// in the loop - and the four partial (O, m, l) are merged through LDS at the end.  Every XCD (workgroup numbers that are
+// congruent modulo 8) takes one run of (head, query tile) pairs, so that a head's K/V rows are fetched into one or two L2s
+// and four heads still reach all eight XCDs (4 heads x 1792 queries: 23.7 us with a head on one XCD, 12.6 spread).
+// What bounds it is latency: 32 heads x 256 queries x 512 keys take 10.3 us, about 5 of them until the first block is there (11.8
+// with V transposed by vector instructions on its way through registers).  Two blocks per wave are in flight; three or four
+// 11.0 and 11.7, eight waves with one or two blocks each 11.8.
+constexpr int kNarrowVS = 36;      // fp32: elements per transposed-V row: 32 keys + padding
+constexpr int kNarrowShift = 16;   // bytes by which every group of 32 rows is shifted further
 
 // NW waves per workgroup split the key axis.
 template <typename T, int D, int NW>
@@ -287,7 +290,9 @@ struct NarrowCfg {
   static constexpr int kVP = 32 * kPPR / 64;     // V pieces per lane per block
   static constexpr int kDB = D / 32;
   static constexpr int kSets = kRowB <= 256 ? 2 : 1;  // blocks a wave keeps in flight (512-byte rows: registers for one)
-  static constexpr int kVtBytes = D * kNarrowVS * kEB + (D / 32) * kNarrowShift;  // per wave
+  static constexpr int kVBlock = 32 * kRowB;     // bf16: a block of V as it comes, two per wave
+  static constexpr int kRPI = 1024 / kRowB;      // rows moved by one transfer
+  static constexpr int kVtBytes = kEB == 2 ? kSets * kVBlock : D * kNarrowVS * kEB + (D / 32) * kNarrowShift;  // per wave
   static constexpr int kMergeBytes = NW * kDB * 16 * 64 * 4;        // partial O of the waves
   static constexpr int kLds = (kMergeBytes > NW * kVtBytes ? kMergeBytes : NW * kVtBytes) + NW * 32 * 8;
 };
@@ -307,7 +312,7 @@ __global__ __launch_bounds__((NarrowCfg<T, D, NW>::kThreads)) void attend_narrow
   const int b = bh / prm.H;
   const int h = bh % prm.H;
   const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r = lane & 31;
   const int g = lane >> 5;
 
@@ -322,35 +327,42 @@ __global__ __launch_bounds__((NarrowCfg<T, D, NW>::kThreads)) void attend_narrow
   auto key_row = [&](const char* packed, const View& rest, int j) -> const char* {
     return j < len_a ? packed + (int64_t)j * C::kRowB : rest.row(b, h, j - len_a);
   };
-  // Ask for block blk: K in MFMA fragment layout (lane = key row), V as row pieces for the transposition
-  // (bf16: item = (key pair, 16-byte slice); pieces 2i and 2i+1 are the pair's two rows).  Rows past the end of
-  // the key axis re-read its last row and are masked.
-  auto request = [&](int blk, u32x4 (&kf)[C::kSteps], u32x4 (&vr)[C::kVP]) {
-    const char* krow = key_row(a_k, prm.K2, min(blk * 32 + r, Lk - 1)) + g * 16;
+  // Ask for block blk: K in MFMA fragment layout (lane = key row); V in fp32 as row pieces for the transposition, in bf16 by
+  // direct transfers into slot `set` of this wave, ahead of the K loads, so that V is there when K is.  Rows past the
+  // end of the key axis re-read its last row and are masked.
+  const uint32_t lds_v = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem + wave * C::kVtBytes;
+  auto request = [&](int blk, u32x4 (&kf)[C::kSteps], u32x4 (&vr)[C::kVP], int set) {
+    if constexpr (kPairs) {
+      const int first = blk * 32, mrow = lane / C::kPPR;
+      const uint32_t piece = ((uint32_t)lane % C::kPPR ^ v_swizzle<D>(mrow) << 1) << 4;
+      const uint32_t to = lds_v + set * C::kVBlock;
+      if (first + 32 <= Lk && (first >= len_a || first + 32 <= len_a)) {
+        const bool in_a = first < len_a;
+        const int64_t st = in_a ? C::kRowB : prm.V2.stride_t;
+        const char* base = in_a ? a_v + (int64_t)first * C::kRowB : prm.V2.row(b, h, first - len_a);
 #pragma unroll
-    for (int s = 0; s < C::kSteps; ++s) kf[s] = *reinterpret_cast<const u32x4*>(krow + s * 32);
-    if constexpr (!kPairs) {
+        for (int i = 0; i < 32 / C::kRPI; ++i) dma16(base + i * C::kRPI * st, mrow * (uint32_t)st + piece, to + i * 1024);
+      } else {
+#pragma unroll
+        for (int i = 0; i < 32 / C::kRPI; ++i)
+          dma16_from(key_row(a_v, prm.V2, min(first + i * C::kRPI + mrow, Lk - 1)) + piece, to + i * 1024);
+      }
+    } else {
 #pragma unroll
       for (int i = 0; i < C::kVP; ++i) {
         const int p = lane + i * 64;
         vr[i] = *reinterpret_cast<const u32x4*>(key_row(a_v, prm.V2, min(blk * 32 + p / C::kPPR, Lk - 1)) + p % C::kPPR * 16);
       }
-      return;
     }
+    const char* krow = key_row(a_k, prm.K2, min(blk * 32 + r, Lk - 1)) + g * 16;
 #pragma unroll
-    for (int i = 0; i < C::kVP / 2; ++i) {
-      const int item = lane + i * 64;
-      const int pair = item / C::kPPR, col = item % C::kPPR;
-      const int j0 = min(blk * 32 + 2 * pair, Lk - 1), j1 = min(blk * 32 + 2 * pair + 1, Lk - 1);
-      vr[2 * i] = *reinterpret_cast<const u32x4*>(key_row(a_v, prm.V2, j0) + col * 16);
-      vr[2 * i + 1] = *reinterpret_cast<const u32x4*>(key_row(a_v, prm.V2, j1) + col * 16);
-    }
+    for (int s = 0; s < C::kSteps; ++s) kf[s] = *reinterpret_cast<const u32x4*>(krow + s * 32);
   };
 
   // the first blocks of this wave are asked for before anything else: their latency covers the query loads
   u32x4 kfa[C::kSteps], vra[C::kVP], kfb[C::kSteps], vrb[C::kVP];
-  if (wave < nblk) request(wave, kfa, vra);
-  if (C::kSets == 2 && wave + NW < nblk) request(wave + NW, kfb, vrb);
+  if (wave < nblk) request(wave, kfa, vra, 0);
+  if (C::kSets == 2 && wave + NW < nblk) request(wave + NW, kfb, vrb, 1);
 
   const int q = qt * 32 + r;
   u32x4 qf[C::kSteps];
@@ -365,41 +377,33 @@ __global__ __launch_bounds__((NarrowCfg<T, D, NW>::kThreads)) void attend_narrow
   float m = kNegBig, l = 0.f;
   const float c = prm.c;
   uint32_t* vt32 = reinterpret_cast<uint32_t*>(smem + wave * C::kVtBytes);
+  uint32_t va[C::kDB];  // bf16: this lane's transposing reads of a V block
+#pragma unroll
+  for (int db = 0; db < C::kDB; ++db) va[db] = lds_v + v_read_offset<D>(lane, db);
 
-  auto step = [&](int blk, u32x4 (&kf)[C::kSteps], u32x4 (&vr)[C::kVP]) {
-    // V^T of the block into this wave's LDS tile: a 32-bit word holds keys (2*pair, 2*pair+1) of one element.
-    // The tile is private to the wave; the fences order this block's stores after the previous block's
-    // fragment loads and before this block's.
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    if constexpr (kPairs) {
-#pragma unroll
-      for (int i = 0; i < C::kVP / 2; ++i) {
-        const int item = lane + i * 64;
-        const int pair = item / C::kPPR, col = item % C::kPPR;
-        const u32x4 a = vr[2 * i], bq = vr[2 * i + 1];
-#pragma unroll
-        for (int w = 0; w < 4; ++w) {
-          const int word = (col * 8 + 2 * w) * (kNarrowVS / 2) + (col / 4) * (kNarrowShift / 4) + pair;
-          vt32[word] = (a[w] & 0xFFFFu) | (bq[w] << 16);
-          vt32[word + kNarrowVS / 2] = (a[w] >> 16) | (bq[w] & 0xFFFF0000u);
-        }
-      }
-    } else {
+  auto step = [&](int blk, u32x4 (&kf)[C::kSteps], u32x4 (&vr)[C::kVP], int set) {
+    // fp32: V^T of the block into this wave's LDS tile.  The tile is private to the wave; the fences order this block's
+    // stores after the previous block's fragment loads and before this block's.
+    if constexpr (!kPairs) {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
 #pragma unroll
       for (int i = 0; i < C::kVP; ++i) {
         const int p = lane + i * 64, row = p / C::kPPR, col = p % C::kPPR;
 #pragma unroll
         for (int w = 0; w < 4; ++w) vt32[(col * 4 + w) * kNarrowVS + (col / 8) * (kNarrowShift / 4) + row] = vr[i][w];
       }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
     // S^T = K Q^T: keys on rows, queries on columns
     f32x16 s = f32x16{};
 #pragma unroll
     for (int st = 0; st < C::kSteps; ++st) mfma_step<T>(kf[st], qf[st], s);
-    if (blk + C::kSets * NW < nblk) request(blk + C::kSets * NW, kf, vr);
+    if constexpr (kPairs)
+      asm volatile("" : "+v"(s) : : "memory");  // K has been waited for, and so has V: its reads stay below
+    else if (blk + C::kSets * NW < nblk)
+      request(blk + C::kSets * NW, kf, vr, set);
     const int nvalid = Lk - blk * 32;
     if (nvalid < 32) {
 #pragma unroll
@@ -441,13 +445,15 @@ __global__ __launch_bounds__((NarrowCfg<T, D, NW>::kThreads)) void attend_narrow
         for (int w = 0; w < 4; ++w) pf[w] = pack_bf16x2(s[8 * tp + 2 * w], s[8 * tp + 2 * w + 1]);
 #pragma unroll
         for (int db = 0; db < C::kDB; ++db) {
-          const char* rowp =
-              vt + ((db * 32 + r) * kNarrowVS + 16 * tp + 4 * g) * 2 + db * kNarrowShift;
-          const u32x2 lo = *reinterpret_cast<const u32x2*>(rowp);
-          const u32x2 hi = *reinterpret_cast<const u32x2*>(rowp + 16);
+          const int imm = 16 * tp * C::kRowB;
+          const u32x2 lo = read_transposed(va[db] + set * C::kVBlock, imm), hi = read_transposed(va[db] + set * C::kVBlock, imm + 8 * C::kRowB);
           const u32x4 vf = {lo[0], lo[1], hi[0], hi[1]};
           mfma_step<T>(vf, pf, o[db]);
         }
+      }
+      if (blk + C::kSets * NW < nblk) {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the slot has been read
+        request(blk + C::kSets * NW, kf, vr, set);
       }
     } else {
 #pragma unroll
@@ -466,8 +472,8 @@ __global__ __launch_bounds__((NarrowCfg<T, D, NW>::kThreads)) void attend_narrow
   };
 
   for (int blk = wave; blk < nblk; blk += C::kSets * NW) {
-    step(blk, kfa, vra);
-    if (C::kSets == 2 && blk + NW < nblk) step(blk + NW, kfb, vrb);
+    step(blk, kfa, vra, 0);
+    if (C::kSets == 2 && blk + NW < nblk) step(blk + NW, kfb, vrb, 1);
   }
 
   // ---- merge the waves' partial results through LDS (the V tiles are no longer needed)

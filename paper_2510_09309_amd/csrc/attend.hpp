@@ -2,6 +2,7 @@
 #pragma once
 
 #include "kernels.hpp"
+#include "lds.hpp"
 
 namespace maskkv {
 
@@ -23,6 +24,28 @@ struct AttendParams {
   float* part_o;     // [BH][n_splits][n_q][D]
   float2* part_ml;   // [BH][n_splits][n_q]
 };
+
+// Rows of V (bf16) in LDS as direct transfers leave them: no padding, the 32-byte unit u of a row in slot u ^ v_swizzle(row).  A
+// transposing read takes 32 bytes of four rows per 16 lanes and 64 bytes of four rows per 32 lanes, and both sets fall on
+// different banks.
+template <int D>
+__device__ __forceinline__ uint32_t v_swizzle(uint32_t row) {
+  return D == 128 ? ((row & 3) << 1 | (row & 3) >> 1) : row & 3;
+}
+// Where a lane points for keys 4g .. 4g+3 of the A operand of O^T = V^T P^T, head-dim elements 32 db .. (keys 8 on: 8 rows on).
+template <int D>
+__device__ __forceinline__ uint32_t v_read_offset(uint32_t lane, uint32_t db) {
+  const uint32_t i = lane & 15, row = i >> 2;
+  return (4 * (lane >> 5) + row) * (2 * D) + (((2 * db + ((lane >> 4) & 1)) ^ v_swizzle<D>(row)) << 5) + (i & 3) * 8;
+}
+
+typedef __attribute__((ext_vector_type(4))) short s16x4;
+
+// LDS read of 8 bytes a lane with a transposition inside each group of 16 lanes: lanes 4j .. 4j+3 point at 16 elements of row j,
+// lane i receives element i of rows 0 .. 3.
+__device__ __forceinline__ u32x2 read_transposed(uint32_t addr, int imm) {
+  return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16(in_lds<s16x4>(addr, imm)));
+}
 
 // attend_tiles.hip: the tiled kernel for bf16.
 // Queries per workgroup for `units` heads of n_q query rows.

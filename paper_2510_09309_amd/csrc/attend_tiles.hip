@@ -50,19 +50,9 @@ struct TileCfg {
   static constexpr int kPV = 4 * kDB;               // MFMAs of a tile's output update
   // A direct transfer writes 1 KiB of consecutive LDS, so rows carry no padding; instead a row's pieces are permuted.
   // K: piece p sits in slot p ^ swz_k(row): 16 consecutive rows of a fragment read fall on different 16-byte columns.
-  // V: 32-byte unit u sits in slot u ^ swz_v(row): a transposing read takes 32 bytes of four rows per 16 lanes and 64
-  // bytes of four rows per 32 lanes, and both sets fall on different banks.
+  // V: see v_swizzle.
   __device__ static uint32_t swz_k(uint32_t row) { return D == 128 ? row & 15 : (row >> 1) & 7; }
-  __device__ static uint32_t swz_v(uint32_t row) { return D == 128 ? ((row & 3) << 1 | (row & 3) >> 1) : row & 3; }
 };
-
-typedef __attribute__((ext_vector_type(4))) short s16x4;
-
-// LDS read of 8 bytes a lane with a transposition inside each group of 16 lanes: lanes 4j .. 4j+3 point at 16 elements of row j,
-// lane i receives element i of rows 0 .. 3.
-__device__ __forceinline__ u32x2 read_transposed(uint32_t addr, int imm) {
-  return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16(in_lds<s16x4>(addr, imm)));
-}
 
 template <int D, bool HALVES>
 __global__ __launch_bounds__(kWaves * 64) void attend_tiles_kernel(const AttendParams prm) {
@@ -137,7 +127,7 @@ __global__ __launch_bounds__(kWaves * 64) void attend_tiles_kernel(const AttendP
   };
   // K's permutation depends on the transfer j by one exclusive-or (j * kRPI and the lane's row are row bits side by side, and
   // the permutation of j rows of transfers is j times that of one), V's does not.
-  const uint32_t ksw = C::swz_k(part * C::kMoveRows + mrow), vsw = C::swz_v(mrow) << 1;
+  const uint32_t ksw = C::swz_k(part * C::kMoveRows + mrow), vsw = v_swizzle<D>(mrow) << 1;
   auto ring = [&](int t) { return HALVES ? (second ? 2 : 0) + (t & 1) : t & 3; };
   auto move_k = [&](int t) {
     move(a_k, rest_k, prm.K2.stride_t, t, lds0 + ring(t) * C::kTileB, ksw, C::swz_k(C::kRPI) << 4);
@@ -165,12 +155,8 @@ __global__ __launch_bounds__(kWaves * 64) void attend_tiles_kernel(const AttendP
   uint32_t ka[C::kSteps], va[C::kDB];
 #pragma unroll
   for (int i = 0; i < C::kSteps; ++i) ka[i] = own + r * C::kRowB + (((2 * i + g) ^ C::swz_k(r)) << 4);
-  {
-    const uint32_t i = lane & 15, row = i >> 2;
 #pragma unroll
-    for (int db = 0; db < C::kDB; ++db)
-      va[db] = own + 4 * C::kTileB + (4 * g + row) * C::kRowB + (((2 * db + ((lane >> 4) & 1)) ^ C::swz_v(row)) << 5) + (i & 3) * 8;
-  }
+  for (int db = 0; db < C::kDB; ++db) va[db] = own + 4 * C::kTileB + v_read_offset<D>(lane, db);
 #pragma unroll
   for (int i = 0; i < C::kSteps; ++i) asm volatile("" : "+v"(ka[i]));
 #pragma unroll
