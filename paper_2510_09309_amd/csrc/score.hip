@@ -424,33 +424,37 @@ __global__ __launch_bounds__(256) void score_group_sum_kernel(const ScoreParams 
 }
 
 // Prompt mass as the sum of a head's scores (the column sums of the prompt columns add up to the prompt's share of
-// the voting rows' attention), for calls that do not run pass 1: one 1024-thread workgroup per (b, h), eight
+// the voting rows' attention), for calls that do not run pass 1: one 1024-thread workgroup per (b, h), 32
 // independent loads in flight per thread, fixed summation order.
 constexpr int kMassThreads = 1024;
 
 __global__ __launch_bounds__(kMassThreads) void score_mass_kernel(const ScoreParams prm) {
-  __shared__ float red[kMassThreads];
+  constexpr int kInFlight = 32;  // (a whole 32k prompt at once: the loop's round trips are what a head's sum waits for)
+  __shared__ float red[kMassThreads / 64];
   const int bh = blockIdx.x;
   const int P = prm.lens.P[bh / prm.H];
   const float* row = prm.scores + (int64_t)bh * prm.score_stride;
   float acc = 0.f;
-  for (int j0 = threadIdx.x; j0 < P; j0 += 8 * kMassThreads) {
-    float v[8];
+  for (int j0 = threadIdx.x; j0 < P; j0 += kInFlight * kMassThreads) {
+    float v[kInFlight];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
+    for (int u = 0; u < kInFlight; ++u) {
       const int j = j0 + u * kMassThreads;
       v[u] = j < P ? row[j] : 0.f;
     }
 #pragma unroll
-    for (int u = 0; u < 8; ++u) acc += v[u];
+    for (int u = 0; u < kInFlight; ++u) acc += v[u];
   }
-  red[threadIdx.x] = acc;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
   __syncthreads();
-  for (int s = kMassThreads / 2; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-    __syncthreads();
+  if (threadIdx.x < 64) {
+    float v = threadIdx.x < kMassThreads / 64 ? red[threadIdx.x] : 0.f;
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    if (threadIdx.x == 0) prm.prompt_mass[bh] = v;
   }
-  if (threadIdx.x == 0) prm.prompt_mass[bh] = red[0];
 }
 
 int tile_keys(const maskkv_desc*) { return 64; }  // every configuration uses 64-key tiles
