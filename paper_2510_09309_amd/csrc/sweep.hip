@@ -138,11 +138,14 @@ __global__ __launch_bounds__(kThreads) void sweep_start_kernel(const SweepParams
   const int P = prm.lens.P[b];
   const char* keys = prm.K.row(b, h, P);
   auto dma = [&](int t) {
+    // (a tile's rows are up to 127 x 16 MiB apart and fit 32 bits, those of the whole span do not)
+    const char* base = keys + (int64_t)(t * kKeys) * prm.K.stride_t;
+    const int last = prm.n_resp - 1 - t * kKeys;
 #pragma unroll
     for (int j = 0; j < C::kMoves; ++j) {
       const int row = wave * (kKeys / kWaves) + j * C::kRPI + lane / C::kPPR;
       const int piece = (lane % C::kPPR) ^ C::swz(row);
-      dma16(keys, (uint32_t)min(row + t * kKeys, prm.n_resp - 1) * (uint32_t)prm.K.stride_t + piece * 16,
+      dma16(base, (uint32_t)min(row, last) * (uint32_t)prm.K.stride_t + piece * 16,
             lds0 + (t & 1) * C::kKBytes + (wave * (kKeys / kWaves) + j * C::kRPI) * C::kRowB);
     }
   };

@@ -86,3 +86,27 @@ def test_calls_on_two_streams_at_once():
         assert torch.allclose(g[1], w[1], rtol=5e-6, atol=0)
     after = hp.gpu_score(batches[0])     # the device is free again
     assert torch.equal(after[0][:, :batches[0].P[0]], want[0][0][:, :batches[0].P[0]])
+
+
+@pytest.mark.parametrize("d,P,n_m,row_bytes", [(128, 40, 300, 1 << 24), (64, 200, 260, 1 << 24), (128, 60, 8230, 1 << 19)])
+def test_response_rows_more_than_4_gib_apart(d, P, n_m, row_bytes):
+    """Token strides up to 16 MiB: the response span of one head may reach over more than 32 bits of offset."""
+    m = hp.mk()
+    n_q = 40
+    L = synth.make_layer(93, H=1, d=d, P=P, n_m=n_m, dtype="bf16", n_planted=0, amplitude=0.0, query_shift=4.0)
+    for h in range(L.H):     # rows differ along the response span, so that rows read twice or not at all show
+        L.K[h, P:] += (np.linspace(0.0, 4.0, n_m, dtype=np.float32) * np.float32(np.sqrt(d) / 4.0))[:, None] * L.u[h]
+    L.K[:] = synth.round_to_bf16(L.K)
+    wide = torch.empty((P + n_m, row_bytes // 2), dtype=torch.bfloat16, device="cuda")
+    K = wide[:, :d]
+    K.copy_(torch.from_numpy(L.K[0]).to("cuda"))
+    Q = hp.upload(L.Q[None, :, :n_q], "bf16")
+    desc = m.Desc(B=1, H=1, d=d, dtype=m.MASKKV_BF16, n_resp=n_m, P_max=P, n_query=n_q)
+    scores = torch.full((1, 256), float("nan"), device="cuda")
+    mass = torch.zeros(1, device="cuda")
+    m.maskkv_score(desc, Q, K[None, None], 0.0, scores, 256, mass, hp.workspace(m.maskkv_score_workspace_bytes(desc)))
+    I, want = orc.score(L.Q[0, :n_q], L.K[0], P)
+    got = scores[0, :P].double().cpu().numpy()
+    # raw logits below 100 in fp32 are 2^-17 coarse at most: some 1e-5 of an exponential, and rows read wrongly are off by 0.1
+    assert np.abs(got / I - 1).max() <= 1e-4
+    assert abs(float(mass[0]) / want - 1) <= 1e-4
