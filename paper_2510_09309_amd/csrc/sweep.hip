@@ -5,8 +5,9 @@
 // voting rows, keeps them in registers (64 per lane), publishes the chunk's row sums, forms the next chunk, and by then
 // the row sums of all chunks of that unit have arrived and the kept chunk is turned into column sums.
 //
-//   start kernel  row references (the response span's log-sum-exp, which is also the rows' sum over the response keys), zeroed
-//                 sums, and the voting rows packed in MFMA fragment order.
+//   start kernel  row references (the response span's log-sum-exp), the rows' sums over the response keys in units of them (1
+//                 but for the rounding of the reference) as the initial values of the sums, and the voting rows packed in
+//                 MFMA fragment order.
 //   sweep kernel  one workgroup of eight waves (32 rows each) per compute unit; chunk x of the launch, all units end to
 //                 end, belongs to workgroup x mod G, so that the workgroups work on the same unit at the same time.
 //
@@ -51,6 +52,18 @@ constexpr float kHighScale = 16.f;         // 2^4
 constexpr float kHighLimit = 1099511627776.f;  // 2^40 (kMaxGroups chunks of either limit stay below 2^54)
 constexpr uint64_t kPatience = 2000000;    // 20 ms of the 100 MHz clock
 
+// A row's mass is its prompt sum over its whole sum.  The former comes out of the exchange with an error of about 1e-8 (256
+// chunks rounded to units of 2^-28) and of the rounding of the row's reference, 1e-7 to 1e-6 of the response span's sum: below fp32's
+// own error only as long as the prompt's share is not small.  Where more of a wave's 32 rows have a whole sum below kSmallSum than
+// above, the mass of these rows is taken from the column sums instead, which are as accurate as fp32 however small they are:
+// that wave of every chunk's workgroup (all see the same row sums, so they agree) leaves the sum of its part of the column
+// sums, and the workgroup of the unit's leading chunk adds these up in a fixed order after its walk.  (Within what two runs
+// differ by, a call without such waves takes the time it took when every mass came from the row sums.)
+constexpr float kSmallSum = 2.f;
+constexpr float kNoRow = 0.5f;             // whole sum of a row that does not exist (its mass is then cut off at 0; a row that does has 1)
+constexpr uint32_t kNoPart = 0xFFFFFFFFu;  // not there (a part has its sign bit clear)
+
+constexpr int kMaxUnits = 16384;           // of a launch, see sweep_wanted
 constexpr int kMaxGroups = 256;            // workgroups of a sweep, and chunks of a unit, at most (one per compute unit)
 
 struct Control {
@@ -74,10 +87,14 @@ struct SweepParams {
   float c;          // scale * log2(e)
   uint64_t* low;    // [units][kCopies][256]
   uint64_t* high;   // [units][256]
-  float* start;     // [units][256]: minus the response span's log-sum-exp, in units of the raw logits
+  float* start;     // [units][8 waves][2][32]: the rows' references, minus the response span's log-sum-exp in units of the raw
+                    // logits; and the sums of the response span in units of these references, 1 but for their rounding
   char* qpack;      // [units][8 waves] 32 rows in MFMA fragment order
   Control* ctl;
   int* spans_done;  // [units] spans of the unit whose statistics are there (fallback)
+  uint32_t* parts;  // [units][8 waves][n_parts] bits of a chunk's part of the mass of 32 rows, or kNoPart
+  int n_parts;      // chunks of the longest prompt
+  int* late;        // [units] 1 + the next unit of a workgroup's list for late_masses, or 0
   float2* stats;    // [units][kSpans][256] (reference, sum) of a span of chunks (fallback)
   float* out;       // [units][out_stride]: the scores, or with more than one query group the groups' column sums
   int64_t out_stride;
@@ -104,7 +121,8 @@ struct Cfg {
   static constexpr int kOffW = kOffCs + 2 * kWaves * kKeys * 4;  // [kWaves][32] floats
   static constexpr int kOffInf = kOffW + kWaves * 128;         // 32 floats: -inf
   static constexpr int kOffMass = kOffInf + 128;               // [2][kWaves] floats
-  static constexpr int kOffBad = kOffMass + 2 * kWaves * 4;    // one int
+  static constexpr int kOffBad = kOffMass + 2 * kWaves * 4;    // one int: the scores of this workgroup are void
+  static constexpr int kOffLate = kOffBad + 4;                 // one int: 1 + the first unit that late_masses has to do, or 0
   static constexpr int kLds = kOffBad + 64;
   // Rows are stored without padding (a direct transfer writes 1 KiB of consecutive LDS); piece p of row r sits in
   // slot p ^ swz(r), which spreads the fragment reads of 16 consecutive rows over all banks.
@@ -115,9 +133,37 @@ __device__ __forceinline__ uint64_t peek(Base b, uint32_t off) {
   return __hip_atomic_load(at<uint64_t>(b, off), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+__device__ __forceinline__ bool mostly_small(float L) {  // the same in every lane of a wave
+  const uint64_t small = __ballot(fabsf(L - 0.5f * (0.75f + kSmallSum)) < 0.5f * (kSmallSum - 0.75f));  // (but not kNoRow)
+  return __popcll(small) > __popcll(__ballot(L >= kSmallSum));
+}
+__device__ __forceinline__ float row_mass(float L, float inv) { return fmaxf(L - 1.f, 0.f) * inv; }
+// the reciprocal of a row's sum
+__device__ __forceinline__ float reciprocal(float L) {
+  const float w = __builtin_amdgcn_rcpf(L);
+  return fmaf(fmaf(-L, w, 1.f), w, w);
+}
+__device__ __forceinline__ float whole(uint64_t v) {  // an exchanged sum without the count
+  return fmaf((float)((uint32_t)(v >> 32) & ((1u << (kCountShift - 32)) - 1)), 4294967296.f, (float)(uint32_t)v);
+}
+
 template <int CTRL>
 __device__ __forceinline__ float dpp(float v) {
   return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, false));
+}
+
+// The sum over a wave, in every lane, without the LDS.
+__device__ __forceinline__ float wave_sum(float v) {
+  v += dpp<0xB1>(v);   // neighbours
+  v += dpp<0x4E>(v);   // pairs
+  v += dpp<0x141>(v);  // half rows, mirrored
+  v += dpp<0x140>(v);  // rows of 16, mirrored
+  const auto a = __builtin_amdgcn_permlane16_swap(as_u32(v), as_u32(v), false, false);
+  const unsigned a0 = a[0], a1 = a[1];
+  v = as_f32(a0) + as_f32(a1);
+  const auto b = __builtin_amdgcn_permlane32_swap(as_u32(v), as_u32(v), false, false);
+  const unsigned b0 = b[0], b1 = b[1];
+  return as_f32(b0) + as_f32(b1);
 }
 
 // ---- response span: row references, zeroed sums, and the voting rows in the order in which the sweep reads them.
@@ -175,9 +221,10 @@ __global__ __launch_bounds__(kThreads) void sweep_start_kernel(const SweepParams
   if (part_of == 0) {
     if (lane < 32) {
 #pragma unroll
-      for (int i = 0; i < kCopies; ++i) prm.low[((int64_t)unit * kCopies + i) * kRows + rb * 32 + lane] = 0;
+      for (int i = 1; i < kCopies; ++i) prm.low[((int64_t)unit * kCopies + i) * kRows + rb * 32 + lane] = 0;
       prm.high[row0 + lane] = 0;
     }
+    for (int i = lane; i < ceil_div(P, kKeys); i += 64) prm.parts[((int64_t)unit * kWaves + rb) * prm.n_parts + i] = kNoPart;
     u32x4* pack = reinterpret_cast<u32x4*>(prm.qpack + row0 * C::kRowB) + lane;
 #pragma unroll
     for (int s = 0; s < S; ++s) pack[s * 64] = qf[s];
@@ -233,7 +280,16 @@ __global__ __launch_bounds__(kThreads) void sweep_start_kernel(const SweepParams
       m = M;
       l = L;
     }
-    prm.start[row0 + lane] = rb * 32 < prm.rows && q0 + lane < prm.n_query ? -(m + __log2f(l)) / prm.c : -INFINITY;
+    // The logarithm and its sum with m carry what they lost along; what the rounding of the reference itself loses is in `own`.
+    const float lg = __log2f(l), near1 = l * fast_exp2(-lg);
+    const float sum = m + lg, back = sum - m;
+    const float lost = (m - (sum - back)) + (lg - back);
+    const bool live = rb * 32 < prm.rows && q0 + lane < prm.n_query;
+    const float ref = -(sum + (lost + (near1 - 1.f) * kLog2e)) / prm.c;
+    const float own = live ? near1 * fast_exp2(fmaf(ref, prm.c, sum) + lost) : kNoRow;
+    prm.start[row0 * 2 + lane] = live ? ref : -INFINITY;
+    prm.start[row0 * 2 + 32 + lane] = own;
+    prm.low[(int64_t)unit * kCopies * kRows + rb * 32 + lane] = (uint64_t)rintf(own * kLowScale);
   }
 }
 
@@ -278,8 +334,9 @@ __device__ __forceinline__ void sweep_redo(const SweepParams& prm, uint32_t lds0
       }
       __syncthreads();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-      // all spans and the response span (whose sum is 1 in units of its own log-sum-exp)
-      const float ref = -prm.start[row0 + r] * prm.c;  // +inf for a row that does not exist
+      // all spans and the response span
+      const float ref = -prm.start[row0 * 2 + r] * prm.c;  // +inf for a row that does not exist
+      const float own = prm.start[row0 * 2 + 32 + r];
       const bool live = ref != INFINITY;
       float M = live ? ref : 0.f, Lp = 0.f;
       float2 v[kSpans];
@@ -291,7 +348,7 @@ __device__ __forceinline__ void sweep_redo(const SweepParams& prm, uint32_t lds0
       }
 #pragma unroll
       for (int i = 0; i < kSpans; ++i) Lp += v[i].y * fast_exp2(v[i].x - M);
-      const float L = Lp + fast_exp2(ref - M);
+      const float L = fmaf(own, fast_exp2(ref - M), Lp);
       const float nlse = live ? -(M + __log2f(L)) : -INFINITY;
       if (span == 0 && prm.mass) {
         float mass = live && g == 0 ? Lp / L : 0.f;
@@ -381,7 +438,70 @@ __device__ __forceinline__ void sweep_redo(const SweepParams& prm, uint32_t lds0
 // A chunk: number ci of the nc of its unit.
 struct Chunk {
   int unit, ci, nc, P;
+  // the chunk whose workgroup writes the unit's mass (not always the first, so that they are spread over workgroups)
+  __device__ int lead() const { return (unit & 15) < nc ? unit & 15 : 0; }
 };
+
+// After the walk: the masses of the units whose leading chunk was this workgroup's and that have waves with mostly small row sums.
+template <int D>
+__device__ __forceinline__ void late_masses(const SweepParams& prm, uint32_t lds0, int head) {
+  using C = Cfg<D>;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");  // (this workgroup's own parts and its list are there)
+  while (head) {
+    const int unit = head - 1;
+    head = __builtin_amdgcn_readfirstlane(__hip_atomic_load(&prm.late[unit], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    const int nc = ceil_div(prm.lens.P[unit / (prm.H * prm.nqg)], kKeys);
+    const int lead = Chunk{unit, 0, nc, 0}.lead();
+    const uint32_t* part = prm.parts + ((int64_t)unit * kWaves + wave) * prm.n_parts;
+    const uint64_t t0 = wall_clock64();
+    float sum = 0.f;
+    while (wave * 32 < prm.rows) {
+      uint32_t u[kMaxGroups / 64];
+#pragma unroll
+      for (int j = 0; j < kMaxGroups / 64; ++j) {
+        u[j] = 0;
+        if (j * 64 + lane < nc) u[j] = __hip_atomic_load(part + j * 64 + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+      if (__all(__hip_atomic_load(part + lead, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == kNoPart)) {  // not one of those waves
+        const int64_t row = (int64_t)unit * kRows + wave * 32 + lane / 2;
+        uint64_t lo = 0;
+#pragma unroll
+        for (int j = 0; j < kCopies; ++j)
+          lo += __hip_atomic_load(prm.low + (int64_t)unit * (kCopies - 1) * kRows + row + j * kRows, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const uint64_t hi = __hip_atomic_load(prm.high + row, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const float L = fmaf(whole(hi), 1.f / kHighScale, whole(lo) * (1.f / kLowScale));
+        sum = lane % 2 ? 0.f : row_mass(L, reciprocal(L));
+        break;
+      }
+      sum = 0.f;
+      bool there = true;
+#pragma unroll
+      for (int j = 0; j < kMaxGroups / 64; ++j) {
+        there = there && u[j] != kNoPart;
+        sum += as_f32(u[j]);
+      }
+      if (__all(there)) break;
+      if (wall_clock64() - t0 >= kPatience || __any(__hip_atomic_load(&prm.ctl->redo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) {
+        __hip_atomic_store(&prm.ctl->redo, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        *in_lds<int>(lds0 + C::kOffBad) = 1;
+        break;
+      }
+      __builtin_amdgcn_s_sleep(8);
+    }
+    sum = wave_sum(sum);
+    if (lane == 0) *in_lds<float>(lds0 + C::kOffMass + wave * 4) = sum;
+    __syncthreads();
+    if (threadIdx.x == 0 && !*in_lds<const int>(lds0 + C::kOffBad)) {
+      float m = 0.f;
+#pragma unroll
+      for (int w = 0; w < kWaves; ++w) m += *in_lds<const float>(lds0 + C::kOffMass, w * 4);
+      prm.mass[unit] = m;
+    }
+    __syncthreads();
+  }
+}
 
 template <int D>
 __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t lds0) {
@@ -446,7 +566,7 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
     }
   };
   auto dma_start = [&](const Chunk& k, int par) {
-    dma4(reinterpret_cast<const char*>(prm.start + (int64_t)k.unit * kRows + wave * 32), here(lane16) >> 2,
+    dma4(reinterpret_cast<const char*>(prm.start + ((int64_t)k.unit * kRows + wave * 32) * 2), here(lane16) >> 2,
          lds0 + C::kOffStart + (par * kWaves + wave) * 256);
   };
   u32x4 qf[S];
@@ -535,12 +655,17 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
     for (int w = 1; w < kWaves; ++w) v += *in_lds<const float>(cs, w * kKeys * 4);
     const Base out = base_of(prm.out + (int64_t)k.unit * prm.out_stride + k.ci * kKeys);
     if (col < k.P - k.ci * kKeys) *at<float>(out, col * 4) = v;
-    if (k.ci == 0 && col == 0 && prm.mass) {
+    if (k.ci == k.lead() && col == 0 && prm.mass) {
       const uint32_t ms = lds0 + C::kOffMass + par * kWaves * 4;
       float m = 0.f;
 #pragma unroll
       for (int w = 0; w < kWaves; ++w) m += *in_lds<const float>(ms, w * 4);
-      prm.mass[k.unit] = m;
+      if (m >= 0.f) {
+        prm.mass[k.unit] = m;
+      } else if (m < 0.f) {  // (not known yet)
+        __hip_atomic_store(&prm.late[k.unit], *in_lds<const int>(lds0 + C::kOffLate), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        *in_lds<int>(lds0 + C::kOffLate) = k.unit + 1;
+      }
     }
   };
 
@@ -552,7 +677,8 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
     for (int i = 0; i < kCopies; ++i) seen[i] = peek(base_of(low + i * kRows), off);
     asm volatile("" ::: "memory");
   };
-  auto add = [&](const uint64_t* to, float f) {  // one chunk and the whole number f < 2^44
+  auto add = [&](const uint64_t* to, float f) {  // one chunk and the whole number next to f < 2^44
+    f = rintf(f);
     const float top = floorf(f * 2.3283064365386963e-10f);  // 2^-32
     const uint32_t hi = (uint32_t)top + (1u << (kCountShift - 32));
     const uint32_t lo = (uint32_t)fmaf(top, -4294967296.f, f);
@@ -618,20 +744,16 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
       if (!ready || (__any(hi != 0) && __hip_atomic_load(&prm.ctl->redo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)))
         *in_lds<int>(lds0 + C::kOffBad) = 1;
     }
-    auto whole = [](uint64_t v) {  // the sum without the count
-      return fmaf((float)((uint32_t)(v >> 32) & ((1u << (kCountShift - 32)) - 1)), 4294967296.f, (float)(uint32_t)v);
-    };
-    float L = fmaf(whole(lo), 1.f / kLowScale, 1.f);
+    float L = whole(lo) * (1.f / kLowScale);
     if (__any(hi != 0)) L = fmaf(whole(hi), 1.f / kHighScale, L);
-    float w_row = __builtin_amdgcn_rcpf(L);
-    w_row = fmaf(fmaf(-L, w_row, 1.f), w_row, w_row);
+    const float w_row = reciprocal(L);
     const uint32_t wt = lds0 + C::kOffW + wave * 128;
     *in_lds<float>(wt + row8 / 2) = w_row;
-    if (k.ci == 0) {
+    const bool small = mostly_small(L);
+    if (k.ci == k.lead()) {  // the mass of this wave's rows, or a mark that it is not known yet
       const int ln = lane_now();
-      float ms = (ln & 1) ? 0.f : (L - 1.f) * w_row;
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) ms += __shfl_xor(ms, o, 64);
+      float ms = wave_sum((ln & 1) ? 0.f : row_mass(L, w_row));
+      if (small) ms = -1e30f;
       if (ln == 0) *in_lds<float>(lds0 + C::kOffMass + (par * kWaves + wave) * 4) = ms;
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -653,6 +775,12 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
         b = fmaf(pc[kb][i + 1], w[i + 1], b);
       }
       col[kb] = a + b;
+    }
+    if (__builtin_expect(small, 0)) {
+      const float t = wave_sum((col[0] + col[1]) + (col[2] + col[3]));
+      if (lane_now() == 0)
+        __hip_atomic_store(prm.parts + ((int64_t)k.unit * kWaves + wave) * prm.n_parts + k.ci, as_u32(t) & 0x7FFFFFFFu, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
     }
     const uint32_t cs = lds0 + C::kOffCs + (par * kWaves + wave) * kKeys * 4 + lane16 / 4;
 #pragma unroll
@@ -679,7 +807,7 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
   }
   next = ahead;
   if (threadIdx.x < 32) *in_lds<float>(lds0 + C::kOffInf + threadIdx.x * 4) = -INFINITY;
-  if (threadIdx.x == 0) *in_lds<int>(lds0 + C::kOffBad) = 0;
+  if (threadIdx.x < 2) *in_lds<int>(lds0 + C::kOffBad + threadIdx.x * 4) = 0;  // and kOffLate
   for (int i = threadIdx.x; i < 2 * kWaves * kKeys; i += kThreads) *in_lds<float>(lds0 + C::kOffCs + i * 4) = 0.f;
   if (threadIdx.x < 2 * kWaves) *in_lds<float>(lds0 + C::kOffMass + threadIdx.x * 4) = 0.f;
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
@@ -806,7 +934,12 @@ __global__ __launch_bounds__(kThreads, 2) void sweep_kernel(const SweepParams pr
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
   const bool run = prm.ctl->run;  // (if not, another call's sweep is running on this device)
   if (threadIdx.x == 0) __hip_atomic_store(&prm.ctl->started[blockIdx.x], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  if (run) sweep_chunks<D>(prm, lds0);
+  if (run) {
+    sweep_chunks<D>(prm, lds0);
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    const int late = __builtin_amdgcn_readfirstlane(*in_lds<const int>(lds0 + Cfg<D>::kOffLate));
+    if (__builtin_expect(late, 0)) late_masses<D>(prm, lds0, late);
+  }
   if (__hip_atomic_load(&prm.ctl->redo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) sweep_redo<D>(prm, lds0);
   // The lock is given back once every workgroup has been placed: from then on they cannot be kept waiting for each other.
   if (run && blockIdx.x == 0 && threadIdx.x < 64) {
@@ -834,16 +967,20 @@ int cus() {
 size_t pad256(size_t n) { return (n + 255) / 256 * 256; }
 
 struct Layout {
-  size_t control, low, high, start, mass, done, qpack, stats, bytes;  // offsets from the start of the area
+  size_t control, low, high, start, mass, done, late, parts, qpack, stats, bytes;  // offsets from the start of the area
+  int n_parts;
   Layout(const maskkv_desc* d, int nqg) {
     const size_t units = (size_t)d->B * d->H * nqg;
     control = 0;
     low = pad256(sizeof(Control));
     high = low + units * kCopies * kRows * sizeof(uint64_t);
     start = high + units * kRows * sizeof(uint64_t);
-    mass = start + units * kRows * sizeof(float);
+    mass = start + units * kRows * 2 * sizeof(float);
     done = mass + units * sizeof(float);
-    qpack = pad256(done + units * sizeof(int));
+    n_parts = (d->P_max + kKeys - 1) / kKeys;
+    late = done + units * sizeof(int);
+    parts = late + units * sizeof(int);
+    qpack = pad256(parts + units * kWaves * n_parts * sizeof(uint32_t));
     stats = qpack + units * kRows * d->d * 2;
     bytes = stats + units * kSpans * kRows * sizeof(float2);
   }
@@ -925,7 +1062,11 @@ int launch(const maskkv_desc* d, const SweepParams& prm, hipStream_t stream) {
 
 }  // namespace
 
-bool sweep_wanted(const maskkv_desc* d, const Lens& lens, int nqg) { return d->dtype == MASKKV_BF16 && Plan(d, lens, nqg).faster; }
+// A launch of 66000 units (33000 heads of 40 keys, 300 voting rows), once tried, ended in a memory fault whose cause was not found.
+// The sweep is kept to a quarter of that, where no array of the workspace is larger than 2^30 bytes; more take the two passes.
+bool sweep_wanted(const maskkv_desc* d, const Lens& lens, int nqg) {
+  return d->dtype == MASKKV_BF16 && (int64_t)d->B * d->H * nqg <= kMaxUnits && Plan(d, lens, nqg).faster;
+}
 
 size_t sweep_workspace_bytes(const maskkv_desc* d, int nqg) { return Layout(d, nqg).bytes; }
 
@@ -952,6 +1093,9 @@ int launch_sweep(const maskkv_desc* d, const View& Q, const View& K, const Lens&
   char* base = reinterpret_cast<char*>(area);
   prm.ctl = reinterpret_cast<Control*>(base + l.control);
   prm.spans_done = reinterpret_cast<int*>(base + l.done);
+  prm.parts = reinterpret_cast<uint32_t*>(base + l.parts);
+  prm.n_parts = l.n_parts;
+  prm.late = reinterpret_cast<int*>(base + l.late);
   prm.stats = reinterpret_cast<float2*>(base + l.stats);
   prm.low = reinterpret_cast<uint64_t*>(base + l.low);
   prm.high = reinterpret_cast<uint64_t*>(base + l.high);
