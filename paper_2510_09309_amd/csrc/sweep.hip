@@ -43,13 +43,13 @@ constexpr int kCopies = 4;                 // of every row's `low` sum: workgrou
 
 // Row sums are exchanged as integers, so that their total does not depend on the order of arrival: 10 bits count the chunks
 // that have been added, 54 bits hold the sum in units of 2^-28 of the response span's own sum (`low`) or, for a chunk
-// whose sum is above 2^16 of it, in units of 2^-4 (`high`).
+// whose sum is 2^16 of it or more, in units of 2^-7 (`high`), which are the last place of such a sum in fp32 or smaller.
 constexpr int kCountShift = 54;
 constexpr uint64_t kSumMask = (1ull << kCountShift) - 1;
 constexpr float kLowScale = 268435456.f;   // 2^28
 constexpr float kLowLimit = 65536.f;       // 2^16
-constexpr float kHighScale = 16.f;         // 2^4
-constexpr float kHighLimit = 1099511627776.f;  // 2^40 (kMaxGroups chunks of either limit stay below 2^54)
+constexpr float kHighScale = 128.f;        // 2^7
+constexpr float kHighLimit = 549755813888.f;  // 2^39 (kMaxGroups chunks below either limit stay below 2^54 units)
 constexpr uint64_t kPatience = 2000000;    // 20 ms of the 100 MHz clock
 
 // A row's mass is its prompt sum over its whole sum.  The former comes out of the exchange with an error of about 1e-8 (256
@@ -677,7 +677,7 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
     for (int i = 0; i < kCopies; ++i) seen[i] = peek(base_of(low + i * kRows), off);
     asm volatile("" ::: "memory");
   };
-  auto add = [&](const uint64_t* to, float f) {  // one chunk and the whole number next to f < 2^44
+  auto add = [&](const uint64_t* to, float f) {  // one chunk and the whole number next to f < 2^46
     f = rintf(f);
     const float top = floorf(f * 2.3283064365386963e-10f);  // 2^-32
     const uint32_t hi = (uint32_t)top + (1u << (kCountShift - 32));

@@ -162,6 +162,24 @@ def test_prompt_mass_of_heads_of_all_kinds(P, n_m):
         assert abs(float(mass[h].double().cpu()) / want - 1.0) <= 32 * 2.0 ** -24
 
 
+@pytest.mark.parametrize("P,H,lo,hi", [(100, 64, 16.2, 16.9), (128, 64, 16.2, 16.9), (129, 32, 15.5, 16.5), (1000, 16, 30.0, 36.0), (32768, 2, 38.3, 38.6)])
+def test_row_sums_in_the_wide_unit(P, H, lo, hi):
+    """Chunks whose row sums are 2^lo .. 2^hi of the response span's, up to 256 of them just below the limit of the exchange: the
+    unit of the exchange is no coarser than fp32, so a row's scores add up to its mass."""
+    L = synth.make_layer(97, H=H, d=128, P=P, n_m=1, dtype="bf16", n_planted=0, amplitude=0.0, query_shift=4.0)
+    for h, bits in zip(range(H), np.linspace(lo, hi, H)):
+        along = float(L.Q[h, 0] @ L.u[h]) / np.sqrt(L.d)        # a key moved by x along u gains x * along
+        L.K[h, :P] += np.float32((bits * np.log(2.0) - np.log(min(P, 128))) / along) * L.u[h]
+    L.K[:] = synth.round_to_bf16(L.K)
+    batch = hp.Batch([L])
+    scores, mass = hp.gpu_score(batch)
+    for h in range(H):
+        want = orc.score(L.Q[h], L.K[h], P)[1]
+        # a chunk's sum, the exchanged sum, its reciprocal and the weighted sums are rounded to 2^-25 each or better
+        assert abs(float(scores[h, :P].double().sum().cpu()) / want - 1.0) <= 4 * 2.0 ** -24
+        assert abs(float(mass[h].double().cpu()) / want - 1.0) <= 4 * 2.0 ** -24
+
+
 @pytest.mark.skip(reason="ended in a memory fault of the GPU whose cause is not known; the sweep no longer takes launches of this size")
 def test_many_heads_of_one_chunk():
     """33000 heads of one chunk and two groups of voting rows: 66000 units, of which every
