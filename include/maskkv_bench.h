@@ -60,6 +60,14 @@ int maskkv_bench_score_marked(const maskkv_desc* desc, const maskkv_tensor* Q_ma
                               float scale, float* scores, int64_t score_stride, float* prompt_mass,
                               void* workspace, size_t workspace_bytes, void* stream, void* const* events);
 
+/*
+ * Enqueues a kernel that marks the single sweep of maskkv_score (see there) as taken age_us microseconds ago on the
+ * stream's device, as by another call that has not ended; age_us < 0 marks it as free.  A call of maskkv_score that
+ * finds it taken takes the fallback, unless the mark is more than a second old.  For tests and for timing the
+ * fallback; free the mark afterwards.
+ */
+int maskkv_bench_hold_sweep(int64_t age_us, void* stream);
+
 #ifdef __cplusplus
 }
 #endif

@@ -12,7 +12,7 @@ from . import binding as _b
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.environ.get("MASKKV_BENCH_LIB_PATH", os.path.join(_HERE, "libmaskkv_bench.so"))
-SYMBOLS = ["maskkv_bench_last_error", "maskkv_bench_probe", "maskkv_bench_score_marked"]
+SYMBOLS = ["maskkv_bench_last_error", "maskkv_bench_probe", "maskkv_bench_score_marked", "maskkv_bench_hold_sweep"]
 
 
 def _load() -> ct.CDLL:
@@ -54,6 +54,11 @@ def maskkv_bench_score_marked(desc: "_b.Desc", Q_mask, K_full, scale: float, sco
     _b._check(_lib.maskkv_bench_score_marked(ct.byref(desc.c()), ct.byref(q), ct.byref(k), ct.c_float(scale),
                                              _b._ptr(scores), ct.c_int64(score_stride), _b._ptr(prompt_mass), wp, wn,
                                              _b._stream(stream), ev), "maskkv_bench_score_marked")
+
+
+def maskkv_bench_hold_sweep(age_us: int, stream=None) -> None:
+    """Mark the device's sweep as taken ``age_us`` microseconds ago (negative: as free)."""
+    _b._check(_lib.maskkv_bench_hold_sweep(ct.c_int64(age_us), _b._stream(stream)), "maskkv_bench_hold_sweep")
 
 
 def raw_library() -> ct.CDLL:

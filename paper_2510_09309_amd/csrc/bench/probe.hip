@@ -342,6 +342,8 @@ int maskkv_bench_probe(int which, int32_t iters, const void* src, void* dst, int
   }
 }
 
+int maskkv_bench_hold_sweep(int64_t age_us, void* stream) { return hold_sweep(age_us, reinterpret_cast<hipStream_t>(stream)); }
+
 int maskkv_bench_score_marked(const maskkv_desc* desc, const maskkv_tensor* Q_mask, const maskkv_tensor* K_full,
                               float scale, float* scores, int64_t score_stride, float* prompt_mass, void* workspace,
                               size_t workspace_bytes, void* stream, void* const* events) {

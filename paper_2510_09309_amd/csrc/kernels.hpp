@@ -14,6 +14,8 @@ int launch_score(const maskkv_desc* d, const View& Q, const View& K, const Lens&
 // sweep.hip: the scores in one sweep over the keys
 bool sweep_wanted(const maskkv_desc* d, const Lens& lens, int nqg);
 size_t sweep_workspace_bytes(const maskkv_desc* d, int nqg);
+// for tests and measurements: marks the device's sweep as taken age_us ago, as by a call that has not ended (age_us < 0: not taken)
+int hold_sweep(int64_t age_us, hipStream_t stream);
 int launch_sweep(const maskkv_desc* d, const View& Q, const View& K, const Lens& lens, float scale, float* scores,
                  int64_t score_stride, float* prompt_mass, float* group_sums, int64_t group_stride, int nqg, void* area,
                  hipStream_t stream, const float** unit_mass);

@@ -71,6 +71,7 @@ struct Control {
   int redo;     // the sweep could not do the work: the fallback at the end of the kernel does
   int ticket;   // next task of the fallback
   int pad;
+  unsigned long long taken;  // what this call has put into the lock
   int started[kMaxGroups];  // by workgroup of the sweep
 };
 
@@ -102,7 +103,13 @@ struct SweepParams {
 };
 
 // One sweep kernel at a time may run on a device: its workgroups wait for each other, so all of them have to be resident.
-__device__ int sweep_lock;
+// 0, or the time at which a call took the lock, in ticks of the 100 MHz clock (its lowest bit is set).  A call takes it in its start
+// kernel and gives it back in its sweep kernel.  If the latter never runs, because its launch failed or a graph was given up, the
+// lock is up for taking again kStale later; a call that is merely slow then loses nothing but time, since waits are bounded.
+__device__ unsigned long long sweep_lock;
+constexpr int64_t kStale = 100000000;      // 1 s
+
+__device__ __forceinline__ unsigned long long lock_time() { return wall_clock64() | 1; }
 
 __device__ __forceinline__ int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
@@ -206,8 +213,12 @@ __global__ __launch_bounds__(kThreads) void sweep_start_kernel(const SweepParams
   for (int s = 0; s < S; ++s) qf[s] = *reinterpret_cast<const u32x4*>(qrow + s * 32);
 
   if (blockIdx.x == 0 && threadIdx.x == 0) {
-    const int run = atomicCAS(&sweep_lock, 0, 1) == 0;
+    const unsigned long long now = lock_time();
+    unsigned long long old = atomicCAS(&sweep_lock, 0ull, now);
+    if (old != 0 && (int64_t)(now - old) > kStale && atomicCAS(&sweep_lock, old, now) == old) old = 0;
+    const int run = old == 0;
     prm.ctl->run = run;
+    prm.ctl->taken = now;
     prm.ctl->redo = !run;
     prm.ctl->ticket = 0;
   }
@@ -950,9 +961,11 @@ __global__ __launch_bounds__(kThreads, 2) void sweep_kernel(const SweepParams pr
       for (int i = threadIdx.x; i < (int)gridDim.x; i += 64)
         all = all && __hip_atomic_load(&prm.ctl->started[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     } while (!__all(all) && wall_clock64() - t0 < kPatience);
-    if (threadIdx.x == 0) __hip_atomic_store(&sweep_lock, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (threadIdx.x == 0) atomicCAS(&sweep_lock, prm.ctl->taken, 0ull);
   }
 }
+
+__global__ void hold_kernel(int64_t age) { sweep_lock = age < 0 ? 0ull : (wall_clock64() - (unsigned long long)age) | 1; }
 
 int cus() {
   static int n = 0;
@@ -1066,6 +1079,11 @@ int launch(const maskkv_desc* d, const SweepParams& prm, hipStream_t stream) {
 // The sweep is kept to a quarter of that, where no array of the workspace is larger than 2^30 bytes; more take the two passes.
 bool sweep_wanted(const maskkv_desc* d, const Lens& lens, int nqg) {
   return d->dtype == MASKKV_BF16 && (int64_t)d->B * d->H * nqg <= kMaxUnits && Plan(d, lens, nqg).faster;
+}
+
+int hold_sweep(int64_t age_us, hipStream_t stream) {
+  hipLaunchKernelGGL(hold_kernel, dim3(1), dim3(1), 0, stream, age_us < 0 ? -1 : age_us * 100);
+  return check_launch("hold sweep");
 }
 
 size_t sweep_workspace_bytes(const maskkv_desc* d, int nqg) { return Layout(d, nqg).bytes; }

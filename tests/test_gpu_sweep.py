@@ -88,6 +88,36 @@ def test_calls_on_two_streams_at_once():
     assert torch.equal(after[0][:, :batches[0].P[0]], want[0][0][:, :batches[0].P[0]])
 
 
+def swept(batch, ws):
+    """One call, and whether it had the device's sweep (the first word of the workspace)."""
+    m = hp.mk()
+    scores, mass = torch.full((batch.B * batch.H, batch.P_max), float("nan"), device="cuda"), torch.zeros(batch.B * batch.H, device="cuda")
+    m.maskkv_score(batch.desc, batch.Q, batch.K, 0.0, scores, batch.P_max, mass, ws)
+    return scores, mass, int(ws[:4].view(torch.int32)[0])
+
+
+def test_a_lock_that_was_never_given_back():
+    """A call whose start kernel ran and whose sweep kernel did not leaves the lock taken: fallback at first, back to the sweep later."""
+    from paper_2510_09309_amd import bench_binding as bb
+    batch = hp.Batch([synth.make_layer(98, H=8, d=128, P=3000, n_m=100, dtype="bf16", n_planted=50, amplitude=2.5)])
+    ws = hp.workspace(hp.mk().maskkv_score_workspace_bytes(batch.desc))
+    want, want_mass, run = swept(batch, ws)
+    assert run == 1
+    bb.maskkv_bench_hold_sweep(0)
+    for _ in range(2):
+        scores, mass, run = swept(batch, ws)
+        assert run == 0
+        # two ways to form the same fp32 sums: logits of up to 2^5 binary orders
+        assert torch.allclose(scores, want, rtol=32 * 2.0 ** -24, atol=0)
+        assert torch.allclose(mass, want_mass, rtol=32 * 2.0 ** -24, atol=0)
+    bb.maskkv_bench_hold_sweep(2_000_000)
+    for _ in range(2):
+        scores, mass, run = swept(batch, ws)
+        assert run == 1
+        assert torch.equal(scores, want) and torch.equal(mass, want_mass)
+    bb.maskkv_bench_hold_sweep(-1)
+
+
 @pytest.mark.parametrize("d,P,n_m,row_bytes", [(128, 40, 300, 1 << 24), (64, 200, 260, 1 << 24), (128, 60, 8230, 1 << 19)])
 def test_response_rows_more_than_4_gib_apart(d, P, n_m, row_bytes):
     """Token strides up to 16 MiB: the response span of one head may reach over more than 32 bits of offset."""
