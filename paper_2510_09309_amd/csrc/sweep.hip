@@ -24,6 +24,8 @@
 // takes 38 us, 58 before; the ragged batch of bench.py 505 us, 730 before.  Both waves of a SIMD half a step apart, 2 or 8
 // copies of the sums, or asking for the sums earlier in the step: slower (a sum that is asked for before it is
 // complete has to be asked for again, and a line that is being read is slow to add to).
+#include <type_traits>
+
 #include "kernels.hpp"
 #include "lds.hpp"
 namespace maskkv {
@@ -75,7 +77,7 @@ struct Control {
   int started[kMaxGroups];  // by workgroup of the sweep
 };
 
-constexpr int kSpans = 8;                  // pieces of a unit's keys in the fallback
+constexpr int kSpans = 8;                  // pieces of a unit's keys in the fallback, at most
 
 struct SweepParams {
   View Q, K;
@@ -85,6 +87,7 @@ struct SweepParams {
   int n_qh, q_per_kv, nqg;
   int rows;         // voting rows per unit, a multiple of 32 (the last unit of a head may have fewer)
   int chunks;       // in total
+  int spans;        // pieces of a unit's keys in the fallback
   float c;          // scale * log2(e)
   uint64_t* low;    // [units][kCopies][256]
   uint64_t* high;   // [units][256]
@@ -307,29 +310,35 @@ __global__ __launch_bounds__(kThreads) void sweep_start_kernel(const SweepParams
 // ---- fallback: the scores in two passes, as tasks that workgroups take by ticket, whatever their number.  A task is a
 // span of a unit's chunks; first come all tasks that form row statistics, then all that form column sums.  The latter wait
 // for the former of their unit, which have smaller tickets and therefore are with workgroups that are running.
+//
+// A program that scores on two streams runs into it (a call that finds the other's sweep under way comes here), so it is no mere
+// safety net: keys come by direct transfers two chunks ahead, with one barrier a chunk, and statistics and counters by device-scope
+// accesses without cache-wide fences.  us a call (the sweep; this; with keys through registers, three barriers and fences):
+// 32 heads x 128, 256 rows, 4k keys 30, 47, 90; 8k 42, 68, 125; 32k 131, 198, 353; 8 sequences x 8k, 512 rows 481, 773, 1892.
 template <int D>
 __device__ __forceinline__ void sweep_redo(const SweepParams& prm, uint32_t lds0) {
   using C = Cfg<D>;
   constexpr int S = C::kSteps;
   const int lane = threadIdx.x & 63, r = lane & 31, g = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int units = prm.B * prm.H * prm.nqg;
+  const int spans = prm.spans, tasks = prm.B * prm.H * prm.nqg * spans;  // of a pass
   const uint32_t word = lds0 + C::kOffMass;                   // one int: the ticket, or whether to go on
-  const uint32_t colsum = lds0 + C::kOffCs;                   // [kWaves][kKeys] floats
+  const uint32_t colsum = lds0 + C::kOffCs;                   // [2][kWaves][kKeys] floats
   for (;;) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (transfers of the last task that nothing has waited for)
     __syncthreads();
     if (threadIdx.x == 0) *in_lds<int>(word) = __hip_atomic_fetch_add(&prm.ctl->ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
-    const int ticket = *in_lds<int>(word);
-    if (ticket >= 2 * units * kSpans) return;
-    const bool second = ticket >= units * kSpans;
-    const int task = second ? ticket - units * kSpans : ticket;
-    const int unit = task / kSpans, span = task % kSpans;
+    const int ticket = __builtin_amdgcn_readfirstlane(*in_lds<int>(word));
+    if (ticket >= 2 * tasks) return;
+    const bool second = ticket >= tasks;
+    const int task = second ? ticket - tasks : ticket;
+    const int unit = task / spans, span = task % spans;
     const int bh = unit / prm.nqg;
     const int b = bh / prm.H, h = bh - b * prm.H;
     const int P = prm.lens.P[b];
     const int nc = ceil_div(P, kKeys);
-    const int c0 = nc * span / kSpans, c1 = nc * (span + 1) / kSpans;
+    const int c0 = nc * span / spans, c1 = nc * (span + 1) / spans;
     const int64_t row0 = (int64_t)unit * kRows + wave * 32;
     u32x4 qf[S];
 #pragma unroll
@@ -340,11 +349,11 @@ __device__ __forceinline__ void sweep_redo(const SweepParams& prm, uint32_t lds0
     if (second) {
       if (threadIdx.x == 0) {
         const uint64_t t0 = wall_clock64();
-        while (__hip_atomic_load(&prm.spans_done[unit], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) < kSpans && wall_clock64() - t0 < 50 * kPatience)
+        while (__hip_atomic_load(&prm.spans_done[unit], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < spans && wall_clock64() - t0 < 50 * kPatience)
           __builtin_amdgcn_s_sleep(8);
       }
+      asm volatile("" ::: "memory");
       __syncthreads();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
       // all spans and the response span
       const float ref = -prm.start[row0 * 2 + r] * prm.c;  // +inf for a row that does not exist
       const float own = prm.start[row0 * 2 + 32 + r];
@@ -353,8 +362,11 @@ __device__ __forceinline__ void sweep_redo(const SweepParams& prm, uint32_t lds0
       float2 v[kSpans];
 #pragma unroll
       for (int i = 0; i < kSpans; ++i) {
-        v[i].x = __hip_atomic_load(&st[i * kRows].x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        v[i].y = __hip_atomic_load(&st[i * kRows].y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        v[i] = make_float2(kNegBig, 0.f);
+        if (i < spans) {
+          v[i].x = __hip_atomic_load(&st[i * kRows].x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          v[i].y = __hip_atomic_load(&st[i * kRows].y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
         M = fmaxf(M, v[i].x);
       }
 #pragma unroll
@@ -377,60 +389,90 @@ __device__ __forceinline__ void sweep_redo(const SweepParams& prm, uint32_t lds0
 #pragma unroll
       for (int i = 0; i < 16; ++i) nl[i] = __shfl(nlse, 8 * (i / 4) + 4 * g + (i % 4), 64);
     }
-    for (int ci = c0; ci < c1; ++ci) {
-      __syncthreads();
+    auto dma = [&](int n) {  // chunk number n of the span (or its last one) into slot n of the ring
+      const int ci = min(c0 + n, c1 - 1), last = P - 1 - ci * kKeys;
+      const char* base = prm.K.row(b, h, ci * kKeys);
 #pragma unroll
       for (int j = 0; j < C::kMoves; ++j) {
         const int row = wave * (kKeys / kWaves) + j * C::kRPI + lane / C::kPPR;
         const int piece = (lane % C::kPPR) ^ C::swz(row);
-        *in_lds<u32x4>(lds0 + row * C::kRowB + (lane % C::kPPR) * 16) =
-            *reinterpret_cast<const u32x4*>(prm.K.row(b, h, min(ci * kKeys + row, P - 1)) + piece * 16);
+        dma16(base, (uint32_t)min(row, last) * (uint32_t)prm.K.stride_t + piece * 16,
+              lds0 + n % C::kRing * C::kKBytes + (wave * (kKeys / kWaves) + j * C::kRPI) * C::kRowB);
       }
-      __syncthreads();
-      float col[kNB];
+    };
+    auto flush = [&](int n) {  // column sums of chunk n of the span
+      const int j = (c0 + n) * kKeys + (int)threadIdx.x;
+      if ((int)threadIdx.x >= kKeys || j >= P) return;
+      const uint32_t cs = colsum + (n & 1) * kWaves * kKeys * 4 + threadIdx.x * 4;
+      float v = 0.f;
 #pragma unroll
-      for (int kb = 0; kb < kNB; ++kb) {
-        f32x16 a{};
+      for (int w = 0; w < kWaves; ++w) v += *in_lds<const float>(cs, w * kKeys * 4);
+      prm.out[(int64_t)unit * prm.out_stride + j] = v;
+    };
+    if (c0 < c1) {
+      dma(0);
+      dma(1);
+    }
+    auto walk = [&](auto columns) {  // a pass's instructions in a loop of their own
+      constexpr bool kColumns = decltype(columns)::value;
+      for (int n = 0; n < c1 - c0; ++n) {
+        dma(n + 2);  // (its slot was last read before the barrier of the step before)
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"i"(2 * C::kMoves) : "memory");
+        if (kColumns && n > 0) flush(n - 1);
+        const uint32_t chunk = lds0 + n % C::kRing * C::kKBytes;
+        f32x16 a[kNB];
 #pragma unroll
-        for (int s = 0; s < S; ++s) {
-          const u32x4 kf = *in_lds<const u32x4>(lds0 + (kb * 32 + r) * C::kRowB + (((2 * s + g) ^ C::swz(r)) << 4));
-          if (second)
-            mfma_step<bf16_t>(qf[s], kf, a);
-          else
-            mfma_step<bf16_t>(kf, qf[s], a);
-        }
-        if (second) {
-          float v = 0.f;
+        for (int kb = 0; kb < kNB; ++kb) {
+          a[kb] = f32x16{};
 #pragma unroll
-          for (int i = 0; i < 16; ++i) v += fast_exp2(fmaf(a[i], prm.c, nl[i]));
-          col[kb] = v + xor32(v);
-        } else {
-          float bm = m;
-#pragma unroll
-          for (int i = 0; i < 16; ++i) {
-            if (ci * kKeys + kb * 32 + 8 * (i / 4) + 4 * g + (i % 4) >= P) a[i] = -INFINITY;
-            bm = fmaxf(bm, a[i] * prm.c);
+          for (int s = 0; s < S; ++s) {
+            const u32x4 kf = *in_lds<const u32x4>(chunk + (kb * 32 + r) * C::kRowB + (((2 * s + g) ^ C::swz(r)) << 4));
+            if constexpr (kColumns)
+              mfma_step<bf16_t>(qf[s], kf, a[kb]);
+            else
+              mfma_step<bf16_t>(kf, qf[s], a[kb]);
           }
+        }
+        if constexpr (kColumns) {
+#pragma unroll
+          for (int kb = 0; kb < kNB; ++kb) {
+            float v = 0.f;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) v += fast_exp2(fmaf(a[kb][i], prm.c, nl[i]));
+            v += xor32(v);
+            if (g == 0) *in_lds<float>(colsum + ((n & 1) * kWaves * kKeys + wave * kKeys + kb * 32 + r) * 4) = v;
+          }
+        } else {
+          const int left = P - (c0 + n) * kKeys;
+          if (left < kKeys)
+#pragma unroll
+            for (int kb = 0; kb < kNB; ++kb)
+#pragma unroll
+              for (int i = 0; i < 16; ++i)
+                if (kb * 32 + 8 * (i / 4) + 4 * g + (i % 4) >= left) a[kb][i] = -INFINITY;
+          float top = a[0][0];
+#pragma unroll
+          for (int kb = 0; kb < kNB; ++kb)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) top = fmaxf(top, a[kb][i]);
+          const float bm = fmaxf(m, top * prm.c);
           float v = 0.f;
 #pragma unroll
-          for (int i = 0; i < 16; ++i) v += fast_exp2(fmaf(a[i], prm.c, -bm));
+          for (int kb = 0; kb < kNB; ++kb)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) v += fast_exp2(fmaf(a[kb][i], prm.c, -bm));
           l = l * fast_exp2(m - bm) + v;
           m = bm;
         }
       }
-      if (second) {
-        if (g == 0)
-#pragma unroll
-          for (int kb = 0; kb < kNB; ++kb) *in_lds<float>(colsum + (wave * kKeys + kb * 32 + r) * 4) = col[kb];
-        __syncthreads();
-        const int j = ci * kKeys + (int)threadIdx.x;
-        if ((int)threadIdx.x < kKeys && j < P) {
-          float v = 0.f;
-#pragma unroll
-          for (int w = 0; w < kWaves; ++w) v += *in_lds<const float>(colsum + (w * kKeys + threadIdx.x) * 4);
-          prm.out[(int64_t)unit * prm.out_stride + j] = v;
-        }
-      }
+    };
+    if (second)
+      walk(std::true_type());
+    else
+      walk(std::false_type());
+    if (second && c0 < c1) {
+      __syncthreads();
+      flush(c1 - c0 - 1);
     }
     if (!second) {
       const float mo = xor32(m), lo = xor32(l);
@@ -439,9 +481,11 @@ __device__ __forceinline__ void sweep_redo(const SweepParams& prm, uint32_t lds0
         __hip_atomic_store(&st[span * kRows].x, mm, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __hip_atomic_store(&st[span * kRows].y, l * fast_exp2(m - mm) + lo * fast_exp2(mo - mm), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+      // (Device-scope stores that have completed are seen by every device-scope load that is issued later; a release here would
+      // write back the whole L2, an acquire above throw it away.)
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       __syncthreads();
-      if (threadIdx.x == 0) __hip_atomic_fetch_add(&prm.spans_done[unit], 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+      if (threadIdx.x == 0) __hip_atomic_fetch_add(&prm.spans_done[unit], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   }
 }
@@ -939,6 +983,15 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
   flush(prev, par, mine + 1);
 }
 
+// The kernel's argument, from a pointer hidden from the optimiser: what follows the walk then loads what it needs when it needs it,
+// instead of having it loaded before the walk and kept in registers, or spilled, for the whole of it.
+__device__ __forceinline__ const SweepParams& argument_again() {
+  typedef const __attribute__((address_space(4))) SweepParams* Arg;
+  Arg p = (Arg)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return *(const SweepParams*)p;
+}
+
 template <int D>
 __global__ __launch_bounds__(kThreads, 2) void sweep_kernel(const SweepParams prm) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
@@ -949,9 +1002,9 @@ __global__ __launch_bounds__(kThreads, 2) void sweep_kernel(const SweepParams pr
     sweep_chunks<D>(prm, lds0);
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     const int late = __builtin_amdgcn_readfirstlane(*in_lds<const int>(lds0 + Cfg<D>::kOffLate));
-    if (__builtin_expect(late, 0)) late_masses<D>(prm, lds0, late);
+    if (__builtin_expect(late, 0)) late_masses<D>(argument_again(), lds0, late);
   }
-  if (__hip_atomic_load(&prm.ctl->redo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) sweep_redo<D>(prm, lds0);
+  if (__hip_atomic_load(&prm.ctl->redo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) sweep_redo<D>(argument_again(), lds0);
   // The lock is given back once every workgroup has been placed: from then on they cannot be kept waiting for each other.
   if (run && blockIdx.x == 0 && threadIdx.x < 64) {
     const uint64_t t0 = wall_clock64();
@@ -1106,6 +1159,8 @@ int launch_sweep(const maskkv_desc* d, const View& Q, const View& K, const Lens&
   int x = 0;
   for (int b = 0; b < d->B; ++b) x += (lens.P[b] + kKeys - 1) / kKeys * d->H * nqg;
   prm.chunks = x;
+  // Two tasks a pass for every compute unit: a task costs about as much as two chunks before its first one.
+  prm.spans = max(1, min(kSpans, 2 * kMaxGroups / (d->B * d->H * nqg)));
   prm.c = scale * kLog2e;
   const Layout l(d, nqg);
   char* base = reinterpret_cast<char*>(area);
