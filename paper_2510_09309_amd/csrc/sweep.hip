@@ -69,12 +69,9 @@ constexpr int kMaxUnits = 16384;           // of a launch, see sweep_wanted
 constexpr int kMaxGroups = 256;            // workgroups of a sweep, and chunks of a unit, at most (one per compute unit)
 
 struct Control {
-  int run;      // this call holds the device's sweep lock
+  int run;      // this call's workgroups may be placed as a sweep's
   int redo;     // the sweep could not do the work: the fallback at the end of the kernel does
   int ticket;   // next task of the fallback
-  int pad;
-  unsigned long long taken;  // what this call has put into the lock
-  int started[kMaxGroups];  // by workgroup of the sweep
 };
 
 constexpr int kSpans = 8;                  // pieces of a unit's keys in the fallback, at most
@@ -87,6 +84,7 @@ struct SweepParams {
   int n_qh, q_per_kv, nqg;
   int rows;         // voting rows per unit, a multiple of 32 (the last unit of a head may have fewer)
   int chunks;       // in total
+  int groups;       // workgroups of the sweep
   int spans;        // pieces of a unit's keys in the fallback
   float c;          // scale * log2(e)
   uint64_t* low;    // [units][kCopies][256]
@@ -105,14 +103,47 @@ struct SweepParams {
   float* mass;      // [units] or null
 };
 
-// One sweep kernel at a time may run on a device: its workgroups wait for each other, so all of them have to be resident.
-// 0, or the time at which a call took the lock, in ticks of the 100 MHz clock (its lowest bit is set).  A call takes it in its start
-// kernel and gives it back in its sweep kernel.  If the latter never runs, because its launch failed or a graph was given up, the
-// lock is up for taking again kStale later; a call that is merely slow then loses nothing but time, since waits are bounded.
+// The workgroups of a sweep wait for each other, so all of them have to be resident, and two sweeps may not be placed on a device at
+// the same time.  The lock holds how many workgroups all sweeps together have been or are to be placed (32 bits, wrapping),
+// and when it was last changed (32 bits, in kTick); what has been placed counts itself in 16 places, since 256 additions to one
+// word at the beginning of a sweep hold it up by 10 us.  A call adds its workgroups in its start kernel.  At no difference
+// between the two the next sweep may line up behind this one; while there is one its start kernel waits, which
+// keeps that compute unit from the others: it goes on when no more than kWaiters are to come.  These have waited for a
+// place since before this call's sweep is launched, so they come first.  After kStartWait the call takes the fallback.
+// If a sweep kernel never runs, because its launch failed or a graph was given up, its workgroups are forgotten kStale
+// later; a call that is merely slow then loses nothing but time, since all waits are bounded.
+// us a call on two streams at once (one stream; the fallback for whoever finds the lock taken; the two passes): 4k keys 24, 28, 31, 30;
+// 8k 38, 40, 40, 58; 32k 119, 121, 168, 162; 8 sequences x 8k with 512 rows 445, 454, 605, 648.
 __device__ unsigned long long sweep_lock;
-constexpr int64_t kStale = 100000000;      // 1 s
+constexpr int kPlaces = 16;
+constexpr int kPlaceWords = 32;            // (a line each)
+__device__ unsigned sweep_placed[kPlaces * kPlaceWords];
+constexpr int kWaiters = 8;
+constexpr int kTick = 20;                  // 2^20 ticks of the 100 MHz clock: 10 ms
+constexpr uint32_t kStale = 100;           // 1 s
+constexpr uint64_t kStartWait = 50000;     // 500 us, which is what the fallback costs more than the sweep in large calls
 
-__device__ __forceinline__ unsigned long long lock_time() { return wall_clock64() | 1; }
+__device__ __forceinline__ uint32_t placed() {  // by all sweeps (to be called by a whole wave)
+  const int lane = threadIdx.x & 63;
+  uint32_t v = lane < kPlaces ? __hip_atomic_load(&sweep_placed[lane * kPlaceWords], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  return v;
+}
+
+// Adds a call's workgroups if no more than most_left are to come (to be called by a whole wave; the same in every lane).
+__device__ __forceinline__ bool take_lock(int groups, int most_left) {
+  unsigned long long seen = __hip_atomic_load(&sweep_lock, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const uint32_t there = placed();  // (it only grows: at worst too many seem to be left)
+  const uint32_t now = (uint32_t)(wall_clock64() >> kTick);
+  const bool stale = now - (uint32_t)(seen >> 32) - 1 < 0x7FFFFFFFu && now - (uint32_t)(seen >> 32) > kStale;
+  const int left = (int)((uint32_t)seen - there);
+  if (left > most_left && !stale) return false;
+  const uint32_t all = (left > 0 && !stale ? (uint32_t)seen : there) + (uint32_t)groups;
+  unsigned long long was = 0;
+  if ((threadIdx.x & 63) == 0) was = atomicCAS(&sweep_lock, seen, ((unsigned long long)now << 32) | all);
+  return __all((threadIdx.x & 63) != 0 || was == seen);
+}
 
 __device__ __forceinline__ int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
@@ -179,10 +210,31 @@ __device__ __forceinline__ float wave_sum(float v) {
 // ---- response span: row references, zeroed sums, and the voting rows in the order in which the sweep reads them.
 // A workgroup serves BLOCKS blocks of 32 rows of a unit; 8 / BLOCKS waves share a block's keys, which come through LDS 128
 // at a time.  (Eight blocks where there are units enough to fill the chip: each key is then read once per unit.)
+// Takes the lock, or waits for it: 2 us.  Where units are few, that is for a workgroup of its own, the last; where they fill the
+// chip and one workgroup more would start alone at the end, the first does it when it is done.
+__device__ __forceinline__ void start_lock(const SweepParams& prm) {
+  if (threadIdx.x >= 64) return;
+  bool run = take_lock(prm.groups, 0);
+  const uint64_t t0 = wall_clock64();
+  while (!run && wall_clock64() - t0 < kStartWait) {
+    __builtin_amdgcn_s_sleep(32);
+    run = take_lock(prm.groups, kWaiters);
+  }
+  if (threadIdx.x == 0) {
+    prm.ctl->run = run;
+    prm.ctl->redo = !run;
+    prm.ctl->ticket = 0;
+  }
+}
+
 template <int D, int BLOCKS>
 __global__ __launch_bounds__(kThreads) void sweep_start_kernel(const SweepParams prm) {
   using C = Cfg<D>;
   constexpr int S = C::kSteps, SPLIT = kWaves / BLOCKS;
+  if (BLOCKS == 2 && blockIdx.x == gridDim.x - 1) {
+    start_lock(prm);
+    return;
+  }
   extern __shared__ __attribute__((aligned(1024))) char lds[];  // two tiles of 128 keys
   __shared__ float2 part[kWaves][32];
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
@@ -215,18 +267,6 @@ __global__ __launch_bounds__(kThreads) void sweep_start_kernel(const SweepParams
 #pragma unroll
   for (int s = 0; s < S; ++s) qf[s] = *reinterpret_cast<const u32x4*>(qrow + s * 32);
 
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    const unsigned long long now = lock_time();
-    unsigned long long old = atomicCAS(&sweep_lock, 0ull, now);
-    if (old != 0 && (int64_t)(now - old) > kStale && atomicCAS(&sweep_lock, old, now) == old) old = 0;
-    const int run = old == 0;
-    prm.ctl->run = run;
-    prm.ctl->taken = now;
-    prm.ctl->redo = !run;
-    prm.ctl->ticket = 0;
-  }
-  if (blockIdx.x == 0)
-    for (int i = threadIdx.x; i < kMaxGroups; i += kThreads) prm.ctl->started[i] = 0;
   if (rb == 0 && part_of == 0 && lane == 0) {
     prm.spans_done[unit] = 0;
     if (P == 0 && prm.mass) prm.mass[unit] = 0.f;
@@ -305,14 +345,15 @@ __global__ __launch_bounds__(kThreads) void sweep_start_kernel(const SweepParams
     prm.start[row0 * 2 + 32 + lane] = own;
     prm.low[(int64_t)unit * kCopies * kRows + rb * 32 + lane] = (uint64_t)rintf(own * kLowScale);
   }
+  if (BLOCKS == 8 && blockIdx.x == 0) start_lock(prm);
 }
 
 // ---- fallback: the scores in two passes, as tasks that workgroups take by ticket, whatever their number.  A task is a
 // span of a unit's chunks; first come all tasks that form row statistics, then all that form column sums.  The latter wait
 // for the former of their unit, which have smaller tickets and therefore are with workgroups that are running.
 //
-// A program that scores on two streams runs into it (a call that finds the other's sweep under way comes here), so it is no mere
-// safety net: keys come by direct transfers two chunks ahead, with one barrier a chunk, and statistics and counters by device-scope
+// A call comes here if a row's sum is out of range, if the device's sweep stays taken, or if another program's kernels keep its
+// workgroups apart, so it is no mere safety net: keys come by direct transfers two chunks ahead, with one barrier a chunk, and statistics and counters by device-scope
 // accesses without cache-wide fences.  us a call (the sweep; this; with keys through registers, three barriers and fences):
 // 32 heads x 128, 256 rows, 4k keys 30, 47, 90; 8k 42, 68, 125; 32k 131, 198, 353; 8 sequences x 8k, 512 rows 481, 773, 1892.
 template <int D>
@@ -996,29 +1037,22 @@ template <int D>
 __global__ __launch_bounds__(kThreads, 2) void sweep_kernel(const SweepParams prm) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
-  const bool run = prm.ctl->run;  // (if not, another call's sweep is running on this device)
-  if (threadIdx.x == 0) __hip_atomic_store(&prm.ctl->started[blockIdx.x], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  if (run) {
+  if (prm.ctl->run) {
+    if (threadIdx.x == 0)
+      __hip_atomic_fetch_add(&sweep_placed[blockIdx.x % kPlaces * kPlaceWords], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     sweep_chunks<D>(prm, lds0);
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     const int late = __builtin_amdgcn_readfirstlane(*in_lds<const int>(lds0 + Cfg<D>::kOffLate));
     if (__builtin_expect(late, 0)) late_masses<D>(argument_again(), lds0, late);
   }
   if (__hip_atomic_load(&prm.ctl->redo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) sweep_redo<D>(argument_again(), lds0);
-  // The lock is given back once every workgroup has been placed: from then on they cannot be kept waiting for each other.
-  if (run && blockIdx.x == 0 && threadIdx.x < 64) {
-    const uint64_t t0 = wall_clock64();
-    bool all;
-    do {
-      all = true;
-      for (int i = threadIdx.x; i < (int)gridDim.x; i += 64)
-        all = all && __hip_atomic_load(&prm.ctl->started[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    } while (!__all(all) && wall_clock64() - t0 < kPatience);
-    if (threadIdx.x == 0) atomicCAS(&sweep_lock, prm.ctl->taken, 0ull);
-  }
 }
 
-__global__ void hold_kernel(int64_t age) { sweep_lock = age < 0 ? 0ull : (wall_clock64() - (unsigned long long)age) | 1; }
+__global__ void hold_kernel(int64_t age) {
+  const uint32_t there = placed();
+  const uint32_t then = (uint32_t)((wall_clock64() - (age < 0 ? 0 : (uint64_t)age)) >> kTick);
+  if (threadIdx.x == 0) sweep_lock = ((unsigned long long)then << 32) | (there + (age < 0 ? 0 : kMaxGroups));
+}
 
 int cus() {
   static int n = 0;
@@ -1120,9 +1154,9 @@ int launch(const maskkv_desc* d, const SweepParams& prm, hipStream_t stream) {
   if (units >= 128)
     hipLaunchKernelGGL((sweep_start_kernel<D, 8>), dim3(units), dim3(kThreads), lds_start, stream, prm);
   else
-    hipLaunchKernelGGL((sweep_start_kernel<D, 2>), dim3(units * 4), dim3(kThreads), lds_start, stream, prm);
+    hipLaunchKernelGGL((sweep_start_kernel<D, 2>), dim3(units * 4 + 1), dim3(kThreads), lds_start, stream, prm);
   if (int e = check_launch("score (sweep start)")) return e;
-  hipLaunchKernelGGL(sweep_kernel<D>, dim3(Plan(d, prm.lens, prm.nqg).groups), dim3(kThreads), Cfg<D>::kLds, stream, prm);
+  hipLaunchKernelGGL(sweep_kernel<D>, dim3(prm.groups), dim3(kThreads), Cfg<D>::kLds, stream, prm);
   return check_launch("score (sweep)");
 }
 
@@ -1135,7 +1169,7 @@ bool sweep_wanted(const maskkv_desc* d, const Lens& lens, int nqg) {
 }
 
 int hold_sweep(int64_t age_us, hipStream_t stream) {
-  hipLaunchKernelGGL(hold_kernel, dim3(1), dim3(1), 0, stream, age_us < 0 ? -1 : age_us * 100);
+  hipLaunchKernelGGL(hold_kernel, dim3(1), dim3(64), 0, stream, age_us < 0 ? -1 : age_us * 100);
   return check_launch("hold sweep");
 }
 
@@ -1159,6 +1193,7 @@ int launch_sweep(const maskkv_desc* d, const View& Q, const View& K, const Lens&
   int x = 0;
   for (int b = 0; b < d->B; ++b) x += (lens.P[b] + kKeys - 1) / kKeys * d->H * nqg;
   prm.chunks = x;
+  prm.groups = Plan(d, lens, nqg).groups;
   // Two tasks a pass for every compute unit: a task costs about as much as two chunks before its first one.
   prm.spans = max(1, min(kSpans, 2 * kMaxGroups / (d->B * d->H * nqg)));
   prm.c = scale * kLog2e;

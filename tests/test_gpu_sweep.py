@@ -67,7 +67,7 @@ def test_prompt_far_above_the_response_span(d, boost, keys):
 
 
 def test_calls_on_two_streams_at_once():
-    """Only one sweep at a time has a device to itself; a call that finds another one running takes the fallback."""
+    """Sweeps on one device line up behind each other; a call that would have to wait for long takes the fallback."""
     m = hp.mk()
     batches = [hp.Batch([synth.make_layer(95 + i, H=16, d=128, P=4000 + 77 * i, n_m=128, dtype="bf16", n_planted=50, amplitude=2.5)])
                for i in range(2)]
@@ -97,7 +97,7 @@ def swept(batch, ws):
 
 
 def test_a_lock_that_was_never_given_back():
-    """A call whose start kernel ran and whose sweep kernel did not leaves the lock taken: fallback at first, back to the sweep later."""
+    """A call whose start kernel ran and whose sweep kernel did not: fallback at first, back to the sweep a second later."""
     from paper_2510_09309_amd import bench_binding as bb
     batch = hp.Batch([synth.make_layer(98, H=8, d=128, P=3000, n_m=100, dtype="bf16", n_planted=50, amplitude=2.5)])
     ws = hp.workspace(hp.mk().maskkv_score_workspace_bytes(batch.desc))
@@ -116,6 +116,31 @@ def test_a_lock_that_was_never_given_back():
         assert run == 1
         assert torch.equal(scores, want) and torch.equal(mass, want_mass)
     bb.maskkv_bench_hold_sweep(-1)
+
+
+def test_sweeps_on_two_streams_line_up():
+    """Of calls that two streams make at once, at most a few need the fallback, and all give what one stream gives."""
+    m = hp.mk()
+    batches = [hp.Batch([synth.make_layer(99 + i, H=32, d=128, P=4096 - 100 * i, n_m=256, dtype="bf16", n_planted=50, amplitude=2.5)])
+               for i in range(2)]
+    n = 25
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    ws = [[torch.zeros(m.maskkv_score_workspace_bytes(b.desc), dtype=torch.uint8, device="cuda") for _ in range(n)] for b in batches]
+    out = [[(torch.zeros(32, b.P_max, device="cuda"), torch.zeros(32, device="cuda")) for _ in range(n)] for b in batches]
+    want = [hp.gpu_score(b) for b in batches]
+    torch.cuda.synchronize()
+    for i in range(n):
+        for b, w, o, st in zip(batches, ws, out, streams):
+            m.maskkv_score(b.desc, b.Q, b.K, 0.0, o[i][0], b.P_max, o[i][1], w[i], st)
+    torch.cuda.synchronize()
+    swept = sum(int(w[:4].view(torch.int32)[0]) for per in ws for w in per)
+    print("swept", swept, "of", 2 * n, flush=True)
+    assert swept >= n                    # (before they lined up, every other call took the fallback)
+    for b, o, w in zip(batches, out, want):
+        for scores, mass in o:
+            # the same sums or, in the fallback, the same fp32 exponentials summed in another way
+            assert torch.allclose(scores, w[0][:, :b.P_max], rtol=32 * 2.0 ** -24, atol=0)
+            assert torch.allclose(mass, w[1], rtol=32 * 2.0 ** -24, atol=0)
 
 
 @pytest.mark.parametrize("d,P,n_m,row_bytes", [(128, 40, 300, 1 << 24), (64, 200, 260, 1 << 24), (128, 60, 8230, 1 << 19)])
