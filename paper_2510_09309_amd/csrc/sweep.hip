@@ -52,7 +52,7 @@ constexpr float kLowScale = 268435456.f;   // 2^28
 constexpr float kLowLimit = 65536.f;       // 2^16
 constexpr float kHighScale = 128.f;        // 2^7
 constexpr float kHighLimit = 549755813888.f;  // 2^39 (kMaxGroups chunks below either limit stay below 2^54 units)
-constexpr uint64_t kPatience = 2000000;    // 20 ms of the 100 MHz clock
+constexpr uint64_t kTaskWait = 100000000;  // 1 s of the 100 MHz clock: a task of the fallback for tasks that are being done
 
 // A row's mass is its prompt sum over its whole sum.  The former comes out of the exchange with an error of about 1e-8 (256
 // chunks rounded to units of 2^-28) and of the rounding of the row's reference, 1e-7 to 1e-6 of the response span's sum: below fp32's
@@ -85,6 +85,7 @@ struct SweepParams {
   int rows;         // voting rows per unit, a multiple of 32 (the last unit of a head may have fewer)
   int chunks;       // in total
   int groups;       // workgroups of the sweep
+  int patience;     // how long a workgroup waits for the others' row sums, in ticks of the 100 MHz clock
   int spans;        // pieces of a unit's keys in the fallback
   float c;          // scale * log2(e)
   uint64_t* low;    // [units][kCopies][256]
@@ -112,6 +113,9 @@ struct SweepParams {
 // place since before this call's sweep is launched, so they come first.  After kStartWait the call takes the fallback.
 // If a sweep kernel never runs, because its launch failed or a graph was given up, its workgroups are forgotten kStale
 // later; a call that is merely slow then loses nothing but time, since all waits are bounded.
+// The lock is a variable of this library: other processes on the device, or a second copy of the library, have their own, and other
+// kernels may hold compute units as well (a workgroup needs 145 KB of LDS and, at head_dim 128, all registers).  Workgroups that are
+// kept apart that way give up after `patience`, and those that run do the work in the fallback.
 // us a call on two streams at once (one stream; the fallback for whoever finds the lock taken; the two passes): 4k keys 24, 28, 31, 30;
 // 8k 38, 40, 40, 58; 32k 119, 121, 168, 162; 8 sequences x 8k with 512 rows 445, 454, 605, 648.
 __device__ unsigned long long sweep_lock;
@@ -390,7 +394,7 @@ __device__ __forceinline__ void sweep_redo(const SweepParams& prm, uint32_t lds0
     if (second) {
       if (threadIdx.x == 0) {
         const uint64_t t0 = wall_clock64();
-        while (__hip_atomic_load(&prm.spans_done[unit], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < spans && wall_clock64() - t0 < 50 * kPatience)
+        while (__hip_atomic_load(&prm.spans_done[unit], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < spans && wall_clock64() - t0 < kTaskWait)
           __builtin_amdgcn_s_sleep(8);
       }
       asm volatile("" ::: "memory");
@@ -579,7 +583,7 @@ __device__ __forceinline__ void late_masses(const SweepParams& prm, uint32_t lds
         sum += as_f32(u[j]);
       }
       if (__all(there)) break;
-      if (wall_clock64() - t0 >= kPatience || __any(__hip_atomic_load(&prm.ctl->redo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) {
+      if (wall_clock64() - t0 >= (uint64_t)prm.patience || __any(__hip_atomic_load(&prm.ctl->redo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) {
         __hip_atomic_store(&prm.ctl->redo, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         *in_lds<int>(lds0 + C::kOffBad) = 1;
         break;
@@ -830,7 +834,7 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
 #pragma unroll
         for (int i = 0; i < kCopies; ++i) lo += seen[i];
         ready = __all((int)(lo >> kCountShift) + (int)(hi >> kCountShift) == k.nc);
-      } while (!ready && wall_clock64() - t0 < kPatience);
+      } while (!ready && wall_clock64() - t0 < (uint64_t)prm.patience);
       // Not every workgroup is running, or a row's sum is out of range: the scores of this workgroup are void from here on.
       if (!ready) {
         patient = false;
@@ -903,10 +907,14 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
   }
   next = ahead;
   if (threadIdx.x < 32) *in_lds<float>(lds0 + C::kOffInf + threadIdx.x * 4) = -INFINITY;
-  if (threadIdx.x < 2) *in_lds<int>(lds0 + C::kOffBad + threadIdx.x * 4) = 0;  // and kOffLate
+  // (kOffBad and kOffLate; a workgroup that is placed when others have already given up goes straight to the fallback)
+  if (threadIdx.x < 2)
+    *in_lds<int>(lds0 + C::kOffBad + threadIdx.x * 4) =
+        threadIdx.x == 0 ? __hip_atomic_load(&prm.ctl->redo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
   for (int i = threadIdx.x; i < 2 * kWaves * kKeys; i += kThreads) *in_lds<float>(lds0 + C::kOffCs + i * 4) = 0.f;
   if (threadIdx.x < 2 * kWaves) *in_lds<float>(lds0 + C::kOffMass + threadIdx.x * 4) = 0.f;
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  if (__builtin_amdgcn_readfirstlane(*in_lds<const int>(lds0 + C::kOffBad))) return;
   f32x16 pre, pa[kNB], pb[kNB];
   auto first_block = [&](int par, const Chunk& k) {
 #pragma unroll
@@ -1194,6 +1202,10 @@ int launch_sweep(const maskkv_desc* d, const View& Q, const View& K, const Lens&
   for (int b = 0; b < d->B; ++b) x += (lens.P[b] + kKeys - 1) / kKeys * d->H * nqg;
   prm.chunks = x;
   prm.groups = Plan(d, lens, nqg).groups;
+  // 100 us and about what the sweep takes, in which the fallback would be done, too.  (What keeps workgroups from being placed is
+  // another program's kernels, a sweep of another process among them, whose lock is its own, or of another stream: the time
+  // these take has nothing to do with this call's.  Two processes that score 32k keys at once, us a call of each: 455, with 20 ms 5000.)
+  prm.patience = 10000 + (int)min((int64_t)x / prm.groups * 500, (int64_t)1000000);
   // Two tasks a pass for every compute unit: a task costs about as much as two chunks before its first one.
   prm.spans = max(1, min(kSpans, 2 * kMaxGroups / (d->B * d->H * nqg)));
   prm.c = scale * kLog2e;

@@ -143,6 +143,33 @@ def test_sweeps_on_two_streams_line_up():
             assert torch.allclose(mass, w[1], rtol=32 * 2.0 ** -24, atol=0)
 
 
+def test_a_sweep_that_is_kept_apart_by_another_kernel():
+    """A kernel of another stream that holds 32 compute units for some 60 ms keeps as many of the sweep's workgroups from being
+    placed; the others do the work in the fallback, after a wait that goes with the call's size."""
+    from paper_2510_09309_amd import bench_binding as bb
+    batch = hp.Batch([synth.make_layer(100, H=2, d=128, P=32768, n_m=64, dtype="bf16", n_planted=50, amplitude=2.5)])
+    ws = hp.workspace(hp.mk().maskkv_score_workspace_bytes(batch.desc))
+    want, want_mass, run = swept(batch, ws)
+    assert run == 1
+    torch.cuda.synchronize()
+    other, out = torch.cuda.Stream(), torch.empty(32 * 256, dtype=torch.int32, device="cuda")
+    a, b, held = (torch.cuda.Event(enable_timing=True) for _ in range(3))
+    bb.maskkv_bench_probe(0, 1000000, None, out, 32, other)
+    held.record(other)
+    a.record()
+    scores, mass, run = swept(batch, ws)
+    b.record()
+    b.synchronize()
+    assert not held.query(), "the other kernel was to run for longer than the call"
+    redo = int(ws[4:8].view(torch.int32)[0])
+    print("call", a.elapsed_time(b), "ms, run", run, "redo", redo, flush=True)
+    torch.cuda.synchronize()
+    assert redo == 1 and a.elapsed_time(b) < 10.0      # (waits of 100 us and some steps, and a fallback of some 200 us)
+    # two ways to form the same fp32 sums: logits of up to 2^5 binary orders
+    assert torch.allclose(scores, want, rtol=32 * 2.0 ** -24, atol=0)
+    assert torch.allclose(mass, want_mass, rtol=32 * 2.0 ** -24, atol=0)
+
+
 @pytest.mark.parametrize("d,P,n_m,row_bytes", [(128, 40, 300, 1 << 24), (64, 200, 260, 1 << 24), (128, 60, 8230, 1 << 19)])
 def test_response_rows_more_than_4_gib_apart(d, P, n_m, row_bytes):
     """Token strides up to 16 MiB: the response span of one head may reach over more than 32 bits of offset."""
