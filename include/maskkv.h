@@ -132,7 +132,7 @@ int maskkv_score_workspace_bytes(const maskkv_desc* desc, size_t* bytes);
  * is the faster way.  Its workgroups, one per compute unit, wait for each other's row sums, so they all have to be
  * resident.  Calls on several streams of a process line up for that and take what they take on one stream.  Another
  * process that scores on the same GPU (or a second copy of this library) is not seen, nor is any other kernel
- * that leaves a compute unit less than 145 KB of LDS or half of its registers for a long time: workgroups that have
+ * that leaves a compute unit less than 145 KB of LDS or not all of its registers for a long time: workgroups that have
  * waited for the others for 0.1 ms and about as long again as the sweep takes give up, and the call is done in two
  * passes by those that run, with the same results to fp32 rounding.  (Two processes that score 32 heads x 32k keys at
  * once: 0.45 ms a call of each, 0.12 ms alone.)

@@ -5,20 +5,22 @@
 
 namespace maskkv {
 
-// score.hip
-size_t score_workspace_bytes(const maskkv_desc* d, const Lens& lens, bool two_pass = false);
+// score.hip.  sweep_groups: workgroups of the single sweep, or 0 for the two passes.  (Choosing takes some 10 us of host time for
+// the largest batches: once per call.)
+int score_sweep_groups(const maskkv_desc* d, const Lens& lens);
+size_t score_workspace_bytes(const maskkv_desc* d, const Lens& lens, int sweep_groups);
 int launch_score(const maskkv_desc* d, const View& Q, const View& K, const Lens& lens, float scale, float* scores,
                  int64_t score_stride, float* prompt_mass, void* workspace, hipStream_t stream,
-                 void* const* events, const float* row_lse = nullptr, bool two_pass = false);
+                 void* const* events, int sweep_groups, const float* row_lse = nullptr);
 
 // sweep.hip: the scores in one sweep over the keys
-bool sweep_wanted(const maskkv_desc* d, const Lens& lens, int nqg);
+int sweep_groups(const maskkv_desc* d, const Lens& lens, int nqg);
 size_t sweep_workspace_bytes(const maskkv_desc* d, int nqg);
 // for tests and measurements: marks the device's sweep as taken age_us ago, as by a call that has not ended (age_us < 0: not taken)
 int hold_sweep(int64_t age_us, hipStream_t stream);
 int launch_sweep(const maskkv_desc* d, const View& Q, const View& K, const Lens& lens, float scale, float* scores,
-                 int64_t score_stride, float* prompt_mass, float* group_sums, int64_t group_stride, int nqg, void* area,
-                 hipStream_t stream, const float** unit_mass);
+                 int64_t score_stride, float* prompt_mass, float* group_sums, int64_t group_stride, int nqg, int groups,
+                 void* area, hipStream_t stream, const float** unit_mass);
 
 // select.hip
 size_t select_workspace_bytes(const maskkv_desc* d);

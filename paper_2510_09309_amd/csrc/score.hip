@@ -582,13 +582,15 @@ struct ScoreArea {
 
 }  // namespace
 
-size_t score_workspace_bytes(const maskkv_desc* d, const Lens& lens, bool two_pass) {
-  return ScoreArea(d, lens, !two_pass && sweep_wanted(d, lens, query_groups(d))).bytes;
+int score_sweep_groups(const maskkv_desc* d, const Lens& lens) { return sweep_groups(d, lens, query_groups(d)); }
+
+size_t score_workspace_bytes(const maskkv_desc* d, const Lens& lens, int sweep_groups) {
+  return ScoreArea(d, lens, sweep_groups > 0).bytes;
 }
 
 int launch_score(const maskkv_desc* d, const View& Q, const View& K, const Lens& lens, float scale, float* scores,
                  int64_t score_stride, float* prompt_mass, void* workspace, hipStream_t stream,
-                 void* const* events, const float* row_lse, bool two_pass) {
+                 void* const* events, int sweep_groups, const float* row_lse) {
   ScoreParams prm;
   prm.row_lse = row_lse;
   prm.Q = Q;
@@ -604,7 +606,7 @@ int launch_score(const maskkv_desc* d, const View& Q, const View& K, const Lens&
   prm.n_query = d->n_query * prm.q_per_kv;
   stat_slots(d, lens, prm.map1, &prm.parts_p, &prm.parts_r);
   prm.c = scale * kLog2e;
-  const bool sweep = !two_pass && !row_lse && sweep_wanted(d, lens, query_groups(d));
+  const bool sweep = sweep_groups > 0 && !row_lse;
   const ScoreArea area(d, lens, sweep);
   char* ws = reinterpret_cast<char*>(workspace);
   prm.stats = reinterpret_cast<float2*>(ws);
@@ -618,7 +620,7 @@ int launch_score(const maskkv_desc* d, const View& Q, const View& K, const Lens&
   if (sweep) {
     if (int e = mark(events, 0, stream)) return e;
     if (int e = launch_sweep(d, Q, K, lens, scale, scores, score_stride, prompt_mass, prm.group_sums, prm.group_stride,
-                             query_groups(d), ws, stream, &prm.unit_mass))
+                             query_groups(d), sweep_groups, ws, stream, &prm.unit_mass))
       return e;
     if (int e = mark(events, 1, stream)) return e;
     if (int e = mark(events, 2, stream)) return e;

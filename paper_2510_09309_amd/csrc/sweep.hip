@@ -65,7 +65,7 @@ constexpr float kSmallSum = 2.f;
 constexpr float kNoRow = 0.5f;             // whole sum of a row that does not exist (its mass is then cut off at 0; a row that does has 1)
 constexpr uint32_t kNoPart = 0xFFFFFFFFu;  // not there (a part has its sign bit clear)
 
-constexpr int kMaxUnits = 16384;           // of a launch, see sweep_wanted
+constexpr int kMaxUnits = 16384;           // of a launch, see sweep_groups
 constexpr int kMaxGroups = 256;            // workgroups of a sweep, and chunks of a unit, at most (one per compute unit)
 
 struct Control {
@@ -1172,8 +1172,10 @@ int launch(const maskkv_desc* d, const SweepParams& prm, hipStream_t stream) {
 
 // A launch of 66000 units (33000 heads of 40 keys, 300 voting rows), once tried, ended in a memory fault whose cause was not found.
 // The sweep is kept to a quarter of that, where no array of the workspace is larger than 2^30 bytes; more take the two passes.
-bool sweep_wanted(const maskkv_desc* d, const Lens& lens, int nqg) {
-  return d->dtype == MASKKV_BF16 && (int64_t)d->B * d->H * nqg <= kMaxUnits && Plan(d, lens, nqg).faster;
+int sweep_groups(const maskkv_desc* d, const Lens& lens, int nqg) {
+  if (d->dtype != MASKKV_BF16 || (int64_t)d->B * d->H * nqg > kMaxUnits) return 0;
+  const Plan plan(d, lens, nqg);
+  return plan.faster ? plan.groups : 0;
 }
 
 int hold_sweep(int64_t age_us, hipStream_t stream) {
@@ -1184,8 +1186,8 @@ int hold_sweep(int64_t age_us, hipStream_t stream) {
 size_t sweep_workspace_bytes(const maskkv_desc* d, int nqg) { return Layout(d, nqg).bytes; }
 
 int launch_sweep(const maskkv_desc* d, const View& Q, const View& K, const Lens& lens, float scale, float* scores,
-                 int64_t score_stride, float* prompt_mass, float* group_sums, int64_t group_stride, int nqg, void* area,
-                 hipStream_t stream, const float** unit_mass) {
+                 int64_t score_stride, float* prompt_mass, float* group_sums, int64_t group_stride, int nqg, int groups,
+                 void* area, hipStream_t stream, const float** unit_mass) {
   SweepParams prm;
   prm.Q = Q;
   prm.K = K;
@@ -1201,7 +1203,7 @@ int launch_sweep(const maskkv_desc* d, const View& Q, const View& K, const Lens&
   int x = 0;
   for (int b = 0; b < d->B; ++b) x += (lens.P[b] + kKeys - 1) / kKeys * d->H * nqg;
   prm.chunks = x;
-  prm.groups = Plan(d, lens, nqg).groups;
+  prm.groups = groups;
   // 100 us and about what the sweep takes, in which the fallback would be done, too.  (What keeps workgroups from being placed is
   // another program's kernels, a sweep of another process among them, whose lock is its own, or of another stream: the time
   // these take has nothing to do with this call's.  Two processes that score 32k keys at once, us a call of each: 455, with 20 ms 5000.)
