@@ -17,13 +17,14 @@
 // waits for a sum that is not needed yet, and every wait is bounded: if the workgroups turn out not to be all resident, or a
 // row's sum leaves the range of the integers, a two-pass fallback at the end of the same kernel does the work.
 //
-// What bounds it (32 heads x 128, 32k tokens, 256 rows: 119 us for the sweep, of 163 us for two passes and merge before): in a
-// loop of such calls the board's power.  The clock falls to 1.6 GHz, where a step is 5400 cycles, 2048 of them MFMAs, and
-// variants with fewer vector instructions take the same time at a lower clock; without the MFMAs 66 us, without the
-// loads of rows and keys 87, without exponentials 96, without exchange and column sums 94.  At 8k tokens (1.9 GHz) the call
-// takes 38 us, 58 before; the ragged batch of bench.py 505 us, 730 before.  Both waves of a SIMD half a step apart, 2 or 8
-// copies of the sums, or asking for the sums earlier in the step: slower (a sum that is asked for before it is
-// complete has to be asked for again, and a line that is being read is slow to add to).
+// What bounds it (32 heads x 128, 32k tokens, 256 rows: 114 us for the sweep, of 163 us for two passes and merge before): a step of 7100
+// to 7500 cycles, 2048 of them MFMAs and about twice as many vector instructions of a SIMD's two waves, which overlap only
+// partly, with waits for packed rows and row sums from L2 on top.  When it took 119 us: without the MFMAs 66 us, without the
+// loads of rows and keys 87, without exponentials 96, without exchange and column sums 94.  In a loop of such calls the
+// board is at its 1400 W and the clock 10 % below that of short calls (2.1 against 2.3 GHz).  At 8k tokens the call takes 38 us, 58
+// before; the ragged batch of perf/cases.py 520 us, 730 before, that of bench.py 577-620, 760-876 before.  Both waves of a SIMD
+// half a step apart, 2 or 8 copies of the sums, or asking for the sums earlier in the step: slower (a sum that is asked for
+// before it is complete has to be asked for again, and a line that is being read is slow to add to).
 #include <type_traits>
 
 #include "kernels.hpp"
@@ -117,7 +118,8 @@ struct SweepParams {
 // kernels may hold compute units as well (a workgroup needs 145 KB of LDS and, at head_dim 128, all registers).  Workgroups that are
 // kept apart that way give up after `patience`, and those that run do the work in the fallback.
 // us a call on two streams at once (one stream; the fallback for whoever finds the lock taken; the two passes): 4k keys 24, 28, 31, 30;
-// 8k 38, 40, 40, 58; 32k 119, 121, 168, 162; 8 sequences x 8k with 512 rows 445, 454, 605, 648.
+// 8k 38, 40, 40, 58; 32k 119, 121, 168, 162; 8 sequences x 8k with 512 rows 445, 454, 605, 648.  Six threads with a stream each: 4k 24
+// (30 with the two passes), 32k 200 (146: with several waiting at once most calls take the fallback; 240 with waits of 500 us).
 __device__ unsigned long long sweep_lock;
 constexpr int kPlaces = 16;
 constexpr int kPlaceWords = 32;            // (a line each)
@@ -125,7 +127,9 @@ __device__ unsigned sweep_placed[kPlaces * kPlaceWords];
 constexpr int kWaiters = 8;
 constexpr int kTick = 20;                  // 2^20 ticks of the 100 MHz clock: 10 ms
 constexpr uint32_t kStale = 100;           // 1 s
-constexpr uint64_t kStartWait = 50000;     // 500 us, which is what the fallback costs more than the sweep in large calls
+// 100 us.  Longer gains nothing (25 us are enough for two streams, and a start kernel that waits behind the same hardware queue as the
+// sweep it waits for, or that keeps a place from it beside other waiting ones, waits in vain), 10 us is too short.
+constexpr uint64_t kStartWait = 10000;
 
 __device__ __forceinline__ uint32_t placed() {  // by all sweeps (to be called by a whole wave)
   const int lane = threadIdx.x & 63;
