@@ -13,9 +13,9 @@ Prints ONE JSON line.  `value` is the metric's own definition: prompt tokens sco
 second per layer = P / (t_score + t_select + t_compact), the three calls bracketed by HIP events
 inside the timed region; `ms_per_step` is the wall time of the whole step (attention included).
 The line also carries per-call timings (mean, median, minimum over the timed steps), compressed- and
-full-cache attention TFLOP/s, a roofline object for the dominant kernel (score pass 1, bracketed by
-HIP events on the launch stream inside the timed region) with the whole scoring call beside it, the
-same calls on peaky logits, the other configurations (a single 4k-prompt layer, the 8k-prompt
+full-cache attention TFLOP/s, a roofline object for the scoring sweep (its start kernel and the sweep
+kernel, bracketed by HIP events on the launch stream inside the timed region) with the whole scoring
+call beside it, the same calls on peaky logits, the other configurations (a single 4k-prompt layer, the 8k-prompt
 32-layer stack with its budget schedule, the 32k-prompt stack with on-device head budgets, the
 batched ragged configuration), probes of what the box sustains, and the CPU oracle timed on bounded
 samples.
@@ -37,9 +37,9 @@ if ROOT not in sys.path:
 
 MFMA_BF16_PEAK_TFLOPS = 2500.0   # MI355X dense bf16
 HBM_PEAK_GBS = 8000.0
-# HBM bytes read + written by one launch of score pass 1 at the 32k prompt: rocprofv3 --pmc FETCH_SIZE and WRITE_SIZE,
-# each scaled by what it reads for a copy of known size (profiles/score_pass1_c4_hbm_traffic.md).  Other workloads: null.
-SCORE_PASS1_TRAFFIC_BYTES = {"C4": 141373.0 * 1024 * 2.0 + 1126.0 * 1024}
+# HBM bytes read + written by the two kernels of the scoring sweep at the 32k prompt: rocprofv3 --pmc FETCH_SIZE and WRITE_SIZE,
+# each scaled by what it reads for a copy of known size (profiles/c4_hbm_traffic.md).  Other workloads: null.
+SCORE_SWEEP_TRAFFIC_BYTES = {"C4": (140894.3 + 5167.8) * 1024 * 2.0 + (20489.0 + 2688.3) * 1024}
 
 
 def workload(name: str) -> dict:
@@ -140,12 +140,12 @@ class Path:
 
     def score(self, i, stream, marks=None, bb=None):
         Q, K, _ = self.layers[i % len(self.layers)]
-        if self.row_lse is not None:   # the second scoring pass alone, from given row normalisers
+        if self.row_lse is not None:   # the column-sum pass alone, from given row normalisers
             self.mk.maskkv_score_given_lse(self.desc, Q, K, 0.0, self.row_lse[i % len(self.layers)], self.scores,
                                            self.stride, self.mass, self.ws_score, stream)
         elif marks is None:
             self.mk.maskkv_score(self.desc, Q, K, 0.0, self.scores, self.stride, self.mass, self.ws_score, stream)
-        else:   # the same launches, with events recorded around the passes
+        else:   # the same launches, with events recorded between them
             bb.maskkv_bench_score_marked(self.desc, Q, K, 0.0, self.scores, self.stride, self.mass, self.ws_score,
                                          marks, stream)
 
@@ -172,7 +172,7 @@ def timed_steps(torch, hev, path, budgets, steps, warmup, bb, every_call=False):
     """`warmup` untimed steps, then exactly `steps` whole-path steps timed by the wall clock, with HIP events on the
     launch stream inside the region.  An event between two kernels costs a few microseconds (the second kernel
     starts only after the event has been processed; kernels enqueued back to back start within 10 ns of each other),
-    so the region proper records three per step: at the start of the step, after score pass 1, and after compact.
+    so the region proper records three per step: at the start of the step, after the scoring sweep, and after compact.
     `every_call` also brackets score, select, compact and attend separately (used for the per-call breakdown, not for
     the headline)."""
     stream = torch.cuda.current_stream()
@@ -181,15 +181,15 @@ def timed_steps(torch, hev, path, budgets, steps, warmup, bb, every_call=False):
         path.select(i, budgets, stream)
         path.compact(i, stream)
         path.attend(i, stream)
-    two_pass = path.row_lse is None   # (the mark after pass 1 exists only in the two-pass scoring call)
-    # per step: 0 start, 2 after pass 1, 3 scored, 4 selected, 5 gathered; one more event closes the last step
+    marked = path.row_lse is None   # (a call with given normalisers takes no marks)
+    # per step: 0 start, 2 after the sweep, 3 scored, 4 selected, 5 gathered; one more event closes the last step
     ev = [[hev.create() for _ in range(6)] for _ in range(steps + 1)]
     torch.cuda.synchronize()
     t0 = time.perf_counter()
     for i in range(steps):
         e = ev[i]
         hev.record(e[0], stream)
-        path.score(i, stream, marks=(0, e[2], 0, 0) if two_pass else None, bb=bb)
+        path.score(i, stream, marks=(0, e[2], 0, 0) if marked else None, bb=bb)
         if every_call:
             hev.record(e[3], stream)
         path.select(i, budgets, stream)
@@ -205,8 +205,8 @@ def timed_steps(torch, hev, path, budgets, steps, warmup, bb, every_call=False):
     out = {"wall_ms_per_step": wall_ms, "evict": span(0, 5),
            "attend": [hev.elapsed_ms(ev[i][5], ev[i + 1][0]) for i in range(steps)],
            "step": [hev.elapsed_ms(ev[i][0], ev[i + 1][0]) for i in range(steps)]}
-    if two_pass:
-        out["pass1"] = span(0, 2)
+    if marked:
+        out["sweep"] = span(0, 2)
     if every_call:
         out.update({"score": span(0, 3), "select": span(3, 4), "compact": span(4, 5)})
     for e in ev:
@@ -624,7 +624,7 @@ def main():
     # ---- the timed region: exactly --steps whole-path steps
     tr = timed_steps(torch, hev, path, budgets, args.steps, args.warmup, bb)
     ms_per_step = tr["wall_ms_per_step"]
-    pass1_ms = float(np.mean(tr["pass1"]))
+    sweep_ms = float(np.mean(tr["sweep"]))
     evict_ms = float(np.mean(tr["evict"]))
     attend_ms = float(np.mean(tr["attend"]))
     # ---- the same steps again with every call bracketed (each extra event costs the step a few microseconds)
@@ -656,13 +656,13 @@ def main():
                                f"step (score, select, compact, attend), {len(layers)} resident layers rotated",
                    "global_batch": 1, "seq_len": N},
         "whole_step_prompt_tokens_per_s": P / (ms_per_step * 1e-3),
-        "timed_region_ms": {k: stats(tr[k]) for k in ("evict", "pass1", "attend", "step")},
+        "timed_region_ms": {k: stats(tr[k]) for k in ("evict", "sweep", "attend", "step")},
         "every_call_bracketed_ms": {"steps": len(tb["step"]), "ms_per_step": tb["wall_ms_per_step"],
-                                    **{k: stats(tb[k]) for k in ("score", "pass1", "select", "compact", "attend",
+                                    **{k: stats(tb[k]) for k in ("score", "sweep", "select", "compact", "attend",
                                                                  "evict", "step")}},
         "breakdown_ms": {"score": score_ms, "select": float(np.mean(tb["select"])), "compact": compact_ms,
                          "attend": float(np.mean(tb["attend"])), "attend_full": t_full["median"],
-                         "score_pass1_in_timed_region": pass1_ms, "score_hot_same_layer": t_score_hot["median"]},
+                         "score_sweep_in_timed_region": sweep_ms, "score_hot_same_layer": t_score_hot["median"]},
         "attend_full_ms": t_full,
         "attend_compressed_tflops": flop_attend / (attend_ms * 1e-3) / 1e12,
         "attend_compressed_frac_of_mfma_peak": flop_attend / (attend_ms * 1e-3) / 1e12 / MFMA_BF16_PEAK_TFLOPS,
@@ -673,26 +673,24 @@ def main():
         "score_k_read_gbs_algorithmic": bytes_k / (score_ms * 1e-3) / 1e9,
         "gather_gbs": bytes_gather / (compact_ms * 1e-3) / 1e9,
         "roofline": {
-            "kernel": "score_kernel<bf16,128,pass 1> (QK^T over all keys + exp + row statistics)",
-            "bound": "mfma", "achieved": flop_qk_all / (pass1_ms * 1e-3) / 1e12, "peak": MFMA_BF16_PEAK_TFLOPS,
-            "unit": "TFLOP/s", "frac": flop_qk_all / (pass1_ms * 1e-3) / 1e12 / MFMA_BF16_PEAK_TFLOPS,
-            "traffic": SCORE_PASS1_TRAFFIC_BYTES.get(args.workload),
-            "note": "achieved = the method's one QK^T (2*n_m*N*d*H flop) over the duration of pass 1 alone; maskkv_score "
-                    "forms the logits twice (pass 1, merge, pass 2): whole_call prices the call on the same single QK^T",
-            "whole_call": {"what": "maskkv_score (pass 1 + merge + pass 2)",
+            "kernel": "sweep_start_kernel + sweep_kernel (QK^T over all keys, exponentials, row sums, column sums)",
+            "bound": "mfma", "achieved": flop_qk_all / (sweep_ms * 1e-3) / 1e12, "peak": MFMA_BF16_PEAK_TFLOPS,
+            "unit": "TFLOP/s", "frac": flop_qk_all / (sweep_ms * 1e-3) / 1e12 / MFMA_BF16_PEAK_TFLOPS,
+            "traffic": SCORE_SWEEP_TRAFFIC_BYTES.get(args.workload),
+            "note": "achieved = the method's one QK^T (2*n_m*N*d*H flop), which the sweep forms once, over the duration of both "
+                    "kernels; whole_call: the call between events of its own, in the run with every call bracketed",
+            "whole_call": {"what": "maskkv_score",
                            "achieved": flop_qk_all / (score_ms * 1e-3) / 1e12,
-                           "frac": flop_qk_all / (score_ms * 1e-3) / 1e12 / MFMA_BF16_PEAK_TFLOPS,
-                           "frac_counting_executed_flops":
-                               2.0 * flop_qk_all / (score_ms * 1e-3) / 1e12 / MFMA_BF16_PEAK_TFLOPS},
-            "hbm_view": {"achieved_GBs": (bytes_k + 2.0 * n_m * d * H) / (pass1_ms * 1e-3) / 1e9,
+                           "frac": flop_qk_all / (score_ms * 1e-3) / 1e12 / MFMA_BF16_PEAK_TFLOPS},
+            "hbm_view": {"achieved_GBs": (bytes_k + 2.0 * n_m * d * H) / (sweep_ms * 1e-3) / 1e9,
                          "peak_GBs": HBM_PEAK_GBS},
         },
     }
 
     if not args.no_extras:
         # ---- scoring when the rows' normalisers come from the model's own first-step attention over the full sequence
-        # (maskkv_attend_full returns them): the second scoring pass alone.  Not the headline: `value` above is the
-        # stand-alone two-pass call.
+        # (maskkv_attend_full returns them): the column-sum pass alone.  Not the headline: `value` above is the
+        # stand-alone call.
         path.row_lse = []
         for (Q, K, V) in layers:
             lse = torch.empty(H * n_m, dtype=torch.float32, device="cuda")
@@ -707,7 +705,7 @@ def main():
             "timed_region_ms": {k: stats(tg[k]) for k in ("score", "select", "compact", "attend", "evict")},
             "prompt_tokens_scored_evicted_per_s": P / (float(np.mean(tg["evict"])) * 1e-3)}
         # ---- the same MFMA calls on peaky logits (components 9.5 x wider: softmax rows concentrate on few keys, so
-        # the lazily raised running references of scoring and attention leave their cheapest branch)
+        # the attention's lazily raised running references leave their cheapest branch)
         peaky = [device_layer(torch, cfg, 100 + l, sigma=9.5) for l in range(2)]
         pk = Path(torch, mk, cfg, peaky, cap)
         pk.score(0, stream)
@@ -739,9 +737,9 @@ def main():
     if not args.no_extras:
         out["layer_importance"] = layer_importance_rate(torch, mk, N)
         peaks = measured_peaks(torch, bb)
-        n_exp = float(n_m) * N * H                       # exponentials of one pass
+        n_exp = float(n_m) * N * H                       # exponentials of a call
         gauss2 = peaks["mfma_bf16_tflops_gaussian_operands"]["two_waves_per_simd"]
-        peaks["score_pass1_vs_measured"] = {
+        peaks["score_sweep_vs_measured"] = {
             "frac_of_mfma_on_constant_operands": out["roofline"]["achieved"] / peaks["mfma_bf16_tflops_constant_operands"],
             "frac_of_mfma_on_gaussian_operands": out["roofline"]["achieved"] / gauss2,
             "mfma_time_us_on_gaussian_operands": flop_qk_all / (gauss2 * 1e12) * 1e6,
@@ -750,7 +748,7 @@ def main():
             "pipeline_on_gaussian_operands_time_us": flop_qk_all / (
                 peaks["score_pipeline_on_gaussian_operands_tflops"]["two_waves_per_simd"] * 1e12) * 1e6,
             "k_stream_time_us": bytes_k / (peaks["stream_read_gbs"] * 1e9) * 1e6,
-            "measured_us": pass1_ms * 1e3}
+            "measured_us": sweep_ms * 1e3}
         out["measured_peaks"] = peaks
         out["batched"] = batched_ragged(torch, mk, synth)
     if not args.no_cpu_baseline:

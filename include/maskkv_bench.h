@@ -53,8 +53,10 @@ int maskkv_bench_probe(int which, int32_t iters, const void* src, void* dst, int
 /*
  * maskkv_score (same arguments, same result, same kernels: it calls the body of maskkv_score in libmaskkv.so)
  * with timing marks.  events: HOST array of 4 hipEvent_t (each may be NULL), created by the caller with timing
- * enabled; they are recorded on the stream before pass 1 (row statistics), before the merge, before pass 2
- * (column sums) and after pass 2.  Errors are reported through maskkv_last_error() of libmaskkv.so.
+ * enabled; they are recorded on the stream before the first kernel, twice in between and after the last kernel.
+ * Where the call is scored in two passes the two in between stand before the merge and before pass 2 (column
+ * sums); where it is scored in one sweep, both stand behind the sweep kernel, before the sums over query groups.
+ * Errors are reported through maskkv_last_error() of libmaskkv.so.
  */
 int maskkv_bench_score_marked(const maskkv_desc* desc, const maskkv_tensor* Q_mask, const maskkv_tensor* K_full,
                               float scale, float* scores, int64_t score_stride, float* prompt_mass,
