@@ -2,9 +2,9 @@
 // maskkv.h and makes the call.  Argument marshalling only.
 //
 // Why it is native: a layer step is four to five library calls whose kernels take 60 us together at short prompts; with the
-// arguments built as ctypes objects the four calls cost 51 us of host time, of which the HIP launches are 25 (measured at
-// 4 heads x 512 tokens: score 18.1 -> 12.6, select 9.5 -> 3.1, compact 10.1 -> 3.1, attend 14.5 -> 6.6 us with the
-// arguments already in place).  Here a tensor argument is a few loads.
+// arguments built as ctypes objects the four calls cost 43 us of host time, now 16.5 (4 heads x 512 tokens, fp32, each call
+// on a drained queue, median of 500: score 14.3 -> 7.5, select 7.9 -> 2.9, compact 8.9 -> 2.9, attend 12.0 -> 3.2 us; of that
+// select and attend have a kernel less to launch than then).  Here a tensor argument is a few loads.
 //
 // The entry points of the library come in as addresses (bind()), so whichever build of libmaskkv.so binding.py has loaded
 // is the one that runs.  The GIL is released around every call, as ctypes does.
