@@ -66,7 +66,7 @@ constexpr float kSmallSum = 2.f;
 constexpr float kNoRow = 0.5f;             // whole sum of a row that does not exist (its mass is then cut off at 0; a row that does has 1)
 constexpr uint32_t kNoPart = 0xFFFFFFFFu;  // not there (a part has its sign bit clear)
 
-constexpr int kMaxUnits = 16384;           // of a launch, see sweep_groups
+constexpr int kMaxUnits = 4096;            // of a launch, see sweep_groups
 constexpr int kMaxGroups = 256;            // workgroups of a sweep, and chunks of a unit, at most (one per compute unit)
 
 struct Control {
@@ -1175,7 +1175,7 @@ int launch(const maskkv_desc* d, const SweepParams& prm, hipStream_t stream) {
 }  // namespace
 
 // A launch of 66000 units (33000 heads of 40 keys, 300 voting rows), once tried, ended in a memory fault whose cause was not found.
-// The sweep is kept to a quarter of that, where no array of the workspace is larger than 2^30 bytes; more take the two passes.
+// The sweep is kept to the sizes that are in use (64 sequences x 32 heads x 2 groups of voting rows); more take the two passes.
 int sweep_groups(const maskkv_desc* d, const Lens& lens, int nqg) {
   if (d->dtype != MASKKV_BF16 || (int64_t)d->B * d->H * nqg > kMaxUnits) return 0;
   const Plan plan(d, lens, nqg);

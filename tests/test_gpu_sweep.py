@@ -118,6 +118,27 @@ def test_a_lock_that_was_never_given_back():
     bb.maskkv_bench_hold_sweep(-1)
 
 
+@pytest.mark.parametrize("d,n_m,H,Ps", [
+    (128, 1, 3, (1,)), (128, 31, 3, (127, 128, 129)), (64, 33, 3, (96, 0, 2049)), (128, 257, 3, (640, 1000)), (64, 300, 3, (5, 4000, 1)),
+    (128, 40, 1, (385,)), (64, 64, 90, (300, 1281)), (128, 300, 160, (513,))])
+def test_fallback_at_edges_of_chunks_spans_and_row_groups(d, n_m, H, Ps):
+    """A call that finds the device's sweep taken: one to three chunks a task and none, one task a unit and eight."""
+    from paper_2510_09309_amd import bench_binding as bb
+    batch = hp.Batch([synth.make_layer(70 + i, H=H, d=d, P=P, n_m=n_m, dtype="bf16", n_planted=P // 50, amplitude=2.5)
+                      for i, P in enumerate(Ps)])
+    ws = hp.workspace(hp.mk().maskkv_score_workspace_bytes(batch.desc))
+    want, want_mass, run = swept(batch, ws)
+    assert run == 1
+    bb.maskkv_bench_hold_sweep(0)
+    scores, mass, run = swept(batch, ws)
+    bb.maskkv_bench_hold_sweep(-1)
+    assert run == 0
+    assert hp.check_scores(batch, scores, mass, heads=range(min(H, 3))) <= 1e-4
+    # two ways to form the same fp32 sums: logits of up to 2^5 binary orders
+    assert torch.allclose(scores, want, rtol=32 * 2.0 ** -24, atol=0, equal_nan=True)
+    assert torch.allclose(mass, want_mass, rtol=32 * 2.0 ** -24, atol=0)
+
+
 def test_sweeps_on_two_streams_line_up():
     """Of calls that two streams make at once, at most a few need the fallback, and all give what one stream gives."""
     m = hp.mk()
