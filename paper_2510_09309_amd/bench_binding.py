@@ -1,5 +1,5 @@
-"""ctypes binding of libmaskkv_bench.so (``include/maskkv_bench.h``): measurement probes and maskkv_score with stage
-marks.  For benchmark harnesses and their tests only; nothing of the method's path goes through this module."""
+"""ctypes binding of libmaskkv_bench.so (``include/maskkv_bench.h``): measurement probes, maskkv_score with stage
+marks, and a mark that makes it take its fallback.  For benchmark harnesses and their tests only; nothing of the method's path goes through this module."""
 from __future__ import annotations
 
 import ctypes as ct

@@ -2,7 +2,8 @@
 //   maskkv_bench_probe         kernels that each exercise one resource of the chip, so that a harness can quote
 //                              kernel rates against what this machine sustains at the clock it actually runs at;
 //   maskkv_bench_score_marked  maskkv_score with HIP events recorded at its stage boundaries (it calls the body
-//                              of maskkv_score inside libmaskkv.so).
+//                              of maskkv_score inside libmaskkv.so);
+//   maskkv_bench_hold_sweep    makes maskkv_score take its fallback.
 #include <stdio.h>
 
 #include "../kernels.hpp"

@@ -1,5 +1,6 @@
 """The single-sweep scoring kernel (bf16, prompts of at most one chunk of 128 keys per compute unit): edges of its chunks, row
-groups and response span, its fallback for row sums out of range, and calls on two streams at once (needs an MI355X).
+groups and response span, the range of its row sums and the digits of its masses, its fallback, and calls on several streams at
+once (needs an MI355X).
 
 Reference: the oracle, or for long prompts maskkv_score_given_lse with the normalisers of maskkv_attend_full, which is another
 kernel (the second of two passes) on the same inputs.
