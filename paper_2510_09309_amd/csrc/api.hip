@@ -175,10 +175,10 @@ int score_entry(const maskkv_desc* desc, const maskkv_tensor* Q_mask, const mask
     set_error("scores is NULL or score_stride %lld < P_max %d", (long long)score_stride, desc->P_max);
     return MASKKV_EINVAL;
   }
-  const int groups = score_sweep_groups(desc, lens);
-  if (int e = check_workspace("score", workspace, workspace_bytes, score_workspace_bytes(desc, lens, groups))) return e;
+  const SweepPlan plan = score_sweep_plan(desc, lens);
+  if (int e = check_workspace("score", workspace, workspace_bytes, score_workspace_bytes(desc, lens, plan))) return e;
   return launch_score(desc, q, k, lens, pick_scale(desc, scale), scores, score_stride, prompt_mass, workspace,
-                      reinterpret_cast<hipStream_t>(stream), events, groups);
+                      reinterpret_cast<hipStream_t>(stream), events, plan);
 }
 
 }  // namespace maskkv
@@ -211,7 +211,7 @@ int maskkv_score_workspace_bytes(const maskkv_desc* desc, size_t* bytes) {
     set_error("bytes is NULL");
     return MASKKV_EINVAL;
   }
-  *bytes = score_workspace_bytes(desc, lens, score_sweep_groups(desc, lens));
+  *bytes = score_workspace_bytes(desc, lens, score_sweep_plan(desc, lens));
   return MASKKV_OK;
 }
 
@@ -234,11 +234,11 @@ int maskkv_score_given_lse(const maskkv_desc* desc, const maskkv_tensor* Q_mask,
     set_error("row_lse or scores is NULL, or score_stride %lld < P_max %d", (long long)score_stride, desc->P_max);
     return MASKKV_EINVAL;
   }
-  const int groups = score_sweep_groups(desc, lens);
-  if (int e = check_workspace("score_given_lse", workspace, workspace_bytes, score_workspace_bytes(desc, lens, groups)))
+  const SweepPlan plan = score_sweep_plan(desc, lens);  // (the workspace is asked for as for maskkv_score)
+  if (int e = check_workspace("score_given_lse", workspace, workspace_bytes, score_workspace_bytes(desc, lens, plan)))
     return e;
   return launch_score(desc, q, k, lens, pick_scale(desc, scale), scores, score_stride, prompt_mass, workspace,
-                      reinterpret_cast<hipStream_t>(stream), nullptr, 0, row_lse);
+                      reinterpret_cast<hipStream_t>(stream), nullptr, SweepPlan{}, row_lse);
 }
 
 int maskkv_score_static(const maskkv_desc* desc, const maskkv_tensor* Q_mask, const maskkv_tensor* K_full, float scale,
@@ -253,9 +253,9 @@ int maskkv_score_static(const maskkv_desc* desc, const maskkv_tensor* Q_mask, co
     return MASKKV_EINVAL;
   }
   // (the single sweep needs more scratch than the two passes: a description that only the latter fit takes them)
-  int groups = score_sweep_groups(desc, lens);
-  if (score_workspace_bytes(desc, lens, groups) > kStaticScratchBytes) groups = 0;
-  const size_t need = score_workspace_bytes(desc, lens, groups);
+  SweepPlan plan = score_sweep_plan(desc, lens);
+  if (score_workspace_bytes(desc, lens, plan) > kStaticScratchBytes) plan = SweepPlan{};
+  const size_t need = score_workspace_bytes(desc, lens, plan);
   if (need > kStaticScratchBytes) {
     set_error("score_static: this description needs %zu bytes of scratch, the static array holds %zu; use maskkv_score "
               "with a caller workspace", need, kStaticScratchBytes);
@@ -264,7 +264,7 @@ int maskkv_score_static(const maskkv_desc* desc, const maskkv_tensor* Q_mask, co
   void* ws = nullptr;
   if (int e = static_scratch(&ws)) return e;
   return launch_score(desc, q, k, lens, pick_scale(desc, scale), scores, score_stride, prompt_mass, ws,
-                      reinterpret_cast<hipStream_t>(stream), nullptr, groups);
+                      reinterpret_cast<hipStream_t>(stream), nullptr, plan);
 }
 
 int maskkv_select_workspace_bytes(const maskkv_desc* desc, size_t* bytes) {

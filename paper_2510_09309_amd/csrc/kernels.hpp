@@ -5,21 +5,46 @@
 
 namespace maskkv {
 
-// score.hip.  sweep_groups: workgroups of the single sweep, or 0 for the two passes.  (Choosing takes some 10 us of host time for
-// the largest batches: once per call.)
-int score_sweep_groups(const maskkv_desc* d, const Lens& lens);
-size_t score_workspace_bytes(const maskkv_desc* d, const Lens& lens, int sweep_groups);
+// How the single sweep's workgroups are dealt out (sweep.hip).  A run: from workgroup `place` on, `side` heads of a sequence side by
+// side, `width` workgroups in all, for its heads from `head` on, `times` times.  The runs of a round follow each other and have the
+// same number of times.
+constexpr int kMaxRuns = 2 * MASKKV_MAX_BATCH;
+struct SweepPlan {
+  int groups;   // workgroups, or 0: two passes
+  int subsets;  // a head's groups of voting rows are dealt to as many sets of workgroups
+  int runs;
+  int rounds;   // the most chunks of a workgroup
+  uint32_t places[kMaxRuns], heads[kMaxRuns], repeats[kMaxRuns];
+  __host__ __device__ int place(int i) const { return places[i] & 0xFFFF; }
+  __host__ __device__ int width(int i) const { return places[i] >> 16; }
+  __host__ __device__ int head(int i) const { return heads[i] & 0xFFFF; }
+  __host__ __device__ int side(int i) const { return heads[i] >> 16; }
+  __host__ __device__ int times(int i) const { return repeats[i] & 0xFFFF; }
+  __host__ __device__ int sequence(int i) const { return repeats[i] >> 16; }
+  __host__ __device__ bool has(int i, int w) const { return w >= place(i) && w < place(i) + width(i); }
+  __host__ __device__ bool serves(int i, int b, int h) const { return sequence(i) == b && h >= head(i) && h < head(i) + side(i) * times(i); }
+  void put(int i, int p, int s, int w, int b, int h) {
+    places[i] = (uint32_t)p | (uint32_t)w << 16;
+    heads[i] = (uint32_t)h | (uint32_t)s << 16;
+    repeats[i] = (uint32_t)b << 16;
+  }
+  void repeat(int i, int t) { repeats[i] |= (uint32_t)t; }
+};
+
+// score.hip.  (Choosing takes some 10 us of host time for the largest batches: once per call.)
+SweepPlan score_sweep_plan(const maskkv_desc* d, const Lens& lens);
+size_t score_workspace_bytes(const maskkv_desc* d, const Lens& lens, const SweepPlan& plan);
 int launch_score(const maskkv_desc* d, const View& Q, const View& K, const Lens& lens, float scale, float* scores,
                  int64_t score_stride, float* prompt_mass, void* workspace, hipStream_t stream,
-                 void* const* events, int sweep_groups, const float* row_lse = nullptr);
+                 void* const* events, const SweepPlan& plan, const float* row_lse = nullptr);
 
 // sweep.hip: the scores in one sweep over the keys
-int sweep_groups(const maskkv_desc* d, const Lens& lens, int nqg);
-size_t sweep_workspace_bytes(const maskkv_desc* d, int nqg);
+SweepPlan sweep_plan(const maskkv_desc* d, const Lens& lens, int nqg);
+size_t sweep_workspace_bytes(const maskkv_desc* d, int nqg, const SweepPlan& plan);
 // for tests and measurements: marks the device's sweep as taken age_us ago, as by a call that has not ended (age_us < 0: not taken)
 int hold_sweep(int64_t age_us, hipStream_t stream);
 int launch_sweep(const maskkv_desc* d, const View& Q, const View& K, const Lens& lens, float scale, float* scores,
-                 int64_t score_stride, float* prompt_mass, float* group_sums, int64_t group_stride, int nqg, int groups,
+                 int64_t score_stride, float* prompt_mass, float* group_sums, int64_t group_stride, int nqg, const SweepPlan& plan,
                  void* area, hipStream_t stream, const float** unit_mass);
 
 // select.hip

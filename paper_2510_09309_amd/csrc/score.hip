@@ -88,7 +88,7 @@ struct ScoreParams {
   float* group_sums;  // [B*H][nqg][group_stride] column sums per query group (more than one group only)
   int64_t group_stride;
   float* prompt_mass; // [B*H] or null
-  const float* unit_mass;  // [B*H][nqg] prompt masses of the query groups, from the single sweep, or null
+  const float* unit_mass;  // [B*H][nqg] prompt masses of the groups, from the single sweep, or null
 };
 
 __device__ __forceinline__ int ceil_div(int a, int b) { return (a + b - 1) / b; }
@@ -566,7 +566,7 @@ namespace {
 // Workspace: [row statistics and normalisers, or what the single sweep needs][column sums per query group]
 struct ScoreArea {
   size_t stats, sums, bytes;
-  ScoreArea(const maskkv_desc* d, const Lens& lens, bool sweep) {
+  ScoreArea(const maskkv_desc* d, const Lens& lens, const SweepPlan& plan) {
     int pp, pr;
     stat_slots(d, lens, make_map(d, lens, true), &pp, &pr);
     const int64_t bh = (int64_t)d->B * d->H;
@@ -575,22 +575,22 @@ struct ScoreArea {
     stats = ((size_t)(bh * (pp + pr) * nq) * sizeof(float2) + 255) / 256 * 256;
     const size_t lse = ((size_t)(bh * nq) * sizeof(float) + 255) / 256 * 256;
     sums = stats + lse;
-    if (sweep) sums = max(sums, sweep_workspace_bytes(d, nqg));
+    if (plan.groups > 0) sums = max(sums, (sweep_workspace_bytes(d, nqg, plan) + 255) / 256 * 256);
     bytes = sums + (nqg > 1 ? (size_t)(bh * nqg * group_stride(d)) * sizeof(float) : 0);
   }
 };
 
 }  // namespace
 
-int score_sweep_groups(const maskkv_desc* d, const Lens& lens) { return sweep_groups(d, lens, query_groups(d)); }
+SweepPlan score_sweep_plan(const maskkv_desc* d, const Lens& lens) { return sweep_plan(d, lens, query_groups(d)); }
 
-size_t score_workspace_bytes(const maskkv_desc* d, const Lens& lens, int sweep_groups) {
-  return ScoreArea(d, lens, sweep_groups > 0).bytes;
+size_t score_workspace_bytes(const maskkv_desc* d, const Lens& lens, const SweepPlan& plan) {
+  return ScoreArea(d, lens, plan).bytes;
 }
 
 int launch_score(const maskkv_desc* d, const View& Q, const View& K, const Lens& lens, float scale, float* scores,
                  int64_t score_stride, float* prompt_mass, void* workspace, hipStream_t stream,
-                 void* const* events, int sweep_groups, const float* row_lse) {
+                 void* const* events, const SweepPlan& plan, const float* row_lse) {
   ScoreParams prm;
   prm.row_lse = row_lse;
   prm.Q = Q;
@@ -606,8 +606,8 @@ int launch_score(const maskkv_desc* d, const View& Q, const View& K, const Lens&
   prm.n_query = d->n_query * prm.q_per_kv;
   stat_slots(d, lens, prm.map1, &prm.parts_p, &prm.parts_r);
   prm.c = scale * kLog2e;
-  const bool sweep = sweep_groups > 0 && !row_lse;
-  const ScoreArea area(d, lens, sweep);
+  const bool sweep = plan.groups > 0 && !row_lse;
+  const ScoreArea area(d, lens, plan);
   char* ws = reinterpret_cast<char*>(workspace);
   prm.stats = reinterpret_cast<float2*>(ws);
   prm.lse2 = reinterpret_cast<float*>(ws + area.stats);
@@ -620,12 +620,12 @@ int launch_score(const maskkv_desc* d, const View& Q, const View& K, const Lens&
   if (sweep) {
     if (int e = mark(events, 0, stream)) return e;
     if (int e = launch_sweep(d, Q, K, lens, scale, scores, score_stride, prompt_mass, prm.group_sums, prm.group_stride,
-                             query_groups(d), sweep_groups, ws, stream, &prm.unit_mass))
+                             query_groups(d), plan, ws, stream, &prm.unit_mass))
       return e;
     if (int e = mark(events, 1, stream)) return e;
     if (int e = mark(events, 2, stream)) return e;
-    if (map2.nqg > 1)
-      if (int e = launch_group_sum(prm, map2.nqg, stream)) return e;
+    if (plan.subsets > 1)
+      if (int e = launch_group_sum(prm, plan.subsets, stream)) return e;
     return mark(events, 3, stream);
   }
   if (d->dtype == MASKKV_BF16)

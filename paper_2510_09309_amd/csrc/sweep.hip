@@ -6,25 +6,32 @@
 // the row sums of all chunks of that unit have arrived and the kept chunk is turned into column sums.
 //
 //   start kernel  row references (the response span's log-sum-exp), the rows' sums over the response keys in units of them (1
-//                 but for the rounding of the reference) as the initial values of the sums, and the voting rows packed in
-//                 MFMA fragment order.
-//   sweep kernel  one workgroup of eight waves (32 rows each) per compute unit; chunk x of the launch, all units end to
-//                 end, belongs to workgroup x mod G, so that the workgroups work on the same unit at the same time.
+//                 but for the rounding of the reference) as the initial values of the sums, the voting rows packed in
+//                 MFMA fragment order, and a table of every workgroup's chunks.
+//   sweep kernel  one workgroup of eight waves (32 rows each) per compute unit.  The chunks of a head are with as many workgroups
+//                 at the same time (a round, see Packing); a workgroup takes its chunk through all groups of 256 voting rows of
+//                 the head, with the keys in LDS, and adds the groups' column sums in registers.
+//
+// A step is a matrix phase (the logits of the chunk and their exponentials) and a vector phase (row sums published, the chunk of the
+// step before completed).  Waves 4-7 run half a step behind waves 0-3, one of each on a SIMD, kept so by a barrier per phase:
+// the vector phase is mostly latency, which the other wave's matrix phase fills.
 //
 // Per step a workgroup loads 64 KB of packed rows (from L2, into registers, each fragment as soon as the last MFMA that read
-// the old one is issued) and 32 KB of keys (direct transfers into a ring of four chunks, two steps ahead).  Row sums are added
+// the old one is issued) and per chunk 32 KB of keys (direct transfers into a ring of four chunks, three chunks ahead, and at the
+// end of the vector phase: earlier they delay the answers that it waits for, in the matrix phase they stall it).  Row sums are added
 // with 64-bit integer atomics, 4 copies of each sum; a step later every wave reads the sums of its own rows.  Nothing
 // waits for a sum that is not needed yet, and every wait is bounded: if the workgroups turn out not to be all resident, or a
 // row's sum leaves the range of the integers, a two-pass fallback at the end of the same kernel does the work.
 //
-// What bounds it (32 heads x 128, 32k tokens, 256 rows: 114 us for the sweep, of 163 us for two passes and merge before): a step of 7100
-// to 7500 cycles, 2048 of them MFMAs and about twice as many vector instructions of a SIMD's two waves, which overlap only
-// partly, with waits for packed rows and row sums from L2 on top.  When it took 119 us: without the MFMAs 66 us, without the
-// loads of rows and keys 87, without exponentials 96, without exchange and column sums 94.  In a loop of such calls the
-// board is at its 1400 W and the clock 10 % below that of short calls (2.1 against 2.3 GHz).  At 8k tokens the call takes 38 us, 58
-// before; the ragged batch of perf/cases.py 520 us, 730 before, that of bench.py 577-620, 760-876 before.  Both waves of a SIMD
-// half a step apart, 2 or 8 copies of the sums, or asking for the sums earlier in the step: slower (a sum that is asked for
-// before it is complete has to be asked for again, and a line that is being read is slow to add to).
+// What bounds it: a step of 6700 to 7100 cycles, 2048 of them MFMAs.  A wave issues an instruction every 4 to 5 cycles, a matrix phase
+// has 1800 cycles of them, a vector phase 1500 to 2000, and the two waves of a SIMD share the vector pipe, where v_exp_f32
+// takes 8 cycles and an MFMA about as many.  In a loop of such calls the board is at its 1400 W and the clock 10 % below that of
+// short calls (2.1 against 2.3 GHz).  us a call, with both groups of waves in the same phase, chunks dealt out end to end and keys
+// transferred for every group of rows before: 32 heads x 128 with 256 rows, 4k keys 28.7 -> 28.2, 8k 39 -> 37.9, 32k 120 -> 115; 4
+// heads with 1792 rows over 30k keys 93.5 -> 87.6; the ragged batch of perf/cases.py 518 -> 481.  (Without transfers of keys, with
+// wrong results, the ragged batch took 420 instead of 505, without loads of rows 455, without the exchange 465.)  Slower: raised
+// wave priority in the vector phase or for waves 4-7; a first sum per XCD that the last of its workgroups adds to the whole
+// (two latencies instead of one); 2 or 8 copies of the sums.
 #include <type_traits>
 
 #include "kernels.hpp"
@@ -77,17 +84,29 @@ struct Control {
 
 constexpr int kSpans = 8;                  // pieces of a unit's keys in the fallback, at most
 
+// A chunk of a head's keys.
+struct __attribute__((aligned(16))) Chunk {
+  int bh;
+  uint32_t shape;     // its number, 8 bits; the head's number of chunks less one, 8 bits; its number of keys
+  const char* keys;
+};
+
 struct SweepParams {
   View Q, K;
   Lens lens;
   int B, H, n_resp;
   int n_query;      // voting rows per key/value head: q_per_kv query heads of n_qh mask queries each
-  int n_qh, q_per_kv, nqg;
+  int n_qh, q_per_kv;
+  int subsets;      // of a head's groups of voting rows; each counts as a head of its own, with the same keys
+  int nqg;          // groups of a subset
   int rows;         // voting rows per unit, a multiple of 32 (the last unit of a head may have fewer)
-  int chunks;       // in total
-  int groups;       // workgroups of the sweep
+  SweepPlan plan;
+  struct Chunk* table;  // [groups][rounds] what a workgroup's chunks are, in turn
+  int* counts;          // [groups] how many they are
+  int rounds;
   int patience;     // how long a workgroup waits for the others' row sums, in ticks of the 100 MHz clock
-  int spans;        // pieces of a unit's keys in the fallback
+  int spans;        // pieces of a unit's keys in the fallback's first pass
+  int spans2;       // pieces of a head's keys in its second pass
   float c;          // scale * log2(e)
   uint64_t* low;    // [units][kCopies][256]
   uint64_t* high;   // [units][256]
@@ -100,9 +119,10 @@ struct SweepParams {
   int n_parts;      // chunks of the longest prompt
   int* late;        // [units] 1 + the next unit of a workgroup's list for late_masses, or 0
   float2* stats;    // [units][kSpans][256] (reference, sum) of a span of chunks (fallback)
-  float* out;       // [units][out_stride]: the scores, or with more than one query group the groups' column sums
+  float* out;       // [B*H*subsets][out_stride]
   int64_t out_stride;
-  float* mass;      // [units] or null
+  float* mass;      // [B*H*subsets] or null
+  __device__ int heads() const { return H * subsets; }  // of a sequence, subsets counted as heads
 };
 
 // The workgroups of a sweep wait for each other, so all of them have to be resident, and two sweeps may not be placed on a device at
@@ -221,17 +241,43 @@ __device__ __forceinline__ float wave_sum(float v) {
 // Takes the lock, or waits for it: 2 us.  Where units are few, that is for a workgroup of its own, the last; where they fill the
 // chip and one workgroup more would start alone at the end, the first does it when it is done.
 __device__ __forceinline__ void start_lock(const SweepParams& prm) {
+  const int w = threadIdx.x;
+  if (w < prm.plan.groups) {
+    int n = 0;
+    for (int i = 0; i < prm.plan.runs; ++i) n += prm.plan.has(i, w) ? prm.plan.times(i) : 0;
+    prm.counts[w] = n;
+  }
   if (threadIdx.x >= 64) return;
-  bool run = take_lock(prm.groups, 0);
+  bool run = take_lock(prm.plan.groups, 0);
   const uint64_t t0 = wall_clock64();
   while (!run && wall_clock64() - t0 < kStartWait) {
     __builtin_amdgcn_s_sleep(32);
-    run = take_lock(prm.groups, kWaiters);
+    run = take_lock(prm.plan.groups, kWaiters);
   }
   if (threadIdx.x == 0) {
     prm.ctl->run = run;
     prm.ctl->redo = !run;
     prm.ctl->ticket = 0;
+  }
+}
+
+// The table's entries of a head (to be called by a whole wave).
+__device__ __forceinline__ void start_table(const SweepParams& prm, int b, int vh) {
+  const int lane = threadIdx.x & 63;
+  const int P = prm.lens.P[b], nc = (P + kKeys - 1) / kKeys;
+  int i = 0;
+  while (i < prm.plan.runs && !prm.plan.serves(i, b, vh)) ++i;
+  if (i == prm.plan.runs) return;  // (no prompt)
+  const int nth = vh - prm.plan.head(i), side = prm.plan.side(i);
+  const int w0 = prm.plan.place(i) + nth % side * nc;
+  for (int ci = lane; ci < nc; ci += 64) {
+    int t = nth / side;
+    for (int j = 0; j < i; ++j) t += prm.plan.has(j, w0 + ci) ? prm.plan.times(j) : 0;
+    Chunk c;
+    c.bh = b * prm.heads() + vh;
+    c.shape = (uint32_t)ci | (uint32_t)(nc - 1) << 8 | (uint32_t)min(P - ci * kKeys, kKeys) << 16;
+    c.keys = prm.K.row(b, vh / prm.subsets, (int64_t)ci * kKeys);
+    prm.table[(int64_t)(w0 + ci) * prm.rounds + t] = c;
   }
 }
 
@@ -249,8 +295,9 @@ __global__ __launch_bounds__(kThreads) void sweep_start_kernel(const SweepParams
   const int lane = threadIdx.x & 63, r = lane & 31, g = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int unit = blockIdx.x / SPLIT;
-  const int bh = unit / prm.nqg, qg = unit - bh * prm.nqg;
-  const int b = bh / prm.H, h = bh - b * prm.H;
+  const int bh = unit / prm.nqg, vh = bh % prm.heads();
+  const int b = bh / prm.heads(), h = vh / prm.subsets;
+  const int qg = (vh - h * prm.subsets) * prm.nqg + unit - bh * prm.nqg;
   const int P = prm.lens.P[b];
   const char* keys = prm.K.row(b, h, P);
   auto dma = [&](int t) {
@@ -277,8 +324,9 @@ __global__ __launch_bounds__(kThreads) void sweep_start_kernel(const SweepParams
 
   if (rb == 0 && part_of == 0 && lane == 0) {
     prm.spans_done[unit] = 0;
-    if (P == 0 && prm.mass) prm.mass[unit] = 0.f;
+    if (P == 0 && prm.mass) prm.mass[bh] = 0.f;
   }
+  if (blockIdx.x % SPLIT == SPLIT - 1 && wave == kWaves - 1 && unit == bh * prm.nqg) start_table(prm, b, vh);
   const int64_t row0 = (int64_t)unit * kRows + rb * 32;
   if (part_of == 0) {
     if (lane < 32) {
@@ -370,7 +418,7 @@ __device__ __forceinline__ void sweep_redo(const SweepParams& prm, uint32_t lds0
   constexpr int S = C::kSteps;
   const int lane = threadIdx.x & 63, r = lane & 31, g = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int spans = prm.spans, tasks = prm.B * prm.H * prm.nqg * spans;  // of a pass
+  const int spans = prm.spans, tasks = prm.B * prm.heads() * prm.nqg * spans, tasks2 = prm.B * prm.heads() * prm.spans2;  // of the two passes
   const uint32_t word = lds0 + C::kOffMass;                   // one int: the ticket, or whether to go on
   const uint32_t colsum = lds0 + C::kOffCs;                   // [2][kWaves][kKeys] floats
   for (;;) {
@@ -379,174 +427,189 @@ __device__ __forceinline__ void sweep_redo(const SweepParams& prm, uint32_t lds0
     if (threadIdx.x == 0) *in_lds<int>(word) = __hip_atomic_fetch_add(&prm.ctl->ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
     const int ticket = __builtin_amdgcn_readfirstlane(*in_lds<int>(word));
-    if (ticket >= 2 * tasks) return;
+    if (ticket >= tasks + tasks2) return;
     const bool second = ticket >= tasks;
+    const int pieces = second ? prm.spans2 : spans;
     const int task = second ? ticket - tasks : ticket;
-    const int unit = task / spans, span = task % spans;
-    const int bh = unit / prm.nqg;
-    const int b = bh / prm.H, h = bh - b * prm.H;
+    const int span = task % pieces, first = second ? task / pieces * prm.nqg : task / pieces;  // (first unit)
+    const int bh = first / prm.nqg;
+    const int b = bh / prm.heads(), h = bh % prm.heads() / prm.subsets;
     const int P = prm.lens.P[b];
     const int nc = ceil_div(P, kKeys);
-    const int c0 = nc * span / spans, c1 = nc * (span + 1) / spans;
-    const int64_t row0 = (int64_t)unit * kRows + wave * 32;
-    u32x4 qf[S];
+    const int c0 = nc * span / pieces, c1 = nc * (span + 1) / pieces;
+    float head_mass = 0.f;
+    for (int unit = first; unit < first + (second ? prm.nqg : 1); ++unit) {
+      const int64_t row0 = (int64_t)unit * kRows + wave * 32;
+      u32x4 qf[S];
 #pragma unroll
-    for (int s = 0; s < S; ++s) qf[s] = *reinterpret_cast<const u32x4*>(prm.qpack + row0 * C::kRowB + s * 1024 + lane * 16);
-    float2* st = prm.stats + (int64_t)unit * kSpans * kRows + wave * 32 + r;  // (of query row r; one span is kRows further)
-    float m = kNegBig, l = 0.f;
-    float nl[16];  // second pass: minus the base-2 log-sum-exp of this lane's rows
-    if (second) {
-      if (threadIdx.x == 0) {
-        const uint64_t t0 = wall_clock64();
-        while (__hip_atomic_load(&prm.spans_done[unit], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < spans && wall_clock64() - t0 < kTaskWait)
-          __builtin_amdgcn_s_sleep(8);
-      }
-      asm volatile("" ::: "memory");
-      __syncthreads();
-      // all spans and the response span
-      const float ref = -prm.start[row0 * 2 + r] * prm.c;  // +inf for a row that does not exist
-      const float own = prm.start[row0 * 2 + 32 + r];
-      const bool live = ref != INFINITY;
-      float M = live ? ref : 0.f, Lp = 0.f;
-      float2 v[kSpans];
-#pragma unroll
-      for (int i = 0; i < kSpans; ++i) {
-        v[i] = make_float2(kNegBig, 0.f);
-        if (i < spans) {
-          v[i].x = __hip_atomic_load(&st[i * kRows].x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          v[i].y = __hip_atomic_load(&st[i * kRows].y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-        M = fmaxf(M, v[i].x);
-      }
-#pragma unroll
-      for (int i = 0; i < kSpans; ++i) Lp += v[i].y * fast_exp2(v[i].x - M);
-      const float L = fmaf(own, fast_exp2(ref - M), Lp);
-      const float nlse = live ? -(M + __log2f(L)) : -INFINITY;
-      if (span == 0 && prm.mass) {
-        float mass = live && g == 0 ? Lp / L : 0.f;
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) mass += __shfl_xor(mass, o, 64);
-        if (lane == 0) *in_lds<float>(colsum + wave * 4) = mass;
-        __syncthreads();
+      for (int s = 0; s < S; ++s) qf[s] = *reinterpret_cast<const u32x4*>(prm.qpack + row0 * C::kRowB + s * 1024 + lane * 16);
+      float2* st = prm.stats + (int64_t)unit * kSpans * kRows + wave * 32 + r;  // (of query row r; one span is kRows further)
+      float m = kNegBig, l = 0.f;
+      float nl[16];  // second pass: minus the base-2 log-sum-exp of this lane's rows
+      if (second) {
         if (threadIdx.x == 0) {
-          float t = 0.f;
-          for (int w = 0; w < kWaves; ++w) t += *in_lds<float>(colsum + w * 4);
-          prm.mass[unit] = t;
+          const uint64_t t0 = wall_clock64();
+          while (__hip_atomic_load(&prm.spans_done[unit], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < spans && wall_clock64() - t0 < kTaskWait)
+            __builtin_amdgcn_s_sleep(8);
         }
+        asm volatile("" ::: "memory");
         __syncthreads();
-      }
+        // all spans and the response span
+        const float ref = -prm.start[row0 * 2 + r] * prm.c;  // +inf for a row that does not exist
+        const float own = prm.start[row0 * 2 + 32 + r];
+        const bool live = ref != INFINITY;
+        float M = live ? ref : 0.f, Lp = 0.f;
+        float2 v[kSpans];
 #pragma unroll
-      for (int i = 0; i < 16; ++i) nl[i] = __shfl(nlse, 8 * (i / 4) + 4 * g + (i % 4), 64);
-    }
-    auto dma = [&](int n) {  // chunk number n of the span (or its last one) into slot n of the ring
-      const int ci = min(c0 + n, c1 - 1), last = P - 1 - ci * kKeys;
-      const char* base = prm.K.row(b, h, ci * kKeys);
-#pragma unroll
-      for (int j = 0; j < C::kMoves; ++j) {
-        const int row = wave * (kKeys / kWaves) + j * C::kRPI + lane / C::kPPR;
-        const int piece = (lane % C::kPPR) ^ C::swz(row);
-        dma16(base, (uint32_t)min(row, last) * (uint32_t)prm.K.stride_t + piece * 16,
-              lds0 + n % C::kRing * C::kKBytes + (wave * (kKeys / kWaves) + j * C::kRPI) * C::kRowB);
-      }
-    };
-    auto flush = [&](int n) {  // column sums of chunk n of the span
-      const int j = (c0 + n) * kKeys + (int)threadIdx.x;
-      if ((int)threadIdx.x >= kKeys || j >= P) return;
-      const uint32_t cs = colsum + (n & 1) * kWaves * kKeys * 4 + threadIdx.x * 4;
-      float v = 0.f;
-#pragma unroll
-      for (int w = 0; w < kWaves; ++w) v += *in_lds<const float>(cs, w * kKeys * 4);
-      prm.out[(int64_t)unit * prm.out_stride + j] = v;
-    };
-    if (c0 < c1) {
-      dma(0);
-      dma(1);
-    }
-    auto walk = [&](auto columns) {  // a pass's instructions in a loop of their own
-      constexpr bool kColumns = decltype(columns)::value;
-      for (int n = 0; n < c1 - c0; ++n) {
-        dma(n + 2);  // (its slot was last read before the barrier of the step before)
-        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"i"(2 * C::kMoves) : "memory");
-        if (kColumns && n > 0) flush(n - 1);
-        const uint32_t chunk = lds0 + n % C::kRing * C::kKBytes;
-        f32x16 a[kNB];
-#pragma unroll
-        for (int kb = 0; kb < kNB; ++kb) {
-          a[kb] = f32x16{};
-#pragma unroll
-          for (int s = 0; s < S; ++s) {
-            const u32x4 kf = *in_lds<const u32x4>(chunk + (kb * 32 + r) * C::kRowB + (((2 * s + g) ^ C::swz(r)) << 4));
-            if constexpr (kColumns)
-              mfma_step<bf16_t>(qf[s], kf, a[kb]);
-            else
-              mfma_step<bf16_t>(kf, qf[s], a[kb]);
+        for (int i = 0; i < kSpans; ++i) {
+          v[i] = make_float2(kNegBig, 0.f);
+          if (i < spans) {
+            v[i].x = __hip_atomic_load(&st[i * kRows].x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            v[i].y = __hip_atomic_load(&st[i * kRows].y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           }
+          M = fmaxf(M, v[i].x);
         }
-        if constexpr (kColumns) {
+#pragma unroll
+        for (int i = 0; i < kSpans; ++i) Lp += v[i].y * fast_exp2(v[i].x - M);
+        const float L = fmaf(own, fast_exp2(ref - M), Lp);
+        const float nlse = live ? -(M + __log2f(L)) : -INFINITY;
+        if (span == 0 && prm.mass) {
+          float mass = live && g == 0 ? Lp / L : 0.f;
+#pragma unroll
+          for (int o = 32; o > 0; o >>= 1) mass += __shfl_xor(mass, o, 64);
+          if (lane == 0) *in_lds<float>(colsum + wave * 4) = mass;
+          __syncthreads();
+          if (threadIdx.x == 0) {
+            float t = 0.f;
+            for (int w = 0; w < kWaves; ++w) t += *in_lds<float>(colsum + w * 4);
+            head_mass += t;
+            if (unit == first + prm.nqg - 1) prm.mass[bh] = head_mass;
+          }
+          __syncthreads();
+        }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) nl[i] = __shfl(nlse, 8 * (i / 4) + 4 * g + (i % 4), 64);
+      }
+      auto dma = [&](int n) {  // chunk number n of the span (or its last one) into slot n of the ring
+        const int ci = min(c0 + n, c1 - 1), last = P - 1 - ci * kKeys;
+        const char* base = prm.K.row(b, h, ci * kKeys);
+#pragma unroll
+        for (int j = 0; j < C::kMoves; ++j) {
+          const int row = wave * (kKeys / kWaves) + j * C::kRPI + lane / C::kPPR;
+          const int piece = (lane % C::kPPR) ^ C::swz(row);
+          dma16(base, (uint32_t)min(row, last) * (uint32_t)prm.K.stride_t + piece * 16,
+                lds0 + n % C::kRing * C::kKBytes + (wave * (kKeys / kWaves) + j * C::kRPI) * C::kRowB);
+        }
+      };
+      auto flush = [&](int n) {  // column sums of chunk n of the span
+        const int j = (c0 + n) * kKeys + (int)threadIdx.x;
+        if ((int)threadIdx.x >= kKeys || j >= P) return;
+        const uint32_t cs = colsum + (n & 1) * kWaves * kKeys * 4 + threadIdx.x * 4;
+        float v = 0.f;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) v += *in_lds<const float>(cs, w * kKeys * 4);
+        float* to = prm.out + (int64_t)bh * prm.out_stride + j;  // (this thread has written the sums of the groups before)
+        if (unit > first) v += __hip_atomic_load(to, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(to, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      };
+      if (c0 < c1) {
+        dma(0);
+        dma(1);
+      }
+      auto walk = [&](auto columns) {  // a pass's instructions in a loop of their own
+        constexpr bool kColumns = decltype(columns)::value;
+        for (int n = 0; n < c1 - c0; ++n) {
+          dma(n + 2);  // (its slot was last read before the barrier of the step before)
+          asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"i"(2 * C::kMoves) : "memory");
+          if (kColumns && n > 0) flush(n - 1);
+          const uint32_t chunk = lds0 + n % C::kRing * C::kKBytes;
+          f32x16 a[kNB];
 #pragma unroll
           for (int kb = 0; kb < kNB; ++kb) {
-            float v = 0.f;
+            a[kb] = f32x16{};
 #pragma unroll
-            for (int i = 0; i < 16; ++i) v += fast_exp2(fmaf(a[kb][i], prm.c, nl[i]));
-            v += xor32(v);
-            if (g == 0) *in_lds<float>(colsum + ((n & 1) * kWaves * kKeys + wave * kKeys + kb * 32 + r) * 4) = v;
+            for (int s = 0; s < S; ++s) {
+              const u32x4 kf = *in_lds<const u32x4>(chunk + (kb * 32 + r) * C::kRowB + (((2 * s + g) ^ C::swz(r)) << 4));
+              if constexpr (kColumns)
+                mfma_step<bf16_t>(qf[s], kf, a[kb]);
+              else
+                mfma_step<bf16_t>(kf, qf[s], a[kb]);
+            }
           }
-        } else {
-          const int left = P - (c0 + n) * kKeys;
-          if (left < kKeys)
+          if constexpr (kColumns) {
+#pragma unroll
+            for (int kb = 0; kb < kNB; ++kb) {
+              float v = 0.f;
+#pragma unroll
+              for (int i = 0; i < 16; ++i) v += fast_exp2(fmaf(a[kb][i], prm.c, nl[i]));
+              v += xor32(v);
+              if (g == 0) *in_lds<float>(colsum + ((n & 1) * kWaves * kKeys + wave * kKeys + kb * 32 + r) * 4) = v;
+            }
+          } else {
+            const int left = P - (c0 + n) * kKeys;
+            if (left < kKeys)
+#pragma unroll
+              for (int kb = 0; kb < kNB; ++kb)
+#pragma unroll
+                for (int i = 0; i < 16; ++i)
+                  if (kb * 32 + 8 * (i / 4) + 4 * g + (i % 4) >= left) a[kb][i] = -INFINITY;
+            float top = a[0][0];
 #pragma unroll
             for (int kb = 0; kb < kNB; ++kb)
 #pragma unroll
-              for (int i = 0; i < 16; ++i)
-                if (kb * 32 + 8 * (i / 4) + 4 * g + (i % 4) >= left) a[kb][i] = -INFINITY;
-          float top = a[0][0];
+              for (int i = 0; i < 16; ++i) top = fmaxf(top, a[kb][i]);
+            const float bm = fmaxf(m, top * prm.c);
+            float v = 0.f;
 #pragma unroll
-          for (int kb = 0; kb < kNB; ++kb)
+            for (int kb = 0; kb < kNB; ++kb)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) top = fmaxf(top, a[kb][i]);
-          const float bm = fmaxf(m, top * prm.c);
-          float v = 0.f;
-#pragma unroll
-          for (int kb = 0; kb < kNB; ++kb)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) v += fast_exp2(fmaf(a[kb][i], prm.c, -bm));
-          l = l * fast_exp2(m - bm) + v;
-          m = bm;
+              for (int i = 0; i < 16; ++i) v += fast_exp2(fmaf(a[kb][i], prm.c, -bm));
+            l = l * fast_exp2(m - bm) + v;
+            m = bm;
+          }
         }
+      };
+      if (second)
+        walk(std::true_type());
+      else
+        walk(std::false_type());
+      if (second && c0 < c1) {
+        __syncthreads();
+        flush(c1 - c0 - 1);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (the next group adds to these sums, and its transfers reuse the ring)
+        __syncthreads();
       }
-    };
-    if (second)
-      walk(std::true_type());
-    else
-      walk(std::false_type());
-    if (second && c0 < c1) {
-      __syncthreads();
-      flush(c1 - c0 - 1);
-    }
-    if (!second) {
-      const float mo = xor32(m), lo = xor32(l);
-      const float mm = fmaxf(m, mo);
-      if (g == 0) {
-        __hip_atomic_store(&st[span * kRows].x, mm, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(&st[span * kRows].y, l * fast_exp2(m - mm) + lo * fast_exp2(mo - mm), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (!second) {
+        const float mo = xor32(m), lo = xor32(l);
+        const float mm = fmaxf(m, mo);
+        if (g == 0) {
+          __hip_atomic_store(&st[span * kRows].x, mm, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          __hip_atomic_store(&st[span * kRows].y, l * fast_exp2(m - mm) + lo * fast_exp2(mo - mm), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        // (Device-scope stores that have completed are seen by every device-scope load that is issued later; a release here would
+        // write back the whole L2, an acquire above throw it away.)
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (threadIdx.x == 0) __hip_atomic_fetch_add(&prm.spans_done[unit], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
-      // (Device-scope stores that have completed are seen by every device-scope load that is issued later; a release here would
-      // write back the whole L2, an acquire above throw it away.)
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      __syncthreads();
-      if (threadIdx.x == 0) __hip_atomic_fetch_add(&prm.spans_done[unit], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   }
 }
 
-// A chunk: number ci of the nc of its unit.
-struct Chunk {
-  int unit, ci, nc, P;
-  // the chunk whose workgroup writes the unit's mass (not always the first, so that they are spread over workgroups)
-  __device__ int lead() const { return (unit & 15) < nc ? unit & 15 : 0; }
+// What a step of a walk works on: a chunk of a head's keys and one of the head's groups of voting rows.
+struct Task {
+  int bh, qg;
+  uint32_t shape;
+  __device__ int ci() const { return shape & 255; }
+  __device__ int nc() const { return (shape >> 8 & 255) + 1; }
+  __device__ int keys() const { return shape >> 16; }
+  __device__ int unit(const SweepParams& prm) const { return bh * prm.nqg + qg; }
 };
+// the chunk whose workgroup writes the head's mass (not always the first, so that they are spread over workgroups)
+__device__ __forceinline__ int lead_of(int bh, int nc) { return (bh & 15) < nc ? bh & 15 : 0; }
 
-// After the walk: the masses of the units whose leading chunk was this workgroup's and that have waves with mostly small row sums.
+// After the walk: the masses of the units whose leading chunk was this workgroup's and that have waves with mostly small row sums,
+// added to those of their heads.
 template <int D>
 __device__ __forceinline__ void late_masses(const SweepParams& prm, uint32_t lds0, int head) {
   using C = Cfg<D>;
@@ -556,8 +619,9 @@ __device__ __forceinline__ void late_masses(const SweepParams& prm, uint32_t lds
   while (head) {
     const int unit = head - 1;
     head = __builtin_amdgcn_readfirstlane(__hip_atomic_load(&prm.late[unit], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-    const int nc = ceil_div(prm.lens.P[unit / (prm.H * prm.nqg)], kKeys);
-    const int lead = Chunk{unit, 0, nc, 0}.lead();
+    const int bh = unit / prm.nqg;
+    const int nc = ceil_div(prm.lens.P[bh / prm.heads()], kKeys);
+    const int lead = lead_of(bh, nc);
     const uint32_t* part = prm.parts + ((int64_t)unit * kWaves + wave) * prm.n_parts;
     const uint64_t t0 = wall_clock64();
     float sum = 0.f;
@@ -601,7 +665,10 @@ __device__ __forceinline__ void late_masses(const SweepParams& prm, uint32_t lds
       float m = 0.f;
 #pragma unroll
       for (int w = 0; w < kWaves; ++w) m += *in_lds<const float>(lds0 + C::kOffMass, w * 4);
-      prm.mass[unit] = m;
+      // (the head's other groups' are there: this thread has written them)
+      m += __hip_atomic_load(&prm.mass[bh], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(&prm.mass[bh], m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
     __syncthreads();
   }
@@ -615,8 +682,6 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r = lane & 31, g = lane >> 5;
   const float c = prm.c;
-  const int G = gridDim.x;
-  const int mine = (prm.chunks - (int)blockIdx.x + G - 1) / G;  // chunks blockIdx.x, + G, + 2G, ...
   // A value hidden from the optimiser: what a step derives from it is then worth an instruction or two each time instead of
   // a register for the whole loop.
   auto here = [&](uint32_t v) {
@@ -625,62 +690,44 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
   };
   auto lane_now = [&]() { return (int)here(lane); };
 
-  // ---- the walk over this workgroup's chunks
-  int at_b = 0, at_h = 0, at_g = 0;
-  Chunk ahead{0, (int)blockIdx.x, (prm.lens.P[0] + kKeys - 1) / kKeys, prm.lens.P[0]};
-  const char* kbase = prm.K.row(0, 0, 0);
-  auto settle = [&]() {
-    while (ahead.ci >= ahead.nc) {
-      ahead.ci -= ahead.nc;
-      ++ahead.unit;
-      if (++at_g == prm.nqg) {
-        at_g = 0;
-        kbase += prm.K.stride_h;
-        if (++at_h == prm.H) {
-          at_h = 0;
-          ++at_b;
-          kbase = prm.K.row(at_b, 0, 0);
-          ahead.P = prm.lens.P[at_b];
-          ahead.nc = (ahead.P + kKeys - 1) / kKeys;
-        }
-      }
-    }
-  };
+  // ---- the walk
+  typedef const __attribute__((address_space(4))) Chunk* Table;
+  const Table table = (Table)(prm.table + (int64_t)blockIdx.x * prm.rounds);
+  const int chunks = *(const __attribute__((address_space(4))) int*)(prm.counts + blockIdx.x);
+  const int mine = chunks * prm.nqg;  // steps: each chunk with all groups of voting rows, so that keys are transferred once
   const uint32_t kstride = (uint32_t)prm.K.stride_t;
   const uint32_t lane16 = lane * 16;
   // Row wave * 16 + j * kRPI + rl of the chunk (rl: this lane's row of transfer j) has its pieces permuted by the low bits of
   // that number, which are j's and rl's side by side: one exclusive-or with a constant per transfer.
   const uint32_t krow = (uint32_t)lane / C::kPPR, kpiece = ((uint32_t)lane % C::kPPR ^ C::swz(krow)) << 4;
   const uint32_t koff = krow * kstride;
-  auto dma_k = [&](int slot) {  // the chunk `ahead` into slot `slot` of the ring
-    const char* base = kbase + (int64_t)(ahead.ci * kKeys + wave * (kKeys / kWaves)) * prm.K.stride_t;
-    const int last = ahead.P - 1 - ahead.ci * kKeys - wave * (kKeys / kWaves);  // row of the last key, counted from this wave's first
-    const uint32_t to = lds0 + slot * C::kKBytes + wave * (kKeys / kWaves) * C::kRowB;
-    if (last >= kKeys / kWaves - 1) {
-      const uint32_t piece = here(kpiece);
+  // Chunk number t into its slot of the ring: this wave's part.  (Rows past the last key re-read it; a wave all of whose rows are
+  // past it reads the chunk's first.)
+  auto dma_k = [&](int t) {
+    const Table c = table + min(t, chunks - 1);
+    const int last = (int)(c->shape >> 16) - 1 - wave * (kKeys / kWaves);  // row of the last key, counted from this wave's first
+    const char* base = c->keys + (uint64_t)(last < 0 ? 0 : wave * (kKeys / kWaves)) * kstride;
+    const uint32_t most = (uint32_t)max(last, 0) * kstride;
+    const uint32_t to = lds0 + t % C::kRing * C::kKBytes + wave * (kKeys / kWaves) * C::kRowB;
 #pragma unroll
-      for (int j = 0; j < C::kMoves; ++j)
-        dma16(base + (int64_t)(j * C::kRPI) * prm.K.stride_t, (piece ^ (C::swz(j * C::kRPI) << 4)) + koff, to + j * 1024);
-    } else {
-#pragma unroll
-      for (int j = 0; j < C::kMoves; ++j) {
-        const int row = min(j * C::kRPI + (int)here(krow), max(last, 0));
-        dma16(last >= 0 ? base : kbase, (here(kpiece) ^ (C::swz(j * C::kRPI) << 4)) + (uint32_t)row * kstride, to + j * 1024);
-      }
-    }
+    for (int j = 0; j < C::kMoves; ++j)
+      dma16(base, min(here(koff) + (uint32_t)(j * C::kRPI) * kstride, most) + (here(kpiece) ^ (C::swz(j * C::kRPI) << 4)), to + j * 1024);
   };
-  auto dma_start = [&](const Chunk& k, int par) {
-    dma4(reinterpret_cast<const char*>(prm.start + ((int64_t)k.unit * kRows + wave * 32) * 2), here(lane16) >> 2,
+  auto dma_start = [&](const Task& k, int par) {
+    dma4(reinterpret_cast<const char*>(prm.start + ((int64_t)k.unit(prm) * kRows + wave * 32) * 2), here(lane16) >> 2,
          lds0 + C::kOffStart + (par * kWaves + wave) * 256);
   };
   u32x4 qf[S];
   Base qlo, qhi;  // (two: an immediate offset reaches 4 KiB)
-  auto aim_q = [&](const Chunk& k) {
-    const char* q = prm.qpack + ((int64_t)k.unit * kWaves + wave) * C::kQBytes;
+  auto aim_q = [&](const Task& k) {
+    const char* q = prm.qpack + ((int64_t)k.unit(prm) * kWaves + wave) * C::kQBytes;
     qlo = base_of(q);
     qhi = base_of(q + 4096);
   };
-  auto load_q = [&](int ks, uint32_t off) { qf[ks] = *at<const u32x4>(ks < 4 ? qlo : qhi, off, ks % 4 * 1024); };
+  // (The loads of the walk are asm, and waited for by asm: the compiler does not see the transfers and would wait for all of them.)
+  auto load_q = [&](int ks, uint32_t off) {
+    asm volatile("global_load_dwordx4 %0, %1, %2 offset:%3" : "=v"(qf[ks]) : "v"(off), "s"(ks < 4 ? qlo : qhi), "i"(ks % 4 * 1024));
+  };
 
   // the row (of this wave's 32) whose sum the butterfly below leaves in a lane; lanes 2n and 2n+1 hold the same one
   auto row_of = [](int ln) {
@@ -703,28 +750,29 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
       for (int e = 0; e < 4; ++e) a[4 * i4 + e] = v[e];
     }
   };
-  // The ring's four chunks are addressed as two pairs: fa points at this lane's fragments of the first chunk of a pair (the
-  // second is an immediate offset away) and changes sides every other step.
-  uint32_t fa[S];
+  uint32_t fa[S];  // this lane's fragments of the chunk
 #pragma unroll
   for (int ks = 0; ks < S; ++ks) {
     fa[ks] = lds0 + r * C::kRowB + (((2 * ks + g) ^ C::swz(r)) << 4);
     asm volatile("" : "+v"(fa[ks]));
   }
-  auto turn = [&]() {
+  int slot = 0;
+  auto turn = [&]() {  // to the ring's next chunk
+    const int by = slot == C::kRing - 1 ? (1 - C::kRing) * C::kKBytes : C::kKBytes;
+    slot = slot == C::kRing - 1 ? 0 : slot + 1;
 #pragma unroll
-    for (int ks = 0; ks < S; ++ks) fa[ks] ^= 2 * C::kKBytes;
+    for (int ks = 0; ks < S; ++ks) fa[ks] += by;
   };
   u32x4 kf[kAhead + 1];
-  auto fetch = [&](int par, int n) {  // fragment n % S of block n / S of chunk `par` of the pair
-    kf[n % (kAhead + 1)] = *in_lds<const u32x4>(fa[n % S], par * C::kKBytes + n / S * 32 * C::kRowB);
+  auto fetch = [&](int n) {  // fragment n % S of block n / S
+    kf[n % (kAhead + 1)] = *in_lds<const u32x4>(fa[n % S], n / S * 32 * C::kRowB);
   };
   float rs[16];
   constexpr int E = 16 / S;  // logits per slot
   float arg[E];
   // Slot m of the exponentials of a chunk: the arguments of the next slot's, this slot's exponentials, the sums of the last
   // slot's (three independent strands: a wave issues in order and would wait for each result in turn).
-  auto expo = [&](int m, const f32x16& pre, f32x16 (&p)[kNB]) {
+  auto expo = [&](int m, f32x16 (&p)[kNB]) {
     float v[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) {
@@ -732,7 +780,7 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
       if (m >= 0 && m < kNB * S) v[e] = fast_exp2(arg[e]);
       if (m + 1 >= 0 && m + 1 < kNB * S) {
         const int j = (m + 1) % S * E + e;
-        arg[e] = (m + 1 < S ? pre[j] : p[(m + 1) / S][j]) * c;
+        arg[e] = p[(m + 1) / S][j] * c;
         asm volatile("" : "+v"(arg[e]));
       }
       if (m >= 1) {
@@ -749,47 +797,78 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
     }
   };
 
-  // Column sums of a completed chunk: add the waves' parts.  Two waves do it, another pair at every step.
-  auto flush = [&](const Chunk& k, int par, int turn) {
-    if (wave / 2 != turn % (kWaves / 2) || *in_lds<const int>(lds0 + C::kOffBad)) return;
-    const int col = (wave & 1) * 64 + lane_now();
-    const uint32_t cs = lds0 + C::kOffCs + par * kWaves * kKeys * 4 + col * 4;
-    float v = *in_lds<const float>(cs);
+  // Column sums of a chunk that is completed for all groups of voting rows: add the waves' parts.  The first four waves do it, 32
+  // keys each; the halves of a wave add four parts each.  (One store is issued in any case: vector() counts it.)  And the mass.
+  float mass = 0.f;  // of the head, as far as it is known
+  auto flush = [&](const Task& k, int par, bool there) {
+    const int ln = lane_now();
+    const int col = wave * 32 + (ln & 31);
+    const uint32_t cs = lds0 + C::kOffCs + (par * kWaves + (ln >> 5) * (kWaves / 2)) * kKeys * 4 + col * 4;
+    const int bad = *in_lds<const int>(lds0 + C::kOffBad);
+    float v[kWaves / 2];
 #pragma unroll
-    for (int w = 1; w < kWaves; ++w) v += *in_lds<const float>(cs, w * kKeys * 4);
-    const Base out = base_of(prm.out + (int64_t)k.unit * prm.out_stride + k.ci * kKeys);
-    if (col < k.P - k.ci * kKeys) *at<float>(out, col * 4) = v;
-    if (k.ci == k.lead() && col == 0 && prm.mass) {
+    for (int w = 0; w < kWaves / 2; ++w) v[w] = *in_lds<const float>(cs, w * kKeys * 4);
+    const bool whole = k.qg == prm.nqg - 1;
+    const int good = __builtin_amdgcn_readfirstlane(there ? bad ^ 1 : 0);
+    const int keys = good && whole ? min(max(k.keys() - wave * 32, 0), 32) : 0;
+    const uint32_t lanes = __builtin_amdgcn_readfirstlane((uint32_t)((1ull << keys) - 1));
+    float t = (v[0] + v[1]) + (v[2] + v[3]);
+    const auto sw = __builtin_amdgcn_permlane32_swap(as_u32(t), as_u32(t), false, false);
+    const unsigned u0 = sw[0], u1 = sw[1];
+    t = as_f32(u0) + as_f32(u1);
+    // (the compiler may have loaded the kernel's argument into vector registers; what one has written is not yet an address)
+    const uint64_t to = (uint64_t)(uintptr_t)(prm.out + (int64_t)k.bh * prm.out_stride + k.ci() * kKeys);
+    const uint64_t out = ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(to >> 32)) << 32) | (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)to);
+    uint64_t exec;
+    asm volatile("s_mov_b64 %0, exec\n\ts_mov_b64 exec, %1\n\ts_nop 4\n\tglobal_store_dword %2, %3, %4\n\ts_mov_b64 exec, %0"
+                 : "=&s"(exec) : "s"((uint64_t)lanes), "v"(col * 4), "v"(t), "s"(out) : "memory");
+    if (wave == 0 && good && k.ci() == lead_of(k.bh, k.nc()) && prm.mass) {
       const uint32_t ms = lds0 + C::kOffMass + par * kWaves * 4;
       float m = 0.f;
 #pragma unroll
       for (int w = 0; w < kWaves; ++w) m += *in_lds<const float>(ms, w * 4);
-      if (m >= 0.f) {
-        prm.mass[k.unit] = m;
-      } else if (m < 0.f) {  // (not known yet)
-        __hip_atomic_store(&prm.late[k.unit], *in_lds<const int>(lds0 + C::kOffLate), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        *in_lds<int>(lds0 + C::kOffLate) = k.unit + 1;
+      if (m < 0.f) {  // (not known yet)
+        if (ln == 0) {
+          const int unit = k.unit(prm);
+          __hip_atomic_store(at<int>(base_of(prm.late + unit), here(0)), *in_lds<const int>(lds0 + C::kOffLate), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          *in_lds<int>(lds0 + C::kOffLate) = unit + 1;
+        }
+      } else {
+        mass += m;
+      }
+      if (whole) {
+        if (ln == 0) __hip_atomic_store(&prm.mass[k.bh], mass, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        mass = 0.f;
       }
     }
   };
 
   uint64_t seen[kCopies];
-  auto ask = [&](const Chunk& k) {
-    const uint64_t* low = prm.low + ((int64_t)k.unit * kCopies * kRows + wave * 32);
+  auto ask = [&](const Task& k) {
+    const uint64_t* low = prm.low + ((int64_t)k.unit(prm) * kCopies * kRows + wave * 32);
+    const uint32_t off = here(row8);
+#pragma unroll
+    for (int i = 0; i < kCopies; ++i)
+      asm volatile("global_load_dwordx2 %0, %1, %2 offset:%3 sc1" : "=v"(seen[i]) : "v"(off), "s"(base_of(low + i / 2 * 2 * kRows)), "i"(i % 2 * kRows * 8));
+  };
+  auto ask_again = [&](const Task& k) {
+    const uint64_t* low = prm.low + ((int64_t)k.unit(prm) * kCopies * kRows + wave * 32);
     const uint32_t off = here(row8);
 #pragma unroll
     for (int i = 0; i < kCopies; ++i) seen[i] = peek(base_of(low + i * kRows), off);
     asm volatile("" ::: "memory");
   };
-  auto add = [&](const uint64_t* to, float f) {  // one chunk and the whole number next to f < 2^46
+  auto add = [&](const uint64_t* to, float f, uint64_t lanes) {  // one chunk and the whole number next to f < 2^46, by these lanes
     f = rintf(f);
     const float top = floorf(f * 2.3283064365386963e-10f);  // 2^-32
     const uint32_t hi = (uint32_t)top + (1u << (kCountShift - 32));
     const uint32_t lo = (uint32_t)fmaf(top, -4294967296.f, f);
-    __hip_atomic_fetch_add(at<uint64_t>(base_of(to), here(row8)), ((uint64_t)hi << 32) | lo, __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_AGENT);
+    const uint64_t v = ((uint64_t)hi << 32) | lo;
+    uint64_t exec;
+    asm volatile("s_mov_b64 %0, exec\n\ts_mov_b64 exec, %1\n\tglobal_atomic_add_x2 %2, %3, %4\n\ts_mov_b64 exec, %0"
+                 : "=&s"(exec) : "s"(lanes), "v"(here(row8)), "v"(v), "s"(base_of(to)) : "memory");
   };
-  auto publish = [&](const Chunk& k) {  // this wave's row sums (rs) of the chunk just formed
+  auto publish = [&](const Task& k) {  // this wave's row sums (rs) of the chunk just formed
     // sum over the 32 lanes of a half: 16 values, halved at every exchange
     float t8[8], t4[4], t2[2];
 #pragma unroll
@@ -812,32 +891,33 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
     float sum = (ln & 2) ? q1 : q0;
     sum += dpp<0xB1>(sum);  // neighbours
     const bool low = sum < kLowLimit;
-    if (!(ln & 1) && low) add(prm.low + (((int64_t)k.unit * kCopies + copy) * kRows + wave * 32), sum * kLowScale);
+    add(prm.low + (((int64_t)k.unit(prm) * kCopies + copy) * kRows + wave * 32), fminf(sum, kLowLimit) * kLowScale, __ballot(!(ln & 1) && low));
     if (!__all(low)) {  // (rare)
       const bool fits = sum < kHighLimit;
       if (!__all(low || fits)) {  // known to every workgroup of the unit before its row sums are complete
         __hip_atomic_store(&prm.ctl->redo, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
       }
-      if (!(ln & 1) && !low) add(prm.high + ((int64_t)k.unit * kRows + wave * 32), fits ? sum * kHighScale : 0.f);
+      add(prm.high + ((int64_t)k.unit(prm) * kRows + wave * 32), fits ? sum * kHighScale : 0.f, __ballot(!(ln & 1) && !low));
     }
   };
-  // Column sums of the chunk held in pc, once the row sums of its unit are all there.
-  auto complete = [&](const Chunk& k, int par, f32x16 (&pc)[kNB]) {
+  // Column sums of the chunk held in pc, once the row sums of its unit are all there, added to those of the groups before.
+  float sums[kNB / 2] = {};
+  auto complete = [&](const Task& k, int par, f32x16 (&pc)[kNB]) {
     uint64_t lo = 0, hi = 0;
 #pragma unroll
     for (int i = 0; i < kCopies; ++i) lo += seen[i];
-    bool ready = __all((int)(lo >> kCountShift) == k.nc);
+    bool ready = __all((int)(lo >> kCountShift) == k.nc());
     if (!ready && patient) {
       const uint64_t t0 = wall_clock64();
       do {
         __builtin_amdgcn_s_sleep(8);  // (a line that is asked for is slow to add to)
-        ask(k);
-        hi = peek(base_of(prm.high + ((int64_t)k.unit * kRows + wave * 32)), row8);
+        ask_again(k);
+        hi = peek(base_of(prm.high + ((int64_t)k.unit(prm) * kRows + wave * 32)), row8);
         lo = 0;
 #pragma unroll
         for (int i = 0; i < kCopies; ++i) lo += seen[i];
-        ready = __all((int)(lo >> kCountShift) + (int)(hi >> kCountShift) == k.nc);
+        ready = __all((int)(lo >> kCountShift) + (int)(hi >> kCountShift) == k.nc());
       } while (!ready && wall_clock64() - t0 < (uint64_t)prm.patience);
       // Not every workgroup is running, or a row's sum is out of range: the scores of this workgroup are void from here on.
       if (!ready) {
@@ -854,7 +934,7 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
     const uint32_t wt = lds0 + C::kOffW + wave * 128;
     *in_lds<float>(wt + row8 / 2) = w_row;
     const bool small = mostly_small(L);
-    if (k.ci == k.lead()) {  // the mass of this wave's rows, or a mark that it is not known yet
+    if (k.ci() == lead_of(k.bh, k.nc())) {  // the mass of this wave's rows, or a mark that it is not known yet
       const int ln = lane_now();
       float ms = wave_sum((ln & 1) ? 0.f : row_mass(L, w_row));
       if (small) ms = -1e30f;
@@ -883,33 +963,47 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
     if (__builtin_expect(small, 0)) {
       const float t = wave_sum((col[0] + col[1]) + (col[2] + col[3]));
       if (lane_now() == 0)
-        __hip_atomic_store(prm.parts + ((int64_t)k.unit * kWaves + wave) * prm.n_parts + k.ci, as_u32(t) & 0x7FFFFFFFu, __ATOMIC_RELAXED,
+        __hip_atomic_store(prm.parts + ((int64_t)k.unit(prm) * kWaves + wave) * prm.n_parts + k.ci(), as_u32(t) & 0x7FFFFFFFu, __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_AGENT);
     }
-    const uint32_t cs = lds0 + C::kOffCs + (par * kWaves + wave) * kKeys * 4 + lane16 / 4;
 #pragma unroll
     for (int j = 0; j < kNB; j += 2) {  // lanes below 32 get block j, the others block j+1
       const auto sw = __builtin_amdgcn_permlane32_swap(as_u32(col[j]), as_u32(col[j + 1]), false, false);
       const unsigned u0 = sw[0], u1 = sw[1];
-      *in_lds<float>(cs, j * 128) = as_f32(u0) + as_f32(u1);
+      sums[j / 2] += as_f32(u0) + as_f32(u1);
+    }
+    if (k.qg == prm.nqg - 1) {
+      const uint32_t cs = lds0 + C::kOffCs + (par * kWaves + wave) * kKeys * 4 + lane16 / 4;
+#pragma unroll
+      for (int j = 0; j < kNB / 2; ++j) {
+        *in_lds<float>(cs, j * 256) = sums[j];
+        sums[j] = 0.f;
+      }
     }
   };
 
-  // ---- prologue: the first two chunks' keys, the first chunk's rows and its first block of logits
-  settle();
-  Chunk cur = ahead, next = ahead, prev = ahead, done = ahead;
+  // ---- prologue: the first two chunks' keys, the first two steps' references and the first one's rows, then the third chunk's keys
+  const bool second = wave >= kWaves / 2;  // the group that runs half a step behind
+  int fresh = 0;  // number of the chunk of `ahead`
+  Task ahead{table->bh, 0, table->shape};
+  auto advance = [&]() {  // `ahead` to the walk's next task (which at the end of the walk may be of its last chunk again)
+    if (++ahead.qg < prm.nqg) return;
+    ahead.qg = 0;
+    const Table c = table + min(++fresh, chunks - 1);
+    ahead.bh = c->bh;
+    ahead.shape = c->shape;
+  };
+  Task cur = ahead, prev = ahead, done = ahead;
   dma_start(cur, 0);
   dma_k(0);
   aim_q(cur);
   uint32_t q_off = lane16;
 #pragma unroll
   for (int ks = 0; ks < S; ++ks) load_q(ks, q_off);
-  if (mine > 1) {
-    ahead.ci += G;
-    settle();
-    dma_k(1);
-  }
-  next = ahead;
+  advance();
+  Task next = ahead;
+  dma_start(next, 1);
+  dma_k(1);
   if (threadIdx.x < 32) *in_lds<float>(lds0 + C::kOffInf + threadIdx.x * 4) = -INFINITY;
   // (kOffBad and kOffLate; a workgroup that is placed when others have already given up goes straight to the fallback)
   if (threadIdx.x < 2)
@@ -918,122 +1012,126 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
   for (int i = threadIdx.x; i < 2 * kWaves * kKeys; i += kThreads) *in_lds<float>(lds0 + C::kOffCs + i * 4) = 0.f;
   if (threadIdx.x < 2 * kWaves) *in_lds<float>(lds0 + C::kOffMass + threadIdx.x * 4) = 0.f;
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+#pragma unroll
+  for (int ks = 0; ks < S; ++ks) asm volatile("" : "+v"(qf[ks]));
   if (__builtin_amdgcn_readfirstlane(*in_lds<const int>(lds0 + C::kOffBad))) return;
-  f32x16 pre, pa[kNB], pb[kNB];
-  auto first_block = [&](int par, const Chunk& k) {
-#pragma unroll
-    for (int i = 0; i < kAhead; ++i) fetch(par, i);
-    init(par, 0, k.P - k.ci * kKeys - r, pre);
-  };
-  first_block(0, cur);
-#pragma unroll
-  for (int n = 0; n < S; ++n) {
-    if (n + kAhead < S) fetch(0, n + kAhead);
-    mfma_step<bf16_t>(qf[n], kf[n % (kAhead + 1)], pre);
-  }
+  advance();
+  dma_k(2);
+  int keys_at = 3;  // number of the next chunk whose keys are asked for
+  f32x16 pa[kNB], pb[kNB];
 #pragma unroll
   for (int kb = 0; kb < kNB; ++kb) {
     pa[kb] = f32x16{};
     pb[kb] = f32x16{};
   }
   __builtin_amdgcn_sched_barrier(0);
-  auto meet = [&]() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
-
-  if (wave * 32 >= prm.rows) {  // no rows for this wave: it only helps to move keys and to add columns
-    for (int s = 0; s < mine; ++s) {
-      if (s + 2 < mine) {
-        ahead.ci += G;
-        settle();
-      }
-      dma_k((s + 2) % C::kRing);
-      asm volatile("s_waitcnt vmcnt(%0)" ::"i"(C::kMoves) : "memory");  // its part of chunk s+1
-      meet();
-      if (s >= 2) flush(done, s & 1 ^ 1, s);
-      done = prev;
-      prev = cur;
-      cur = next;
-      next = ahead;
-    }
-    meet();
-    if (mine >= 2) flush(done, mine & 1 ^ 1, mine);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    meet();
-    flush(prev, mine & 1, mine + 1);
-    return;
-  }
-
-  // Step s: chunk s is formed into pf (its first block of logits is in `pre`), chunk s-1, held in pc, is completed; the rows
-  // of chunk s+1 and the keys of chunk s+2 are asked for.  (At the end of the walk the last chunk is asked for again, so
-  // that the counts of outstanding accesses below hold in every step.)
-  auto step = [&](int s, int par, f32x16 (&pf)[kNB], f32x16 (&pc)[kNB]) {
-    dma_start(next, par ^ 1);
-    if (s + 2 < mine) {
-      ahead.ci += G;
-      settle();
-    }
-    dma_k((s + 2) % C::kRing);
-    aim_q(next);
-    const int left = cur.P - cur.ci * kKeys - r;  // keys of the chunk from this lane's on
-#pragma unroll
-    for (int i = 0; i < kAhead; ++i) fetch(par, S + i);
-    init(par, 1, left, pf[1]);
-#pragma unroll
-    for (int n = S; n < kNB * S; ++n) {
-      const int kb = n / S, ks = n % S;
-      if (n == kNB * S - 1) ask(prev);  // as late as an answer can be hidden: a sum that is asked for too early has to be asked for twice
-      if (n == (kNB - 1) * S) q_off = here(lane16);
-      if (n + kAhead < kNB * S) fetch(par, n + kAhead);
-      if (ks == S / 2 && kb + 1 < kNB) init(par, kb + 1, left, pf[kb + 1]);
-      mfma_step<bf16_t>(qf[ks], kf[n % (kAhead + 1)], pf[kb]);
-      expo(n - S - kLag, pre, pf);
-      if (kb == kNB - 1) load_q(ks, q_off);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    meet();
-    // Chunk s+1's keys were there a step ago (its rows' loads were waited for after them), its rows' references are there now:
-    // only this step's transfers of keys, the loads of ask() and those of the rows are younger.
-    asm volatile("s_waitcnt vmcnt(%0)" ::"i"(C::kMoves + kCopies + S) : "memory");
-    if (par) turn();
-#pragma unroll
-    for (int i = 0; i < kAhead; ++i) fetch(par ^ 1, i);
-    init(par ^ 1, 0, next.P - next.ci * kKeys - r, pre);
-    expo(kNB * S - S - kLag, pre, pf);
+  auto end_matrix = [&](int s) {
     __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int n = 0; n < S; ++n) {
-      if (n + kAhead < S) fetch(par ^ 1, n + kAhead);
-      mfma_step<bf16_t>(qf[n], kf[n % (kAhead + 1)], pre);
-      expo(kNB * S - S - kLag + 1 + n, pre, pf);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-#pragma unroll
-    for (int m = kNB * S - kLag + 1; m <= kNB * S; ++m) expo(m, pre, pf);
-    // The row sums asked for are waited for before this step's additions go out: accesses are counted in order.
-#pragma unroll
-    for (int i = 0; i < kCopies; ++i) asm volatile("" : "+v"(seen[i]));
-    if (s >= 2) flush(done, par ^ 1, s);
-    publish(cur);
-    if (s > 0) complete(prev, par, pc);
+    if (s == 0 && mine > 16)  // (what was asked for so far, at once: 32k keys 113 us, 116 without; short walks lose by it)
+      asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+    else
+      asm volatile("s_barrier" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto end_vector = [&]() {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto shift = [&]() {
     done = prev;
     prev = cur;
     cur = next;
     next = ahead;
+    advance();
+  };
+  if (second) asm volatile("s_barrier" ::: "memory");
+
+  if (wave * 32 >= prm.rows) {  // no rows for this wave: it only helps to move keys and to add columns
+    for (int s = 0; s < mine; ++s) {
+      end_matrix(s);
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      if (cur.qg == 0 && keys_at < chunks) dma_k(keys_at++);
+      if (!second) flush(done, s & 1 ^ 1, s >= 2);
+      shift();
+      end_vector();
+    }
+    end_vector();
+    if (!second) flush(done, mine & 1 ^ 1, mine >= 2);
+    if (!second) {
+      end_vector();
+      flush(prev, mine & 1, true);
+    }
+    return;
+  }
+
+  // Step s, matrix phase: chunk s is formed into pf; the rows of step s+1 are asked for as soon as their registers are free, then
+  // the row sums of step s-1 (as late as an answer can be hidden: a sum that is asked for too early has to be asked for twice).
+  auto matrix = [&](int par, f32x16 (&pf)[kNB]) {
+    const int left = cur.keys() - r;  // keys of the chunk from this lane's on
+    aim_q(next);
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) fetch(i);
+    init(par, 0, left, pf[0]);
+#pragma unroll
+    for (int n = 0; n < kNB * S; ++n) {
+      const int kb = n / S, ks = n % S;
+      if (n == (kNB - 1) * S) q_off = here(lane16);
+      if (n + kAhead < kNB * S) fetch(n + kAhead);
+      if (ks == S / 2 && kb + 1 < kNB) init(par, kb + 1, left, pf[kb + 1]);
+      mfma_step<bf16_t>(qf[ks], kf[n % (kAhead + 1)], pf[kb]);
+      expo(n - S - kLag, pf);
+      if (kb == kNB - 1) load_q(ks, q_off);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    ask(prev);
+    if (cur.qg == prm.nqg - 1) turn();
+#pragma unroll
+    for (int m = kNB * S - S - kLag; m <= kNB * S; ++m) expo(m, pf);
+  };
+  // Vector phase: the row sums published; step s-1, held in pc, is completed; the keys of the chunk after the next two and the
+  // references of step s+2 are asked for.
+  auto vector = [&](int s, int par, f32x16 (&pc)[kNB]) {
+    publish(cur);
+    if (!second) flush(done, par ^ 1, s >= 2);
+    // All but the addition and the store just issued: the rows, the row sums, and the transfers of the step before.
+    if (second)
+      asm volatile("s_waitcnt vmcnt(1)" ::: "memory");
+    else
+      asm volatile("s_waitcnt vmcnt(2)" ::: "memory");
+#pragma unroll
+    for (int i = 0; i < kCopies; ++i) asm volatile("" : "+v"(seen[i]));
+#pragma unroll
+    for (int ks = 0; ks < S; ++ks) asm volatile("" : "+v"(qf[ks]));
+    dma_start(ahead, par);
+    if (s > 0) complete(prev, par, pc);
+    if (cur.qg == 0 && keys_at < chunks) dma_k(keys_at++);
+    shift();
+  };
+  auto step = [&](int s, int par, f32x16 (&pf)[kNB], f32x16 (&pc)[kNB]) {
+    matrix(par, pf);
+    end_matrix(s);
+    vector(s, par, pc);
+    end_vector();
   };
   for (int s = 0; s < mine; s += 2) {
     step(s, 0, pa, pb);
     if (s + 1 < mine) step(s + 1, 1, pb, pa);
   }
-  // ---- the last chunk
+  // ---- the last step: completed at once, by the first group while the second publishes it
   const int par = mine & 1;
-  meet();
-  if (mine >= 2) flush(done, par ^ 1, mine);
-  ask(prev);
+  ask_again(prev);
   if (par)
     complete(prev, par, pa);
   else
     complete(prev, par, pb);
-  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");  // (also this workgroup's last transfers into LDS)
-  flush(prev, par, mine + 1);
+  end_vector();
+  if (!second) flush(done, par ^ 1, mine >= 2);
+  if (!second) {
+    end_vector();
+    flush(prev, par, true);
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (no transfer into LDS outlives its workgroup)
 }
 
 // The kernel's argument, from a pointer hidden from the optimiser: what follows the walk then loads what it needs when it needs it,
@@ -1079,12 +1177,14 @@ int cus() {
 size_t pad256(size_t n) { return (n + 255) / 256 * 256; }
 
 struct Layout {
-  size_t control, low, high, start, mass, done, late, parts, qpack, stats, bytes;  // offsets from the start of the area
+  size_t control, table, counts, low, high, start, mass, done, late, parts, qpack, stats, bytes;  // offsets from the start of the area
   int n_parts;
-  Layout(const maskkv_desc* d, int nqg) {
+  Layout(const maskkv_desc* d, int nqg, const SweepPlan& plan) {
     const size_t units = (size_t)d->B * d->H * nqg;
     control = 0;
-    low = pad256(sizeof(Control));
+    table = pad256(sizeof(Control));
+    counts = table + (size_t)plan.groups * plan.rounds * sizeof(Chunk);
+    low = pad256(counts + plan.groups * sizeof(int));
     high = low + units * kCopies * kRows * sizeof(uint64_t);
     start = high + units * kRows * sizeof(uint64_t);
     mass = start + units * kRows * 2 * sizeof(float);
@@ -1098,49 +1198,87 @@ struct Layout {
   }
 };
 
-// How a description would be swept: by how many workgroups, and whether that is faster than the two passes.
+// How a description would be swept, and whether that is faster than the two passes.
 //
-// At most one workgroup per compute unit, since all have to be resident.  Units whose chunks do not divide the workgroups evenly
-// straddle two steps, and the first of them then waits for the second: measured at 32 heads of dimension 128, a step of 256
-// workgroups takes 3.3 us where units are whole, and where they are not 4.0 us at 120 chunks per unit, 5.9 us at 160, 7.5 us at 235.
-// So the candidates are all compute units, or as many as hold whole units of some sequence, and the cheapest is taken.
-struct Plan {
-  int groups;
-  bool faster;
-  Plan(const maskkv_desc* d, const Lens& lens, int nqg) : groups(0), faster(false) {
-    const int n = cus();
-    int nc[MASKKV_MAX_BATCH], most = 0;
-    int64_t chunks = 0;
+// At most one workgroup per compute unit, since all have to be resident.  The workgroups of a head (one a chunk) wait for each
+// other, so they work on it at the same time: a round puts as many heads side by side as there are workgroups for, the longest
+// first, and is repeated for the next heads of the same sequences as long as these last.  (Dealt out end to end, heads straddle
+// two rounds, and the first workgroups of such a head wait for the last: 503 instead of 481 us for the ragged batch, whose 18112
+// chunks take 75 rounds of 256 workgroups instead of 71.)  Many sequences can make more runs than the plan has room for; each
+// sequence then has rounds of its own.
+//
+// A head's groups of voting rows are one workgroup's turn, which needs its keys once, unless that leaves workgroups without work: a
+// head then counts as several with the same keys, and their column sums are added by a kernel of their own (5 us).
+struct Packing {
+  SweepPlan plan;
+  Packing(const maskkv_desc* d, const int* nc, int n, int subsets, int nqg, bool mixed) : plan{} {
+    int left[MASKKV_MAX_BATCH], order[MASKKV_MAX_BATCH], B = 0;
     for (int b = 0; b < d->B; ++b) {
-      nc[b] = (lens.P[b] + kKeys - 1) / kKeys;
-      most = max(most, nc[b]);
-      chunks += (int64_t)nc[b] * d->H * nqg;
+      left[b] = nc[b] > 0 ? d->H * subsets : 0;
+      if (left[b] == 0) continue;
+      int i = B++;
+      for (; i > 0 && nc[order[i - 1]] < nc[b]; --i) order[i] = order[i - 1];
+      order[i] = b;
     }
-    if (most == 0 || most > n || n > kMaxGroups || chunks > 0x7FFFFFFF) return;
-    double best = 0.0;
-    for (int i = -1; i < d->B; ++i) {
-      const int g = i < 0 ? n : nc[i] > 0 ? n / nc[i] * nc[i] : 0;
-      if (g < most) continue;
-      double steps = 0.0;
-      for (int b = 0; b < d->B; ++b) {
-        const double share = (double)nc[b] / g;
-        steps += share * (nc[b] > 0 && g % nc[b] != 0 ? 1.0 + fmin(1.3, 3.0 * share * share) : 1.0);
+    plan.subsets = subsets;
+    for (int first = 0; first < B;) {
+      if (left[order[first]] == 0) {
+        ++first;
+        continue;
       }
-      steps *= (double)d->H * nqg;
-      if (groups == 0 || steps < best) {
-        best = steps;
-        groups = g;
+      int room = n, times = 0x7FFFFFFF;
+      const int run = plan.runs;
+      for (int i = first; i < B && room > 0; ++i) {
+        const int b = order[i], side = min(left[b], room / nc[b]);
+        if (side == 0) continue;
+        if (plan.runs == kMaxRuns) {
+          plan.groups = 0;
+          return;
+        }
+        plan.put(plan.runs++, n - room, side, side * nc[b], b, d->H * subsets - left[b]);
+        room -= side * nc[b];
+        times = min(times, left[b] / side);
+        if (!mixed) break;
       }
+      for (int i = run; i < plan.runs; ++i) {
+        plan.repeat(i, times);
+        left[plan.sequence(i)] -= plan.side(i) * times;
+      }
+      plan.rounds += times;
+      plan.groups = max(plan.groups, n - room);
     }
-    groups = (int)min((int64_t)groups, chunks);
-    // Microseconds.  A step: 2.72 (head_dim 64: 2.45), and more where more than 150 workgroups add to one row's sum; the two
-    // passes: 0.017 (0.010) per chunk; what either costs besides.  (32 heads, head_dim 128: 122 against 163 at 32k tokens, 75 / 85
-    // at 15k, 39 / 59 at 8k, but 103 / 95 at 17k; head_dim 64: 32 / 42 at 8k, 51 / 61 at 16k, but 57 / 53 at 12.5k, 140 / 105 at 32k.)
-    const bool wide = d->d == 128;
-    const double step = (wide ? 2.72 : 2.45) + max(0, most - 150) * (wide ? 0.007 : 0.0157);
-    faster = 14.0 + best * step < 23.0 + (double)chunks * (wide ? 0.0169 : 0.0101);
   }
 };
+
+SweepPlan make_plan(const maskkv_desc* d, const Lens& lens, int nqg) {
+  const int n = min(cus(), kMaxGroups);
+  SweepPlan best{};
+  int nc[MASKKV_MAX_BATCH], most = 0;
+  int64_t chunks = 0;
+  for (int b = 0; b < d->B; ++b) {
+    nc[b] = (lens.P[b] + kKeys - 1) / kKeys;
+    most = max(most, nc[b]);
+    chunks += (int64_t)nc[b] * d->H;
+  }
+  if (most == 0 || most > n) return best;
+  // Microseconds.  A step: 2.72 (head_dim 64: 2.45), and more where more than 150 workgroups add to one row's sum; the two
+  // passes: 0.017 (0.010) per chunk; what either costs besides.  (32 heads, head_dim 128: 122 against 163 at 32k tokens, 75 / 85
+  // at 15k, 39 / 59 at 8k, but 103 / 95 at 17k; head_dim 64: 32 / 42 at 8k, 51 / 61 at 16k, but 57 / 53 at 12.5k, 140 / 105 at 32k.)
+  const bool wide = d->d == 128;
+  const double step = (wide ? 2.72 : 2.45) + max(0, most - 150) * (wide ? 0.007 : 0.0157);
+  double cost = 23.0 + (double)chunks * nqg * (wide ? 0.0169 : 0.0101);
+  for (int subsets = 1; subsets <= nqg; ++subsets) {
+    if (nqg % subsets) continue;
+    Packing p(d, nc, n, subsets, nqg, true);
+    if (!p.plan.groups) p = Packing(d, nc, n, subsets, nqg, false);
+    const double c = 14.0 + p.plan.rounds * (nqg / subsets) * step + (subsets > 1 ? 5.0 : 0.0);
+    if (c < cost) {
+      cost = c;
+      best = p.plan;
+    }
+  }
+  return best;
+}
 
 template <int D>
 int launch(const maskkv_desc* d, const SweepParams& prm, hipStream_t stream) {
@@ -1162,13 +1300,13 @@ int launch(const maskkv_desc* d, const SweepParams& prm, hipStream_t stream) {
     }
     raised = true;
   }
-  const int units = prm.B * prm.H * prm.nqg;
+  const int units = prm.B * prm.H * prm.subsets * prm.nqg;
   if (units >= 128)
     hipLaunchKernelGGL((sweep_start_kernel<D, 8>), dim3(units), dim3(kThreads), lds_start, stream, prm);
   else
     hipLaunchKernelGGL((sweep_start_kernel<D, 2>), dim3(units * 4 + 1), dim3(kThreads), lds_start, stream, prm);
   if (int e = check_launch("score (sweep start)")) return e;
-  hipLaunchKernelGGL(sweep_kernel<D>, dim3(prm.groups), dim3(kThreads), Cfg<D>::kLds, stream, prm);
+  hipLaunchKernelGGL(sweep_kernel<D>, dim3(prm.plan.groups), dim3(kThreads), Cfg<D>::kLds, stream, prm);
   return check_launch("score (sweep)");
 }
 
@@ -1176,10 +1314,9 @@ int launch(const maskkv_desc* d, const SweepParams& prm, hipStream_t stream) {
 
 // A launch of 66000 units (33000 heads of 40 keys, 300 voting rows), once tried, ended in a memory fault whose cause was not found.
 // The sweep is kept to the sizes that are in use (64 sequences x 32 heads x 2 groups of voting rows); more take the two passes.
-int sweep_groups(const maskkv_desc* d, const Lens& lens, int nqg) {
-  if (d->dtype != MASKKV_BF16 || (int64_t)d->B * d->H * nqg > kMaxUnits) return 0;
-  const Plan plan(d, lens, nqg);
-  return plan.faster ? plan.groups : 0;
+SweepPlan sweep_plan(const maskkv_desc* d, const Lens& lens, int nqg) {
+  if (d->dtype != MASKKV_BF16 || (int64_t)d->B * d->H * nqg > kMaxUnits) return SweepPlan{};
+  return make_plan(d, lens, nqg);
 }
 
 int hold_sweep(int64_t age_us, hipStream_t stream) {
@@ -1187,10 +1324,10 @@ int hold_sweep(int64_t age_us, hipStream_t stream) {
   return check_launch("hold sweep");
 }
 
-size_t sweep_workspace_bytes(const maskkv_desc* d, int nqg) { return Layout(d, nqg).bytes; }
+size_t sweep_workspace_bytes(const maskkv_desc* d, int nqg, const SweepPlan& plan) { return Layout(d, nqg, plan).bytes; }
 
 int launch_sweep(const maskkv_desc* d, const View& Q, const View& K, const Lens& lens, float scale, float* scores,
-                 int64_t score_stride, float* prompt_mass, float* group_sums, int64_t group_stride, int nqg, int groups,
+                 int64_t score_stride, float* prompt_mass, float* group_sums, int64_t group_stride, int nqg, const SweepPlan& plan,
                  void* area, hipStream_t stream, const float** unit_mass) {
   SweepParams prm;
   prm.Q = Q;
@@ -1202,22 +1339,26 @@ int launch_sweep(const maskkv_desc* d, const View& Q, const View& K, const Lens&
   prm.q_per_kv = query_heads_per_kv(d);
   prm.n_qh = d->n_query;
   prm.n_query = d->n_query * prm.q_per_kv;
-  prm.nqg = nqg;
+  prm.subsets = plan.subsets;
+  prm.nqg = nqg / plan.subsets;
   prm.rows = ((prm.n_query + nqg - 1) / nqg + 31) / 32 * 32;  // (as even as they can be: 300 rows are 160 and 140)
-  int x = 0;
-  for (int b = 0; b < d->B; ++b) x += (lens.P[b] + kKeys - 1) / kKeys * d->H * nqg;
-  prm.chunks = x;
-  prm.groups = groups;
+  prm.plan = plan;
+  int64_t x = 0;  // steps of all workgroups
+  for (int b = 0; b < d->B; ++b) x += (int64_t)((lens.P[b] + kKeys - 1) / kKeys) * d->H * nqg;
   // 100 us and about what the sweep takes, in which the fallback would be done, too.  (What keeps workgroups from being placed is
   // another program's kernels, a sweep of another process among them, whose lock is its own, or of another stream: the time
   // these take has nothing to do with this call's.  Two processes that score 32k keys at once, us a call of each: 455, with 20 ms 5000.)
-  prm.patience = 10000 + (int)min((int64_t)x / prm.groups * 500, (int64_t)1000000);
+  prm.patience = 10000 + (int)min(x / plan.groups * 500, (int64_t)1000000);
   // Two tasks a pass for every compute unit: a task costs about as much as two chunks before its first one.
   prm.spans = max(1, min(kSpans, 2 * kMaxGroups / (d->B * d->H * nqg)));
+  prm.spans2 = max(1, min(kMaxGroups, 2 * kMaxGroups / (d->B * d->H * plan.subsets)));
   prm.c = scale * kLog2e;
-  const Layout l(d, nqg);
+  const Layout l(d, nqg, plan);
   char* base = reinterpret_cast<char*>(area);
   prm.ctl = reinterpret_cast<Control*>(base + l.control);
+  prm.table = reinterpret_cast<Chunk*>(base + l.table);
+  prm.counts = reinterpret_cast<int*>(base + l.counts);
+  prm.rounds = plan.rounds;
   prm.spans_done = reinterpret_cast<int*>(base + l.done);
   prm.parts = reinterpret_cast<uint32_t*>(base + l.parts);
   prm.n_parts = l.n_parts;
@@ -1227,10 +1368,10 @@ int launch_sweep(const maskkv_desc* d, const View& Q, const View& K, const Lens&
   prm.high = reinterpret_cast<uint64_t*>(base + l.high);
   prm.start = reinterpret_cast<float*>(base + l.start);
   prm.qpack = base + l.qpack;
-  prm.out = nqg == 1 ? scores : group_sums;
-  prm.out_stride = nqg == 1 ? score_stride : group_stride;
-  prm.mass = nqg == 1 ? prompt_mass : reinterpret_cast<float*>(base + l.mass);
-  *unit_mass = nqg == 1 ? nullptr : prm.mass;
+  prm.out = plan.subsets == 1 ? scores : group_sums;
+  prm.out_stride = plan.subsets == 1 ? score_stride : group_stride;
+  prm.mass = plan.subsets == 1 ? prompt_mass : reinterpret_cast<float*>(base + l.mass);
+  *unit_mass = plan.subsets == 1 ? nullptr : prm.mass;
   return d->d == 128 ? launch<128>(d, prm, stream) : launch<64>(d, prm, stream);
 }
 

@@ -89,6 +89,40 @@ def test_calls_on_two_streams_at_once():
     assert torch.equal(after[0][:, :batches[0].P[0]], want[0][0][:, :batches[0].P[0]])
 
 
+@pytest.mark.parametrize("d,n,H,g,Ps,fallback", [
+    (128, 40, 2, 1, tuple(range(100, 6100, 250)), False),                   # 24 lengths: rounds of several sequences
+    (64, 33, 1, 1, tuple((i * 37) % 64 * 33 for i in range(64)), False),    # 64 sequences, one of them empty
+    (128, 32, 11, 1, tuple(range(128, 8193, 128)), False),                  # more runs than a plan has room for
+    (128, 100, 2, 7, (3000,), False), (128, 100, 2, 7, (3000,), True),      # three groups of rows: a workgroup each
+    (128, 256, 3, 4, (5000, 300, 9000), False), (128, 256, 3, 4, (5000, 300, 9000), True),  # four: one workgroup for all or two
+    (64, 512, 32, 1, (4100, 2049), False), (64, 512, 32, 1, (4100, 2049), True)])
+def test_rounds_of_heads_and_groups_of_rows(d, n, H, g, Ps, fallback):
+    """Heads against float64 (fp32 sums of products of bf16 inputs: logits of up to 2^5 binary orders)."""
+    from paper_2510_09309_amd import bench_binding as bb
+    m = hp.mk()
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    B, P_max = len(Ps), max(Ps)
+    Q = (torch.randn((B, H * g, n, d), generator=gen, device="cuda") * 1.5).bfloat16()
+    K = torch.randn((B, H, P_max + n, d), generator=gen, device="cuda").bfloat16()
+    desc = m.Desc(B=B, H=H, d=d, dtype=m.MASKKV_BF16, n_resp=n, P_max=P_max, prompt_len=None if B == 1 else list(Ps), q_per_kv=0 if g == 1 else g)
+    scores, mass = torch.full((B * H, P_max), float("nan"), device="cuda"), torch.full((B * H,), float("nan"), device="cuda")
+    ws = hp.workspace(m.maskkv_score_workspace_bytes(desc))
+    if fallback:
+        bb.maskkv_bench_hold_sweep(0)
+    m.maskkv_score(desc, Q, K, 0.0, scores, P_max, mass, ws)
+    if fallback:
+        bb.maskkv_bench_hold_sweep(-1)
+    assert int(ws[:4].view(torch.int32)[0]) == (0 if fallback else 1)
+    for b, P in enumerate(Ps):
+        for h in range(b % 5, H, 5) if B * H > 200 else range(H):
+            q = Q[b, h * g:(h + 1) * g].reshape(g * n, d).double()
+            A = torch.softmax(q @ K[b, h, :P + n].double().T / d ** 0.5, dim=1)
+            want = A[:, :P].sum(0)
+            assert torch.allclose(scores[b * H + h, :P].double(), want, rtol=32 * 2.0 ** -24, atol=0), (b, h)
+            assert torch.isnan(scores[b * H + h, P:]).all()
+            assert abs(float(mass[b * H + h]) - float(want.sum())) <= 32 * 2.0 ** -24 * float(want.sum()), (b, h)
+
+
 def swept(batch, ws):
     """One call, and whether it had the device's sweep (the first word of the workspace)."""
     m = hp.mk()
