@@ -24,11 +24,12 @@
 // row's sum leaves the range of the integers, a two-pass fallback at the end of the same kernel does the work.
 //
 // What bounds it: a step of 6700 to 7100 cycles, 2048 of them MFMAs.  A wave issues an instruction every 4 to 5 cycles, a matrix phase
-// has 1800 cycles of them, a vector phase 1500 to 2000, and the two waves of a SIMD share the vector pipe, where v_exp_f32
+// has 1800 cycles of them, a vector phase 1300 to 1800, and the two waves of a SIMD share the vector pipe, where v_exp_f32
 // takes 8 cycles and an MFMA about as many.  In a loop of such calls the board is at its 1400 W and the clock 10 % below that of
 // short calls (2.1 against 2.3 GHz).  us a call, with both groups of waves in the same phase, chunks dealt out end to end and keys
 // transferred for every group of rows before: 32 heads x 128 with 256 rows, 4k keys 28.7 -> 28.2, 8k 39 -> 37.9, 32k 120 -> 115; 4
-// heads with 1792 rows over 30k keys 93.5 -> 87.6; the ragged batch of perf/cases.py 518 -> 481.  (Without transfers of keys, with
+// heads with 1792 rows over 30k keys 93.5 -> 87.8; the ragged batch of perf/cases.py 518 -> 473 (481 with 64-bit
+// addresses formed for every access).  (Without transfers of keys, with
 // wrong results, the ragged batch took 420 instead of 505, without loads of rows 455, without the exchange 465.)  Slower: raised
 // wave priority in the vector phase or for waves 4-7; a first sum per XCD that the last of its workgroups adds to the whole
 // (two latencies instead of one); 2 or 8 copies of the sums.
@@ -76,6 +77,15 @@ constexpr uint32_t kNoPart = 0xFFFFFFFFu;  // not there (a part has its sign bit
 constexpr int kMaxUnits = 4096;            // of a launch, see sweep_groups
 constexpr int kMaxGroups = 256;            // workgroups of a sweep, and chunks of a unit, at most (one per compute unit)
 
+// What a unit has in the workspace, one behind the other, so that a base and 32 bits address all of it:
+//   row sums  [kCopies][256] `low`, [256] `high` (64 bits each)
+//   [8 waves][2][32] floats: the rows' references, minus the response span's log-sum-exp in units of the raw logits; and the sums
+//   of the response span in units of these references, 1 but for their rounding
+//   [8 waves] 32 rows in MFMA fragment order
+constexpr uint32_t kHighAt = kCopies * kRows * 8, kRefsAt = kHighAt + kRows * 8, kRowsAt = kRefsAt + kWaves * 256;
+template <int D>
+constexpr uint32_t kUnitBytes = kRowsAt + kRows * D * 2;
+
 struct Control {
   int run;      // this call's workgroups may be placed as a sweep's
   int redo;     // the sweep could not do the work: the fallback at the end of the kernel does
@@ -89,6 +99,8 @@ struct __attribute__((aligned(16))) Chunk {
   int bh;
   uint32_t shape;     // its number, 8 bits; the head's number of chunks less one, 8 bits; its number of keys
   const char* keys;
+  float* out;         // its scores
+  int64_t pad;
 };
 
 struct SweepParams {
@@ -108,11 +120,7 @@ struct SweepParams {
   int spans;        // pieces of a unit's keys in the fallback's first pass
   int spans2;       // pieces of a head's keys in its second pass
   float c;          // scale * log2(e)
-  uint64_t* low;    // [units][kCopies][256]
-  uint64_t* high;   // [units][256]
-  float* start;     // [units][8 waves][2][32]: the rows' references, minus the response span's log-sum-exp in units of the raw
-                    // logits; and the sums of the response span in units of these references, 1 but for their rounding
-  char* qpack;      // [units][8 waves] 32 rows in MFMA fragment order
+  char* units;      // [units][unit_bytes], see kHighAt
   Control* ctl;
   int* spans_done;  // [units] spans of the unit whose statistics are there (fallback)
   uint32_t* parts;  // [units][8 waves][n_parts] bits of a chunk's part of the mass of 32 rows, or kNoPart
@@ -277,6 +285,7 @@ __device__ __forceinline__ void start_table(const SweepParams& prm, int b, int v
     c.bh = b * prm.heads() + vh;
     c.shape = (uint32_t)ci | (uint32_t)(nc - 1) << 8 | (uint32_t)min(P - ci * kKeys, kKeys) << 16;
     c.keys = prm.K.row(b, vh / prm.subsets, (int64_t)ci * kKeys);
+    c.out = prm.out + (int64_t)c.bh * prm.out_stride + ci * kKeys;
     prm.table[(int64_t)(w0 + ci) * prm.rounds + t] = c;
   }
 }
@@ -327,15 +336,15 @@ __global__ __launch_bounds__(kThreads) void sweep_start_kernel(const SweepParams
     if (P == 0 && prm.mass) prm.mass[bh] = 0.f;
   }
   if (blockIdx.x % SPLIT == SPLIT - 1 && wave == kWaves - 1 && unit == bh * prm.nqg) start_table(prm, b, vh);
-  const int64_t row0 = (int64_t)unit * kRows + rb * 32;
+  char* area = prm.units + (int64_t)unit * kUnitBytes<D>;
+  uint64_t* sums = reinterpret_cast<uint64_t*>(area) + rb * 32;
   if (part_of == 0) {
     if (lane < 32) {
 #pragma unroll
-      for (int i = 1; i < kCopies; ++i) prm.low[((int64_t)unit * kCopies + i) * kRows + rb * 32 + lane] = 0;
-      prm.high[row0 + lane] = 0;
+      for (int i = 1; i <= kCopies; ++i) sums[i * kRows + lane] = 0;  // (the last one is `high`)
     }
     for (int i = lane; i < ceil_div(P, kKeys); i += 64) prm.parts[((int64_t)unit * kWaves + rb) * prm.n_parts + i] = kNoPart;
-    u32x4* pack = reinterpret_cast<u32x4*>(prm.qpack + row0 * C::kRowB) + lane;
+    u32x4* pack = reinterpret_cast<u32x4*>(area + kRowsAt + rb * C::kQBytes) + lane;
 #pragma unroll
     for (int s = 0; s < S; ++s) pack[s * 64] = qf[s];
   }
@@ -397,9 +406,10 @@ __global__ __launch_bounds__(kThreads) void sweep_start_kernel(const SweepParams
     const bool live = rb * 32 < prm.rows && q0 + lane < prm.n_query;
     const float ref = -(sum + (lost + (near1 - 1.f) * kLog2e)) / prm.c;
     const float own = live ? near1 * fast_exp2(fmaf(ref, prm.c, sum) + lost) : kNoRow;
-    prm.start[row0 * 2 + lane] = live ? ref : -INFINITY;
-    prm.start[row0 * 2 + 32 + lane] = own;
-    prm.low[(int64_t)unit * kCopies * kRows + rb * 32 + lane] = (uint64_t)rintf(own * kLowScale);
+    float* refs = reinterpret_cast<float*>(area + kRefsAt) + rb * 64 + lane;
+    refs[0] = live ? ref : -INFINITY;
+    refs[32] = own;
+    sums[lane] = (uint64_t)rintf(own * kLowScale);
   }
   if (BLOCKS == 8 && blockIdx.x == 0) start_lock(prm);
 }
@@ -439,10 +449,10 @@ __device__ __forceinline__ void sweep_redo(const SweepParams& prm, uint32_t lds0
     const int c0 = nc * span / pieces, c1 = nc * (span + 1) / pieces;
     float head_mass = 0.f;
     for (int unit = first; unit < first + (second ? prm.nqg : 1); ++unit) {
-      const int64_t row0 = (int64_t)unit * kRows + wave * 32;
+      const char* area = prm.units + (int64_t)unit * kUnitBytes<D>;
       u32x4 qf[S];
 #pragma unroll
-      for (int s = 0; s < S; ++s) qf[s] = *reinterpret_cast<const u32x4*>(prm.qpack + row0 * C::kRowB + s * 1024 + lane * 16);
+      for (int s = 0; s < S; ++s) qf[s] = *reinterpret_cast<const u32x4*>(area + kRowsAt + wave * C::kQBytes + s * 1024 + lane * 16);
       float2* st = prm.stats + (int64_t)unit * kSpans * kRows + wave * 32 + r;  // (of query row r; one span is kRows further)
       float m = kNegBig, l = 0.f;
       float nl[16];  // second pass: minus the base-2 log-sum-exp of this lane's rows
@@ -455,8 +465,9 @@ __device__ __forceinline__ void sweep_redo(const SweepParams& prm, uint32_t lds0
         asm volatile("" ::: "memory");
         __syncthreads();
         // all spans and the response span
-        const float ref = -prm.start[row0 * 2 + r] * prm.c;  // +inf for a row that does not exist
-        const float own = prm.start[row0 * 2 + 32 + r];
+        const float* refs = reinterpret_cast<const float*>(area + kRefsAt) + wave * 64 + r;
+        const float ref = -refs[0] * prm.c;  // +inf for a row that does not exist
+        const float own = refs[32];
         const bool live = ref != INFINITY;
         float M = live ? ref : 0.f, Lp = 0.f;
         float2 v[kSpans];
@@ -600,6 +611,7 @@ __device__ __forceinline__ void sweep_redo(const SweepParams& prm, uint32_t lds0
 struct Task {
   int bh, qg;
   uint32_t shape;
+  uint32_t at;  // its unit's place in SweepParams::units
   __device__ int ci() const { return shape & 255; }
   __device__ int nc() const { return (shape >> 8 & 255) + 1; }
   __device__ int keys() const { return shape >> 16; }
@@ -633,12 +645,12 @@ __device__ __forceinline__ void late_masses(const SweepParams& prm, uint32_t lds
         if (j * 64 + lane < nc) u[j] = __hip_atomic_load(part + j * 64 + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
       if (__all(__hip_atomic_load(part + lead, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == kNoPart)) {  // not one of those waves
-        const int64_t row = (int64_t)unit * kRows + wave * 32 + lane / 2;
+        const uint64_t* low = reinterpret_cast<const uint64_t*>(prm.units + (int64_t)unit * kUnitBytes<D>) + wave * 32 + lane / 2;
         uint64_t lo = 0;
 #pragma unroll
         for (int j = 0; j < kCopies; ++j)
-          lo += __hip_atomic_load(prm.low + (int64_t)unit * (kCopies - 1) * kRows + row + j * kRows, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const uint64_t hi = __hip_atomic_load(prm.high + row, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          lo += __hip_atomic_load(low + j * kRows, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const uint64_t hi = __hip_atomic_load(low + kCopies * kRows, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         const float L = fmaf(whole(hi), 1.f / kHighScale, whole(lo) * (1.f / kLowScale));
         sum = lane % 2 ? 0.f : row_mass(L, reciprocal(L));
         break;
@@ -700,40 +712,34 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
   // Row wave * 16 + j * kRPI + rl of the chunk (rl: this lane's row of transfer j) has its pieces permuted by the low bits of
   // that number, which are j's and rl's side by side: one exclusive-or with a constant per transfer.
   const uint32_t krow = (uint32_t)lane / C::kPPR, kpiece = ((uint32_t)lane % C::kPPR ^ C::swz(krow)) << 4;
-  const uint32_t koff = krow * kstride;
-  // Chunk number t into its slot of the ring: this wave's part.  (Rows past the last key re-read it; a wave all of whose rows are
-  // past it reads the chunk's first.)
+  const uint32_t koff = (wave * (kKeys / kWaves) + krow) * kstride;  // (a chunk's rows are up to 127 x 16 MiB apart)
+  // Chunk number t into its slot of the ring: this wave's part.  (Rows past the last key re-read it.)
   auto dma_k = [&](int t) {
     const Table c = table + min(t, chunks - 1);
-    const int last = (int)(c->shape >> 16) - 1 - wave * (kKeys / kWaves);  // row of the last key, counted from this wave's first
-    const char* base = c->keys + (uint64_t)(last < 0 ? 0 : wave * (kKeys / kWaves)) * kstride;
-    const uint32_t most = (uint32_t)max(last, 0) * kstride;
+    const uint32_t most = ((c->shape >> 16) - 1) * kstride;
     const uint32_t to = lds0 + t % C::kRing * C::kKBytes + wave * (kKeys / kWaves) * C::kRowB;
 #pragma unroll
     for (int j = 0; j < C::kMoves; ++j)
-      dma16(base, min(here(koff) + (uint32_t)(j * C::kRPI) * kstride, most) + (here(kpiece) ^ (C::swz(j * C::kRPI) << 4)), to + j * 1024);
+      dma16(c->keys, min(here(koff) + (uint32_t)(j * C::kRPI) * kstride, most) + (here(kpiece) ^ (C::swz(j * C::kRPI) << 4)), to + j * 1024);
   };
+  const Base units = base_of(prm.units);
   auto dma_start = [&](const Task& k, int par) {
-    dma4(reinterpret_cast<const char*>(prm.start + ((int64_t)k.unit(prm) * kRows + wave * 32) * 2), here(lane16) >> 2,
-         lds0 + C::kOffStart + (par * kWaves + wave) * 256);
+    dma4((const char*)units, (here(lane16) >> 2) + (k.at + kRefsAt + wave * 256), lds0 + C::kOffStart + (par * kWaves + wave) * 256);
   };
   u32x4 qf[S];
-  Base qlo, qhi;  // (two: an immediate offset reaches 4 KiB)
-  auto aim_q = [&](const Task& k) {
-    const char* q = prm.qpack + ((int64_t)k.unit(prm) * kWaves + wave) * C::kQBytes;
-    qlo = base_of(q);
-    qhi = base_of(q + 4096);
-  };
   // (The loads of the walk are asm, and waited for by asm: the compiler does not see the transfers and would wait for all of them.)
-  auto load_q = [&](int ks, uint32_t off) {
-    asm volatile("global_load_dwordx4 %0, %1, %2 offset:%3" : "=v"(qf[ks]) : "v"(off), "s"(ks < 4 ? qlo : qhi), "i"(ks % 4 * 1024));
+  uint32_t q_at = 0;
+  auto aim_q = [&](const Task& k) { q_at = here(lane16) + (k.at + kRowsAt + wave * C::kQBytes); };
+  auto load_q = [&](int ks) {
+    if (ks == 4) q_at += 4096;  // (what an immediate offset reaches)
+    asm volatile("global_load_dwordx4 %0, %1, %2 offset:%3" : "=v"(qf[ks]) : "v"(q_at), "s"(units), "i"(ks % 4 * 1024));
   };
 
   // the row (of this wave's 32) whose sum the butterfly below leaves in a lane; lanes 2n and 2n+1 hold the same one
   auto row_of = [](int ln) {
     return 8 * (((ln >> 4) & 1) * 2 + ((ln >> 3) & 1)) + 4 * (ln >> 5) + (((ln >> 2) & 1) * 2 + ((ln >> 1) & 1));
   };
-  const uint32_t row8 = row_of(lane) * 8;
+  const uint32_t row8 = (wave * 32 + row_of(lane)) * 8;
   const int copy = (int)blockIdx.x % kCopies;
   bool patient = true;
 
@@ -800,6 +806,7 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
   // Column sums of a chunk that is completed for all groups of voting rows: add the waves' parts.  The first four waves do it, 32
   // keys each; the halves of a wave add four parts each.  (One store is issued in any case: vector() counts it.)  And the mass.
   float mass = 0.f;  // of the head, as far as it is known
+  int flushed = 0;   // chunks
   auto flush = [&](const Task& k, int par, bool there) {
     const int ln = lane_now();
     const int col = wave * 32 + (ln & 31);
@@ -816,12 +823,10 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
     const auto sw = __builtin_amdgcn_permlane32_swap(as_u32(t), as_u32(t), false, false);
     const unsigned u0 = sw[0], u1 = sw[1];
     t = as_f32(u0) + as_f32(u1);
-    // (the compiler may have loaded the kernel's argument into vector registers; what one has written is not yet an address)
-    const uint64_t to = (uint64_t)(uintptr_t)(prm.out + (int64_t)k.bh * prm.out_stride + k.ci() * kKeys);
-    const uint64_t out = ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(to >> 32)) << 32) | (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)to);
     uint64_t exec;
-    asm volatile("s_mov_b64 %0, exec\n\ts_mov_b64 exec, %1\n\ts_nop 4\n\tglobal_store_dword %2, %3, %4\n\ts_mov_b64 exec, %0"
-                 : "=&s"(exec) : "s"((uint64_t)lanes), "v"(col * 4), "v"(t), "s"(out) : "memory");
+    asm volatile("s_mov_b64 %0, exec\n\ts_mov_b64 exec, %1\n\tglobal_store_dword %2, %3, %4\n\ts_mov_b64 exec, %0"
+                 : "=&s"(exec) : "s"((uint64_t)lanes), "v"(col * 4), "v"(t), "s"(table[flushed].out) : "memory");
+    if (there && whole) ++flushed;
     if (wave == 0 && good && k.ci() == lead_of(k.bh, k.nc()) && prm.mass) {
       const uint32_t ms = lds0 + C::kOffMass + par * kWaves * 4;
       float m = 0.f;
@@ -845,20 +850,18 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
 
   uint64_t seen[kCopies];
   auto ask = [&](const Task& k) {
-    const uint64_t* low = prm.low + ((int64_t)k.unit(prm) * kCopies * kRows + wave * 32);
-    const uint32_t off = here(row8);
+    const uint32_t off = here(row8) + k.at;
 #pragma unroll
     for (int i = 0; i < kCopies; ++i)
-      asm volatile("global_load_dwordx2 %0, %1, %2 offset:%3 sc1" : "=v"(seen[i]) : "v"(off), "s"(base_of(low + i / 2 * 2 * kRows)), "i"(i % 2 * kRows * 8));
+      asm volatile("global_load_dwordx2 %0, %1, %2 offset:%3 sc1" : "=v"(seen[i]) : "v"(off + i / 2 * 2 * kRows * 8), "s"(units), "i"(i % 2 * kRows * 8));
   };
   auto ask_again = [&](const Task& k) {
-    const uint64_t* low = prm.low + ((int64_t)k.unit(prm) * kCopies * kRows + wave * 32);
-    const uint32_t off = here(row8);
+    const uint32_t off = here(row8) + k.at;
 #pragma unroll
-    for (int i = 0; i < kCopies; ++i) seen[i] = peek(base_of(low + i * kRows), off);
+    for (int i = 0; i < kCopies; ++i) seen[i] = peek(units, off + i * kRows * 8);
     asm volatile("" ::: "memory");
   };
-  auto add = [&](const uint64_t* to, float f, uint64_t lanes) {  // one chunk and the whole number next to f < 2^46, by these lanes
+  auto add = [&](uint32_t at, float f, uint64_t lanes) {  // one chunk and the whole number next to f < 2^46, by these lanes
     f = rintf(f);
     const float top = floorf(f * 2.3283064365386963e-10f);  // 2^-32
     const uint32_t hi = (uint32_t)top + (1u << (kCountShift - 32));
@@ -866,7 +869,7 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
     const uint64_t v = ((uint64_t)hi << 32) | lo;
     uint64_t exec;
     asm volatile("s_mov_b64 %0, exec\n\ts_mov_b64 exec, %1\n\tglobal_atomic_add_x2 %2, %3, %4\n\ts_mov_b64 exec, %0"
-                 : "=&s"(exec) : "s"(lanes), "v"(here(row8)), "v"(v), "s"(base_of(to)) : "memory");
+                 : "=&s"(exec) : "s"(lanes), "v"(here(row8) + at), "v"(v), "s"(units) : "memory");
   };
   auto publish = [&](const Task& k) {  // this wave's row sums (rs) of the chunk just formed
     // sum over the 32 lanes of a half: 16 values, halved at every exchange
@@ -878,27 +881,30 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
       t8[i] = as_f32(u0) + as_f32(u1);
     }
     // x + (x of the mirrored lane) in the lanes whose bit is clear, y + (y of the mirrored lane) in the others
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      asm("s_nop 1\n\tv_add_f32_dpp %0, %1, %1 row_mirror row_mask:0xf bank_mask:0x3\n\t"
-          "v_add_f32_dpp %0, %2, %2 row_mirror row_mask:0xf bank_mask:0xc" : "=&v"(t4[i]) : "v"(t8[i]), "v"(t8[i + 4]));
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-      asm("s_nop 1\n\tv_add_f32_dpp %0, %1, %1 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
-          "v_add_f32_dpp %0, %2, %2 row_half_mirror row_mask:0xf bank_mask:0xa" : "=&v"(t2[i]) : "v"(t4[i]), "v"(t4[i + 2]));
+    asm("s_nop 1\n\t"
+        "v_add_f32_dpp %0, %4, %4 row_mirror row_mask:0xf bank_mask:0x3\n\tv_add_f32_dpp %1, %5, %5 row_mirror row_mask:0xf bank_mask:0x3\n\t"
+        "v_add_f32_dpp %2, %6, %6 row_mirror row_mask:0xf bank_mask:0x3\n\tv_add_f32_dpp %3, %7, %7 row_mirror row_mask:0xf bank_mask:0x3\n\t"
+        "v_add_f32_dpp %0, %8, %8 row_mirror row_mask:0xf bank_mask:0xc\n\tv_add_f32_dpp %1, %9, %9 row_mirror row_mask:0xf bank_mask:0xc\n\t"
+        "v_add_f32_dpp %2, %10, %10 row_mirror row_mask:0xf bank_mask:0xc\n\tv_add_f32_dpp %3, %11, %11 row_mirror row_mask:0xf bank_mask:0xc"
+        : "=&v"(t4[0]), "=&v"(t4[1]), "=&v"(t4[2]), "=&v"(t4[3])
+        : "v"(t8[0]), "v"(t8[1]), "v"(t8[2]), "v"(t8[3]), "v"(t8[4]), "v"(t8[5]), "v"(t8[6]), "v"(t8[7]));
+    asm("s_nop 1\n\t"
+        "v_add_f32_dpp %0, %2, %2 row_half_mirror row_mask:0xf bank_mask:0x5\n\tv_add_f32_dpp %1, %3, %3 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
+        "v_add_f32_dpp %0, %4, %4 row_half_mirror row_mask:0xf bank_mask:0xa\n\tv_add_f32_dpp %1, %5, %5 row_half_mirror row_mask:0xf bank_mask:0xa"
+        : "=&v"(t2[0]), "=&v"(t2[1]) : "v"(t4[0]), "v"(t4[1]), "v"(t4[2]), "v"(t4[3]));
     const int ln = lane_now();
     const float q0 = t2[0] + dpp<0x1B>(t2[0]), q1 = t2[1] + dpp<0x1B>(t2[1]);  // quad mirror
     float sum = (ln & 2) ? q1 : q0;
     sum += dpp<0xB1>(sum);  // neighbours
     const bool low = sum < kLowLimit;
-    add(prm.low + (((int64_t)k.unit(prm) * kCopies + copy) * kRows + wave * 32), fminf(sum, kLowLimit) * kLowScale, __ballot(!(ln & 1) && low));
+    add(k.at + copy * kRows * 8, fminf(sum, kLowLimit) * kLowScale, __ballot(!(ln & 1) && low));
     if (!__all(low)) {  // (rare)
       const bool fits = sum < kHighLimit;
       if (!__all(low || fits)) {  // known to every workgroup of the unit before its row sums are complete
         __hip_atomic_store(&prm.ctl->redo, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
       }
-      add(prm.high + ((int64_t)k.unit(prm) * kRows + wave * 32), fits ? sum * kHighScale : 0.f, __ballot(!(ln & 1) && !low));
+      add(k.at + kHighAt, fits ? sum * kHighScale : 0.f, __ballot(!(ln & 1) && !low));
     }
   };
   // Column sums of the chunk held in pc, once the row sums of its unit are all there, added to those of the groups before.
@@ -913,7 +919,7 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
       do {
         __builtin_amdgcn_s_sleep(8);  // (a line that is asked for is slow to add to)
         ask_again(k);
-        hi = peek(base_of(prm.high + ((int64_t)k.unit(prm) * kRows + wave * 32)), row8);
+        hi = peek(units, here(row8) + (k.at + kHighAt));
         lo = 0;
 #pragma unroll
         for (int i = 0; i < kCopies; ++i) lo += seen[i];
@@ -931,8 +937,7 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
     float L = whole(lo) * (1.f / kLowScale);
     if (__any(hi != 0)) L = fmaf(whole(hi), 1.f / kHighScale, L);
     const float w_row = reciprocal(L);
-    const uint32_t wt = lds0 + C::kOffW + wave * 128;
-    *in_lds<float>(wt + row8 / 2) = w_row;
+    *in_lds<float>(lds0 + C::kOffW + row8 / 2) = w_row;
     const bool small = mostly_small(L);
     if (k.ci() == lead_of(k.bh, k.nc())) {  // the mass of this wave's rows, or a mark that it is not known yet
       const int ln = lane_now();
@@ -945,7 +950,7 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
     float w[16];
 #pragma unroll
     for (int i4 = 0; i4 < 4; ++i4) {
-      const f32x4 v = *in_lds<const f32x4>(wt + 16 * g, 32 * i4);
+      const f32x4 v = *in_lds<const f32x4>(lds0 + C::kOffW + wave * 128 + 16 * g, 32 * i4);
 #pragma unroll
       for (int e = 0; e < 4; ++e) w[4 * i4 + e] = v[e];
     }
@@ -985,21 +990,22 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
   // ---- prologue: the first two chunks' keys, the first two steps' references and the first one's rows, then the third chunk's keys
   const bool second = wave >= kWaves / 2;  // the group that runs half a step behind
   int fresh = 0;  // number of the chunk of `ahead`
-  Task ahead{table->bh, 0, table->shape};
+  Task ahead{table->bh, 0, table->shape, (uint32_t)(table->bh * prm.nqg) * kUnitBytes<D>};
   auto advance = [&]() {  // `ahead` to the walk's next task (which at the end of the walk may be of its last chunk again)
+    ahead.at += kUnitBytes<D>;
     if (++ahead.qg < prm.nqg) return;
     ahead.qg = 0;
     const Table c = table + min(++fresh, chunks - 1);
     ahead.bh = c->bh;
     ahead.shape = c->shape;
+    ahead.at = (uint32_t)(c->bh * prm.nqg) * kUnitBytes<D>;
   };
   Task cur = ahead, prev = ahead, done = ahead;
   dma_start(cur, 0);
   dma_k(0);
   aim_q(cur);
-  uint32_t q_off = lane16;
 #pragma unroll
-  for (int ks = 0; ks < S; ++ks) load_q(ks, q_off);
+  for (int ks = 0; ks < S; ++ks) load_q(ks);
   advance();
   Task next = ahead;
   dma_start(next, 1);
@@ -1069,19 +1075,18 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
   // the row sums of step s-1 (as late as an answer can be hidden: a sum that is asked for too early has to be asked for twice).
   auto matrix = [&](int par, f32x16 (&pf)[kNB]) {
     const int left = cur.keys() - r;  // keys of the chunk from this lane's on
-    aim_q(next);
 #pragma unroll
     for (int i = 0; i < kAhead; ++i) fetch(i);
     init(par, 0, left, pf[0]);
 #pragma unroll
     for (int n = 0; n < kNB * S; ++n) {
       const int kb = n / S, ks = n % S;
-      if (n == (kNB - 1) * S) q_off = here(lane16);
       if (n + kAhead < kNB * S) fetch(n + kAhead);
       if (ks == S / 2 && kb + 1 < kNB) init(par, kb + 1, left, pf[kb + 1]);
       mfma_step<bf16_t>(qf[ks], kf[n % (kAhead + 1)], pf[kb]);
       expo(n - S - kLag, pf);
-      if (kb == kNB - 1) load_q(ks, q_off);
+      if (n == (kNB - 1) * S) aim_q(next);
+      if (kb == kNB - 1) load_q(ks);
       __builtin_amdgcn_sched_barrier(0);
     }
     ask(prev);
@@ -1177,24 +1182,21 @@ int cus() {
 size_t pad256(size_t n) { return (n + 255) / 256 * 256; }
 
 struct Layout {
-  size_t control, table, counts, low, high, start, mass, done, late, parts, qpack, stats, bytes;  // offsets from the start of the area
+  size_t control, table, counts, mass, done, late, parts, units, stats, bytes;  // offsets from the start of the area
   int n_parts;
   Layout(const maskkv_desc* d, int nqg, const SweepPlan& plan) {
-    const size_t units = (size_t)d->B * d->H * nqg;
+    const size_t n = (size_t)d->B * d->H * nqg;  // units
     control = 0;
     table = pad256(sizeof(Control));
     counts = table + (size_t)plan.groups * plan.rounds * sizeof(Chunk);
-    low = pad256(counts + plan.groups * sizeof(int));
-    high = low + units * kCopies * kRows * sizeof(uint64_t);
-    start = high + units * kRows * sizeof(uint64_t);
-    mass = start + units * kRows * 2 * sizeof(float);
-    done = mass + units * sizeof(float);
+    mass = counts + plan.groups * sizeof(int);
+    done = mass + n * sizeof(float);
     n_parts = (d->P_max + kKeys - 1) / kKeys;
-    late = done + units * sizeof(int);
-    parts = late + units * sizeof(int);
-    qpack = pad256(parts + units * kWaves * n_parts * sizeof(uint32_t));
-    stats = qpack + units * kRows * d->d * 2;
-    bytes = stats + units * kSpans * kRows * sizeof(float2);
+    late = done + n * sizeof(int);
+    parts = late + n * sizeof(int);
+    units = pad256(parts + n * kWaves * n_parts * sizeof(uint32_t));
+    stats = units + n * (d->d == 128 ? kUnitBytes<128> : kUnitBytes<64>);
+    bytes = stats + n * kSpans * kRows * sizeof(float2);
   }
 };
 
@@ -1364,10 +1366,7 @@ int launch_sweep(const maskkv_desc* d, const View& Q, const View& K, const Lens&
   prm.n_parts = l.n_parts;
   prm.late = reinterpret_cast<int*>(base + l.late);
   prm.stats = reinterpret_cast<float2*>(base + l.stats);
-  prm.low = reinterpret_cast<uint64_t*>(base + l.low);
-  prm.high = reinterpret_cast<uint64_t*>(base + l.high);
-  prm.start = reinterpret_cast<float*>(base + l.start);
-  prm.qpack = base + l.qpack;
+  prm.units = base + l.units;
   prm.out = plan.subsets == 1 ? scores : group_sums;
   prm.out_stride = plan.subsets == 1 ? score_stride : group_stride;
   prm.mass = plan.subsets == 1 ? prompt_mass : reinterpret_cast<float*>(base + l.mass);
