@@ -11,7 +11,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmaskkv.so")
 BENCH_LIB = os.path.join(HERE, "libmaskkv_bench.so")
-SOURCES = ["api.hip", "score.hip", "sweep.hip", "select.hip", "compact.hip", "attend.hip", "attend_tiles.hip", "layer.hip"]
+SOURCES = ["api.hip", "score.hip", "sweep.hip", "rows.hip", "select.hip", "compact.hip", "attend.hip", "attend_tiles.hip", "layer.hip"]
 MARSHAL = os.path.join(HERE, "_marshal" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))
 BENCH_SOURCES = [os.path.join("bench", "probe.hip")]
 FLAGS = [

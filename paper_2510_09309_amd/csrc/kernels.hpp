@@ -14,6 +14,7 @@ struct SweepPlan {
   int subsets;  // a head's groups of voting rows are dealt to as many sets of workgroups
   int runs;
   int rounds;   // the most chunks of a workgroup
+  int parts;    // not 0: no sweep, but a head's voting rows are dealt to so many workgroups that keep all of their keys (rows.hip)
   uint32_t places[kMaxRuns], heads[kMaxRuns], repeats[kMaxRuns];
   __host__ __device__ int place(int i) const { return places[i] & 0xFFFF; }
   __host__ __device__ int width(int i) const { return places[i] >> 16; }
@@ -37,6 +38,21 @@ size_t score_workspace_bytes(const maskkv_desc* d, const Lens& lens, const Sweep
 int launch_score(const maskkv_desc* d, const View& Q, const View& K, const Lens& lens, float scale, float* scores,
                  int64_t score_stride, float* prompt_mass, void* workspace, hipStream_t stream,
                  void* const* events, const SweepPlan& plan, const float* row_lse = nullptr);
+
+// rows.hip: the scores of short fp32 prompts in one pass.  score_rows_parts: column sums per head that it leaves, or 0 where it does not apply.
+struct RowsParams {
+  View Q, K;
+  Lens lens;
+  int B, H, n_resp;
+  int n_query;      // voting rows per key/value head: q_per_kv query heads of n_qh mask queries each
+  int n_qh, q_per_kv;
+  float c;          // scale * log2(e)
+  float* out;       // [B*H][parts][out_stride]
+  int64_t out_stride;
+  float* mass;      // [B*H][parts] or null
+};
+int score_rows_parts(const maskkv_desc* d, const Lens& lens);
+int launch_score_rows(const RowsParams& prm, int d, int parts, hipStream_t stream);
 
 // sweep.hip: the scores in one sweep over the keys
 SweepPlan sweep_plan(const maskkv_desc* d, const Lens& lens, int nqg);

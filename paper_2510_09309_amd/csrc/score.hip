@@ -6,7 +6,7 @@
 //   merge   per-row log-sum-exp over the segments (+ the prompt's share of each row = prompt mass),
 //   pass 2  logits again, p = exp2(s*c - lse), summed over the queries for every prompt key.
 // Storing the n_m x N logits instead would cost far more HBM traffic than the second MFMA pass.
-// These passes serve fp32, prompts of more than one chunk of 128 keys per compute unit, the shapes at which they are the faster
+// These passes serve fp32 (short prompts: rows.hip), prompts of more than one chunk of 128 keys per compute unit, the shapes at which they are the faster
 // way (see Plan in sweep.hip), and given normalisers; everything else is scored in one sweep (sweep.hip).
 //
 // Work decomposition: the key axis of every (b, h) is cut into 64-key tiles (prompt tiles, then response
@@ -576,13 +576,18 @@ struct ScoreArea {
     const size_t lse = ((size_t)(bh * nq) * sizeof(float) + 255) / 256 * 256;
     sums = stats + lse;
     if (plan.groups > 0) sums = max(sums, (sweep_workspace_bytes(d, nqg, plan) + 255) / 256 * 256);
-    bytes = sums + (nqg > 1 ? (size_t)(bh * nqg * group_stride(d)) * sizeof(float) : 0);
+    const int parts = max(nqg, plan.parts);  // (column sums of a head)
+    bytes = sums + (parts > 1 ? (size_t)(bh * parts * group_stride(d)) * sizeof(float) : 0);
   }
 };
 
 }  // namespace
 
-SweepPlan score_sweep_plan(const maskkv_desc* d, const Lens& lens) { return sweep_plan(d, lens, query_groups(d)); }
+SweepPlan score_sweep_plan(const maskkv_desc* d, const Lens& lens) {
+  SweepPlan plan = sweep_plan(d, lens, query_groups(d));
+  plan.parts = score_rows_parts(d, lens);
+  return plan;
+}
 
 size_t score_workspace_bytes(const maskkv_desc* d, const Lens& lens, const SweepPlan& plan) {
   return ScoreArea(d, lens, plan).bytes;
@@ -626,6 +631,31 @@ int launch_score(const maskkv_desc* d, const View& Q, const View& K, const Lens&
     if (int e = mark(events, 2, stream)) return e;
     if (plan.subsets > 1)
       if (int e = launch_group_sum(prm, plan.subsets, stream)) return e;
+    return mark(events, 3, stream);
+  }
+  if (plan.parts > 0 && !row_lse) {
+    RowsParams rp;
+    rp.Q = Q;
+    rp.K = K;
+    rp.lens = lens;
+    rp.B = prm.B;
+    rp.H = prm.H;
+    rp.n_resp = prm.n_resp;
+    rp.n_query = prm.n_query;
+    rp.n_qh = prm.n_qh;
+    rp.q_per_kv = prm.q_per_kv;
+    rp.c = prm.c;
+    const bool whole = plan.parts == 1;
+    rp.out = whole ? scores : prm.group_sums;
+    rp.out_stride = whole ? score_stride : prm.group_stride;
+    rp.mass = whole ? prompt_mass : reinterpret_cast<float*>(ws);
+    prm.unit_mass = whole ? nullptr : rp.mass;
+    if (int e = mark(events, 0, stream)) return e;
+    if (int e = launch_score_rows(rp, d->d, plan.parts, stream)) return e;
+    for (int i = 1; i < 3; ++i)
+      if (int e = mark(events, i, stream)) return e;
+    if (!whole)
+      if (int e = launch_group_sum(prm, plan.parts, stream)) return e;
     return mark(events, 3, stream);
   }
   if (d->dtype == MASKKV_BF16)

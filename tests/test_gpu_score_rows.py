@@ -1,0 +1,46 @@
+"""The one-pass scoring kernel of short fp32 prompts: edges of its tiles of 16 keys and of its groups of 16 rows, several groups of
+a workgroup, grouped queries, empty prompts, strides, its longest prompts and the first ones that are too long (needs an MI355X).
+
+Reference: float64 on the same inputs.  fp32 logits of up to 2^4 are off by 2^-20 or less, an exponential and a sum of them by as
+much relative to themselves.
+"""
+import pytest
+import torch
+
+from tests import helpers as hp
+
+pytestmark = pytest.mark.gpu
+
+RTOL = 2.0 ** -19
+# The two passes accumulate logits from minus the row's normaliser over scale * log2(e), a number of up to 2^7: eight times the rounding.
+RTOL_TWO_PASSES = 2.0 ** -16
+
+
+@pytest.mark.parametrize("d,n,H,g,Ps", [
+    (64, 1, 1, 1, (1,)), (128, 15, 2, 1, (15, 16, 17, 0)), (64, 17, 3, 1, (128, 367, 368, 95)), (128, 33, 2, 1, (351, 352, 607)),
+    (64, 48, 5, 4, (640, 463)), (128, 16, 2, 7, (1008, 1009, 1500)),
+    (64, 60, 100, 1, (300, 20)), (128, 40, 130, 1, (200, 333, 64, 1)),       # several groups of rows a workgroup, or all of them
+    (128, 100, 12, 1, (2972,)), (128, 100, 12, 1, (2973,))])                 # the most keys, and one more (two passes)
+def test_against_float64(d, n, H, g, Ps):
+    m = hp.mk()
+    gen = torch.Generator(device="cuda").manual_seed(d + n + H)
+    B, P_max = len(Ps), max(Ps)
+    Q = torch.randn((B, H * g, n, d), generator=gen, device="cuda")
+    K = torch.randn((B, P_max + n, H, d), generator=gen, device="cuda").transpose(1, 2)   # (rows of a head are H * d apart)
+    desc = m.Desc(B=B, H=H, d=d, dtype=m.MASKKV_F32, n_resp=n, P_max=P_max, prompt_len=None if B == 1 else list(Ps), q_per_kv=0 if g == 1 else g)
+    scores, mass = torch.full((B * H, P_max + 3), float("nan"), device="cuda"), torch.full((B * H,), float("nan"), device="cuda")
+    ws = hp.workspace(m.maskkv_score_workspace_bytes(desc))
+    m.maskkv_score(desc, Q, K, 0.0, scores, P_max + 3, mass, ws)
+    rtol = RTOL if P_max + n <= 3072 else RTOL_TWO_PASSES
+    for b, P in enumerate(Ps):
+        for h in range(0, H, 1 + H // 8):
+            q = Q[b, h * g:(h + 1) * g].reshape(g * n, d).double()
+            want = torch.softmax(q @ K[b, h, :P + n].double().T / d ** 0.5, dim=1)[:, :P].sum(0)
+            assert torch.allclose(scores[b * H + h, :P].double(), want, rtol=rtol, atol=0), (b, h)
+            assert torch.isnan(scores[b * H + h, P:]).all()
+            assert abs(float(mass[b * H + h]) - float(want.sum())) <= rtol * float(want.sum()), (b, h)
+    again, mass2 = torch.empty_like(scores), torch.empty_like(mass)
+    m.maskkv_score(desc, Q, K, 0.0, again, P_max + 3, mass2, ws)
+    assert torch.equal(mass, mass2)
+    for b, P in enumerate(Ps):
+        assert torch.equal(again[b * H:(b + 1) * H, :P], scores[b * H:(b + 1) * H, :P])
