@@ -11,11 +11,13 @@ namespace maskkv {
 constexpr int kMaxRuns = 2 * MASKKV_MAX_BATCH;
 struct SweepPlan {
   int groups;   // workgroups, or 0: two passes
+  int grid;     // of the launch; where there are more groups, each half of a workgroup is one
   int subsets;  // a head's groups of voting rows are dealt to as many sets of workgroups
   int runs;
   int rounds;   // the most chunks of a workgroup
   int parts;    // not 0: no sweep, but a head's voting rows are dealt to so many workgroups that keep all of their keys (rows.hip)
   uint32_t places[kMaxRuns], heads[kMaxRuns], repeats[kMaxRuns];
+  __host__ __device__ bool halves() const { return groups > grid; }
   __host__ __device__ int place(int i) const { return places[i] & 0xFFFF; }
   __host__ __device__ int width(int i) const { return places[i] >> 16; }
   __host__ __device__ int head(int i) const { return heads[i] & 0xFFFF; }

@@ -97,7 +97,7 @@ constexpr int kSpans = 8;                  // pieces of a unit's keys in the fal
 // A chunk of a head's keys.
 struct __attribute__((aligned(16))) Chunk {
   int bh;
-  uint32_t shape;     // its number, 8 bits; the head's number of chunks less one, 8 bits; its number of keys
+  uint32_t shape;     // its number, 8 bits; the head's number of chunks less one, 8 bits; its number of keys, or 0: none (HALVES)
   const char* keys;
   float* out;         // its scores
   int64_t pad;
@@ -199,7 +199,7 @@ struct Cfg {
   static constexpr int kOffInf = kOffW + kWaves * 128;         // 32 floats: -inf
   static constexpr int kOffMass = kOffInf + 128;               // [2][kWaves] floats
   static constexpr int kOffBad = kOffMass + 2 * kWaves * 4;    // one int: the scores of this workgroup are void
-  static constexpr int kOffLate = kOffBad + 4;                 // one int: 1 + the first unit that late_masses has to do, or 0
+  static constexpr int kOffLate = kOffBad + 4;                 // two ints: 1 + the first unit that late_masses has to do, or 0
   static constexpr int kLds = kOffBad + 64;
   // Rows are stored without padding (a direct transfer writes 1 KiB of consecutive LDS); piece p of row r sits in
   // slot p ^ swz(r), which spreads the fragment reads of 16 consecutive rows over all banks.
@@ -252,15 +252,29 @@ __device__ __forceinline__ void start_lock(const SweepParams& prm) {
   const int w = threadIdx.x;
   if (w < prm.plan.groups) {
     int n = 0;
-    for (int i = 0; i < prm.plan.runs; ++i) n += prm.plan.has(i, w) ? prm.plan.times(i) : 0;
+    for (int i = 0; i < prm.plan.runs;) {
+      const int times = prm.plan.times(i);
+      bool has = false;
+      do has = has || prm.plan.has(i, w);
+      while (++i < prm.plan.runs && prm.plan.place(i) > 0);  // (to the end of the round)
+      if (!has && prm.plan.halves()) {
+        Chunk c;
+        c.bh = 0;
+        c.shape = 0;
+        c.keys = prm.K.row(0, 0, 0);
+        c.out = prm.out;
+        for (int t = n; t < n + times; ++t) prm.table[(int64_t)w * prm.rounds + t] = c;
+      }
+      n += has || prm.plan.halves() ? times : 0;
+    }
     prm.counts[w] = n;
   }
   if (threadIdx.x >= 64) return;
-  bool run = take_lock(prm.plan.groups, 0);
+  bool run = take_lock(prm.plan.grid, 0);
   const uint64_t t0 = wall_clock64();
   while (!run && wall_clock64() - t0 < kStartWait) {
     __builtin_amdgcn_s_sleep(32);
-    run = take_lock(prm.plan.groups, kWaiters);
+    run = take_lock(prm.plan.grid, kWaiters);
   }
   if (threadIdx.x == 0) {
     prm.ctl->run = run;
@@ -279,14 +293,22 @@ __device__ __forceinline__ void start_table(const SweepParams& prm, int b, int v
   const int nth = vh - prm.plan.head(i), side = prm.plan.side(i);
   const int w0 = prm.plan.place(i) + nth % side * nc;
   for (int ci = lane; ci < nc; ci += 64) {
+    const int w = w0 + ci;
     int t = nth / side;
-    for (int j = 0; j < i; ++j) t += prm.plan.has(j, w0 + ci) ? prm.plan.times(j) : 0;
+    for (int j = 0; j < i;) {
+      const int times = prm.plan.times(j);
+      bool has = prm.plan.halves();
+      do has = has || prm.plan.has(j, w);
+      while (++j < i && prm.plan.place(j) > 0);
+      // (the round that run i belongs to may have begun before it: its other runs have other workgroups)
+      t += has && (j < i || prm.plan.place(i) == 0) ? times : 0;
+    }
     Chunk c;
     c.bh = b * prm.heads() + vh;
     c.shape = (uint32_t)ci | (uint32_t)(nc - 1) << 8 | (uint32_t)min(P - ci * kKeys, kKeys) << 16;
     c.keys = prm.K.row(b, vh / prm.subsets, (int64_t)ci * kKeys);
     c.out = prm.out + (int64_t)c.bh * prm.out_stride + ci * kKeys;
-    prm.table[(int64_t)(w0 + ci) * prm.rounds + t] = c;
+    prm.table[(int64_t)w * prm.rounds + t] = c;
   }
 }
 
@@ -612,6 +634,7 @@ struct Task {
   int bh, qg;
   uint32_t shape;
   uint32_t at;  // its unit's place in SweepParams::units
+  __device__ bool idle() const { return shape == 0; }
   __device__ int ci() const { return shape & 255; }
   __device__ int nc() const { return (shape >> 8 & 255) + 1; }
   __device__ int keys() const { return shape >> 16; }
@@ -686,13 +709,22 @@ __device__ __forceinline__ void late_masses(const SweepParams& prm, uint32_t lds
   }
 }
 
-template <int D>
+// HALVES: a head has at most 128 voting rows, and each half of the workgroup works on chunks of its own, as a workgroup of four waves
+// (with a ring of two chunks, and in the rounds without one on an idle task).
+template <int D, bool HALVES>
 __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t lds0) {
   using C = Cfg<D>;
   constexpr int S = C::kSteps;
+  constexpr int kTeam = HALVES ? kWaves / 2 : kWaves;  // waves that share a chunk
+  constexpr int kSlots = HALVES ? C::kRing / 2 : C::kRing;
+  constexpr int kShare = kKeys / kTeam;                // keys that a wave moves
+  constexpr int kMoves = kShare / C::kRPI;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r = lane & 31, g = lane >> 5;
+  const bool second = wave >= kWaves / 2;  // the group of waves that runs half a step behind
+  const int rb = wave % kTeam;             // this wave's block of 32 rows
+  const int lds_ring = lds0 + (HALVES && second ? kSlots * C::kKBytes : 0);
   const float c = prm.c;
   // A value hidden from the optimiser: what a step derives from it is then worth an instruction or two each time instead of
   // a register for the whole loop.
@@ -704,32 +736,34 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
 
   // ---- the walk
   typedef const __attribute__((address_space(4))) Chunk* Table;
-  const Table table = (Table)(prm.table + (int64_t)blockIdx.x * prm.rounds);
-  const int chunks = *(const __attribute__((address_space(4))) int*)(prm.counts + blockIdx.x);
+  const int team = (int)blockIdx.x + (HALVES && second ? (int)gridDim.x : 0);
+  const Table table = (Table)(prm.table + (int64_t)team * prm.rounds);
+  auto count = [&](int t) { return *(const __attribute__((address_space(4))) int*)(prm.counts + t); };
+  const int chunks = HALVES && team >= prm.plan.groups ? 0 : count(team);
   const int mine = chunks * prm.nqg;  // steps: each chunk with all groups of voting rows, so that keys are transferred once
   const uint32_t kstride = (uint32_t)prm.K.stride_t;
   const uint32_t lane16 = lane * 16;
-  // Row wave * 16 + j * kRPI + rl of the chunk (rl: this lane's row of transfer j) has its pieces permuted by the low bits of
+  // Row rb * kShare + j * kRPI + rl of the chunk (rl: this lane's row of transfer j) has its pieces permuted by the low bits of
   // that number, which are j's and rl's side by side: one exclusive-or with a constant per transfer.
   const uint32_t krow = (uint32_t)lane / C::kPPR, kpiece = ((uint32_t)lane % C::kPPR ^ C::swz(krow)) << 4;
-  const uint32_t koff = (wave * (kKeys / kWaves) + krow) * kstride;  // (a chunk's rows are up to 127 x 16 MiB apart)
+  const uint32_t koff = (rb * kShare + krow) * kstride;  // (a chunk's rows are up to 127 x 16 MiB apart)
   // Chunk number t into its slot of the ring: this wave's part.  (Rows past the last key re-read it.)
   auto dma_k = [&](int t) {
     const Table c = table + min(t, chunks - 1);
-    const uint32_t most = ((c->shape >> 16) - 1) * kstride;
-    const uint32_t to = lds0 + t % C::kRing * C::kKBytes + wave * (kKeys / kWaves) * C::kRowB;
+    const uint32_t most = (max(c->shape >> 16, 1u) - 1) * kstride;
+    const uint32_t to = lds_ring + t % kSlots * C::kKBytes + rb * kShare * C::kRowB;
 #pragma unroll
-    for (int j = 0; j < C::kMoves; ++j)
+    for (int j = 0; j < kMoves; ++j)
       dma16(c->keys, min(here(koff) + (uint32_t)(j * C::kRPI) * kstride, most) + (here(kpiece) ^ (C::swz(j * C::kRPI) << 4)), to + j * 1024);
   };
   const Base units = base_of(prm.units);
   auto dma_start = [&](const Task& k, int par) {
-    dma4((const char*)units, (here(lane16) >> 2) + (k.at + kRefsAt + wave * 256), lds0 + C::kOffStart + (par * kWaves + wave) * 256);
+    dma4((const char*)units, (here(lane16) >> 2) + (k.at + kRefsAt + rb * 256), lds0 + C::kOffStart + (par * kWaves + wave) * 256);
   };
   u32x4 qf[S];
   // (The loads of the walk are asm, and waited for by asm: the compiler does not see the transfers and would wait for all of them.)
   uint32_t q_at = 0;
-  auto aim_q = [&](const Task& k) { q_at = here(lane16) + (k.at + kRowsAt + wave * C::kQBytes); };
+  auto aim_q = [&](const Task& k) { q_at = here(lane16) + (k.at + kRowsAt + rb * C::kQBytes); };
   auto load_q = [&](int ks) {
     if (ks == 4) q_at += 4096;  // (what an immediate offset reaches)
     asm volatile("global_load_dwordx4 %0, %1, %2 offset:%3" : "=v"(qf[ks]) : "v"(q_at), "s"(units), "i"(ks % 4 * 1024));
@@ -739,8 +773,8 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
   auto row_of = [](int ln) {
     return 8 * (((ln >> 4) & 1) * 2 + ((ln >> 3) & 1)) + 4 * (ln >> 5) + (((ln >> 2) & 1) * 2 + ((ln >> 1) & 1));
   };
-  const uint32_t row8 = (wave * 32 + row_of(lane)) * 8;
-  const int copy = (int)blockIdx.x % kCopies;
+  const uint32_t row8 = (rb * 32 + row_of(lane)) * 8;
+  const int copy = team % kCopies;
   bool patient = true;
 
   // The logits are formed 32 keys at a time, minus the rows' references, which are the accumulators' initial values (a
@@ -759,13 +793,13 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
   uint32_t fa[S];  // this lane's fragments of the chunk
 #pragma unroll
   for (int ks = 0; ks < S; ++ks) {
-    fa[ks] = lds0 + r * C::kRowB + (((2 * ks + g) ^ C::swz(r)) << 4);
+    fa[ks] = lds_ring + r * C::kRowB + (((2 * ks + g) ^ C::swz(r)) << 4);
     asm volatile("" : "+v"(fa[ks]));
   }
   int slot = 0;
   auto turn = [&]() {  // to the ring's next chunk
-    const int by = slot == C::kRing - 1 ? (1 - C::kRing) * C::kKBytes : C::kKBytes;
-    slot = slot == C::kRing - 1 ? 0 : slot + 1;
+    const int by = slot == kSlots - 1 ? (1 - kSlots) * C::kKBytes : C::kKBytes;
+    slot = slot == kSlots - 1 ? 0 : slot + 1;
 #pragma unroll
     for (int ks = 0; ks < S; ++ks) fa[ks] += by;
   };
@@ -803,23 +837,25 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
     }
   };
 
-  // Column sums of a chunk that is completed for all groups of voting rows: add the waves' parts.  The first four waves do it, 32
-  // keys each; the halves of a wave add four parts each.  (One store is issued in any case: vector() counts it.)  And the mass.
+  // Column sums of a chunk that is completed for all groups of voting rows: add the waves' parts.  Four waves do it, 32 keys each;
+  // the halves of a wave add half of the parts each.  (One store is issued in any case: vector() counts it.)  And the mass.
+  const bool flushes = HALVES || !second;
   float mass = 0.f;  // of the head, as far as it is known
   int flushed = 0;   // chunks
   auto flush = [&](const Task& k, int par, bool there) {
     const int ln = lane_now();
-    const int col = wave * 32 + (ln & 31);
-    const uint32_t cs = lds0 + C::kOffCs + (par * kWaves + (ln >> 5) * (kWaves / 2)) * kKeys * 4 + col * 4;
+    const int col = rb * 32 + (ln & 31);
+    const uint32_t cs = lds0 + C::kOffCs + (par * kWaves + (HALVES && second ? kTeam : 0) + (ln >> 5) * (kTeam / 2)) * kKeys * 4 + col * 4;
     const int bad = *in_lds<const int>(lds0 + C::kOffBad);
-    float v[kWaves / 2];
+    float v[kTeam / 2];
 #pragma unroll
-    for (int w = 0; w < kWaves / 2; ++w) v[w] = *in_lds<const float>(cs, w * kKeys * 4);
+    for (int w = 0; w < kTeam / 2; ++w) v[w] = *in_lds<const float>(cs, w * kKeys * 4);
     const bool whole = k.qg == prm.nqg - 1;
-    const int good = __builtin_amdgcn_readfirstlane(there ? bad ^ 1 : 0);
-    const int keys = good && whole ? min(max(k.keys() - wave * 32, 0), 32) : 0;
+    const int good = __builtin_amdgcn_readfirstlane(there && !(HALVES && k.idle()) ? bad ^ 1 : 0);
+    const int keys = good && whole ? min(max(k.keys() - rb * 32, 0), 32) : 0;
     const uint32_t lanes = __builtin_amdgcn_readfirstlane((uint32_t)((1ull << keys) - 1));
-    float t = (v[0] + v[1]) + (v[2] + v[3]);
+    float t = v[0] + v[1];
+    if (!HALVES) t += v[kTeam / 2 - 2] + v[kTeam / 2 - 1];
     const auto sw = __builtin_amdgcn_permlane32_swap(as_u32(t), as_u32(t), false, false);
     const unsigned u0 = sw[0], u1 = sw[1];
     t = as_f32(u0) + as_f32(u1);
@@ -827,16 +863,17 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
     asm volatile("s_mov_b64 %0, exec\n\ts_mov_b64 exec, %1\n\tglobal_store_dword %2, %3, %4\n\ts_mov_b64 exec, %0"
                  : "=&s"(exec) : "s"((uint64_t)lanes), "v"(col * 4), "v"(t), "s"(table[flushed].out) : "memory");
     if (there && whole) ++flushed;
-    if (wave == 0 && good && k.ci() == lead_of(k.bh, k.nc()) && prm.mass) {
-      const uint32_t ms = lds0 + C::kOffMass + par * kWaves * 4;
+    if (rb == 0 && good && k.ci() == lead_of(k.bh, k.nc()) && prm.mass) {
+      const uint32_t ms = lds0 + C::kOffMass + (par * kWaves + wave) * 4;
+      const uint32_t late = lds0 + C::kOffLate + (HALVES && second ? 4 : 0);
       float m = 0.f;
 #pragma unroll
-      for (int w = 0; w < kWaves; ++w) m += *in_lds<const float>(ms, w * 4);
+      for (int w = 0; w < kTeam; ++w) m += *in_lds<const float>(ms, w * 4);
       if (m < 0.f) {  // (not known yet)
         if (ln == 0) {
           const int unit = k.unit(prm);
-          __hip_atomic_store(at<int>(base_of(prm.late + unit), here(0)), *in_lds<const int>(lds0 + C::kOffLate), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          *in_lds<int>(lds0 + C::kOffLate) = unit + 1;
+          __hip_atomic_store(at<int>(base_of(prm.late + unit), here(0)), *in_lds<const int>(late), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          *in_lds<int>(late) = unit + 1;
         }
       } else {
         mass += m;
@@ -897,8 +934,8 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
     float sum = (ln & 2) ? q1 : q0;
     sum += dpp<0xB1>(sum);  // neighbours
     const bool low = sum < kLowLimit;
-    add(k.at + copy * kRows * 8, fminf(sum, kLowLimit) * kLowScale, __ballot(!(ln & 1) && low));
-    if (!__all(low)) {  // (rare)
+    add(k.at + copy * kRows * 8, fminf(sum, kLowLimit) * kLowScale, HALVES && k.idle() ? 0 : __ballot(!(ln & 1) && low));
+    if (!__all(low) && !(HALVES && k.idle())) {  // (rare)
       const bool fits = sum < kHighLimit;
       if (!__all(low || fits)) {  // known to every workgroup of the unit before its row sums are complete
         __hip_atomic_store(&prm.ctl->redo, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -937,7 +974,7 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
     float L = whole(lo) * (1.f / kLowScale);
     if (__any(hi != 0)) L = fmaf(whole(hi), 1.f / kHighScale, L);
     const float w_row = reciprocal(L);
-    *in_lds<float>(lds0 + C::kOffW + row8 / 2) = w_row;
+    *in_lds<float>(lds0 + C::kOffW + (HALVES && second ? kTeam * 128 : 0) + row8 / 2) = w_row;
     const bool small = mostly_small(L);
     if (k.ci() == lead_of(k.bh, k.nc())) {  // the mass of this wave's rows, or a mark that it is not known yet
       const int ln = lane_now();
@@ -968,7 +1005,7 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
     if (__builtin_expect(small, 0)) {
       const float t = wave_sum((col[0] + col[1]) + (col[2] + col[3]));
       if (lane_now() == 0)
-        __hip_atomic_store(prm.parts + ((int64_t)k.unit(prm) * kWaves + wave) * prm.n_parts + k.ci(), as_u32(t) & 0x7FFFFFFFu, __ATOMIC_RELAXED,
+        __hip_atomic_store(prm.parts + ((int64_t)k.unit(prm) * kWaves + rb) * prm.n_parts + k.ci(), as_u32(t) & 0x7FFFFFFFu, __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_AGENT);
     }
 #pragma unroll
@@ -988,31 +1025,37 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
   };
 
   // ---- prologue: the first two chunks' keys, the first two steps' references and the first one's rows, then the third chunk's keys
-  const bool second = wave >= kWaves / 2;  // the group that runs half a step behind
+  // (HALVES: the ring holds two chunks; a half without chunks asks for nothing)
   int fresh = 0;  // number of the chunk of `ahead`
-  Task ahead{table->bh, 0, table->shape, (uint32_t)(table->bh * prm.nqg) * kUnitBytes<D>};
-  auto advance = [&]() {  // `ahead` to the walk's next task (which at the end of the walk may be of its last chunk again)
-    ahead.at += kUnitBytes<D>;
-    if (++ahead.qg < prm.nqg) return;
-    ahead.qg = 0;
-    const Table c = table + min(++fresh, chunks - 1);
+  Task ahead{0, 0, 0, 0};
+  auto take = [&](int t) {
+    const Table c = table + t;
     ahead.bh = c->bh;
     ahead.shape = c->shape;
     ahead.at = (uint32_t)(c->bh * prm.nqg) * kUnitBytes<D>;
   };
-  Task cur = ahead, prev = ahead, done = ahead;
-  dma_start(cur, 0);
-  dma_k(0);
-  aim_q(cur);
+  auto advance = [&]() {  // `ahead` to the walk's next task (which at the end of the walk may be of its last chunk again)
+    ahead.at += kUnitBytes<D>;
+    if (++ahead.qg < prm.nqg) return;
+    ahead.qg = 0;
+    take(min(++fresh, chunks - 1));
+  };
+  if (!HALVES || chunks > 0) take(0);
+  Task cur = ahead, next = ahead, prev = ahead, done = ahead;
+  if (!HALVES || chunks > 0) {
+    dma_start(cur, 0);
+    dma_k(0);
+    aim_q(cur);
 #pragma unroll
-  for (int ks = 0; ks < S; ++ks) load_q(ks);
-  advance();
-  Task next = ahead;
-  dma_start(next, 1);
-  dma_k(1);
+    for (int ks = 0; ks < S; ++ks) load_q(ks);
+    advance();
+    next = ahead;
+    dma_start(next, 1);
+    dma_k(1);
+  }
   if (threadIdx.x < 32) *in_lds<float>(lds0 + C::kOffInf + threadIdx.x * 4) = -INFINITY;
   // (kOffBad and kOffLate; a workgroup that is placed when others have already given up goes straight to the fallback)
-  if (threadIdx.x < 2)
+  if (threadIdx.x < 3)
     *in_lds<int>(lds0 + C::kOffBad + threadIdx.x * 4) =
         threadIdx.x == 0 ? __hip_atomic_load(&prm.ctl->redo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
   for (int i = threadIdx.x; i < 2 * kWaves * kKeys; i += kThreads) *in_lds<float>(lds0 + C::kOffCs + i * 4) = 0.f;
@@ -1021,9 +1064,9 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
 #pragma unroll
   for (int ks = 0; ks < S; ++ks) asm volatile("" : "+v"(qf[ks]));
   if (__builtin_amdgcn_readfirstlane(*in_lds<const int>(lds0 + C::kOffBad))) return;
-  advance();
-  dma_k(2);
-  int keys_at = 3;  // number of the next chunk whose keys are asked for
+  if (!HALVES || chunks > 0) advance();
+  if (!HALVES) dma_k(2);
+  int keys_at = HALVES ? 2 : 3;  // number of the next chunk whose keys are asked for
   f32x16 pa[kNB], pb[kNB];
 #pragma unroll
   for (int kb = 0; kb < kNB; ++kb) {
@@ -1053,20 +1096,30 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
   };
   if (second) asm volatile("s_barrier" ::: "memory");
 
-  if (wave * 32 >= prm.rows) {  // no rows for this wave: it only helps to move keys and to add columns
+  if (HALVES && mine == 0) {  // no such half is in any round: it only meets the other's barriers
+    for (int s = 0; s < count(team - (int)gridDim.x); ++s) {
+      end_vector();
+      end_vector();
+    }
+    end_vector();
+    if (!second) end_vector();
+    return;
+  }
+  if (rb * 32 >= prm.rows) {  // no rows for this wave: it only helps to move keys and to add columns
     for (int s = 0; s < mine; ++s) {
       end_matrix(s);
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       if (cur.qg == 0 && keys_at < chunks) dma_k(keys_at++);
-      if (!second) flush(done, s & 1 ^ 1, s >= 2);
+      if (flushes) flush(done, s & 1 ^ 1, s >= 2);
       shift();
       end_vector();
     }
     end_vector();
-    if (!second) flush(done, mine & 1 ^ 1, mine >= 2);
+    if (flushes) flush(done, mine & 1 ^ 1, mine >= 2);
+    if (HALVES) flush(prev, mine & 1, true);
     if (!second) {
       end_vector();
-      flush(prev, mine & 1, true);
+      if (!HALVES) flush(prev, mine & 1, true);
     }
     return;
   }
@@ -1098,9 +1151,9 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
   // references of step s+2 are asked for.
   auto vector = [&](int s, int par, f32x16 (&pc)[kNB]) {
     publish(cur);
-    if (!second) flush(done, par ^ 1, s >= 2);
+    if (flushes) flush(done, par ^ 1, s >= 2);
     // All but the addition and the store just issued: the rows, the row sums, and the transfers of the step before.
-    if (second)
+    if (!flushes)
       asm volatile("s_waitcnt vmcnt(1)" ::: "memory");
     else
       asm volatile("s_waitcnt vmcnt(2)" ::: "memory");
@@ -1109,7 +1162,7 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
 #pragma unroll
     for (int ks = 0; ks < S; ++ks) asm volatile("" : "+v"(qf[ks]));
     dma_start(ahead, par);
-    if (s > 0) complete(prev, par, pc);
+    if (s > 0 && !(HALVES && prev.idle())) complete(prev, par, pc);
     if (cur.qg == 0 && keys_at < chunks) dma_k(keys_at++);
     shift();
   };
@@ -1125,16 +1178,19 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
   }
   // ---- the last step: completed at once, by the first group while the second publishes it
   const int par = mine & 1;
-  ask_again(prev);
-  if (par)
-    complete(prev, par, pa);
-  else
-    complete(prev, par, pb);
+  if (!HALVES || !prev.idle()) {
+    ask_again(prev);
+    if (par)
+      complete(prev, par, pa);
+    else
+      complete(prev, par, pb);
+  }
   end_vector();
-  if (!second) flush(done, par ^ 1, mine >= 2);
+  if (flushes) flush(done, par ^ 1, mine >= 2);
+  if (HALVES) flush(prev, par, true);
   if (!second) {
     end_vector();
-    flush(prev, par, true);
+    if (!HALVES) flush(prev, par, true);
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (no transfer into LDS outlives its workgroup)
 }
@@ -1148,17 +1204,19 @@ __device__ __forceinline__ const SweepParams& argument_again() {
   return *(const SweepParams*)p;
 }
 
-template <int D>
+template <int D, bool HALVES>
 __global__ __launch_bounds__(kThreads, 2) void sweep_kernel(const SweepParams prm) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
   if (prm.ctl->run) {
     if (threadIdx.x == 0)
       __hip_atomic_fetch_add(&sweep_placed[blockIdx.x % kPlaces * kPlaceWords], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    sweep_chunks<D>(prm, lds0);
+    sweep_chunks<D, HALVES>(prm, lds0);
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     const int late = __builtin_amdgcn_readfirstlane(*in_lds<const int>(lds0 + Cfg<D>::kOffLate));
+    const int late2 = HALVES ? __builtin_amdgcn_readfirstlane(*in_lds<const int>(lds0 + Cfg<D>::kOffLate, 4)) : 0;
     if (__builtin_expect(late, 0)) late_masses<D>(argument_again(), lds0, late);
+    if (HALVES && __builtin_expect(late2, 0)) late_masses<D>(argument_again(), lds0, late2);
   }
   if (__hip_atomic_load(&prm.ctl->redo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) sweep_redo<D>(argument_again(), lds0);
 }
@@ -1211,6 +1269,12 @@ struct Layout {
 //
 // A head's groups of voting rows are one workgroup's turn, which needs its keys once, unless that leaves workgroups without work: a
 // head then counts as several with the same keys, and their column sums are added by a kernel of their own (5 us).
+//
+// Where no head has more than 128 voting rows, four of a workgroup's waves would have none: the halves of a workgroup can then be two
+// workgroups, each with chunks of its own (4 sequences of 28 heads, head_dim 64, 116 rows, 22 chunks: 37.6 instead of 44.9 us).
+// They meet at each step's barriers, so a step has the same number as its round in every half, and a half that a round
+// has no chunk for goes through an idle step: with the steps of a list closed up, one half waits for a head of a later round
+// than the other's, and halves that hold each other up this way can wait in a circle.
 struct Packing {
   SweepPlan plan;
   Packing(const maskkv_desc* d, const int* nc, int n, int subsets, int nqg, bool mixed) : plan{} {
@@ -1263,22 +1327,26 @@ SweepPlan make_plan(const maskkv_desc* d, const Lens& lens, int nqg) {
     chunks += (int64_t)nc[b] * d->H;
   }
   if (most == 0 || most > n) return best;
-  // Microseconds.  A step: 2.72 (head_dim 64: 2.45), and more where more than 150 workgroups add to one row's sum; the two
-  // passes: 0.017 (0.010) per chunk; what either costs besides.  (32 heads, head_dim 128: 122 against 163 at 32k tokens, 75 / 85
-  // at 15k, 39 / 59 at 8k, but 103 / 95 at 17k; head_dim 64: 32 / 42 at 8k, 51 / 61 at 16k, but 57 / 53 at 12.5k, 140 / 105 at 32k.)
-  const bool wide = d->d == 128;
-  const double step = (wide ? 2.72 : 2.45) + max(0, most - 150) * (wide ? 0.007 : 0.0157);
+  // Microseconds, from 44 batches of the sizes that bf16 prompts come in, each timed in every way: a step of 256 rows, with half of
+  // the waves idle, and of two chunks side by side; the two passes per chunk; and what each costs besides.  (Rounds against two
+  // passes, head_dim 128: 16 heads of 218 chunks 59 / 79, of 227 with two groups of rows 92 / 143, the 5952 chunks of 5 sequences
+  // with 7 queries a head 88 / 131; head_dim 64: 28 heads of 213 chunks with two groups of rows 128 / 154, 1300 chunks 30 / 51.
+  // Rounds against halves: 32 heads of 87 chunks, 16 steps against 7, 44.9 / 35.8; 8 sequences of 32 heads, 18 / 9, 60.1 / 51.2; 13 /
+  // 7, 39.9 / 37.8; 4 / 2, 22.2 / 21.9; but 5 / 3, 23.5 / 23.9; 6 / 3, 25.4 / 26.3; 2 / 1, 14.0 / 14.4.)
+  const bool wide = d->d == 128, few = (int64_t)d->n_query * query_heads_per_kv(d) <= kRows / 2;
   double cost = 23.0 + (double)chunks * nqg * (wide ? 0.0169 : 0.0101);
-  for (int subsets = 1; subsets <= nqg; ++subsets) {
-    if (nqg % subsets) continue;
-    Packing p(d, nc, n, subsets, nqg, true);
-    if (!p.plan.groups) p = Packing(d, nc, n, subsets, nqg, false);
-    const double c = 14.0 + p.plan.rounds * (nqg / subsets) * step + (subsets > 1 ? 5.0 : 0.0);
-    if (c < cost) {
-      cost = c;
-      best = p.plan;
-    }
-  }
+  auto consider = [&](int workgroups, int subsets, double besides, double step) {
+    Packing p(d, nc, workgroups, subsets, nqg, true);
+    if (!p.plan.groups) p = Packing(d, nc, workgroups, subsets, nqg, false);
+    p.plan.grid = min(p.plan.groups, n);
+    const double c = besides + p.plan.rounds * (nqg / subsets) * step;
+    if (c >= cost) return;
+    cost = c;
+    best = p.plan;
+  };
+  for (int subsets = 1; subsets <= nqg; ++subsets)
+    if (nqg % subsets == 0) consider(n, subsets, subsets > 1 ? 19.0 : 14.0, few ? (wide ? 1.95 : 1.75) : (wide ? 2.5 : 2.1));
+  if (few) consider(2 * n, 1, 16.5, wide ? 3.1 : 2.5);
   return best;
 }
 
@@ -1287,8 +1355,11 @@ int launch(const maskkv_desc* d, const SweepParams& prm, hipStream_t stream) {
   const int lds_start = 2 * Cfg<D>::kKBytes;
   static bool raised = false;
   if (!raised) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&sweep_kernel<D>),
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&sweep_kernel<D, false>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, Cfg<D>::kLds);
+    if (e == hipSuccess)
+      e = hipFuncSetAttribute(reinterpret_cast<const void*>(&sweep_kernel<D, true>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                              Cfg<D>::kLds);
     if (e == hipSuccess)
       e = hipFuncSetAttribute(reinterpret_cast<const void*>(&sweep_start_kernel<D, 8>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, lds_start);
@@ -1308,7 +1379,10 @@ int launch(const maskkv_desc* d, const SweepParams& prm, hipStream_t stream) {
   else
     hipLaunchKernelGGL((sweep_start_kernel<D, 2>), dim3(units * 4 + 1), dim3(kThreads), lds_start, stream, prm);
   if (int e = check_launch("score (sweep start)")) return e;
-  hipLaunchKernelGGL(sweep_kernel<D>, dim3(prm.plan.groups), dim3(kThreads), Cfg<D>::kLds, stream, prm);
+  if (prm.plan.groups > prm.plan.grid)
+    hipLaunchKernelGGL((sweep_kernel<D, true>), dim3(prm.plan.grid), dim3(kThreads), Cfg<D>::kLds, stream, prm);
+  else
+    hipLaunchKernelGGL((sweep_kernel<D, false>), dim3(prm.plan.grid), dim3(kThreads), Cfg<D>::kLds, stream, prm);
   return check_launch("score (sweep)");
 }
 

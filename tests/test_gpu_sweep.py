@@ -95,9 +95,15 @@ def test_calls_on_two_streams_at_once():
     (128, 32, 11, 1, tuple(range(128, 8193, 128)), False),                  # more runs than a plan has room for
     (128, 100, 2, 7, (3000,), False), (128, 100, 2, 7, (3000,), True),      # three groups of rows: a workgroup each
     (128, 256, 3, 4, (5000, 300, 9000), False), (128, 256, 3, 4, (5000, 300, 9000), True),  # four: one workgroup for all or two
-    (64, 512, 32, 1, (4100, 2049), False), (64, 512, 32, 1, (4100, 2049), True)])
+    (64, 512, 32, 1, (4100, 2049), False), (64, 512, 32, 1, (4100, 2049), True),
+    # at most 128 rows: halves of workgroups, also in rounds that have no chunk for them, or in none
+    (128, 69, 32, 1, (1135, 3503, 1500, 2000, 2900, 2300, 1700, 1300), False), (128, 69, 32, 1, (1135, 3503, 1500), True),
+    (64, 100, 5, 1, (16500, 300), False), (64, 100, 5, 1, (16500, 300), True),
+    (128, 128, 16, 1, (12000,), False), (64, 18, 12, 7, (9001, 100, 5000), False), (128, 1, 16, 1, (12289, 1, 0, 129), False)])
 def test_rounds_of_heads_and_groups_of_rows(d, n, H, g, Ps, fallback):
     """Heads against float64 (fp32 sums of products of bf16 inputs: logits of up to 2^5 binary orders)."""
+    # One row's errors are not averaged with others': its logits of up to 2^5 binary orders are rounded (2^-20) once for every 16 products.
+    rtol = (32 if n > 1 else d) * 2.0 ** -24
     from paper_2510_09309_amd import bench_binding as bb
     m = hp.mk()
     gen = torch.Generator(device="cuda").manual_seed(5)
@@ -118,9 +124,9 @@ def test_rounds_of_heads_and_groups_of_rows(d, n, H, g, Ps, fallback):
             q = Q[b, h * g:(h + 1) * g].reshape(g * n, d).double()
             A = torch.softmax(q @ K[b, h, :P + n].double().T / d ** 0.5, dim=1)
             want = A[:, :P].sum(0)
-            assert torch.allclose(scores[b * H + h, :P].double(), want, rtol=32 * 2.0 ** -24, atol=0), (b, h)
+            assert torch.allclose(scores[b * H + h, :P].double(), want, rtol=rtol, atol=0), (b, h)
             assert torch.isnan(scores[b * H + h, P:]).all()
-            assert abs(float(mass[b * H + h]) - float(want.sum())) <= 32 * 2.0 ** -24 * float(want.sum()), (b, h)
+            assert abs(float(mass[b * H + h]) - float(want.sum())) <= rtol * float(want.sum()), (b, h)
 
 
 def swept(batch, ws):
