@@ -115,6 +115,7 @@ struct SweepParams {
   SweepPlan plan;
   struct Chunk* table;  // [groups][rounds] what a workgroup's chunks are, in turn
   int* counts;          // [groups] how many they are
+  int tables;           // workgroups of the start kernel that fill the table, a wave a head
   int rounds;
   int patience;     // how long a workgroup waits for the others' row sums, in ticks of the 100 MHz clock
   int spans;        // pieces of a unit's keys in the fallback's first pass
@@ -312,22 +313,38 @@ __device__ __forceinline__ void start_table(const SweepParams& prm, int b, int v
   }
 }
 
+// BLOCKS blocks of 32 rows a workgroup, and each block's response keys on 8 / BLOCKS waves: 2 where that gives every compute unit work.
+//
+// What bounds it: with few units the latency of its loads (issued at once: rows and two tiles of keys; 7 to 8 us with the rest of the
+// chain: launch, loads, logarithms, stores), with many the memory (96 MB in the ragged batch of perf/cases.py, 20 of 35 us) and
+// the exponentials (12 us), which all workgroups come to at the same time.  us there, 40.6 -> 35: the sweep's table written by
+// workgroups of their own instead of by a wave that the others wait for, tiles asked for before the rows' arrival instead of
+// after it, the packed rows stored after the last wait, masks only where the span ends.  8 sequences of 32 heads with 69 rows: 51 -> 48
+// for the whole call, 6 of 28 with 116 rows 36.4 -> 33.0.  Not better: units dealt to the XCDs by head, four blocks a workgroup (39).
 template <int D, int BLOCKS>
 __global__ __launch_bounds__(kThreads) void sweep_start_kernel(const SweepParams prm) {
   using C = Cfg<D>;
   constexpr int S = C::kSteps, SPLIT = kWaves / BLOCKS;
-  if (BLOCKS == 2 && blockIdx.x == gridDim.x - 1) {
-    start_lock(prm);
+  const int lane = threadIdx.x & 63, r = lane & 31, g = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if ((int)blockIdx.x <= prm.tables) {
+    if (blockIdx.x == 0) {
+      start_lock(prm);
+    } else {
+      const int head = ((int)blockIdx.x - 1) * kWaves + wave;
+      if (head < prm.B * prm.heads()) start_table(prm, head / prm.heads(), head % prm.heads());
+    }
     return;
   }
   extern __shared__ __attribute__((aligned(1024))) char lds[];  // two tiles of 128 keys
   __shared__ float2 part[kWaves][32];
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
-  const int lane = threadIdx.x & 63, r = lane & 31, g = lane >> 5;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int unit = blockIdx.x / SPLIT;
-  const int bh = unit / prm.nqg, vh = bh % prm.heads();
-  const int b = bh / prm.heads(), h = vh / prm.subsets;
+  const int block = (int)blockIdx.x - 1 - prm.tables;
+  const int unit = block / SPLIT;
+  // (a division is a chain of some twenty instructions before the first load)
+  const int bh = prm.nqg == 1 ? unit : unit / prm.nqg;
+  const int b = prm.B == 1 ? 0 : bh / prm.heads(), vh = bh - b * prm.heads();
+  const int h = prm.subsets == 1 ? vh : vh / prm.subsets;
   const int qg = (vh - h * prm.subsets) * prm.nqg + unit - bh * prm.nqg;
   const int P = prm.lens.P[b];
   const char* keys = prm.K.row(b, h, P);
@@ -344,39 +361,40 @@ __global__ __launch_bounds__(kThreads) void sweep_start_kernel(const SweepParams
     }
   };
   const int tiles = ceil_div(prm.n_resp, kKeys);
-  dma(0);
-  const int rb = (blockIdx.x % SPLIT) * BLOCKS + wave / SPLIT;  // block of 32 rows
+  const int rb = block % SPLIT * BLOCKS + wave / SPLIT;  // block of 32 rows
   const int part_of = wave % SPLIT;
   const int q0 = qg * prm.rows + rb * 32;
   u32x4 qf[S];
   const char* qrow = prm.Q.group_row(b, h, prm.q_per_kv, prm.n_qh, min(q0 + r, prm.n_query - 1)) + g * 16;
 #pragma unroll
-  for (int s = 0; s < S; ++s) qf[s] = *reinterpret_cast<const u32x4*>(qrow + s * 32);
+  for (int s = 0; s < S; ++s) asm volatile("global_load_dwordx4 %0, %1, off offset:%2" : "=v"(qf[s]) : "v"(qrow), "i"(s * 32));
+  dma(0);
+  if (tiles > 1) dma(1);
 
-  if (rb == 0 && part_of == 0 && lane == 0) {
-    prm.spans_done[unit] = 0;
-    if (P == 0 && prm.mass) prm.mass[bh] = 0.f;
-  }
-  if (blockIdx.x % SPLIT == SPLIT - 1 && wave == kWaves - 1 && unit == bh * prm.nqg) start_table(prm, b, vh);
   char* area = prm.units + (int64_t)unit * kUnitBytes<D>;
   uint64_t* sums = reinterpret_cast<uint64_t*>(area) + rb * 32;
-  if (part_of == 0) {
-    if (lane < 32) {
-#pragma unroll
-      for (int i = 1; i <= kCopies; ++i) sums[i * kRows + lane] = 0;  // (the last one is `high`)
-    }
-    for (int i = lane; i < ceil_div(P, kKeys); i += 64) prm.parts[((int64_t)unit * kWaves + rb) * prm.n_parts + i] = kNoPart;
-    u32x4* pack = reinterpret_cast<u32x4*>(area + kRowsAt + rb * C::kQBytes) + lane;
-#pragma unroll
-    for (int s = 0; s < S; ++s) pack[s * 64] = qf[s];
-  }
   float m = kNegBig, l = 0.f;
   for (int t = 0; t < tiles; ++t) {
-    if (t + 1 < tiles) dma(t + 1);  // (its tile was read two steps ago, before the last barrier)
     if (t + 1 < tiles)
       asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"i"(C::kMoves) : "memory");
     else
       asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+#pragma unroll
+    for (int s = 0; s < S; ++s) asm volatile("" : "+v"(qf[s]));
+    if (t + 1 == tiles && part_of == 0) {  // (stores before the last wait would be waited for)
+      if (lane < 32) {
+#pragma unroll
+        for (int i = 1; i <= kCopies; ++i) sums[i * kRows + lane] = 0;  // (the last one is `high`)
+      }
+      for (int i = lane; i < ceil_div(P, kKeys); i += 64) prm.parts[((int64_t)unit * kWaves + rb) * prm.n_parts + i] = kNoPart;
+      u32x4* pack = reinterpret_cast<u32x4*>(area + kRowsAt + rb * C::kQBytes) + lane;
+#pragma unroll
+      for (int s = 0; s < S; ++s) pack[s * 64] = qf[s];
+      if (rb == 0 && lane == 0) {
+        prm.spans_done[unit] = 0;
+        if (P == 0 && prm.mass) prm.mass[bh] = 0.f;
+      }
+    }
     for (int kb = part_of; kb < kNB; kb += SPLIT) {
       const int k0 = t * kKeys + kb * 32;
       if (k0 >= prm.n_resp) break;
@@ -386,20 +404,27 @@ __global__ __launch_bounds__(kThreads) void sweep_start_kernel(const SweepParams
         const u32x4 kf = *in_lds<const u32x4>(lds0 + (t & 1) * C::kKBytes + (kb * 32 + r) * C::kRowB + (((2 * s + g) ^ C::swz(r)) << 4));
         mfma_step<bf16_t>(kf, qf[s], a);
       }
-      float bm = kNegBig;
+      if (k0 + 32 > prm.n_resp)
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        if (k0 + 8 * (i / 4) + 4 * g + (i % 4) >= prm.n_resp) a[i] = -INFINITY;
-        bm = fmaxf(bm, a[i] * prm.c);
+        for (int i = 0; i < 16; ++i)
+          if (k0 + 8 * (i / 4) + 4 * g + (i % 4) >= prm.n_resp) a[i] = -INFINITY;
+      float top = a[0];
+#pragma unroll
+      for (int i = 1; i < 16; ++i) top = fmaxf(top, a[i]);
+      const float m_new = fmaxf(m, top * prm.c);
+      float s0 = 0.f, s1 = 0.f;
+#pragma unroll
+      for (int i = 0; i < 16; i += 2) {
+        s0 += fast_exp2(fmaf(a[i], prm.c, -m_new));
+        s1 += fast_exp2(fmaf(a[i + 1], prm.c, -m_new));
       }
-      const float m_new = fmaxf(m, bm);
-      float s = 0.f;
-#pragma unroll
-      for (int i = 0; i < 16; ++i) s += fast_exp2(fmaf(a[i], prm.c, -m_new));
-      l = l * fast_exp2(m - m_new) + s;
+      l = l * fast_exp2(m - m_new) + (s0 + s1);
       m = m_new;
     }
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    if (t + 2 < tiles) {
+      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      dma(t + 2);
+    }
   }
   {
     const float mo = xor32(m), lo = xor32(l);
@@ -433,7 +458,6 @@ __global__ __launch_bounds__(kThreads) void sweep_start_kernel(const SweepParams
     refs[32] = own;
     sums[lane] = (uint64_t)rintf(own * kLowScale);
   }
-  if (BLOCKS == 8 && blockIdx.x == 0) start_lock(prm);
 }
 
 // ---- fallback: the scores in two passes, as tasks that workgroups take by ticket, whatever their number.  A task is a
@@ -1375,9 +1399,9 @@ int launch(const maskkv_desc* d, const SweepParams& prm, hipStream_t stream) {
   }
   const int units = prm.B * prm.H * prm.subsets * prm.nqg;
   if (units >= 128)
-    hipLaunchKernelGGL((sweep_start_kernel<D, 8>), dim3(units), dim3(kThreads), lds_start, stream, prm);
+    hipLaunchKernelGGL((sweep_start_kernel<D, 8>), dim3(1 + prm.tables + units), dim3(kThreads), lds_start, stream, prm);
   else
-    hipLaunchKernelGGL((sweep_start_kernel<D, 2>), dim3(units * 4 + 1), dim3(kThreads), lds_start, stream, prm);
+    hipLaunchKernelGGL((sweep_start_kernel<D, 2>), dim3(1 + prm.tables + units * 4), dim3(kThreads), lds_start, stream, prm);
   if (int e = check_launch("score (sweep start)")) return e;
   if (prm.plan.groups > prm.plan.grid)
     hipLaunchKernelGGL((sweep_kernel<D, true>), dim3(prm.plan.grid), dim3(kThreads), Cfg<D>::kLds, stream, prm);
@@ -1434,6 +1458,7 @@ int launch_sweep(const maskkv_desc* d, const View& Q, const View& K, const Lens&
   prm.ctl = reinterpret_cast<Control*>(base + l.control);
   prm.table = reinterpret_cast<Chunk*>(base + l.table);
   prm.counts = reinterpret_cast<int*>(base + l.counts);
+  prm.tables = (d->B * d->H * plan.subsets + kWaves - 1) / kWaves;
   prm.rounds = plan.rounds;
   prm.spans_done = reinterpret_cast<int*>(base + l.done);
   prm.parts = reinterpret_cast<uint32_t*>(base + l.parts);
