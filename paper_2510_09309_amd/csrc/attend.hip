@@ -5,10 +5,11 @@
 // Flash-style single pass with an online softmax.  The logits are formed transposed (keys on the MFMA row axis, queries on
 // the column axis), so a lane owns one query: its running max / sum stay in the lane and the probabilities it holds are
 // already laid out as the B operand of O^T = V^T P^T.  The key axis is the concatenation of two segments (packed cache rows,
-// then a strided view); long key axes are split across workgroups and merged by a second small kernel.
+// then a strided view; the narrow bf16 kernel takes the view first); long key axes are split across workgroups and merged by a
+// second small kernel.
 //
 // Here: the tiled kernel for fp32 (8 waves = 256 queries of one (b, h) sharing every staged K/V tile, V written to LDS
-// transposed so that the A operand of the second product is read with 16-byte LDS loads), the narrow kernel for small bf16
+// transposed so that the A operand of the second product is read with 16-byte LDS loads), the narrow kernels for small
 // launches, the merge and the rules that choose.  attend_tiles.hip: the tiled kernel for bf16.
 #include "attend.hpp"
 #include "lds.hpp"
@@ -267,40 +268,36 @@ __global__ __launch_bounds__((AttCfg<D>::kThreads)) void attend_kernel(const Att
 
 // ---------------------------------------------------------------------------------------------
 // Narrow launches (few heads x query tiles): a tiled kernel would occupy a fraction of the compute units with one long serial
-// chain of tiles each.  Here a workgroup serves 32 queries and its four waves split the key axis: wave w takes the 32-key
-// blocks w, w+4, ... on its own - K fragments straight from global memory into registers, V (bf16) by direct transfers into
-// wave-private LDS, read with transposing loads, or (fp32) through a wave-private transposed LDS tile, no workgroup barrier
-// in the loop - and the four partial (O, m, l) are merged through LDS at the end.  Every XCD (workgroup numbers that are
-// congruent modulo 8) takes one run of (head, query tile) pairs, so that a head's K/V rows are fetched into one or two L2s
-// and four heads still reach all eight XCDs (4 heads x 1792 queries: 23.7 us with a head on one XCD, 12.6 spread).
-// What bounds it is latency: 32 heads x 256 queries x 512 keys take 10.3 us, about 5 of them until the first block is there (11.8
-// with V transposed by vector instructions on its way through registers).  Two blocks per wave are in flight; three or four
-// 11.0 and 11.7, eight waves with one or two blocks each 11.8.
-constexpr int kNarrowVS = 36;      // fp32: elements per transposed-V row: 32 keys + padding
+// chain of tiles each.  Here a workgroup serves 32 queries and its waves split the key axis: wave w of n takes the 32-key
+// blocks w, w + n, ... on its own, no workgroup barrier in the loop, and the partial (O, m, l) are merged through LDS at the
+// end.  Every XCD (workgroup numbers that are congruent modulo 8) takes one run of (head, query tile) pairs, so that a head's K/V
+// rows are fetched into one or two L2s and four heads still reach all eight XCDs (4 heads x 1792 queries: 23.7 us with a head on
+// one XCD, 12.6 spread).
+//
+// fp32: four waves, K fragments from global memory into registers, V through a wave-private transposed LDS tile, two blocks in flight.
+constexpr int kNarrowVS = 36;      // elements per transposed-V row: 32 keys + padding
 constexpr int kNarrowShift = 16;   // bytes by which every group of 32 rows is shifted further
 
-// NW waves per workgroup split the key axis.
-template <typename T, int D, int NW>
+template <int D>
 struct NarrowCfg {
-  static constexpr int kEB = (int)sizeof(T);
-  static constexpr int kThreads = 64 * NW;
+  static constexpr int kWaves = 4;  // that split the key axis
+  static constexpr int kEB = 4;
+  static constexpr int kThreads = 64 * kWaves;
   static constexpr int kRowB = D * kEB;
   static constexpr int kSteps = kRowB / 32;
   static constexpr int kPPR = kRowB / 16;        // 16-byte pieces per row
   static constexpr int kVP = 32 * kPPR / 64;     // V pieces per lane per block
   static constexpr int kDB = D / 32;
   static constexpr int kSets = kRowB <= 256 ? 2 : 1;  // blocks a wave keeps in flight (512-byte rows: registers for one)
-  static constexpr int kVBlock = 32 * kRowB;     // bf16: a block of V as it comes, two per wave
-  static constexpr int kRPI = 1024 / kRowB;      // rows moved by one transfer
-  static constexpr int kVtBytes = kEB == 2 ? kSets * kVBlock : D * kNarrowVS * kEB + (D / 32) * kNarrowShift;  // per wave
-  static constexpr int kMergeBytes = NW * kDB * 16 * 64 * 4;        // partial O of the waves
-  static constexpr int kLds = (kMergeBytes > NW * kVtBytes ? kMergeBytes : NW * kVtBytes) + NW * 32 * 8;
+  static constexpr int kVtBytes = D * kNarrowVS * kEB + (D / 32) * kNarrowShift;  // per wave
+  static constexpr int kMergeBytes = kWaves * kDB * 16 * 64 * 4;                   // partial O of the waves
+  static constexpr int kLds = (kMergeBytes > kWaves * kVtBytes ? kMergeBytes : kWaves * kVtBytes) + kWaves * 32 * 8;
 };
 
-template <typename T, int D, int NW>
-__global__ __launch_bounds__((NarrowCfg<T, D, NW>::kThreads)) void attend_narrow_kernel(const AttendParams prm) {
-  using C = NarrowCfg<T, D, NW>;
-  constexpr bool kPairs = sizeof(T) == 2;
+template <int D>
+__global__ __launch_bounds__(NarrowCfg<D>::kThreads) void attend_narrow_kernel(const AttendParams prm) {
+  using C = NarrowCfg<D>;
+  constexpr int NW = C::kWaves;
   extern __shared__ __attribute__((aligned(16))) char smem[];
 
   const int nqt = (prm.n_q + 31) / 32;
@@ -327,32 +324,13 @@ __global__ __launch_bounds__((NarrowCfg<T, D, NW>::kThreads)) void attend_narrow
   auto key_row = [&](const char* packed, const View& rest, int j) -> const char* {
     return j < len_a ? packed + (int64_t)j * C::kRowB : rest.row(b, h, j - len_a);
   };
-  // Ask for block blk: K in MFMA fragment layout (lane = key row); V in fp32 as row pieces for the transposition, in bf16 by
-  // direct transfers into slot `set` of this wave, ahead of the K loads, so that V is there when K is.  Rows past the
-  // end of the key axis re-read its last row and are masked.
-  const uint32_t lds_v = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem + wave * C::kVtBytes;
-  auto request = [&](int blk, u32x4 (&kf)[C::kSteps], u32x4 (&vr)[C::kVP], int set) {
-    if constexpr (kPairs) {
-      const int first = blk * 32, mrow = lane / C::kPPR;
-      const uint32_t piece = ((uint32_t)lane % C::kPPR ^ v_swizzle<D>(mrow) << 1) << 4;
-      const uint32_t to = lds_v + set * C::kVBlock;
-      if (first + 32 <= Lk && (first >= len_a || first + 32 <= len_a)) {
-        const bool in_a = first < len_a;
-        const int64_t st = in_a ? C::kRowB : prm.V2.stride_t;
-        const char* base = in_a ? a_v + (int64_t)first * C::kRowB : prm.V2.row(b, h, first - len_a);
+  // Ask for block blk: K in MFMA fragment layout (lane = key row), V as row pieces for the transposition.  Rows past the end of the
+  // key axis re-read its last row and are masked.
+  auto request = [&](int blk, u32x4 (&kf)[C::kSteps], u32x4 (&vr)[C::kVP]) {
 #pragma unroll
-        for (int i = 0; i < 32 / C::kRPI; ++i) dma16(base + i * C::kRPI * st, mrow * (uint32_t)st + piece, to + i * 1024);
-      } else {
-#pragma unroll
-        for (int i = 0; i < 32 / C::kRPI; ++i)
-          dma16_from(key_row(a_v, prm.V2, min(first + i * C::kRPI + mrow, Lk - 1)) + piece, to + i * 1024);
-      }
-    } else {
-#pragma unroll
-      for (int i = 0; i < C::kVP; ++i) {
-        const int p = lane + i * 64;
-        vr[i] = *reinterpret_cast<const u32x4*>(key_row(a_v, prm.V2, min(blk * 32 + p / C::kPPR, Lk - 1)) + p % C::kPPR * 16);
-      }
+    for (int i = 0; i < C::kVP; ++i) {
+      const int p = lane + i * 64;
+      vr[i] = *reinterpret_cast<const u32x4*>(key_row(a_v, prm.V2, min(blk * 32 + p / C::kPPR, Lk - 1)) + p % C::kPPR * 16);
     }
     const char* krow = key_row(a_k, prm.K2, min(blk * 32 + r, Lk - 1)) + g * 16;
 #pragma unroll
@@ -361,8 +339,8 @@ __global__ __launch_bounds__((NarrowCfg<T, D, NW>::kThreads)) void attend_narrow
 
   // the first blocks of this wave are asked for before anything else: their latency covers the query loads
   u32x4 kfa[C::kSteps], vra[C::kVP], kfb[C::kSteps], vrb[C::kVP];
-  if (wave < nblk) request(wave, kfa, vra, 0);
-  if (C::kSets == 2 && wave + NW < nblk) request(wave + NW, kfb, vrb, 1);
+  if (wave < nblk) request(wave, kfa, vra);
+  if (C::kSets == 2 && wave + NW < nblk) request(wave + NW, kfb, vrb);
 
   const int q = qt * 32 + r;
   u32x4 qf[C::kSteps];
@@ -377,33 +355,25 @@ __global__ __launch_bounds__((NarrowCfg<T, D, NW>::kThreads)) void attend_narrow
   float m = kNegBig, l = 0.f;
   const float c = prm.c;
   uint32_t* vt32 = reinterpret_cast<uint32_t*>(smem + wave * C::kVtBytes);
-  uint32_t va[C::kDB];  // bf16: this lane's transposing reads of a V block
-#pragma unroll
-  for (int db = 0; db < C::kDB; ++db) va[db] = lds_v + v_read_offset<D>(lane, db);
 
-  auto step = [&](int blk, u32x4 (&kf)[C::kSteps], u32x4 (&vr)[C::kVP], int set) {
-    // fp32: V^T of the block into this wave's LDS tile.  The tile is private to the wave; the fences order this block's
+  auto step = [&](int blk, u32x4 (&kf)[C::kSteps], u32x4 (&vr)[C::kVP]) {
+    // V^T of the block into this wave's LDS tile.  The tile is private to the wave; the fences order this block's
     // stores after the previous block's fragment loads and before this block's.
-    if constexpr (!kPairs) {
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 #pragma unroll
-      for (int i = 0; i < C::kVP; ++i) {
-        const int p = lane + i * 64, row = p / C::kPPR, col = p % C::kPPR;
+    for (int i = 0; i < C::kVP; ++i) {
+      const int p = lane + i * 64, row = p / C::kPPR, col = p % C::kPPR;
 #pragma unroll
-        for (int w = 0; w < 4; ++w) vt32[(col * 4 + w) * kNarrowVS + (col / 8) * (kNarrowShift / 4) + row] = vr[i][w];
-      }
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
+      for (int w = 0; w < 4; ++w) vt32[(col * 4 + w) * kNarrowVS + (col / 8) * (kNarrowShift / 4) + row] = vr[i][w];
     }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
     // S^T = K Q^T: keys on rows, queries on columns
     f32x16 s = f32x16{};
 #pragma unroll
-    for (int st = 0; st < C::kSteps; ++st) mfma_step<T>(kf[st], qf[st], s);
-    if constexpr (kPairs)
-      asm volatile("" : "+v"(s) : : "memory");  // K has been waited for, and so has V: its reads stay below
-    else if (blk + C::kSets * NW < nblk)
-      request(blk + C::kSets * NW, kf, vr, set);
+    for (int st = 0; st < C::kSteps; ++st) mfma_step<float>(kf[st], qf[st], s);
+    if (blk + C::kSets * NW < nblk) request(blk + C::kSets * NW, kf, vr);
     const int nvalid = Lk - blk * 32;
     if (nvalid < 32) {
 #pragma unroll
@@ -437,43 +407,18 @@ __global__ __launch_bounds__((NarrowCfg<T, D, NW>::kThreads)) void attend_narrow
     l += psum;
     // O^T += V^T P^T
     const char* vt = reinterpret_cast<const char*>(vt32);
-    if constexpr (kPairs) {
 #pragma unroll
-      for (int tp = 0; tp < 2; ++tp) {
-        u32x4 pf;
+    for (int qd = 0; qd < 4; ++qd) {
+      const u32x4 pf = {as_u32(s[4 * qd]), as_u32(s[4 * qd + 1]), as_u32(s[4 * qd + 2]), as_u32(s[4 * qd + 3])};
 #pragma unroll
-        for (int w = 0; w < 4; ++w) pf[w] = pack_bf16x2(s[8 * tp + 2 * w], s[8 * tp + 2 * w + 1]);
-#pragma unroll
-        for (int db = 0; db < C::kDB; ++db) {
-          const int imm = 16 * tp * C::kRowB;
-          const u32x2 lo = read_transposed(va[db] + set * C::kVBlock, imm), hi = read_transposed(va[db] + set * C::kVBlock, imm + 8 * C::kRowB);
-          const u32x4 vf = {lo[0], lo[1], hi[0], hi[1]};
-          mfma_step<T>(vf, pf, o[db]);
-        }
-      }
-      if (blk + C::kSets * NW < nblk) {
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the slot has been read
-        request(blk + C::kSets * NW, kf, vr, set);
-      }
-    } else {
-#pragma unroll
-      for (int qd = 0; qd < 4; ++qd) {
-        u32x4 pf;
-#pragma unroll
-        for (int w = 0; w < 4; ++w) {
-          const float pv = s[4 * qd + w];
-          pf[w] = as_u32(pv);
-        }
-#pragma unroll
-        for (int db = 0; db < C::kDB; ++db)
-          mfma_step<T>(*reinterpret_cast<const u32x4*>(vt + ((db * 32 + r) * kNarrowVS + 8 * qd + 4 * g) * 4 + db * kNarrowShift), pf, o[db]);
-      }
+      for (int db = 0; db < C::kDB; ++db)
+        mfma_step<float>(*reinterpret_cast<const u32x4*>(vt + ((db * 32 + r) * kNarrowVS + 8 * qd + 4 * g) * 4 + db * kNarrowShift), pf, o[db]);
     }
   };
 
   for (int blk = wave; blk < nblk; blk += C::kSets * NW) {
-    step(blk, kfa, vra, 0);
-    if (C::kSets == 2 && blk + NW < nblk) step(blk + NW, kfb, vrb, 1);
+    step(blk, kfa, vra);
+    if (C::kSets == 2 && blk + NW < nblk) step(blk + NW, kfb, vrb);
   }
 
   // ---- merge the waves' partial results through LDS (the V tiles are no longer needed)
@@ -513,16 +458,257 @@ __global__ __launch_bounds__((NarrowCfg<T, D, NW>::kThreads)) void attend_narrow
       v[e] = acc * inv;
     }
     char* to = orow + (db * 32 + 8 * qd + 4 * g) * C::kEB;
-    if constexpr (kPairs) {
-      u32x2 wout;
-      wout[0] = pack_bf16x2(v[0], v[1]);
-      wout[1] = pack_bf16x2(v[2], v[3]);
-      *reinterpret_cast<u32x2*>(to) = wout;
-    } else {
-      *reinterpret_cast<float4*>(to) = make_float4(v[0], v[1], v[2], v[3]);
-    }
+    *reinterpret_cast<float4*>(to) = make_float4(v[0], v[1], v[2], v[3]);
   }
   if (prm.lse && wave == 0 && g == 0) prm.lse[(int64_t)bh * prm.n_q + q] = (M + __log2f(L)) * kLn2;
+}
+
+typedef __attribute__((ext_vector_type(2))) float f32x2;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+
+// The same for bf16: eight waves, K, V and the queries by direct transfers into LDS (a load of K fragments touches 32 rows for
+// 1 KiB), V read with transposing loads.  A wave has one block in flight: the next K is asked for once the logits are formed, the
+// next V once the block is added, and each is waited for on its own (the compiler, which does not see the transfers, would wait
+// for later ones as well).  The key axis begins with the response segment, whose blocks are asked for before the head's budget is known.
+// The partial results are merged by rows, so that 16 threads write a row in whole pieces.
+//
+// What bounds it: the latency of each round of blocks, 1.5 us for loads at about the rate of L2 and the arithmetic of two waves a SIMD;
+// 32 heads x 256 queries x 512 keys take 9.3 us: 1.8 for an empty launch, 2.1 until the first blocks are there, 1.0 and 1.5 per
+// round, 1.2 for the merge.  Before, four waves with K straight into registers and two blocks in flight 10.9 (13.7 against 9.3 in a
+// layer over 4k tokens, where K and V are not in L2); four waves with K by transfers 11.5, the merge with each lane writing the 8 bytes
+// of its accumulators 10.2.
+template <int D>
+struct PairsCfg {
+  static constexpr int kWaves = 8, kThreads = 64 * kWaves;
+  static constexpr int kRowB = 2 * D;
+  static constexpr int kSteps = kRowB / 32;
+  static constexpr int kPPR = kRowB / 16;        // 16-byte pieces per row
+  static constexpr int kRPI = 1024 / kRowB;      // rows moved by one transfer
+  static constexpr int kMoves = 32 / kRPI;       // transfers of a block
+  static constexpr int kDB = D / 32;
+  static constexpr int kBlock = 32 * kRowB;
+  static constexpr int kWaveB = 2 * kBlock;      // K and V of a wave's block; at the end its partial O
+  static constexpr int kOffQ = kWaves * kWaveB;
+  static constexpr int kOffMl = kOffQ + kBlock;  // [wave][query] (m, l)
+  static constexpr int kLds = kOffMl + kWaves * 32 * 8;
+  // Piece p of row r of K or Q is in slot p ^ swz(r): the fragments of 16 consecutive rows are on different banks.
+  static __device__ constexpr uint32_t swz(uint32_t row) { return D == 128 ? row & 15 : (row >> 1) & 7; }
+};
+
+template <int D>
+__global__ __launch_bounds__(PairsCfg<D>::kThreads) void attend_pairs_kernel(const AttendParams prm) {
+  using C = PairsCfg<D>;
+  constexpr int S = C::kSteps, M = C::kMoves;
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
+
+  const int nqt = (prm.n_q + 31) / 32;
+  // eight runs of consecutive (head, query tile) pairs, one per XCD
+  const int pair = (blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
+  const int bh = pair / nqt;
+  const int qt = pair - bh * nqt;
+  if (bh >= prm.BH) return;
+  const int b = bh / prm.H;
+  const int h = bh - b * prm.H;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int r = lane & 31;
+  const int g = lane >> 5;
+  const auto cu = (const __attribute__((address_space(4))) int32_t*)(prm.cu + bh);
+  const int64_t cu0 = cu[0], cu1 = cu[1];
+
+  // Rows past the end of a segment re-read its last row and are masked.
+  const uint32_t mrow = (uint32_t)lane / C::kPPR, slot = (uint32_t)lane % C::kPPR;
+  const uint32_t vpiece = (slot ^ v_swizzle<D>(mrow) << 1) << 4;
+  const uint32_t own = lds0 + wave * C::kWaveB;
+  auto move = [&](const char* base, uint32_t st, int last, bool k, uint32_t to) {
+    auto piece = [&](int i) { return k ? (slot ^ C::swz(mrow) ^ C::swz(i * C::kRPI)) << 4 : vpiece; };
+    if (last >= 31) {
+      const uint32_t off = mrow * st;
+#pragma unroll
+      for (int i = 0; i < M; ++i) dma16(base + (int64_t)(i * C::kRPI) * st, off + piece(i), to + i * 1024);
+    } else {
+#pragma unroll
+      for (int i = 0; i < M; ++i) dma16(base, (uint32_t)min(i * C::kRPI + (int)mrow, last) * st + piece(i), to + i * 1024);
+    }
+  };
+  const int nb2 = (prm.n_resp + 31) / 32;
+  const char *k2 = prm.K2.row(b, h, 0), *v2 = prm.V2.row(b, h, 0);
+  const uint32_t kst = (uint32_t)prm.K2.stride_t, vst = (uint32_t)prm.V2.stride_t;
+
+  // this wave's part of the queries, then its first blocks
+  {
+#pragma unroll
+    for (int j = wave; j < M; j += C::kWaves) {
+      const char* qrow = prm.Q.group_row(b, h, prm.q_per_kv, prm.n_resp, min(qt * 32 + j * C::kRPI + (int)mrow, prm.n_q - 1));
+      dma16_from(qrow + ((slot ^ C::swz(j * C::kRPI + mrow)) << 4), lds0 + C::kOffQ + j * 1024);
+    }
+  }
+  auto resp_k = [&](int t) { move(k2 + (int64_t)(t * 32) * kst, kst, prm.n_resp - 1 - t * 32, true, own); };
+  auto resp_v = [&](int t) { move(v2 + (int64_t)(t * 32) * vst, vst, prm.n_resp - 1 - t * 32, false, own + C::kBlock); };
+  if (wave < nb2) {
+    resp_k(wave);
+    resp_v(wave);
+  }
+  const int64_t c0 = min(cu0, prm.capacity);
+  const int len_a = (int)(min(cu1, prm.capacity) - c0);
+  const char *a_k = prm.Kc + c0 * C::kRowB, *a_v = prm.Vc + c0 * C::kRowB;
+  const int nblk = nb2 + (len_a + 31) / 32;
+  auto ask_k = [&](int t) {
+    if (t < nb2)
+      resp_k(t);
+    else
+      move(a_k + (int64_t)((t - nb2) * 32) * C::kRowB, C::kRowB, len_a - 1 - (t - nb2) * 32, true, own);
+  };
+  auto ask_v = [&](int t) {
+    if (t < nb2)
+      resp_v(t);
+    else
+      move(a_v + (int64_t)((t - nb2) * 32) * C::kRowB, C::kRowB, len_a - 1 - (t - nb2) * 32, false, own + C::kBlock);
+  };
+  if (wave >= nb2 && wave < nblk) {
+    ask_k(wave);
+    ask_v(wave);
+  }
+  // the queries are there: only the block may be on its way
+  if (wave < nblk)
+    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"i"(2 * M) : "memory");
+  else
+    asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+  uint32_t fa[S];  // this lane's pieces of row r
+  u32x4 qf[S];
+#pragma unroll
+  for (int s = 0; s < S; ++s) {
+    fa[s] = r * C::kRowB + (((2 * s + g) ^ C::swz(r)) << 4);
+    qf[s] = *in_lds<const u32x4>(lds0 + C::kOffQ + fa[s]);
+    fa[s] += own;
+  }
+  uint32_t va[C::kDB];  // this lane's transposing reads of a V block
+#pragma unroll
+  for (int db = 0; db < C::kDB; ++db) va[db] = own + C::kBlock + v_read_offset<D>(lane, db);
+
+  f32x16 o[C::kDB];
+#pragma unroll
+  for (int db = 0; db < C::kDB; ++db) o[db] = f32x16{};
+  float m = kNegBig, l = 0.f;
+  const float c = prm.c;
+  for (int t = wave; t < nblk; t += C::kWaves) {
+    const bool more = t + C::kWaves < nblk;
+    asm volatile("s_waitcnt vmcnt(%0)" ::"i"(M) : "memory");  // K is there, V may be on its way
+    // S^T = K Q^T: keys on rows, queries on columns
+    f32x16 s = f32x16{};
+#pragma unroll
+    for (int st = 0; st < S; ++st) {
+      const u32x4 kf = *in_lds<const u32x4>(fa[st]);
+      mfma_step<bf16_t>(kf, qf[st], s);
+    }
+    asm volatile("" : "+v"(s) : : "memory");  // (the slot has been read)
+    if (more) ask_k(t + C::kWaves);
+    const int valid = t < nb2 ? prm.n_resp - t * 32 : len_a - (t - nb2) * 32;
+    if (valid < 32) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        if (8 * (i / 4) + 4 * g + (i % 4) >= valid) s[i] = -INFINITY;
+    }
+    // online softmax; lanes l and l^32 hold the same query
+    float bm = s[0];
+#pragma unroll
+    for (int i = 1; i < 16; ++i) bm = fmaxf(bm, s[i]);
+    bm = fmaxf(bm, xor32(bm));
+    const float cand = bm * c;
+    const bool bump = cand > m + kLazyBump;  // the reference is raised lazily, as in the tiled kernel
+    if (__any(bump)) {
+      const float m_new = bump ? cand : m;
+      const float alpha = fast_exp2(m - m_new);
+      m = m_new;
+      l *= alpha;
+#pragma unroll
+      for (int db = 0; db < C::kDB; ++db)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) o[db][i] *= alpha;
+    }
+    float psum = 0.f;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const float pv = fast_exp2(fmaf(s[i], c, -m));
+      s[i] = pv;
+      psum += pv;
+    }
+    l += psum;
+    if (more)
+      asm volatile("s_waitcnt vmcnt(%0)" ::"i"(M) : "memory");
+    else
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (valid < 32) {  // (rows that do not exist: zero times an infinity of the row that was read instead is no zero)
+      for (int i = valid * C::kPPR + lane; i < 32 * C::kPPR; i += 64) *in_lds<u32x4>(own + i * 16, C::kBlock) = u32x4{0u, 0u, 0u, 0u};
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    }
+    // O^T += V^T P^T
+#pragma unroll
+    for (int tp = 0; tp < 2; ++tp) {
+      u32x4 pf;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) pf[w] = pack_bf16x2(s[8 * tp + 2 * w], s[8 * tp + 2 * w + 1]);
+#pragma unroll
+      for (int db = 0; db < C::kDB; ++db) {
+        const int imm = 16 * tp * C::kRowB;
+        const u32x2 lo = read_transposed(va[db], imm), hi = read_transposed(va[db], imm + 8 * C::kRowB);
+        const u32x4 vf = {lo[0], lo[1], hi[0], hi[1]};
+        mfma_step<bf16_t>(vf, pf, o[db]);
+      }
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the slot has been read
+    if (more) ask_v(t + C::kWaves);
+  }
+
+  // ---- the waves' partial results, each in its wave's own LDS: four elements of O^T at a time, group k = d / 8 of a query and half
+  // g = d / 4 % 2 in slot (query + 32 g) ^ mix(k, g) of 64, so that a row's pieces, which its threads read next, are on different banks
+  constexpr int kPieces = D / 64;  // of four elements a thread, side by side
+  auto mix = [](int k, int g) { return D == 128 ? k : k ^ g << 3; };
+  const float l_tot = l + xor32(l);
+#pragma unroll
+  for (int k = 0; k < D / 8; ++k)
+    *in_lds<f32x4>(own + ((lane ^ mix(k, g)) << 4), k * 1024) = f32x4{o[k / 4][k % 4 * 4], o[k / 4][k % 4 * 4 + 1], o[k / 4][k % 4 * 4 + 2], o[k / 4][k % 4 * 4 + 3]};
+  if (g == 0) *in_lds<f32x2>(lds0 + C::kOffMl + (wave * 32 + r) * 8) = f32x2{m, l_tot};
+  __syncthreads();
+  const int row = (int)threadIdx.x / 16, p0 = (int)threadIdx.x % 16 * kPieces;  // (16 threads a row)
+  f32x2 ml[C::kWaves];
+  f32x4 part[kPieces][C::kWaves];
+#pragma unroll
+  for (int w = 0; w < C::kWaves; ++w) ml[w] = *in_lds<const f32x2>(lds0 + C::kOffMl + row * 8, w * 32 * 8);
+#pragma unroll
+  for (int i = 0; i < kPieces; ++i) {
+    const int k = (p0 + i) / 2, half = (p0 + i) % 2;
+    const uint32_t from = lds0 + k * 1024 + (((row + 32 * half) ^ mix(k, half)) << 4);
+#pragma unroll
+    for (int w = 0; w < C::kWaves; ++w) part[i][w] = *in_lds<const f32x4>(from, w * C::kWaveB);
+  }
+  float top = kNegBig, L = 0.f, wgt[C::kWaves];
+#pragma unroll
+  for (int w = 0; w < C::kWaves; ++w) top = fmaxf(top, ml[w][0]);
+#pragma unroll
+  for (int w = 0; w < C::kWaves; ++w) {
+    wgt[w] = fast_exp2(ml[w][0] - top);
+    L += wgt[w] * ml[w][1];
+  }
+  const int q = qt * 32 + row;
+  if (q >= prm.n_q) return;
+  const float inv = 1.f / L;
+  uint32_t out[2 * kPieces];
+#pragma unroll
+  for (int i = 0; i < kPieces; ++i) {
+    f32x4 v = wgt[0] * part[i][0];
+#pragma unroll
+    for (int w = 1; w < C::kWaves; ++w) v += wgt[w] * part[i][w];
+    out[2 * i] = pack_bf16x2(v[0] * inv, v[1] * inv);
+    out[2 * i + 1] = pack_bf16x2(v[2] * inv, v[3] * inv);
+  }
+  char* to = prm.O.group_row(b, h, prm.q_per_kv, prm.n_resp, q) + p0 * 8;
+  if constexpr (kPieces == 2)
+    *reinterpret_cast<u32x4*>(to) = u32x4{out[0], out[1], out[2], out[3]};
+  else
+    *reinterpret_cast<u32x2*>(to) = u32x2{out[0], out[1]};
+  if (prm.lse && p0 == 0) prm.lse[(int64_t)bh * prm.n_q + q] = (top + __log2f(L)) * kLn2;
 }
 
 // Merge the key splits of the query rows: O = sum_s w_s O_s / sum_s w_s l_s, w_s = 2^(m_s - max m).
@@ -624,35 +810,41 @@ int attend_splits(const maskkv_desc* d, bool full) {
   return (int)s;
 }
 
-// bf16: the narrow kernel is used where its workgroups of 32 queries are all resident at once and fast: one per compute unit
-// at head_dim 128, about two at 64 (measured, narrow against tiled, us a call without the tiled kernel's ordering: head_dim 128
-// and 256 queries, 32 heads 11.8 / 15.6, 64 heads 22.2 / 16; 32 heads x 512 queries x 1536 keys 43 / 28; 4 heads x 1792
-// queries 14 / 17; head_dim 64, 512 workgroups 9.5 / 10.2).
+// bf16: the narrow kernel's workgroups of 32 queries are all resident at one (head_dim 128) or two (64) a compute unit.  It is used
+// as far as that (half a round more at head_dim 64), and for up to two rounds at head_dim 128 where the key axis is short, as far as
+// the capacity of the packed rows tells: each workgroup reads all of its head's keys, the tiled kernel's share them among 128 or 256
+// queries (us a call, narrow against tiled.  head_dim 128, 256 workgroups: 512 keys 9.3 / 16.8, 3256 keys 33 / 51; 320 to
+// 512 workgroups: 32 heads x 280 queries x 536 keys 15.8 / 18.3, 64 x 256 x 512 15.4 / 17.2, 32 x 512 x 1024 22.1 / 23.0, 32 x 512 x
+// 1536 28.2 / 28.9, but 64 x 256 x 1756 38 / 34, 32 x 512 x 4512 75 / 66.  head_dim 64, 512 workgroups: 768 keys 10.6 / 15.3,
+// 3512 keys 30 / 42; 640: 2140 keys 26.8 / 29.3; 768: 1024 keys 17.1 / 18.0, 3768 keys 45.6 / 45.2; 1024: 768 keys 18.5 / 16.1.)
 // fp32: a round of narrow workgroups takes a quarter (head_dim 64) to a seventh (128) of a round of the tiled kernel's, whose eight
 // waves walk the whole key axis (32 heads x 256 queries x 512 keys: 16.8 / 75 and 29.5 / 143 us; 4 heads x 64 queries x 576 keys
 // 18.7 / 78.6), so it is taken up to four times as many rounds.
-bool attend_is_narrow(const maskkv_desc* d, bool full) {
+bool attend_is_narrow(const maskkv_desc* d, bool full, int64_t capacity) {
   if (full) return false;
   const int64_t n_q = (int64_t)d->n_resp * query_heads_per_kv(d), heads = (int64_t)d->B * d->H;
   const int64_t groups = (n_q + 31) / 32 * heads;
-  if (d->dtype == MASKKV_BF16) return groups <= (d->d == 128 ? kUnits : 9 * kUnits / 4);
+  if (d->dtype == MASKKV_BF16) {
+    if (d->d == 64) return groups <= 5 * kUnits / 2;
+    return groups <= kUnits || (groups <= 2 * kUnits && capacity / heads + d->n_resp <= 1280);
+  }
   const int64_t tiled = (n_q + AttCfg<128>::kQPerBlock - 1) / AttCfg<128>::kQPerBlock * heads;
   return groups <= 4 * kUnits * ((tiled + kUnits - 1) / kUnits);
 }
 
 // Heads are only put in order where not every workgroup of the tiled kernel starts at once.
-bool attend_is_ordered(const maskkv_desc* d, bool full) {
-  if (full || attend_is_narrow(d, full)) return false;
+bool attend_is_ordered(const maskkv_desc* d, bool full, int64_t capacity) {
+  if (full || attend_is_narrow(d, full, capacity)) return false;
   const int per_block = tiled_queries(d, full);
   return ((int64_t)d->n_resp * query_heads_per_kv(d) + per_block - 1) / per_block * d->B * d->H > kUnits;
 }
 
-template <typename T, int D, int NW>
+template <int D>
 int launch_attend_narrow(const AttendParams& prm, hipStream_t stream) {
-  using C = NarrowCfg<T, D, NW>;
+  using C = NarrowCfg<D>;
   static bool raised = false;  // one-time opt-in to more than the default dynamic LDS size
   if (C::kLds > 48 * 1024 && !raised) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attend_narrow_kernel<T, D, NW>),
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attend_narrow_kernel<D>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, C::kLds);
     if (e != hipSuccess) {
       set_error("attend: cannot raise dynamic LDS limit: %s", hipGetErrorString(e));
@@ -663,7 +855,25 @@ int launch_attend_narrow(const AttendParams& prm, hipStream_t stream) {
   }
   const int nqt = (prm.n_q + 31) / 32;
   const int groups = (prm.BH * nqt + 7) / 8 * 8;
-  hipLaunchKernelGGL((attend_narrow_kernel<T, D, NW>), dim3(groups), dim3(C::kThreads), C::kLds, stream, prm);
+  hipLaunchKernelGGL((attend_narrow_kernel<D>), dim3(groups), dim3(C::kThreads), C::kLds, stream, prm);
+  return check_launch("attend (narrow)");
+}
+
+template <int D>
+int launch_attend_pairs(const AttendParams& prm, hipStream_t stream) {
+  using C = PairsCfg<D>;
+  static bool raised = false;  // one-time opt-in to more than the default dynamic LDS size
+  if (!raised) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attend_pairs_kernel<D>), hipFuncAttributeMaxDynamicSharedMemorySize, C::kLds);
+    if (e != hipSuccess) {
+      set_error("attend: cannot raise dynamic LDS limit: %s", hipGetErrorString(e));
+      (void)hipGetLastError();
+      return MASKKV_EHIP;
+    }
+    raised = true;
+  }
+  const int groups = (prm.BH * ((prm.n_q + 31) / 32) + 7) / 8 * 8;
+  hipLaunchKernelGGL((attend_pairs_kernel<D>), dim3(groups), dim3(C::kThreads), C::kLds, stream, prm);
   return check_launch("attend (narrow)");
 }
 
@@ -713,7 +923,7 @@ int launch_attend_t(const AttendParams& prm, int B, hipStream_t stream) {
 
 size_t attend_workspace_bytes(const maskkv_desc* d, bool full) {
   const int s = attend_splits(d, full);
-  if (!full) return attend_is_ordered(d, full) ? ((size_t)d->B * d->H * sizeof(int32_t) + 255) / 256 * 256 : 0;
+  if (!full) return attend_is_ordered(d, full, INT64_MAX) ? ((size_t)d->B * d->H * sizeof(int32_t) + 255) / 256 * 256 : 0;
   if (s == 1) return 0;
   const size_t rows = (size_t)d->B * d->H * s * d->n_resp * query_heads_per_kv(d);
   return (rows * d->d * sizeof(float) + 255) / 256 * 256 + rows * sizeof(float2);
@@ -741,7 +951,7 @@ int launch_attend(const maskkv_desc* d, const Lens& lens, bool full, const View&
   prm.n_splits = attend_splits(d, full);
   prm.c = scale * kLog2e;
   prm.lse = lse;
-  prm.order = attend_is_ordered(d, full) ? reinterpret_cast<const int32_t*>(workspace) : nullptr;
+  prm.order = attend_is_ordered(d, full, capacity) ? reinterpret_cast<const int32_t*>(workspace) : nullptr;
   prm.part_o = nullptr;
   prm.part_ml = nullptr;
   if (prm.n_splits > 1) {
@@ -750,10 +960,9 @@ int launch_attend(const maskkv_desc* d, const Lens& lens, bool full, const View&
     prm.part_ml = reinterpret_cast<float2*>(reinterpret_cast<char*>(workspace) +
                                             (rows * d->d * sizeof(float) + 255) / 256 * 256);
   }
-  if (attend_is_narrow(d, full)) {  // (eight waves per 32-query tile measured slower: 20.6 vs 17.6 us at the 32k prompt)
-    if (d->dtype == MASKKV_BF16)
-      return d->d == 128 ? launch_attend_narrow<bf16_t, 128, 4>(prm, stream) : launch_attend_narrow<bf16_t, 64, 4>(prm, stream);
-    return d->d == 128 ? launch_attend_narrow<float, 128, 4>(prm, stream) : launch_attend_narrow<float, 64, 4>(prm, stream);
+  if (attend_is_narrow(d, full, capacity)) {
+    if (d->dtype == MASKKV_BF16) return d->d == 128 ? launch_attend_pairs<128>(prm, stream) : launch_attend_pairs<64>(prm, stream);
+    return d->d == 128 ? launch_attend_narrow<128>(prm, stream) : launch_attend_narrow<64>(prm, stream);
   }
   if (d->dtype == MASKKV_BF16)
     return d->d == 128 ? launch_attend_t<bf16_t, 128>(prm, d->B, stream) : launch_attend_t<bf16_t, 64>(prm, d->B, stream);

@@ -35,7 +35,7 @@ struct View {
   // Query row r of key/value head h when g query heads of n_per rows each share that head:
   // rows [gi*n_per, (gi+1)*n_per) are query head h*g + gi.
   __device__ __forceinline__ char* group_row(int b, int h, int g, int n_per, int r) const {
-    const int gi = r / n_per;
+    const int gi = g == 1 ? 0 : r / n_per;
     return row(b, h * g + gi, r - gi * n_per);
   }
 };
