@@ -52,7 +52,12 @@ struct SelectParams {
 __device__ __forceinline__ uint32_t order_key(float v) {
   uint32_t u = __builtin_bit_cast(uint32_t, v);
   if (u == 0x80000000u) u = 0u;                         // -0 and +0 compare equal: one key for both
-  return u ^ ((u >> 31) ? 0xFFFFFFFFu : 0x80000000u);  // larger float <=> larger unsigned key
+  return u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);  // larger float <=> larger unsigned key
+}
+// The same of a value that is no zero.
+__device__ __forceinline__ uint32_t order_key_nonzero(float v) {
+  const uint32_t u = __builtin_bit_cast(uint32_t, v);
+  return u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
 }
 
 // Wave-level scans and reductions on the data-parallel-primitive path of the vector ALU (row shifts inside the
@@ -180,19 +185,20 @@ __device__ __forceinline__ uint64_t exact_cut(SelShared<THREADS>& s, uint32_t lo
   Range g{lo, hi, k, n};
   refine(s, g, kRankable, [&](auto&& f) { each([&](uint32_t key, uint32_t, bool valid) { f(key, valid); }); });
   if (g.krem == g.pop) return (uint64_t)g.lo << 32;  // the whole bin is kept
-  uint64_t from = (uint64_t)g.lo << 32, to = (uint64_t)g.hi << 32 | 0xFFFFFFFFu;
+  const uint32_t key_from = g.lo, key_span = g.hi - g.lo;
+  uint32_t last = 0xFFFFFFFFu, first = 0u;  // ~position
   if (g.pop > kRankable) {  // one key, many entries: refine over their positions (lowest first: ~position descending)
     const uint32_t tau = g.lo;
     g.lo = ~last_pos;
     g.hi = 0xFFFFFFFFu;
     refine(s, g, kRankable, [&](auto&& f) { each([&](uint32_t key, uint32_t pos, bool valid) { f(~pos, valid && key == tau); }); });
-    from = (uint64_t)tau << 32 | g.lo;
-    to = (uint64_t)tau << 32 | g.hi;
-    if (g.krem == g.pop) return from;
+    if (g.krem == g.pop) return (uint64_t)tau << 32 | g.lo;
+    first = g.lo;
+    last = g.hi;
   }
   each([&](uint32_t key, uint32_t pos, bool valid) {
-    const uint64_t code = code_of(key, pos);
-    if (valid && code >= from && code <= to) s.list[atomicAdd(&s.listed, 1)] = code;  // (g.pop <= kRankable of them)
+    if (valid & (key - key_from <= key_span) & (~pos >= first) & (~pos <= last))
+      s.list[atomicAdd(&s.listed, 1)] = code_of(key, pos);  // (g.pop <= kRankable of them)
   });
   __syncthreads();
   if (threadIdx.x < 64) {
@@ -219,6 +225,20 @@ __device__ __forceinline__ uint32_t pooled_key(const float* x, int j, int P, int
   }
   return order_key(v);
 }
+
+// x / w for a whole w of 1 .. 17, correctly rounded, given y = 1 / w correctly rounded: Markstein's correction of the product by its
+// exact remainder (the result equals the quotient for every significand of x and each of these w).  Three instructions instead of a
+// dozen; x has to be far from both ends of the exponents' range, so that neither step leaves it.
+__device__ __forceinline__ float divided(float x, float w, float y) {
+  const float q = x * y;
+  return fmaf(fmaf(-q, w, x), y, q);
+}
+// 1 / w for these w, correctly rounded: one Newton step from within a last place of it.
+__device__ __forceinline__ float inverse(float w) {
+  const float y = __builtin_amdgcn_rcpf(w);
+  return fmaf(fmaf(-w, y, 1.f), y, y);
+}
+constexpr uint32_t kDividableFrom = 67u << 23, kDividableTo = 187u << 23;  // bits of 2^-60 and 2^60
 
 // Keys of G groups of four consecutive positions, group i at j0 + i * step (0 for positions past the prompt).  A group's
 // windows overlap, so it is loaded as whole 16-byte pieces (R rounded up to a piece on either side), all groups before the
@@ -253,23 +273,55 @@ __device__ __forceinline__ void pool_groups(const float* x, int j0, int step, in
         v[i][t] = (j >= 0 && j < P) ? x[j] : neutral;
       }
     }
+    float acc[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const int j = g0 + e;
-      float acc;
       if (mode == MASKKV_POOL_MAX) {
-        acc = __builtin_nanf("");
+        acc[e] = __builtin_nanf("");
 #pragma unroll
         for (int t = -R; t <= R; ++t)
-          if (FIXED || (t >= -r && t <= r)) acc = fmaxf(acc, v[i][e + A + t]);
+          if (FIXED || (t >= -r && t <= r)) acc[e] = fmaxf(acc[e], v[i][e + A + t]);
       } else {
-        acc = 0.f;  // (0 + x is x but for the sign of a zero, which the key does not see)
+        acc[e] = 0.f;  // (0 + x is x but for the sign of a zero, which the key does not see)
 #pragma unroll
         for (int t = -R; t <= R; ++t)
-          if (FIXED || (t >= -r && t <= r)) acc = __fadd_rn(acc, v[i][e + A + t]);
-        if (R > 0) acc = __fdiv_rn(acc, (float)(min(P - 1, j + r) - max(0, j - r) + 1));
+          if (FIXED || (t >= -r && t <= r)) acc[e] = __fadd_rn(acc[e], v[i][e + A + t]);
       }
-      key[4 * i + e] = j < P ? order_key(acc) : 0u;
+    }
+    uint32_t least = 0u, most = 0xFFFFFFFFu;  // of the sums' magnitudes (a NaN or an infinity is above every number)
+    if (R > 0 && mode != MASKKV_POOL_MAX) {
+      uint32_t u[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) u[e] = __builtin_bit_cast(uint32_t, acc[e]) & 0x7FFFFFFFu;
+      least = min(min(u[0], u[1]), min(u[2], u[3]));
+      most = max(max(u[0], u[1]), max(u[2], u[3]));
+    }
+    if (least >= kDividableFrom && most <= kDividableTo) {
+      float w[4], y[4];
+      w[0] = (float)(2 * r + 1);
+      y[0] = inverse(w[0]);
+#pragma unroll
+      for (int e = 1; e < 4; ++e) {
+        w[e] = w[0];
+        y[e] = y[0];
+      }
+      if (!inner) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int j = g0 + e;  // (of a position past the prompt nothing is used)
+          w[e] = (float)max(min(P - 1, j + r) - max(0, j - r) + 1, 1);
+          y[e] = inverse(w[e]);
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) key[4 * i + e] = inner || g0 + e < P ? order_key_nonzero(divided(acc[e], w[e], y[e])) : 0u;
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int j = g0 + e;
+        if (R > 0 && mode != MASKKV_POOL_MAX) acc[e] = __fdiv_rn(acc[e], (float)(min(P - 1, j + r) - max(0, j - r) + 1));
+        key[4 * i + e] = j < P ? order_key(acc[e]) : 0u;
+      }
     }
   }
 }
@@ -321,8 +373,10 @@ __device__ __forceinline__ int take_base(const SelShared<THREADS>& s) {
 }
 
 // ---- one workgroup per head: grid (BH), 4 * G keys a thread.  32 heads of 4096 positions: 16.0 us before (keys in LDS, one
-// wave walking the histogram, refinement to a single key, two passes for the ordered output), 6.6 us now; 8192
-// positions 20.0 us before (two stages) and 8.5 now; 256 heads of 4096 ... 16384 positions 38 and 15 us.
+// wave walking the histogram, refinement to a single key, two passes for the ordered output), 6.3 us now; 8192
+// positions 20.0 us before (two stages) and 7.8 now (8.7 with a division per mean); 256 heads of 4096 ... 16384 positions 38
+// and 13.6 us (14.1).  Of the 13 thousand cycles at 4096 positions a third goes by until the keys are there, two thirds are the chain behind
+// them.  Not better: the list ranked by all waves, each comparing a few, and the kept entries as a mask of bits.
 template <int THREADS, int G>
 __global__ __launch_bounds__(THREADS) void select_head_kernel(const SelectParams prm) {
   __shared__ SelShared<THREADS> s;
@@ -342,13 +396,19 @@ __global__ __launch_bounds__(THREADS) void select_head_kernel(const SelectParams
   uint32_t kmin = 0xFFFFFFFFu, kmax = 0u;
   if (kh > 0) {
 #pragma unroll
-    for (int i = 0; i < G; ++i)
+    for (int i = 0; i < G; ++i) {
+      if (valid(i, 3)) {
+        kmin = min(kmin, min(min(key[4 * i], key[4 * i + 1]), min(key[4 * i + 2], key[4 * i + 3])));
+        kmax = max(kmax, max(max(key[4 * i], key[4 * i + 1]), max(key[4 * i + 2], key[4 * i + 3])));
+      } else {
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (valid(i, e)) {
-          kmin = min(kmin, key[4 * i + e]);
-          kmax = max(kmax, key[4 * i + e]);
-        }
+        for (int e = 0; e < 3; ++e)
+          if (valid(i, e)) {
+            kmin = min(kmin, key[4 * i + e]);
+            kmax = max(kmax, key[4 * i + e]);
+          }
+      }
+    }
   }
   uint32_t lo, hi;
   key_range(s, kmin, kmax, lo, hi);

@@ -43,6 +43,26 @@ def test_one_stage(P, window, mode):
         assert np.array_equal(keeps[h], ref), f"P {P} window {window} mode {mode} head {h} ({kinds[h // 4]})"
 
 
+@pytest.mark.parametrize("P", [9, 3000, 9001, 20000])
+@pytest.mark.parametrize("window", [5, 7, 11, 17])
+@pytest.mark.parametrize("scale", [1.0, 2.0 ** -59, 2.0 ** -62, 2.0 ** 56, 2.0 ** 59, 2.0 ** 120])
+def test_means_a_last_place_apart(P, window, scale):
+    """Means whose order hangs on the rounding of the quotient, on either side of what the product with the reciprocal is taken for."""
+    m = hp.mk()
+    rng = np.random.default_rng(P + window)
+    H = 6
+    sc = ((1 + rng.integers(0, 64, (H, P)) * 2.0 ** -23) * scale).astype(np.float32)
+    budgets = np.array([1, 2, P // 3, P // 2, min(P - 1, 900), P], dtype=np.int32)
+    cap = int(budgets.sum())
+    desc = m.Desc(B=1, H=H, d=64, dtype=m.MASKKV_BF16, n_resp=8, P_max=P)
+    idx, cu = torch.zeros(cap, dtype=torch.int32, device="cuda"), torch.zeros(H + 1, dtype=torch.int32, device="cuda")
+    m.maskkv_select(desc, torch.from_numpy(sc).to("cuda"), P, window, 0, torch.from_numpy(budgets).to("cuda"), idx, cu, cap,
+                    hp.workspace(max(1, m.maskkv_select_workspace_bytes(desc))))
+    keeps, _ = hp.split_idx(idx, cu)
+    for h in range(H):
+        assert np.array_equal(keeps[h], orc.select(orc.pool(sc[h], window, "mean", dtype=np.float32), int(budgets[h]))), h
+
+
 @pytest.mark.parametrize("H", [1, 32, 64, 65, 256, 300])
 def test_head_budgets_around_one_wave_of_heads(H):
     m = hp.mk()
