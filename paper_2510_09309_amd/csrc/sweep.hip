@@ -772,13 +772,16 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
   const uint32_t krow = (uint32_t)lane / C::kPPR, kpiece = ((uint32_t)lane % C::kPPR ^ C::swz(krow)) << 4;
   const uint32_t koff = (rb * kShare + krow) * kstride;  // (a chunk's rows are up to 127 x 16 MiB apart)
   // Chunk number t into its slot of the ring: this wave's part.  (Rows past the last key re-read it.)
-  auto dma_k = [&](int t) {
-    const Table c = table + min(t, chunks - 1);
-    const uint32_t most = (max(c->shape >> 16, 1u) - 1) * kstride;
+  auto dma_keys = [&](int t, uint32_t shape, const char* keys) {
+    const uint32_t most = (max(shape >> 16, 1u) - 1) * kstride;
     const uint32_t to = lds_ring + t % kSlots * C::kKBytes + rb * kShare * C::kRowB;
 #pragma unroll
     for (int j = 0; j < kMoves; ++j)
-      dma16(c->keys, min(here(koff) + (uint32_t)(j * C::kRPI) * kstride, most) + (here(kpiece) ^ (C::swz(j * C::kRPI) << 4)), to + j * 1024);
+      dma16(keys, min(here(koff) + (uint32_t)(j * C::kRPI) * kstride, most) + (here(kpiece) ^ (C::swz(j * C::kRPI) << 4)), to + j * 1024);
+  };
+  auto dma_k = [&](int t) {
+    const Table c = table + min(t, chunks - 1);
+    dma_keys(t, c->shape, c->keys);
   };
   const Base units = base_of(prm.units);
   auto dma_start = [&](const Task& k, int par) {
@@ -1052,23 +1055,42 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
   // (HALVES: the ring holds two chunks; a half without chunks asks for nothing)
   int fresh = 0;  // number of the chunk of `ahead`
   Task ahead{0, 0, 0, 0};
-  auto take = [&](int t) {
-    const Table c = table + t;
-    ahead.bh = c->bh;
-    ahead.shape = c->shape;
-    ahead.at = (uint32_t)(c->bh * prm.nqg) * kUnitBytes<D>;
+  auto take = [&](int bh, uint32_t shape) {
+    ahead.bh = bh;
+    ahead.shape = shape;
+    ahead.at = (uint32_t)(bh * prm.nqg) * kUnitBytes<D>;
   };
   auto advance = [&]() {  // `ahead` to the walk's next task (which at the end of the walk may be of its last chunk again)
     ahead.at += kUnitBytes<D>;
     if (++ahead.qg < prm.nqg) return;
     ahead.qg = 0;
-    take(min(++fresh, chunks - 1));
+    const Table c = table + min(++fresh, chunks - 1);
+    take(c->bh, c->shape);
   };
-  if (!HALVES || chunks > 0) take(0);
+  // The first of a single sequence's chunks is where the plan has it (run 0 has a chunk for every workgroup), which is known before the table
+  // is there; all that is asked for here is asked for before anything is waited for.  (One latency of a load that misses L2, of three: the
+  // lock's word, the table, keys and rows.  4 to 16 rounds, us a call: 16 heads x 89 rows x 9.7k keys 25.5 -> 24.1, x 203 x 28k 59.6 ->
+  // 58.5, 32 heads x 256 rows x 8k 37.2 -> 36.6, x 32k 115.5 -> 113.6, 4 heads x 1792 x 30k 89.8 -> 87.4.)
+  const int run = *(const __attribute__((address_space(4))) int*)&prm.ctl->run;
+  const int redo = *(const __attribute__((address_space(4))) int*)&prm.ctl->redo;
+  uint32_t shape0;
+  const char* keys0;
+  if (prm.B == 1) {
+    const int P = prm.lens.P[0], nc = (P + kKeys - 1) / kKeys, nth = team / nc, ci = team - nth * nc, vh = prm.plan.head(0) + nth;
+    take(vh, (uint32_t)ci | (uint32_t)(nc - 1) << 8 | (uint32_t)min(P - ci * kKeys, kKeys) << 16);
+    shape0 = ahead.shape;
+    keys0 = prm.K.row(0, prm.subsets == 1 ? vh : vh / prm.subsets, (int64_t)ci * kKeys);
+  } else {
+    take(table->bh, table->shape);
+    shape0 = table->shape;
+    keys0 = table->keys;
+  }
   Task cur = ahead, next = ahead, prev = ahead, done = ahead;
+  uint32_t shape2 = 0;
+  const char* keys2 = nullptr;
   if (!HALVES || chunks > 0) {
     dma_start(cur, 0);
-    dma_k(0);
+    dma_keys(0, shape0, keys0);
     aim_q(cur);
 #pragma unroll
     for (int ks = 0; ks < S; ++ks) load_q(ks);
@@ -1076,20 +1098,28 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
     next = ahead;
     dma_start(next, 1);
     dma_k(1);
+    advance();
+    const Table c = table + min(2, chunks - 1);
+    shape2 = c->shape;
+    keys2 = c->keys;
   }
+  if (run && threadIdx.x == 0)
+    __hip_atomic_fetch_add(&sweep_placed[blockIdx.x % kPlaces * kPlaceWords], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   if (threadIdx.x < 32) *in_lds<float>(lds0 + C::kOffInf + threadIdx.x * 4) = -INFINITY;
-  // (kOffBad and kOffLate; a workgroup that is placed when others have already given up goes straight to the fallback)
-  if (threadIdx.x < 3)
-    *in_lds<int>(lds0 + C::kOffBad + threadIdx.x * 4) =
-        threadIdx.x == 0 ? __hip_atomic_load(&prm.ctl->redo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+  // (kOffBad and kOffLate; a workgroup that is placed when others have already given up, or that may not run as a sweep's, goes straight to
+  // the fallback; what one wave has read of `redo` holds for all)
+  if (threadIdx.x < 3) *in_lds<int>(lds0 + C::kOffBad + threadIdx.x * 4) = threadIdx.x == 0 ? redo : 0;
   for (int i = threadIdx.x; i < 2 * kWaves * kKeys; i += kThreads) *in_lds<float>(lds0 + C::kOffCs + i * 4) = 0.f;
   if (threadIdx.x < 2 * kWaves) *in_lds<float>(lds0 + C::kOffMass + threadIdx.x * 4) = 0.f;
-  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  // (all but the second step's; that is waited for with the first step's sums)
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"i"(1 + kMoves) : "memory");
 #pragma unroll
   for (int ks = 0; ks < S; ++ks) asm volatile("" : "+v"(qf[ks]));
-  if (__builtin_amdgcn_readfirstlane(*in_lds<const int>(lds0 + C::kOffBad))) return;
-  if (!HALVES || chunks > 0) advance();
-  if (!HALVES) dma_k(2);
+  if (__builtin_amdgcn_readfirstlane(*in_lds<const int>(lds0 + C::kOffBad))) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (no transfer into LDS outlives its workgroup, or meets the fallback's)
+    return;
+  }
+  if (!HALVES) dma_keys(2, shape2, keys2);
   int keys_at = HALVES ? 2 : 3;  // number of the next chunk whose keys are asked for
   f32x16 pa[kNB], pb[kNB];
 #pragma unroll
@@ -1232,16 +1262,12 @@ template <int D, bool HALVES>
 __global__ __launch_bounds__(kThreads, 2) void sweep_kernel(const SweepParams prm) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
-  if (prm.ctl->run) {
-    if (threadIdx.x == 0)
-      __hip_atomic_fetch_add(&sweep_placed[blockIdx.x % kPlaces * kPlaceWords], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    sweep_chunks<D, HALVES>(prm, lds0);
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    const int late = __builtin_amdgcn_readfirstlane(*in_lds<const int>(lds0 + Cfg<D>::kOffLate));
-    const int late2 = HALVES ? __builtin_amdgcn_readfirstlane(*in_lds<const int>(lds0 + Cfg<D>::kOffLate, 4)) : 0;
-    if (__builtin_expect(late, 0)) late_masses<D>(argument_again(), lds0, late);
-    if (HALVES && __builtin_expect(late2, 0)) late_masses<D>(argument_again(), lds0, late2);
-  }
+  sweep_chunks<D, HALVES>(prm, lds0);
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  const int late = __builtin_amdgcn_readfirstlane(*in_lds<const int>(lds0 + Cfg<D>::kOffLate));
+  const int late2 = HALVES ? __builtin_amdgcn_readfirstlane(*in_lds<const int>(lds0 + Cfg<D>::kOffLate, 4)) : 0;
+  if (__builtin_expect(late, 0)) late_masses<D>(argument_again(), lds0, late);
+  if (HALVES && __builtin_expect(late2, 0)) late_masses<D>(argument_again(), lds0, late2);
   if (__hip_atomic_load(&prm.ctl->redo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) sweep_redo<D>(argument_again(), lds0);
 }
 
