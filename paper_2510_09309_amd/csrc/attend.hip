@@ -755,7 +755,8 @@ __global__ __launch_bounds__(256) void attend_merge_kernel(const AttendParams pr
 // hands workgroups to compute units in launch order, and the longest heads should not start last (measured
 // on 256 heads with 576...1536 keys: 101 us in this order, 123 us in the given order).  A counting sort by
 // 64-key tile count in one workgroup; the order inside a bucket is whatever the atomics give, which does not
-// matter: every head's result is independent of when it runs.
+// matter: every head's result is independent of when it runs.  (fp32, and bf16 with more heads than kRankHeads: up to that number
+// the workgroups of the bf16 kernel find their heads themselves.)
 constexpr int kOrderThreads = 1024;
 constexpr int kOrderBuckets = 1024;
 
@@ -951,7 +952,9 @@ int launch_attend(const maskkv_desc* d, const Lens& lens, bool full, const View&
   prm.n_splits = attend_splits(d, full);
   prm.c = scale * kLog2e;
   prm.lse = lse;
-  prm.order = attend_is_ordered(d, full, capacity) ? reinterpret_cast<const int32_t*>(workspace) : nullptr;
+  const bool ordered = attend_is_ordered(d, full, capacity);
+  prm.ranked = ordered && d->dtype == MASKKV_BF16 && prm.BH <= kRankHeads;
+  prm.order = ordered && !prm.ranked ? reinterpret_cast<const int32_t*>(workspace) : nullptr;
   prm.part_o = nullptr;
   prm.part_ml = nullptr;
   if (prm.n_splits > 1) {

@@ -54,6 +54,59 @@ struct TileCfg {
   __device__ static uint32_t swz_k(uint32_t row) { return D == 128 ? row & 15 : (row >> 1) & 7; }
 };
 
+// The head of a given rank by descending number of 64-key tiles (equal ones by ascending number), and where its packed rows begin
+// and end, found by every wave on its own: its lanes hold all heads' counts, a bit of the wanted count takes a comparison per 64
+// heads, and of the heads with that count it is the one with so many before it.  That takes about as long as the load of the head's
+// number did, which a kernel in front of this one had sorted (us a call, with it and without: 256 heads x 512 queries over 576 ...
+// 1536 keys 79.2 / 78.0, over 812 keys 80.2 / 77.7; 192 x 190 over 720, head_dim 64, 30.9 / 28.9; 112 x 262 over 562 38.3 / 36.8).  Not
+// beyond 256 heads: with eight of them a lane 448 heads x 300 took 69 instead of 63.
+__device__ __forceinline__ int head_of_rank(const AttendParams& prm, int rank, int& c0, int& c1) {
+  constexpr int N = kRankHeads / 64;
+  const int lane = threadIdx.x & 63, capacity = (int)prm.capacity;
+  int from[N], to[N], tiles[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const int head = min(i * 64 + lane, prm.BH - 1);
+    from[i] = prm.cu[head];
+    to[i] = prm.cu[head + 1];
+  }
+  int most = 0;
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    from[i] = min(from[i], capacity);
+    to[i] = min(to[i], capacity);
+    tiles[i] = i * 64 + lane < prm.BH ? min(max((to[i] - from[i] + prm.n_resp + kTK - 1) / kTK, 1), 0xFFFF) : 0;
+    most = max(most, tiles[i]);
+  }
+#pragma unroll
+  for (int o = 1; o < 64; o *= 2) most = max(most, __shfl_xor(most, o, 64));
+  int found = 0, above = 0;  // the count, and how many heads have more tiles
+  for (int bit = 1 << (31 - __builtin_clz(__builtin_amdgcn_readfirstlane(most))); bit > 0; bit >>= 1) {
+    int n = 0;
+#pragma unroll
+    for (int i = 0; i < N; ++i) n += __popcll(__ballot(tiles[i] >= (found | bit)));
+    if (n > rank)
+      found |= bit;
+    else
+      above = n;
+  }
+  int left = rank - above, head = 0;
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const uint64_t same = __ballot(tiles[i] == found);
+    const int n = __popcll(same);
+    if (left >= 0 && left < n) {
+      const int before = __builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0));
+      const int at = __builtin_ctzll(__ballot(tiles[i] == found && before == left));
+      head = i * 64 + at;
+      c0 = __builtin_amdgcn_readlane(from[i], at);
+      c1 = __builtin_amdgcn_readlane(to[i], at);
+    }
+    left -= n;
+  }
+  return head;
+}
+
 template <int D, bool HALVES>
 __global__ __launch_bounds__(kWaves * 64) void attend_tiles_kernel(const AttendParams prm) {
   using C = TileCfg<D, HALVES>;
@@ -64,12 +117,23 @@ __global__ __launch_bounds__(kWaves * 64) void attend_tiles_kernel(const AttendP
   // split) get consecutive slots of one XCD, and their K/V rows come from HBM once.  Ordered heads are dealt to the XCDs in
   // turn, otherwise each XCD takes a run of units.
   const int qtiles = (prm.n_q + C::kQueries - 1) / C::kQueries;
-  const int slot = blockIdx.x / 8 + (prm.order ? 0 : blockIdx.x % 8 * (gridDim.x / 8));
-  const int unit = prm.order ? (slot / qtiles) * 8 + blockIdx.x % 8 : slot / qtiles;  // (head, split) pair
+  const bool ordered = prm.order || prm.ranked;
+  const int slot = blockIdx.x / 8 + (ordered ? 0 : blockIdx.x % 8 * (gridDim.x / 8));
+  const int unit = ordered ? (slot / qtiles) * 8 + blockIdx.x % 8 : slot / qtiles;  // (head, split) pair
   const int qtile = slot % qtiles;
   if (unit >= prm.BH * prm.n_splits) return;
-  const int bh = __builtin_amdgcn_readfirstlane(prm.order ? prm.order[unit] : unit / prm.n_splits);  // (an order is only given without splits)
-  const int split = prm.order ? 0 : unit % prm.n_splits;
+  int c0 = 0, c1 = 0;  // rows of the packed segment
+  int bh;
+  if (prm.ranked) {  // (heads are only ordered without splits)
+    bh = head_of_rank(prm, unit, c0, c1);
+  } else {
+    bh = __builtin_amdgcn_readfirstlane(prm.order ? prm.order[unit] : unit / prm.n_splits);
+    if (!prm.full) {
+      c0 = (int)min((int64_t)prm.cu[bh], prm.capacity);
+      c1 = (int)min((int64_t)prm.cu[bh + 1], prm.capacity);
+    }
+  }
+  const int split = ordered ? 0 : unit % prm.n_splits;
   const int b = bh / prm.H;
   const int h = bh % prm.H;
   const int lane = threadIdx.x & 63;
@@ -84,11 +148,9 @@ __global__ __launch_bounds__(kWaves * 64) void attend_tiles_kernel(const AttendP
   if (prm.full) {
     len_b = prm.lens.P[b] + prm.n_resp;
   } else {
-    const int64_t c0 = min((int64_t)prm.cu[bh], prm.capacity);
-    const int64_t c1 = min((int64_t)prm.cu[bh + 1], prm.capacity);
-    a_k = prm.Kc + c0 * C::kRowB;
-    a_v = prm.Vc + c0 * C::kRowB;
-    len_a = (int)(c1 - c0);
+    a_k = prm.Kc + (int64_t)c0 * C::kRowB;
+    a_v = prm.Vc + (int64_t)c0 * C::kRowB;
+    len_a = c1 - c0;
   }
   const int Lk = len_a + len_b;
   const int Ls = ((Lk + prm.n_splits - 1) / prm.n_splits + kTK - 1) / kTK * kTK;
@@ -401,7 +463,7 @@ int attend_tiles_queries(int64_t units, int n_q, bool full) {
 
 int launch_attend_tiles(const AttendParams& prm, int d, int queries, hipStream_t stream) {
   const int64_t qtiles = (prm.n_q + queries - 1) / queries, units = (int64_t)prm.BH * prm.n_splits;
-  const unsigned groups = (unsigned)(prm.order ? (units + 7) / 8 * 8 * qtiles : (units * qtiles + 7) / 8 * 8);
+  const unsigned groups = (unsigned)(prm.order || prm.ranked ? (units + 7) / 8 * 8 * qtiles : (units * qtiles + 7) / 8 * 8);
   if (queries == 128) return d == 128 ? launch<128, true>(prm, groups, stream) : launch<64, true>(prm, groups, stream);
   return d == 128 ? launch<128, false>(prm, groups, stream) : launch<64, false>(prm, groups, stream);
 }
