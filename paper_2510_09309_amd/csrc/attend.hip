@@ -274,7 +274,7 @@ __global__ __launch_bounds__((AttCfg<D>::kThreads)) void attend_kernel(const Att
 // rows are fetched into one or two L2s and four heads still reach all eight XCDs (4 heads x 1792 queries: 23.7 us with a head on
 // one XCD, 12.6 spread).
 //
-// fp32: four waves, K fragments from global memory into registers, V through a wave-private transposed LDS tile, two blocks in flight.
+// fp32, 32 queries: four waves, K fragments from global memory into registers, V through a wave-private transposed LDS tile, two blocks in flight.
 constexpr int kNarrowVS = 36;      // elements per transposed-V row: 32 keys + padding
 constexpr int kNarrowShift = 16;   // bytes by which every group of 32 rows is shifted further
 
@@ -466,7 +466,194 @@ __global__ __launch_bounds__(NarrowCfg<D>::kThreads) void attend_narrow_kernel(c
 typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 
-// The same for bf16: eight waves, K, V and the queries by direct transfers into LDS (a load of K fragments touches 32 rows for
+// fp32 in pieces of 16 queries and 16 keys: eight waves a workgroup, two blocks in flight a wave, no LDS before the merge.  For launches
+// that leave compute units without a workgroup of 32 queries: what bounds these is a wave's own chain, of which the products of a
+// block of 32 x 32 are 4096 cycles (head_dim 64) on one wave, and here 1024.  The elements of a row are taken in an
+// order in which a lane's operands are 16 consecutive bytes: in the logits' k-step 4t + e lane group g has element 16t + 4g + e of K and
+// Q; of V lane c has elements 4c .. 4c+3 of key 4g + i, one for each of four tiles of O^T, and the probabilities are the other operand
+// as they come.
+template <int D>
+struct SmallCfg {
+  static constexpr int kWaves = 8, kThreads = 64 * kWaves;
+  static constexpr int kQ = 16, kKeys = 16;
+  static constexpr int kRowB = 4 * D;
+  static constexpr int kChunks = D / 16;        // 16-byte pieces of a row of K or Q per lane
+  static constexpr int kHalves = D / 64;        // tiles of O^T, in fours
+  static constexpr int kRowP = kRowB + 16;      // a row of partial O in LDS
+  static constexpr int kOffMl = kWaves * kQ * kRowP;
+  static constexpr int kLds = kOffMl + kWaves * kQ * 8;
+};
+
+__device__ __forceinline__ float max_of_groups(float v) {  // over the lanes c, c + 16, c + 32, c + 48
+  const auto sw = __builtin_amdgcn_permlane16_swap(as_u32(v), as_u32(v), false, false);
+  const unsigned u0 = sw[0], u1 = sw[1];
+  v = fmaxf(as_f32(u0), as_f32(u1));
+  return fmaxf(v, xor32(v));
+}
+__device__ __forceinline__ float sum_of_groups(float v) {
+  const auto sw = __builtin_amdgcn_permlane16_swap(as_u32(v), as_u32(v), false, false);
+  const unsigned u0 = sw[0], u1 = sw[1];
+  v = as_f32(u0) + as_f32(u1);
+  return v + xor32(v);
+}
+
+template <int D>
+__global__ __launch_bounds__(SmallCfg<D>::kThreads) void attend_small_kernel(const AttendParams prm) {
+  using C = SmallCfg<D>;
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
+  const int nqt = (prm.n_q + C::kQ - 1) / C::kQ;
+  // eight runs of consecutive (head, query tile) pairs, one per XCD
+  const int pair = (blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
+  const int bh = pair / nqt;
+  const int qt = pair - bh * nqt;
+  if (bh >= prm.BH) return;
+  const int b = bh / prm.H;
+  const int h = bh - b * prm.H;
+  const int lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const auto cu = (const __attribute__((address_space(4))) int32_t*)(prm.cu + bh);
+  const int64_t cu0 = cu[0], cu1 = cu[1];
+
+  const int nb2 = (prm.n_resp + C::kKeys - 1) / C::kKeys;
+  struct Block {
+    f32x4 k[C::kChunks], v[C::kHalves][4];
+  };
+  // Rows past the end of a segment re-read its last row; their logits are masked and their values zeroed.
+  auto load = [&](const char* k, int64_t kst, const char* v, int64_t vst, int last, Block& to) {
+    const char* krow = k + min(c, last) * kst + g * 16;
+#pragma unroll
+    for (int t = 0; t < C::kChunks; ++t) to.k[t] = *reinterpret_cast<const f32x4*>(krow + t * 64);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const char* vrow = v + min(4 * g + i, last) * vst + c * 16;
+#pragma unroll
+      for (int half = 0; half < C::kHalves; ++half) to.v[half][i] = *reinterpret_cast<const f32x4*>(vrow + half * 256);
+    }
+  };
+  const char *k2 = prm.K2.row(b, h, 0), *v2 = prm.V2.row(b, h, 0);
+  auto resp = [&](int t, Block& to) {
+    const int first = t * C::kKeys;
+    load(k2 + first * prm.K2.stride_t, prm.K2.stride_t, v2 + first * prm.V2.stride_t, prm.V2.stride_t, prm.n_resp - 1 - first, to);
+  };
+  Block one, two;
+  // (the response segment comes first: its blocks are asked for before the head's budget is known)
+  if (wave < nb2) resp(wave, one);
+  f32x4 qf[C::kChunks];
+  {
+    const char* qrow = prm.Q.group_row(b, h, prm.q_per_kv, prm.n_resp, min(qt * C::kQ + c, prm.n_q - 1)) + g * 16;
+#pragma unroll
+    for (int t = 0; t < C::kChunks; ++t) qf[t] = *reinterpret_cast<const f32x4*>(qrow + t * 64);
+  }
+  const int64_t c0 = min(cu0, prm.capacity);
+  const int len_a = (int)(min(cu1, prm.capacity) - c0);
+  const char *a_k = prm.Kc + c0 * C::kRowB, *a_v = prm.Vc + c0 * C::kRowB;
+  const int nblk = nb2 + (len_a + C::kKeys - 1) / C::kKeys;
+  auto ask = [&](int t, Block& to) {
+    if (t < nb2) {
+      resp(t, to);
+    } else {
+      const int64_t first = (int64_t)(t - nb2) * C::kKeys;
+      load(a_k + first * C::kRowB, C::kRowB, a_v + first * C::kRowB, C::kRowB, len_a - 1 - (int)first, to);
+    }
+  };
+  if (wave >= nb2 && wave < nblk) ask(wave, one);
+  if (wave + C::kWaves < nblk) ask(wave + C::kWaves, two);
+
+  f32x4 o[C::kHalves][4];
+#pragma unroll
+  for (int half = 0; half < C::kHalves; ++half)
+#pragma unroll
+    for (int t = 0; t < 4; ++t) o[half][t] = f32x4{};
+  float m = kNegBig, l = 0.f;
+  auto step = [&](int t, Block& of) {
+    // S^T = K Q^T: this lane's keys are 4g .. 4g+3 of the block, its query is c
+    f32x4 s = f32x4{}, s1 = f32x4{};
+#pragma unroll
+    for (int p = 0; p < C::kChunks; ++p)
+#pragma unroll
+      for (int e = 0; e < 4; e += 2) {
+        s = __builtin_amdgcn_mfma_f32_16x16x4f32(of.k[p][e], qf[p][e], s, 0, 0, 0);
+        s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(of.k[p][e + 1], qf[p][e + 1], s1, 0, 0, 0);
+      }
+    s += s1;
+    const int valid = t < nb2 ? prm.n_resp - t * C::kKeys : len_a - (t - nb2) * C::kKeys;
+    if (valid < C::kKeys) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (4 * g + i >= valid) {
+          s[i] = -INFINITY;
+#pragma unroll
+          for (int half = 0; half < C::kHalves; ++half) of.v[half][i] = f32x4{};
+        }
+    }
+    // online softmax, the reference raised lazily as in the tiled kernel
+    const float cand = max_of_groups(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]))) * prm.c;
+    const bool bump = cand > m + kLazyBump;
+    if (__any(bump)) {
+      const float m_new = bump ? cand : m;
+      const float alpha = fast_exp2(m - m_new);
+      m = m_new;
+      l *= alpha;
+#pragma unroll
+      for (int half = 0; half < C::kHalves; ++half)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) o[half][u] *= alpha;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      s[i] = fast_exp2(fmaf(s[i], prm.c, -m));
+      l += s[i];
+    }
+    // O^T += V^T P^T: row r of tile u is element 4r + u
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int half = 0; half < C::kHalves; ++half)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) o[half][u] = __builtin_amdgcn_mfma_f32_16x16x4f32(of.v[half][i][u], s[i], o[half][u], 0, 0, 0);
+    if (t + 2 * C::kWaves < nblk) ask(t + 2 * C::kWaves, of);
+  };
+  for (int t = wave; t < nblk; t += 2 * C::kWaves) {
+    step(t, one);
+    if (t + C::kWaves < nblk) step(t + C::kWaves, two);
+  }
+
+  // ---- the waves' partial results through LDS, by rows
+  const float l_tot = sum_of_groups(l);
+#pragma unroll
+  for (int half = 0; half < C::kHalves; ++half)
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      *in_lds<f32x4>(lds0 + (wave * C::kQ + c) * C::kRowP + g * 64, half * 256 + i * 16) = f32x4{o[half][0][i], o[half][1][i], o[half][2][i], o[half][3][i]};
+  if (g == 0) *in_lds<f32x2>(lds0 + C::kOffMl + (wave * C::kQ + c) * 8) = f32x2{m, l_tot};
+  __syncthreads();
+  const int row = (int)threadIdx.x / (D / 4), piece = (int)threadIdx.x % (D / 4);
+  const int q = qt * C::kQ + row;
+  if (row >= C::kQ || q >= prm.n_q) return;
+  f32x2 ml[C::kWaves];
+  f32x4 part[C::kWaves];
+#pragma unroll
+  for (int w = 0; w < C::kWaves; ++w) {
+    ml[w] = *in_lds<const f32x2>(lds0 + C::kOffMl + row * 8, w * C::kQ * 8);
+    part[w] = *in_lds<const f32x4>(lds0 + row * C::kRowP + piece * 16, w * C::kQ * C::kRowP);
+  }
+  float top = kNegBig, L = 0.f;
+#pragma unroll
+  for (int w = 0; w < C::kWaves; ++w) top = fmaxf(top, ml[w][0]);
+  f32x4 acc = f32x4{};
+#pragma unroll
+  for (int w = 0; w < C::kWaves; ++w) {
+    const float weight = fast_exp2(ml[w][0] - top);
+    L += weight * ml[w][1];
+    acc += weight * part[w];
+  }
+  acc *= 1.f / L;
+  *reinterpret_cast<f32x4*>(prm.O.group_row(b, h, prm.q_per_kv, prm.n_resp, q) + piece * 16) = acc;
+  if (prm.lse && piece == 0) prm.lse[(int64_t)bh * prm.n_q + q] = (top + __log2f(L)) * kLn2;
+}
+
+// bf16: eight waves, 32 queries, K, V and the queries by direct transfers into LDS (a load of K fragments touches 32 rows for
 // 1 KiB), V read with transposing loads.  A wave has one block in flight: the next K is asked for once the logits are formed, the
 // next V once the block is added, and each is waited for on its own (the compiler, which does not see the transfers, would wait
 // for later ones as well).  The key axis begins with the response segment, whose blocks are asked for before the head's budget is known.
@@ -833,6 +1020,14 @@ bool attend_is_narrow(const maskkv_desc* d, bool full, int64_t capacity) {
   return groups <= 4 * kUnits * ((tiled + kUnits - 1) / kUnits);
 }
 
+// fp32: workgroups of 16 queries as long as there is one a compute unit at most (us a call, against the narrow kernel's 32: 4 heads x 64
+// queries x 96 keys, head_dim 64, 6.1 / 7.7; 12 x 73 x 273, head_dim 128, 12.7 / 21.8; 16 x 256 x 512 11.4 / 16.8 and 19.2 / 27.3; but
+// 20 x 256 x 512 18.9 / 16.6 and 33.9 / 27.3, 32 x 512 x 2512 256 / 209).
+bool attend_is_small(const maskkv_desc* d) {
+  const int64_t n_q = (int64_t)d->n_resp * query_heads_per_kv(d);
+  return (n_q + 15) / 16 * d->B * d->H <= kUnits;
+}
+
 // Heads are only put in order where not every workgroup of the tiled kernel starts at once.
 bool attend_is_ordered(const maskkv_desc* d, bool full, int64_t capacity) {
   if (full || attend_is_narrow(d, full, capacity)) return false;
@@ -858,6 +1053,24 @@ int launch_attend_narrow(const AttendParams& prm, hipStream_t stream) {
   const int groups = (prm.BH * nqt + 7) / 8 * 8;
   hipLaunchKernelGGL((attend_narrow_kernel<D>), dim3(groups), dim3(C::kThreads), C::kLds, stream, prm);
   return check_launch("attend (narrow)");
+}
+
+template <int D>
+int launch_attend_small(const AttendParams& prm, hipStream_t stream) {
+  using C = SmallCfg<D>;
+  static bool raised = false;  // one-time opt-in to more than the default dynamic LDS size
+  if (C::kLds > 48 * 1024 && !raised) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attend_small_kernel<D>), hipFuncAttributeMaxDynamicSharedMemorySize, C::kLds);
+    if (e != hipSuccess) {
+      set_error("attend: cannot raise dynamic LDS limit: %s", hipGetErrorString(e));
+      (void)hipGetLastError();
+      return MASKKV_EHIP;
+    }
+    raised = true;
+  }
+  const int groups = (prm.BH * ((prm.n_q + C::kQ - 1) / C::kQ) + 7) / 8 * 8;
+  hipLaunchKernelGGL((attend_small_kernel<D>), dim3(groups), dim3(C::kThreads), C::kLds, stream, prm);
+  return check_launch("attend (small)");
 }
 
 template <int D>
@@ -965,6 +1178,7 @@ int launch_attend(const maskkv_desc* d, const Lens& lens, bool full, const View&
   }
   if (attend_is_narrow(d, full, capacity)) {
     if (d->dtype == MASKKV_BF16) return d->d == 128 ? launch_attend_pairs<128>(prm, stream) : launch_attend_pairs<64>(prm, stream);
+    if (attend_is_small(d)) return d->d == 128 ? launch_attend_small<128>(prm, stream) : launch_attend_small<64>(prm, stream);
     return d->d == 128 ? launch_attend_narrow<128>(prm, stream) : launch_attend_narrow<64>(prm, stream);
   }
   if (d->dtype == MASKKV_BF16)
