@@ -1067,20 +1067,22 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
     const Table c = table + min(++fresh, chunks - 1);
     take(c->bh, c->shape);
   };
-  // The first of a single sequence's chunks is where the plan has it (run 0 has a chunk for every workgroup), which is known before the table
+  // The first of a single sequence's chunks is where the plan has it, which is known before the table
   // is there; all that is asked for here is asked for before anything is waited for.  (One latency of a load that misses L2, of three: the
   // lock's word, the table, keys and rows.  4 to 16 rounds, us a call: 16 heads x 89 rows x 9.7k keys 25.5 -> 24.1, x 203 x 28k 59.6 ->
   // 58.5, 32 heads x 256 rows x 8k 37.2 -> 36.6, x 32k 115.5 -> 113.6, 4 heads x 1792 x 30k 89.8 -> 87.4.)
   const int run = *(const __attribute__((address_space(4))) int*)&prm.ctl->run;
   const int redo = *(const __attribute__((address_space(4))) int*)&prm.ctl->redo;
-  uint32_t shape0;
-  const char* keys0;
-  if (prm.B == 1) {
-    const int P = prm.lens.P[0], nc = (P + kKeys - 1) / kKeys, nth = team / nc, ci = team - nth * nc, vh = prm.plan.head(0) + nth;
+  uint32_t shape0 = 0;
+  const char* keys0 = nullptr;
+  const int run0 = HALVES && second && prm.plan.place(1) > 0 ? 1 : 0;
+  if (prm.B == 1 && prm.plan.has(run0, team)) {
+    const int P = prm.lens.P[0], nc = (P + kKeys - 1) / kKeys, off = team - prm.plan.place(run0);
+    const int nth = off / nc, ci = off - nth * nc, vh = prm.plan.head(run0) + nth;
     take(vh, (uint32_t)ci | (uint32_t)(nc - 1) << 8 | (uint32_t)min(P - ci * kKeys, kKeys) << 16);
     shape0 = ahead.shape;
     keys0 = prm.K.row(0, prm.subsets == 1 ? vh : vh / prm.subsets, (int64_t)ci * kKeys);
-  } else {
+  } else if (!HALVES || chunks > 0) {
     take(table->bh, table->shape);
     shape0 = table->shape;
     keys0 = table->keys;
@@ -1322,12 +1324,14 @@ struct Layout {
 //
 // Where no head has more than 128 voting rows, four of a workgroup's waves would have none: the halves of a workgroup can then be two
 // workgroups, each with chunks of its own (4 sequences of 28 heads, head_dim 64, 116 rows, 22 chunks: 37.6 instead of 44.9 us).
-// They meet at each step's barriers, so a step has the same number as its round in every half, and a half that a round
+// The first halves and the second halves are packed by themselves (`half` workgroups each) unless a head on both saves enough.
+// The halves meet at each step's barriers, so a step has the same number as its round in every half, and a half that a round
 // has no chunk for goes through an idle step: with the steps of a list closed up, one half waits for a head of a later round
 // than the other's, and halves that hold each other up this way can wait in a circle.
 struct Packing {
   SweepPlan plan;
-  Packing(const maskkv_desc* d, const int* nc, int n, int subsets, int nqg, bool mixed) : plan{} {
+  int across = 0;  // of a head that lies on either side of `edge`, the chunks beyond it (the most of all rounds)
+  Packing(const maskkv_desc* d, const int* nc, int n, int half, int edge, int subsets, bool mixed) : plan{} {
     int left[MASKKV_MAX_BATCH], order[MASKKV_MAX_BATCH], B = 0;
     for (int b = 0; b < d->B; ++b) {
       left[b] = nc[b] > 0 ? d->H * subsets : 0;
@@ -1342,26 +1346,34 @@ struct Packing {
         ++first;
         continue;
       }
-      int room = n, times = 0x7FFFFFFF;
       const int run = plan.runs;
-      for (int i = first; i < B && room > 0; ++i) {
-        const int b = order[i], side = min(left[b], room / nc[b]);
-        if (side == 0) continue;
-        if (plan.runs == kMaxRuns) {
-          plan.groups = 0;
-          return;
+      int side_of[MASKKV_MAX_BATCH] = {};  // heads of a sequence in this round
+      for (int from = 0; from < n; from += half) {
+        int room = half;
+        for (int i = first; i < (mixed ? B : first + 1) && room > 0; ++i) {
+          const int b = order[i], side = min(left[b] - side_of[b], room / nc[b]);
+          if (side == 0) continue;
+          if (plan.runs == kMaxRuns) {
+            plan.groups = 0;
+            return;
+          }
+          const int at = from + half - room;
+          plan.put(plan.runs++, at, side, side * nc[b], b, 0);
+          if (at < edge && edge < at + side * nc[b] && (edge - at) % nc[b]) across = max(across, nc[b] - (edge - at) % nc[b]);
+          room -= side * nc[b];
+          side_of[b] += side;
+          plan.groups = max(plan.groups, from + half - room);
         }
-        plan.put(plan.runs++, n - room, side, side * nc[b], b, d->H * subsets - left[b]);
-        room -= side * nc[b];
-        times = min(times, left[b] / side);
-        if (!mixed) break;
       }
+      int times = 0x7FFFFFFF;
+      for (int i = run; i < plan.runs; ++i) times = min(times, left[plan.sequence(i)] / side_of[plan.sequence(i)]);
       for (int i = run; i < plan.runs; ++i) {
+        const int b = plan.sequence(i), side = plan.side(i);
+        plan.put(i, plan.place(i), side, plan.width(i), b, d->H * subsets - left[b]);
         plan.repeat(i, times);
-        left[plan.sequence(i)] -= plan.side(i) * times;
+        left[b] -= side * times;
       }
       plan.rounds += times;
-      plan.groups = max(plan.groups, n - room);
     }
   }
 };
@@ -1377,26 +1389,32 @@ SweepPlan make_plan(const maskkv_desc* d, const Lens& lens, int nqg) {
     chunks += (int64_t)nc[b] * d->H;
   }
   if (most == 0 || most > n) return best;
-  // Microseconds, from 44 batches of the sizes that bf16 prompts come in, each timed in every way: a step of 256 rows, with half of
-  // the waves idle, and of two chunks side by side; the two passes per chunk; and what each costs besides.  (Rounds against two
+  // Microseconds, from 70 batches of the sizes that bf16 prompts come in, each timed in every way: what a call costs besides its steps,
+  // a step (256 rows; with half of the waves idle; of two chunks side by side), two passes per chunk.  (Rounds against two
   // passes, head_dim 128: 16 heads of 218 chunks 59 / 79, of 227 with two groups of rows 92 / 143, the 5952 chunks of 5 sequences
   // with 7 queries a head 88 / 131; head_dim 64: 28 heads of 213 chunks with two groups of rows 128 / 154, 1300 chunks 30 / 51.
-  // Rounds against halves: 32 heads of 87 chunks, 16 steps against 7, 44.9 / 35.8; 8 sequences of 32 heads, 18 / 9, 60.1 / 51.2; 13 /
-  // 7, 39.9 / 37.8; 4 / 2, 22.2 / 21.9; but 5 / 3, 23.5 / 23.9; 6 / 3, 25.4 / 26.3; 2 / 1, 14.0 / 14.4.)
+  // Rounds against halves, head_dim 128: 32 heads of 87 chunks, 16 steps against 8, 43.6 / 38.3; 28 of 211, 28 / 14, 68.6 / 61; 16
+  // of 163, 16 / 8, 46.6 / 41.3; but 8 of 163, 8 / 4, 29.7 / 30.0; 8 of 235, 8 / 4, 31.9 / 35.9; 28 of 39, 5 / 3, 22.4 / 22.9.)
+  // A head on both halves of workgroups waits for the later one at every step, the longer the more of its chunks are there, but can
+  // save rounds: 8 heads of 131 chunks, 6 across, 3 rounds against 4, 23.6 / 28.6; 32 of 87, 5 across, 7 / 8, 35.3 / 38.3; but
+  // 8 of 163, 70 across, 3 / 4, 32.8 / 30.0; 28 of 211, 166 across, as many rounds, 115 / 61.
   const bool wide = d->d == 128, few = (int64_t)d->n_query * query_heads_per_kv(d) <= kRows / 2;
   double cost = 23.0 + (double)chunks * nqg * (wide ? 0.0169 : 0.0101);
-  auto consider = [&](int workgroups, int subsets, double besides, double step) {
-    Packing p(d, nc, workgroups, subsets, nqg, true);
-    if (!p.plan.groups) p = Packing(d, nc, workgroups, subsets, nqg, false);
+  auto consider = [&](int workgroups, int half, int subsets, double besides, double step) {
+    Packing p(d, nc, workgroups, half, n, subsets, true);
+    if (!p.plan.groups) p = Packing(d, nc, workgroups, half, n, subsets, false);
+    if (!p.plan.groups) return;
     p.plan.grid = min(p.plan.groups, n);
-    const double c = besides + p.plan.rounds * (nqg / subsets) * step;
+    const double c = besides + p.plan.rounds * ((nqg / subsets) * step + 0.02 * p.across);
     if (c >= cost) return;
     cost = c;
     best = p.plan;
   };
   for (int subsets = 1; subsets <= nqg; ++subsets)
-    if (nqg % subsets == 0) consider(n, subsets, subsets > 1 ? 19.0 : 14.0, few ? (wide ? 1.95 : 1.75) : (wide ? 2.5 : 2.1));
-  if (few) consider(2 * n, 1, 16.5, wide ? 3.1 : 2.5);
+    if (nqg % subsets == 0)
+      consider(n, n, subsets, few ? (wide ? 12.4 : 10.6) : subsets > 1 ? 19.0 : 14.0, few ? (wide ? 2.07 : 1.87) : (wide ? 2.5 : 2.1));
+  if (few)
+    for (int half = n; half <= 2 * n; half += n) consider(2 * n, half, 1, wide ? 12.9 + 0.039 * most : 10.5 + 0.02 * most, wide ? 2.92 : 2.4);
   return best;
 }
 

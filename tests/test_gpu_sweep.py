@@ -99,7 +99,9 @@ def test_calls_on_two_streams_at_once():
     # at most 128 rows: halves of workgroups, also in rounds that have no chunk for them, or in none
     (128, 69, 32, 1, (1135, 3503, 1500, 2000, 2900, 2300, 1700, 1300), False), (128, 69, 32, 1, (1135, 3503, 1500), True),
     (64, 100, 5, 1, (16500, 300), False), (64, 100, 5, 1, (16500, 300), True),
-    (128, 128, 16, 1, (12000,), False), (64, 18, 12, 7, (9001, 100, 5000), False), (128, 1, 16, 1, (12289, 1, 0, 129), False)])
+    (128, 128, 16, 1, (12000,), False), (64, 18, 12, 7, (9001, 100, 5000), False), (128, 1, 16, 1, (12289, 1, 0, 129), False),
+    (128, 66, 9, 1, (27000,), False), (128, 99, 8, 1, (16700,), False),    # heads in one half each, a head across the halves
+    (64, 33, 2, 1, tuple((i * 37) % 64 * 33 for i in range(64)), False)])   # more runs than a plan has room for, in halves
 def test_rounds_of_heads_and_groups_of_rows(d, n, H, g, Ps, fallback):
     """Heads against float64 (fp32 sums of products of bf16 inputs: logits of up to 2^5 binary orders)."""
     # One row's errors are not averaged with others': its logits of up to 2^5 binary orders are rounded (2^-20) once for every 16 products.
