@@ -27,9 +27,9 @@
 // has 1800 cycles of them, a vector phase 1300 to 1800, and the two waves of a SIMD share the vector pipe, where v_exp_f32
 // takes 8 cycles and an MFMA about as many.  In a loop of such calls the board is at its 1400 W and the clock 10 % below that of
 // short calls (2.1 against 2.3 GHz).  us a call, with both groups of waves in the same phase, chunks dealt out end to end and keys
-// transferred for every group of rows before: 32 heads x 128 with 256 rows, 4k keys 28.7 -> 28.2, 8k 39 -> 37.9, 32k 120 -> 115; 4
-// heads with 1792 rows over 30k keys 93.5 -> 87.8; the ragged batch of perf/cases.py 518 -> 473 (481 with 64-bit
-// addresses formed for every access).  (Without transfers of keys, with
+// transferred for every group of rows before: 32 heads x 128 with 256 rows, 4k keys 28.7 -> 27.1, 8k 39 -> 36.6, 32k 120 -> 114; 4
+// heads with 1792 rows over 30k keys 93.5 -> 87.4; the ragged batch of perf/cases.py 518 -> 466 (8 more with 64-bit
+// addresses formed for every access, 6 more with the start kernel's loads in turn).  (Without transfers of keys, with
 // wrong results, the ragged batch took 420 instead of 505, without loads of rows 455, without the exchange 465.)  Slower: raised
 // wave priority in the vector phase or for waves 4-7; a first sum per XCD that the last of its workgroups adds to the whole
 // (two latencies instead of one); 2 or 8 copies of the sums.
