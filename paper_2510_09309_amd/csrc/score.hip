@@ -7,7 +7,7 @@
 //   pass 2  logits again, p = exp2(s*c - lse), summed over the queries for every prompt key.
 // Storing the n_m x N logits instead would cost far more HBM traffic than the second MFMA pass.
 // These passes serve fp32 (short prompts: rows.hip), prompts of more than one chunk of 128 keys per compute unit, the shapes at which they are the faster
-// way (see make_plan in sweep.hip), short fp32 prompts (rows.hip), and given normalisers; everything else is scored in one sweep (sweep.hip).
+// way (see make_plan in sweep.hip), and given normalisers; everything else is scored in one sweep (sweep.hip).
 //
 // Work decomposition: the key axis of every (b, h) is cut into 64-key tiles (prompt tiles, then response
 // tiles; a tile never straddles the prompt/response boundary).  All tiles of the launch form one global
