@@ -313,12 +313,15 @@ __global__ __launch_bounds__(NarrowCfg<D>::kThreads) void attend_narrow_kernel(c
   const int r = lane & 31;
   const int g = lane >> 5;
 
-  const int64_t c0 = min((int64_t)prm.cu[bh], prm.capacity);
-  const int64_t c1 = min((int64_t)prm.cu[bh + 1], prm.capacity);
+  int64_t c0 = 0, c1 = 0;
+  if (!prm.full) {
+    c0 = min((int64_t)prm.cu[bh], prm.capacity);
+    c1 = min((int64_t)prm.cu[bh + 1], prm.capacity);
+  }
   const char* a_k = prm.Kc + c0 * C::kRowB;
   const char* a_v = prm.Vc + c0 * C::kRowB;
   const int len_a = (int)(c1 - c0);
-  const int Lk = len_a + prm.n_resp;
+  const int Lk = len_a + prm.n_resp + (prm.full ? prm.lens.P[b] : 0);
   const int nblk = (Lk + 31) / 32;
 
   auto key_row = [&](const char* packed, const View& rest, int j) -> const char* {
@@ -512,10 +515,15 @@ __global__ __launch_bounds__(SmallCfg<D>::kThreads) void attend_small_kernel(con
   const int h = bh - b * prm.H;
   const int lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const auto cu = (const __attribute__((address_space(4))) int32_t*)(prm.cu + bh);
-  const int64_t cu0 = cu[0], cu1 = cu[1];
+  int64_t cu0 = 0, cu1 = 0;
+  if (!prm.full) {
+    const auto cu = (const __attribute__((address_space(4))) int32_t*)(prm.cu + bh);
+    cu0 = cu[0];
+    cu1 = cu[1];
+  }
+  const int n2 = prm.n_resp + (prm.full ? prm.lens.P[b] : 0);  // rows of the second segment
 
-  const int nb2 = (prm.n_resp + C::kKeys - 1) / C::kKeys;
+  const int nb2 = (n2 + C::kKeys - 1) / C::kKeys;
   struct Block {
     f32x4 k[C::kChunks], v[C::kHalves][4];
   };
@@ -534,7 +542,7 @@ __global__ __launch_bounds__(SmallCfg<D>::kThreads) void attend_small_kernel(con
   const char *k2 = prm.K2.row(b, h, 0), *v2 = prm.V2.row(b, h, 0);
   auto resp = [&](int t, Block& to) {
     const int first = t * C::kKeys;
-    load(k2 + first * prm.K2.stride_t, prm.K2.stride_t, v2 + first * prm.V2.stride_t, prm.V2.stride_t, prm.n_resp - 1 - first, to);
+    load(k2 + first * prm.K2.stride_t, prm.K2.stride_t, v2 + first * prm.V2.stride_t, prm.V2.stride_t, n2 - 1 - first, to);
   };
   Block one, two;
   // (the response segment comes first: its blocks are asked for before the head's budget is known)
@@ -577,7 +585,7 @@ __global__ __launch_bounds__(SmallCfg<D>::kThreads) void attend_small_kernel(con
         s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(of.k[p][e + 1], qf[p][e + 1], s1, 0, 0, 0);
       }
     s += s1;
-    const int valid = t < nb2 ? prm.n_resp - t * C::kKeys : len_a - (t - nb2) * C::kKeys;
+    const int valid = t < nb2 ? n2 - t * C::kKeys : len_a - (t - nb2) * C::kKeys;
     if (valid < C::kKeys) {
 #pragma unroll
       for (int i = 0; i < 4; ++i)
@@ -701,8 +709,13 @@ __global__ __launch_bounds__(PairsCfg<D>::kThreads) void attend_pairs_kernel(con
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r = lane & 31;
   const int g = lane >> 5;
-  const auto cu = (const __attribute__((address_space(4))) int32_t*)(prm.cu + bh);
-  const int64_t cu0 = cu[0], cu1 = cu[1];
+  int64_t cu0 = 0, cu1 = 0;
+  if (!prm.full) {
+    const auto cu = (const __attribute__((address_space(4))) int32_t*)(prm.cu + bh);
+    cu0 = cu[0];
+    cu1 = cu[1];
+  }
+  const int n2 = prm.n_resp + (prm.full ? prm.lens.P[b] : 0);  // rows of the second segment
 
   // Rows past the end of a segment re-read its last row and are masked.
   const uint32_t mrow = (uint32_t)lane / C::kPPR, slot = (uint32_t)lane % C::kPPR;
@@ -719,7 +732,7 @@ __global__ __launch_bounds__(PairsCfg<D>::kThreads) void attend_pairs_kernel(con
       for (int i = 0; i < M; ++i) dma16(base, (uint32_t)min(i * C::kRPI + (int)mrow, last) * st + piece(i), to + i * 1024);
     }
   };
-  const int nb2 = (prm.n_resp + 31) / 32;
+  const int nb2 = (n2 + 31) / 32;
   const char *k2 = prm.K2.row(b, h, 0), *v2 = prm.V2.row(b, h, 0);
   const uint32_t kst = (uint32_t)prm.K2.stride_t, vst = (uint32_t)prm.V2.stride_t;
 
@@ -731,8 +744,8 @@ __global__ __launch_bounds__(PairsCfg<D>::kThreads) void attend_pairs_kernel(con
       dma16_from(qrow + ((slot ^ C::swz(j * C::kRPI + mrow)) << 4), lds0 + C::kOffQ + j * 1024);
     }
   }
-  auto resp_k = [&](int t) { move(k2 + (int64_t)(t * 32) * kst, kst, prm.n_resp - 1 - t * 32, true, own); };
-  auto resp_v = [&](int t) { move(v2 + (int64_t)(t * 32) * vst, vst, prm.n_resp - 1 - t * 32, false, own + C::kBlock); };
+  auto resp_k = [&](int t) { move(k2 + (int64_t)(t * 32) * kst, kst, n2 - 1 - t * 32, true, own); };
+  auto resp_v = [&](int t) { move(v2 + (int64_t)(t * 32) * vst, vst, n2 - 1 - t * 32, false, own + C::kBlock); };
   if (wave < nb2) {
     resp_k(wave);
     resp_v(wave);
@@ -791,7 +804,7 @@ __global__ __launch_bounds__(PairsCfg<D>::kThreads) void attend_pairs_kernel(con
     }
     asm volatile("" : "+v"(s) : : "memory");  // (the slot has been read)
     if (more) ask_k(t + C::kWaves);
-    const int valid = t < nb2 ? prm.n_resp - t * 32 : len_a - (t - nb2) * 32;
+    const int valid = t < nb2 ? n2 - t * 32 : len_a - (t - nb2) * 32;
     if (valid < 32) {
 #pragma unroll
       for (int i = 0; i < 16; ++i)
@@ -1028,6 +1041,25 @@ bool attend_is_small(const maskkv_desc* d) {
   return (n_q + 15) / 16 * d->B * d->H <= kUnits;
 }
 
+// The un-evicted call of few query tiles over a short prompt: one of the narrow kernels instead of a tiled one on splits of the key axis and a
+// merge, as long as the key axis, which each of their workgroups walks alone, is not too long for the launch (us a call,
+// narrow / tiled.  bf16, head_dim 128: 4 heads x 64 queries, 1064 keys 11 / 17, 3064 21 / 21; 32 x 256, 1256 14 / 29, 5256
+// 42 / 45, 8256 65 / 56; 64 x 256, 1256 26 / 30, 3256 59 / 50; head_dim 64: 4 x 64, 3064 15.5 / 17.0, 5064 22 / 19; 32 x 256, 8256 35 / 38; 32 x 400,
+// 5400 38 / 41, 8400 56 / 55.  fp32, 16 queries a workgroup: 4 x 36, head_dim 128, 336 keys 14 / 94, 2936 74 / 141; 16 x 256, head_dim 64,
+// 3156 42 / 80; 32: 32 x 256, 2900 + 256 keys 76 / 82 and 140 / 148, 32 x 512, 1512 70 / 80 and 139 / 152, 3412 143 / 131 and 296 / 246.)
+bool attend_full_is_narrow(const maskkv_desc* d, const Lens& lens) {
+  const int64_t n_q = (int64_t)d->n_resp * query_heads_per_kv(d), groups = (n_q + 31) / 32 * d->B * d->H;
+  int64_t keys = 0;
+  for (int b = 0; b < d->B; ++b) keys = max(keys, (int64_t)lens.P[b] + d->n_resp);
+  if (d->dtype == MASKKV_BF16) {
+    const bool wide = d->d == 128;
+    if (groups <= kUnits) return keys <= (wide ? 2700 + 10 * groups : 3800 + 20 * groups);
+    return groups <= 2 * kUnits && keys <= (wide ? 1800 : 5000);
+  }
+  if (attend_is_small(d)) return keys <= 5000;
+  return groups <= kUnits ? keys <= 3200 : groups <= 2 * kUnits && keys <= 1500;
+}
+
 // Heads are only put in order where not every workgroup of the tiled kernel starts at once.
 bool attend_is_ordered(const maskkv_desc* d, bool full, int64_t capacity) {
   if (full || attend_is_narrow(d, full, capacity)) return false;
@@ -1176,7 +1208,7 @@ int launch_attend(const maskkv_desc* d, const Lens& lens, bool full, const View&
     prm.part_ml = reinterpret_cast<float2*>(reinterpret_cast<char*>(workspace) +
                                             (rows * d->d * sizeof(float) + 255) / 256 * 256);
   }
-  if (attend_is_narrow(d, full, capacity)) {
+  if (full ? attend_full_is_narrow(d, lens) : attend_is_narrow(d, full, capacity)) {
     if (d->dtype == MASKKV_BF16) return d->d == 128 ? launch_attend_pairs<128>(prm, stream) : launch_attend_pairs<64>(prm, stream);
     if (attend_is_small(d)) return d->d == 128 ? launch_attend_small<128>(prm, stream) : launch_attend_small<64>(prm, stream);
     return d->d == 128 ? launch_attend_narrow<128>(prm, stream) : launch_attend_narrow<64>(prm, stream);

@@ -35,5 +35,5 @@ def test_every_head_is_served_once(d, B, H, n, kind):
         rows = slice(int(cu[i]), int(cu[i + 1]))
         k, v = torch.cat([Kc[rows], K[i // H, i % H]]).double(), torch.cat([Vc[rows], V[i // H, i % H]]).double()
         p = torch.softmax(Q[i // H, i % H].double() @ k.T / d ** 0.5, dim=1)
-        # probabilities and results are rounded to bf16 (2^-9 each)
-        assert ((O[i // H, i % H].double() - p @ v).abs() <= 2.0 ** -8 * (p @ v.abs())).all(), i
+        # probabilities and results are rounded to bf16's 8 significant bits (2^-8 each)
+        assert ((O[i // H, i % H].double() - p @ v).abs() <= 2.0 ** -7 * (p @ v.abs())).all(), i
