@@ -1347,7 +1347,7 @@ struct Packing {
         continue;
       }
       const int run = plan.runs;
-      int side_of[MASKKV_MAX_BATCH] = {};  // heads of a sequence in this round
+      int side_of[MASKKV_MAX_BATCH] = {};  // heads of a sequence in the round
       for (int from = 0; from < n; from += half) {
         int room = half;
         for (int i = first; i < (mixed ? B : first + 1) && room > 0; ++i) {
