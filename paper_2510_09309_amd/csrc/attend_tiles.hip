@@ -107,7 +107,8 @@ __device__ __forceinline__ int head_of_rank(const AttendParams& prm, int rank, i
   return head;
 }
 
-template <int D, bool HALVES>
+// RANKED: the heads are taken by rank (an instantiation of its own: as a branch it costs the other calls 0.5 %).
+template <int D, bool HALVES, bool RANKED>
 __global__ __launch_bounds__(kWaves * 64) void attend_tiles_kernel(const AttendParams prm) {
   using C = TileCfg<D, HALVES>;
   extern __shared__ __attribute__((aligned(1024))) char tiles_lds[];
@@ -117,22 +118,17 @@ __global__ __launch_bounds__(kWaves * 64) void attend_tiles_kernel(const AttendP
   // split) get consecutive slots of one XCD, and their K/V rows come from HBM once.  Ordered heads are dealt to the XCDs in
   // turn, otherwise each XCD takes a run of units.
   const int qtiles = (prm.n_q + C::kQueries - 1) / C::kQueries;
-  const bool ordered = prm.order || prm.ranked;
+  const bool ordered = RANKED || prm.order;
   const int slot = blockIdx.x / 8 + (ordered ? 0 : blockIdx.x % 8 * (gridDim.x / 8));
   const int unit = ordered ? (slot / qtiles) * 8 + blockIdx.x % 8 : slot / qtiles;  // (head, split) pair
   const int qtile = slot % qtiles;
   if (unit >= prm.BH * prm.n_splits) return;
   int c0 = 0, c1 = 0;  // rows of the packed segment
   int bh;
-  if (prm.ranked) {  // (heads are only ordered without splits)
+  if constexpr (RANKED)  // (heads are only ordered without splits)
     bh = head_of_rank(prm, unit, c0, c1);
-  } else {
+  else
     bh = __builtin_amdgcn_readfirstlane(prm.order ? prm.order[unit] : unit / prm.n_splits);
-    if (!prm.full) {
-      c0 = (int)min((int64_t)prm.cu[bh], prm.capacity);
-      c1 = (int)min((int64_t)prm.cu[bh + 1], prm.capacity);
-    }
-  }
   const int split = ordered ? 0 : unit % prm.n_splits;
   const int b = bh / prm.H;
   const int h = bh % prm.H;
@@ -148,6 +144,10 @@ __global__ __launch_bounds__(kWaves * 64) void attend_tiles_kernel(const AttendP
   if (prm.full) {
     len_b = prm.lens.P[b] + prm.n_resp;
   } else {
+    if constexpr (!RANKED) {
+      c0 = (int)min((int64_t)prm.cu[bh], prm.capacity);
+      c1 = (int)min((int64_t)prm.cu[bh + 1], prm.capacity);
+    }
     a_k = prm.Kc + (int64_t)c0 * C::kRowB;
     a_v = prm.Vc + (int64_t)c0 * C::kRowB;
     len_a = c1 - c0;
@@ -433,12 +433,12 @@ __global__ __launch_bounds__(kWaves * 64) void attend_tiles_kernel(const AttendP
   }
 }
 
-template <int D, bool HALVES>
+template <int D, bool HALVES, bool RANKED>
 int launch(const AttendParams& prm, unsigned groups, hipStream_t stream) {
   using C = TileCfg<D, HALVES>;
   static bool raised = false;  // one-time opt-in to more than the default dynamic LDS size
   if (!raised) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attend_tiles_kernel<D, HALVES>),
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attend_tiles_kernel<D, HALVES, RANKED>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, C::kLds);
     if (e != hipSuccess) {
       set_error("attend: cannot raise dynamic LDS limit: %s", hipGetErrorString(e));
@@ -447,8 +447,14 @@ int launch(const AttendParams& prm, unsigned groups, hipStream_t stream) {
     }
     raised = true;
   }
-  hipLaunchKernelGGL((attend_tiles_kernel<D, HALVES>), dim3(groups), dim3(kWaves * 64), C::kLds, stream, prm);
+  hipLaunchKernelGGL((attend_tiles_kernel<D, HALVES, RANKED>), dim3(groups), dim3(kWaves * 64), C::kLds, stream, prm);
   return check_launch("attend (tiles)");
+}
+
+template <bool HALVES>
+int launch(const AttendParams& prm, int d, unsigned groups, hipStream_t stream) {
+  if (prm.ranked) return d == 128 ? launch<128, HALVES, true>(prm, groups, stream) : launch<64, HALVES, true>(prm, groups, stream);
+  return d == 128 ? launch<128, HALVES, false>(prm, groups, stream) : launch<64, HALVES, false>(prm, groups, stream);
 }
 
 }  // namespace
@@ -464,8 +470,7 @@ int attend_tiles_queries(int64_t units, int n_q, bool full) {
 int launch_attend_tiles(const AttendParams& prm, int d, int queries, hipStream_t stream) {
   const int64_t qtiles = (prm.n_q + queries - 1) / queries, units = (int64_t)prm.BH * prm.n_splits;
   const unsigned groups = (unsigned)(prm.order || prm.ranked ? (units + 7) / 8 * 8 * qtiles : (units * qtiles + 7) / 8 * 8);
-  if (queries == 128) return d == 128 ? launch<128, true>(prm, groups, stream) : launch<64, true>(prm, groups, stream);
-  return d == 128 ? launch<128, false>(prm, groups, stream) : launch<64, false>(prm, groups, stream);
+  return queries == 128 ? launch<true>(prm, d, groups, stream) : launch<false>(prm, d, groups, stream);
 }
 
 }  // namespace maskkv
