@@ -1113,7 +1113,7 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
   if (threadIdx.x < 3) *in_lds<int>(lds0 + C::kOffBad + threadIdx.x * 4) = threadIdx.x == 0 ? redo : 0;
   for (int i = threadIdx.x; i < 2 * kWaves * kKeys; i += kThreads) *in_lds<float>(lds0 + C::kOffCs + i * 4) = 0.f;
   if (threadIdx.x < 2 * kWaves) *in_lds<float>(lds0 + C::kOffMass + threadIdx.x * 4) = 0.f;
-  // (all but the second step's; that is waited for with the first step's sums)
+  // (all but the second chunk's keys: each group of waves waits for its part of them before the other one forms that chunk, see below)
   asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"i"(1 + kMoves) : "memory");
 #pragma unroll
   for (int ks = 0; ks < S; ++ks) asm volatile("" : "+v"(qf[ks]));
@@ -1150,7 +1150,11 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
     next = ahead;
     advance();
   };
-  if (second) asm volatile("s_barrier" ::: "memory");
+  // The first group forms the second chunk between this group's matrix and vector phase of the first, i.e. before this group has waited
+  // for anything else: its part of that chunk's keys has to be there by now (the third's, kMoves transfers, may be in flight).  It costs
+  // nothing, as the barrier is a matrix phase of the first group away.  (That group's part is waited for in its first vector phase, which
+  // ends before this group forms the second chunk; halves move their own keys.)
+  if (second) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"i"(kMoves) : "memory");
 
   if (HALVES && mine == 0) {  // no such half is in any round: it only meets the other's barriers
     for (int s = 0; s < count(team - (int)gridDim.x); ++s) {
@@ -1161,6 +1165,7 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
     if (!second) end_vector();
     return;
   }
+  __builtin_assume(mine > 0);  // (a workgroup that no round has a chunk for is not launched, see Packing)
   if (rb * 32 >= prm.rows) {  // no rows for this wave: it only helps to move keys and to add columns
     for (int s = 0; s < mine; ++s) {
       end_matrix(s);
