@@ -71,7 +71,7 @@ __global__ __launch_bounds__(kThreads, 2) void score_rows_kernel(const RowsParam
   const int b = blockIdx.z, h = blockIdx.y, bh = b * prm.H + h;
   const int P = prm.lens.P[b], N = P + prm.n_resp;
   const char* keys = prm.K.row(b, h, 0);
-  float mass = 0.f;
+  double mass = 0.;  // (in fp32 the groups' sums, one after the other, would lose more than the two passes' tree does)
   float col[NT];
   if (MANY)
 #pragma unroll
@@ -143,7 +143,7 @@ __global__ __launch_bounds__(kThreads, 2) void score_rows_kernel(const RowsParam
       if (n == 0) wave_sum[wave][4 * g + i] = make_float2(lp[i], lr[i]);
     }
     __syncthreads();
-    float w[4];
+    float w[4], share = 0.f;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       float sp = 0.f, sr = 0.f;
@@ -154,8 +154,9 @@ __global__ __launch_bounds__(kThreads, 2) void score_rows_kernel(const RowsParam
         sr += x.y;
       }
       w[i] = q0 + 4 * g + i < prm.n_query ? 1.f / (sp + sr) : 0.f;
-      mass += sp * w[i];
+      share += sp * w[i];
     }
+    mass += share;
     // ---- column sums
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
@@ -171,8 +172,8 @@ __global__ __launch_bounds__(kThreads, 2) void score_rows_kernel(const RowsParam
     const float v = sum_quarters(col[t]);
     if (lane < 16 && key < P) out[key] = v;
   }
-  mass = sum_quarters(mass);  // (every lane of a quarter has the same)
-  if (threadIdx.x == 0 && prm.mass) prm.mass[part] = mass;
+  const float all = sum_quarters((float)mass);  // (every lane of a quarter has the same)
+  if (threadIdx.x == 0 && prm.mass) prm.mass[part] = all;
 }
 
 template <int D, int NT>

@@ -406,15 +406,16 @@ __global__ __launch_bounds__(256) void score_merge_kernel(const ScoreParams prm)
   if (threadIdx.x == 0 && prm.prompt_mass) prm.prompt_mass[bh] = red[0];
 }
 
-// More than one query group: scores = sum of the groups' column sums, added in group order.
+// More than one query group: scores = sum of the groups' column sums, added in group order.  The masses are added in 64 bits: of up to 512
+// parts one after the other, the last additions in fp32 would each round as much as the whole result does (256 parts: 2e-7 of the mass).
 __global__ __launch_bounds__(256) void score_group_sum_kernel(const ScoreParams prm, int nqg) {
   const int bh = blockIdx.y;
   const int P = prm.lens.P[bh / prm.H];
   const int j = (int)blockIdx.x * 256 + (int)threadIdx.x;
   if (j == 0 && prm.unit_mass && prm.prompt_mass) {
-    float m = 0.f;
+    double m = 0.;
     for (int i = 0; i < nqg; ++i) m += prm.unit_mass[(int64_t)bh * nqg + i];
-    prm.prompt_mass[bh] = m;
+    prm.prompt_mass[bh] = (float)m;
   }
   if (j >= P) return;
   const float* src = prm.group_sums + (int64_t)bh * nqg * prm.group_stride + j;

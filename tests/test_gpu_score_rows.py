@@ -44,3 +44,21 @@ def test_against_float64(d, n, H, g, Ps):
     assert torch.equal(mass, mass2)
     for b, P in enumerate(Ps):
         assert torch.equal(again[b * H:(b + 1) * H, :P], scores[b * H:(b + 1) * H, :P])
+
+
+@pytest.mark.parametrize("d,n,H,g,B,P", [(64, 64, 2, 64, 1, 300), (128, 96, 2, 32, 1, 300), (64, 60, 32, 4, 16, 60)])
+def test_masses_of_many_groups_of_rows(d, n, H, g, B, P):
+    """256 and 192 workgroups a head, and 15 groups of a head in one: adding their masses loses less than rounding the result does."""
+    m = hp.mk()
+    gen = torch.Generator(device="cuda").manual_seed(d + n)
+    Q = torch.randn((B, H * g, n, d), generator=gen, device="cuda")
+    K = torch.randn((B, H, P + n, d), generator=gen, device="cuda")
+    desc = m.Desc(B=B, H=H, d=d, dtype=m.MASKKV_F32, n_resp=n, P_max=P, q_per_kv=g)
+    scores, mass = torch.empty((B * H, P), device="cuda"), torch.empty((B * H,), device="cuda")
+    m.maskkv_score(desc, Q, K, 0.0, scores, P, mass, hp.workspace(m.maskkv_score_workspace_bytes(desc)))
+    A = torch.softmax(Q.double().view(B * H, g * n, d) @ K.double().view(B * H, P + n, d).transpose(1, 2).contiguous() / d ** 0.5, dim=2)
+    want = A[:, :, :P].sum((1, 2))
+    # a row's share is off by some 2^-22, at random, so the mean of a thousand rows or more by 2^-26; the quarters of 16 rows are added
+    # and stored in fp32 (once, or 192 times at random), and the result is rounded by up to 2^-24
+    rms = ((mass.double() / want - 1) ** 2).mean().sqrt()
+    assert float(rms) <= 2.0 ** -24
