@@ -244,6 +244,20 @@ __device__ __forceinline__ float wave_sum(float v) {
   return as_f32(b0) + as_f32(b1);
 }
 
+// The sum of the waves' masses, by halves: in turn, the last additions would each round as much as the whole does (two sequences of 14k and
+// 24k keys: errors against 64 bits of 4.3e-8, the two passes 3.2e-8).
+template <int N>
+__device__ __forceinline__ float sum_of_waves(uint32_t lds) {
+  float v[N];
+#pragma unroll
+  for (int w = 0; w < N; ++w) v[w] = *in_lds<const float>(lds, w * 4);
+#pragma unroll
+  for (int n = N / 2; n > 0; n /= 2)
+#pragma unroll
+    for (int w = 0; w < n; ++w) v[w] += v[w + n];
+  return v[0];
+}
+
 // ---- response span: row references, zeroed sums, and the voting rows in the order in which the sweep reads them.
 // A workgroup serves BLOCKS blocks of 32 rows of a unit; 8 / BLOCKS waves share a block's keys, which come through LDS 128
 // at a time.  (Eight blocks where there are units enough to fill the chip: each key is then read once per unit.)
@@ -721,9 +735,7 @@ __device__ __forceinline__ void late_masses(const SweepParams& prm, uint32_t lds
     if (lane == 0) *in_lds<float>(lds0 + C::kOffMass + wave * 4) = sum;
     __syncthreads();
     if (threadIdx.x == 0 && !*in_lds<const int>(lds0 + C::kOffBad)) {
-      float m = 0.f;
-#pragma unroll
-      for (int w = 0; w < kWaves; ++w) m += *in_lds<const float>(lds0 + C::kOffMass, w * 4);
+      float m = sum_of_waves<kWaves>(lds0 + C::kOffMass);
       // (the head's other groups' are there: this thread has written them)
       m += __hip_atomic_load(&prm.mass[bh], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       __hip_atomic_store(&prm.mass[bh], m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -893,9 +905,7 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
     if (rb == 0 && good && k.ci() == lead_of(k.bh, k.nc()) && prm.mass) {
       const uint32_t ms = lds0 + C::kOffMass + (par * kWaves + wave) * 4;
       const uint32_t late = lds0 + C::kOffLate + (HALVES && second ? 4 : 0);
-      float m = 0.f;
-#pragma unroll
-      for (int w = 0; w < kTeam; ++w) m += *in_lds<const float>(ms, w * 4);
+      const float m = sum_of_waves<kTeam>(ms);
       if (m < 0.f) {  // (not known yet)
         if (ln == 0) {
           const int unit = k.unit(prm);

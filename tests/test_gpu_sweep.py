@@ -319,6 +319,26 @@ def test_prompt_mass_of_heads_of_all_kinds(P, n_m):
         assert abs(float(mass[h].double().cpu()) / want - 1.0) <= 32 * 2.0 ** -24
 
 
+@pytest.mark.parametrize("d", [128, 64])
+def test_masses_are_added_by_halves(d):
+    """The prompt masses of 256 heads.  An addition rounds by up to 2^-24, 2.4e-8 rms over all mantissas; additions by halves make up to
+    1 + 1/2 + 1/4 ... = 2 of its square, 3.4e-8, the sums of eight waves in turn 8/3 and the halves within a wave, 4.2e-8 and more."""
+    m = hp.mk()
+    H, n_m, P = 256, 256, 1000
+    gen = torch.Generator(device="cuda").manual_seed(98)
+    rnd = lambda *shape: torch.randn(shape, generator=gen, device="cuda")
+    u = rnd(1, H, 1, d)
+    u /= u.norm(dim=3, keepdim=True)
+    Q = (rnd(1, H, n_m, d) * (3.4 / d ** 0.25) + d ** 0.5 * u).bfloat16()
+    K = (rnd(1, H, P + n_m, d) * (3.4 / d ** 0.25) + rnd(1, H, P + n_m, 1) * u).bfloat16()
+    desc = m.Desc(B=1, H=H, d=d, dtype=m.MASKKV_BF16, n_resp=n_m, P_max=P)
+    scores, mass = torch.empty((H, P), device="cuda"), torch.empty(H, device="cuda")
+    m.maskkv_score(desc, Q, K, 0.0, scores, P, mass, hp.workspace(m.maskkv_score_workspace_bytes(desc)))
+    want = torch.stack([torch.softmax(Q[0, h].double() @ K[0, h].double().T / d ** 0.5, dim=1)[:, :P].sum() for h in range(H)])
+    rms = ((mass.double() / want - 1) ** 2).mean().sqrt()
+    assert float(rms) <= 4.0e-8
+
+
 @pytest.mark.parametrize("P,H,lo,hi", [(100, 64, 16.2, 16.9), (128, 64, 16.2, 16.9), (129, 32, 15.5, 16.5), (1000, 16, 30.0, 36.0), (32768, 2, 38.3, 38.6)])
 def test_row_sums_in_the_wide_unit(P, H, lo, hi):
     """Chunks whose row sums are 2^lo .. 2^hi of the response span's, up to 256 of them just below the limit of the exchange: the
