@@ -1033,7 +1033,7 @@ bool attend_is_narrow(const maskkv_desc* d, bool full, int64_t capacity) {
   const int64_t groups = (n_q + 31) / 32 * heads;
   if (d->dtype == MASKKV_BF16) {
     if (d->d == 64) return groups <= 5 * kUnits / 2;
-    return groups <= kUnits || (groups <= 2 * kUnits && capacity / heads + d->n_resp <= 1280);
+    return groups <= kUnits || (groups <= 2 * kUnits && capacity / heads <= 1280 - d->n_resp);  // (capacity may be any int64_t)
   }
   const int64_t tiled = (n_q + AttCfg<128>::kQPerBlock - 1) / AttCfg<128>::kQPerBlock * heads;
   return groups <= 4 * kUnits * ((tiled + kUnits - 1) / kUnits);
