@@ -70,6 +70,15 @@ int maskkv_bench_score_marked(const maskkv_desc* desc, const maskkv_tensor* Q_ma
  */
 int maskkv_bench_hold_sweep(int64_t age_us, void* stream);
 
+/*
+ * How maskkv_score would score a description.  plan: HOST array of 5:
+ *   [0] workgroups of the single sweep, or 0 where there is none; [1] how many of these are launched: fewer where halves of
+ *   workgroups have chunks of their own; [2] sets of workgroups that a head's groups of 256 voting rows are dealt to; [3] rounds of heads;
+ *   [4] workgroups per head of the one-pass kernel of short fp32 prompts, or 0.  With [0] and [4] zero it takes two passes.
+ * Enqueues nothing.  Errors are reported through maskkv_last_error() of libmaskkv.so.
+ */
+int maskkv_bench_score_plan(const maskkv_desc* desc, int32_t* plan);
+
 #ifdef __cplusplus
 }
 #endif

@@ -1,10 +1,10 @@
 """ctypes binding of libmaskkv_bench.so (``include/maskkv_bench.h``): measurement probes, maskkv_score with stage
-marks, and a mark that makes it take its fallback.  For benchmark harnesses and their tests only; nothing of the method's path goes through this module."""
+marks, a mark that makes it take its fallback, and the plan that it makes.  For benchmark harnesses and their tests only; nothing of the method's path goes through this module."""
 from __future__ import annotations
 
 import ctypes as ct
 import os
-from typing import Optional, Sequence
+from typing import NamedTuple, Optional, Sequence
 
 import torch
 
@@ -12,7 +12,8 @@ from . import binding as _b
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.environ.get("MASKKV_BENCH_LIB_PATH", os.path.join(_HERE, "libmaskkv_bench.so"))
-SYMBOLS = ["maskkv_bench_last_error", "maskkv_bench_probe", "maskkv_bench_score_marked", "maskkv_bench_hold_sweep"]
+SYMBOLS = ["maskkv_bench_last_error", "maskkv_bench_probe", "maskkv_bench_score_marked", "maskkv_bench_hold_sweep",
+           "maskkv_bench_score_plan"]
 
 
 def _load() -> ct.CDLL:
@@ -59,6 +60,21 @@ def maskkv_bench_score_marked(desc: "_b.Desc", Q_mask, K_full, scale: float, sco
 def maskkv_bench_hold_sweep(age_us: int, stream=None) -> None:
     """Mark the device's sweep as taken ``age_us`` microseconds ago (negative: as free)."""
     _b._check(_lib.maskkv_bench_hold_sweep(ct.c_int64(age_us), _b._stream(stream)), "maskkv_bench_hold_sweep")
+
+
+class ScorePlan(NamedTuple):
+    """How maskkv_score would score a description (see maskkv_bench.h)."""
+    groups: int
+    grid: int
+    subsets: int
+    rounds: int
+    parts: int
+
+
+def maskkv_bench_score_plan(desc: "_b.Desc") -> ScorePlan:
+    plan = (ct.c_int32 * 5)()
+    _b._check(_lib.maskkv_bench_score_plan(ct.byref(desc.c()), plan), "maskkv_bench_score_plan")
+    return ScorePlan(*plan)
 
 
 def raw_library() -> ct.CDLL:

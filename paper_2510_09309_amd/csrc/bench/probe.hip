@@ -4,6 +4,7 @@
 //   maskkv_bench_score_marked  maskkv_score with HIP events recorded at its stage boundaries (it calls the body
 //                              of maskkv_score inside libmaskkv.so);
 //   maskkv_bench_hold_sweep    makes maskkv_score take its fallback.
+//   maskkv_bench_score_plan    how maskkv_score would score a description.
 #include <stdio.h>
 
 #include "../kernels.hpp"
@@ -344,6 +345,14 @@ int maskkv_bench_probe(int which, int32_t iters, const void* src, void* dst, int
 }
 
 int maskkv_bench_hold_sweep(int64_t age_us, void* stream) { return hold_sweep(age_us, reinterpret_cast<hipStream_t>(stream)); }
+
+int maskkv_bench_score_plan(const maskkv_desc* desc, int32_t* plan) {
+  SweepPlan p;
+  if (int e = score_plan(desc, &p)) return e;
+  const int32_t v[5] = {p.groups, p.grid, p.subsets, p.rounds, p.parts};
+  for (int i = 0; i < 5; ++i) plan[i] = v[i];
+  return MASKKV_OK;
+}
 
 int maskkv_bench_score_marked(const maskkv_desc* desc, const maskkv_tensor* Q_mask, const maskkv_tensor* K_full,
                               float scale, float* scores, int64_t score_stride, float* prompt_mass, void* workspace,

@@ -97,5 +97,7 @@ int launch_value_shift(const void* v_now, const void* v_prev, int64_t n, int wid
 int score_entry(const maskkv_desc* desc, const maskkv_tensor* Q_mask, const maskkv_tensor* K_full, float scale,
                 float* scores, int64_t score_stride, float* prompt_mass, void* workspace, size_t workspace_bytes,
                 void* stream, void* const* events);
+// The plan that it makes for a description.
+int score_plan(const maskkv_desc* desc, SweepPlan* plan);
 
 }  // namespace maskkv

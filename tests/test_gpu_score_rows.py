@@ -31,6 +31,8 @@ def test_against_float64(d, n, H, g, Ps):
     scores, mass = torch.full((B * H, P_max + 3), float("nan"), device="cuda"), torch.full((B * H,), float("nan"), device="cuda")
     ws = hp.workspace(m.maskkv_score_workspace_bytes(desc))
     m.maskkv_score(desc, Q, K, 0.0, scores, P_max + 3, mass, ws)
+    from paper_2510_09309_amd import bench_binding as bb
+    assert (bb.maskkv_bench_score_plan(desc).parts > 0) == (P_max + n <= 3072)
     rtol = RTOL if P_max + n <= 3072 else RTOL_TWO_PASSES
     for b, P in enumerate(Ps):
         for h in range(0, H, 1 + H // 8):
@@ -46,14 +48,16 @@ def test_against_float64(d, n, H, g, Ps):
         assert torch.equal(again[b * H:(b + 1) * H, :P], scores[b * H:(b + 1) * H, :P])
 
 
-@pytest.mark.parametrize("d,n,H,g,B,P", [(64, 64, 2, 64, 1, 300), (128, 96, 2, 32, 1, 300), (64, 60, 32, 4, 16, 60)])
-def test_masses_of_many_groups_of_rows(d, n, H, g, B, P):
+@pytest.mark.parametrize("d,n,H,g,B,P,parts", [(64, 64, 2, 64, 1, 300, 256), (128, 96, 2, 32, 1, 300, 192), (64, 60, 32, 4, 16, 60, 1)])
+def test_masses_of_many_groups_of_rows(d, n, H, g, B, P, parts):
     """256 and 192 workgroups a head, and 15 groups of a head in one: adding their masses loses less than rounding the result does."""
     m = hp.mk()
     gen = torch.Generator(device="cuda").manual_seed(d + n)
     Q = torch.randn((B, H * g, n, d), generator=gen, device="cuda")
     K = torch.randn((B, H, P + n, d), generator=gen, device="cuda")
     desc = m.Desc(B=B, H=H, d=d, dtype=m.MASKKV_F32, n_resp=n, P_max=P, q_per_kv=g)
+    from paper_2510_09309_amd import bench_binding as bb
+    assert bb.maskkv_bench_score_plan(desc).parts == parts
     scores, mass = torch.empty((B * H, P), device="cuda"), torch.empty((B * H,), device="cuda")
     m.maskkv_score(desc, Q, K, 0.0, scores, P, mass, hp.workspace(m.maskkv_score_workspace_bytes(desc)))
     A = torch.softmax(Q.double().view(B * H, g * n, d) @ K.double().view(B * H, P + n, d).transpose(1, 2).contiguous() / d ** 0.5, dim=2)

@@ -89,20 +89,26 @@ def test_calls_on_two_streams_at_once():
     assert torch.equal(after[0][:, :batches[0].P[0]], want[0][0][:, :batches[0].P[0]])
 
 
-@pytest.mark.parametrize("d,n,H,g,Ps,fallback", [
-    (128, 40, 2, 1, tuple(range(100, 6100, 250)), False),                   # 24 lengths: rounds of several sequences
-    (64, 33, 1, 1, tuple((i * 37) % 64 * 33 for i in range(64)), False),    # 64 sequences, one of them empty
-    (128, 32, 11, 1, tuple(range(128, 8193, 128)), False),                  # more runs than a plan has room for
-    (128, 100, 2, 7, (3000,), False), (128, 100, 2, 7, (3000,), True),      # three groups of rows: a workgroup each
-    (128, 256, 3, 4, (5000, 300, 9000), False), (128, 256, 3, 4, (5000, 300, 9000), True),  # four: one workgroup for all or two
-    (64, 512, 32, 1, (4100, 2049), False), (64, 512, 32, 1, (4100, 2049), True),
+@pytest.mark.parametrize("d,n,H,g,Ps,fallback,halves,subsets", [
+    (128, 40, 2, 1, tuple(range(100, 6100, 250)), False, False, 1),                   # 24 lengths: rounds of several sequences
+    (64, 33, 1, 1, tuple((i * 37) % 64 * 33 for i in range(64)), False, True, 1),     # 64 sequences, one of them empty
+    (128, 32, 11, 1, tuple(range(128, 8193, 128)), False, True, 1),                   # more runs than a plan has room for
+    (128, 100, 2, 7, (3000,), False, False, 1), (128, 100, 2, 7, (3000,), True, False, 1),  # three groups of rows: one workgroup for all
+    (128, 256, 3, 4, (5000, 300, 9000), False, False, 1), (128, 256, 3, 4, (5000, 300, 9000), True, False, 1),  # four
+    (64, 512, 32, 1, (4100, 2049), False, False, 1), (64, 512, 32, 1, (4100, 2049), True, False, 1),
+    # groups of rows dealt to several workgroups: one each, of one or several sequences, one of them empty, and two or four each
+    (128, 256, 4, 4, (2000,), False, False, 4), (128, 256, 4, 4, (2000,), True, False, 4),
+    (64, 512, 4, 7, (2500,), False, False, 14), (64, 512, 4, 7, (2500,), True, False, 14),
+    (128, 512, 4, 7, (1000, 300, 0), False, False, 14), (128, 512, 4, 7, (1000, 300, 0), True, False, 14),
+    (128, 512, 2, 7, (3000, 500), False, False, 7), (128, 512, 2, 7, (3000, 500), True, False, 7),
+    (128, 1000, 8, 4, (1000,), False, False, 4), (128, 1000, 8, 4, (1000,), True, False, 4),
     # at most 128 rows: halves of workgroups, also in rounds that have no chunk for them, or in none
-    (128, 69, 32, 1, (1135, 3503, 1500, 2000, 2900, 2300, 1700, 1300), False), (128, 69, 32, 1, (1135, 3503, 1500), True),
-    (64, 100, 5, 1, (16500, 300), False), (64, 100, 5, 1, (16500, 300), True),
-    (128, 128, 16, 1, (12000,), False), (64, 18, 12, 7, (9001, 100, 5000), False), (128, 1, 16, 1, (12289, 1, 0, 129), False),
-    (128, 66, 9, 1, (27000,), False), (128, 99, 8, 1, (16700,), False),    # heads in one half each, a head across the halves
-    (64, 33, 2, 1, tuple((i * 37) % 64 * 33 for i in range(64)), False)])   # more runs than a plan has room for, in halves
-def test_rounds_of_heads_and_groups_of_rows(d, n, H, g, Ps, fallback):
+    (128, 69, 32, 1, (1135, 3503, 1500, 2000, 2900, 2300, 1700, 1300), False, True, 1), (128, 69, 32, 1, (1135, 3503, 1500), True, True, 1),
+    (64, 100, 5, 1, (16500, 300), False, True, 1), (64, 100, 5, 1, (16500, 300), True, True, 1),
+    (128, 128, 16, 1, (12000,), False, True, 1), (64, 18, 12, 7, (9001, 100, 5000), False, True, 1), (128, 1, 16, 1, (12289, 1, 0, 129), False, True, 1),
+    (128, 66, 9, 1, (27000,), False, False, 1), (128, 99, 8, 1, (16700,), False, True, 1),    # half of the waves idle; a head across the halves
+    (64, 33, 2, 1, tuple((i * 37) % 64 * 33 for i in range(64)), False, True, 1)])    # more runs than a plan has room for, in halves
+def test_rounds_of_heads_and_groups_of_rows(d, n, H, g, Ps, fallback, halves, subsets):
     """Heads against float64 (fp32 sums of products of bf16 inputs: logits of up to 2^5 binary orders)."""
     # One row's errors are not averaged with others': its logits of up to 2^5 binary orders are rounded (2^-20) once for every 16 products.
     rtol = (32 if n > 1 else d) * 2.0 ** -24
@@ -113,6 +119,8 @@ def test_rounds_of_heads_and_groups_of_rows(d, n, H, g, Ps, fallback):
     Q = (torch.randn((B, H * g, n, d), generator=gen, device="cuda") * 1.5).bfloat16()
     K = torch.randn((B, H, P_max + n, d), generator=gen, device="cuda").bfloat16()
     desc = m.Desc(B=B, H=H, d=d, dtype=m.MASKKV_BF16, n_resp=n, P_max=P_max, prompt_len=None if B == 1 else list(Ps), q_per_kv=0 if g == 1 else g)
+    plan = bb.maskkv_bench_score_plan(desc)      # (a change of the cost model could take a case past what it is here for)
+    assert plan.groups > 0 and (plan.groups > plan.grid, plan.subsets) == (halves, subsets)
     scores, mass = torch.full((B * H, P_max), float("nan"), device="cuda"), torch.full((B * H,), float("nan"), device="cuda")
     ws = hp.workspace(m.maskkv_score_workspace_bytes(desc))
     if fallback:
