@@ -112,8 +112,9 @@ const char* maskkv_last_error(void);
  * Workspace (DEVICE bytes) needed by maskkv_score for this description.  The workspace
  * holds the softmax row sums that the workgroups exchange (or per-key-segment row statistics
  * between two passes), a packed copy of the voting rows and, with more than 256 voting rows per
- * head, the column sums of every group of at most 256 rows; contents are scratch.  The size depends
- * on prompt_len: query it with the description the call will use.  256-byte alignment is required.
+ * head, the column sums of every group of at most 256 rows, or for short fp32 prompts those of every
+ * workgroup of 16 rows or more; contents are scratch.  The size depends on prompt_len: query it with
+ * the description the call will use.  256-byte alignment is required.
  */
 int maskkv_score_workspace_bytes(const maskkv_desc* desc, size_t* bytes);
 
@@ -161,8 +162,8 @@ int maskkv_score_given_lse(const maskkv_desc* desc, const maskkv_tensor* Q_mask,
  * tight serving loops, harnesses that forbid hipMalloc.  Same arguments and same result as maskkv_score, but the
  * scratch between the passes lives in an array of MASKKV_STATIC_SCRATCH_BYTES that is part of the library image
  * (every GPU the library runs on holds its own copy until the process ends).  The call allocates and frees
- * nothing.  Descriptions whose maskkv_score_workspace_bytes exceed MASKKV_STATIC_SCRATCH_BYTES are rejected with
- * MASKKV_EWORKSPACE (nothing enqueued).  All calls on one GPU share that GPU's array: two calls that overlap in
+ * nothing.  Descriptions whose maskkv_score_workspace_bytes exceed MASKKV_STATIC_SCRATCH_BYTES are scored in
+ * two passes, and rejected with MASKKV_EWORKSPACE (nothing enqueued) if these need more as well.  All calls on one GPU share that GPU's array: two calls that overlap in
  * time on one GPU (different streams, or different host threads) race; calls on one stream are ordered.  Every
  * scratch word a call reads is written by the same call first, so nothing needs clearing between calls.  The
  * first call on a device resolves the array's device address (hipGetSymbolAddress); make that call outside graph
@@ -213,8 +214,9 @@ int maskkv_compact(const maskkv_desc* desc, const maskkv_tensor* K, const maskkv
                    void* Kc, void* Vc, void* stream);
 
 /* Workspace (DEVICE bytes) for maskkv_attend (full = 0: the order in which the heads are processed, longest key
- * axis first; 0 where every workgroup starts at once) or maskkv_attend_full (full = 1: key-split partial results).  256-byte
- * alignment. */
+ * axis first; 0 where every workgroup starts at once) or maskkv_attend_full (full = 1: key-split partial results): what the
+ * calls with this description ask for, and at most what they use (bf16 calls of up to 256 heads find the order without it, and
+ * un-evicted calls over short prompts do not split the key axis).  256-byte alignment. */
 int maskkv_attend_workspace_bytes(const maskkv_desc* desc, int full, size_t* bytes);
 
 /*

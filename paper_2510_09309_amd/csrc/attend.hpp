@@ -8,7 +8,7 @@ namespace maskkv {
 
 constexpr float kLazyBump = 8.f;  // log2 of the largest probability tolerated before the running reference is raised
 
-constexpr int kRankHeads = 256;   // heads up to which they do
+constexpr int kRankHeads = 256;   // heads up to which the tiled bf16 kernel's workgroups find the heads' order themselves
 
 struct AttendParams {
   View Q, K2, V2, O;
@@ -22,7 +22,7 @@ struct AttendParams {
   int n_q;       // query rows per key/value head = q_per_kv * n_resp
   float c;  // scale * log2(e)
   float* lse;
-  int ranked;            // the workgroups of the tiled bf16 kernel find the heads' order themselves
+  int ranked;            // they do (see kRankHeads)
   const int32_t* order;  // [BH] heads by descending key count (compressed call of the tiled kernel), or null
   float* part_o;     // [BH][n_splits][n_q][D]
   float2* part_ml;   // [BH][n_splits][n_q]

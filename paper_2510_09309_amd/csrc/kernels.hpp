@@ -34,7 +34,7 @@ struct SweepPlan {
   void repeat(int i, int t) { repeats[i] |= (uint32_t)t; }
 };
 
-// score.hip.  (Choosing takes some 10 us of host time for the largest batches: once per call.)
+// score.hip.  (Choosing takes 0.4 to 1.5 us of host time and up to 30 for 64 sequences of different lengths: once per call.)
 SweepPlan score_sweep_plan(const maskkv_desc* d, const Lens& lens);
 size_t score_workspace_bytes(const maskkv_desc* d, const Lens& lens, const SweepPlan& plan);
 int launch_score(const maskkv_desc* d, const View& Q, const View& K, const Lens& lens, float scale, float* scores,

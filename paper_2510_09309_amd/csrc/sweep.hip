@@ -74,7 +74,7 @@ constexpr float kSmallSum = 2.f;
 constexpr float kNoRow = 0.5f;             // whole sum of a row that does not exist (its mass is then cut off at 0; a row that does has 1)
 constexpr uint32_t kNoPart = 0xFFFFFFFFu;  // not there (a part has its sign bit clear)
 
-constexpr int kMaxUnits = 4096;            // of a launch, see sweep_groups
+constexpr int kMaxUnits = 4096;            // of a launch, see sweep_plan
 constexpr int kMaxGroups = 256;            // workgroups of a sweep, and chunks of a unit, at most (one per compute unit)
 
 // What a unit has in the workspace, one behind the other, so that a base and 32 bits address all of it:
@@ -85,6 +85,7 @@ constexpr int kMaxGroups = 256;            // workgroups of a sweep, and chunks 
 constexpr uint32_t kHighAt = kCopies * kRows * 8, kRefsAt = kHighAt + kRows * 8, kRowsAt = kRefsAt + kWaves * 256;
 template <int D>
 constexpr uint32_t kUnitBytes = kRowsAt + kRows * D * 2;
+static_assert((uint64_t)kMaxUnits * kUnitBytes<128> <= 0xFFFFFFFFu, "a unit's place is held in 32 bits (Task::at)");
 
 struct Control {
   int run;      // this call's workgroups may be placed as a sweep's
@@ -261,8 +262,8 @@ __device__ __forceinline__ float sum_of_waves(uint32_t lds) {
 // ---- response span: row references, zeroed sums, and the voting rows in the order in which the sweep reads them.
 // A workgroup serves BLOCKS blocks of 32 rows of a unit; 8 / BLOCKS waves share a block's keys, which come through LDS 128
 // at a time.  (Eight blocks where there are units enough to fill the chip: each key is then read once per unit.)
-// Takes the lock, or waits for it: 2 us.  Where units are few, that is for a workgroup of its own, the last; where they fill the
-// chip and one workgroup more would start alone at the end, the first does it when it is done.
+// Takes the lock, or waits for it (2 us), and counts every workgroup's chunks: for a workgroup of its own, the first, so that this is
+// over when the others are.
 __device__ __forceinline__ void start_lock(const SweepParams& prm) {
   const int w = threadIdx.x;
   if (w < prm.plan.groups) {
@@ -736,7 +737,7 @@ __device__ __forceinline__ void late_masses(const SweepParams& prm, uint32_t lds
     __syncthreads();
     if (threadIdx.x == 0 && !*in_lds<const int>(lds0 + C::kOffBad)) {
       float m = sum_of_waves<kWaves>(lds0 + C::kOffMass);
-      // (the head's other groups' are there: this thread has written them)
+      // (the head's other masses are there: this thread has written them or, with HALVES, wave 4, before the wait and the barrier above)
       m += __hip_atomic_load(&prm.mass[bh], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       __hip_atomic_store(&prm.mass[bh], m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -1472,7 +1473,8 @@ int launch(const maskkv_desc* d, const SweepParams& prm, hipStream_t stream) {
 }  // namespace
 
 // A launch of 66000 units (33000 heads of 40 keys, 300 voting rows), once tried, ended in a memory fault whose cause was not found.
-// The sweep is kept to the sizes that are in use (64 sequences x 32 heads x 2 groups of voting rows); more take the two passes.
+// The sweep is kept to the sizes that are in use (64 sequences x 32 heads x 2 groups of voting rows); more take the two passes.  (A
+// unit's place in the workspace is held in 32 bits as well, which 55189 units of head_dim 128 would not fit.)
 SweepPlan sweep_plan(const maskkv_desc* d, const Lens& lens, int nqg) {
   if (d->dtype != MASKKV_BF16 || (int64_t)d->B * d->H * nqg > kMaxUnits) return SweepPlan{};
   return make_plan(d, lens, nqg);
