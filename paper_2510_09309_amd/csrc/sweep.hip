@@ -1176,16 +1176,18 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
     if (!second) end_vector();
     return;
   }
-  __builtin_assume(mine > 0);  // (a workgroup that no round has a chunk for is not launched, see Packing)
+  // (Every workgroup that is launched has a step in some round, see Packing.  `for` loops, with that assumed for the compiler, took 146.1 us
+  // for the 32k layer and 480 for the ragged scoring, these 144.9 and 477.)
   if (rb * 32 >= prm.rows) {  // no rows for this wave: it only helps to move keys and to add columns
-    for (int s = 0; s < mine; ++s) {
+    int s = 0;
+    do {
       end_matrix(s);
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       if (cur.qg == 0 && keys_at < chunks) dma_k(keys_at++);
       if (flushes) flush(done, s & 1 ^ 1, s >= 2);
       shift();
       end_vector();
-    }
+    } while (++s < mine);
     end_vector();
     if (flushes) flush(done, mine & 1 ^ 1, mine >= 2);
     if (HALVES) flush(prev, mine & 1, true);
@@ -1244,10 +1246,12 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
     vector(s, par, pc);
     end_vector();
   };
-  for (int s = 0; s < mine; s += 2) {
+  int s = 0;
+  do {
     step(s, 0, pa, pb);
     if (s + 1 < mine) step(s + 1, 1, pb, pa);
-  }
+    s += 2;
+  } while (s < mine);
   // ---- the last step: completed at once, by the first group while the second publishes it
   const int par = mine & 1;
   if (!HALVES || !prev.idle()) {
