@@ -58,7 +58,7 @@ struct TileCfg {
 // and end, found by every wave on its own: its lanes hold all heads' counts, a bit of the wanted count takes a comparison per 64
 // heads, and of the heads with that count it is the one with so many before it.  That takes about as long as the load of the head's
 // number did, which a kernel in front of this one had sorted (us a call, with it and without: 256 heads x 512 queries over 576 ...
-// 1536 keys 79.2 / 78.0, over 812 keys 80.2 / 77.7; 192 x 190 over 720, head_dim 64, 30.9 / 28.9; 112 x 262 over 562 38.3 / 36.8).  Not
+// 1536 keys 79.2 / 78.0 (among other calls 83.6 / 81.9, on another board 81.1 / 81.0), over 812 keys 80.2 / 77.7; 192 x 190 over 720, head_dim 64, 30.9 / 28.9; 112 x 262 over 562 38.3 / 36.8).  Not
 // beyond 256 heads: with eight of them a lane 448 heads x 300 took 69 instead of 63.
 __device__ __forceinline__ int head_of_rank(const AttendParams& prm, int rank, int& c0, int& c1) {
   constexpr int N = kRankHeads / 64;

@@ -27,7 +27,8 @@ constexpr int kCmpRows = 2;  // destination rows per thread
 
 // Up to this many heads a wave holds the ends of all of them in its lanes: what precedes the rows themselves is then two loads in turn,
 // the ends and the positions, instead of five (the number of rows, two of the search, the walk, the positions).  256 heads x 64 ...
-// 1024 rows, with the selection: 29.5 -> 28.9 us; 4 heads in a layer over 30k tokens 110.6 -> 109.1.
+// 1024 rows, with the selection: 29.5 -> 28.9 us in a loop of their own (33.9 -> 33.5 among other calls, twice what two runs differ by);
+// 4 heads in a layer over 30k tokens 110.6 -> 109.1.
 constexpr int kFewHeads = 256;
 
 __global__ __launch_bounds__(256) void compact_few_kernel(const CompactParams prm) {

@@ -23,13 +23,13 @@
 // waits for a sum that is not needed yet, and every wait is bounded: if the workgroups turn out not to be all resident, or a
 // row's sum leaves the range of the integers, a two-pass fallback at the end of the same kernel does the work.
 //
-// What bounds it: a step of 6700 to 7100 cycles, 2048 of them MFMAs.  A wave issues an instruction every 4 to 5 cycles, a matrix phase
+// What bounds it: a step of 5900 to 7100 cycles, 2048 of them MFMAs.  A wave issues an instruction every 4 to 5 cycles, a matrix phase
 // has 1800 cycles of them, a vector phase 1300 to 1800, and the two waves of a SIMD share the vector pipe, where v_exp_f32
-// takes 8 cycles and an MFMA about as many.  In a loop of such calls the board is at its 1400 W and the clock 10 % below that of
-// short calls (2.1 against 2.3 GHz).  us a call, with both groups of waves in the same phase, chunks dealt out end to end and keys
-// transferred for every group of rows before: 32 heads x 128 with 256 rows, 4k keys 28.7 -> 27.1, 8k 39 -> 36.6, 32k 120 -> 114; 4
-// heads with 1792 rows over 30k keys 93.5 -> 87.4; the ragged batch of perf/cases.py 518 -> 466 (8 more with 64-bit
-// addresses formed for every access, 6 more with the start kernel's loads in turn).  (Without transfers of keys, with
+// takes 8 cycles and an MFMA about as many.  In a loop of nothing but long calls the board is at its 1400 W and the clock 10 % below that
+// of short calls (2.1 against 2.3 GHz); as part of a layer the sweep is below that.  us a call, with both groups of waves in the same
+// phase, chunks dealt out end to end and keys transferred for every group of rows before: 32 heads x 128 with 256 rows, 4k keys 28.7
+// -> 27.1, 8k 39 -> 36.6, 32k 120 -> 114; 4 heads with 1792 rows over 30k keys 93.5 -> 87.4; the ragged batch of perf/cases.py 518 ->
+// 466 (8 more with 64-bit addresses formed for every access, 6 more with the start kernel's loads in turn).  (Without transfers of keys, with
 // wrong results, the ragged batch took 420 instead of 505, without loads of rows 455, without the exchange 465.)  Slower: raised
 // wave priority in the vector phase or for waves 4-7; a first sum per XCD that the last of its workgroups adds to the whole
 // (two latencies instead of one); 2 or 8 copies of the sums.
@@ -1336,7 +1336,7 @@ struct Layout {
 // other, so they work on it at the same time: a round puts as many heads side by side as there are workgroups for, the longest
 // first, and is repeated for the next heads of the same sequences as long as these last.  (Dealt out end to end, heads straddle
 // two rounds, and the first workgroups of such a head wait for the last: 503 instead of 481 us for the ragged batch, whose 18112
-// chunks take 75 rounds of 256 workgroups instead of 71.)  Many sequences can make more runs than the plan has room for; each
+// chunks take 74 rounds of 256 workgroups instead of 71.)  Many sequences can make more runs than the plan has room for; each
 // sequence then has rounds of its own.
 //
 // A head's groups of voting rows are one workgroup's turn, which needs its keys once, unless that leaves workgroups without work: a
