@@ -564,7 +564,9 @@ int launch_score_t(ScoreParams& prm, const TileMap& map2, hipStream_t stream, vo
 
 namespace {
 
-// Workspace: [row statistics and normalisers, or what the single sweep needs][column sums per query group]
+// Workspace: [row statistics and normalisers, or what the single sweep needs][column sums per query group, or part, or set of workgroups].
+// Where a sweep is planned, what the two passes need is asked for all the same, in the same bytes: maskkv_score_given_lse, which
+// has the same workspace, is served by them.
 struct ScoreArea {
   size_t stats, sums, bytes;
   ScoreArea(const maskkv_desc* d, const Lens& lens, const SweepPlan& plan) {
@@ -575,10 +577,13 @@ struct ScoreArea {
     const int nqg = query_groups(d);
     stats = ((size_t)(bh * (pp + pr) * nq) * sizeof(float2) + 255) / 256 * 256;
     const size_t lse = ((size_t)(bh * nq) * sizeof(float) + 255) / 256 * 256;
+    auto columns = [&](int parts) { return parts > 1 ? (size_t)(bh * parts * group_stride(d)) * sizeof(float) : 0; };
     sums = stats + lse;
-    if (plan.groups > 0) sums = max(sums, (sweep_workspace_bytes(d, nqg, plan) + 255) / 256 * 256);
-    const int parts = max(nqg, plan.parts);  // (column sums of a head)
-    bytes = sums + (parts > 1 ? (size_t)(bh * parts * group_stride(d)) * sizeof(float) : 0);
+    bytes = sums + columns(max(nqg, plan.parts));
+    if (plan.groups > 0) {
+      sums = (sweep_workspace_bytes(d, nqg, plan) + 255) / 256 * 256;
+      bytes = max(bytes, sums + columns(plan.subsets));
+    }
   }
 };
 

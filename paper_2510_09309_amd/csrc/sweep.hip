@@ -128,7 +128,7 @@ struct SweepParams {
   uint32_t* parts;  // [units][8 waves][n_parts] bits of a chunk's part of the mass of 32 rows, or kNoPart
   int n_parts;      // chunks of the longest prompt
   int* late;        // [units] 1 + the next unit of a workgroup's list for late_masses, or 0
-  float2* stats;    // [units][kSpans][256] (reference, sum) of a span of chunks (fallback)
+  float2* stats;    // [units][spans][256] (reference, sum) of a span of chunks (fallback)
   float* out;       // [B*H*subsets][out_stride]
   int64_t out_stride;
   float* mass;      // [B*H*subsets] or null
@@ -514,7 +514,7 @@ __device__ __forceinline__ void sweep_redo(const SweepParams& prm, uint32_t lds0
       u32x4 qf[S];
 #pragma unroll
       for (int s = 0; s < S; ++s) qf[s] = *reinterpret_cast<const u32x4*>(area + kRowsAt + wave * C::kQBytes + s * 1024 + lane * 16);
-      float2* st = prm.stats + (int64_t)unit * kSpans * kRows + wave * 32 + r;  // (of query row r; one span is kRows further)
+      float2* st = prm.stats + (int64_t)unit * spans * kRows + wave * 32 + r;  // (of query row r; one span is kRows further)
       float m = kNegBig, l = 0.f;
       float nl[16];  // second pass: minus the base-2 log-sum-exp of this lane's rows
       if (second) {
@@ -1311,6 +1311,10 @@ int cus() {
 
 size_t pad256(size_t n) { return (n + 255) / 256 * 256; }
 
+// Pieces of a unit's keys in the fallback's first pass: two tasks for every compute unit, since a task costs about as much as two
+// chunks before its first one.
+int spans_of(int units) { return max(1, min(kSpans, 2 * kMaxGroups / units)); }
+
 struct Layout {
   size_t control, table, counts, mass, done, late, parts, units, stats, bytes;  // offsets from the start of the area
   int n_parts;
@@ -1326,7 +1330,7 @@ struct Layout {
     parts = late + n * sizeof(int);
     units = pad256(parts + n * kWaves * n_parts * sizeof(uint32_t));
     stats = units + n * (d->d == 128 ? kUnitBytes<128> : kUnitBytes<64>);
-    bytes = stats + n * kSpans * kRows * sizeof(float2);
+    bytes = stats + n * spans_of((int)n) * kRows * sizeof(float2);
   }
 };
 
@@ -1514,8 +1518,7 @@ int launch_sweep(const maskkv_desc* d, const View& Q, const View& K, const Lens&
   // another program's kernels, a sweep of another process among them, whose lock is its own, or of another stream: the time
   // these take has nothing to do with this call's.  Two processes that score 32k keys at once, us a call of each: 455, with 20 ms 5000.)
   prm.patience = 10000 + (int)min(x / plan.groups * 500, (int64_t)1000000);
-  // Two tasks a pass for every compute unit: a task costs about as much as two chunks before its first one.
-  prm.spans = max(1, min(kSpans, 2 * kMaxGroups / (d->B * d->H * nqg)));
+  prm.spans = spans_of(d->B * d->H * nqg);
   prm.spans2 = max(1, min(kMaxGroups, 2 * kMaxGroups / (d->B * d->H * plan.subsets)));
   prm.c = scale * kLog2e;
   const Layout l(d, nqg, plan);
