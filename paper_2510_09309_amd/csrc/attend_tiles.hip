@@ -6,22 +6,24 @@
 //   - K and V tiles come by direct transfers into two rings of four LDS slots, three tiles ahead, and no register or vector
 //     instruction touches them on the way.  V stays row-major; the A operand V^T is read with transposing LDS loads.
 //   - Waves 0-3 and 4-7 (one of each on a SIMD) run half a tile apart.  A tile is a matrix phase (its logits, and the output
-//     update of the tile before) and a vector phase (its softmax); a barrier after every phase keeps one group of waves
-//     in the one while the other is in the other.
+//     update of the tile before) and a vector phase (its softmax).  One barrier a tile keeps one group of waves in the one while the
+//     other is in the other: between barriers t and t+1 group 0 has the matrix phase of tile t and then its vector phase, group 1 the
+//     vector phase of tile t-1 and then the matrix phase of tile t.
 //
-// Slot k lies between two barriers: group 0 has the matrix phase of tile t in slot 2t and its softmax in 2t+1, group 1
-// the same one slot later.  The transfers K(t+3), V(t+2) ("pair t+3") are issued at the start of the vector phase of tile t;
-// their slots were last read in matrix phases t-1 (K(t-1), V(t-2)), which both groups have left.
+// The transfers K(t+3), V(t+2) ("pair t+3") are issued at the start of the vector phase of tile t; their slots were last read in
+// matrix phases t-1 (K(t-1), V(t-2)), which both groups have left behind barrier t.
 //
 // Where 256 queries a workgroup leave compute units idle (HALVES), a workgroup serves 128: both groups have the same queries, group
 // i takes tiles 2u + i through rings of two slots of its own, and the two partial results are merged through LDS.
 //
-// What bounds it: 33024 keys x 32 heads x 256 queries (head_dim 128) take 150-185 us, depending on the clock that the board's power
-// leaves (181 us and 64-row tiles staged through registers before; with head_dim 64 about 105, 180 before).  Transfers and barriers
-// alone take 107 us, which is the 541 MB of K and V at 5 TB/s; the MFMAs with their LDS reads alone 105-118, the softmax alone
-// 79-86: the three overlap, but each takes power from the others.  Eight sequences x 32 heads x 512 queries over 576 ... 1536 keys
-// (33 tiles on the busiest compute unit, 28 on average): 84 us for the call, 96 before.  Grouping even and odd waves instead
-// (both of a SIMD in the same phase): 173-215 and 100 us.  Raised wave priority in the matrix phase: the same.
+// What bounds it: power, in a loop of nothing but these calls, and before that the vector phase.  A tile of 256 queries takes 3150 cycles
+// (2048 of them MFMAs: a matrix phase is 1370 cycles, a vector phase 340 for the transfers and 1100 to 1250 for the softmax), 3850 with
+// the transfers' bases, strides and cases formed anew for each tile (690 cycles) and a barrier after every phase (the matrix phase's
+// group waited 750 cycles for the other at each).  That is 18 % fewer cycles, of which the clock takes back three quarters: 33024 keys x 32 heads x
+// 256 queries (head_dim 128), un-evicted call with its merge, 164 -> 157 us; eight sequences x 32 heads x 512 queries over 576 ... 1536
+// keys (33 tiles on the busiest compute unit, 28 on average) 77.4 -> 74.4.  (The steps one by one: transfers 158 and 74.9, one barrier a tile
+// 157 and 74.4.)  Not better: transfers between the MFMAs of the matrix phase (74.9 -> 77.3), five or seven fragments ahead (1 % in the former, nothing in
+// the latter), even and odd waves as groups (both of a SIMD in the same phase), raised wave priority in the matrix phase.
 #include "attend.hpp"
 #include "lds.hpp"
 
@@ -161,40 +163,82 @@ __global__ __launch_bounds__(kWaves * 64) void attend_tiles_kernel(const AttendP
   const int ntiles = HALVES ? (all_tiles + 1) / 2 : all_tiles;
   const int mine = HALVES ? (all_tiles + (second ? 0 : 1)) / 2 : all_tiles;
   auto first_key = [&](int t) { return j0 + (HALVES ? 2 * t + (second ? 1 : 0) : t) * kTK; };
-  const char* rest_k = prm.K2.row(b, h, 0);
-  const char* rest_v = prm.V2.row(b, h, 0);
 
-  // ---- transfers: a wave moves kMoveRows rows of a tile
+  // ---- transfers: a wave moves kMoveRows rows of a tile, of K and of V.  As long as these rows lie in one segment, a tile takes a
+  // scalar base that goes on by the same step, and offsets that the lanes keep; where they straddle the segments or the end, each lane
+  // forms its own address.
   const uint32_t mrow = (uint32_t)lane / C::kPPR, mpiece = (uint32_t)lane % C::kPPR;
-  auto move = [&](const char* packed, const char* rest, int64_t stride, int t, uint32_t to, uint32_t swz, uint32_t swz_step) {
-    const int first = first_key(t) + part * C::kMoveRows;  // (t beyond the last tile: rows past the end re-read the last row)
+  struct Feed {
+    const char *packed, *rest, *base;  // base: of the next tile's rows
+    uint32_t stride, step;             // of the second segment's rows; from a tile's rows to the next one's
+    int whole;                         // how many tiles from the next one on are taken by base and step
+    uint32_t off[C::kMoves], piece[C::kMoves];
+  };
+  auto uniform = [](const char* p) {  // (the same in every lane, but the compiler may hold it in vector registers)
+    const uint64_t u = (uint64_t)p;
+    return (const char*)((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(u >> 32)) << 32 | (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)u));
+  };
+  constexpr int kNext = HALVES ? 2 * kTK : kTK;  // keys from a tile of this group to the next
+  // (On every way through `move`: where one comes without it the compiler moves the whole loop's state into vector registers.)
+  auto scalar = [](Feed& f) { asm volatile("" : "+s"(f.whole), "+s"(f.base), "+s"(f.step)); };
+  auto aim = [&](Feed& f, int t) {  // at tile t
+    const int first = first_key(t) + part * C::kMoveRows;
+    const bool in_a = first < len_a;
+    const uint32_t st = in_a ? (uint32_t)C::kRowB : f.stride;
+    const int left = (in_a ? min(len_a, j1) : j1) - first - C::kMoveRows;
+    f.whole = __builtin_amdgcn_readfirstlane(left >= 0 ? left / kNext + 1 : 0);
+    f.base = uniform(in_a ? f.packed + (int64_t)first * C::kRowB : f.rest + (int64_t)(first - len_a) * f.stride);
+    f.step = __builtin_amdgcn_readfirstlane(kNext * st);
+    scalar(f);
+#pragma unroll
+    for (int j = 0; j < C::kMoves; ++j) f.off[j] = (mrow + j * C::kRPI) * st + f.piece[j];
+  };
+  auto move = [&](Feed& f, int t, uint32_t to) {
     to += part * C::kMoveRows * C::kRowB;
-    const uint32_t piece = (mpiece ^ swz) << 4;
-    if (first + C::kMoveRows <= j1 && (first >= len_a || first + C::kMoveRows <= len_a)) {
-      const bool in_a = first < len_a;
-      const int64_t st = in_a ? C::kRowB : stride;
-      const char* base = in_a ? packed + (int64_t)first * C::kRowB : rest + (int64_t)(first - len_a) * stride;
-      const uint32_t off = mrow * (uint32_t)st;
+    if (__builtin_expect(f.whole > 0, 1)) {
 #pragma unroll
-      for (int j = 0; j < C::kMoves; ++j)
-        dma16(base + j * C::kRPI * st, off + (piece ^ swz_step * j), to + j * 1024);
-    } else {
-#pragma unroll
-      for (int j = 0; j < C::kMoves; ++j) {
-        const int k = min(first + j * C::kRPI + (int)mrow, j1 - 1);
-        const char* src = k < len_a ? packed + (int64_t)k * C::kRowB : rest + (int64_t)(k - len_a) * stride;
-        dma16_from(src + (piece ^ swz_step * j), to + j * 1024);
-      }
+      for (int j = 0; j < C::kMoves; ++j) dma16(f.base, f.off[j], to + j * 1024);
+      f.base += f.step;
+      --f.whole;
+      scalar(f);
+      return;
     }
+    const int first = first_key(t) + part * C::kMoveRows;  // (rows past the end re-read the last row, also those of tiles beyond the last one)
+    if (first >= j1) {
+      const char* last = uniform(j1 <= len_a ? f.packed + (int64_t)(j1 - 1) * C::kRowB : f.rest + (int64_t)(j1 - 1 - len_a) * f.stride);
+#pragma unroll
+      for (int j = 0; j < C::kMoves; ++j) dma16(last, f.piece[j], to + j * 1024);
+      scalar(f);
+      return;
+    }
+#pragma unroll
+    for (int j = 0; j < C::kMoves; ++j) {
+      const int k = min(first + j * C::kRPI + (int)mrow, j1 - 1);
+      const bool in_a = k < len_a;
+      const char* from = in_a ? f.packed : f.rest;
+      dma16_from(from + ((uint64_t)(uint32_t)(in_a ? k : k - len_a) * (in_a ? (uint32_t)C::kRowB : f.stride) + f.piece[j]), to + j * 1024);
+    }
+    aim(f, t + 1);
   };
   // K's permutation depends on the transfer j by one exclusive-or (j * kRPI and the lane's row are row bits side by side, and
   // the permutation of j rows of transfers is j times that of one), V's does not.
-  const uint32_t ksw = C::swz_k(part * C::kMoveRows + mrow), vsw = v_swizzle<D>(mrow) << 1;
+  Feed fk, fv;
+  fk.packed = a_k;
+  fk.rest = prm.K2.row(b, h, 0);
+  fk.stride = (uint32_t)prm.K2.stride_t;
+  fv.packed = a_v;
+  fv.rest = prm.V2.row(b, h, 0);
+  fv.stride = (uint32_t)prm.V2.stride_t;
+#pragma unroll
+  for (int j = 0; j < C::kMoves; ++j) {
+    fk.piece[j] = (mpiece ^ C::swz_k(part * C::kMoveRows + mrow) ^ j * C::swz_k(C::kRPI)) << 4;
+    fv.piece[j] = (mpiece ^ v_swizzle<D>(mrow) << 1) << 4;
+  }
+  aim(fk, 0);
+  aim(fv, 0);
   auto ring = [&](int t) { return HALVES ? (second ? 2 : 0) + (t & 1) : t & 3; };
-  auto move_k = [&](int t) {
-    move(a_k, rest_k, prm.K2.stride_t, t, lds0 + ring(t) * C::kTileB, ksw, C::swz_k(C::kRPI) << 4);
-  };
-  auto move_v = [&](int t) { move(a_v, rest_v, prm.V2.stride_t, t, lds0 + (4 + ring(t)) * C::kTileB, vsw, 0); };
+  auto move_k = [&](int t) { move(fk, t, lds0 + ring(t) * C::kTileB); };
+  auto move_v = [&](int t) { move(fv, t, lds0 + (4 + ring(t)) * C::kTileB); };
 
   const int q = qtile * C::kQueries + part * 32 + r;
   const bool active = qtile * C::kQueries + part * 32 < prm.n_q;  // (a wave without queries only helps to move the tiles)
@@ -312,15 +356,16 @@ __global__ __launch_bounds__(kWaves * 64) void attend_tiles_kernel(const AttendP
     l += psum;
   };
 
-  // ---- barriers.  Before matrix phase t of group 0 every wave has waited for its part of pair t: group 0 at the end of its
-  // vector phase t-1, where pairs t+1 and t+2 are younger, group 1 at the end of its matrix phase t-1, where pair t+1 is.
+  // ---- barriers.  At barrier t every wave has waited for its part of pair t: group 0 at the end of its vector phase t-1, where pairs
+  // t+1 and t+2 are younger, group 1 at the end of its matrix phase t-1, where pair t+1 is.  One more barrier behind group 0's first
+  // matrix phase lets group 1 start half a tile late.
   // With HALVES a group moves its own tiles, pair t+2 in vector phase t (into the slots of K(t) and V(t-1), which it has
-  // read), and waits for pair t+1 at the end of that phase.
-  auto end_matrix = [&]() {
+  // read), and waits for pair t+1 at the end of that phase; the groups meet at a barrier after every phase.
+  auto end_matrix = [&](bool first) {
     __builtin_amdgcn_sched_barrier(0);
     if (!HALVES && second)
       asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"i"(2 * C::kMoves) : "memory");
-    else
+    else if (HALVES || first)
       asm volatile("s_barrier" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
   };
@@ -328,9 +373,7 @@ __global__ __launch_bounds__(kWaves * 64) void attend_tiles_kernel(const AttendP
     __builtin_amdgcn_sched_barrier(0);
     if (HALVES)
       asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"i"(2 * C::kMoves) : "memory");
-    else if (second)
-      asm volatile("s_barrier" ::: "memory");
-    else
+    else if (!second)
       asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"i"(4 * C::kMoves) : "memory");
     __builtin_amdgcn_sched_barrier(0);
   };
@@ -357,17 +400,17 @@ __global__ __launch_bounds__(kWaves * 64) void attend_tiles_kernel(const AttendP
     if (second) asm volatile("s_barrier" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
     if (active && mine > 0) matrix(0, C::kQK, 0, 0);
-    end_matrix();
+    end_matrix(true);
     vector(0);
     for (int t = 1; t < ntiles; t += 2) {
       if (active && t < mine) matrix(0, C::kQK + C::kPV, 1, 0);
       turn_k();
-      end_matrix();
+      end_matrix(false);
       vector(t);
       if (t + 1 < ntiles) {
         if (active && t + 1 < mine) matrix(0, C::kQK + C::kPV, 0, 1);
         turn_v();
-        end_matrix();
+        end_matrix(false);
         vector(t + 1);
       }
     }
@@ -377,7 +420,7 @@ __global__ __launch_bounds__(kWaves * 64) void attend_tiles_kernel(const AttendP
       else
         matrix(C::kQK, C::kQK + C::kPV, 0, 1);
     }
-    if (!second) asm volatile("s_barrier" ::: "memory");
+    if (HALVES && !second) asm volatile("s_barrier" ::: "memory");
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (no transfer into LDS outlives its workgroup)
   }
 
