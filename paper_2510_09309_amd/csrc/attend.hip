@@ -1066,11 +1066,25 @@ bool attend_full_is_narrow(const maskkv_desc* d, const Lens& lens) {
   return groups <= kUnits ? keys <= 3200 : groups <= 2 * kUnits && keys <= 1500;
 }
 
+constexpr int64_t kCacheBytes = (int64_t)256 << 20;  // of the memory-side cache
+
 // Heads are only put in order where not every workgroup of the tiled kernel starts at once.
 bool attend_is_ordered(const maskkv_desc* d, bool full, int64_t capacity) {
   if (full || attend_is_narrow(d, full, capacity)) return false;
   const int per_block = tiled_queries(d, full);
   return ((int64_t)d->n_resp * query_heads_per_kv(d) + per_block - 1) / per_block * d->B * d->H > kUnits;
+}
+
+// The un-evicted call's V passes by the memory-side cache where it is read once (one tile of queries) and K and V together are larger
+// than that cache: V would push out K, which the scoring that follows reads again.  (us for this call and scoring with its normalisers, 32 heads x
+// 256 queries, head_dim 128, with it and without, in a loop over the same tensors; over four sets of them in turn: 9k keys 86.3 / 84.6;
+// 90.9 / 91.4, 13k 106.4 / 105.3; 113.6 / 114.1, 16k 123.3 / 125.3; 133.5 / 134.7, 20k 144.6 / 150.5; 155.0 / 155.5, 26k 180 / 191; 190.5 / 194.9,
+// 33k 226 / 240; 235.9 / 240.3, 48k 328 / 335; 335 / 338.  K as well: 242 / 244 at 33k keys.  Scoring from the last key to the first: the same.)
+bool attend_is_streamed(const maskkv_desc* d, const Lens& lens, bool full) {
+  if (!full || d->n_resp * query_heads_per_kv(d) > tiled_queries(d, true)) return false;
+  int64_t keys = 0;
+  for (int b = 0; b < d->B; ++b) keys += lens.P[b] + d->n_resp;
+  return keys * d->H * d->d * 4 > kCacheBytes;
 }
 
 template <int D>
@@ -1205,6 +1219,7 @@ int launch_attend(const maskkv_desc* d, const Lens& lens, bool full, const View&
   prm.lse = lse;
   const bool ordered = attend_is_ordered(d, full, capacity);
   prm.ranked = ordered && d->dtype == MASKKV_BF16 && prm.BH <= kRankHeads;
+  prm.streamed = attend_is_streamed(d, lens, full);
   prm.order = ordered && !prm.ranked ? reinterpret_cast<const int32_t*>(workspace) : nullptr;
   prm.part_o = nullptr;
   prm.part_ml = nullptr;

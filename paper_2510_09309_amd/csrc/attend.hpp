@@ -23,6 +23,7 @@ struct AttendParams {
   float c;  // scale * log2(e)
   float* lse;
   int ranked;            // they do (see kRankHeads)
+  int streamed;          // V passes by the memory-side cache (see attend_is_streamed)
   const int32_t* order;  // [BH] heads by descending key count (compressed call of the tiled kernel), or null
   float* part_o;     // [BH][n_splits][n_q][D]
   float2* part_ml;   // [BH][n_splits][n_q]

@@ -24,6 +24,8 @@
 // keys (33 tiles on the busiest compute unit, 28 on average) 77.4 -> 74.4.  (The steps one by one: transfers 158 and 74.9, one barrier a tile
 // 157 and 74.4.)  Not better: transfers between the MFMAs of the matrix phase (74.9 -> 77.3), five or seven fragments ahead (1 % in the former, nothing in
 // the latter), even and odd waves as groups (both of a SIMD in the same phase), raised wave priority in the matrix phase.
+#include <type_traits>
+
 #include "attend.hpp"
 #include "lds.hpp"
 
@@ -109,10 +111,13 @@ __device__ __forceinline__ int head_of_rank(const AttendParams& prm, int rank, i
   return head;
 }
 
-// RANKED: the heads are taken by rank (an instantiation of its own: as a branch it costs the other calls 0.5 %).
-template <int D, bool HALVES, bool RANKED>
+// KIND: kRanked, the heads are taken by rank; kStreamed, V is too large to be kept (instantiations of their own: as a branch the former
+// costs the other calls 0.5 %, the latter 1 %).
+enum { kPlain, kRanked, kStreamed };
+template <int D, bool HALVES, int KIND>
 __global__ __launch_bounds__(kWaves * 64) void attend_tiles_kernel(const AttendParams prm) {
   using C = TileCfg<D, HALVES>;
+  constexpr bool RANKED = KIND == kRanked;
   extern __shared__ __attribute__((aligned(1024))) char tiles_lds[];
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)tiles_lds;
 
@@ -193,11 +198,11 @@ __global__ __launch_bounds__(kWaves * 64) void attend_tiles_kernel(const AttendP
 #pragma unroll
     for (int j = 0; j < C::kMoves; ++j) f.off[j] = (mrow + j * C::kRPI) * st + f.piece[j];
   };
-  auto move = [&](Feed& f, int t, uint32_t to) {
+  auto move = [&](Feed& f, int t, uint32_t to, auto streamed) {
     to += part * C::kMoveRows * C::kRowB;
     if (__builtin_expect(f.whole > 0, 1)) {
 #pragma unroll
-      for (int j = 0; j < C::kMoves; ++j) dma16(f.base, f.off[j], to + j * 1024);
+      for (int j = 0; j < C::kMoves; ++j) decltype(streamed)::value ? dma16_streamed(f.base, f.off[j], to + j * 1024) : dma16(f.base, f.off[j], to + j * 1024);
       f.base += f.step;
       --f.whole;
       scalar(f);
@@ -237,8 +242,8 @@ __global__ __launch_bounds__(kWaves * 64) void attend_tiles_kernel(const AttendP
   aim(fk, 0);
   aim(fv, 0);
   auto ring = [&](int t) { return HALVES ? (second ? 2 : 0) + (t & 1) : t & 3; };
-  auto move_k = [&](int t) { move(fk, t, lds0 + ring(t) * C::kTileB); };
-  auto move_v = [&](int t) { move(fv, t, lds0 + (4 + ring(t)) * C::kTileB); };
+  auto move_k = [&](int t) { move(fk, t, lds0 + ring(t) * C::kTileB, std::false_type()); };
+  auto move_v = [&](int t) { move(fv, t, lds0 + (4 + ring(t)) * C::kTileB, std::bool_constant<KIND == kStreamed>()); };
 
   const int q = qtile * C::kQueries + part * 32 + r;
   const bool active = qtile * C::kQueries + part * 32 < prm.n_q;  // (a wave without queries only helps to move the tiles)
@@ -476,12 +481,12 @@ __global__ __launch_bounds__(kWaves * 64) void attend_tiles_kernel(const AttendP
   }
 }
 
-template <int D, bool HALVES, bool RANKED>
+template <int D, bool HALVES, int KIND>
 int launch(const AttendParams& prm, unsigned groups, hipStream_t stream) {
   using C = TileCfg<D, HALVES>;
   static bool raised = false;  // one-time opt-in to more than the default dynamic LDS size
   if (!raised) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attend_tiles_kernel<D, HALVES, RANKED>),
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attend_tiles_kernel<D, HALVES, KIND>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, C::kLds);
     if (e != hipSuccess) {
       set_error("attend: cannot raise dynamic LDS limit: %s", hipGetErrorString(e));
@@ -490,14 +495,15 @@ int launch(const AttendParams& prm, unsigned groups, hipStream_t stream) {
     }
     raised = true;
   }
-  hipLaunchKernelGGL((attend_tiles_kernel<D, HALVES, RANKED>), dim3(groups), dim3(kWaves * 64), C::kLds, stream, prm);
+  hipLaunchKernelGGL((attend_tiles_kernel<D, HALVES, KIND>), dim3(groups), dim3(kWaves * 64), C::kLds, stream, prm);
   return check_launch("attend (tiles)");
 }
 
 template <bool HALVES>
 int launch(const AttendParams& prm, int d, unsigned groups, hipStream_t stream) {
-  if (prm.ranked) return d == 128 ? launch<128, HALVES, true>(prm, groups, stream) : launch<64, HALVES, true>(prm, groups, stream);
-  return d == 128 ? launch<128, HALVES, false>(prm, groups, stream) : launch<64, HALVES, false>(prm, groups, stream);
+  if (prm.ranked) return d == 128 ? launch<128, HALVES, kRanked>(prm, groups, stream) : launch<64, HALVES, kRanked>(prm, groups, stream);
+  if (prm.streamed) return d == 128 ? launch<128, HALVES, kStreamed>(prm, groups, stream) : launch<64, HALVES, kStreamed>(prm, groups, stream);
+  return d == 128 ? launch<128, HALVES, kPlain>(prm, groups, stream) : launch<64, HALVES, kPlain>(prm, groups, stream);
 }
 
 }  // namespace
