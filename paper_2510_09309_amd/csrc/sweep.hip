@@ -330,7 +330,7 @@ __device__ __forceinline__ void start_table(const SweepParams& prm, int b, int v
 
 // BLOCKS blocks of 32 rows a workgroup, and each block's response keys on 8 / BLOCKS waves: 2 where that gives every compute unit work.
 //
-// What bounds it: with few units the latency of its loads (issued at once: rows and two tiles of keys; 7 to 8 us with the rest of the
+// What bounds it: with few units the latency of its loads (issued at once: rows and two tiles of keys; 5.9 to 6.7 us with the rest of the
 // chain: launch, loads, logarithms, stores), with many the memory (96 MB in the ragged batch of perf/cases.py, 20 of 35 us) and
 // the exponentials (12 us), which all workgroups come to at the same time.  us there, 40.6 -> 35: the sweep's table written by
 // workgroups of their own instead of by a wave that the others wait for, tiles asked for before the rows' arrival instead of
@@ -340,6 +340,7 @@ template <int D, int BLOCKS>
 __global__ __launch_bounds__(kThreads) void sweep_start_kernel(const SweepParams prm) {
   using C = Cfg<D>;
   constexpr int S = C::kSteps, SPLIT = kWaves / BLOCKS;
+  constexpr bool kShared = BLOCKS < 8;
   const int lane = threadIdx.x & 63, r = lane & 31, g = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if ((int)blockIdx.x <= prm.tables) {
@@ -351,9 +352,9 @@ __global__ __launch_bounds__(kThreads) void sweep_start_kernel(const SweepParams
     }
     return;
   }
-  extern __shared__ __attribute__((aligned(1024))) char lds[];  // two tiles of 128 keys
-  __shared__ float2 part[kWaves][32];
+  extern __shared__ __attribute__((aligned(1024))) char lds[];  // two tiles of 128 keys, and with kShared the rows
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
+  float2(&part)[kWaves][32] = *reinterpret_cast<float2(*)[kWaves][32]>(lds + 2 * C::kKBytes);  // (in the rows' place: two workgroups fit a compute unit)
   const int block = (int)blockIdx.x - 1 - prm.tables;
   const int unit = block / SPLIT;
   // (a division is a chain of some twenty instructions before the first load)
@@ -380,9 +381,23 @@ __global__ __launch_bounds__(kThreads) void sweep_start_kernel(const SweepParams
   const int part_of = wave % SPLIT;
   const int q0 = qg * prm.rows + rb * 32;
   u32x4 qf[S];
-  const char* qrow = prm.Q.group_row(b, h, prm.q_per_kv, prm.n_qh, min(q0 + r, prm.n_query - 1)) + g * 16;
+  const uint32_t rows = lds0 + 2 * C::kKBytes + wave / SPLIT * C::kQBytes;  // (behind the tiles)
+  // Two blocks: a block's waves move its rows as whole rows, each row once.  (Each wave loading the fragments of all its rows, a row a
+  // lane, keeps the texture path busy for four times as long, and that four times over: first data after 3.4 us of 5.2 instead of 2.2
+  // of 4.2; us a layer 4k keys 45.6 -> 44.4, 8k 57.8 -> 56.8, two sequences of 3k and 5k at head_dim 64 41.3 -> 40.3, 8 heads x 410 x 4 rows, 4.7k
+  // keys, scoring alone 45.3 -> 44.3.  Eight blocks have too little LDS for it, or one more wait: the ragged batch takes the same.)
+  if (kShared) {
 #pragma unroll
-  for (int s = 0; s < S; ++s) asm volatile("global_load_dwordx4 %0, %1, off offset:%2" : "=v"(qf[s]) : "v"(qrow), "i"(s * 32));
+    for (int j = 0; j < C::kQBytes / 1024 / SPLIT; ++j) {
+      const int row = (part_of * (C::kQBytes / 1024 / SPLIT) + j) * C::kRPI + lane / C::kPPR;
+      const char* from = prm.Q.group_row(b, h, prm.q_per_kv, prm.n_qh, min(q0 + row, prm.n_query - 1));
+      dma16_from(from + ((lane % C::kPPR ^ C::swz(row)) << 4), rows + (part_of * (C::kQBytes / 1024 / SPLIT) + j) * 1024);
+    }
+  } else {
+    const char* qrow = prm.Q.group_row(b, h, prm.q_per_kv, prm.n_qh, min(q0 + r, prm.n_query - 1)) + g * 16;
+#pragma unroll
+    for (int s = 0; s < S; ++s) asm volatile("global_load_dwordx4 %0, %1, off offset:%2" : "=v"(qf[s]) : "v"(qrow), "i"(s * 32));
+  }
   dma(0);
   if (tiles > 1) dma(1);
 
@@ -394,6 +409,9 @@ __global__ __launch_bounds__(kThreads) void sweep_start_kernel(const SweepParams
       asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"i"(C::kMoves) : "memory");
     else
       asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    if (kShared && t == 0)
+#pragma unroll
+      for (int s = 0; s < S; ++s) qf[s] = *in_lds<const u32x4>(rows + r * C::kRowB + (((2 * s + g) ^ C::swz(r)) << 4));
 #pragma unroll
     for (int s = 0; s < S; ++s) asm volatile("" : "+v"(qf[s]));
     if (t + 1 == tiles && part_of == 0) {  // (stores before the last wait would be waited for)
@@ -448,6 +466,7 @@ __global__ __launch_bounds__(kThreads) void sweep_start_kernel(const SweepParams
     m = mm;
   }
   if (SPLIT > 1) {
+    if (tiles == 1) __syncthreads();  // (every wave has its rows)
     if (g == 0) part[wave][r] = make_float2(m, l);
     __syncthreads();
   }
@@ -1444,7 +1463,7 @@ SweepPlan make_plan(const maskkv_desc* d, const Lens& lens, int nqg) {
 
 template <int D>
 int launch(const maskkv_desc* d, const SweepParams& prm, hipStream_t stream) {
-  const int lds_start = 2 * Cfg<D>::kKBytes;
+  const int lds_start = 2 * Cfg<D>::kKBytes, lds_start2 = lds_start + 2 * Cfg<D>::kQBytes;
   static bool raised = false;
   if (!raised) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&sweep_kernel<D, false>),
@@ -1457,7 +1476,7 @@ int launch(const maskkv_desc* d, const SweepParams& prm, hipStream_t stream) {
                               hipFuncAttributeMaxDynamicSharedMemorySize, lds_start);
     if (e == hipSuccess)
       e = hipFuncSetAttribute(reinterpret_cast<const void*>(&sweep_start_kernel<D, 2>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, lds_start);
+                              hipFuncAttributeMaxDynamicSharedMemorySize, lds_start2);
     if (e != hipSuccess) {
       set_error("score: cannot raise dynamic LDS limit: %s", hipGetErrorString(e));
       (void)hipGetLastError();
@@ -1469,7 +1488,7 @@ int launch(const maskkv_desc* d, const SweepParams& prm, hipStream_t stream) {
   if (units >= 128)
     hipLaunchKernelGGL((sweep_start_kernel<D, 8>), dim3(1 + prm.tables + units), dim3(kThreads), lds_start, stream, prm);
   else
-    hipLaunchKernelGGL((sweep_start_kernel<D, 2>), dim3(1 + prm.tables + units * 4), dim3(kThreads), lds_start, stream, prm);
+    hipLaunchKernelGGL((sweep_start_kernel<D, 2>), dim3(1 + prm.tables + units * 4), dim3(kThreads), lds_start2, stream, prm);
   if (int e = check_launch("score (sweep start)")) return e;
   if (prm.plan.groups > prm.plan.grid)
     hipLaunchKernelGGL((sweep_kernel<D, true>), dim3(prm.plan.grid), dim3(kThreads), Cfg<D>::kLds, stream, prm);
