@@ -35,7 +35,6 @@ namespace {
 
 constexpr int kWaves = 8;
 constexpr int kTK = 64;      // keys per tile
-constexpr int kAheadFrag = 3;  // LDS fragments requested ahead of the MFMA that takes them
 
 template <int D, bool HALVES>
 struct TileCfg {
@@ -118,6 +117,8 @@ template <int D, bool HALVES, int KIND>
 __global__ __launch_bounds__(kWaves * 64) void attend_tiles_kernel(const AttendParams prm) {
   using C = TileCfg<D, HALVES>;
   constexpr bool RANKED = KIND == kRanked;
+  constexpr bool kFew = HALVES && D == 64;  // registers: no more than 168, up to which the next workgroup starts when the last one's second group has left
+  constexpr int kAheadFrag = kFew && RANKED ? 2 : 3;  // LDS fragments requested ahead of the MFMA that takes them
   extern __shared__ __attribute__((aligned(1024))) char tiles_lds[];
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)tiles_lds;
 
@@ -171,7 +172,8 @@ __global__ __launch_bounds__(kWaves * 64) void attend_tiles_kernel(const AttendP
 
   // ---- transfers: a wave moves kMoveRows rows of a tile, of K and of V.  As long as these rows lie in one segment, a tile takes a
   // scalar base that goes on by the same step, and offsets that the lanes keep; where they straddle the segments or the end, each lane
-  // forms its own address.
+  // forms its own address.  (kFew: base and offsets are formed for each tile.  us a call, kept / formed: 168 heads x 214 queries over 270 keys
+  // 19.5 / 17.6, over 900 31.9 / 29.3, x 120 over 270 10.2 / 9.5, 256 heads x 100 over 600 17.5 / 17.2.)
   const uint32_t mrow = (uint32_t)lane / C::kPPR, mpiece = (uint32_t)lane % C::kPPR;
   struct Feed {
     const char *packed, *rest, *base;  // base: of the next tile's rows
@@ -200,9 +202,11 @@ __global__ __launch_bounds__(kWaves * 64) void attend_tiles_kernel(const AttendP
   };
   auto move = [&](Feed& f, int t, uint32_t to, auto streamed) {
     to += part * C::kMoveRows * C::kRowB;
+    if (kFew) aim(f, t);
     if (__builtin_expect(f.whole > 0, 1)) {
 #pragma unroll
       for (int j = 0; j < C::kMoves; ++j) decltype(streamed)::value ? dma16_streamed(f.base, f.off[j], to + j * 1024) : dma16(f.base, f.off[j], to + j * 1024);
+      if (kFew) return;
       f.base += f.step;
       --f.whole;
       scalar(f);
@@ -213,7 +217,7 @@ __global__ __launch_bounds__(kWaves * 64) void attend_tiles_kernel(const AttendP
       const char* last = uniform(j1 <= len_a ? f.packed + (int64_t)(j1 - 1) * C::kRowB : f.rest + (int64_t)(j1 - 1 - len_a) * f.stride);
 #pragma unroll
       for (int j = 0; j < C::kMoves; ++j) dma16(last, f.piece[j], to + j * 1024);
-      scalar(f);
+      if (!kFew) scalar(f);
       return;
     }
 #pragma unroll
@@ -223,7 +227,7 @@ __global__ __launch_bounds__(kWaves * 64) void attend_tiles_kernel(const AttendP
       const char* from = in_a ? f.packed : f.rest;
       dma16_from(from + ((uint64_t)(uint32_t)(in_a ? k : k - len_a) * (in_a ? (uint32_t)C::kRowB : f.stride) + f.piece[j]), to + j * 1024);
     }
-    aim(f, t + 1);
+    if (!kFew) aim(f, t + 1);
   };
   // K's permutation depends on the transfer j by one exclusive-or (j * kRPI and the lane's row are row bits side by side, and
   // the permutation of j rows of transfers is j times that of one), V's does not.
@@ -239,8 +243,10 @@ __global__ __launch_bounds__(kWaves * 64) void attend_tiles_kernel(const AttendP
     fk.piece[j] = (mpiece ^ C::swz_k(part * C::kMoveRows + mrow) ^ j * C::swz_k(C::kRPI)) << 4;
     fv.piece[j] = (mpiece ^ v_swizzle<D>(mrow) << 1) << 4;
   }
-  aim(fk, 0);
-  aim(fv, 0);
+  if (!kFew) {
+    aim(fk, 0);
+    aim(fv, 0);
+  }
   auto ring = [&](int t) { return HALVES ? (second ? 2 : 0) + (t & 1) : t & 3; };
   auto move_k = [&](int t) { move(fk, t, lds0 + ring(t) * C::kTileB, std::false_type()); };
   auto move_v = [&](int t) { move(fv, t, lds0 + (4 + ring(t)) * C::kTileB, std::bool_constant<KIND == kStreamed>()); };
