@@ -52,9 +52,18 @@ struct RowsParams {
   float* out;       // [B*H][parts][out_stride]
   int64_t out_stride;
   float* mass;      // [B*H][parts] or null
+  int part_keys, parts;  // not 0: keys are dealt out in so many parts of so many keys
+  float4* stats;    // [B*H][n_query][parts]
 };
+struct RowsSplit {
+  int groups, tiles;     // groups of 16 rows a wave of the first kernel, tiles of 16 keys a workgroup of the second
+  int part_keys, parts;  // keys a workgroup of the first, and how many of them, or 0
+};
+// Whether rows and keys are both dealt out, and how.
+RowsSplit score_rows_split(const maskkv_desc* d, const Lens& lens);
+size_t score_rows_split_bytes(const maskkv_desc* d, const RowsSplit& split);
 int score_rows_parts(const maskkv_desc* d, const Lens& lens);
-int launch_score_rows(const RowsParams& prm, int d, int parts, hipStream_t stream);
+int launch_score_rows(const RowsParams& prm, int d, int parts, const RowsSplit& split, hipStream_t stream);
 
 // sweep.hip: the scores in one sweep over the keys
 SweepPlan sweep_plan(const maskkv_desc* d, const Lens& lens, int nqg);

@@ -569,6 +569,7 @@ namespace {
 // has the same workspace, is served by them.
 struct ScoreArea {
   size_t stats, sums, bytes;
+  RowsSplit split;
   ScoreArea(const maskkv_desc* d, const Lens& lens, const SweepPlan& plan) {
     int pp, pr;
     stat_slots(d, lens, make_map(d, lens, true), &pp, &pr);
@@ -580,6 +581,8 @@ struct ScoreArea {
     auto columns = [&](int parts) { return parts > 1 ? (size_t)(bh * parts * group_stride(d)) * sizeof(float) : 0; };
     sums = stats + lse;
     bytes = sums + columns(max(nqg, plan.parts));
+    split = score_rows_split(d, lens);
+    if (score_rows_split_bytes(d, split) > bytes) split = RowsSplit{};  // (never more than the other ways ask for)
     if (plan.groups > 0) {
       sums = (sweep_workspace_bytes(d, nqg, plan) + 255) / 256 * 256;
       bytes = max(bytes, sums + columns(plan.subsets));
@@ -639,7 +642,8 @@ int launch_score(const maskkv_desc* d, const View& Q, const View& K, const Lens&
       if (int e = launch_group_sum(prm, plan.subsets, stream)) return e;
     return mark(events, 3, stream);
   }
-  if (plan.parts > 0 && !row_lse) {
+  const RowsSplit& split = area.split;
+  if ((plan.parts > 0 || split.parts > 0) && !row_lse) {
     RowsParams rp;
     rp.Q = Q;
     rp.K = K;
@@ -651,13 +655,16 @@ int launch_score(const maskkv_desc* d, const View& Q, const View& K, const Lens&
     rp.n_qh = prm.n_qh;
     rp.q_per_kv = prm.q_per_kv;
     rp.c = prm.c;
-    const bool whole = plan.parts == 1;
+    rp.part_keys = split.part_keys;
+    rp.parts = split.parts;
+    rp.stats = reinterpret_cast<float4*>(ws);
+    const bool whole = plan.parts == 1 || split.parts;
     rp.out = whole ? scores : prm.group_sums;
     rp.out_stride = whole ? score_stride : prm.group_stride;
     rp.mass = whole ? prompt_mass : reinterpret_cast<float*>(ws);
     prm.unit_mass = whole ? nullptr : rp.mass;
     if (int e = mark(events, 0, stream)) return e;
-    if (int e = launch_score_rows(rp, d->d, plan.parts, stream)) return e;
+    if (int e = launch_score_rows(rp, d->d, plan.parts, split, stream)) return e;
     for (int i = 1; i < 3; ++i)
       if (int e = mark(events, i, stream)) return e;
     if (!whole)
