@@ -127,7 +127,8 @@ __device__ __forceinline__ void refine(SelShared<THREADS>& s, Range& g, int enou
     const int top = (int)(width >> shift);
     // bins are numbered from the top of the range: bin 0 holds the largest values
     each([&](uint32_t v, bool valid) {
-      if (valid && v >= g.lo && v <= g.hi) atomicAdd(&s.hist[top - (int)((v - g.lo) >> shift)], 1);
+      const uint32_t at = v - g.lo;
+      if (valid & (at <= width)) atomicAdd(&s.hist[top - (int)(at >> shift)], 1);
     });
     __syncthreads();
     const u32x2 two = reinterpret_cast<u32x2*>(s.hist)[tid];
@@ -184,7 +185,7 @@ __device__ __forceinline__ uint64_t exact_cut(SelShared<THREADS>& s, uint32_t lo
                                               Each&& each) {
   Range g{lo, hi, k, n};
   refine(s, g, kRankable, [&](auto&& f) { each([&](uint32_t key, uint32_t, bool valid) { f(key, valid); }); });
-  if (g.krem == g.pop) return (uint64_t)g.lo << 32;  // the whole bin is kept
+  if (g.krem == g.pop) return code_of(g.lo, last_pos);  // the whole bin is kept
   const uint32_t key_from = g.lo, key_span = g.hi - g.lo;
   uint32_t last = 0xFFFFFFFFu, first = 0u;  // ~position
   if (g.pop > kRankable) {  // one key, many entries: refine over their positions (lowest first: ~position descending)
@@ -240,59 +241,101 @@ __device__ __forceinline__ float inverse(float w) {
 }
 constexpr uint32_t kDividableFrom = 67u << 23, kDividableTo = 187u << 23;  // bits of 2^-60 and 2^60
 
-// Keys of G groups of four consecutive positions, group i at j0 + i * step (0 for positions past the prompt).  A group's
-// windows overlap, so it is loaded as whole 16-byte pieces (R rounded up to a piece on either side), all groups before the
-// first use; only groups that touch an end of the prompt are read again, element by element.  Positions outside the prompt
-// take the neutral element of the pooling, which leaves the sum (resp. the maximum) of the in-range terms as it is.
-// R: radius of the window, or (not FIXED) a bound of it.  P >= 4.
-template <int R, bool FIXED, int G>
-__device__ __forceinline__ void pool_groups(const float* x, int j0, int step, int P, int r, int mode, uint32_t (&key)[4 * G]) {
+// The four positions from p0 (a multiple of 4) of a head, as loaded from min(max(p0, 0), P - 4): those outside the prompt take
+// the neutral element.
+__device__ __forceinline__ void within_prompt(float (&w)[4], int p0, int P, float neutral) {
+  const int late = p0 - (P - 4);  // the load was moved down by so many
+  if (p0 < 0 || late > 0) {
+    const bool none = p0 < 0 || late >= 4, one = late & 1, two = late & 2;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) w[e] = one ? (e < 3 ? w[e < 3 ? e + 1 : 0] : neutral) : w[e];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) w[e] = two ? (e < 2 ? w[e < 2 ? e + 2 : 0] : neutral) : w[e];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) w[e] = none ? neutral : w[e];
+  }
+}
+
+// Keys of G groups of four consecutive positions, group i at j0 + i * step, adjacent lanes adjacent groups (0 for positions past
+// the prompt).  Every lane loads its own four positions; the others of its windows come from the lanes beside it, and only the
+// first and the last lane load theirs (R rounded up to a piece of four) from memory.  All loads are under way before the first
+// use, and positions outside the prompt take the neutral element of the pooling, which leaves the sum (resp. the maximum) of the
+// in-range terms as it is.
+// R: radius of the window, or (not FIXED) a bound of it.  P >= 4, j0 and step multiples of 4, all lanes of a wave together.
+template <int R, bool FIXED, int MODE, int G>
+__device__ __forceinline__ void pool_groups(const float* x, int j0, int step, int P, int r, uint32_t (&key)[4 * G]) {
   typedef __attribute__((ext_vector_type(4), aligned(4))) float f32x4u;
-  constexpr int A = (R + 3) / 4 * 4;
+  constexpr int E = (R + 3) / 4;  // pieces beside the own one
+  constexpr int A = 4 * E;
   constexpr int N = 4 + 2 * A;
   if (FIXED) r = R;
-  float v[G][N];
+  const float neutral = MODE == MASKKV_POOL_MAX ? __builtin_nanf("") : 0.f;  // (fmaxf passes over a NaN)
+  const int lane = threadIdx.x & 63;
+  auto load = [&](float (&w)[4], int p0) {
+    const f32x4u q = *reinterpret_cast<const f32x4u*>(x + min(max(p0, 0), P - 4));
+#pragma unroll
+    for (int e = 0; e < 4; ++e) w[e] = q[e];
+  };
+  const int side = lane == 0 ? -4 : 4;
+  float own[G][4], end[G][E][4];
+#pragma unroll
+  for (int i = 0; i < G; ++i) load(own[i], j0 + i * step);
 #pragma unroll
   for (int i = 0; i < G; ++i)
 #pragma unroll
-    for (int p = 0; p < N / 4; ++p) {
-      const int at = min(max(j0 + i * step - A + 4 * p, 0), P - 4);
-      const f32x4u w = *reinterpret_cast<const f32x4u*>(x + at);
+    for (int p = 0; p < E; ++p)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) v[i][4 * p + e] = w[e];
+      for (int e = 0; e < 4; ++e) end[i][p][e] = 0.f;
+  if (lane == 0 || lane == 63) {
+#pragma unroll
+    for (int i = 0; i < G; ++i)
+#pragma unroll
+      for (int p = 0; p < E; ++p) load(end[i][p], j0 + i * step + side * (p + 1));
+  }
+  float v[G][N];
+#pragma unroll
+  for (int i = 0; i < G; ++i) {
+    within_prompt(own[i], j0 + i * step, P, neutral);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[i][A + e] = own[i][e];
+#pragma unroll
+    for (int p = 0; p < E; ++p) {
+      within_prompt(end[i][p], j0 + i * step + side * (p + 1), P, neutral);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        auto beside = [&](float of, int left) {  // (the lane that has none there keeps its own piece)
+          const int kept = __builtin_bit_cast(int, end[i][p][e]), moved = __builtin_bit_cast(int, of);
+          return __builtin_bit_cast(float, left ? __builtin_amdgcn_update_dpp(kept, moved, 0x138, 0xf, 0xf, false)     // wave_shr:1
+                                                : __builtin_amdgcn_update_dpp(kept, moved, 0x130, 0xf, 0xf, false));  // wave_shl:1
+        };
+        v[i][A - 4 * (p + 1) + e] = beside(v[i][A - 4 * p + e], 1);
+        v[i][A + 4 * (p + 1) + e] = beside(v[i][A + 4 * p + e], 0);
+      }
+    }
+  }
+  float acc[G][4];
+#pragma unroll
+  for (int i = 0; i < G; ++i)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc[i][e] = neutral;  // (0 + x is x but for the sign of a zero, which the key does not see)
+#pragma unroll
+  for (int t = -R; t <= R; ++t)
+    if (FIXED || (t >= -r && t <= r)) {
+#pragma unroll
+      for (int i = 0; i < G; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          acc[i][e] = MODE == MASKKV_POOL_MAX ? fmaxf(acc[i][e], v[i][e + A + t]) : __fadd_rn(acc[i][e], v[i][e + A + t]);
     }
 #pragma unroll
   for (int i = 0; i < G; ++i) {
     const int g0 = j0 + i * step;
     const bool inner = g0 >= A && g0 + 4 + A <= P;
-    if (!inner) {
-      const float neutral = mode == MASKKV_POOL_MAX ? __builtin_nanf("") : 0.f;  // (fmaxf passes over a NaN)
-#pragma unroll
-      for (int t = 0; t < N; ++t) {
-        const int j = g0 - A + t;
-        v[i][t] = (j >= 0 && j < P) ? x[j] : neutral;
-      }
-    }
-    float acc[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      if (mode == MASKKV_POOL_MAX) {
-        acc[e] = __builtin_nanf("");
-#pragma unroll
-        for (int t = -R; t <= R; ++t)
-          if (FIXED || (t >= -r && t <= r)) acc[e] = fmaxf(acc[e], v[i][e + A + t]);
-      } else {
-        acc[e] = 0.f;  // (0 + x is x but for the sign of a zero, which the key does not see)
-#pragma unroll
-        for (int t = -R; t <= R; ++t)
-          if (FIXED || (t >= -r && t <= r)) acc[e] = __fadd_rn(acc[e], v[i][e + A + t]);
-      }
-    }
     uint32_t least = 0u, most = 0xFFFFFFFFu;  // of the sums' magnitudes (a NaN or an infinity is above every number)
-    if (R > 0 && mode != MASKKV_POOL_MAX) {
+    if (MODE != MASKKV_POOL_MAX) {
       uint32_t u[4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) u[e] = __builtin_bit_cast(uint32_t, acc[e]) & 0x7FFFFFFFu;
+      for (int e = 0; e < 4; ++e) u[e] = __builtin_bit_cast(uint32_t, acc[i][e]) & 0x7FFFFFFFu;
       least = min(min(u[0], u[1]), min(u[2], u[3]));
       most = max(max(u[0], u[1]), max(u[2], u[3]));
     }
@@ -314,13 +357,14 @@ __device__ __forceinline__ void pool_groups(const float* x, int j0, int step, in
         }
       }
 #pragma unroll
-      for (int e = 0; e < 4; ++e) key[4 * i + e] = inner || g0 + e < P ? order_key_nonzero(divided(acc[e], w[e], y[e])) : 0u;
+      for (int e = 0; e < 4; ++e)
+        key[4 * i + e] = inner || g0 + e < P ? order_key_nonzero(divided(acc[i][e], w[e], y[e])) : 0u;
     } else {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const int j = g0 + e;
-        if (R > 0 && mode != MASKKV_POOL_MAX) acc[e] = __fdiv_rn(acc[e], (float)(min(P - 1, j + r) - max(0, j - r) + 1));
-        key[4 * i + e] = j < P ? order_key(acc[e]) : 0u;
+        if (MODE != MASKKV_POOL_MAX) acc[i][e] = __fdiv_rn(acc[i][e], (float)(min(P - 1, j + r) - max(0, j - r) + 1));
+        key[4 * i + e] = j < P ? order_key(acc[i][e]) : 0u;
       }
     }
   }
@@ -329,21 +373,18 @@ __device__ __forceinline__ void pool_groups(const float* x, int j0, int step, in
 template <int G>
 __device__ __forceinline__ void pooled_keys(const float* x, int j0, int step, int P, int window, int mode, uint32_t (&key)[4 * G]) {
   const int r = (window - 1) / 2;
-  if (P >= 4 && r == 3 && mode == MASKKV_POOL_MEAN) {
-    pool_groups<3, true, G>(x, j0, step, P, r, MASKKV_POOL_MEAN, key);
-  } else if (P >= 4 && r <= 8) {  // group by group: registers of one group's wide windows only
-#pragma unroll 1
-    for (int i = 0; i < G; ++i) {
-      uint32_t k4[4];
+  if (P >= 4 && r <= 8) {
+    if (mode == MASKKV_POOL_MAX) {
       if (r <= 4)
-        pool_groups<4, false, 1>(x, j0 + i * step, 0, P, r, mode, k4);
+        pool_groups<4, false, MASKKV_POOL_MAX, G>(x, j0, step, P, r, key);
       else
-        pool_groups<8, false, 1>(x, j0 + i * step, 0, P, r, mode, k4);
-#pragma unroll
-      for (int u = 0; u < G; ++u)
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (u == i) key[4 * u + e] = k4[e];
+        pool_groups<8, false, MASKKV_POOL_MAX, G>(x, j0, step, P, r, key);
+    } else if (r == 3) {
+      pool_groups<3, true, MASKKV_POOL_MEAN, G>(x, j0, step, P, r, key);
+    } else if (r <= 4) {
+      pool_groups<4, false, MASKKV_POOL_MEAN, G>(x, j0, step, P, r, key);
+    } else {
+      pool_groups<8, false, MASKKV_POOL_MEAN, G>(x, j0, step, P, r, key);
     }
   } else {
 #pragma unroll
@@ -373,9 +414,11 @@ __device__ __forceinline__ int take_base(const SelShared<THREADS>& s) {
 }
 
 // ---- one workgroup per head: grid (BH), 4 * G keys a thread.  32 heads of 4096 positions: 16.0 us before (keys in LDS, one
-// wave walking the histogram, refinement to a single key, two passes for the ordered output), 6.3 us now; 8192
-// positions 20.0 us before (two stages) and 7.8 now (8.7 with a division per mean); 256 heads of 4096 ... 16384 positions 38
-// and 13.6 us (14.1).  Of the 13 thousand cycles at 4096 positions a third goes by until the keys are there, two thirds are the chain behind
+// wave walking the histogram, refinement to a single key, two passes for the ordered output), 6.1 us now; 8192
+// positions 20.0 us before (two stages) and 7.5 now; 12000 positions 11.7 us with every lane loading all of its windows, the ends of
+// the prompt read a second time and four groups a thread, 9.1 now, and 14.3 and 9.4 with a window other than 7 (group after group
+// before, each waiting for its own loads); 16384 positions 11.4 and 10.5; 256 heads of 4096 ... 16384 positions 38
+// and 13.6 us.  Of the 13 thousand cycles at 4096 positions a third goes by until the keys are there, two thirds are the chain behind
 // them.  Not better: the list ranked by all waves, each comparing a few, and the kept entries as a mask of bits.
 template <int THREADS, int G>
 __global__ __launch_bounds__(THREADS) void select_head_kernel(const SelectParams prm) {
@@ -429,7 +472,7 @@ __global__ __launch_bounds__(THREADS) void select_head_kernel(const SelectParams
   // ---- ordered output: the groups of all threads follow one another, so every group has a scan of its own; the counts of
   // two groups (at most 4 * THREADS <= 4096 each) share a word
   auto kept = [&](int i, int e) {
-    return valid(i, e) && code_of(key[4 * i + e], (uint32_t)(4 * (tid + i * THREADS) + e)) >= cut;
+    return code_of(key[4 * i + e], (uint32_t)(4 * (tid + i * THREADS) + e)) >= cut;
   };
   constexpr int kPairs = (G + 1) / 2;
   int own[kPairs], incl[kPairs];
@@ -750,18 +793,26 @@ int launch_select(const maskkv_desc* d, const Lens& lens, const float* scores, i
   prm.cand_key = reinterpret_cast<uint32_t*>(workspace);
   prm.cand_pos = reinterpret_cast<int32_t*>(prm.cand_key + select_cand_slots(d));
   prm.cand_cnt = prm.cand_pos + select_cand_slots(d);
-  // The fewest keys a thread that the prompt allows: the chain's length is what counts, and four waves start and meet at a
-  // barrier sooner than sixteen.
+  // One workgroup per head takes the fewest groups a thread that the prompt allows, and then the fewest waves: a group more costs
+  // 1.5 us (the chain of every wave is longer by its keys), 256 threads more 0.4 to 0.8 (four waves start and meet at a barrier
+  // sooner than sixteen).  32 heads, us, threads x groups: 2000 positions 256x2 6.3, 512x1 5.5, 768x1 5.8, 1024x1 6.3; 3000: 512x2
+  // 6.2, 768x1 5.8, 1024x1 6.2; 4096: 512x2 6.2, 1024x1 6.1; 6000: 512x3 7.3, 768x2 6.9, 1024x2 7.6; 8192: 512x4 8.1, 768x3 8.1,
+  // 1024x2 7.5; 12000: 768x4 9.5, 1024x3 9.2, 1024x4 11.0.
   if (d->P_max <= kSinglePrompt) {
-    const dim3 grid(prm.BH);
-    if (d->P_max <= 1024)
-      hipLaunchKernelGGL((select_head_kernel<256, 1>), grid, dim3(256), 0, stream, prm);
-    else if (d->P_max <= 4096)
-      hipLaunchKernelGGL((select_head_kernel<1024, 1>), grid, dim3(1024), 0, stream, prm);
-    else if (d->P_max <= 8192)
-      hipLaunchKernelGGL((select_head_kernel<1024, 2>), grid, dim3(1024), 0, stream, prm);
-    else
-      hipLaunchKernelGGL((select_head_kernel<1024, 4>), grid, dim3(1024), 0, stream, prm);
+    const int groups = max(1, (int)((d->P_max + 4 * kSelThreads - 1) / (4 * kSelThreads)));
+    const int threads = max(1, (int)((d->P_max + 1024 * groups - 1) / (1024 * groups))) * 256;
+    auto start = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(prm.BH), dim3(threads), 0, stream, prm); };
+    switch (groups << 16 | threads) {
+      case 1 << 16 | 256: start(select_head_kernel<256, 1>); break;
+      case 1 << 16 | 512: start(select_head_kernel<512, 1>); break;
+      case 1 << 16 | 768: start(select_head_kernel<768, 1>); break;
+      case 1 << 16 | 1024: start(select_head_kernel<1024, 1>); break;
+      case 2 << 16 | 768: start(select_head_kernel<768, 2>); break;
+      case 2 << 16 | 1024: start(select_head_kernel<1024, 2>); break;
+      case 3 << 16 | 768: start(select_head_kernel<768, 3>); break;
+      case 3 << 16 | 1024: start(select_head_kernel<1024, 3>); break;
+      default: start(select_head_kernel<1024, 4>); break;  // (four groups: more than 12288 positions)
+    }
     return check_launch("select (one stage)");
   }
   constexpr size_t dyn = (size_t)kSelLdsCap * sizeof(uint32_t);
