@@ -919,7 +919,10 @@ __global__ __launch_bounds__(PairsCfg<D>::kThreads) void attend_pairs_kernel(con
 
 // Merge the key splits of the query rows: O = sum_s w_s O_s / sum_s w_s l_s, w_s = 2^(m_s - max m).
 // A row is served by D/4 consecutive threads (four output elements each, 16-byte loads of the partials).
-template <typename T, int D>
+// N splits' partials are asked for before the first is used, as the waits are what it takes its time for.  Two splits need N = 2, more of
+// them 4 or 8 (us before, each loop waiting for its loads, and now: 2 splits of 16 x 506 rows 8.9 / 7.3, 64 x 106 rows, 8 splits, 6.9 / 4.8,
+// 4 x 265 rows, 20 splits, 12.2 / 6.4; with eight asked for where there are two 7.4 and, 96 x 148 rows, 5.6 for 5.3).
+template <typename T, int D, int N>
 __global__ __launch_bounds__(256) void attend_merge_kernel(const AttendParams prm) {
   constexpr int kTPR = D / 4;          // threads per row
   constexpr int kRows = 256 / kTPR;    // rows per workgroup
@@ -928,21 +931,44 @@ __global__ __launch_bounds__(256) void attend_merge_kernel(const AttendParams pr
   const int q = blockIdx.x * kRows + (int)threadIdx.x / kTPR;
   const int e = ((int)threadIdx.x % kTPR) * 4;
   if (q >= prm.n_q) return;
+  const float2* ml_of = prm.part_ml + (int64_t)bh * prm.n_splits * prm.n_q + q;
+  const float* o_of = prm.part_o + ((int64_t)bh * prm.n_splits * prm.n_q + q) * D + e;
+  float2 ml[N];
+  float4 o[N];
+  auto ask_ml = [&](int s0) {
+#pragma unroll
+    for (int u = 0; u < N; ++u)
+      if (s0 + u < prm.n_splits) ml[u] = ml_of[(int64_t)(s0 + u) * prm.n_q];
+  };
+  auto ask_o = [&](int s0) {
+#pragma unroll
+    for (int u = 0; u < N; ++u)
+      if (s0 + u < prm.n_splits) o[u] = *reinterpret_cast<const float4*>(o_of + (int64_t)(s0 + u) * prm.n_q * D);
+  };
+  ask_ml(0);
+  ask_o(0);
   float M = kNegBig;
-  for (int s = 0; s < prm.n_splits; ++s)
-    M = fmaxf(M, prm.part_ml[((int64_t)bh * prm.n_splits + s) * prm.n_q + q].x);
+  for (int s0 = 0; s0 < prm.n_splits; s0 += N) {
+    if (s0 > 0) ask_ml(s0);
+#pragma unroll
+    for (int u = 0; u < N; ++u)
+      if (s0 + u < prm.n_splits) M = fmaxf(M, ml[u].x);
+  }
   float L = 0.f;
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int s = 0; s < prm.n_splits; ++s) {
-    const int64_t slot = ((int64_t)bh * prm.n_splits + s) * prm.n_q + q;
-    const float2 ml = prm.part_ml[slot];
-    const float w = fast_exp2(ml.x - M);
-    const float4 v = *reinterpret_cast<const float4*>(prm.part_o + slot * D + e);
-    L += w * ml.y;
-    acc.x += w * v.x;
-    acc.y += w * v.y;
-    acc.z += w * v.z;
-    acc.w += w * v.w;
+  for (int s0 = 0; s0 < prm.n_splits; s0 += N) {
+    if (prm.n_splits > N) ask_ml(s0);
+    if (s0 > 0) ask_o(s0);
+#pragma unroll
+    for (int u = 0; u < N; ++u)
+      if (s0 + u < prm.n_splits) {
+        const float w = fast_exp2(ml[u].x - M);
+        L += w * ml[u].y;
+        acc.x += w * o[u].x;
+        acc.y += w * o[u].y;
+        acc.z += w * o[u].z;
+        acc.w += w * o[u].w;
+      }
   }
   const float inv = 1.f / L;
   char* orow = prm.O.group_row(b, h, prm.q_per_kv, prm.n_resp, q);
@@ -1178,8 +1204,13 @@ int launch_attend_t(const AttendParams& prm, int B, hipStream_t stream) {
   }
   if (prm.n_splits > 1) {
     constexpr int kRows = 256 / (D / 4);
-    hipLaunchKernelGGL((attend_merge_kernel<T, D>), dim3((prm.n_q + kRows - 1) / kRows, B * prm.H), dim3(256), 0,
-                       stream, prm);
+    const dim3 grid((prm.n_q + kRows - 1) / kRows, B * prm.H);
+    if (prm.n_splits <= 2)
+      hipLaunchKernelGGL((attend_merge_kernel<T, D, 2>), grid, dim3(256), 0, stream, prm);
+    else if (prm.n_splits <= 4)
+      hipLaunchKernelGGL((attend_merge_kernel<T, D, 4>), grid, dim3(256), 0, stream, prm);
+    else
+      hipLaunchKernelGGL((attend_merge_kernel<T, D, 8>), grid, dim3(256), 0, stream, prm);
     return check_launch("attend merge");
   }
   return MASKKV_OK;
