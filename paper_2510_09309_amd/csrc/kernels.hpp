@@ -72,7 +72,7 @@ size_t sweep_workspace_bytes(const maskkv_desc* d, int nqg, const SweepPlan& pla
 int hold_sweep(int64_t age_us, hipStream_t stream);
 int launch_sweep(const maskkv_desc* d, const View& Q, const View& K, const Lens& lens, float scale, float* scores,
                  int64_t score_stride, float* prompt_mass, float* group_sums, int64_t group_stride, int nqg, const SweepPlan& plan,
-                 void* area, hipStream_t stream, const float** unit_mass);
+                 void* area, hipStream_t stream, float** unit_mass);
 
 // select.hip
 size_t select_workspace_bytes(const maskkv_desc* d);
