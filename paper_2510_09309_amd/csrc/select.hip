@@ -54,12 +54,6 @@ __device__ __forceinline__ uint32_t order_key(float v) {
   if (u == 0x80000000u) u = 0u;                         // -0 and +0 compare equal: one key for both
   return u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);  // larger float <=> larger unsigned key
 }
-// The same of a value that is no zero.
-__device__ __forceinline__ uint32_t order_key_nonzero(float v) {
-  const uint32_t u = __builtin_bit_cast(uint32_t, v);
-  return u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
-}
-
 // Wave-level scans and reductions on the data-parallel-primitive path of the vector ALU (row shifts inside the
 // rows of 16 lanes, then the two row broadcasts): six dependent vector instructions, no LDS round trips.
 template <typename Op>
@@ -115,21 +109,27 @@ struct Range {
 };
 
 // Narrow `g` until it holds at most `enough` entries or a single value.  `each(f)` calls f(value, valid) for the entries of
-// this thread.  All threads call this; the histogram is clear on entry and on return.
-template <int THREADS, typename Each>
-__device__ __forceinline__ void refine(SelShared<THREADS>& s, Range& g, int enough, Each&& each) {
+// this thread; those that are not valid are `absent` or less, and LONG: a thread has so many that a test of each is worth a branch.
+// All threads call this; the histogram is clear on entry and on return.
+template <bool LONG, int THREADS, typename Each>
+__device__ __forceinline__ void refine(SelShared<THREADS>& s, Range& g, int enough, uint32_t absent, Each&& each) {
   constexpr int kBins = SelShared<THREADS>::kBins;
   constexpr int kWaves = SelShared<THREADS>::kWaves;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   while (g.lo != g.hi && g.pop > enough) {
     const uint32_t width = g.hi - g.lo;
     const int shift = max(0, 32 - __clz(width) - (31 - __builtin_clz(kBins)));  // (width >> shift) < kBins
-    const int top = (int)(width >> shift);
-    // bins are numbered from the top of the range: bin 0 holds the largest values
-    each([&](uint32_t v, bool valid) {
-      const uint32_t at = v - g.lo;
-      if (valid & (at <= width)) atomicAdd(&s.hist[top - (int)(at >> shift)], 1);
-    });
+    // bins are counted from the top of the range: bin 0 holds the largest values
+    if (LONG && g.lo > absent)
+      each([&](uint32_t v, bool) {
+        const uint32_t below = g.hi - v;
+        if (below <= width) atomicAdd(&s.hist[below >> shift], 1);
+      });
+    else
+      each([&](uint32_t v, bool valid) {
+        const uint32_t below = g.hi - v;
+        if (valid & (below <= width)) atomicAdd(&s.hist[below >> shift], 1);
+      });
     __syncthreads();
     const u32x2 two = reinterpret_cast<u32x2*>(s.hist)[tid];
     reinterpret_cast<u32x2*>(s.hist)[tid] = u32x2{0u, 0u};
@@ -146,16 +146,27 @@ __device__ __forceinline__ void refine(SelShared<THREADS>& s, Range& g, int enou
     if (above < g.krem && above + h0 + h1 >= g.krem) {  // exactly one thread owns the bin
       const bool second = above + h0 < g.krem;
       const int bin = 2 * tid + (second ? 1 : 0);
-      const uint32_t nlo = g.lo + ((uint32_t)(top - bin) << shift);
-      const uint32_t span = shift == 0 ? 0u : ((1u << shift) - 1u);
-      s.lo = nlo;
-      s.hi = (uint32_t)min((uint64_t)g.hi, (uint64_t)nlo + span);
+      const uint32_t from = (uint32_t)bin << shift;  // (below g.hi, and not more than width)
+      s.hi = g.hi - from;
+      s.lo = g.hi - min(from + ((1u << shift) - 1u), width);
       s.krem = g.krem - above - (second ? h0 : 0);
       s.pop = second ? h1 : h0;
     }
     __syncthreads();
     g = Range{s.lo, s.hi, s.krem, s.pop};
   }
+}
+
+// The largest values of a thread's quad or row of 16 lanes, of which the lowest of a workgroup bounds the k-th largest from below where
+// there are k quads or rows of them.
+__device__ __forceinline__ uint32_t quad_max(uint32_t v) {
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xf, 0xf, false));         // quad_perm:[1,0,3,2]
+  return max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xf, 0xf, false));      // quad_perm:[2,3,0,1]
+}
+__device__ __forceinline__ uint32_t row_max(uint32_t v) {
+  v = quad_max(v);
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x124, 0xf, 0xf, false));        // row_ror:4
+  return max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x128, 0xf, 0xf, false));     // row_ror:8
 }
 
 // Key range of the workgroup's entries from every thread's own (one barrier).
@@ -180,11 +191,11 @@ __device__ __forceinline__ void key_range(SelShared<THREADS>& s, uint32_t kmin, 
 
 // The code of the k-th entry in the order of the answer, or one that separates the first k from the rest (1 <= k <= n);
 // `each(f)` calls f(key, position, valid) for the entries of this thread.
-template <int THREADS, typename Each>
+template <bool LONG, int THREADS, typename Each>
 __device__ __forceinline__ uint64_t exact_cut(SelShared<THREADS>& s, uint32_t lo, uint32_t hi, int k, int n, uint32_t last_pos,
                                               Each&& each) {
   Range g{lo, hi, k, n};
-  refine(s, g, kRankable, [&](auto&& f) { each([&](uint32_t key, uint32_t, bool valid) { f(key, valid); }); });
+  refine<LONG>(s, g, kRankable, 0u, [&](auto&& f) { each([&](uint32_t key, uint32_t, bool valid) { f(key, valid); }); });
   if (g.krem == g.pop) return code_of(g.lo, last_pos);  // the whole bin is kept
   const uint32_t key_from = g.lo, key_span = g.hi - g.lo;
   uint32_t last = 0xFFFFFFFFu, first = 0u;  // ~position
@@ -192,15 +203,21 @@ __device__ __forceinline__ uint64_t exact_cut(SelShared<THREADS>& s, uint32_t lo
     const uint32_t tau = g.lo;
     g.lo = ~last_pos;
     g.hi = 0xFFFFFFFFu;
-    refine(s, g, kRankable, [&](auto&& f) { each([&](uint32_t key, uint32_t pos, bool valid) { f(~pos, valid && key == tau); }); });
+    refine<false>(s, g, kRankable, 0xFFFFFFFFu,
+                  [&](auto&& f) { each([&](uint32_t key, uint32_t pos, bool valid) { f(~pos, valid && key == tau); }); });
     if (g.krem == g.pop) return (uint64_t)tau << 32 | g.lo;
     first = g.lo;
     last = g.hi;
   }
-  each([&](uint32_t key, uint32_t pos, bool valid) {
-    if (valid & (key - key_from <= key_span) & (~pos >= first) & (~pos <= last))
-      s.list[atomicAdd(&s.listed, 1)] = code_of(key, pos);  // (g.pop <= kRankable of them)
-  });
+  const bool any = key_from > 0u && first == 0u && last == 0xFFFFFFFFu;  // (positions past the prompt have the key 0)
+  if (LONG && any)
+    each([&](uint32_t key, uint32_t pos, bool) {
+      if (key - key_from <= key_span) s.list[atomicAdd(&s.listed, 1)] = code_of(key, pos);  // (g.pop <= kRankable of them)
+    });
+  else
+    each([&](uint32_t key, uint32_t pos, bool valid) {
+      if (valid & (key - key_from <= key_span) & (~pos >= first) & (~pos <= last)) s.list[atomicAdd(&s.listed, 1)] = code_of(key, pos);
+    });
   __syncthreads();
   if (threadIdx.x < 64) {
     const uint64_t mine = (int)threadIdx.x < g.pop ? s.list[threadIdx.x] : 0u;
@@ -331,34 +348,19 @@ __device__ __forceinline__ void pool_groups(const float* x, int j0, int step, in
   for (int i = 0; i < G; ++i) {
     const int g0 = j0 + i * step;
     const bool inner = g0 >= A && g0 + 4 + A <= P;
-    uint32_t least = 0u, most = 0xFFFFFFFFu;  // of the sums' magnitudes (a NaN or an infinity is above every number)
+    // (as unsigned numbers negative sums, infinities and NaNs are above kDividableTo)
+    uint32_t least = 0u, most = 0xFFFFFFFFu;
     if (MODE != MASKKV_POOL_MAX) {
       uint32_t u[4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) u[e] = __builtin_bit_cast(uint32_t, acc[i][e]) & 0x7FFFFFFFu;
+      for (int e = 0; e < 4; ++e) u[e] = __builtin_bit_cast(uint32_t, acc[i][e]);
       least = min(min(u[0], u[1]), min(u[2], u[3]));
       most = max(max(u[0], u[1]), max(u[2], u[3]));
     }
-    if (least >= kDividableFrom && most <= kDividableTo) {
-      float w[4], y[4];
-      w[0] = (float)(2 * r + 1);
-      y[0] = inverse(w[0]);
+    if (inner && least >= kDividableFrom && most <= kDividableTo) {
+      const float w = (float)(2 * r + 1), y = inverse(w);
 #pragma unroll
-      for (int e = 1; e < 4; ++e) {
-        w[e] = w[0];
-        y[e] = y[0];
-      }
-      if (!inner) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int j = g0 + e;  // (of a position past the prompt nothing is used)
-          w[e] = (float)max(min(P - 1, j + r) - max(0, j - r) + 1, 1);
-          y[e] = inverse(w[e]);
-        }
-      }
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        key[4 * i + e] = inner || g0 + e < P ? order_key_nonzero(divided(acc[i][e], w[e], y[e])) : 0u;
+      for (int e = 0; e < 4; ++e) key[4 * i + e] = __builtin_bit_cast(uint32_t, divided(acc[i][e], w, y)) | 0x80000000u;
     } else {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
@@ -415,10 +417,13 @@ __device__ __forceinline__ int take_base(const SelShared<THREADS>& s) {
 
 // ---- one workgroup per head: grid (BH), 4 * G keys a thread.  32 heads of 4096 positions: 16.0 us before (keys in LDS, one
 // wave walking the histogram, refinement to a single key, two passes for the ordered output), 6.1 us now; 8192
-// positions 20.0 us before (two stages) and 7.5 now; 12000 positions 11.7 us with every lane loading all of its windows, the ends of
-// the prompt read a second time and four groups a thread, 9.1 now, and 14.3 and 9.4 with a window other than 7 (group after group
-// before, each waiting for its own loads); 16384 positions 11.4 and 10.5; 256 heads of 4096 ... 16384 positions 38
-// and 13.6 us.  Of the 13 thousand cycles at 4096 positions a third goes by until the keys are there, two thirds are the chain behind
+// positions 20.0 us before (two stages) and 7.2 now; 12000 positions 11.7 us with every lane loading all of its windows, the ends of
+// the prompt read a second time and four groups a thread, 8.6 now, and 14.3 and 8.9 with a window other than 7 (group after group
+// before, each waiting for its own loads); 16384 positions 11.4 and 9.5; 256 heads of 4096 ... 16384 positions 38
+// and 11 us.  With three or four groups a thread it is the instructions a key that count, some 30 in all (1.4 us a group; 1.1 us of 10.5
+// went with keys of positive means by one instruction instead of four, bins counted from the top, and, from three groups on, no bounds
+// where the key tells and the keys below the k-th largest for certain left out of the histogram: with fewer groups the code that this
+// adds costs a cold call as much as it saves).  Of the 13 thousand cycles at 4096 positions a third goes by until the keys are there, two thirds are the chain behind
 // them.  Not better: the list ranked by all waves, each comparing a few, and the kept entries as a mask of bits.
 template <int THREADS, int G>
 __global__ __launch_bounds__(THREADS) void select_head_kernel(const SelectParams prm) {
@@ -453,6 +458,21 @@ __global__ __launch_bounds__(THREADS) void select_head_kernel(const SelectParams
       }
     }
   }
+  // Of the k largest keys none is below the lowest of k or more threads' (quads', rows') largest: the other two thirds (nine tenths) of
+  // the keys need no place in the histogram.
+  const int threads = min(THREADS, (P + 3) / 4);  // that have a key
+  if (G > 2 && kh <= threads && P > kRankable) {
+    kmin = kmax;
+    int of = 1;
+    if (kh <= (threads + 15) / 16) {
+      kmin = row_max(kmax);
+      of = 16;
+    } else if (kh <= (threads + 3) / 4) {
+      kmin = quad_max(kmax);
+      of = 4;
+    }
+    if ((tid & -of) >= threads) kmin = 0xFFFFFFFFu;
+  }
   uint32_t lo, hi;
   key_range(s, kmin, kmax, lo, hi);
   const int base = take_base(s);
@@ -462,7 +482,7 @@ __global__ __launch_bounds__(THREADS) void select_head_kernel(const SelectParams
   }
   if (kh == 0) return;
 
-  const uint64_t cut = exact_cut(s, lo, hi, kh, P, (uint32_t)(P - 1), [&](auto&& f) {
+  const uint64_t cut = exact_cut<(G > 2)>(s, lo, hi, kh, P, (uint32_t)(P - 1), [&](auto&& f) {
 #pragma unroll
     for (int i = 0; i < G; ++i)
 #pragma unroll
@@ -548,7 +568,7 @@ __global__ __launch_bounds__(kSelThreads, 8) void select_chunk_kernel(const Sele
   // of that bin becomes a candidate, so the bound need not be tight; the final stage finds the cut exactly).
   Range g{lo, hi, kc, n};
   if (kc < n)
-    refine(s, g, kRankable, [&](auto&& f) {
+    refine<false>(s, g, kRankable, 0u, [&](auto&& f) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) f(key[e], e < nmine);
     });
@@ -686,7 +706,7 @@ __global__ __launch_bounds__(kSelThreads) void select_final_kernel(const SelectP
   key_range(s, kmin, kmax, lo, hi);
 
   // (an entry's number in the list stands for its position: the list is in position order)
-  const uint64_t cut = exact_cut(s, lo, hi, kh, n, (uint32_t)(n - 1), [&](auto&& f) {
+  const uint64_t cut = exact_cut<false>(s, lo, hi, kh, n, (uint32_t)(n - 1), [&](auto&& f) {
     for (int e = tid; e < n; e += kSelThreads) f(key_at(e), (uint32_t)e, true);
   });
 
@@ -797,7 +817,7 @@ int launch_select(const maskkv_desc* d, const Lens& lens, const float* scores, i
   // 1.5 us (the chain of every wave is longer by its keys), 256 threads more 0.4 to 0.8 (four waves start and meet at a barrier
   // sooner than sixteen).  32 heads, us, threads x groups: 2000 positions 256x2 6.3, 512x1 5.5, 768x1 5.8, 1024x1 6.3; 3000: 512x2
   // 6.2, 768x1 5.8, 1024x1 6.2; 4096: 512x2 6.2, 1024x1 6.1; 6000: 512x3 7.3, 768x2 6.9, 1024x2 7.6; 8192: 512x4 8.1, 768x3 8.1,
-  // 1024x2 7.5; 12000: 768x4 9.5, 1024x3 9.2, 1024x4 11.0.
+  // 1024x2 7.5; 12000: 768x4 9.5, 1024x3 9.2, 1024x4 11.0 (all before the last 0.3 to 1.0 us went).
   if (d->P_max <= kSinglePrompt) {
     const int groups = max(1, (int)((d->P_max + 4 * kSelThreads - 1) / (4 * kSelThreads)));
     const int threads = max(1, (int)((d->P_max + 1024 * groups - 1) / (1024 * groups))) * 256;

@@ -53,3 +53,23 @@ def test_scores_of_the_lowest_key_are_ties_within_the_prompt(P):
     keeps = run(sc, [P], budgets, 1, 0)
     for bh in range(2):
         assert np.array_equal(keeps[bh], np.arange(budgets[bh]))
+
+
+@pytest.mark.parametrize("P", [8193, 9217, 12289, 16384])
+def test_budgets_around_the_bounds_of_the_histogram(P):
+    """As many kept positions as there are threads, quads and rows of lanes with a key, and one more or less; scores in ascending order and
+    ones of which all but a few lie in one thread's four positions put the k-th largest at the bound."""
+    rng = np.random.default_rng(P)
+    threads = min((1024 if P > 9216 or P <= 8192 else 768), (P + 3) // 4)
+    ks = [k + e for k in ((threads + 15) // 16, (threads + 3) // 4, threads) for e in (-1, 0, 1)]
+    for kind in range(3):
+        sc = rng.random((len(ks), P)).astype(np.float32)
+        if kind == 1:
+            sc = np.sort(sc, axis=1)
+        if kind == 2:
+            sc[:, 256:] *= np.float32(2.0 ** -20)
+        budgets = np.array(ks, dtype=np.int32)
+        for window in (1, 7):
+            keeps = run(sc, [P], budgets, window, 0)
+            for h in range(len(ks)):
+                assert np.array_equal(keeps[h], orc.select(orc.pool(sc[h], window, "mean", dtype=np.float32), ks[h])), (kind, window, ks[h])
