@@ -25,7 +25,6 @@ struct SweepPlan {
   __host__ __device__ int times(int i) const { return repeats[i] & 0xFFFF; }
   __host__ __device__ int sequence(int i) const { return repeats[i] >> 16; }
   __host__ __device__ bool has(int i, int w) const { return w >= place(i) && w < place(i) + width(i); }
-  __host__ __device__ bool serves(int i, int b, int h) const { return sequence(i) == b && h >= head(i) && h < head(i) + side(i) * times(i); }
   void put(int i, int p, int s, int w, int b, int h) {
     places[i] = (uint32_t)p | (uint32_t)w << 16;
     heads[i] = (uint32_t)h | (uint32_t)s << 16;

@@ -262,29 +262,82 @@ __device__ __forceinline__ float sum_of_waves(uint32_t lds) {
 // ---- response span: row references, zeroed sums, and the voting rows in the order in which the sweep reads them.
 // A workgroup serves BLOCKS blocks of 32 rows of a unit; 8 / BLOCKS waves share a block's keys, which come through LDS 128
 // at a time.  (Eight blocks where there are units enough to fill the chip: each key is then read once per unit.)
+// The plan's runs in the lanes of a wave: what a loop over them reads is then a register of the wave's instead of a scalar load that it
+// waits for (all of them once; a round of the loop costs the waits 0.3 us).
+struct Runs {
+  uint32_t places[kMaxRuns / 64], heads[kMaxRuns / 64], repeats[kMaxRuns / 64];
+  int n;
+  bool halves;
+  __device__ __forceinline__ explicit Runs(const SweepPlan& plan) : n(plan.runs), halves(plan.halves()) {
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int k = 0; k < kMaxRuns / 64; ++k)
+      if (k == 0 || n > 64 * k) {
+        places[k] = plan.places[64 * k + lane];
+        heads[k] = plan.heads[64 * k + lane];
+        repeats[k] = plan.repeats[64 * k + lane];
+        asm volatile("" : "+v"(places[k]), "+v"(heads[k]), "+v"(repeats[k]));  // (here, where all lanes are: others read them later)
+      }
+  }
+  static __device__ __forceinline__ uint32_t of(const uint32_t (&v)[kMaxRuns / 64], int i) {
+    uint32_t x = (uint32_t)__builtin_amdgcn_readlane((int)v[0], i & 63);
+#pragma unroll
+    for (int k = 1; k < kMaxRuns / 64; ++k)
+      if (i >= 64 * k) x = (uint32_t)__builtin_amdgcn_readlane((int)v[k], i & 63);
+    return x;
+  }
+  // The run that serves a head of a sequence, or n.
+  __device__ __forceinline__ int serving(int b, int h) const {
+    const int lane = threadIdx.x & 63;
+    int i = n;
+#pragma unroll
+    for (int k = kMaxRuns / 64 - 1; k >= 0; --k)
+      if (k == 0 || n > 64 * k) {
+        const int from = heads[k] & 0xFFFF, side = heads[k] >> 16, times = repeats[k] & 0xFFFF;
+        const uint64_t they =
+            __builtin_amdgcn_ballot_w64(64 * k + lane < n && (int)(repeats[k] >> 16) == b && h >= from && h < from + side * times);
+        if (they) i = 64 * k + __builtin_ctzll(they);
+      }
+    return i;
+  }
+  // Calls each(w has a chunk in it, its repetitions) for the rounds that end before run i.
+  template <typename Each>
+  __device__ __forceinline__ void rounds(int i, int w, Each&& each) const {
+    bool has = false;
+    uint32_t times = 0;
+    for (int j = 0; j < i; ++j) {
+      const uint32_t place = of(places, j);
+      const int at = place & 0xFFFF;
+      if (at == 0 || j == 0) {
+        if (j > 0) each(has, (int)times);
+        has = false;
+        times = of(repeats, j) & 0xFFFF;
+      }
+      has = has || (w >= at && w < at + (int)(place >> 16));
+    }
+    // (the round that run i belongs to may have begun before it)
+    if (i > 0 && (i == n || (of(places, i) & 0xFFFF) == 0)) each(has, (int)times);
+  }
+};
+
 // Takes the lock, or waits for it (2 us), and counts every workgroup's chunks: for a workgroup of its own, the first, so that this is
 // over when the others are.
 __device__ __forceinline__ void start_lock(const SweepParams& prm) {
+  const Runs runs(prm.plan);
   const int w = threadIdx.x;
-  if (w < prm.plan.groups) {
-    int n = 0;
-    for (int i = 0; i < prm.plan.runs;) {
-      const int times = prm.plan.times(i);
-      bool has = false;
-      do has = has || prm.plan.has(i, w);
-      while (++i < prm.plan.runs && prm.plan.place(i) > 0);  // (to the end of the round)
-      if (!has && prm.plan.halves()) {
-        Chunk c;
-        c.bh = 0;
-        c.shape = 0;
-        c.keys = prm.K.row(0, 0, 0);
-        c.out = prm.out;
-        for (int t = n; t < n + times; ++t) prm.table[(int64_t)w * prm.rounds + t] = c;
-      }
-      n += has || prm.plan.halves() ? times : 0;
+  int n = 0;
+  runs.rounds(runs.n, w, [&](bool has, int times) {
+    if (!has && runs.halves && w < prm.plan.groups) {
+      Chunk c;
+      c.bh = 0;
+      c.shape = 0;
+      c.keys = prm.K.row(0, 0, 0);
+      c.out = prm.out;
+      for (int t = n; t < n + times; ++t) prm.table[(int64_t)w * prm.rounds + t] = c;
     }
-    prm.counts[w] = n;
-  }
+    n += has || runs.halves ? times : 0;
+  });
+  if (w < prm.plan.groups) prm.counts[w] = n;
   if (threadIdx.x >= 64) return;
   bool run = take_lock(prm.plan.grid, 0);
   const uint64_t t0 = wall_clock64();
@@ -301,30 +354,24 @@ __device__ __forceinline__ void start_lock(const SweepParams& prm) {
 
 // The table's entries of a head (to be called by a whole wave).
 __device__ __forceinline__ void start_table(const SweepParams& prm, int b, int vh) {
+  const Runs runs(prm.plan);
   const int lane = threadIdx.x & 63;
   const int P = prm.lens.P[b], nc = (P + kKeys - 1) / kKeys;
-  int i = 0;
-  while (i < prm.plan.runs && !prm.plan.serves(i, b, vh)) ++i;
-  if (i == prm.plan.runs) return;  // (no prompt)
-  const int nth = vh - prm.plan.head(i), side = prm.plan.side(i);
-  const int w0 = prm.plan.place(i) + nth % side * nc;
-  for (int ci = lane; ci < nc; ci += 64) {
-    const int w = w0 + ci;
+  const int i = runs.serving(b, vh);
+  if (i == runs.n) return;  // (no prompt)
+  const uint32_t heads = Runs::of(runs.heads, i);
+  const int nth = vh - (int)(heads & 0xFFFF), side = heads >> 16;
+  const int w0 = (int)(Runs::of(runs.places, i) & 0xFFFF) + nth % side * nc;
+  for (int c0 = 0; c0 < nc; c0 += 64) {
+    const int ci = c0 + lane, w = w0 + ci;
     int t = nth / side;
-    for (int j = 0; j < i;) {
-      const int times = prm.plan.times(j);
-      bool has = prm.plan.halves();
-      do has = has || prm.plan.has(j, w);
-      while (++j < i && prm.plan.place(j) > 0);
-      // (the round that run i belongs to may have begun before it: its other runs have other workgroups)
-      t += has && (j < i || prm.plan.place(i) == 0) ? times : 0;
-    }
+    runs.rounds(i, w, [&](bool has, int times) { t += has || runs.halves ? times : 0; });
     Chunk c;
     c.bh = b * prm.heads() + vh;
     c.shape = (uint32_t)ci | (uint32_t)(nc - 1) << 8 | (uint32_t)min(P - ci * kKeys, kKeys) << 16;
     c.keys = prm.K.row(b, vh / prm.subsets, (int64_t)ci * kKeys);
     c.out = prm.out + (int64_t)c.bh * prm.out_stride + ci * kKeys;
-    prm.table[(int64_t)w * prm.rounds + t] = c;
+    if (ci < nc) prm.table[(int64_t)w * prm.rounds + t] = c;
   }
 }
 
