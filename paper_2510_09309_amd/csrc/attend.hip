@@ -296,6 +296,7 @@ struct NarrowCfg {
 
 template <int D>
 __global__ __launch_bounds__(NarrowCfg<D>::kThreads) void attend_narrow_kernel(const AttendParams prm) {
+  fetch_attend_arguments<true>();
   using C = NarrowCfg<D>;
   constexpr int NW = C::kWaves;
   extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -502,6 +503,7 @@ __device__ __forceinline__ float sum_of_groups(float v) {
 
 template <int D>
 __global__ __launch_bounds__(SmallCfg<D>::kThreads) void attend_small_kernel(const AttendParams prm) {
+  fetch_attend_arguments<true>();
   using C = SmallCfg<D>;
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
@@ -698,6 +700,7 @@ struct PairsCfg {
 
 template <int D>
 __global__ __launch_bounds__(PairsCfg<D>::kThreads) void attend_pairs_kernel(const AttendParams prm) {
+  fetch_attend_arguments<true>();
   using C = PairsCfg<D>;
   constexpr int S = C::kSteps, M = C::kMoves;
   extern __shared__ __attribute__((aligned(1024))) char smem[];
@@ -924,6 +927,7 @@ __global__ __launch_bounds__(PairsCfg<D>::kThreads) void attend_pairs_kernel(con
 // 4 x 265 rows, 20 splits, 12.2 / 6.4; with eight asked for where there are two 7.4 and, 96 x 148 rows, 5.6 for 5.3).
 template <typename T, int D, int N>
 __global__ __launch_bounds__(256) void attend_merge_kernel(const AttendParams prm) {
+  fetch_arguments({MASKKV_VIEW_ARGUMENTS(AttendParams, O), MASKKV_ARGUMENT(AttendParams, H), MASKKV_ARGUMENT(AttendParams, part_ml)});
   constexpr int kTPR = D / 4;          // threads per row
   constexpr int kRows = 256 / kTPR;    // rows per workgroup
   const int bh = blockIdx.y;

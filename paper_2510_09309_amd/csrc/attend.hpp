@@ -29,6 +29,14 @@ struct AttendParams {
   float2* part_ml;   // [BH][n_splits][n_q]
 };
 
+// GRID: the kernel uses the size of its grid, which lies behind the parameter.
+template <bool GRID>
+__device__ __forceinline__ void fetch_attend_arguments() {
+  typedef AttendParams A;
+  fetch_arguments({MASKKV_VIEW_ARGUMENTS(A, Q), MASKKV_VIEW_ARGUMENTS(A, K2), MASKKV_VIEW_ARGUMENTS(A, V2), MASKKV_VIEW_ARGUMENTS(A, O),
+                   MASKKV_ARGUMENT(A, lens), MASKKV_ARGUMENT(A, Kc), MASKKV_ARGUMENT(A, H), (uint32_t)(GRID ? sizeof(A) : offsetof(A, part_o))});
+}
+
 // Rows of V (bf16) in LDS as direct transfers leave them: no padding, the 32-byte unit u of a row in slot u ^ v_swizzle(row).  A
 // transposing read takes 32 bytes of four rows per 16 lanes and 64 bytes of four rows per 32 lanes, and both sets fall on
 // different banks.

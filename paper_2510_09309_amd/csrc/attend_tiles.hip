@@ -119,6 +119,7 @@ __global__ __launch_bounds__(kWaves * 64) void attend_tiles_kernel(const AttendP
   constexpr bool RANKED = KIND == kRanked;
   constexpr bool kFew = HALVES && D == 64;  // registers: no more than 168, up to which the next workgroup starts when the last one's second group has left
   constexpr int kAheadFrag = kFew && RANKED ? 2 : 3;  // LDS fragments requested ahead of the MFMA that takes them
+  fetch_attend_arguments<!RANKED>();
   extern __shared__ __attribute__((aligned(1024))) char tiles_lds[];
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)tiles_lds;
 

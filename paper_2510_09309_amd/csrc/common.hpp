@@ -2,6 +2,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 #include "../../include/maskkv.h"
@@ -39,6 +40,27 @@ struct View {
     return row(b, h * g + gi, r - gi * n_per);
   }
 };
+
+// A kernel's arguments are written for each launch, so no cache holds them, and every 64-byte line of them that is first read behind a
+// wait costs a latency of its own (0.2 to 0.3 us; two to five in turn before the first load of a kernel's inputs).  This asks for a word
+// of each line at once (`at`: offsets within the kernel's only parameter); what is read later comes from the scalar cache.  us a
+// layer: 4k keys 42.9 -> 42.3, 3k and 5k at head_dim 64 37.8 -> 37.1, 30k with 7 query heads a head 108.8 -> 107.9; eviction of 8
+// sequences of 32 heads 32.1 -> 31.6.  (Not in the sweep kernel, whose arguments are in its caches when most of its loads are issued:
+// 8 x 32 heads with 512 rows 488 us without, 491 with.)
+template <int N>
+__device__ __forceinline__ void fetch_arguments(const uint32_t (&at)[N]) {
+  const auto words = (const __attribute__((address_space(4))) uint32_t*)__builtin_amdgcn_kernarg_segment_ptr();
+  static_assert(N <= 16, "sixteen words are what is asked for at once");
+  uint32_t w[16];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) w[i] = words[at[i < N ? i : 0] / 4];
+  asm volatile("" ::"s"(w[0]), "s"(w[1]), "s"(w[2]), "s"(w[3]), "s"(w[4]), "s"(w[5]), "s"(w[6]), "s"(w[7]), "s"(w[8]), "s"(w[9]),
+               "s"(w[10]), "s"(w[11]), "s"(w[12]), "s"(w[13]), "s"(w[14]), "s"(w[15]));
+  __builtin_amdgcn_sched_barrier(0);
+}
+#define MASKKV_ARGUMENT(params, member) (uint32_t) offsetof(params, member)
+// Of a view: where its strides and its first sequences' offsets lie.
+#define MASKKV_VIEW_ARGUMENTS(params, view) (uint32_t) offsetof(params, view), (uint32_t)(offsetof(params, view) + offsetof(View, boff) + 40)
 
 // Query heads that share one key/value head (1 for plain multi-head attention).
 __host__ __device__ inline int query_heads_per_kv(const maskkv_desc* d) { return d->q_per_kv > 1 ? d->q_per_kv : 1; }

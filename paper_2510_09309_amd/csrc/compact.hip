@@ -32,6 +32,9 @@ constexpr int kCmpRows = 2;  // destination rows per thread
 constexpr int kFewHeads = 256;
 
 __global__ __launch_bounds__(256) void compact_few_kernel(const CompactParams prm) {
+  typedef CompactParams A;
+  fetch_arguments({MASKKV_VIEW_ARGUMENTS(A, K), MASKKV_VIEW_ARGUMENTS(A, V), MASKKV_ARGUMENT(A, lens), MASKKV_ARGUMENT(A, B),
+                   MASKKV_ARGUMENT(A, capacity), MASKKV_ARGUMENT(A, Vc)});
   constexpr int N = kFewHeads / 64;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int ppr = prm.row_bytes / 16;  // pieces per row: 8, 16 or 32

@@ -38,6 +38,12 @@ __device__ __forceinline__ void mfma16(const u32x4& a, const u32x4& b, f32x4& ac
   }
 }
 
+__device__ __forceinline__ void fetch_rows_arguments() {
+  typedef RowsParams R;
+  fetch_arguments({MASKKV_VIEW_ARGUMENTS(R, Q), MASKKV_VIEW_ARGUMENTS(R, K), MASKKV_ARGUMENT(R, lens), MASKKV_ARGUMENT(R, B), MASKKV_ARGUMENT(R, out),
+                   MASKKV_ARGUMENT(R, stats)});
+}
+
 template <int CTRL>
 __device__ __forceinline__ float dpp(float v) {
   return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, false));
@@ -70,6 +76,7 @@ __global__ __launch_bounds__(kThreads, 2) void score_rows_kernel(const RowsParam
   constexpr int kInFlight = D * NT > 128 * 16 ? 8 : 16;        // fragments of keys (as the registers allow)
   __shared__ float wave_max[kWaves][kRowsWG];
   __shared__ float2 wave_sum[kWaves][kRowsWG];  // over the prompt's keys and the response span's
+  fetch_rows_arguments();
   const int lane = threadIdx.x & 63, n = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int b = blockIdx.z, h = blockIdx.y, bh = b * prm.H + h;
@@ -189,6 +196,7 @@ template <int D, int RG>
 __global__ __launch_bounds__(64 * kStatWaves) void rows_stats_kernel(const RowsParams prm) {
   constexpr int S = D * 4 / 64;
   __shared__ float4 of_wave[kStatWaves][RG * kRowsWG];
+  fetch_rows_arguments();
   const int lane = threadIdx.x & 63, n = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int bh = blockIdx.z, b = prm.B == 1 ? 0 : bh / prm.H, h = bh - b * prm.H;
@@ -274,6 +282,7 @@ __global__ __launch_bounds__(kThreads) void rows_columns_kernel(const RowsParams
   constexpr int S = D * 4 / 64;
   __shared__ float of_wave[kWaves][NT * kTile];
   __shared__ double mass_of_wave[kWaves];
+  fetch_rows_arguments();
   const int lane = threadIdx.x & 63, n = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int bh = blockIdx.y, b = prm.B == 1 ? 0 : bh / prm.H, h = bh - b * prm.H;

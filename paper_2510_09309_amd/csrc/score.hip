@@ -127,6 +127,9 @@ __global__ __launch_bounds__((ScoreCfg<T, D, PASS>::kThreads), (ScoreCfg<T, D, P
   extern __shared__ __attribute__((aligned(16))) char kt_raw[];  // two K tiles
   __shared__ float cs[3][C::kWaves][C::kTK];  // pass 2: per-wave column partials of the last three tiles
   __shared__ float nlse[kQPerGroup];            // pass 2: -lse2 of the current query group
+  typedef ScoreParams A;
+  fetch_arguments({MASKKV_VIEW_ARGUMENTS(A, Q), MASKKV_VIEW_ARGUMENTS(A, K), MASKKV_ARGUMENT(A, lens), MASKKV_ARGUMENT(A, map),
+                   (uint32_t)(offsetof(A, map) + 64), MASKKV_ARGUMENT(A, B), MASKKV_ARGUMENT(A, stats), MASKKV_ARGUMENT(A, prompt_mass)});
 
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
@@ -357,6 +360,8 @@ __global__ __launch_bounds__((ScoreCfg<T, D, PASS>::kThreads), (ScoreCfg<T, D, P
 // head, which took its groups one after the other: 8 heads of 2317 rows and 8272 positions 21.9 us, 5.0 now; 658 rows and 20439
 // positions 13.1 and 6.2.)
 __global__ __launch_bounds__(256) void score_merge_kernel(const ScoreParams prm) {
+  fetch_arguments({MASKKV_ARGUMENT(ScoreParams, lens), (uint32_t)offsetof(ScoreParams, map1), (uint32_t)(offsetof(ScoreParams, map1) + 64),
+                   MASKKV_ARGUMENT(ScoreParams, B), MASKKV_ARGUMENT(ScoreParams, stats), MASKKV_ARGUMENT(ScoreParams, prompt_mass)});
   __shared__ float red[256];
   const TileMap& map = prm.map1;
   const int bh = blockIdx.x / map.nqg, group = blockIdx.x % map.nqg;
@@ -422,6 +427,8 @@ __global__ __launch_bounds__(256) void score_merge_kernel(const ScoreParams prm)
 // with each load waited for and one thread walking the masses, 4.5 now; 689 positions, 651 rows of 8 heads 13.2 and 5.8; two parts as
 // before (5.3 us at 8373 positions and 112 heads).
 __global__ __launch_bounds__(256) void score_group_sum_kernel(const ScoreParams prm, int nqg) {
+  fetch_arguments({MASKKV_ARGUMENT(ScoreParams, lens), MASKKV_ARGUMENT(ScoreParams, B), MASKKV_ARGUMENT(ScoreParams, scores),
+                   MASKKV_ARGUMENT(ScoreParams, mass_step)});  // (the last one's line has nqg as well)
   constexpr int kInFlight = 16;
   const int bh = blockIdx.y;
   const int P = prm.lens.P[bh / prm.H];
@@ -467,6 +474,8 @@ __global__ __launch_bounds__(256) void score_group_sum_kernel(const ScoreParams 
 constexpr int kMassThreads = 1024;
 
 __global__ __launch_bounds__(kMassThreads) void score_mass_kernel(const ScoreParams prm) {
+  fetch_arguments({MASKKV_ARGUMENT(ScoreParams, lens), MASKKV_ARGUMENT(ScoreParams, B), MASKKV_ARGUMENT(ScoreParams, scores),
+                   MASKKV_ARGUMENT(ScoreParams, prompt_mass)});
   constexpr int kInFlight = 32;  // (a whole 32k prompt at once: the loop's round trips are what a head's sum waits for)
   __shared__ float red[kMassThreads / 64];
   const int bh = blockIdx.x;

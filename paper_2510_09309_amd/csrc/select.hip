@@ -49,6 +49,11 @@ struct SelectParams {
   int32_t* cand_cnt;   // [BH][max_chunks] candidates per chunk
 };
 
+__device__ __forceinline__ void fetch_select_arguments() {
+  typedef SelectParams A;
+  fetch_arguments({MASKKV_ARGUMENT(A, lens), MASKKV_ARGUMENT(A, H), MASKKV_ARGUMENT(A, capacity)});
+}
+
 __device__ __forceinline__ uint32_t order_key(float v) {
   uint32_t u = __builtin_bit_cast(uint32_t, v);
   if (u == 0x80000000u) u = 0u;                         // -0 and +0 compare equal: one key for both
@@ -427,6 +432,7 @@ __device__ __forceinline__ int take_base(const SelShared<THREADS>& s) {
 // them.  Not better: the list ranked by all waves, each comparing a few, and the kept entries as a mask of bits.
 template <int THREADS, int G>
 __global__ __launch_bounds__(THREADS) void select_head_kernel(const SelectParams prm) {
+  fetch_select_arguments();
   __shared__ SelShared<THREADS> s;
   const int bh = blockIdx.x;
   const int b = bh / prm.H;
@@ -540,6 +546,7 @@ __global__ __launch_bounds__(THREADS) void select_head_kernel(const SelectParams
 // ---- chunk stage: grid (BH, max_chunks).  Eight waves per SIMD, i.e. at most 64 registers: two workgroups then fit a
 // compute unit.  32 heads of 32768 positions: 10.8 us before, 7.0 now.
 __global__ __launch_bounds__(kSelThreads, 8) void select_chunk_kernel(const SelectParams prm) {
+  fetch_select_arguments();
   __shared__ SelShared<kSelThreads> s;
   const int bh = blockIdx.x;
   const int b = bh / prm.H;
@@ -604,6 +611,7 @@ __global__ __launch_bounds__(kSelThreads, 8) void select_chunk_kernel(const Sele
 // ---- final stage: grid (BH), over the chunk stage's candidates.  32 heads of 32768 positions and 171 ... 341 kept rows:
 // 14.0 us before, 8.4 now.
 __global__ __launch_bounds__(kSelThreads) void select_final_kernel(const SelectParams prm) {
+  fetch_select_arguments();
   extern __shared__ uint32_t lds_words[];
   __shared__ SelShared<kSelThreads> s;
   __shared__ int coff[kMaxChunks + 1];  // candidates before chunk c

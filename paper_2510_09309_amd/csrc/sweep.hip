@@ -135,6 +135,13 @@ struct SweepParams {
   __device__ int heads() const { return H * subsets; }  // of a sequence, subsets counted as heads
 };
 
+__device__ __forceinline__ void fetch_sweep_arguments() {
+  typedef SweepParams A;
+  fetch_arguments({MASKKV_VIEW_ARGUMENTS(A, Q), MASKKV_VIEW_ARGUMENTS(A, K), MASKKV_ARGUMENT(A, lens), MASKKV_ARGUMENT(A, B), MASKKV_ARGUMENT(A, n_qh),
+                   MASKKV_ARGUMENT(A, plan.places), MASKKV_ARGUMENT(A, plan.heads), MASKKV_ARGUMENT(A, table), MASKKV_ARGUMENT(A, patience),
+                   MASKKV_ARGUMENT(A, units), MASKKV_ARGUMENT(A, parts), MASKKV_ARGUMENT(A, out)});
+}
+
 // The workgroups of a sweep wait for each other, so all of them have to be resident, and two sweeps may not be placed on a device at
 // the same time.  The lock holds how many workgroups all sweeps together have been or are to be placed (32 bits, wrapping),
 // and when it was last changed (32 bits, in kTick); what has been placed counts itself in 16 places, since 256 additions to one
@@ -386,6 +393,7 @@ __device__ __forceinline__ void start_table(const SweepParams& prm, int b, int v
 template <int D, int BLOCKS>
 __global__ __launch_bounds__(kThreads) void sweep_start_kernel(const SweepParams prm) {
   using C = Cfg<D>;
+  fetch_sweep_arguments();
   constexpr int S = C::kSteps, SPLIT = kWaves / BLOCKS;
   constexpr bool kShared = BLOCKS < 8;
   const int lane = threadIdx.x & 63, r = lane & 31, g = lane >> 5;
