@@ -209,6 +209,7 @@ struct Cfg {
   static constexpr int kOffMass = kOffInf + 128;               // [2][kWaves] floats
   static constexpr int kOffBad = kOffMass + 2 * kWaves * 4;    // one int: the scores of this workgroup are void
   static constexpr int kOffLate = kOffBad + 4;                 // two ints: 1 + the first unit that late_masses has to do, or 0
+  static constexpr int kOffRedo = kOffBad + 12;                // one int: another workgroup's are
   static constexpr int kLds = kOffBad + 64;
   // Rows are stored without padding (a direct transfer writes 1 KiB of consecutive LDS); piece p of row r sits in
   // slot p ^ swz(r), which spreads the fragment reads of 16 consecutive rows over all banks.
@@ -1193,9 +1194,9 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
   if (run && threadIdx.x == 0)
     __hip_atomic_fetch_add(&sweep_placed[blockIdx.x % kPlaces * kPlaceWords], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   if (threadIdx.x < 32) *in_lds<float>(lds0 + C::kOffInf + threadIdx.x * 4) = -INFINITY;
-  // (kOffBad and kOffLate; a workgroup that is placed when others have already given up, or that may not run as a sweep's, goes straight to
+  // (kOffBad, kOffLate and kOffRedo; a workgroup that is placed when others have already given up, or that may not run as a sweep's, goes straight to
   // the fallback; what one wave has read of `redo` holds for all)
-  if (threadIdx.x < 3) *in_lds<int>(lds0 + C::kOffBad + threadIdx.x * 4) = threadIdx.x == 0 ? redo : 0;
+  if (threadIdx.x < 4) *in_lds<int>(lds0 + C::kOffBad + threadIdx.x * 4) = threadIdx.x == 0 ? redo : 0;
   for (int i = threadIdx.x; i < 2 * kWaves * kKeys; i += kThreads) *in_lds<float>(lds0 + C::kOffCs + i * 4) = 0.f;
   if (threadIdx.x < 2 * kWaves) *in_lds<float>(lds0 + C::kOffMass + threadIdx.x * 4) = 0.f;
   // (all but the second chunk's keys: each group of waves waits for its part of them before the other one forms that chunk, see below)
@@ -1328,6 +1329,10 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
   } while (s < mine);
   // ---- the last step: completed at once, by the first group while the second publishes it
   const int par = mine & 1;
+  // Whether others have given up, for the kernel's end (who gives up itself has kOffBad): by one wave for all of them, who have to agree,
+  // and here, where its answer comes with those of the sums.  Each wave asking at the end: 0.5 us of every call.
+  int others = 0;
+  if (wave == 0) others = __hip_atomic_load(&prm.ctl->redo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   if (!HALVES || !prev.idle()) {
     ask_again(prev);
     if (par)
@@ -1335,6 +1340,7 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
     else
       complete(prev, par, pb);
   }
+  if (wave == 0 && lane == 0) *in_lds<int>(lds0 + C::kOffRedo) = others;
   end_vector();
   if (flushes) flush(done, par ^ 1, mine >= 2);
   if (HALVES) flush(prev, par, true);
@@ -1364,7 +1370,8 @@ __global__ __launch_bounds__(kThreads, 2) void sweep_kernel(const SweepParams pr
   const int late2 = HALVES ? __builtin_amdgcn_readfirstlane(*in_lds<const int>(lds0 + Cfg<D>::kOffLate, 4)) : 0;
   if (__builtin_expect(late, 0)) late_masses<D>(argument_again(), lds0, late);
   if (HALVES && __builtin_expect(late2, 0)) late_masses<D>(argument_again(), lds0, late2);
-  if (__hip_atomic_load(&prm.ctl->redo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) sweep_redo<D>(argument_again(), lds0);
+  const int redo = *in_lds<const int>(lds0 + Cfg<D>::kOffBad) | *in_lds<const int>(lds0 + Cfg<D>::kOffRedo);
+  if (__builtin_amdgcn_readfirstlane(redo)) sweep_redo<D>(argument_again(), lds0);
 }
 
 __global__ void hold_kernel(int64_t age) {
