@@ -1330,7 +1330,7 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
   // ---- the last step: completed at once, by the first group while the second publishes it
   const int par = mine & 1;
   // Whether others have given up, for the kernel's end (who gives up itself has kOffBad): by one wave for all of them, who have to agree,
-  // and here, where its answer comes with those of the sums.  Each wave asking at the end: 0.5 us of every call.
+  // and here, where its answer comes with those of the sums.
   int others = 0;
   if (wave == 0) others = __hip_atomic_load(&prm.ctl->redo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   if (!HALVES || !prev.idle()) {
