@@ -260,8 +260,10 @@ __global__ __launch_bounds__(kWaves * 64) void attend_tiles_kernel(const AttendP
   // a lane, keep the texture path busy four times as long, in front of the first tiles: 256 heads x 256 queries over 320 ... 768 keys 30.65
   // us against 30.25, 140 x 311, head_dim 64, 28.2 / 27.4, 256 x 512 over 576 ... 1536 76.5 / 75.8.)
   if constexpr (!HALVES) {
+    const int moves = ntiles > 0 ? 32 / C::kRPI : 0;  // (a part of the keys may be empty: nothing then waits for a transfer)
 #pragma unroll
     for (int j = 0; j < 32 / C::kRPI; ++j) {
+      if (j >= moves) break;
       const uint32_t row = j * C::kRPI + mrow;
       const char* from = prm.Q.group_row(b, h, prm.q_per_kv, prm.n_resp, min(qtile * C::kQueries + part * 32 + (int)row, prm.n_q - 1));
       dma16_from(from + ((mpiece ^ C::swz_k(row)) << 4), lds0 + C::kOffQ + part * 32 * C::kRowB + j * 1024);

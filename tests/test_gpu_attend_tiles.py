@@ -77,3 +77,26 @@ def test_tiles_full_sequence(P, n, d):
         ref, rl = orc.attend_full(*[x[0, h].float().numpy() for x in t], return_lse=True)
         assert np.abs(O[0, h].float().cpu().numpy() - ref).max() <= hp.ATTEND_ATOL_BF16
         assert np.abs(lse.cpu().numpy().reshape(H, n)[h] - rl).max() <= 1e-3
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("n", [100, 256, 300])
+def test_tiles_empty_parts(n, d):
+    """The un-evicted call over a batch whose shortest sequences leave parts of the key axis without a key: such a part has nothing to
+    wait for, and may not leave a transfer into LDS behind for whoever gets that LDS next."""
+    m = hp.mk()
+    gen = torch.Generator(device="cuda").manual_seed(n + d)
+    B, H, Ps = 3, 4, [9000, 1, 200]
+    N = max(Ps) + n
+    desc = m.Desc(B=B, H=H, d=d, dtype=m.MASKKV_BF16, n_resp=n, P_max=max(Ps), prompt_len=Ps)
+    Q, K, V = (torch.randn((B, H, x, d), generator=gen, device="cuda").to(torch.bfloat16) for x in (n, N, N))
+    O = torch.full((B, H, n, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    lse = torch.full((B * H, n), float("nan"), dtype=torch.float32, device="cuda")
+    m.maskkv_attend_full(desc, Q, K, V, 0.0, O, lse, hp.workspace(m.maskkv_attend_workspace_bytes(desc, True)))
+    for b, P in enumerate(Ps):
+        for h in range(H):
+            s = Q[b, h].double() @ K[b, h, :P + n].double().T / d ** 0.5
+            p, v = torch.softmax(s, dim=1), V[b, h, :P + n].double()
+            # a probability and the result are rounded to bf16, by up to 2^-8 of themselves each
+            assert ((O[b, h].double() - p @ v).abs() <= 2.0 ** -7 * (p @ v.abs())).all()
+            assert ((lse[b * H + h].double() - torch.logsumexp(s, dim=1)).abs() <= 2.0 ** -14).all()
