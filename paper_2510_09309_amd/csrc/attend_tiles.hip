@@ -14,7 +14,7 @@
 // matrix phases t-1 (K(t-1), V(t-2)), which both groups have left behind barrier t.
 //
 // Where 256 queries a workgroup leave compute units idle (HALVES), a workgroup serves 128: both groups have the same queries, group
-// i takes tiles 2u + i through rings of two slots of its own, and the two partial results are merged through LDS.
+// i takes tiles 2u + i through rings of two slots of its own, and the two partial results are merged through LDS, half by each group.
 //
 // What bounds it: power, in a loop of nothing but these calls, and before that the vector phase.  A tile of 256 queries takes 3150 cycles
 // (2048 of them MFMAs: a matrix phase is 1370 cycles, a vector phase 340 for the transfers and 1100 to 1250 for the softmax), 3850 with
@@ -32,6 +32,8 @@
 namespace maskkv {
 
 namespace {
+
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 constexpr int kWaves = 8;
 constexpr int kTK = 64;      // keys per tile
@@ -258,20 +260,17 @@ __global__ __launch_bounds__(kWaves * 64) void attend_tiles_kernel(const AttendP
   u32x4 qf[C::kSteps];
   // A wave moves its 32 rows as whole rows, into LDS that no tile needs before the third one.  (Its fragments straight from memory, a row
   // a lane, keep the texture path busy four times as long, in front of the first tiles: 256 heads x 256 queries over 320 ... 768 keys 30.65
-  // us against 30.25, 140 x 311, head_dim 64, 28.2 / 27.4, 256 x 512 over 576 ... 1536 76.5 / 75.8.)
-  if constexpr (!HALVES) {
-    const int moves = ntiles > 0 ? 32 / C::kRPI : 0;  // (a part of the keys may be empty: nothing then waits for a transfer)
+  // us against 30.25, 140 x 311, head_dim 64, 28.2 / 27.4, 256 x 512 over 576 ... 1536 76.5 / 75.8.
+  // With HALVES the second V tiles' slots have room for them, and the two waves of the same rows move half of these each.)
+  constexpr int kQRows = HALVES ? 16 : 32;
+  const uint32_t q_at = lds0 + (HALVES ? (5 + part / 2 * 2) * C::kTileB + part % 2 * (32 * C::kRowB) : C::kOffQ + part * (32 * C::kRowB));
+  if (ntiles > 0) {  // (a part of the keys may be empty: nothing then waits for a transfer)
 #pragma unroll
-    for (int j = 0; j < 32 / C::kRPI; ++j) {
-      if (j >= moves) break;
-      const uint32_t row = j * C::kRPI + mrow;
+    for (int j = 0; j < kQRows / C::kRPI; ++j) {
+      const uint32_t row = (HALVES && second ? kQRows : 0) + j * C::kRPI + mrow;
       const char* from = prm.Q.group_row(b, h, prm.q_per_kv, prm.n_resp, min(qtile * C::kQueries + part * 32 + (int)row, prm.n_q - 1));
-      dma16_from(from + ((mpiece ^ C::swz_k(row)) << 4), lds0 + C::kOffQ + part * 32 * C::kRowB + j * 1024);
+      dma16_from(from + ((mpiece ^ C::swz_k(row)) << 4), q_at + (HALVES && second ? kQRows * C::kRowB : 0) + j * 1024);
     }
-  } else {
-    const char* qrow = prm.Q.group_row(b, h, prm.q_per_kv, prm.n_resp, min(q, prm.n_q - 1));
-#pragma unroll
-    for (int s = 0; s < C::kSteps; ++s) qf[s] = *reinterpret_cast<const u32x4*>(qrow + s * 32 + g * 16);
   }
 
   f32x16 o[C::kDB], s[2];
@@ -419,13 +418,14 @@ __global__ __launch_bounds__(kWaves * 64) void attend_tiles_kernel(const AttendP
       move_k(2);
       move_v(1);
     }
-    if (!HALVES) {
+    if (HALVES)
+      asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"i"(3 * C::kMoves) : "memory");
+    else
       asm volatile("s_waitcnt vmcnt(%0)" ::"i"(5 * C::kMoves) : "memory");
 #pragma unroll
-      for (int i = 0; i < C::kSteps; ++i) qf[i] = *in_lds<const u32x4>(ka[i] + C::kOffQ + part * 32 * C::kRowB);
-    }
+    for (int i = 0; i < C::kSteps; ++i) qf[i] = *in_lds<const u32x4>(q_at + (ka[i] - own));
 #pragma unroll
-    for (int i = 0; i < C::kSteps; ++i) asm volatile("" : "+v"(qf[i]));  // (read before the barrier: the third V tile takes their place)
+    for (int i = 0; i < C::kSteps; ++i) asm volatile("" : "+v"(qf[i]));  // (read before the barrier: V tiles take their place)
     asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"i"((HALVES ? 2 : 4) * C::kMoves) : "memory");
     if (second) asm volatile("s_barrier" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
@@ -455,35 +455,67 @@ __global__ __launch_bounds__(kWaves * 64) void attend_tiles_kernel(const AttendP
   }
 
   float l_tot = l + xor32(l);
-  if (HALVES) {  // group 1 leaves its part in LDS, group 0 adds it to its own
-    float* po = reinterpret_cast<float*>(tiles_lds) + part * (C::kDB * 16 * 64);  // [db][i][lane]
-    float2* ml = reinterpret_cast<float2*>(tiles_lds + 4 * C::kDB * 16 * 64 * 4) + part * 64;
-    __syncthreads();
-    if (second) {
+  // HALVES: each group has half of the head dimension in the end; the other half of its part is for the other group, through LDS.  (us a
+  // call, with all of it put together by one group, 4 bytes a lane, and the queries a row a lane, before: 196 heads x 167 queries over 230 ... 350
+  // keys 26.2 / 24.8, 48 x 1200 over 360 ... 700 32.1 / 30.6.)
+  constexpr int kOwn = HALVES ? C::kDB / 2 : C::kDB;  // blocks of 32 elements
+  f32x16 res[kOwn];
+  int e0 = 0;  // its first element
+  if constexpr (HALVES) {
+    f32x4* const parts = reinterpret_cast<f32x4*>(tiles_lds);  // [wave][kOwn][4][lane]
+    float2* const ml = reinterpret_cast<float2*>(tiles_lds + kWaves * kOwn * 4 * 64 * 16);
+    f32x4* const to = parts + wave * (kOwn * 4 * 64) + lane;
+    const f32x4* const from = parts + (wave ^ 4) * (kOwn * 4 * 64) + lane;
+    auto give = [&](int db0) {
 #pragma unroll
-      for (int db = 0; db < C::kDB; ++db)
+      for (int db = 0; db < kOwn; ++db)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) po[(db * 16 + i) * 64 + lane] = o[db][i];
-      ml[lane] = make_float2(m, l_tot);
-    }
+        for (int i = 0; i < 4; ++i)
+          to[(db * 4 + i) * 64] = f32x4{o[db0 + db][4 * i], o[db0 + db][4 * i + 1], o[db0 + db][4 * i + 2], o[db0 + db][4 * i + 3]};
+    };
     __syncthreads();
-    if (second) return;
-    const float2 other = ml[lane];
+    if (second)
+      give(0);
+    else
+      give(kOwn);
+    ml[wave * 64 + lane] = make_float2(m, l_tot);
+    __syncthreads();
+    const float2 other = ml[(wave ^ 4) * 64 + lane];
     const float top = fmaxf(m, other.x);
-    const float wa = fast_exp2(m - top), wb = fast_exp2(other.x - top);
+    const float w_own = fast_exp2(m - top), w_other = fast_exp2(other.x - top);
+    const float wa = second ? w_other : w_own, wb = second ? w_own : w_other;  // of group 0 and of group 1
     m = top;
-    l_tot = wa * l_tot + wb * other.y;
+    l_tot = wa * (second ? other.y : l_tot) + wb * (second ? l_tot : other.y);
+    auto take = [&](auto group) {
+      constexpr bool kFirst = decltype(group)::value == 0;
+      constexpr int db0 = kFirst ? 0 : kOwn;
 #pragma unroll
-    for (int db = 0; db < C::kDB; ++db)
+      for (int db = 0; db < kOwn; ++db)
 #pragma unroll
-      for (int i = 0; i < 16; ++i) o[db][i] = wa * o[db][i] + wb * po[(db * 16 + i) * 64 + lane];
+        for (int i = 0; i < 4; ++i) {
+          const f32x4 v = from[(db * 4 + i) * 64];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float mine_of = o[db0 + db][4 * i + e], theirs = v[e];
+            res[db][4 * i + e] = wa * (kFirst ? mine_of : theirs) + wb * (kFirst ? theirs : mine_of);
+          }
+        }
+    };
+    if (second)
+      take(std::integral_constant<int, 1>());
+    else
+      take(std::integral_constant<int, 0>());
+    e0 = second ? kOwn * 32 : 0;
+  } else {
+#pragma unroll
+    for (int db = 0; db < kOwn; ++db) res[db] = o[db];
   }
   if (q >= prm.n_q) return;  // (of two lanes 32 apart both or none)
   if (prm.n_splits == 1) {
     const float inv = 1.f / l_tot;
-    char* orow = prm.O.group_row(b, h, prm.q_per_kv, prm.n_resp, q) + 16 * g;
+    char* orow = prm.O.group_row(b, h, prm.q_per_kv, prm.n_resp, q) + 2 * e0 + 16 * g;
 #pragma unroll
-    for (int db = 0; db < C::kDB; ++db)
+    for (int db = 0; db < kOwn; ++db)
 #pragma unroll
       for (int qd = 0; qd < 4; qd += 2) {
         // A lane has four elements of each eight, the lane 32 on the other four: one gives the second four for the first ones of the next
@@ -494,8 +526,8 @@ __global__ __launch_bounds__(kWaves * 64) void attend_tiles_kernel(const AttendP
         u32x4 w;
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
-          const uint32_t first = pack_bf16x2(o[db][4 * qd + 2 * i] * inv, o[db][4 * qd + 2 * i + 1] * inv);
-          const uint32_t next = pack_bf16x2(o[db][4 * qd + 4 + 2 * i] * inv, o[db][4 * qd + 5 + 2 * i] * inv);
+          const uint32_t first = pack_bf16x2(res[db][4 * qd + 2 * i] * inv, res[db][4 * qd + 2 * i + 1] * inv);
+          const uint32_t next = pack_bf16x2(res[db][4 * qd + 4 + 2 * i] * inv, res[db][4 * qd + 5 + 2 * i] * inv);
           const auto sw = __builtin_amdgcn_permlane32_swap(first, next, false, false);
           const unsigned w0 = sw[0], w1 = sw[1];
           w[i] = w0;
@@ -503,17 +535,17 @@ __global__ __launch_bounds__(kWaves * 64) void attend_tiles_kernel(const AttendP
         }
         *reinterpret_cast<u32x4*>(orow + (db * 32 + 8 * qd) * 2) = w;
       }
-    if (prm.lse && g == 0) prm.lse[(int64_t)bh * prm.n_q + q] = (m + __log2f(l_tot)) * kLn2;
+    if (prm.lse && g == 0 && e0 == 0) prm.lse[(int64_t)bh * prm.n_q + q] = (m + __log2f(l_tot)) * kLn2;
   } else {
     const int64_t at = ((int64_t)bh * prm.n_splits + split) * prm.n_q + q;
-    float* po = prm.part_o + at * D;
+    float* po = prm.part_o + at * D + e0;
 #pragma unroll
-    for (int db = 0; db < C::kDB; ++db)
+    for (int db = 0; db < kOwn; ++db)
 #pragma unroll
       for (int qd = 0; qd < 4; ++qd)
         *reinterpret_cast<float4*>(po + db * 32 + 8 * qd + 4 * g) =
-            make_float4(o[db][4 * qd], o[db][4 * qd + 1], o[db][4 * qd + 2], o[db][4 * qd + 3]);
-    if (g == 0) prm.part_ml[at] = make_float2(m, l_tot);
+            make_float4(res[db][4 * qd], res[db][4 * qd + 1], res[db][4 * qd + 2], res[db][4 * qd + 3]);
+    if (g == 0 && e0 == 0) prm.part_ml[at] = make_float2(m, l_tot);
   }
 }
 
