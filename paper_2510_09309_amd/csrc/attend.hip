@@ -185,7 +185,7 @@ __global__ __launch_bounds__((AttCfg<D>::kThreads)) void attend_kernel(const Att
     for (int kb = 0; kb < C::kNKB; ++kb)
 #pragma unroll
       for (int i = 0; i < 16; ++i) bm = fmaxf(bm, s[kb][i]);
-    bm = fmaxf(bm, xor32(bm));
+    bm = max_halves(bm);
     // The reference m is only raised when a tile exceeds it by more than 2^kLazyBump: probabilities then stay
     // below 2^kLazyBump (harmless in fp32 sums and as bf16 operands, whose exponent range is fp32's), and the
     // accumulators are rescaled on few tiles only.
@@ -236,7 +236,7 @@ __global__ __launch_bounds__((AttCfg<D>::kThreads)) void attend_kernel(const Att
     if (t + 1 < ntiles) tile_step(t + 1, kra, vra);
   }
 
-  const float l_tot = l + xor32(l);
+  const float l_tot = sum_halves(l);
   if (q >= prm.n_q) return;
   if (prm.n_splits == 1) {
     const float inv = 1.f / l_tot;
@@ -388,7 +388,7 @@ __global__ __launch_bounds__(NarrowCfg<D>::kThreads) void attend_narrow_kernel(c
     float bm = s[0];
 #pragma unroll
     for (int i = 1; i < 16; ++i) bm = fmaxf(bm, s[i]);
-    bm = fmaxf(bm, xor32(bm));
+    bm = max_halves(bm);
     const float cand = bm * c;
     const bool bump = cand > m + kLazyBump;  // the reference is raised lazily, as in the tiled kernel
     if (__any(bump)) {
@@ -426,7 +426,7 @@ __global__ __launch_bounds__(NarrowCfg<D>::kThreads) void attend_narrow_kernel(c
   }
 
   // ---- merge the waves' partial results through LDS (the V tiles are no longer needed)
-  const float l_tot = l + xor32(l);
+  const float l_tot = sum_halves(l);
   float* mo = reinterpret_cast<float*>(smem);                          // [wave][db][i][lane]
   float2* ml = reinterpret_cast<float2*>(smem + C::kLds - NW * 32 * 8);  // [wave][query]
   __syncthreads();
@@ -492,13 +492,13 @@ __device__ __forceinline__ float max_of_groups(float v) {  // over the lanes c, 
   const auto sw = __builtin_amdgcn_permlane16_swap(as_u32(v), as_u32(v), false, false);
   const unsigned u0 = sw[0], u1 = sw[1];
   v = fmaxf(as_f32(u0), as_f32(u1));
-  return fmaxf(v, xor32(v));
+  return max_halves(v);
 }
 __device__ __forceinline__ float sum_of_groups(float v) {
   const auto sw = __builtin_amdgcn_permlane16_swap(as_u32(v), as_u32(v), false, false);
   const unsigned u0 = sw[0], u1 = sw[1];
   v = as_f32(u0) + as_f32(u1);
-  return v + xor32(v);
+  return sum_halves(v);
 }
 
 template <int D>
@@ -823,7 +823,7 @@ __global__ __launch_bounds__(PairsCfg<D>::kThreads) void attend_pairs_kernel(con
     float bm = s[0];
 #pragma unroll
     for (int i = 1; i < 16; ++i) bm = fmaxf(bm, s[i]);
-    bm = fmaxf(bm, xor32(bm));
+    bm = max_halves(bm);
     const float cand = bm * c;
     const bool bump = cand > m;  // (each time, see above)
     if (__any(bump)) {
@@ -874,7 +874,7 @@ __global__ __launch_bounds__(PairsCfg<D>::kThreads) void attend_pairs_kernel(con
   // g = d / 4 % 2 in slot (query + 32 g) ^ mix(k, g) of 64, so that a row's pieces, which its threads read next, are on different banks
   constexpr int kPieces = D / 64;  // of four elements a thread, side by side
   auto mix = [](int k, int g) { return D == 128 ? k : k ^ g << 3; };
-  const float l_tot = l + xor32(l);
+  const float l_tot = sum_halves(l);
 #pragma unroll
   for (int k = 0; k < D / 8; ++k)
     *in_lds<f32x4>(own + ((lane ^ mix(k, g)) << 4), k * 1024) = f32x4{o[k / 4][k % 4 * 4], o[k / 4][k % 4 * 4 + 1], o[k / 4][k % 4 * 4 + 2], o[k / 4][k % 4 * 4 + 3]};

@@ -363,11 +363,7 @@ __global__ __launch_bounds__(kWaves * 64) void attend_tiles_kernel(const AttendP
     for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
       for (int i = 0; i < 16; ++i) bm = fmaxf(bm, s[kb][i]);
-    {
-      const auto sw = __builtin_amdgcn_permlane32_swap(as_u32(bm), as_u32(bm), false, false);
-      const uint32_t s0 = sw[0], s1 = sw[1];
-      bm = fmaxf(as_f32(s0), as_f32(s1));
-    }
+    bm = max_halves(bm);
     // The reference m is only raised when a tile exceeds it by more than 2^kLazyBump (see attend.hip).
     const float cand = bm * c;
     const bool bump = cand > m + kLazyBump;
@@ -472,7 +468,7 @@ __global__ __launch_bounds__(kWaves * 64) void attend_tiles_kernel(const AttendP
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (no transfer into LDS outlives its workgroup)
   }
 
-  float l_tot = l + xor32(l);
+  float l_tot = sum_halves(l);
   // HALVES: each group has half of the head dimension in the end; the other half of its part is for the other group, through LDS.  (us a
   // call, with all of it put together by one group, 4 bytes a lane, and the queries a row a lane, before: 196 heads x 167 queries over 230 ... 350
   // keys 26.2 / 24.8, 48 x 1200 over 360 ... 700 32.1 / 30.6.)

@@ -298,7 +298,7 @@ __global__ __launch_bounds__((ScoreCfg<T, D, PASS>::kThreads), (ScoreCfg<T, D, P
           for (int blk = 0; blk < C::kNQ; ++blk)
 #pragma unroll
             for (int i = 0; i < 16; ++i) colsum += fast_exp2(a[blk][i] * c);
-          colsum += xor32(colsum);
+          colsum = sum_halves(colsum);
           if (g == 0) cs[t % 3][wave][kb * 32 + r] = colsum;
         }
       };

@@ -689,7 +689,7 @@ __device__ __forceinline__ void sweep_redo(const SweepParams& prm, uint32_t lds0
               float v = 0.f;
 #pragma unroll
               for (int i = 0; i < 16; ++i) v += fast_exp2(fmaf(a[kb][i], prm.c, nl[i]));
-              v += xor32(v);
+              v = sum_halves(v);
               if (g == 0) *in_lds<float>(colsum + ((n & 1) * kWaves * kKeys + wave * kKeys + kb * 32 + r) * 4) = v;
             }
           } else {
