@@ -93,7 +93,8 @@ struct Control {
   int ticket;   // next task of the fallback
 };
 
-constexpr int kSpans = 8;                  // pieces of a unit's keys in the fallback, at most
+constexpr int kSpans = 8;                  // pieces of a unit's keys in the fallback's first pass, at most
+constexpr int kSpanChunks = 8;             // chunks of a piece in its second pass where a head has several groups of rows, at most
 
 // A chunk of a head's keys.
 struct __attribute__((aligned(16))) Chunk {
@@ -202,7 +203,8 @@ struct Cfg {
   static constexpr int kMoves = kKeys / kWaves / kRPI;  // transfers per wave and chunk
   static constexpr int kKBytes = kKeys * kRowB;
   static constexpr int kQBytes = 32 * kRowB;        // per wave
-  static constexpr int kOffStart = kRing * kKBytes; // behind the ring of chunks: [2][kWaves][64] floats
+  static constexpr int kOffStart = kRing * kKBytes; // behind the ring of chunks: [2][kWaves][64] floats (fallback: [kSpanChunks][kKeys])
+  static_assert(kSpanChunks * kKeys == 2 * kWaves * 64, "a piece's column sums take the references' place");
   static constexpr int kOffCs = kOffStart + 2 * kWaves * 256;  // [2][kWaves][kKeys] floats
   static constexpr int kOffW = kOffCs + 2 * kWaves * kKeys * 4;  // [kWaves][32] floats
   static constexpr int kOffInf = kOffW + kWaves * 128;         // 32 floats: -inf
@@ -655,9 +657,14 @@ __device__ __forceinline__ void sweep_redo(const SweepParams& prm, uint32_t lds0
         float v = 0.f;
 #pragma unroll
         for (int w = 0; w < kWaves; ++w) v += *in_lds<const float>(cs, w * kKeys * 4);
-        float* to = prm.out + (int64_t)bh * prm.out_stride + j;  // (this thread has written the sums of the groups before)
-        if (unit > first) v += __hip_atomic_load(to, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(to, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        // Whole sums only are stored: a workgroup that is still in its walk stores the same ones at any time, which would otherwise count
+        // the groups before twice.
+        const uint32_t kept = lds0 + C::kOffStart + (n * kKeys + threadIdx.x) * 4;
+        if (unit > first) v += *in_lds<const float>(kept);
+        if (unit < first + prm.nqg - 1)
+          *in_lds<float>(kept) = v;
+        else
+          __hip_atomic_store(prm.out + (int64_t)bh * prm.out_stride + j, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       };
       if (c0 < c1) {
         dma(0);
@@ -723,7 +730,7 @@ __device__ __forceinline__ void sweep_redo(const SweepParams& prm, uint32_t lds0
       if (second && c0 < c1) {
         __syncthreads();
         flush(c1 - c0 - 1);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (the next group adds to these sums, and its transfers reuse the ring)
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (the next group's transfers reuse the ring)
         __syncthreads();
       }
       if (!second) {
@@ -1601,6 +1608,7 @@ int launch_sweep(const maskkv_desc* d, const View& Q, const View& K, const Lens&
   prm.patience = 10000 + (int)min(x / plan.groups * 500, (int64_t)1000000);
   prm.spans = spans_of(d->B * d->H * nqg);
   prm.spans2 = max(1, min(kMaxGroups, 2 * kMaxGroups / (d->B * d->H * plan.subsets)));
+  if (prm.nqg > 1) prm.spans2 = max(prm.spans2, ((d->P_max + kKeys - 1) / kKeys + kSpanChunks - 1) / kSpanChunks);
   prm.c = scale * kLog2e;
   const Layout l(d, nqg, plan);
   char* base = reinterpret_cast<char*>(area);

@@ -190,6 +190,47 @@ def test_fallback_at_edges_of_chunks_spans_and_row_groups(d, n_m, H, Ps):
     assert torch.allclose(mass, want_mass, rtol=32 * 2.0 ** -24, atol=0)
 
 
+def beside_a_copy(batch, which, value, run, calls=20):
+    """What calls leave, while copies on another stream keep writing `value` over the scores (which = 0) or masses (1) that they write.
+    run: whether they have the device's sweep, or find it taken."""
+    from paper_2510_09309_amd import bench_binding as bb
+    m = hp.mk()
+    ws = hp.workspace(m.maskkv_score_workspace_bytes(batch.desc))
+    outs = [(torch.full((batch.B * batch.H, batch.P_max), float("nan"), device="cuda"), torch.zeros(batch.B * batch.H, device="cuda")) for _ in range(calls)]
+    other = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    for out in outs:
+        if not run:
+            bb.maskkv_bench_hold_sweep(0)
+        with torch.cuda.stream(other):
+            for _ in range(10):
+                out[which].copy_(value)
+            m.maskkv_score(batch.desc, batch.Q, batch.K, 0.0, out[0], batch.P_max, out[1], ws, torch.cuda.default_stream())
+            for _ in range(60):
+                out[which].copy_(value)
+        torch.cuda.synchronize()
+        assert int(ws[:4].view(torch.int32)[0]) == run
+    if not run:
+        bb.maskkv_bench_hold_sweep(-1)
+    return outs
+
+
+@pytest.mark.parametrize("d,n_m,H,Ps", [(128, 512, 2, (900, 5000)), (64, 700, 3, (2500,)), (128, 300, 1, (1025,))])
+def test_fallback_beside_a_workgroup_that_still_stores_its_sums(d, n_m, H, Ps):
+    """Two and three groups of rows a workgroup: the fallback neither adds to sums that a workgroup of the sweep, still in its walk, has
+    stored as a whole, nor leaves a part of its own for long.  (That workgroup's part is played by a copy of the right sums.)"""
+    from paper_2510_09309_amd import bench_binding as bb
+    batch = hp.Batch([synth.make_layer(60 + i, H=H, d=d, P=P, n_m=n_m, dtype="bf16", n_planted=P // 50, amplitude=2.5) for i, P in enumerate(Ps)])
+    plan = bb.maskkv_bench_score_plan(batch.desc)
+    assert plan.groups > 0 and (n_m + 255) // 256 > plan.subsets
+    want, want_mass, run = swept(batch, hp.workspace(hp.mk().maskkv_score_workspace_bytes(batch.desc)))
+    assert run == 1
+    for scores, mass in beside_a_copy(batch, 0, want, 0):
+        # two ways to form the same fp32 sums: logits of up to 2^5 binary orders
+        assert torch.allclose(scores, want, rtol=32 * 2.0 ** -24, atol=0, equal_nan=True)
+        assert torch.allclose(mass, want_mass, rtol=32 * 2.0 ** -24, atol=0)
+
+
 def test_sweeps_on_two_streams_line_up():
     """Of calls that two streams make at once, at most a few need the fallback, and all give what one stream gives."""
     m = hp.mk()
