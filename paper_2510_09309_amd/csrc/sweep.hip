@@ -128,7 +128,7 @@ struct SweepParams {
   int* spans_done;  // [units] spans of the unit whose statistics are there (fallback)
   uint32_t* parts;  // [units][8 waves][n_parts] bits of a chunk's part of the mass of 32 rows, or kNoPart
   int n_parts;      // chunks of the longest prompt
-  int* late;        // [units] 1 + the next unit of a workgroup's list for late_masses, or 0
+  int* late;        // [B*H*subsets] 1 + the next head of a workgroup's list for late_masses, or 0
   float2* stats;    // [units][spans][256] (reference, sum) of a span of chunks (fallback)
   float* out;       // [B*H*subsets][out_stride]
   int64_t out_stride;
@@ -210,7 +210,7 @@ struct Cfg {
   static constexpr int kOffInf = kOffW + kWaves * 128;         // 32 floats: -inf
   static constexpr int kOffMass = kOffInf + 128;               // [2][kWaves] floats
   static constexpr int kOffBad = kOffMass + 2 * kWaves * 4;    // one int: the scores of this workgroup are void
-  static constexpr int kOffLate = kOffBad + 4;                 // two ints: 1 + the first unit that late_masses has to do, or 0
+  static constexpr int kOffLate = kOffBad + 4;                 // two ints: 1 + the first head that late_masses has to do, or 0
   static constexpr int kOffRedo = kOffBad + 12;                // one int: another workgroup's are
   static constexpr int kLds = kOffBad + 64;
   // Rows are stored without padding (a direct transfer writes 1 KiB of consecutive LDS); piece p of row r sits in
@@ -564,15 +564,17 @@ template <int D>
 __device__ __forceinline__ void sweep_redo(const SweepParams& prm, uint32_t lds0) {
   using C = Cfg<D>;
   constexpr int S = C::kSteps;
-  const int lane = threadIdx.x & 63, r = lane & 31, g = lane >> 5;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid), "+s"(lds0));  // (what is formed from them would be kept in registers for the whole of the walk)
+  const int lane = tid & 63, r = lane & 31, g = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int spans = prm.spans, tasks = prm.B * prm.heads() * prm.nqg * spans, tasks2 = prm.B * prm.heads() * prm.spans2;  // of the two passes
   const uint32_t word = lds0 + C::kOffMass;                   // one int: the ticket, or whether to go on
   const uint32_t colsum = lds0 + C::kOffCs;                   // [2][kWaves][kKeys] floats
   for (;;) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (transfers of the last task that nothing has waited for)
     __syncthreads();
-    if (threadIdx.x == 0) *in_lds<int>(word) = __hip_atomic_fetch_add(&prm.ctl->ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (tid == 0) *in_lds<int>(word) = __hip_atomic_fetch_add(&prm.ctl->ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
     const int ticket = __builtin_amdgcn_readfirstlane(*in_lds<int>(word));
     if (ticket >= tasks + tasks2) return;
@@ -595,7 +597,7 @@ __device__ __forceinline__ void sweep_redo(const SweepParams& prm, uint32_t lds0
       float m = kNegBig, l = 0.f;
       float nl[16];  // second pass: minus the base-2 log-sum-exp of this lane's rows
       if (second) {
-        if (threadIdx.x == 0) {
+        if (tid == 0) {
           const uint64_t t0 = wall_clock64();
           while (__hip_atomic_load(&prm.spans_done[unit], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < spans && wall_clock64() - t0 < kTaskWait)
             __builtin_amdgcn_s_sleep(8);
@@ -628,7 +630,7 @@ __device__ __forceinline__ void sweep_redo(const SweepParams& prm, uint32_t lds0
           for (int o = 32; o > 0; o >>= 1) mass += __shfl_xor(mass, o, 64);
           if (lane == 0) *in_lds<float>(colsum + wave * 4) = mass;
           __syncthreads();
-          if (threadIdx.x == 0) {
+          if (tid == 0) {
             float t = 0.f;
             for (int w = 0; w < kWaves; ++w) t += *in_lds<float>(colsum + w * 4);
             head_mass += t;
@@ -651,15 +653,15 @@ __device__ __forceinline__ void sweep_redo(const SweepParams& prm, uint32_t lds0
         }
       };
       auto flush = [&](int n) {  // column sums of chunk n of the span
-        const int j = (c0 + n) * kKeys + (int)threadIdx.x;
-        if ((int)threadIdx.x >= kKeys || j >= P) return;
-        const uint32_t cs = colsum + (n & 1) * kWaves * kKeys * 4 + threadIdx.x * 4;
+        const int j = (c0 + n) * kKeys + (int)tid;
+        if ((int)tid >= kKeys || j >= P) return;
+        const uint32_t cs = colsum + (n & 1) * kWaves * kKeys * 4 + tid * 4;
         float v = 0.f;
 #pragma unroll
         for (int w = 0; w < kWaves; ++w) v += *in_lds<const float>(cs, w * kKeys * 4);
         // Whole sums only are stored: a workgroup that is still in its walk stores the same ones at any time, which would otherwise count
         // the groups before twice.
-        const uint32_t kept = lds0 + C::kOffStart + (n * kKeys + threadIdx.x) * 4;
+        const uint32_t kept = lds0 + C::kOffStart + (n * kKeys + tid) * 4;
         if (unit > first) v += *in_lds<const float>(kept);
         if (unit < first + prm.nqg - 1)
           *in_lds<float>(kept) = v;
@@ -744,7 +746,7 @@ __device__ __forceinline__ void sweep_redo(const SweepParams& prm, uint32_t lds0
         // write back the whole L2, an acquire above throw it away.)
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
-        if (threadIdx.x == 0) __hip_atomic_fetch_add(&prm.spans_done[unit], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (tid == 0) __hip_atomic_fetch_add(&prm.spans_done[unit], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
     }
   }
@@ -764,17 +766,29 @@ struct Task {
 // the chunk whose workgroup writes the head's mass (not always the first, so that they are spread over workgroups)
 __device__ __forceinline__ int lead_of(int bh, int nc) { return (bh & 15) < nc ? bh & 15 : 0; }
 
-// After the walk: the masses of the units whose leading chunk was this workgroup's and that have waves with mostly small row sums,
-// added to those of their heads.
+// the row (of a wave's 32) whose sum the butterfly of `publish` leaves in a lane; lanes 2n and 2n+1 hold the same one
+__device__ __forceinline__ int row_of(int ln) {
+  return 8 * (((ln >> 4) & 1) * 2 + ((ln >> 3) & 1)) + 4 * (ln >> 5) + (((ln >> 2) & 1) * 2 + ((ln >> 1) & 1));
+}
+
+// After the walk: the masses of the heads whose leading chunk was this workgroup's and that have waves with mostly small row sums.  A head's
+// mass is stored once and as a whole: the fallback of another workgroup may have stored it by now, and a part would take its place, or be
+// added to it.
 template <int D>
-__device__ __forceinline__ void late_masses(const SweepParams& prm, uint32_t lds0, int head) {
+__device__ __forceinline__ void late_masses(const SweepParams& prm, uint32_t lds0, int next) {
   using C = Cfg<D>;
-  const int lane = threadIdx.x & 63;
+  int lane = threadIdx.x & 63;
+  asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" : "+v"(lane) : : "memory");  // (this workgroup's own parts and its list are there)
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");  // (this workgroup's own parts and its list are there)
-  while (head) {
-    const int unit = head - 1;
-    head = __builtin_amdgcn_readfirstlane(__hip_atomic_load(&prm.late[unit], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+  int unit = 0, units = 0;  // of the present head: the next one, and how many are left
+  float mass = 0.f;
+  while (next || units) {
+    if (units == 0) {
+      unit = (next - 1) * prm.nqg;
+      units = prm.nqg;
+      mass = 0.f;
+      next = __builtin_amdgcn_readfirstlane(__hip_atomic_load(&prm.late[next - 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    }
     const int bh = unit / prm.nqg;
     const int nc = ceil_div(prm.lens.P[bh / prm.heads()], kKeys);
     const int lead = lead_of(bh, nc);
@@ -789,7 +803,7 @@ __device__ __forceinline__ void late_masses(const SweepParams& prm, uint32_t lds
         if (j * 64 + lane < nc) u[j] = __hip_atomic_load(part + j * 64 + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
       if (__all(__hip_atomic_load(part + lead, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == kNoPart)) {  // not one of those waves
-        const uint64_t* low = reinterpret_cast<const uint64_t*>(prm.units + (int64_t)unit * kUnitBytes<D>) + wave * 32 + lane / 2;
+        const uint64_t* low = reinterpret_cast<const uint64_t*>(prm.units + (int64_t)unit * kUnitBytes<D>) + wave * 32 + row_of(lane);
         uint64_t lo = 0;
 #pragma unroll
         for (int j = 0; j < kCopies; ++j)
@@ -817,12 +831,11 @@ __device__ __forceinline__ void late_masses(const SweepParams& prm, uint32_t lds
     sum = wave_sum(sum);
     if (lane == 0) *in_lds<float>(lds0 + C::kOffMass + wave * 4) = sum;
     __syncthreads();
-    if (threadIdx.x == 0 && !*in_lds<const int>(lds0 + C::kOffBad)) {
-      float m = sum_of_waves<kWaves>(lds0 + C::kOffMass);
-      // (the head's other masses are there: this thread has written them or, with HALVES, wave 4, before the wait and the barrier above)
-      m += __hip_atomic_load(&prm.mass[bh], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __hip_atomic_store(&prm.mass[bh], m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    ++unit;
+    --units;
+    if (threadIdx.x == 0) {
+      mass += sum_of_waves<kWaves>(lds0 + C::kOffMass);
+      if (units == 0 && !*in_lds<const int>(lds0 + C::kOffBad)) __hip_atomic_store(&prm.mass[bh], mass, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __syncthreads();
   }
@@ -891,10 +904,6 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
     asm volatile("global_load_dwordx4 %0, %1, %2 offset:%3" : "=v"(qf[ks]) : "v"(q_at), "s"(units), "i"(ks % 4 * 1024));
   };
 
-  // the row (of this wave's 32) whose sum the butterfly below leaves in a lane; lanes 2n and 2n+1 hold the same one
-  auto row_of = [](int ln) {
-    return 8 * (((ln >> 4) & 1) * 2 + ((ln >> 3) & 1)) + 4 * (ln >> 5) + (((ln >> 2) & 1) * 2 + ((ln >> 1) & 1));
-  };
   const uint32_t row8 = (rb * 32 + row_of(lane)) * 8;
   const int copy = team % kCopies;
   bool patient = true;
@@ -988,18 +997,16 @@ __device__ __forceinline__ void sweep_chunks(const SweepParams& prm, uint32_t ld
     if (rb == 0 && good && k.ci() == lead_of(k.bh, k.nc()) && prm.mass) {
       const uint32_t ms = lds0 + C::kOffMass + (par * kWaves + wave) * 4;
       const uint32_t late = lds0 + C::kOffLate + (HALVES && second ? 4 : 0);
-      const float m = sum_of_waves<kTeam>(ms);
-      if (m < 0.f) {  // (not known yet)
-        if (ln == 0) {
-          const int unit = k.unit(prm);
-          __hip_atomic_store(at<int>(base_of(prm.late + unit), here(0)), *in_lds<const int>(late), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          *in_lds<int>(late) = unit + 1;
-        }
-      } else {
-        mass += m;
-      }
+      mass += sum_of_waves<kTeam>(ms);  // (below 0 from a mark on)
       if (whole) {
-        if (ln == 0) __hip_atomic_store(&prm.mass[k.bh], mass, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (__builtin_amdgcn_readfirstlane((int)as_u32(mass)) < 0) {  // (not known yet)
+          if (ln == 0) {
+            __hip_atomic_store(at<int>(base_of(prm.late + k.bh), here(0)), *in_lds<const int>(late), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            *in_lds<int>(late) = k.bh + 1;
+          }
+        } else if (ln == 0) {
+          __hip_atomic_store(&prm.mass[k.bh], mass, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
         mass = 0.f;
       }
     }

@@ -190,23 +190,23 @@ def test_fallback_at_edges_of_chunks_spans_and_row_groups(d, n_m, H, Ps):
     assert torch.allclose(mass, want_mass, rtol=32 * 2.0 ** -24, atol=0)
 
 
-def beside_a_copy(batch, which, value, run, calls=20):
-    """What calls leave, while copies on another stream keep writing `value` over the scores (which = 0) or masses (1) that they write.
-    run: whether they have the device's sweep, or find it taken."""
+def beside_a_copy(batch, which, value, run, calls=20, after=lambda i: 60):
+    """What calls leave, while copies on another stream keep writing `value` over the scores (which = 0) or masses (1) that they write,
+    after(i) of them after the i-th call.  run: whether they have the device's sweep, or find it taken."""
     from paper_2510_09309_amd import bench_binding as bb
     m = hp.mk()
     ws = hp.workspace(m.maskkv_score_workspace_bytes(batch.desc))
     outs = [(torch.full((batch.B * batch.H, batch.P_max), float("nan"), device="cuda"), torch.zeros(batch.B * batch.H, device="cuda")) for _ in range(calls)]
     other = torch.cuda.Stream()
     torch.cuda.synchronize()
-    for out in outs:
+    for i, out in enumerate(outs):
         if not run:
             bb.maskkv_bench_hold_sweep(0)
         with torch.cuda.stream(other):
             for _ in range(10):
                 out[which].copy_(value)
             m.maskkv_score(batch.desc, batch.Q, batch.K, 0.0, out[0], batch.P_max, out[1], ws, torch.cuda.default_stream())
-            for _ in range(60):
+            for _ in range(after(i)):
                 out[which].copy_(value)
         torch.cuda.synchronize()
         assert int(ws[:4].view(torch.int32)[0]) == run
@@ -229,6 +229,21 @@ def test_fallback_beside_a_workgroup_that_still_stores_its_sums(d, n_m, H, Ps):
         # two ways to form the same fp32 sums: logits of up to 2^5 binary orders
         assert torch.allclose(scores, want, rtol=32 * 2.0 ** -24, atol=0, equal_nan=True)
         assert torch.allclose(mass, want_mass, rtol=32 * 2.0 ** -24, atol=0)
+
+
+@pytest.mark.parametrize("d,n_m,H,Ps", [(128, 512, 24, (7600,)), (128, 300, 9, (3000, 4100)), (64, 100, 32, (7000, 8000))])
+def test_masses_of_the_column_sums_beside_another_workgroups_fallback(d, n_m, H, Ps):
+    """Masses that come from the column sums, after the walk, are not added to what is in their place by then: the fallback of another
+    workgroup may have stored the whole mass there.  (Its part is played by a copy of the right masses.)"""
+    from paper_2510_09309_amd import bench_binding as bb
+    batch = hp.Batch([span_shift(64 + i, d, P, n_m, 4.0, H) for i, P in enumerate(Ps)])
+    plan = bb.maskkv_bench_score_plan(batch.desc)
+    assert plan.groups > 0
+    want, want_mass, run = swept(batch, hp.workspace(hp.mk().maskkv_score_workspace_bytes(batch.desc)))
+    assert run == 1 and 0.0 < float(want_mass.min()) and float(want_mass.max()) < 0.5 * n_m
+    for i, (scores, mass) in enumerate(beside_a_copy(batch, 1, want_mass, 1, after=lambda i: 2 * i)):
+        assert torch.equal(mass, want_mass), i
+        assert torch.equal(torch.nan_to_num(scores), torch.nan_to_num(want)), i
 
 
 def test_sweeps_on_two_streams_line_up():
