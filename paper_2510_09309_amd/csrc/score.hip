@@ -682,6 +682,7 @@ int launch_score(const maskkv_desc* d, const View& Q, const View& K, const Lens&
   prm.score_stride = score_stride;
   prm.prompt_mass = prompt_mass;
   prm.unit_mass = nullptr;
+  prm.mass_head = 0;
   prm.mass_step = 1;
   if (sweep) {
     if (int e = mark(events, 0, stream)) return e;
