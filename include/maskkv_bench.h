@@ -75,9 +75,17 @@ int maskkv_bench_hold_sweep(int64_t age_us, void* stream);
  *   [0] workgroups of the single sweep, or 0 where there is none; [1] how many of these are launched: fewer where halves of
  *   workgroups have chunks of their own; [2] sets of workgroups that a head's groups of 256 voting rows are dealt to; [3] rounds of heads;
  *   [4] workgroups per head of the one-pass kernel of short fp32 prompts, or 0.  With [0] and [4] zero it takes two passes.
+ * (Where maskkv_bench_score_split has parts, these are taken instead of [4] or of the two passes.)
  * Enqueues nothing.  Errors are reported through maskkv_last_error() of libmaskkv.so.
  */
 int maskkv_bench_score_plan(const maskkv_desc* desc, int32_t* plan);
+
+/*
+ * Whether maskkv_score would deal out both rows and keys of a short fp32 prompt, in two kernels.  split: HOST array of 3:
+ *   [0] groups of 16 rows a workgroup of the first (1 or 2); [1] keys a workgroup of it; [2] how many parts of so many keys, or 0: it would not.
+ * Enqueues nothing.  Errors are reported through maskkv_last_error() of libmaskkv.so.
+ */
+int maskkv_bench_score_split(const maskkv_desc* desc, int32_t* split);
 
 #ifdef __cplusplus
 }

@@ -13,7 +13,7 @@ from . import binding as _b
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.environ.get("MASKKV_BENCH_LIB_PATH", os.path.join(_HERE, "libmaskkv_bench.so"))
 SYMBOLS = ["maskkv_bench_last_error", "maskkv_bench_probe", "maskkv_bench_score_marked", "maskkv_bench_hold_sweep",
-           "maskkv_bench_score_plan"]
+           "maskkv_bench_score_plan", "maskkv_bench_score_split"]
 
 
 def _load() -> ct.CDLL:
@@ -75,6 +75,19 @@ def maskkv_bench_score_plan(desc: "_b.Desc") -> ScorePlan:
     plan = (ct.c_int32 * 5)()
     _b._check(_lib.maskkv_bench_score_plan(ct.byref(desc.c()), plan), "maskkv_bench_score_plan")
     return ScorePlan(*plan)
+
+
+class ScoreSplit(NamedTuple):
+    """How maskkv_score would deal out the rows and keys of a short fp32 prompt; no parts: it would not (see maskkv_bench.h)."""
+    groups: int
+    part_keys: int
+    parts: int
+
+
+def maskkv_bench_score_split(desc: "_b.Desc") -> ScoreSplit:
+    split = (ct.c_int32 * 3)()
+    _b._check(_lib.maskkv_bench_score_split(ct.byref(desc.c()), split), "maskkv_bench_score_split")
+    return ScoreSplit(*split)
 
 
 def raw_library() -> ct.CDLL:

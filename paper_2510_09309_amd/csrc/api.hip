@@ -181,10 +181,11 @@ int score_entry(const maskkv_desc* desc, const maskkv_tensor* Q_mask, const mask
                       reinterpret_cast<hipStream_t>(stream), events, plan);
 }
 
-int score_plan(const maskkv_desc* desc, SweepPlan* plan) {
+int score_plan(const maskkv_desc* desc, SweepPlan* plan, RowsSplit* split) {
   Lens lens;
   if (int e = check_desc(desc, &lens)) return e;
   *plan = score_sweep_plan(desc, lens);
+  *split = score_split(desc, lens, *plan);
   return MASKKV_OK;
 }
 

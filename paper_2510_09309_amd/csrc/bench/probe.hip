@@ -4,7 +4,8 @@
 //   maskkv_bench_score_marked  maskkv_score with HIP events recorded at its stage boundaries (it calls the body
 //                              of maskkv_score inside libmaskkv.so);
 //   maskkv_bench_hold_sweep    makes maskkv_score take its fallback.
-//   maskkv_bench_score_plan    how maskkv_score would score a description.
+//   maskkv_bench_score_plan    how maskkv_score would score a description;
+//   maskkv_bench_score_split   whether it would deal out rows and keys of a short fp32 prompt.
 #include <stdio.h>
 
 #include "../kernels.hpp"
@@ -348,9 +349,20 @@ int maskkv_bench_hold_sweep(int64_t age_us, void* stream) { return hold_sweep(ag
 
 int maskkv_bench_score_plan(const maskkv_desc* desc, int32_t* plan) {
   SweepPlan p;
-  if (int e = score_plan(desc, &p)) return e;
+  RowsSplit split;
+  if (int e = score_plan(desc, &p, &split)) return e;
   const int32_t v[5] = {p.groups, p.grid, p.subsets, p.rounds, p.parts};
   for (int i = 0; i < 5; ++i) plan[i] = v[i];
+  return MASKKV_OK;
+}
+
+int maskkv_bench_score_split(const maskkv_desc* desc, int32_t* split) {
+  SweepPlan p;
+  RowsSplit s;
+  if (int e = score_plan(desc, &p, &s)) return e;
+  split[0] = s.groups;
+  split[1] = s.part_keys;
+  split[2] = s.parts;
   return MASKKV_OK;
 }
 

@@ -55,12 +55,13 @@ struct RowsParams {
   float4* stats;    // [B*H][n_query][parts]
 };
 struct RowsSplit {
-  int groups, tiles;     // groups of 16 rows a wave of the first kernel, tiles of 16 keys a workgroup of the second
+  int groups;            // groups of 16 rows a workgroup of the first kernel: 1 (and 32 keys a workgroup of the second) or 2 (64)
   int part_keys, parts;  // keys a workgroup of the first, and how many of them, or 0
 };
 // Whether rows and keys are both dealt out, and how.
 RowsSplit score_rows_split(const maskkv_desc* d, const Lens& lens);
 size_t score_rows_split_bytes(const maskkv_desc* d, const RowsSplit& split);
+RowsSplit score_split(const maskkv_desc* d, const Lens& lens, const SweepPlan& plan);  // (as far as the workspace has room for it)
 int score_rows_parts(const maskkv_desc* d, const Lens& lens);
 int launch_score_rows(const RowsParams& prm, int d, int parts, const RowsSplit& split, hipStream_t stream);
 
@@ -105,7 +106,7 @@ int launch_value_shift(const void* v_now, const void* v_prev, int64_t n, int wid
 int score_entry(const maskkv_desc* desc, const maskkv_tensor* Q_mask, const maskkv_tensor* K_full, float scale,
                 float* scores, int64_t score_stride, float* prompt_mass, void* workspace, size_t workspace_bytes,
                 void* stream, void* const* events);
-// The plan that it makes for a description.
-int score_plan(const maskkv_desc* desc, SweepPlan* plan);
+// The plan that it makes for a description, and whether it deals out rows and keys instead.
+int score_plan(const maskkv_desc* desc, SweepPlan* plan, RowsSplit* split);
 
 }  // namespace maskkv

@@ -189,8 +189,9 @@ __global__ __launch_bounds__(kThreads, 2) void score_rows_kernel(const RowsParam
 
 // ---- few workgroups' worth of rows: the keys are dealt out as well, and the logits formed twice.
 //
-// A workgroup of rows_stats_kernel has 16 rows and 64 * NT keys of a head and leaves each row's maximum and its sums over prompt and
-// response keys; one of rows_columns_kernel has 16 * NT keys, takes the rows' normalisers from all of these and adds its columns over all rows.
+// A workgroup of rows_stats_kernel has 16 * RG rows and prm.part_keys keys of a head (each of its waves every fourth 16 of them) and leaves each
+// row's maximum and its sums over prompt and response keys; one of rows_columns_kernel has 16 * NT keys, takes the rows' normalisers from
+// all of these and adds its columns over all rows.
 
 template <int D, int RG>
 __global__ __launch_bounds__(64 * kStatWaves) void rows_stats_kernel(const RowsParams prm) {
@@ -459,7 +460,7 @@ RowsSplit score_rows_split(const maskkv_desc* d, const Lens& lens) {
   const double many = (wide ? 17.5 : 13.3) + (wide ? 0.0024 : 0.0012) * (double)products + (rounds > 1 ? 5.0 * (ceil(rounds) - rounds) : 0.0);
   const double groups_sum = rows > 256 ? 5.0 : 0.0;  // the two passes' last kernel
   if (fmin(few, many) > 0.9 * fmin(one_pass_us(d, lens), two_passes_us(d, lens) + groups_sum)) return RowsSplit{};
-  RowsSplit s = few < many ? RowsSplit{1, 2, most + d->n_resp > 1024 ? 128 : 64, 0} : RowsSplit{2, 4, 256, 0};
+  RowsSplit s = few < many ? RowsSplit{1, most + d->n_resp > 1024 ? 128 : 64, 0} : RowsSplit{2, 256, 0};
   s.parts = (most + d->n_resp + s.part_keys - 1) / s.part_keys;
   return s;
 }

@@ -649,6 +649,8 @@ SweepPlan score_sweep_plan(const maskkv_desc* d, const Lens& lens) {
   return plan;
 }
 
+RowsSplit score_split(const maskkv_desc* d, const Lens& lens, const SweepPlan& plan) { return ScoreArea(d, lens, plan).split; }
+
 size_t score_workspace_bytes(const maskkv_desc* d, const Lens& lens, const SweepPlan& plan) {
   return ScoreArea(d, lens, plan).bytes;
 }

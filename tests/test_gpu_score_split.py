@@ -15,17 +15,27 @@ pytestmark = pytest.mark.gpu
 RTOL = 2.0 ** -19
 
 
-@pytest.mark.parametrize("d,n,H,g,Ps", [
-    (64, 16, 4, 1, (47, 48, 49, 0)), (128, 17, 3, 1, (111, 112, 175)), (64, 64, 4, 1, (512,)), (128, 36, 4, 1, (544,)),      # parts of 64
-    (64, 33, 2, 1, (991,)), (64, 33, 2, 1, (992,)), (128, 32, 4, 1, (2500, 100)), (128, 31, 1, 4, (3041,)), (64, 130, 2, 1, (1150,)),  # of 128
-    (64, 100, 8, 1, (1180,)), (64, 128, 4, 1, (2500,)), (64, 40, 4, 7, (2499,)), (64, 47, 16, 1, (1233, 0))])                # of 256
-def test_against_float64(d, n, H, g, Ps):
+@pytest.mark.parametrize("d,n,H,g,Ps,split", [
+    # parts of 64 keys, one group of rows a workgroup
+    (64, 17, 3, 1, (366, 367, 368, 0), (1, 64, 7)), (128, 17, 3, 1, (111, 112, 175), (1, 64, 3)), (64, 64, 4, 1, (512,), (1, 64, 9)),
+    (128, 36, 4, 1, (544,), (1, 64, 10)), (64, 33, 2, 1, (991,), (1, 64, 16)),
+    # of 128
+    (64, 33, 2, 1, (992,), (1, 128, 9)), (128, 32, 4, 1, (2500, 100), (1, 128, 20)), (128, 31, 1, 4, (3041,), (1, 128, 24)),
+    (64, 130, 2, 1, (1150,), (1, 128, 10)), (64, 47, 16, 1, (1233, 0), (1, 128, 10)), (128, 64, 8, 1, (1984, 0), (1, 128, 16)),
+    # of 256, two groups of rows: whole parts and a key more, an odd group, grouped queries, short and empty prompts beside the long one
+    (64, 100, 8, 1, (1180,), (2, 256, 5)), (64, 128, 4, 1, (2500,), (2, 256, 11)), (64, 40, 4, 7, (2499,), (2, 256, 10)),
+    (64, 130, 4, 1, (1918, 0), (2, 256, 8)), (64, 130, 4, 1, (1917, 200), (2, 256, 8)), (64, 64, 8, 1, (1985, 0), (2, 256, 9)),
+    (128, 128, 4, 1, (2500,), (2, 256, 11)), (128, 64, 8, 1, (2000,), (2, 256, 9)), (128, 130, 4, 1, (1918, 0), (2, 256, 8)),
+    (128, 130, 4, 1, (1919, 0), (2, 256, 9)), (128, 130, 6, 1, (1917, 3, 0), (2, 256, 8)), (128, 77, 3, 4, (1740, 0, 300), (2, 256, 8))])
+def test_against_float64(d, n, H, g, Ps, split):
     m = hp.mk()
     gen = torch.Generator(device="cuda").manual_seed(d + n + H)
     B, P_max = len(Ps), max(Ps)
     Q = torch.randn((B, H * g, n, d), generator=gen, device="cuda")
     K = torch.randn((B, P_max + n, H, d), generator=gen, device="cuda").transpose(1, 2)   # (rows of a head are H * d apart)
     desc = m.Desc(B=B, H=H, d=d, dtype=m.MASKKV_F32, n_resp=n, P_max=P_max, prompt_len=None if B == 1 else list(Ps), q_per_kv=0 if g == 1 else g)
+    from paper_2510_09309_amd import bench_binding as bb
+    assert bb.maskkv_bench_score_split(desc) == split      # (a change of the cost model could take a case past what it is here for)
     scores, mass = torch.full((B * H, P_max + 3), float("nan"), device="cuda"), torch.full((B * H,), float("nan"), device="cuda")
     ws = hp.workspace(m.maskkv_score_workspace_bytes(desc))
     m.maskkv_score(desc, Q, K, 0.0, scores, P_max + 3, mass, ws)
@@ -50,6 +60,8 @@ def test_logits_far_apart():
     K[:, :, 64:128] *= 40
     K[:, 0, 333] = 0
     desc = m.Desc(B=1, H=H, d=d, dtype=m.MASKKV_F32, n_resp=n, P_max=P)
+    from paper_2510_09309_amd import bench_binding as bb
+    assert bb.maskkv_bench_score_split(desc).parts > 0
     scores, mass = torch.empty((H, P), device="cuda"), torch.empty((H,), device="cuda")
     m.maskkv_score(desc, Q, K, 0.0, scores, P, mass, hp.workspace(m.maskkv_score_workspace_bytes(desc)))
     s = Q[0].double() @ K[0].double().transpose(1, 2).contiguous() / d ** 0.5
