@@ -8,8 +8,9 @@ from tests import helpers as hp
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("d,H,n,P", [(128, 32, 200, 16185), (128, 32, 200, 16184), (64, 32, 100, 32700), (128, 40, 257, 13000)])
-def test_either_side_of_the_cache(d, H, n, P):  # (the third: 128 queries a workgroup; the last: two tiles of queries)
+@pytest.mark.parametrize("d,H,n,P", [(128, 32, 200, 16185), (128, 32, 200, 16184), (64, 32, 100, 32700), (128, 40, 257, 13000),
+                                       (128, 32, 100, 16300), (64, 32, 200, 32700)])
+def test_either_side_of_the_cache(d, H, n, P):  # (100 queries: 128 a workgroup, otherwise 256; 257: two tiles of queries, which is not streamed)
     m = hp.mk()
     gen = torch.Generator(device="cuda").manual_seed(P)
     Q, K, V = (torch.randn((1, H, x, d), generator=gen, device="cuda").to(torch.bfloat16) for x in (n, P + n, P + n))
