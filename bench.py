@@ -39,7 +39,7 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0   # MI355X dense bf16
 HBM_PEAK_GBS = 8000.0
 # HBM bytes read + written by the two kernels of the scoring sweep at the 32k prompt: rocprofv3 --pmc FETCH_SIZE and WRITE_SIZE,
 # each scaled by what it reads for a copy of known size (profiles/c4_hbm_traffic.md).  Other workloads: null.
-SCORE_SWEEP_TRAFFIC_BYTES = {"C4": (141255.7 + 5189.2) * 1024 * 2.0 + (20489.0 + 2947.4) * 1024}
+SCORE_SWEEP_TRAFFIC_BYTES = {"C4": (141225.4 + 5191.7) * 1024 * 2.0 + (20489.0 + 2946.8) * 1024}
 
 
 def workload(name: str) -> dict:

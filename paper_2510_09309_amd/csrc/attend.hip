@@ -1109,7 +1109,10 @@ bool attend_is_ordered(const maskkv_desc* d, bool full, int64_t capacity) {
 // than that cache: V would push out K, which the scoring that follows reads again.  (us for this call and scoring with its normalisers, 32 heads x
 // 256 queries, head_dim 128, with it and without, in a loop over the same tensors; over four sets of them in turn: 9k keys 86.3 / 84.6;
 // 90.9 / 91.4, 13k 106.4 / 105.3; 113.6 / 114.1, 16k 123.3 / 125.3; 133.5 / 134.7, 20k 144.6 / 150.5; 155.0 / 155.5, 26k 180 / 191; 190.5 / 194.9,
-// 33k 226 / 240; 235.9 / 240.3, 48k 328 / 335; 335 / 338.  K as well: 242 / 244 at 33k keys.  Scoring from the last key to the first: the same.)
+// 33k 226 / 240; 235.9 / 240.3, 48k 328 / 335; 335 / 338.  K as well: 242 / 244 at 33k keys.  Scoring from the last key to the first: the same.
+// This call alone: 17k 79 / 84; 85 / 85, 20k 90 / 96; 97 / 97, 26k 112 / 121; 121 / 122, 33k 147 / 149; 148 / 149; with 128 queries 17k 54.5 / 56;
+// 63 / 65, 26k 77 / 90; 86 / 90; head_dim 64, 34k 97 / 102; 101 / 101, 40k 112 / 118; 118 / 118, with 128 queries 68 / 73; 73 / 74; 4 sequences of
+// 5k 95 / 102; 102 / 103.)
 bool attend_is_streamed(const maskkv_desc* d, const Lens& lens, bool full) {
   if (!full || d->n_resp * query_heads_per_kv(d) > tiled_queries(d, true)) return false;
   int64_t keys = 0;

@@ -16,8 +16,9 @@
 // Where 256 queries a workgroup leave compute units idle (HALVES), a workgroup serves 128: both groups have the same queries, group
 // i takes tiles 2u + i through rings of two slots of its own, and the two partial results are merged through LDS, half by each group.
 //
-// What bounds it: power, in a loop of nothing but these calls, and before that the vector phase.  A tile of 256 queries takes 3150 cycles
-// (2048 of them MFMAs: a matrix phase is 1370 cycles, a vector phase 340 for the transfers and 1100 to 1250 for the softmax), 3850 with
+// What bounds it: power, in a loop of nothing but these calls, and before that the vector phase.  A tile of 256 queries takes 2880 cycles
+// in the un-evicted call and 3200 in the short walks of a ragged batch (2048 of them MFMAs: a matrix phase is 1210 to 1250 cycles, a vector
+// phase 230 to 410 for the transfers and 1140 to 1220 for the softmax, the rest waits); an earlier copy with counters gave 3150, and 3850 with
 // the transfers' bases, strides and cases formed anew for each tile (690 cycles) and a barrier after every phase (the matrix phase's
 // group waited 750 cycles for the other at each).  That is 18 % fewer cycles, of which the clock takes back three quarters: 33024 keys x 32 heads x
 // 256 queries (head_dim 128), un-evicted call with its merge, 164 -> 157 us; eight sequences x 32 heads x 512 queries over 576 ... 1536
@@ -51,7 +52,7 @@ struct TileCfg {
   static constexpr int kMoves = kMoveRows / kRPI;   // transfers per wave and tile of K (and of V)
   static constexpr int kTileB = kTK * kRowB;
   static constexpr int kOffQ = 6 * kTileB;          // at first the queries, from the third V tile on (256 of them)
-  static constexpr int kLds = (HALVES ? 8 : 10) * kTileB;  // four K tiles, then four V tiles
+  static constexpr int kLds = (HALVES ? 8 : 10) * kTileB;  // four K tiles, four V tiles and, with 256 queries, room for the last of these
   static constexpr int kQK = 2 * kSteps;            // MFMAs of a tile's logits
   static constexpr int kPV = 4 * kDB;               // MFMAs of a tile's output update
   // A direct transfer writes 1 KiB of consecutive LDS, so rows carry no padding; instead a row's pieces are permuted.

@@ -43,9 +43,11 @@ struct View {
 
 // A kernel's arguments are written for each launch, so no cache holds them, and every 64-byte line of them that is first read behind a
 // wait costs a latency of its own (0.2 to 0.3 us; two to five in turn before the first load of a kernel's inputs).  This asks for a word
-// of each line at once (`at`: offsets within the kernel's only parameter); what is read later comes from the scalar cache.  us a
+// of each line that a kernel of few sequences reads at once (`at`: offsets within the kernel's only parameter); what is read later comes
+// from the scalar cache.  Of a view these are two lines of nine: its strides, and the offsets of its first ten sequences or so.  us a
 // layer: 4k keys 42.9 -> 42.3, 3k and 5k at head_dim 64 37.8 -> 37.1, 30k with 7 query heads a head 108.8 -> 107.9; eviction of 8
-// sequences of 32 heads 32.1 -> 31.6.  (Not in the sweep kernel, whose arguments are in its caches when most of its loads are issued:
+// sequences of 32 heads 32.1 -> 31.6.  (Not in the tiled fp32 attention, the order and gather of many heads, the head budgets and the kernels of
+// layer.hip, where it was not measured, and not in the sweep kernel, whose arguments are in its caches when most of its loads are issued:
 // 8 x 32 heads with 512 rows 488 us without, 491 with.)
 template <int N>
 __device__ __forceinline__ void fetch_arguments(const uint32_t (&at)[N]) {

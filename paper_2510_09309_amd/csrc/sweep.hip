@@ -23,7 +23,7 @@
 // waits for a sum that is not needed yet, and every wait is bounded: if the workgroups turn out not to be all resident, or a
 // row's sum leaves the range of the integers, a two-pass fallback at the end of the same kernel does the work.
 //
-// What bounds it: a step of 5900 to 7100 cycles, 2048 of them MFMAs.  A wave issues an instruction every 4 to 5 cycles, a matrix phase
+// What bounds it: a step of 5800 to 7100 cycles, 2048 of them MFMAs.  A wave issues an instruction every 4 to 5 cycles, a matrix phase
 // has 1800 cycles of them, a vector phase 1300 to 1800, and the two waves of a SIMD share the vector pipe, where v_exp_f32
 // takes 8 cycles and an MFMA about as many.  In a loop of nothing but long calls the board is at its 1400 W and the clock 10 % below that
 // of short calls (2.1 against 2.3 GHz); as part of a layer the sweep is below that.  us a call, with both groups of waves in the same
@@ -269,9 +269,6 @@ __device__ __forceinline__ float sum_of_waves(uint32_t lds) {
   return v[0];
 }
 
-// ---- response span: row references, zeroed sums, and the voting rows in the order in which the sweep reads them.
-// A workgroup serves BLOCKS blocks of 32 rows of a unit; 8 / BLOCKS waves share a block's keys, which come through LDS 128
-// at a time.  (Eight blocks where there are units enough to fill the chip: each key is then read once per unit.)
 // The plan's runs in the lanes of a wave: what a loop over them reads is then a register of the wave's instead of a scalar load that it
 // waits for (all of them once; a round of the loop costs the waits 0.3 us).
 struct Runs {
@@ -385,7 +382,9 @@ __device__ __forceinline__ void start_table(const SweepParams& prm, int b, int v
   }
 }
 
-// BLOCKS blocks of 32 rows a workgroup, and each block's response keys on 8 / BLOCKS waves: 2 where that gives every compute unit work.
+// ---- response span: row references, zeroed sums, and the voting rows in the order in which the sweep reads them.
+// A workgroup serves BLOCKS blocks of 32 rows of a unit; 8 / BLOCKS waves share a block's keys, which come through LDS 128
+// at a time.  Eight blocks where there are units enough to fill the chip (each key is then read once per unit), otherwise two.
 //
 // What bounds it: with few units the latency of its loads (issued at once: rows and two tiles of keys; 5.9 to 6.7 us with the rest of the
 // chain: launch, loads, logarithms, stores), with many the memory (96 MB in the ragged batch of perf/cases.py, 20 of 35 us) and
